@@ -57,3 +57,25 @@ def test_empty_and_bad_arguments():
     z = torch.zeros((2, 12), dtype=torch.bfloat16, device="cuda")     # vocabulary not a multiple of 8
     with pytest.raises(ca.ChunkAttnError):
         fused_ce_inplace(z, torch.zeros((2,), dtype=torch.int32, device="cuda"), torch.zeros((2,), device="cuda"))
+
+
+@pytest.mark.parametrize("vocab", [32768, 32776, 65536, 65544, 131072, 131080, 135168, 163840, 163848, 188416, 188424, 192512, 262136])
+def test_edges_of_the_register_and_lds_variants(vocab):
+    """Vocabularies at which the rows' last chunks change place (registers of one variant or the next, LDS, a thread's
+    last chunk partly or wholly absent); masked entries (-inf) and, in one row, whole threads of them.  Same tolerances."""
+    from paper_2509_21275_amd.fused_ce import fused_ce_inplace
+    g = torch.Generator(device="cpu").manual_seed(vocab)
+    rows, scale = 4, 0.25
+    buf = (torch.randn((rows, vocab), generator=g) * 2.0).to(torch.bfloat16)
+    targets = torch.tensor([0, vocab - 1, vocab // 2, 5], dtype=torch.int32)
+    buf[1, : vocab // 3] = float("-inf")
+    buf[2, vocab // 2 + 8:] = float("-inf")
+    buf[3, :] = float("-inf")
+    buf[3, 5] = 1.5                                 # one finite logit: loss 0, gradient 0
+    want_loss, want_grad = orc.cross_entropy(buf.double().numpy(), targets.numpy(), scale)
+    dev, loss = buf.cuda(), torch.full((rows,), float("nan"), device="cuda")
+    fused_ce_inplace(dev, targets.cuda(), loss, scale)
+    torch.cuda.synchronize()
+    got = dev.cpu().double().numpy()
+    assert np.abs(loss.cpu().double().numpy() - want_loss).max() <= 2e-4 * max(1.0, np.abs(want_loss).max())
+    assert np.all(np.abs(got - want_grad) <= 2.0 ** -8 * np.abs(want_grad) + 2.0 ** -8 * scale * 1e-3)
