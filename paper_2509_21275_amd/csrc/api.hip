@@ -133,43 +133,69 @@ std::atomic<unsigned long long*> g_clock_log{nullptr};
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 // Forward workspace: [work items | transpose jobs | redo flags (zero)] (uploaded as one blob) then the
-// transposed V images.
+// transposed V images or, for head_dim 128, the partial results of items whose walks are cut.
 struct FwdLayout {
   int tile_rows;
-  size_t items_bytes, jobs_off, flags_off, blob_bytes, vt_off, total;
-  int64_t blocks;
+  KeySplit split;  // head_dim 128: how the walks are cut
+  size_t n_items, n_wholes, wholes_off, jobs_off, flags_off, blob_bytes, vt_off, total;
+  int64_t blocks, whole_blocks;
   int64_t kv_tiles;
-  std::vector<FwdItem> items;
+  std::vector<FwdItem> items, wholes;
   std::vector<TileJob> jobs;
 };
 
-void layout_fwd(const chunk_attn_desc* d, FwdLayout& L, bool with_plan) {
+// Scratch memory of the forward that allocates nothing (chunk_attn_fwd_static), below.
+constexpr size_t kStaticScratchBytes = (size_t)16 << 20;
+
+// `may_cut`: false: no walk is cut whatever the chunk.  Partial results take the place of the V images, which head_dim 128
+// does not need, or up to the static forward's scratch memory where the images would be smaller; the cut is a
+// function of the chunk alone, so that every entry point gives the same bits.
+void layout_fwd(const chunk_attn_desc* d, FwdLayout& L, bool with_plan, bool may_cut = true) {
   const int group = d->num_q_heads / d->num_kv_heads;
+  const int inner = d->num_kv_heads * (group / heads_per_wg(group, fwd_waves(d->head_dim)));
+  const bool pipe = d->head_dim == 128;
   L.tile_rows = tile_rows(group, fwd_waves(d->head_dim)) * fwd_qblocks(d->head_dim);
-  size_t n_items = 0;
-  if (with_plan) {
-    L.items = plan_fwd(d, L.tile_rows);
-    L.jobs = tile_jobs(d, true, 64, nullptr);
-    n_items = L.items.size();
-  } else {
-    for (int t = 0; t < d->num_segments; ++t) n_items += (d->segments[t].q_len + L.tile_rows - 1) / L.tile_rows;
-  }
+  L.n_wholes = 0;
+  for (int t = 0; t < d->num_segments; ++t) L.n_wholes += (d->segments[t].q_len + L.tile_rows - 1) / L.tile_rows;
   L.kv_tiles = count_tiles(d, true, 64);
-  L.items_bytes = n_items * sizeof(FwdItem);
-  L.jobs_off = align_up(L.items_bytes);
-  L.blocks = (int64_t)n_items * d->num_kv_heads * (group / heads_per_wg(group, fwd_waves(d->head_dim)));
-  L.flags_off = align_up(L.jobs_off + (size_t)L.kv_tiles * sizeof(TileJob));
-  // one flag per block, then "any flag raised", then the block-queue counters of the pipelined kernel (all zero)
-  L.blob_bytes = L.flags_off + ((size_t)L.blocks + 1 + kBlockQueues) * sizeof(int32_t);
-  L.vt_off = align_up(L.blob_bytes);
-  L.total = L.vt_off + align_up((size_t)L.kv_tiles * d->num_kv_heads * d->head_dim * 64 * sizeof(__bf16));
+  const size_t image_bytes = align_up((size_t)L.kv_tiles * d->num_kv_heads * d->head_dim * 64 * sizeof(__bf16));
+  L.whole_blocks = (int64_t)L.n_wholes * inner;
+  const size_t part_bytes = (size_t)inner * kPartFloats * sizeof(float);
+  // the fixed part of a layout with n items to run: [items | whole items, if any was cut | V tile jobs, if V images are
+  // made | a redo flag per whole block and the block-queue counters of the pipelined kernel (all zero)]
+  auto place = [&](size_t n_items) {
+    L.n_items = n_items;
+    L.wholes_off = n_items == L.n_wholes ? 0 : align_up(n_items * sizeof(FwdItem));
+    L.jobs_off = align_up(L.wholes_off + L.n_wholes * sizeof(FwdItem));
+    L.flags_off = align_up(L.jobs_off + (pipe ? 0 : (size_t)L.kv_tiles * sizeof(TileJob)));
+    L.blob_bytes = L.flags_off + ((size_t)L.whole_blocks + kBlockQueues) * sizeof(int32_t);
+    L.vt_off = align_up(L.blob_bytes);
+  };
+  L.split = KeySplit{};
+  if (pipe && may_cut) {
+    place(L.n_wholes);
+    const size_t room = std::max(image_bytes, L.vt_off < kStaticScratchBytes ? kStaticScratchBytes - L.vt_off : 0);
+    L.split = choose_key_split(d, L.tile_rows, inner, kCus, (int64_t)(room / part_bytes));
+    if (L.split.target > 0) {
+      place((size_t)L.split.pieces);
+      // (the longer item list may not push the static forward's total past its limit)
+      if ((size_t)L.split.parts * part_bytes > std::max(image_bytes, L.vt_off < kStaticScratchBytes ? kStaticScratchBytes - L.vt_off : 0))
+        L.split = KeySplit{};
+    }
+  }
+  if (L.split.target == 0) place(L.n_wholes);
+  L.blocks = (int64_t)L.n_items * inner;
+  L.total = L.vt_off + std::max(image_bytes, align_up((size_t)L.split.parts * part_bytes));
+  if (!with_plan) return;
+  L.wholes = plan_fwd(d, L.tile_rows);
+  L.items = cut_items(L.wholes, L.split.target);
+  if (!pipe) L.jobs = tile_jobs(d, true, 64, nullptr);
 }
 
 // ---- the forward that allocates nothing (chunk_attn_fwd_static) ----
 // Its scratch memory is this array instead of a caller's workspace: every GPU the library runs on holds its own copy, at
 // its own address, until the process ends.  Host code never uses the array's name as an address: static_scratch() asks
 // the runtime for the device address once per device and hands that out.
-constexpr size_t kStaticScratchBytes = (size_t)16 << 20;
 constexpr int kStaticMaxSegments = 64;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
@@ -192,14 +218,15 @@ hipError_t static_scratch(char** out) {
 }
 
 // The forward's schedule made on the device from a segment table passed by value: work items in segment order (their
-// order does not change any result), the 64-row tiles of V, and the redo flags cleared.
+// order does not change any result) and the pieces of those that are cut, the 64-row tiles of V, and the redo flags cleared.
 struct StaticSegs {
   chunk_attn_seg seg[kStaticMaxSegments];
 };
-__global__ __launch_bounds__(256) void plan_fwd_static_kernel(StaticSegs segs, int n_seg, int tile_rows, FwdItem* items,
-                                                              int n_items, TileJob* jobs, int n_jobs, int32_t* flags,
-                                                              int n_flags) {
+__global__ __launch_bounds__(256) void plan_fwd_static_kernel(StaticSegs segs, int n_seg, int tile_rows, FwdItem* wholes,
+                                                              int n_wholes, FwdItem* items, int target, TileJob* jobs,
+                                                              int n_jobs, int32_t* flags, int n_flags) {
   __shared__ int item0[kStaticMaxSegments + 1], job0[kStaticMaxSegments + 1];
+  __shared__ int wave_items[4], wave_parts[4];
   if (threadIdx.x == 0) {
     int ni = 0, nj = 0;
     for (int t = 0; t < n_seg; ++t) {
@@ -212,18 +239,66 @@ __global__ __launch_bounds__(256) void plan_fwd_static_kernel(StaticSegs segs, i
     job0[n_seg] = nj;
   }
   __syncthreads();
-  for (int x = threadIdx.x; x < n_items; x += 256) {
-    int t = 0;
-    while (t + 1 < n_seg && item0[t + 1] <= x) ++t;
-    const chunk_attn_seg s = segs.seg[t];
-    const int i0 = (x - item0[t]) * tile_rows;
+  // 256 whole items at a time; `items_before` and `parts_before` count the pieces of the items before them
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int items_before = 0, parts_before = 0;
+  for (int x0 = 0; x0 < n_wholes; x0 += 256) {
+    const int x = x0 + threadIdx.x;
     FwdItem it{};
-    it.q_row0 = s.q_start + i0;
-    it.q_rows = min(tile_rows, s.q_len - i0);
-    it.kv_row0 = s.kv_start;
-    it.n0 = s.kv_len - s.q_len + i0 + 1;
-    it.kv_tile0 = job0[t];
-    items[x] = it;
+    int stages = 0, n = 0;
+    if (x < n_wholes) {
+      int t = 0;
+      while (t + 1 < n_seg && item0[t + 1] <= x) ++t;
+      const chunk_attn_seg s = segs.seg[t];
+      const int i0 = (x - item0[t]) * tile_rows;
+      it.q_row0 = s.q_start + i0;
+      it.q_rows = min(tile_rows, s.q_len - i0);
+      it.kv_row0 = s.kv_start;
+      it.n0 = s.kv_len - s.q_len + i0 + 1;
+      it.kv_tile0 = job0[t];
+      it.keys = s.kv_len;
+      stages = walk_stages(it.n0, it.q_rows);
+      n = piece_count(stages, it.n0, target);
+    }
+    int item = n, part = n > 1 ? n : 0;  // inclusive sums over the items up to this one
+    for (int o = 1; o < 64; o *= 2) {
+      const int a = __shfl_up(item, o), b = __shfl_up(part, o);
+      if (lane >= o) {
+        item += a;
+        part += b;
+      }
+    }
+    if (lane == 63) {
+      wave_items[wave] = item;
+      wave_parts[wave] = part;
+    }
+    __syncthreads();
+    item += items_before - n;
+    part += parts_before - (n > 1 ? n : 0);
+    for (int w = 0; w < 4; ++w) {
+      if (w < wave) {
+        item += wave_items[w];
+        part += wave_parts[w];
+      }
+      items_before += wave_items[w];
+      parts_before += wave_parts[w];
+    }
+    __syncthreads();
+    for (int k = 0; k < n; ++k) {
+      const int b = piece_begin(stages, n, k) * kStageKeys;
+      FwdItem p = it;
+      p.kv_row0 += b;
+      p.n0 -= b;
+      p.keys = (k + 1 < n ? piece_begin(stages, n, k + 1) * kStageKeys : it.keys) - b;
+      p.whole = x;
+      p.part = n > 1 ? part + k : -1;
+      items[item + k] = p;
+    }
+    if (x < n_wholes && target > 0) {
+      it.whole = n;
+      it.part = n > 1 ? part : -1;
+      wholes[x] = it;
+    }
   }
   for (int x = threadIdx.x; x < n_jobs; x += 256) {
     int t = 0;
@@ -337,6 +412,11 @@ ProfileEvents& profile_events() {
 }
 }  // namespace chunk_attn
 
+namespace {
+int fwd_any(const chunk_attn_desc* desc, const void* q, const void* k, const void* v, void* o, float* lse, void* workspace,
+            size_t workspace_bytes, bool may_cut, void* stream_v);
+}
+
 extern "C" {
 
 int chunk_attn_profile_events(void* start_event, void* stop_event) {
@@ -417,7 +497,7 @@ int chunk_attn_workspace_bytes(const chunk_attn_desc* desc, size_t* fwd_bytes, s
   const chunk_attn_desc w = is_narrow(desc) ? widened(desc) : *desc;
   if (fwd_bytes) {
     FwdLayout L;
-    layout_fwd(&w, L, false);
+    layout_fwd(&w, L, false, !is_narrow(desc));
     *fwd_bytes = is_narrow(desc) ? narrow_fwd_layout(desc, L.total).total : L.total;
   }
   if (bwd_bytes) {
@@ -430,6 +510,13 @@ int chunk_attn_workspace_bytes(const chunk_attn_desc* desc, size_t* fwd_bytes, s
 
 int chunk_attn_fwd(const chunk_attn_desc* desc, const void* q, const void* k, const void* v, void* o, float* lse,
                    void* workspace, size_t workspace_bytes, void* stream_v) {
+  return fwd_any(desc, q, k, v, o, lse, workspace, workspace_bytes, true, stream_v);
+}
+
+}  // extern "C"
+namespace {
+int fwd_any(const chunk_attn_desc* desc, const void* q, const void* k, const void* v, void* o, float* lse, void* workspace,
+            size_t workspace_bytes, bool may_cut, void* stream_v) {
   const int rc = validate(desc);
   if (rc != CHUNK_ATTN_OK) return rc;
   if (!q || !k || !v || !o || !lse || !workspace) return CHUNK_ATTN_INVALID_ARG;
@@ -439,7 +526,7 @@ int chunk_attn_fwd(const chunk_attn_desc* desc, const void* q, const void* k, co
   if (is_narrow(desc)) {  // run as head_dim 128 on zero-padded copies
     const chunk_attn_desc w = widened(desc);
     FwdLayout Lw;
-    layout_fwd(&w, Lw, false);
+    layout_fwd(&w, Lw, false, false);
     const NarrowFwdLayout N = narrow_fwd_layout(desc, Lw.total);
     if (workspace_bytes < N.total) return CHUNK_ATTN_WORKSPACE_TOO_SMALL;
     hipStream_t st = static_cast<hipStream_t>(stream_v);
@@ -449,20 +536,22 @@ int chunk_attn_fwd(const chunk_attn_desc* desc, const void* q, const void* k, co
     if ((pe = pad_rows(q, base + N.q_off, qr, 2, st)) != hipSuccess || (pe = pad_rows(k, base + N.k_off, kr, 2, st)) != hipSuccess ||
         (pe = pad_rows(v, base + N.v_off, kr, 2, st)) != hipSuccess)
       return hip_fail(pe, "padding launch");
-    const int r = chunk_attn_fwd(&w, base + N.q_off, base + N.k_off, base + N.v_off, base + N.o_off, lse, base + N.inner_off,
-                                 workspace_bytes - N.inner_off, stream_v);
+    const int r = fwd_any(&w, base + N.q_off, base + N.k_off, base + N.v_off, base + N.o_off, lse, base + N.inner_off,
+                          workspace_bytes - N.inner_off, false, stream_v);
     if (r != CHUNK_ATTN_OK) return r;
     if ((pe = unpad_rows(base + N.o_off, o, qr, 2, st)) != hipSuccess) return hip_fail(pe, "unpadding launch");
     return CHUNK_ATTN_OK;
   }
   FwdLayout L;
-  layout_fwd(desc, L, true);
+  layout_fwd(desc, L, true, may_cut);
+  if (workspace_bytes < L.total && may_cut) layout_fwd(desc, L, true, false);  // too small for partial results: nothing is cut
   if (workspace_bytes < L.total) return CHUNK_ATTN_WORKSPACE_TOO_SMALL;
   hipStream_t stream = static_cast<hipStream_t>(stream_v);
   char* ws = static_cast<char*>(workspace);
 
   std::vector<char> blob(L.blob_bytes, 0);
-  std::memcpy(blob.data(), L.items.data(), L.items_bytes);
+  std::memcpy(blob.data() + L.wholes_off, L.wholes.data(), L.wholes.size() * sizeof(FwdItem));
+  std::memcpy(blob.data(), L.items.data(), L.items.size() * sizeof(FwdItem));
   std::memcpy(blob.data() + L.jobs_off, L.jobs.data(), L.jobs.size() * sizeof(TileJob));
   hipError_t e = g_ring.upload(ws, blob.data(), blob.size(), stream);
   if (e != hipSuccess) return hip_fail(e, "schedule upload");
@@ -476,6 +565,8 @@ int chunk_attn_fwd(const chunk_attn_desc* desc, const void* q, const void* k, co
   p.lse = lse;
   p.vt = vt;
   p.items = reinterpret_cast<const FwdItem*>(ws);
+  p.wholes = reinterpret_cast<const FwdItem*>(ws + L.wholes_off);
+  p.parts = reinterpret_cast<float*>(ws + L.vt_off);
   p.total_kv_tiles = L.kv_tiles;
   p.num_q_heads = desc->num_q_heads;
   p.num_kv_heads = desc->num_kv_heads;
@@ -485,8 +576,7 @@ int chunk_attn_fwd(const chunk_attn_desc* desc, const void* q, const void* k, co
   p.total_q = desc->total_q;
   p.scale_log2 = desc->softmax_scale * 1.4426950408889634f;
   p.redo = desc->head_dim == 128 ? reinterpret_cast<int32_t*>(ws + L.flags_off) : nullptr;
-  p.any_redo = reinterpret_cast<int32_t*>(ws + L.flags_off) + L.blocks;
-  p.taken = p.any_redo + 1;
+  p.taken = reinterpret_cast<int32_t*>(ws + L.flags_off) + L.whole_blocks;
   p.clock_log = clock_log(0);
   p.ref_limit = g_fwd_rescale_limit.load();
   const int64_t blocks = L.blocks;
@@ -494,11 +584,16 @@ int chunk_attn_fwd(const chunk_attn_desc* desc, const void* q, const void* k, co
   ProfileEvents pe = profile_events();
   profile_events() = ProfileEvents{};
   if (pe.start && (e = hipEventRecord(pe.start, stream)) != hipSuccess) return hip_fail(e, "event record");
-  e = launch_fwd(p, desc->head_dim, (int)blocks, reinterpret_cast<const TileJob*>(ws + L.jobs_off), (int)L.jobs.size(), stream);
+  e = launch_fwd(p, desc->head_dim, (int)blocks, (int)L.whole_blocks, reinterpret_cast<const TileJob*>(ws + L.jobs_off),
+                 (int)L.jobs.size(), stream);
   if (e != hipSuccess) return hip_fail(e, "forward launch");
   if (pe.stop && (e = hipEventRecord(pe.stop, stream)) != hipSuccess) return hip_fail(e, "event record");
   return CHUNK_ATTN_OK;
 }
+
+}  // namespace
+
+extern "C" {
 
 int chunk_attn_fwd_static(const chunk_attn_desc* desc, const void* q, const void* k, const void* v, void* o, float* lse,
                           void* stream_v) {
@@ -509,7 +604,7 @@ int chunk_attn_fwd_static(const chunk_attn_desc* desc, const void* q, const void
     return CHUNK_ATTN_INVALID_ARG;
   const chunk_attn_desc wide = is_narrow(desc) ? widened(desc) : *desc;
   FwdLayout L;
-  layout_fwd(&wide, L, false);
+  layout_fwd(&wide, L, false, !is_narrow(desc));
   const NarrowFwdLayout N = is_narrow(desc) ? narrow_fwd_layout(desc, L.total) : NarrowFwdLayout{0, 0, 0, 0, 0, L.total};
   if (desc->num_segments > kStaticMaxSegments || N.total > kStaticScratchBytes || L.blocks > 0x7fffffff)
     return CHUNK_ATTN_TOO_LARGE;
@@ -533,10 +628,10 @@ int chunk_attn_fwd_static(const chunk_attn_desc* desc, const void* q, const void
 
   StaticSegs segs;
   for (int t = 0; t < desc->num_segments; ++t) segs.seg[t] = desc->segments[t];
-  const int n_items = (int)(L.items_bytes / sizeof(FwdItem));
   hipLaunchKernelGGL(plan_fwd_static_kernel, dim3(1), dim3(256), 0, stream, segs, desc->num_segments, L.tile_rows,
-                     reinterpret_cast<FwdItem*>(ws), n_items, reinterpret_cast<TileJob*>(ws + L.jobs_off), (int)L.kv_tiles,
-                     reinterpret_cast<int32_t*>(ws + L.flags_off), (int)L.blocks + 1 + kBlockQueues);
+                     reinterpret_cast<FwdItem*>(ws + L.wholes_off), (int)L.n_wholes, reinterpret_cast<FwdItem*>(ws),
+                     L.split.target, reinterpret_cast<TileJob*>(ws + L.jobs_off), desc->head_dim == 128 ? 0 : (int)L.kv_tiles,
+                     reinterpret_cast<int32_t*>(ws + L.flags_off), (int)L.whole_blocks + kBlockQueues);
   if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "schedule kernel launch");
 
   FwdParams p;
@@ -547,6 +642,8 @@ int chunk_attn_fwd_static(const chunk_attn_desc* desc, const void* q, const void
   p.lse = lse;
   p.vt = reinterpret_cast<__bf16*>(ws + L.vt_off);
   p.items = reinterpret_cast<const FwdItem*>(ws);
+  p.wholes = reinterpret_cast<const FwdItem*>(ws + L.wholes_off);
+  p.parts = reinterpret_cast<float*>(ws + L.vt_off);
   p.total_kv_tiles = L.kv_tiles;
   p.num_q_heads = desc->num_q_heads;
   p.num_kv_heads = desc->num_kv_heads;
@@ -556,11 +653,11 @@ int chunk_attn_fwd_static(const chunk_attn_desc* desc, const void* q, const void
   p.total_q = desc->total_q;
   p.scale_log2 = desc->softmax_scale * 1.4426950408889634f;
   p.redo = desc->head_dim == 128 ? reinterpret_cast<int32_t*>(ws + L.flags_off) : nullptr;
-  p.any_redo = reinterpret_cast<int32_t*>(ws + L.flags_off) + L.blocks;
-  p.taken = p.any_redo + 1;
+  p.taken = reinterpret_cast<int32_t*>(ws + L.flags_off) + L.whole_blocks;
   p.clock_log = clock_log(0);
   p.ref_limit = g_fwd_rescale_limit.load();
-  e = launch_fwd(p, desc->head_dim, (int)L.blocks, reinterpret_cast<const TileJob*>(ws + L.jobs_off), (int)L.kv_tiles, stream);
+  e = launch_fwd(p, desc->head_dim, (int)L.blocks, (int)L.whole_blocks, reinterpret_cast<const TileJob*>(ws + L.jobs_off),
+                 (int)L.kv_tiles, stream);
   if (e != hipSuccess) return hip_fail(e, "forward launch");
   if (o != o_user && (e = unpad_rows(o, o_user, qr, 2, stream)) != hipSuccess) return hip_fail(e, "unpadding launch");
   return CHUNK_ATTN_OK;
@@ -580,7 +677,7 @@ int bwd_any(const chunk_attn_desc* desc, const void* q, const void* k, const voi
   if (is_narrow(desc)) {  // run as head_dim 128 on zero-padded copies
     const chunk_attn_desc w = widened(desc);
     BwdPlan Pw;
-    bwd_layout(&w, Pw, false);
+    bwd_layout(&w, Pw, false, false);
     const NarrowBwdLayout N = narrow_bwd_layout(desc, Pw.total);
     if (workspace_bytes < N.total) return CHUNK_ATTN_WORKSPACE_TOO_SMALL;
     hipStream_t st = static_cast<hipStream_t>(stream_v);
@@ -607,6 +704,7 @@ int bwd_any(const chunk_attn_desc* desc, const void* q, const void* k, const voi
   }
   BwdPlan P;
   bwd_layout(desc, P, true);
+  if (workspace_bytes < P.total) bwd_layout(desc, P, true, false);  // too small for a cut's item lists: nothing is cut
   if (workspace_bytes < P.total) return CHUNK_ATTN_WORKSPACE_TOO_SMALL;
   hipStream_t stream = static_cast<hipStream_t>(stream_v);
   BwdArgs a;

@@ -90,6 +90,7 @@ struct DqParams {
   int64_t total_kv32_tiles, total_q_tiles;
   int32_t num_q_heads, num_kv_heads, group, heads_per_wg, head_splits;
   float scale, scale_log2;
+  float* parts;          // partial results of pieces (pipelined kernel), kPartRowFloats per (slot, inner index)
   int32_t* taken;        // 8 block-queue counters of the pipelined kernel (zero before the launch)
   unsigned long long* clock_log;  // null, or where the pipelined kernel's workgroups log their clocks
 };
@@ -1244,7 +1245,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_pipe_kernel(DqParams p, int num
     row0[u] = (unit / p.heads_per_wg) * 32;
   }
 
-  const int n_wg = it.n0 + it.q_rows - 1;    // keys visible to the last valid row
+  const int n_wg = min(it.n0 + it.q_rows - 1, it.keys);  // keys the last valid row sees of the item's range
   const int nt = (n_wg + BN - 1) / BN;       // stages
 
   const int64_t q_stride = (int64_t)p.num_q_heads * D, kv_stride = (int64_t)p.num_kv_heads * D;
@@ -1528,6 +1529,17 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_pipe_kernel(DqParams p, int num
   int lane_e = lane;
   asm volatile("" : "+v"(lane_e));
   const int l32_e = lane_e & 31, hh_e = lane_e >> 5;
+  if (it.part >= 0) {  // a piece: dQ^T as it is, put together by bwd_dq_merge_kernel
+    float* const out = p.parts + ((int64_t)it.part * inner_n + inner) * kPartRowFloats + wave * (2 * 4096) + lane_e * 4;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          *reinterpret_cast<f32x4*>(out + u * 4096 + (db * 4 + g) * 256) =
+              f32x4{dq[u][db][4 * g], dq[u][db][4 * g + 1], dq[u][db][4 * g + 2], dq[u][db][4 * g + 3]};
+  } else
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
 #pragma unroll
@@ -1554,6 +1566,34 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_pipe_kernel(DqParams p, int num
   blk = broadcast_from_wave0(next_block, nb);
   }
   clock_log_stamp(p.clock_log, 1);
+}
+
+// dQ rows of the items whose walks were cut: the sum of their partial results, in the order of the pieces, times the
+// scale.  One workgroup per (whole item, inner index), each of its 8 waves one unit of 32 rows in the layout in which
+// the pipelined kernel held it.  Bound by the reads of the partial results (128 KB per block and piece).
+__global__ __launch_bounds__(512) void bwd_dq_merge_kernel(DqParams p, const DqItem* __restrict__ cut) {
+  const int lane = threadIdx.x & 63, l32 = lane & 31, hh = lane >> 5;
+  const int unit = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int inner_n = p.num_kv_heads * p.head_splits, inner = blockIdx.x % inner_n;
+  const DqItem it = cut[blockIdx.x / inner_n];
+  const int kvh = inner % p.num_kv_heads, hs = inner / p.num_kv_heads;
+  const int head = kvh * p.group + hs * p.heads_per_wg + unit % p.heads_per_wg;
+  const int r = (unit / p.heads_per_wg) * 32 + l32;
+  if (r >= it.q_rows) return;
+  const int64_t step = (int64_t)inner_n * kPartRowFloats;
+  const float* src = p.parts + (int64_t)it.part * step + (int64_t)inner * kPartRowFloats + unit * 4096 + lane * 4;
+  f32x4 s[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) s[i] = *reinterpret_cast<const f32x4*>(src + i * 256);
+  for (int k = 1; k < it.kv_tile0; ++k) {  // kv_tile0: number of pieces
+    src += step;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s[i] += *reinterpret_cast<const f32x4*>(src + i * 256);
+  }
+  __bf16* op = p.dq + (int64_t)(it.q_row0 + r) * p.num_q_heads * 128 + (int64_t)head * 128 + 4 * hh;
+#pragma unroll
+  for (int i = 0; i < 16; ++i)
+    *reinterpret_cast<bf16x4*>(op + 8 * i) = pack4(s[i][0] * p.scale, s[i][1] * p.scale, s[i][2] * p.scale, s[i][3] * p.scale);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1619,6 +1659,7 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
     p.num_q_heads = d->num_q_heads; p.num_kv_heads = d->num_kv_heads; p.group = group;
     p.heads_per_wg = heads_per_wg(group, dq_waves(D)); p.head_splits = group / p.heads_per_wg;
     p.scale = d->softmax_scale; p.scale_log2 = d->softmax_scale * kLog2e;
+    p.parts = reinterpret_cast<float*>(ws + P.fdq_off);  // (the one-pass backward's dQ tiles: only one of the two runs)
     p.taken = reinterpret_cast<int32_t*>(ws + P.queues_off);
     p.clock_log = clock_log(1);
     const int64_t blocks = (int64_t)P.dq_items.size() * d->num_kv_heads * p.head_splits;
@@ -1629,6 +1670,11 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
       static const hipError_t attr = raise_smem_limit(&bwd_dq_pipe_kernel<D>, smem);
       if (attr != hipSuccess) return attr;
       hipLaunchKernelGGL((bwd_dq_pipe_kernel<D>), dim3((unsigned)persistent_grid(blocks)), dim3(256), smem, stream, p, (int)blocks);
+      if (P.n_dq_cut > 0) {
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        hipLaunchKernelGGL(bwd_dq_merge_kernel, dim3((unsigned)(P.n_dq_cut * d->num_kv_heads * p.head_splits)), dim3(512), 0, stream, p,
+                           reinterpret_cast<const DqItem*>(ws + P.dq_cut_off));
+      }
     } else {
       const size_t smem = (size_t)9 * 32 * D * 2;  // 3 stages of K, V and K^T tiles
       constexpr int DQW = 4;
@@ -1682,37 +1728,49 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
 
 }  // namespace
 
-void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan) {
+void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, bool may_cut) {
+  P = BwdPlan{};
   const int group = d->num_q_heads / d->num_kv_heads;
   const int dq_rows = tile_rows(group, dq_waves(d->head_dim));
+  const bool pipe = d->head_dim == 128;
   P.q_tiles = count_tiles(d, false, 64);
   P.kv32_tiles = count_tiles(d, true, 32);
   P.qt32_tiles = count_tiles(d, false, 32);
+  // head_dim 128: room for dQ tiles in float32, for the one-pass backward or for the partial results of cut dQ walks
+  const size_t dq_tile_bytes = pipe ? (size_t)fused_num_bufs(d, dkv_keys(128)) * d->num_q_heads * P.qt32_tiles * 4096 * sizeof(float) : 0;
   P.fused = d->head_dim == 128 && bwd_mode() == 2;
   size_t n_dq = 0, n_dkv = 0;
+  if (pipe && may_cut && !P.fused) {
+    const int inner = d->num_kv_heads * (group / heads_per_wg(group, dq_waves(d->head_dim)));
+    P.split = choose_key_split(d, dq_rows, inner, kCus, (int64_t)(dq_tile_bytes / ((size_t)inner * kPartRowFloats * sizeof(float))));
+  }
   if (with_plan) {
     if (P.fused) {
       P.fplan = plan_fused(d, dkv_keys(d->head_dim), kNumXcd, fused_num_bufs(d, dkv_keys(d->head_dim)));
     } else {
       P.dq_items = plan_dq(d, dq_rows);
+      if (P.split.target > 0) P.dq_items = cut_items(P.dq_items, P.split.target, &P.dq_cut);
       // head_dim 128: the pipelined kernel walks either way; the key blocks of one key/value head that run at the same time
       // are the workgroups of the launch (one per CU) over the number of key/value heads
       const int side_by_side = d->head_dim == 128 ? std::max(1, persistent_grid(0x7fffffff) / d->num_kv_heads) : 0;
       P.dkv_items = plan_dkv(d, dkv_keys(d->head_dim), side_by_side);
     }
     P.qjobs = tile_jobs(d, false, 64, nullptr);
-    P.kjobs = tile_jobs(d, true, 32, nullptr);
+    if (!pipe) P.kjobs = tile_jobs(d, true, 32, nullptr);
   }
   // the layout does not depend on which backward runs: item counts follow from the segment table
   for (int t = 0; t < d->num_segments; ++t) {
     n_dq += (d->segments[t].q_len + dq_rows - 1) / dq_rows;
     n_dkv += (d->segments[t].kv_len + dkv_keys(d->head_dim) - 1) / dkv_keys(d->head_dim);
   }
+  // (cut walks: the pieces, then the whole items that were cut, of which there are at most as many as items)
+  P.n_dq_cut = P.dq_cut.size();
   P.dq_items_off = 0;
-  P.dkv_items_off = up256(n_dq * sizeof(DqItem));
+  P.dq_cut_off = P.split.target > 0 ? up256((size_t)P.split.pieces * sizeof(DqItem)) : 0;
+  P.dkv_items_off = P.dq_cut_off + up256(n_dq * sizeof(DqItem));
   P.qjobs_off = P.dkv_items_off + up256(n_dkv * sizeof(DkvItem));
   P.kjobs_off = P.qjobs_off + up256((size_t)P.q_tiles * sizeof(TileJob));
-  P.fitems_off = P.kjobs_off + up256((size_t)P.kv32_tiles * sizeof(TileJob));
+  P.fitems_off = P.kjobs_off + (pipe ? 0 : up256((size_t)P.kv32_tiles * sizeof(TileJob)));
   // the workspace is sized for either backward (the mode may change between the size query and the call): the one-pass
   // backward has one item per (key block, key/value head) and at most 8 x that many workgroup slots
   const size_t n_fused = d->head_dim == 128 ? n_dkv_blocks(d) * (size_t)d->num_kv_heads : 0;
@@ -1731,12 +1789,13 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan) {
   // transposed K images only for head_dim 64 (the head_dim 128 dQ kernel reads K^T from its K tiles)
   // (256 bytes remain in any case: the dK/dV kernels copy the LSE / D rows 64 at a time, up to 32 past a segment's last)
   P.fdq_off = P.kt_off + (d->head_dim == 128 ? 256 : up256((size_t)d->num_kv_heads * P.kv32_tiles * 32 * d->head_dim * sizeof(__bf16)));
-  P.total = P.fdq_off + (d->head_dim == 128 ? (size_t)fused_num_bufs(d, dkv_keys(128)) * d->num_q_heads * P.qt32_tiles * 4096 * sizeof(float) : 0);
+  P.total = P.fdq_off + dq_tile_bytes;
 }
 
 std::vector<char> bwd_blob(const BwdPlan& P) {
   std::vector<char> blob(P.blob_bytes);
   std::memcpy(blob.data() + P.dq_items_off, P.dq_items.data(), P.dq_items.size() * sizeof(DqItem));
+  std::memcpy(blob.data() + P.dq_cut_off, P.dq_cut.data(), P.dq_cut.size() * sizeof(DqItem));
   std::memcpy(blob.data() + P.dkv_items_off, P.dkv_items.data(), P.dkv_items.size() * sizeof(DkvItem));
   std::memcpy(blob.data() + P.qjobs_off, P.qjobs.data(), P.qjobs.size() * sizeof(TileJob));
   std::memcpy(blob.data() + P.kjobs_off, P.kjobs.data(), P.kjobs.size() * sizeof(TileJob));

@@ -12,11 +12,13 @@
 // Two kernels:
 //   fwd_kernel       online softmax with a lazily moved reference maximum, one 32-row query block per wave,
 //                    two waves per SIMD, tiles of 64 keys (K row-major, V as the pre-transposed image of
-//                    transpose_kernel.hip, double-buffered).  Used for head_dim 64, and for head_dim 128 as the
-//                    second pass below.
+//                    transpose_kernel.hip, double-buffered).  Used for head_dim 64 and 256, and for head_dim 128
+//                    (V read transposed from row tiles, no image) as the second pass below.
 //   fwd_pipe_kernel  head_dim 128: one wave per SIMD with 64 query rows, software pipelined over stages of 32
 //                    keys, reference maximum fixed by the first stage; rows whose scores outgrow it are
-//                    flagged and recomputed by fwd_kernel, launched right after over the flagged items only.
+//                    flagged and recomputed by fwd_kernel, launched right after.  Where a chunk has too few items for
+//                    the chip their walks are cut into pieces (plan.hpp); the pieces leave float32 partial results, which
+//                    the second pass puts together.
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -28,6 +30,44 @@
 
 namespace chunk_attn {
 
+// Puts the pieces of one block together: O = sum_s 2^(m_s - M) O_s / l, l = sum_s 2^(m_s - M) l_s over its partial results
+// (O_s unnormalised, m_s the reference maximum, l_s the sum), M the largest m_s.  Each of the 8 waves takes one unit of
+// 32 rows in the layout in which the pipelined kernel held it.  Bound by the reads of the partial results (128 KB per
+// block and piece, mostly out of the caches they were just written to).
+__device__ __forceinline__ void fwd_merge_parts(const FwdParams& p, const FwdItem& it, int kvh, int hs, int inner, int inner_n,
+                                                int unit, int lane) {
+  const int l32 = lane & 31, hh = lane >> 5;
+  const int w = unit >> 1;  // wave of the pipelined kernel
+  const int head = kvh * p.group + hs * p.heads_per_wg + w % p.heads_per_wg;
+  const int r = (w / p.heads_per_wg) * 64 + 32 * (unit & 1) + l32;
+  const int64_t step = (int64_t)inner_n * kPartFloats;
+  const float* const part0 = p.parts + (int64_t)it.part * step + (int64_t)inner * kPartFloats;
+  const float* const ml = part0 + kPartRowFloats + (unit * 32 + l32) * 2;
+  float m = ml[0], l = 0.f;
+  for (int s = 1; s < it.whole; ++s) m = fmaxf(m, ml[s * step]);
+  for (int s = 0; s < it.whole; ++s) l += ml[s * step + 1] * __builtin_amdgcn_exp2f(ml[s * step] - m);
+  f32x4 o[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const float* src = part0 + unit * 4096 + lane * 4;
+  for (int s = 0; s < it.whole; ++s, src += step) {
+    const float f = __builtin_amdgcn_exp2f(ml[s * step] - m);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(src + i * 256);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[i][e] += v[e] * f;
+    }
+  }
+  if (r >= it.q_rows) return;
+  const float inv = 1.0f / l;
+  __bf16* op = p.o + (int64_t)(it.q_row0 + r) * p.num_q_heads * 128 + (int64_t)head * 128 + 4 * hh;
+#pragma unroll
+  for (int i = 0; i < 16; ++i)
+    *reinterpret_cast<bf16x4*>(op + 8 * i) = pack4(o[i][0] * inv, o[i][1] * inv, o[i][2] * inv, o[i][3] * inv);
+  if (hh == 0) p.lse[(int64_t)head * p.total_q + it.q_row0 + r] = (m + log2f(l)) * 0.6931471805599453f;
+}
+
 template <int D, int WAVES>
 __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kernel(FwdParams p) {
   constexpr int QB = 1;        // 32-row query blocks per wave
@@ -38,7 +78,7 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
   constexpr int DB = D / 32;   // 32-row blocks of O^T
   constexpr int KT = BN * D;   // elements per K tile and per V^T image
   constexpr int WR = 32 * QB;  // query rows per wave
-  if (p.redo && p.redo[blockIdx.x] == 0) return;  // second pass: only the items the pipelined kernel gave up on
+  constexpr bool IMG = D != 128;  // V arrives as a transposed image; else as rows, two chunk-major tiles of 32
 
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   __bf16* Ks = reinterpret_cast<__bf16*>(smem);  // [2][BN][D]  swizzled rows
@@ -51,8 +91,14 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
 
   const int inner_n = p.num_kv_heads * p.head_splits;
   const int inner = blockIdx.x % inner_n;
-  const FwdItem it = p.items[blockIdx.x / inner_n];
+  const FwdItem it = (IMG ? p.items : p.wholes)[blockIdx.x / inner_n];
   const int kvh = inner % p.num_kv_heads, hs = inner / p.num_kv_heads;
+  if constexpr (!IMG) {  // second pass: only what the pipelined kernel left to do
+    if (p.redo[blockIdx.x] == 0) {
+      if (it.part >= 0) fwd_merge_parts(p, it, kvh, hs, inner, inner_n, wave, lane);
+      return;
+    }
+  }
   const int head = kvh * p.group + hs * p.heads_per_wg + wave % p.heads_per_wg;
   const int wave_row0 = (wave / p.heads_per_wg) * WR;  // first tile-local row of this wave
 
@@ -66,7 +112,8 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
 
   const int64_t q_stride = (int64_t)p.num_q_heads * D, kv_stride = (int64_t)p.num_kv_heads * D;
   const __bf16* __restrict__ Kg = p.k + (int64_t)it.kv_row0 * kv_stride + (int64_t)kvh * D;
-  const __bf16* __restrict__ Vimg = p.vt + ((int64_t)kvh * p.total_kv_tiles + it.kv_tile0) * KT;
+  const __bf16* __restrict__ Vimg = IMG ? p.vt + ((int64_t)kvh * p.total_kv_tiles + it.kv_tile0) * KT
+                                        : p.v + (int64_t)it.kv_row0 * kv_stride + (int64_t)kvh * D;
 
   // Per-lane source offsets of the global->LDS copies (elements).  A K tile is 64 rows x KC chunks; copy
   // instruction i of wave w fills LDS chunks [(WAVES i + w) 64, +64), so the lane fetches the chunk that the
@@ -95,11 +142,21 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
         dma16(ksrc + off, kdst + (i * WAVES + wave) * 512);
       }
     }
-    const __bf16* vsrc = Vimg + (int64_t)t * KT;              // wave-uniform
     __bf16* vdst = Vs + buf * KT;
+    if constexpr (IMG) {
+      const __bf16* vsrc = Vimg + (int64_t)t * KT;            // wave-uniform
 #pragma unroll
-    for (int i = 0; i < NV; ++i)
-      dma16(vsrc + (unsigned)(((i * WAVES + wave) * 64 + lane) * 8), vdst + (i * WAVES + wave) * 512);
+      for (int i = 0; i < NV; ++i)
+        dma16(vsrc + (unsigned)(((i * WAVES + wave) * 64 + lane) * 8), vdst + (i * WAVES + wave) * 512);
+    } else {
+      const __bf16* vsrc = Vimg + (int64_t)(BN * t) * kv_stride;
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        const int x = (i * WAVES + wave) * 64 + lane, xt = x % (32 * KC);  // slot, slot in its 32-row tile
+        const int row = x / (32 * KC) * 32 + ((xt & 31) ^ (((xt >> 5) & 3) << 2));
+        dma16(vsrc + (int64_t)min(row, last_row) * kv_stride + (xt >> 5) * 8, vdst + (i * WAVES + wave) * 512);
+      }
+    }
   };
 
   dma_tile(0, 0);
@@ -136,6 +193,12 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
   for (int ks = 0; ks < DK; ++ks) k_off[ks] = tile_elem<KC>(l32, 2 * ks + hh);
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) v_off[ks] = tile_elem<8>(l32, 2 * ks + hh);
+  unsigned vt_lo = 0, vt_hi = 0;  // byte addresses of the transposed reads (as in the pipelined kernel) in buffer 0
+  if constexpr (!IMG) {
+    const int j = lane & 15, cl = 2 * ((lane >> 4) & 1) + ((j & 3) >> 1), r0 = 4 * hh + (j >> 2);
+    vt_lo = lds_addr((lds_bf16*)Vs + cm_elem(r0, cl) + 4 * (j & 1));
+    vt_hi = lds_addr((lds_bf16*)Vs + cm_elem(r0 + 8, cl) + 4 * (j & 1));
+  }
 
   const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   bf16x2 ones;
@@ -222,14 +285,37 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
         l_run[qb] += ps0 + ps1;
       }
       // ---- O^T += V^T P^T : [D] x [32 QB queries], contraction over the 64 keys; every V^T fragment feeds QB products ----
+      if constexpr (IMG) {
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
+        for (int ks = 0; ks < 4; ++ks) {
 #pragma unroll
-        for (int db = 0; db < DB; ++db) {
-          const bf16x8 a = *reinterpret_cast<const bf16x8*>(Vt + v_off[ks] + db * 32 * 64);
+          for (int db = 0; db < DB; ++db) {
+            const bf16x8 a = *reinterpret_cast<const bf16x8*>(Vt + v_off[ks] + db * 32 * 64);
 #pragma unroll
-          for (int qb = 0; qb < QB; ++qb) oacc[qb][db] = mfma32(a, pf[qb][ks], oacc[qb][db]);
+            for (int qb = 0; qb < QB; ++qb) oacc[qb][db] = mfma32(a, pf[qb][ks], oacc[qb][db]);
+          }
         }
+      } else {
+        const unsigned lo_addr = vt_lo + buf * (KT * 2), hi_addr = vt_hi + buf * (KT * 2);
+        static_for<0, 4>([&](auto ks_c) __attribute__((always_inline)) {
+          constexpr int ks = decltype(ks_c)::value;
+          s16x4 lo[4], hi[4];
+          static_assert(IMG || DB == 4, "four blocks of O^T");
+          static_for<0, 4>([&](auto db_c) __attribute__((always_inline)) {
+            constexpr int db = decltype(db_c)::value;
+            constexpr int off = ((ks >> 1) * (32 * D) + (ks & 1) * (16 * 8) + db * (4 * 32 * 8)) * 2;
+            lo[db] = lds_asm_read_tr<off>(lo_addr);
+            hi[db] = lds_asm_read_tr<off>(hi_addr);
+          });
+          asm volatile("s_waitcnt lgkmcnt(0)"
+                       : "+v"(lo[0]), "+v"(lo[1]), "+v"(lo[2]), "+v"(lo[3]), "+v"(hi[0]), "+v"(hi[1]), "+v"(hi[2]), "+v"(hi[3]));
+#pragma unroll
+          for (int db = 0; db < 4; ++db) {
+            const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo[db], hi[db], 0, 1, 2, 3, 4, 5, 6, 7));
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) oacc[qb][db % DB] = mfma32(a, pf[qb][ks], oacc[qb][db % DB]);
+          }
+        });
       }
     }
 
@@ -334,7 +420,7 @@ __global__ __launch_bounds__(256, 1) void fwd_pipe_kernel(FwdParams p, int num_b
   const int head = kvh * p.group + hs * p.heads_per_wg + wave % p.heads_per_wg;
   const int wave_row0 = (wave / p.heads_per_wg) * 64;  // the wave's units are rows wave_row0 + 32 u .. + 31 of `head`
 
-  const int n_wg = it.n0 + it.q_rows - 1;    // keys visible to the last valid row
+  const int n_wg = min(it.n0 + it.q_rows - 1, it.keys);  // keys the last valid row sees of the item's range
   const int nt = (n_wg + BN - 1) / BN;       // stages
 
   const int64_t q_stride = (int64_t)p.num_q_heads * D, kv_stride = (int64_t)p.num_kv_heads * D;
@@ -619,15 +705,28 @@ __global__ __launch_bounds__(256, 1) void fwd_pipe_kernel(FwdParams p, int num_b
   // block may fill the ring again
   __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
   if (__any(risk) && lane == 0) {
-    p.redo[blk] = 1;
-    *p.any_redo = 1;
+    p.redo[it.whole * inner_n + inner] = 1;
   }
 
   // ---- epilogue: O = O^T / l, LSE = ln(l) + m scale ----
   // (through the wave's staging tile: the lane that holds four values of a row writes them there, then every lane
   // moves one 16-byte chunk of a row to global memory, four whole rows per instruction; one unit after the other, so
   // that few values are in flight at a time)
-  {
+  if (it.part >= 0) {  // a piece: O^T as it is, the reference maximum and the sum of each row
+    float* const out = p.parts + ((int64_t)it.part * inner_n + inner) * kPartFloats;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const float l_tot = sum_halves(l_run[u]);
+      if (hh == 0) *reinterpret_cast<f32x2*>(out + kPartRowFloats + ((2 * wave + u) * 32 + l32) * 2) = f32x2{mc[u], l_tot};
+      float* const dst = out + (2 * wave + u) * 4096 + lane * 4;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          *reinterpret_cast<f32x4*>(dst + (db * 4 + g) * 256) =
+              f32x4{oacc[u][db][4 * g], oacc[u][db][4 * g + 1], oacc[u][db][4 * g + 2], oacc[u][db][4 * g + 3]};
+    }
+  } else {
     // (the lane index is made opaque here: the addresses below depend on nothing else, and computed ahead of the loop
     // they would take registers for its whole length)
     int lane_e = lane;
@@ -681,7 +780,8 @@ static hipError_t launch_fwd_t(const FwdParams& p, int num_blocks, hipStream_t s
   return hipGetLastError();
 }
 
-hipError_t launch_fwd(const FwdParams& p, int head_dim, int num_blocks, const TileJob* vjobs, int num_vjobs, hipStream_t stream) {
+hipError_t launch_fwd(const FwdParams& p, int head_dim, int num_blocks, int num_wholes, const TileJob* vjobs, int num_vjobs,
+                      hipStream_t stream) {
   hipError_t e;
   if (head_dim != 128) {
     if ((e = launch_transpose(p.v, p.num_kv_heads, head_dim, 64, vjobs, num_vjobs, p.total_kv_tiles, const_cast<__bf16*>(p.vt),
@@ -694,11 +794,9 @@ hipError_t launch_fwd(const FwdParams& p, int head_dim, int num_blocks, const Ti
   if (attr != hipSuccess) return attr;
   hipLaunchKernelGGL((fwd_pipe_kernel<128>), dim3(persistent_grid(num_blocks)), dim3(256), smem, stream, p, num_blocks);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  // Second pass over the same items, 8 waves of 32 rows: a workgroup returns at once unless its flag is raised, and the
-  // transposed V images it reads are only made if any flag is.
-  if ((e = launch_transpose(p.v, p.num_kv_heads, head_dim, 64, vjobs, num_vjobs, p.total_kv_tiles, const_cast<__bf16*>(p.vt),
-                            stream, p.any_redo)) != hipSuccess) return e;
-  return launch_fwd_t<128, 8>(p, num_blocks, stream);
+  // Second pass over the whole items, 8 waves of 32 rows: a workgroup returns at once unless its flag is raised (the item
+  // is recomputed) or its item was cut (its pieces are put together).
+  return launch_fwd_t<128, 8>(p, num_wholes, stream);
 }
 
 }  // namespace chunk_attn

@@ -21,14 +21,15 @@ struct FwdParams {
   float* lse;
   const __bf16* vt;         // transposed V images [Hkv][total_kv_tiles][D][64]
   const FwdItem* items;
+  const FwdItem* wholes;    // head_dim 128: the items before cutting (= items if none was cut)
+  float* parts;             // head_dim 128: partial results of the pieces, kPartFloats per (slot, inner index)
   int64_t total_kv_tiles;
   int32_t num_q_heads, num_kv_heads, group;  // group = Hq / Hkv
   int32_t heads_per_wg;                      // query heads of one group handled by one workgroup (a power of two)
   int32_t head_splits;                       // group / heads_per_wg
   int32_t total_q;
   float scale_log2;                          // softmax scale * log2(e)
-  int32_t* redo;                             // per-workgroup redo flags of the pipelined forward (null: run every item)
-  int32_t* any_redo;                         // raised together with any redo flag (gates the second pass's preparation)
+  int32_t* redo;                             // head_dim 128: redo flag per (whole item, inner index)
   float ref_limit;                           // log2 growth of the row maximum past the first tile's that raises the flag
   int32_t* taken;                            // 8 block-queue counters of the pipelined forward (zero before the launch)
   unsigned long long* clock_log;             // null, or where the pipelined forward's workgroups log their clocks
@@ -61,6 +62,11 @@ inline int persistent_grid(int64_t blocks) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(blocks, cus));
 }
 constexpr int kBlockQueues = 8;  // counters per kernel that claims its blocks
+constexpr int kCus = 256;        // compute units of an MI355X (plans that must not depend on where they are made)
+// A partial result of one block (256 rows of head_dim 128) in the order in which the kernels hold it: [8 units of 32
+// rows][16 accumulator quarters][64 lanes][4] float32; for the forward then [8 units][32 rows] {reference maximum, sum}.
+constexpr int kPartRowFloats = 8 * 16 * 64 * 4;
+constexpr int kPartFloats = kPartRowFloats + 8 * 32 * 2;
 
 // Events armed by chunk_attn_profile_events for the calling thread (null when disarmed).
 struct ProfileEvents {
@@ -79,14 +85,17 @@ struct BwdArgs {
 };
 
 // Host-side plan of one backward call and the layout of its workspace:
-// [dQ items | dK/dV items | 64-row query-tile jobs | 32-row key-tile jobs] (one uploaded blob), then the
-// LSE and D arrays padded to 64-row tiles and the transposed images of K (32-row tiles).
+// [dQ items | dQ items that were cut | dK/dV items | 64-row query-tile jobs | 32-row key-tile jobs] (one uploaded blob), then
+// the LSE and D arrays padded to 64-row tiles and the transposed images of K (32-row tiles; not for head_dim 128).
 struct BwdPlan {
-  std::vector<DqItem> dq_items;
+  KeySplit split;                // head_dim 128: how the dQ walks are cut
+  std::vector<DqItem> dq_items;  // with the pieces of walks that are cut
+  std::vector<DqItem> dq_cut;    // the whole items that were cut
   std::vector<DkvItem> dkv_items;
   std::vector<TileJob> qjobs, kjobs;
   int64_t q_tiles = 0, kv32_tiles = 0;
-  size_t dq_items_off = 0, dkv_items_off = 0, qjobs_off = 0, kjobs_off = 0, queues_off = 0, blob_bytes = 0;
+  size_t n_dq_cut = 0;
+  size_t dq_items_off = 0, dq_cut_off = 0, dkv_items_off = 0, qjobs_off = 0, kjobs_off = 0, queues_off = 0, blob_bytes = 0;
   size_t lse2p_off = 0, dsp_off = 0, kt_off = 0, total = 0;
   // one-pass backward (head_dim 128): its items and workgroup order travel at the end of the blob; then the per-wave
   // progress counters and the status word (cleared by a kernel on every call) and the float32 dQ tiles
@@ -106,20 +115,21 @@ constexpr size_t kClockLogEntries = 4 * 1024;
 unsigned long long* clock_log(int which);
 hipError_t launch_bwd_fused(const chunk_attn_desc* d, const BwdArgs& a, const BwdPlan& plan, const float* lse2p, const float* dsp,
                             hipStream_t stream);
-// Fills the offsets (and, if with_plan, the schedules) for a validated descriptor.
-void bwd_layout(const chunk_attn_desc* d, BwdPlan& plan, bool with_plan);
+// Fills the offsets (and, if with_plan, the schedules) for a validated descriptor.  `may_cut`: false: no dQ walk is cut.
+void bwd_layout(const chunk_attn_desc* d, BwdPlan& plan, bool with_plan, bool may_cut = true);
 // The host image of the blob at the start of the workspace.
 std::vector<char> bwd_blob(const BwdPlan& plan);
 // Enqueues the backward kernels; the blob must already be on its way to the workspace on `stream`.
 hipError_t launch_bwd(const chunk_attn_desc* d, const BwdArgs& a, const BwdPlan& plan, hipStream_t stream);
 
-// The forward kernels of one call.  `vjobs` (device) lists the 64-row tiles of V whose transposed images p.vt receives:
-// before the kernel for head_dim 64, after the pipelined kernel and only if it raised a redo flag for head_dim 128.
-hipError_t launch_fwd(const FwdParams& p, int head_dim, int num_blocks, const TileJob* vjobs, int num_vjobs, hipStream_t stream);
+// The forward kernels of one call over `num_blocks` blocks (items x inner) cut from `num_wholes`.  `vjobs` (device) lists
+// the 64-row tiles of V whose transposed images p.vt receives (head_dim 64 and 256).
+hipError_t launch_fwd(const FwdParams& p, int head_dim, int num_blocks, int num_wholes, const TileJob* vjobs, int num_vjobs,
+                      hipStream_t stream);
 
 // Transposed tile images (width 64 or 32 rows) of x[rows][num_heads][head_dim]:
-// out[num_heads][total_tiles][head_dim][width].  With a non-null `gate` (device) the kernel does nothing unless *gate != 0.
+// out[num_heads][total_tiles][head_dim][width].
 hipError_t launch_transpose(const __bf16* x, int num_heads, int head_dim, int width, const TileJob* jobs, int num_jobs,
-                            int64_t total_tiles, __bf16* out, hipStream_t stream, const int32_t* gate = nullptr);
+                            int64_t total_tiles, __bf16* out, hipStream_t stream);
 
 }  // namespace chunk_attn

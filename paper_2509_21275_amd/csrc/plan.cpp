@@ -92,11 +92,14 @@ std::vector<FwdItem> plan_fwd(const chunk_attn_desc* d, int tile_rows) {
       it.q_rows = std::min<int32_t>(tile_rows, s.q_len - i0);
       it.kv_row0 = s.kv_start;
       it.n0 = C + i0 + 1;
+      it.keys = s.kv_len;
+      it.part = -1;
       items.push_back(it);
     }
     kv_tile0 += (s.kv_len + 63) / 64;
   }
   by_sequence_then_walk(d, items);
+  for (FwdItem& it : items) it.whole = 1;
   return items;
 }
 
@@ -114,12 +117,128 @@ std::vector<DqItem> plan_dq(const chunk_attn_desc* d, int tile_rows) {
       it.n0 = C + i0 + 1;
       it.kv_tile0 = kv_tile0;
       it.q_slot0 = q_tile0 * 64 + i0;
+      it.keys = s.kv_len;
+      it.part = -1;
       items.push_back(it);
     }
     kv_tile0 += (s.kv_len + 31) / 32;
     q_tile0 += (s.q_len + 63) / 64;
   }
   by_sequence_then_walk(d, items);
+  return items;
+}
+
+// The estimate, in stages (one 32-key step of a workgroup, about a microsecond).  A block costs its walk plus kStart
+// for filling the pipeline and writing its rows; a piece kPart more for its float32 rows (twice the bytes).  The blocks of
+// queue 0 (every eighth one) are dealt, longest first, to an eighth of the compute units as they become free.  Putting
+// the pieces together costs kMerge and the time to read the partial results.  A cut has to win 5 % of the uncut time.
+// Measured, uncut -> cut (head_dim 128, 32/8 heads): 1024 queries on 32768 keys, 128 blocks of 1024 stages in two pieces each:
+// forward 744 -> 472 us + 12 us to put them together, dQ 959 -> 625 + 12 us (not half: 128 busy compute units hold a
+// higher clock than 256); 203 queries on 1704 keys next to 611 short rows: forward 48 -> 28 + 6 us.  Chunks the estimate
+// leaves alone (8192 queries on 32768 keys: 1024 equal blocks) run as before.
+KeySplit choose_key_split(const chunk_attn_desc* d, int tile_rows, int inner, int cus, int64_t max_parts) {
+  constexpr int kStart = 12, kPart = 6, kMerge = 6;
+  constexpr int64_t kMaxBlocks = 1024;     // from four blocks per compute unit on they even out by themselves
+  constexpr int64_t kPartsPerStage = 32;   // partial results (128 KB per block) read per stage
+  struct Walk { int stages, n0; };
+  std::vector<Walk> walks;
+  for (int t = 0; t < d->num_segments; ++t) {
+    const chunk_attn_seg& s = d->segments[t];
+    for (int32_t i0 = 0; i0 < s.q_len; i0 += tile_rows) {
+      const int32_t n0 = s.kv_len - s.q_len + i0 + 1, rows = std::min<int32_t>(tile_rows, s.q_len - i0);
+      walks.push_back(Walk{walk_stages(n0, rows), n0});
+      if ((int64_t)walks.size() * inner >= kMaxBlocks) return KeySplit{};
+    }
+  }
+  int longest = 0;
+  for (const Walk& w : walks) longest = std::max(longest, w.stages);
+  const int workers = std::max(1, cus / 8);
+  std::vector<int> cost;
+  std::vector<int64_t> free_at;
+  auto estimate = [&](KeySplit& k) -> int64_t {
+    cost.clear();
+    k.pieces = k.parts = 0;
+    int64_t block = 0;
+    for (const Walk& w : walks) {
+      const int n = piece_count(w.stages, w.n0, k.target);
+      k.pieces += n;
+      if (n > 1) k.parts += n;
+      for (int i = 0; i < n; ++i) {
+        const int len = (i + 1 < n ? piece_begin(w.stages, n, i + 1) : w.stages) - piece_begin(w.stages, n, i);
+        const int64_t end = block + inner;   // blocks block .. end - 1; those divisible by 8 are queue 0's
+        for (int64_t b = (block + 7) / 8 * 8; b < end; b += 8) cost.push_back(len + kStart + (n > 1 ? kPart : 0));
+        block = end;
+      }
+    }
+    std::sort(cost.begin(), cost.end(), [](int a, int b) { return a > b; });
+    free_at.assign(workers, 0);  // a heap, earliest first
+    int64_t last = 0;
+    for (int c : cost) {
+      std::pop_heap(free_at.begin(), free_at.end(), [](int64_t a, int64_t b) { return a > b; });
+      free_at.back() += c;
+      last = std::max(last, free_at.back());
+      std::push_heap(free_at.begin(), free_at.end(), [](int64_t a, int64_t b) { return a > b; });
+    }
+    return last + (k.parts > 0 ? kMerge + k.parts * inner / kPartsPerStage : 0);
+  };
+  KeySplit best;
+  int64_t best_time = estimate(best);
+  best_time -= best_time / 20;
+  for (int n = 2; n <= 16 && longest / n >= kMinPieceStages; ++n) {
+    KeySplit k;
+    k.target = (longest + n - 1) / n;
+    const int64_t time = estimate(k);
+    if (k.pieces * inner > 2 * kMaxBlocks) break;
+    if (k.parts > 0 && k.parts <= max_parts && time < best_time) {
+      best = k;
+      best_time = time;
+    }
+  }
+  return best;
+}
+
+std::vector<FwdItem> cut_items(std::vector<FwdItem>& wholes, int target) {
+  std::vector<FwdItem> items;
+  int32_t part = 0;
+  for (size_t w = 0; w < wholes.size(); ++w) {
+    FwdItem& whole = wholes[w];
+    const int stages = walk_stages(whole.n0, whole.q_rows), n = piece_count(stages, whole.n0, target);
+    whole.whole = n;
+    whole.part = n > 1 ? part : -1;
+    for (int k = 0; k < n; ++k) {
+      const int b = piece_begin(stages, n, k) * kStageKeys;
+      FwdItem it = whole;
+      it.kv_row0 += b;
+      it.n0 -= b;
+      it.keys = (k + 1 < n ? piece_begin(stages, n, k + 1) * kStageKeys : whole.keys) - b;
+      it.whole = (int32_t)w;
+      it.part = n > 1 ? part++ : -1;
+      items.push_back(it);
+    }
+  }
+  return items;
+}
+
+std::vector<DqItem> cut_items(const std::vector<DqItem>& wholes, int target, std::vector<DqItem>* cut) {
+  std::vector<DqItem> items;
+  int32_t part = 0;
+  for (const DqItem& whole : wholes) {
+    const int stages = walk_stages(whole.n0, whole.q_rows), n = piece_count(stages, whole.n0, target);
+    if (n > 1) {
+      cut->push_back(whole);
+      cut->back().part = part;
+      cut->back().kv_tile0 = n;
+    }
+    for (int k = 0; k < n; ++k) {
+      const int b = piece_begin(stages, n, k) * kStageKeys;
+      DqItem it = whole;
+      it.kv_row0 += b;
+      it.n0 -= b;
+      it.keys = (k + 1 < n ? piece_begin(stages, n, k + 1) * kStageKeys : whole.keys) - b;
+      it.part = n > 1 ? part++ : -1;
+      items.push_back(it);
+    }
+  }
   return items;
 }
 

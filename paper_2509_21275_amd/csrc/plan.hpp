@@ -11,6 +11,12 @@
 
 #include "../../include/chunk_attn.h"
 
+#ifdef __HIPCC__
+#define CHUNK_ATTN_HD __host__ __device__
+#else
+#define CHUNK_ATTN_HD
+#endif
+
 namespace chunk_attn {
 
 // A tile (64 or 32 rows) of a tensor to be transposed by the pre-pass: rows [src_row0, src_row0 + valid_rows).
@@ -27,7 +33,10 @@ struct FwdItem {
   int32_t kv_row0;   // first key row of the segment (global)
   int32_t n0;        // keys visible to the tile's first row: C + i0 + 1; row r sees n0 + r
   int32_t kv_tile0;  // index of the transposed image of the segment's first 64-key tile
-  int32_t pad0, pad1, pad2;
+  // head_dim 128, whose walks over the keys may be cut into pieces (choose_key_split):
+  int32_t keys;      // keys of the item's own range: it sees min(n0 + r, keys) of them
+  int32_t whole;     // a piece: index of the whole item.  A whole item: number of its pieces (1: not cut)
+  int32_t part;      // a piece: its slot among the partial results, -1 if it is the whole item.  A whole item: its first slot
 };
 
 // Work item of the dQ kernel: a tile of consecutive query rows of one segment (as in the forward).
@@ -38,7 +47,9 @@ struct DqItem {
   int32_t n0;        // keys visible to the tile's first row
   int32_t kv_tile0;  // index of the transposed image of the segment's first 32-key tile
   int32_t q_slot0;   // slot of the tile's first row in the padded per-row arrays (LSE, D)
-  int32_t pad0, pad1;
+  int32_t keys;      // head_dim 128: keys of the item's own range, as in FwdItem
+  int32_t part;      // head_dim 128: slot among the partial results, -1 if the item is not a piece (whole items that were cut:
+                     // the first slot; their number of pieces is in kv_tile0)
 };
 
 // Work item of the dK/dV kernel: up to 128 consecutive key rows of one segment and the 32-row query tiles
@@ -97,6 +108,38 @@ int64_t pair_count(const chunk_attn_desc* d);
 // Tiles of `tile_rows` query rows per segment, most work first.
 std::vector<FwdItem> plan_fwd(const chunk_attn_desc* d, int tile_rows);
 std::vector<DqItem> plan_dq(const chunk_attn_desc* d, int tile_rows);
+
+// ---- cutting the walks of query-stationary items over the keys ----
+// A work item walks all keys its rows see, one 32-key stage after the other.  A chunk with few query rows and many keys
+// has fewer items than the chip has compute units, or so few that they do not divide evenly; its walks are then cut into
+// pieces that run on different compute units, write float32 partial results and are put together afterwards.
+constexpr int kStageKeys = 32;
+constexpr int kMinPieceStages = 8;  // below that a piece's start and end cost more than its walk
+// First stage of piece k of a walk of `stages` stages cut into `pieces`.  Even: the kernels take steps two at a time.
+CHUNK_ATTN_HD inline int piece_begin(int stages, int pieces, int k) { return (int)((int64_t)stages * k / pieces) & ~1; }
+// Pieces of a walk whose first row sees n0 keys, for a cut into pieces of about `target` stages (0: none are cut).  The
+// last piece begins with a key that every row sees (the rows of a piece need one to begin with).
+CHUNK_ATTN_HD inline int piece_count(int stages, int n0, int target) {
+  if (target <= 0) return 1;
+  int n = (stages + target - 1) / target;
+  if (n > stages / kMinPieceStages) n = stages / kMinPieceStages;
+  while (n > 1 && piece_begin(stages, n, n - 1) * kStageKeys >= n0) --n;
+  return n < 1 ? 1 : n;
+}
+CHUNK_ATTN_HD inline int walk_stages(int n0, int q_rows) { return (n0 + q_rows - 1 + kStageKeys - 1) / kStageKeys; }
+struct KeySplit {
+  int target = 0;      // argument of piece_count; 0: nothing is cut
+  int64_t pieces = 0;  // items to run (pieces and whole items)
+  int64_t parts = 0;   // pieces among them that write a partial result
+};
+// The cut that ends first by the estimate of plan.cpp, given that each item is run for `inner` (key/value head, head
+// split) pairs on `cus` compute units; at most `max_parts` partial results.
+KeySplit choose_key_split(const chunk_attn_desc* d, int tile_rows, int inner, int cus, int64_t max_parts);
+// The items to run for a cut: pieces of one item are consecutive.  In `wholes`, items that were cut get the number of their
+// pieces and their first slot.
+std::vector<FwdItem> cut_items(std::vector<FwdItem>& wholes, int target);
+// The same for the dQ items; `cut` receives the whole items that were cut.
+std::vector<DqItem> cut_items(const std::vector<DqItem>& wholes, int target, std::vector<DqItem>* cut);
 // `keys` consecutive key rows per item.  `side_by_side` = 0: every item walks its query tiles upwards.  > 0: the number
 // of items of one key/value head that run at the same time; the items of a sequence are then ordered, and given a walk
 // direction each, so that those items read the same query rows at about the same time (see plan.cpp).

@@ -1,0 +1,108 @@
+// Cutting the walks of query-stationary work items over the keys (csrc/plan.hpp): random chunks, every target.
+//   * the pieces of an item are consecutive, begin on even stages, cover its keys once and in order;
+//   * the first key of a piece is visible to the item's first row, every piece but the last is visible whole to every row;
+//   * slots of partial results are handed out in order, to pieces of cut items only;
+//   * choose_key_split counts what cut_items makes, respects its limit, cuts chunks with few long walks and no others.
+#include <cstdio>
+#include <random>
+
+#include "../../paper_2509_21275_amd/csrc/plan.hpp"
+
+#define REQUIRE(x) do { if (!(x)) { std::printf("line %d: %s\n", __LINE__, #x); return 1; } } while (0)
+using namespace chunk_attn;
+
+template <class Item>
+static int check(const std::vector<Item>& wholes, const std::vector<Item>& items, int target, int64_t* parts_out) {
+  size_t x = 0;
+  int32_t part = 0;
+  for (size_t w = 0; w < wholes.size(); ++w) {
+    const Item& whole = wholes[w];
+    const int last_key = whole.kv_row0 + whole.n0 + whole.q_rows - 1;  // behind the keys the last row sees
+    const int n = piece_count(walk_stages(whole.n0, whole.q_rows), whole.n0, target);
+    int next = whole.kv_row0;
+    for (int k = 0; k < n; ++k, ++x) {
+      REQUIRE(x < items.size());
+      const Item& it = items[x];
+      REQUIRE(it.q_row0 == whole.q_row0 && it.q_rows == whole.q_rows);
+      REQUIRE(it.kv_row0 == next && (it.kv_row0 - whole.kv_row0) % (2 * kStageKeys) == 0);
+      REQUIRE(it.n0 == whole.n0 - (it.kv_row0 - whole.kv_row0) && it.n0 >= 1);
+      const int end = it.kv_row0 + std::min(it.n0 + it.q_rows - 1, it.keys);
+      if (k + 1 < n) {
+        REQUIRE(it.keys <= it.n0 && it.keys % kStageKeys == 0 && end == it.kv_row0 + it.keys);
+      } else {
+        REQUIRE(end == last_key);
+      }
+      next = end;
+      REQUIRE(it.part == (n > 1 ? part : -1));
+      if (n > 1) ++part;
+    }
+  }
+  REQUIRE(x == items.size());
+  *parts_out = part;
+  return 0;
+}
+
+static int one(const std::vector<chunk_attn_seg>& segs, int heads, int kv_heads, int expect_cut) {
+  int tq = 0, tkv = 0;
+  for (const auto& s : segs) { tq = s.q_start + s.q_len; tkv = s.kv_start + s.kv_len; }
+  chunk_attn_desc d{heads, kv_heads, 128, tq, tkv, (int)segs.size(), segs.data(), 0.1f};
+  REQUIRE(validate(&d) == CHUNK_ATTN_OK);
+  const int group = heads / kv_heads;
+  int h = 1;
+  while (h * 2 <= 4 && group % (h * 2) == 0) h *= 2;
+  const int rows = 256 / h, inner = kv_heads * (group / h);
+  for (int target : {0, 1, 8, 9, 13, 40, 100000}) {
+    int64_t parts = 0;
+    auto w = plan_fwd(&d, rows);
+    const auto items = cut_items(w, target);
+    if (check(w, items, target, &parts)) return 1;
+    size_t x = 0;
+    for (size_t i = 0; i < w.size(); ++i) {
+      REQUIRE(w[i].whole >= 1 && (w[i].part >= 0) == (w[i].whole > 1) && (w[i].part < 0 || w[i].part == items[x].part));
+      for (int k = 0; k < w[i].whole; ++k, ++x) REQUIRE(items[x].whole == (int)i);
+    }
+    const auto q = plan_dq(&d, rows);
+    std::vector<DqItem> cut;
+    if (check(q, cut_items(q, target, &cut), target, &parts)) return 1;
+    int64_t sum = 0;
+    for (const auto& c : cut) { REQUIRE(c.kv_tile0 > 1 && c.part == sum); sum += c.kv_tile0; }
+    REQUIRE(sum == parts);
+  }
+  for (int64_t limit : {(int64_t)0, (int64_t)3, (int64_t)1 << 40}) {
+    const KeySplit k = choose_key_split(&d, rows, inner, 256, limit);
+    REQUIRE(k.parts <= limit);
+    if (limit == 0) REQUIRE(k.target == 0);
+    if (limit > 3 && expect_cut >= 0) REQUIRE((k.target > 0) == (expect_cut > 0));
+    if (k.target > 0) {
+      int64_t parts = 0;
+      auto w = plan_fwd(&d, rows);
+      const auto items = cut_items(w, k.target);
+      if (check(w, items, k.target, &parts)) return 1;
+      REQUIRE(k.parts == parts && k.pieces == (int64_t)items.size() && k.parts > 0);
+    }
+  }
+  return 0;
+}
+
+int main() {
+  std::mt19937 rng(7);
+  auto uni = [&](int a, int b) { return std::uniform_int_distribution<int>(a, b)(rng); };
+  for (int n = 0; n < 400; ++n) {
+    std::vector<chunk_attn_seg> segs;
+    int tq = 0, tkv = 0;
+    for (int i = uni(1, 6); i > 0; --i) {
+      const int q = uni(0, 1) ? uni(1, 70) : uni(1, 1500), c = uni(0, 2) ? 0 : uni(1, 6000);
+      segs.push_back({tq, q, tkv, c + q});
+      tq += q;
+      tkv += c + q + uni(0, 3);
+    }
+    const int kv = 1 << uni(0, 3), g = uni(1, 8);
+    if (one(segs, kv * g, kv, -1)) { std::printf("case %d\n", n); return 1; }
+  }
+  if (one({{0, 1024, 0, 32768}}, 32, 8, 1)) return 1;    // half as many items as compute units, long walks
+  if (one({{0, 1, 0, 1100}}, 8, 2, 1)) return 1;
+  if (one({{0, 8192, 0, 32768}}, 32, 8, 0)) return 1;    // four items per compute unit
+  if (one({{0, 100, 0, 100}, {100, 60, 100, 60}}, 8, 8, 0)) return 1;  // walks too short to cut
+  std::printf("ok\n");
+  return 0;
+}
