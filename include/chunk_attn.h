@@ -70,7 +70,7 @@ typedef struct {
 typedef struct {
   int32_t num_q_heads;  /* Hq > 0 */
   int32_t num_kv_heads; /* Hkv > 0, divides Hq */
-  int32_t head_dim;     /* 64, 96, 128 or 256 (96 runs as 128 on zero-padded copies in the workspace) */
+  int32_t head_dim;     /* 64, 96, 128 or 256 (a workspace for 96 is sized as one for 128 plus padded copies) */
   int32_t total_q;      /* rows of q / o / d_o / dq */
   int32_t total_kv;     /* rows of k / v / dk / dv */
   int32_t num_segments; /* >= 1 */
@@ -84,9 +84,9 @@ typedef struct {
 
 /*
  * Scratch sizes (bytes) for a descriptor: *fwd_bytes for chunk_attn_fwd, *bwd_bytes for
- * chunk_attn_bwd (the tile schedules, the row sums D_i = <dO_i, O_i>, and transposed
- * tile images of the operands; for head_dim 96 also zero-padded copies of the tensors, 128
- * wide).  Either output pointer may be NULL.  Validates the descriptor.
+ * chunk_attn_bwd (the tile schedules, the row sums D_i = <dO_i, O_i>, transposed tile images
+ * of operands (head_dim 64 and 256) or float32 partial results (96 and 128); for head_dim 96
+ * also room for zero-padded copies of the tensors, 128 wide).  Either output pointer may be NULL.  Validates the descriptor.
  */
 int chunk_attn_workspace_bytes(const chunk_attn_desc* desc, size_t* fwd_bytes, size_t* bwd_bytes);
 

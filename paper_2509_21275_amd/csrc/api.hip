@@ -132,6 +132,22 @@ std::atomic<unsigned long long*> g_clock_log{nullptr};
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
+// ---- head_dim 96 ----
+// The kernels have instantiations of their own for it.  Workspaces are laid out and sized as for head_dim 128 plus padded
+// copies of the operands, which the one-pass backward (head_dim 128 only, chunk_attn_test_set_bwd_mode) still runs on: a
+// head of 96 is a head of 128 whose last 32 columns are zero.  Zero columns of Q and K add nothing to a score, zero columns
+// of V and dO give zero columns of O, dV and (through dS K, dS^T Q) of dQ and dK, and D_i = <dO_i, O_i> is unchanged,
+// so every result is the 96-wide one exactly, with the softmax scale the caller gave.
+constexpr int kNarrowDim = 96, kPaddedDim = 128;
+
+inline bool is_narrow(const chunk_attn_desc* d) { return d->head_dim == kNarrowDim; }
+inline chunk_attn_desc widened(const chunk_attn_desc* d) {
+  chunk_attn_desc w = *d;
+  if (is_narrow(d)) w.head_dim = kPaddedDim;
+  return w;
+}
+inline size_t padded_bytes(int64_t rows, int heads, size_t elem) { return align_up((size_t)rows * heads * kPaddedDim * elem); }
+
 // Forward workspace: [work items | transpose jobs | redo flags (zero)] (uploaded as one blob) then the
 // transposed V images or, for head_dim 128, the partial results of items whose walks are cut.
 struct FwdLayout {
@@ -147,13 +163,14 @@ struct FwdLayout {
 // Scratch memory of the forward that allocates nothing (chunk_attn_fwd_static), below.
 constexpr size_t kStaticScratchBytes = (size_t)16 << 20;
 
-// `may_cut`: false: no walk is cut whatever the chunk.  Partial results take the place of the V images, which head_dim 128
-// does not need, or up to the static forward's scratch memory where the images would be smaller; the cut is a
-// function of the chunk alone, so that every entry point gives the same bits.
-void layout_fwd(const chunk_attn_desc* d, FwdLayout& L, bool with_plan, bool may_cut = true) {
+// `may_cut`: false: no walk is cut whatever the chunk.  Partial results take the place of V images, which the pipelined
+// kernels do not need (the room for them stays part of the size), or up to the static forward's scratch memory where the
+// images would be smaller; the cut is a function of the chunk alone, so that every entry point gives the same bits.
+void layout_fwd(const chunk_attn_desc* desc, FwdLayout& L, bool with_plan, bool may_cut = true) {
+  const chunk_attn_desc wide = widened(desc), *d = &wide;
   const int group = d->num_q_heads / d->num_kv_heads;
   const int inner = d->num_kv_heads * (group / heads_per_wg(group, fwd_waves(d->head_dim)));
-  const bool pipe = d->head_dim == 128;
+  const bool pipe = pipelined(d->head_dim);
   L.tile_rows = tile_rows(group, fwd_waves(d->head_dim)) * fwd_qblocks(d->head_dim);
   L.n_wholes = 0;
   for (int t = 0; t < d->num_segments; ++t) L.n_wholes += (d->segments[t].q_len + L.tile_rows - 1) / L.tile_rows;
@@ -172,20 +189,23 @@ void layout_fwd(const chunk_attn_desc* d, FwdLayout& L, bool with_plan, bool may
     L.vt_off = align_up(L.blob_bytes);
   };
   L.split = KeySplit{};
+  place(L.n_wholes);
+  const size_t uncut_total = L.vt_off + image_bytes;
   if (pipe && may_cut) {
-    place(L.n_wholes);
-    const size_t room = std::max(image_bytes, L.vt_off < kStaticScratchBytes ? kStaticScratchBytes - L.vt_off : 0);
-    L.split = choose_key_split(d, L.tile_rows, inner, kCus, (int64_t)(room / part_bytes));
+    const size_t limit = std::max(uncut_total, kStaticScratchBytes);
+    L.split = choose_key_split(d, L.tile_rows, inner, kCus, (int64_t)((limit - L.vt_off) / part_bytes));
     if (L.split.target > 0) {
       place((size_t)L.split.pieces);
-      // (the longer item list may not push the static forward's total past its limit)
-      if ((size_t)L.split.parts * part_bytes > std::max(image_bytes, L.vt_off < kStaticScratchBytes ? kStaticScratchBytes - L.vt_off : 0))
+      if (L.vt_off + align_up((size_t)L.split.parts * part_bytes) > limit) {  // (the longer item list takes room, too)
         L.split = KeySplit{};
+        place(L.n_wholes);
+      }
     }
   }
-  if (L.split.target == 0) place(L.n_wholes);
   L.blocks = (int64_t)L.n_items * inner;
-  L.total = L.vt_off + std::max(image_bytes, align_up((size_t)L.split.parts * part_bytes));
+  L.total = std::max(uncut_total, L.vt_off + align_up((size_t)L.split.parts * part_bytes));
+  if (is_narrow(desc))  // (as much as with padded copies of Q, K, V and O)
+    L.total = std::max(L.total, uncut_total + 2 * padded_bytes(d->total_q, d->num_q_heads, 2) + 2 * padded_bytes(d->total_kv, d->num_kv_heads, 2));
   if (!with_plan) return;
   L.wholes = plan_fwd(d, L.tile_rows);
   L.items = cut_items(L.wholes, L.split.target);
@@ -310,21 +330,6 @@ __global__ __launch_bounds__(256) void plan_fwd_static_kernel(StaticSegs segs, i
   for (int x = threadIdx.x; x < n_flags; x += 256) flags[x] = 0;
 }
 
-// ---- head_dim 96 ----
-// The kernels tile the head dimension in powers of two.  A head of 96 is run as a head of 128 whose last 32 columns
-// are zero: zero columns of Q and K add nothing to a score, zero columns of V and dO give zero columns of O, dV and (through
-// dS K, dS^T Q) of dQ and dK, and D_i = <dO_i, O_i> is unchanged, so every result is the 96-wide one exactly, with the
-// softmax scale the caller gave.  The padded copies live at the head of the workspace; rows move in 16-byte chunks.
-constexpr int kNarrowDim = 96, kPaddedDim = 128;
-
-inline bool is_narrow(const chunk_attn_desc* d) { return d->head_dim == kNarrowDim; }
-inline chunk_attn_desc widened(const chunk_attn_desc* d) {
-  chunk_attn_desc w = *d;
-  w.head_dim = kPaddedDim;
-  return w;
-}
-inline size_t padded_bytes(int64_t rows, int heads, size_t elem) { return align_up((size_t)rows * heads * kPaddedDim * elem); }
-
 // dst[row][0 .. out_chunks) = src[row][0 .. in_chunks) followed by zero chunks
 __global__ __launch_bounds__(256) void pad_rows_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst, int64_t n_out,
                                                        int in_chunks, int out_chunks) {
@@ -362,21 +367,7 @@ hipError_t unpad_rows(const void* src, void* dst, int64_t rows, size_t elem, hip
   return hipGetLastError();
 }
 
-// Padded copies at the head of a workspace, the widened call's own workspace behind them.
-struct NarrowFwdLayout {
-  size_t q_off, k_off, v_off, o_off, inner_off, total;
-};
-NarrowFwdLayout narrow_fwd_layout(const chunk_attn_desc* d, size_t inner_bytes) {
-  const size_t qb = padded_bytes(d->total_q, d->num_q_heads, 2), kb = padded_bytes(d->total_kv, d->num_kv_heads, 2);
-  NarrowFwdLayout N;
-  N.q_off = 0;
-  N.k_off = qb;
-  N.v_off = N.k_off + kb;
-  N.o_off = N.v_off + kb;
-  N.inner_off = N.o_off + qb;
-  N.total = N.inner_off + inner_bytes;
-  return N;
-}
+// Padded copies at the head of a backward workspace, the widened call's own workspace behind them.
 struct NarrowBwdLayout {
   size_t q_off, k_off, v_off, o_off, do_off, dq_off, dk_off, dv_off, inner_off, total;
 };
@@ -411,11 +402,6 @@ ProfileEvents& profile_events() {
   return ev;
 }
 }  // namespace chunk_attn
-
-namespace {
-int fwd_any(const chunk_attn_desc* desc, const void* q, const void* k, const void* v, void* o, float* lse, void* workspace,
-            size_t workspace_bytes, bool may_cut, void* stream_v);
-}
 
 extern "C" {
 
@@ -453,7 +439,7 @@ int chunk_attn_test_bwd_status_offset(const chunk_attn_desc* desc, size_t* offse
   const int rc = validate(desc);
   if (rc != CHUNK_ATTN_OK) return rc;
   if (!offset) return CHUNK_ATTN_INVALID_ARG;
-  const chunk_attn_desc w = is_narrow(desc) ? widened(desc) : *desc;
+  const chunk_attn_desc w = widened(desc);
   BwdPlan P;
   bwd_layout(&w, P, false);
   *offset = P.fprog_off + P.fprog_bytes - kFusedSinkBytes - 256;
@@ -494,13 +480,13 @@ const char* chunk_attn_strerror(int code) {
 int chunk_attn_workspace_bytes(const chunk_attn_desc* desc, size_t* fwd_bytes, size_t* bwd_bytes) {
   const int rc = validate(desc);
   if (rc != CHUNK_ATTN_OK) return rc;
-  const chunk_attn_desc w = is_narrow(desc) ? widened(desc) : *desc;
   if (fwd_bytes) {
     FwdLayout L;
-    layout_fwd(&w, L, false, !is_narrow(desc));
-    *fwd_bytes = is_narrow(desc) ? narrow_fwd_layout(desc, L.total).total : L.total;
+    layout_fwd(desc, L, false);
+    *fwd_bytes = L.total;
   }
   if (bwd_bytes) {
+    const chunk_attn_desc w = widened(desc);
     BwdPlan P;
     bwd_layout(&w, P, false);
     *bwd_bytes = is_narrow(desc) ? narrow_bwd_layout(desc, P.total).total : P.total;
@@ -510,41 +496,15 @@ int chunk_attn_workspace_bytes(const chunk_attn_desc* desc, size_t* fwd_bytes, s
 
 int chunk_attn_fwd(const chunk_attn_desc* desc, const void* q, const void* k, const void* v, void* o, float* lse,
                    void* workspace, size_t workspace_bytes, void* stream_v) {
-  return fwd_any(desc, q, k, v, o, lse, workspace, workspace_bytes, true, stream_v);
-}
-
-}  // extern "C"
-namespace {
-int fwd_any(const chunk_attn_desc* desc, const void* q, const void* k, const void* v, void* o, float* lse, void* workspace,
-            size_t workspace_bytes, bool may_cut, void* stream_v) {
   const int rc = validate(desc);
   if (rc != CHUNK_ATTN_OK) return rc;
   if (!q || !k || !v || !o || !lse || !workspace) return CHUNK_ATTN_INVALID_ARG;
   if ((reinterpret_cast<uintptr_t>(workspace) & (kAlign - 1)) != 0) return CHUNK_ATTN_INVALID_ARG;
   if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(o) || (reinterpret_cast<uintptr_t>(lse) & 3) != 0)
     return CHUNK_ATTN_INVALID_ARG;  // the kernels move rows in 16-byte pieces
-  if (is_narrow(desc)) {  // run as head_dim 128 on zero-padded copies
-    const chunk_attn_desc w = widened(desc);
-    FwdLayout Lw;
-    layout_fwd(&w, Lw, false, false);
-    const NarrowFwdLayout N = narrow_fwd_layout(desc, Lw.total);
-    if (workspace_bytes < N.total) return CHUNK_ATTN_WORKSPACE_TOO_SMALL;
-    hipStream_t st = static_cast<hipStream_t>(stream_v);
-    char* base = static_cast<char*>(workspace);
-    const int64_t qr = (int64_t)desc->total_q * desc->num_q_heads, kr = (int64_t)desc->total_kv * desc->num_kv_heads;
-    hipError_t pe;
-    if ((pe = pad_rows(q, base + N.q_off, qr, 2, st)) != hipSuccess || (pe = pad_rows(k, base + N.k_off, kr, 2, st)) != hipSuccess ||
-        (pe = pad_rows(v, base + N.v_off, kr, 2, st)) != hipSuccess)
-      return hip_fail(pe, "padding launch");
-    const int r = fwd_any(&w, base + N.q_off, base + N.k_off, base + N.v_off, base + N.o_off, lse, base + N.inner_off,
-                          workspace_bytes - N.inner_off, false, stream_v);
-    if (r != CHUNK_ATTN_OK) return r;
-    if ((pe = unpad_rows(base + N.o_off, o, qr, 2, st)) != hipSuccess) return hip_fail(pe, "unpadding launch");
-    return CHUNK_ATTN_OK;
-  }
   FwdLayout L;
-  layout_fwd(desc, L, true, may_cut);
-  if (workspace_bytes < L.total && may_cut) layout_fwd(desc, L, true, false);  // too small for partial results: nothing is cut
+  layout_fwd(desc, L, true);
+  if (workspace_bytes < L.total) layout_fwd(desc, L, true, false);  // too small for partial results: nothing is cut
   if (workspace_bytes < L.total) return CHUNK_ATTN_WORKSPACE_TOO_SMALL;
   hipStream_t stream = static_cast<hipStream_t>(stream_v);
   char* ws = static_cast<char*>(workspace);
@@ -575,7 +535,7 @@ int fwd_any(const chunk_attn_desc* desc, const void* q, const void* k, const voi
   p.head_splits = p.group / p.heads_per_wg;
   p.total_q = desc->total_q;
   p.scale_log2 = desc->softmax_scale * 1.4426950408889634f;
-  p.redo = desc->head_dim == 128 ? reinterpret_cast<int32_t*>(ws + L.flags_off) : nullptr;
+  p.redo = pipelined(desc->head_dim) ? reinterpret_cast<int32_t*>(ws + L.flags_off) : nullptr;
   p.taken = reinterpret_cast<int32_t*>(ws + L.flags_off) + L.whole_blocks;
   p.clock_log = clock_log(0);
   p.ref_limit = g_fwd_rescale_limit.load();
@@ -591,10 +551,6 @@ int fwd_any(const chunk_attn_desc* desc, const void* q, const void* k, const voi
   return CHUNK_ATTN_OK;
 }
 
-}  // namespace
-
-extern "C" {
-
 int chunk_attn_fwd_static(const chunk_attn_desc* desc, const void* q, const void* k, const void* v, void* o, float* lse,
                           void* stream_v) {
   const int rc = validate(desc);
@@ -602,35 +558,19 @@ int chunk_attn_fwd_static(const chunk_attn_desc* desc, const void* q, const void
   if (!q || !k || !v || !o || !lse) return CHUNK_ATTN_INVALID_ARG;
   if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(o) || (reinterpret_cast<uintptr_t>(lse) & 3) != 0)
     return CHUNK_ATTN_INVALID_ARG;
-  const chunk_attn_desc wide = is_narrow(desc) ? widened(desc) : *desc;
   FwdLayout L;
-  layout_fwd(&wide, L, false, !is_narrow(desc));
-  const NarrowFwdLayout N = is_narrow(desc) ? narrow_fwd_layout(desc, L.total) : NarrowFwdLayout{0, 0, 0, 0, 0, L.total};
-  if (desc->num_segments > kStaticMaxSegments || N.total > kStaticScratchBytes || L.blocks > 0x7fffffff)
+  layout_fwd(desc, L, false);
+  if (desc->num_segments > kStaticMaxSegments || L.total > kStaticScratchBytes || L.blocks > 0x7fffffff)
     return CHUNK_ATTN_TOO_LARGE;
   hipStream_t stream = static_cast<hipStream_t>(stream_v);
   char* ws = nullptr;
   hipError_t e = static_scratch(&ws);
   if (e != hipSuccess) return hip_fail(e, "address of the static scratch buffer");
-  void* o_user = o;
-  const int64_t qr = (int64_t)desc->total_q * desc->num_q_heads, kr = (int64_t)desc->total_kv * desc->num_kv_heads;
-  if (is_narrow(desc)) {  // zero-padded copies at the head of the scratch array, the head_dim 128 forward behind them
-    if ((e = pad_rows(q, ws + N.q_off, qr, 2, stream)) != hipSuccess || (e = pad_rows(k, ws + N.k_off, kr, 2, stream)) != hipSuccess ||
-        (e = pad_rows(v, ws + N.v_off, kr, 2, stream)) != hipSuccess)
-      return hip_fail(e, "padding launch");
-    q = ws + N.q_off;
-    k = ws + N.k_off;
-    v = ws + N.v_off;
-    o = ws + N.o_off;
-    ws += N.inner_off;
-    desc = &wide;
-  }
-
   StaticSegs segs;
   for (int t = 0; t < desc->num_segments; ++t) segs.seg[t] = desc->segments[t];
   hipLaunchKernelGGL(plan_fwd_static_kernel, dim3(1), dim3(256), 0, stream, segs, desc->num_segments, L.tile_rows,
                      reinterpret_cast<FwdItem*>(ws + L.wholes_off), (int)L.n_wholes, reinterpret_cast<FwdItem*>(ws),
-                     L.split.target, reinterpret_cast<TileJob*>(ws + L.jobs_off), desc->head_dim == 128 ? 0 : (int)L.kv_tiles,
+                     L.split.target, reinterpret_cast<TileJob*>(ws + L.jobs_off), pipelined(desc->head_dim) ? 0 : (int)L.kv_tiles,
                      reinterpret_cast<int32_t*>(ws + L.flags_off), (int)L.whole_blocks + kBlockQueues);
   if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "schedule kernel launch");
 
@@ -652,14 +592,13 @@ int chunk_attn_fwd_static(const chunk_attn_desc* desc, const void* q, const void
   p.head_splits = p.group / p.heads_per_wg;
   p.total_q = desc->total_q;
   p.scale_log2 = desc->softmax_scale * 1.4426950408889634f;
-  p.redo = desc->head_dim == 128 ? reinterpret_cast<int32_t*>(ws + L.flags_off) : nullptr;
+  p.redo = pipelined(desc->head_dim) ? reinterpret_cast<int32_t*>(ws + L.flags_off) : nullptr;
   p.taken = reinterpret_cast<int32_t*>(ws + L.flags_off) + L.whole_blocks;
   p.clock_log = clock_log(0);
   p.ref_limit = g_fwd_rescale_limit.load();
   e = launch_fwd(p, desc->head_dim, (int)L.blocks, (int)L.whole_blocks, reinterpret_cast<const TileJob*>(ws + L.jobs_off),
                  (int)L.kv_tiles, stream);
   if (e != hipSuccess) return hip_fail(e, "forward launch");
-  if (o != o_user && (e = unpad_rows(o, o_user, qr, 2, stream)) != hipSuccess) return hip_fail(e, "unpadding launch");
   return CHUNK_ATTN_OK;
 }
 
@@ -674,12 +613,14 @@ int bwd_any(const chunk_attn_desc* desc, const void* q, const void* k, const voi
   if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(o) || !aligned16(d_o) || !aligned16(dq) || !aligned16(dk) ||
       !aligned16(dv) || (reinterpret_cast<uintptr_t>(lse) & 3) != 0)
     return CHUNK_ATTN_INVALID_ARG;  // the kernels move rows in 16-byte pieces
-  if (is_narrow(desc)) {  // run as head_dim 128 on zero-padded copies
-    const chunk_attn_desc w = widened(desc);
-    BwdPlan Pw;
-    bwd_layout(&w, Pw, false, false);
-    const NarrowBwdLayout N = narrow_bwd_layout(desc, Pw.total);
-    if (workspace_bytes < N.total) return CHUNK_ATTN_WORKSPACE_TOO_SMALL;
+  const chunk_attn_desc w = widened(desc);
+  BwdPlan P;
+  auto needed = [&]() { return is_narrow(desc) ? narrow_bwd_layout(desc, P.total).total : P.total; };
+  bwd_layout(&w, P, true);
+  if (workspace_bytes < needed()) bwd_layout(&w, P, true, false);  // too small for a cut's item lists: nothing is cut
+  if (workspace_bytes < needed()) return CHUNK_ATTN_WORKSPACE_TOO_SMALL;
+  if (is_narrow(desc) && P.fused) {  // the one-pass backward: run as head_dim 128 on zero-padded copies
+    const NarrowBwdLayout N = narrow_bwd_layout(desc, P.total);
     hipStream_t st = static_cast<hipStream_t>(stream_v);
     char* base = static_cast<char*>(workspace);
     const int64_t qr = (int64_t)desc->total_q * desc->num_q_heads, kr = (int64_t)desc->total_kv * desc->num_kv_heads;
@@ -702,10 +643,6 @@ int bwd_any(const chunk_attn_desc* desc, const void* q, const void* k, const voi
       return hip_fail(pe, "unpadding launch");
     return CHUNK_ATTN_OK;
   }
-  BwdPlan P;
-  bwd_layout(desc, P, true);
-  if (workspace_bytes < P.total) bwd_layout(desc, P, true, false);  // too small for a cut's item lists: nothing is cut
-  if (workspace_bytes < P.total) return CHUNK_ATTN_WORKSPACE_TOO_SMALL;
   hipStream_t stream = static_cast<hipStream_t>(stream_v);
   BwdArgs a;
   a.q = static_cast<const __bf16*>(q);

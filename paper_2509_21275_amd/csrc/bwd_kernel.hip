@@ -36,15 +36,15 @@ constexpr float kLog2e = 1.4426950408889634f;
 #endif
 
 // ------------------------------------------------------------------------------------------------
-// bwd_pre: one workgroup per (64-row query tile, head); D / 8 threads per row, one 16-byte chunk of O and of dO each, so
-// that a wave reads whole rows (the kernel is bound by memory: it reads O and dO once).
+// bwd_pre: one workgroup per (64-row query tile, head); D / 8 threads per row (head_dim 96: 16, of which 12 read), one
+// 16-byte chunk of O and of dO each, so that a wave reads whole rows (the kernel is bound by memory: it reads O and dO once).
 // ------------------------------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(256) void bwd_pre_kernel(const __bf16* __restrict__ o, const __bf16* __restrict__ d_o,
                                                       const float* __restrict__ lse, const TileJob* __restrict__ jobs,
                                                       int64_t total_q_tiles, int total_q, int num_q_heads,
                                                       float* __restrict__ lse2p, float* __restrict__ dsp) {
-  constexpr int TPR = D / 8;         // threads per row
+  constexpr int TPR = D == 96 ? 16 : D / 8;  // threads per row
   constexpr int RPP = 256 / TPR;     // rows per pass
   const int head = blockIdx.x % num_q_heads;
   const TileJob job = jobs[blockIdx.x / num_q_heads];
@@ -54,7 +54,7 @@ __global__ __launch_bounds__(256) void bwd_pre_kernel(const __bf16* __restrict__
     const int r = pass * RPP + threadIdx.x / TPR;
     const bool valid = r < job.valid_rows;
     float acc = 0.f;
-    if (valid) {
+    if (valid && part < D / 8) {
       const int64_t base = ((int64_t)(job.src_row0 + r) * num_q_heads + head) * D + part * 8;
       const bf16x8 a = *reinterpret_cast<const bf16x8*>(o + base);
       const bf16x8 b = *reinterpret_cast<const bf16x8*>(d_o + base);
@@ -680,7 +680,7 @@ static_assert(DkvLdsOrder<0, 16, 8>::wait(0) == 6 && DkvLdsOrder<0, 16, 8>::wait
               DkvLdsOrder<0, 16, 8>::wait(7) == 4 && DkvLdsOrder<0, 16, 8>::wait(8) == 3 && DkvLdsOrder<0, 16, 8>::wait(15) == 6, "role A");
 
 // ------------------------------------------------------------------------------------------------
-// bwd_dkv_pipe (head_dim 128)
+// bwd_dkv_pipe (head_dim 128 and 96)
 //
 // Same work split as bwd_dkv_kernel, laid out for one wave per SIMD: a workgroup of 4 waves covers 128
 // keys; each wave owns 64 keys (two 32-key blocks), waves 0, 1 in role A (S, P, dV^T), waves 2, 3 in role B
@@ -691,7 +691,7 @@ static_assert(DkvLdsOrder<0, 16, 8>::wait(0) == 6 && DkvLdsOrder<0, 16, 8>::wait
 //     role B:  dP(g-2) = dO V^T       dS(g-3) = P(g-3) (dP(g-3) - D)      dK^T += Q^T dS(g-4)
 // (stage n = the n-th (head, 32-row query tile) of the workgroup's walk).  The three pieces of a step are
 // independent of each other.  A wave issues at most one instruction every four cycles and an MFMA holds the
-// matrix pipe for 32, so the step is laid out instruction by instruction: 16 mini-steps of one operand
+// matrix pipe for 32, so the step is laid out instruction by instruction: 16 (head_dim 96: 12) mini-steps of one operand
 // fragment and the two MFMAs it feeds, each MFMA followed by its share of everything else (the vector work
 // of one score, an LDS read, a copy), so that the next MFMA finds the pipe just free.  Fragments are fetched
 // four mini-steps ahead (the first four of a step before the barrier that ends the previous one).  Role A
@@ -700,6 +700,9 @@ static_assert(DkvLdsOrder<0, 16, 8>::wait(0) == 6 && DkvLdsOrder<0, 16, 8>::wait
 // A step runs the same straight-line code whatever the stage.  Stages outside the walk compute on zeros or
 // on stale (finite) data and contribute nothing: LDS starts zeroed, and role A starts the S accumulation of
 // such a stage from -inf (P = 0), just as it does for the entries a query does not see.
+// head_dim 96 is 12 mini-steps of the same kind with the same vector work, which is why a step gets shorter by less than the
+// quarter its MFMAs do.  Against zero-padded copies run as head_dim 128, 8192 queries on 32768 keys, 32/8 heads: this kernel
+// 5.95 -> 5.56 ms, dQ 3.78 -> 3.33, forward 2.80 -> 2.53, and twelve padding passes of 20 us less.
 // S and dP are kept in vector registers, where the vector work reads them directly; the compiler would keep
 // every MFMA result of a kernel this size in accumulation registers (one extra move per element), so those
 // MFMAs are written as opaque instructions.
@@ -718,6 +721,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(DkvParams p, int n
   constexpr int AHEAD = 4;             // fragments in flight
   constexpr int PS = 2 * 4 * 64 * 8;   // elements of one P hand-over slot: 2 wave pairs x 4 fragments x 64 lanes x 8
   constexpr int CH = BM * KC;          // 16-byte chunks per operand tile
+  constexpr int RING = NF % 8 == 0 ? 8 : 6;  // registers of the fragment ring: a step starts where the ring does
   constexpr int NP = CH / 64;          // 64-slot pieces per tile
   // global->LDS copies per wave and stage: the 2 NP operand pieces and the two sets of row values (LSE, D) are dealt
   // unevenly, because issuing a copy costs a wave about as long as an MFMA and role A (the exponentials) is the one the
@@ -725,7 +729,9 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(DkvParams p, int n
   constexpr int PER_A = 2, PER_B = (2 * NP - 2 * PER_A) / 2;  // pieces per wave
   constexpr int CPS_A = PER_A + 1, CPS_B = PER_B;              // copies per wave and stage
   constexpr int RV = 64;               // floats per slot of the LSE / D rows (32 used; a whole wave copies them)
-  static_assert(D == 128 && NF == 16 && PER_B == 6, "the mini-step schedule below is written for head_dim 128");
+  constexpr int VEC0 = NF - 8;         // first mini-step of the vector work (one pair of scores per MFMA)
+  constexpr int BOOK = NF - 2;         // mini-step of the bookkeeping, behind the last copy
+  static_assert(PER_B % 2 == 0 && NF % RING == 0 && RING > AHEAD && VEC0 >= 4 && 3 + 2 * (PER_B - 1) < BOOK, "the schedule of a step");
 
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   lds_bf16* const L = (lds_bf16*)smem;
@@ -788,12 +794,12 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(DkvParams p, int n
   const int n_iter = nqt * G;
 
   // ---- staging: copy i of a role A wave is piece `pair` of Q (i = 0) or of dO (i = 1), the first of the two waves
-  // also copies the stage's LSE rows, the second its D rows; copy i of a role B wave is piece 2 + 2 (i % 3) + pair of Q
-  // (i < 3) or of dO.  Past the last stage the last one is copied again (into a slot nobody reads any more), so
+  // also copies the stage's LSE rows, the second its D rows; copy i of a role B wave is piece 2 + 2 (i % h) + pair of Q
+  // (i < h = PER_B / 2) or of dO.  Past the last stage the last one is copied again (into a slot nobody reads any more), so
   // that every step issues the same number of copies. ----
   // byte offset of the lane's chunk of copy i from the tile's first row, for a full tile and for the segment's
   // last tile (rows past the last query repeat it; their P is 0)
-  auto piece_in_tile = [&](int i) { return role == 0 ? pair : 2 + 2 * (i % 3) + pair; };
+  auto piece_in_tile = [&](int i) { return role == 0 ? pair : 2 + 2 * (i % (PER_B / 2)) + pair; };
   unsigned v_full[PER_B], v_last[PER_B];
   {
     const int last_row = it.q_len - 1 - (it.n_qt - 1) * BM;
@@ -929,7 +935,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(DkvParams p, int n
 #pragma unroll
           for (int i = 0; i < 8; ++i) f[b][kb][ks][i] = (__bf16)0.0f;
       }
-    bf16x8 fr[8];  // ring of operand fragments
+    bf16x8 fr[RING];  // ring of operand fragments
 
     // byte addresses of this lane's operand reads inside slot 0
     const unsigned t_lo0 = lds_addr(t_tile + t_off[0]), t_hi0 = lds_addr(t_tile + t_off[1]);
@@ -1035,21 +1041,21 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(DkvParams p, int n
           static_assert(lgkm >= 0 && lgkm <= 15, "lgkmcnt is a 4-bit counter");
           if constexpr (m == 4) {
             if (ROLE == 0)
-              asm volatile("s_waitcnt lgkmcnt(%5)" : "+v"(fr[m & 7]), "+v"(r4[0]), "+v"(r4[1]), "+v"(r4[2]), "+v"(r4[3]) : "n"(lgkm));
+              asm volatile("s_waitcnt lgkmcnt(%5)" : "+v"(fr[m % RING]), "+v"(r4[0]), "+v"(r4[1]), "+v"(r4[2]), "+v"(r4[3]) : "n"(lgkm));
             else
-              asm volatile("s_waitcnt lgkmcnt(%9)" : "+v"(fr[m & 7]), "+v"(r4[0]), "+v"(r4[1]), "+v"(r4[2]), "+v"(r4[3]),
+              asm volatile("s_waitcnt lgkmcnt(%9)" : "+v"(fr[m % RING]), "+v"(r4[0]), "+v"(r4[1]), "+v"(r4[2]), "+v"(r4[3]),
                            "+v"(ph[0][0]), "+v"(ph[0][1]), "+v"(ph[1][0]), "+v"(ph[1][1]) : "n"(lgkm));
           } else {
-            asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(fr[m & 7]) : "n"(lgkm));
+            asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(fr[m % RING]) : "n"(lgkm));
           }
         }
         {  // read the fragment of mini-step m + AHEAD (past the end: the next step's first transposed fragments)
           constexpr int mm = m + AHEAD;
-          if constexpr (mm < 2 * DB) fr[mm & 7] = load_t(t_lo, t_hi, std::integral_constant<int, mm>{});
-          else if constexpr (mm < NF) fr[mm & 7] = load_a(a_ev, a_od, std::integral_constant<int, mm - 2 * DB>{});
-          else fr[mm & 7] = load_t(n_lo, n_hi, std::integral_constant<int, mm - NF>{});
+          if constexpr (mm < 2 * DB) fr[mm % RING] = load_t(t_lo, t_hi, std::integral_constant<int, mm>{});
+          else if constexpr (mm < NF) fr[mm % RING] = load_a(a_ev, a_od, std::integral_constant<int, mm - 2 * DB>{});
+          else fr[mm % RING] = load_t(n_lo, n_hi, std::integral_constant<int, mm - NF>{});
         }
-        const bf16x8 fa = fr[m & 7];
+        const bf16x8 fa = fr[m % RING];
         // S / dP live in vector registers (the vector work reads them directly) and K / V fragments in accumulation
         // registers; written as opaque instructions since the compiler keeps every MFMA result of a kernel with more
         // than 256 registers in accumulation registers.  Their results are first read one step later.
@@ -1096,7 +1102,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(DkvParams p, int n
         // spread over the whole step (2.1 % slower), one score per MFMA from mini-step 4 on and two in the last four
         // mini-steps (0.5 - 1 % slower) and everything in the last four mini-steps (9.6 % slower); for role B against
         // the second of these (1.2 % slower).
-        if constexpr (m >= 8) vec_pair(std::integral_constant<int, 2 * (m - 8)>{});
+        if constexpr (m >= VEC0) vec_pair(std::integral_constant<int, 2 * (m - VEC0)>{});
         __builtin_amdgcn_sched_barrier(0);
         mma(c1);
         if constexpr (ROLE == 0 && m < 2) {  // (E1)
@@ -1104,8 +1110,8 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(DkvParams p, int n
           r4[2 * m + 1] = lds_asm_read16f<64 * m + 32>(ra);
         }
         if (m >= 3 && m < 3 + 2 * PIECES && ((m - 3) & 1) == 0) dma_piece((m - 3) >> 1);
-        if constexpr (m >= 8) vec_pair(std::integral_constant<int, 2 * (m - 8) + 1>{});
-        if constexpr (m == 14) {  // bookkeeping for the next step (the copies of this step have been issued)
+        if constexpr (m >= VEC0) vec_pair(std::integral_constant<int, 2 * (m - VEC0) + 1>{});
+        if constexpr (m == BOOK) {  // bookkeeping for the next step (the copies of this step have been issued)
           dma_advance();
           sA = sA == NS - 1 ? 0 : sA + 1;
           if (ROLE == 0 && --s_heads == 0) {
@@ -1177,7 +1183,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(DkvParams p, int n
 }
 
 // ------------------------------------------------------------------------------------------------
-// bwd_dq_pipe (head_dim 128)
+// bwd_dq_pipe (head_dim 128 and 96)
 //
 // The dQ kernel in the style of bwd_dkv_pipe_kernel: one wave per SIMD, a workgroup of 4 waves, each wave
 // owning two 32-row query blocks ("units": the workgroup's 8 units are the same (head, row block) pairs the
@@ -1185,7 +1191,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(DkvParams p, int n
 // the t-th 32-key tile of the segment; in step t a wave runs
 //     dP^T(t) = V(t) dO^T        S^T(t+1) = K(t+1) Q^T        dQ^T += K(t-1)^T dS^T(t-1)      (matrix pipe)
 //     P^T(t) = exp2(S^T(t) c - LSE)  and, once dP^T(t) is complete,  dS^T(t) = P^T(t) (dP^T(t) - D)   (vector)
-// as 24 mini-steps of one LDS operand fragment and the two MFMAs it feeds (one per unit), each MFMA followed
+// as 24 (head_dim 96: 18) mini-steps of one LDS operand fragment and the two MFMAs it feeds (one per unit), each MFMA followed
 // by its share of the vector work.  K^T is read from the K tile itself with the LDS transpose read (tiles
 // are stored chunk-major as in the dK/dV kernels), so no transposed image of K is needed.  K and V tiles
 // live in a ring of DIST + 3 slots.  Steps whose tile needs the causal mask (the last one or two of the
@@ -1203,9 +1209,18 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_pipe_kernel(DqParams p, int num
   constexpr int NS = DIST + 3; // ring slots: stages t - 1 .. t + 1 in use, t + 2 .. t + 1 + DIST on their way
   constexpr int NF = 2 * DK + 2 * DB;  // operand fragments (mini-steps) per step: V rows, K rows, K^T
   constexpr int AHEAD = 4;             // fragments in flight
+  constexpr int RING = NF % 8 == 0 ? 8 : 6;  // registers of the fragment ring: a step starts where the ring does
   constexpr int NP = BN * KC / 64;     // 64-slot pieces per tile
   constexpr int PER = 2 * NP / NW;     // global->LDS copies per wave and stage
-  static_assert(D == 128 && NF == 24 && PER == 4, "the mini-step schedule below is written for head_dim 128");
+  constexpr int BOOK = 12;             // mini-step of the bookkeeping, behind the last copy
+  // Vector work of a step: the 16 pairs' exponentials in mini-steps EXP0 .. EXP1 - 1, their dS from DS0 on (dP^T is
+  // complete two mini-steps before), spread evenly.  head_dim 128: one pair of exponentials per mini-step from 6 on (the first
+  // six are left to the MFMAs alone: measured 1 % faster than starting with 0, and faster than starting with 2, 4 or
+  // 8), dS one pair per mini-step from 10 on and two in the last two.
+  constexpr int EXP0 = D == 128 ? 6 : 4, EXP1 = D == 128 ? 22 : 16, DS0 = DK + 2;
+  auto exp_done = [](int m) constexpr { return spread(16, EXP0, EXP1, m); };
+  auto ds_done = [](int m) constexpr { return D == 128 && m < 22 ? spread(12, DS0, 22, m) : D == 128 ? 12 + 2 * (m - 21) : spread(16, DS0, NF, m); };
+  static_assert(2 * NP % NW == 0 && NF % RING == 0 && RING > AHEAD && 3 + 2 * (PER - 1) < BOOK && BOOK < NF, "the schedule of a step");
 
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   lds_bf16* const L = (lds_bf16*)smem;
@@ -1280,10 +1295,11 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_pipe_kernel(DqParams p, int num
   int d_t = 0, d_slot = 0;   // stage to copy next (clamped to the last one) and its slot
   int64_t d_off = 0;         // element offset of its first row
   auto dma_piece = [&](int i) __attribute__((always_inline)) {
-    const int piece = i * NW + wave;  // wave-uniform; i < NP / NW: a piece of K, else of V
+    const int piece = i * NW + wave;  // wave-uniform; the first NP are pieces of K, the others of V
+    const bool of_k = NP % NW == 0 ? i < NP / NW : piece < NP;
     const unsigned voff = d_t == nt - 1 ? v_last[i] : v_full[i];
-    const char* base = reinterpret_cast<const char*>((i < NP / NW ? Kg : Vg) + d_off);
-    lds_bf16* dst = L + (i < NP / NW ? K_OFF + piece * 512 : V_OFF + (piece - NP) * 512) + d_slot * KT;
+    const char* base = reinterpret_cast<const char*>((of_k ? Kg : Vg) + d_off);
+    lds_bf16* dst = L + (of_k ? K_OFF + piece * 512 : V_OFF + (piece - NP) * 512) + d_slot * KT;
     dma16(base + voff, dst);
   };
   auto dma_advance = [&]() __attribute__((always_inline)) {
@@ -1375,14 +1391,16 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_pipe_kernel(DqParams p, int num
 #pragma unroll
         for (int i = 0; i < 8; ++i) f[b][u][ks][i] = (__bf16)0.0f;
   const float c = p.scale_log2;
-  bf16x8 fr[8];  // ring of operand fragments
+  bf16x8 fr[RING];  // ring of operand fragments
 
   // S^T(0) = K(0) Q^T, then the first fragments of step 0 (V rows of stage 0)
   {
     bf16x8 a[DK];
     static_for<0, DK>([&](auto ks_c) __attribute__((always_inline)) { a[decltype(ks_c)::value] = load_rows(k_ev0, k_od0, ks_c); });
     static_for<0, AHEAD>([&](auto ks_c) __attribute__((always_inline)) { fr[decltype(ks_c)::value] = load_rows(v_ev0, v_od0, ks_c); });
-    asm volatile("s_waitcnt lgkmcnt(%8)" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]) : "n"(AHEAD));
+    asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(AHEAD) : "memory");
+#pragma unroll
+    for (int ks = 0; ks < DK; ++ks) asm volatile("" : "+v"(a[ks]));  // (after the wait, in this order)
 #pragma unroll
     for (int ks = 0; ks < DK; ++ks)
 #pragma unroll
@@ -1393,13 +1411,8 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_pipe_kernel(DqParams p, int num
     mfma_settle();
   }
 
-  // In program order mini-step m reads fragment m + 4: one instruction for the rows fragments (0 .. 15 of this step,
-  // 0 .. 3 of the next), two for the transposed ones (16 .. 23).  lgkm_wait(m) = number of LDS instructions between the
-  // read of fragment m and the start of mini-step m, where the wait stands.
-  auto lgkm_wait = [](int m) {
-    constexpr int tab[24] = {3, 3, 3, 3, 3, 3, 3, 3, 3, 3, 3, 3, 3, 4, 5, 6, 6, 6, 6, 6, 6, 5, 4, 3};
-    return tab[m];
-  };
+  // In program order mini-step m reads fragment m + 4: one instruction for the rows fragments (0 .. 2 DK - 1 of this step,
+  // 0 .. 3 of the next), two for the transposed ones.
   int sV = 0;  // slot of stage t
   auto step = [&](int t, f32x16 (&cur)[2], f32x16 (&nxt)[2], bf16x8 (&f_old)[2][2], bf16x8 (&f_new)[2][2],
                   auto masked_c) __attribute__((always_inline)) {
@@ -1440,15 +1453,15 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_pipe_kernel(DqParams p, int num
     __builtin_amdgcn_sched_barrier(0);
     static_for<0, NF>([&](auto m_c) __attribute__((always_inline)) {
       constexpr int m = decltype(m_c)::value;
-      asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(fr[m & 7]) : "n"(lgkm_wait(m)));
+      asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(fr[m % RING]) : "n"(fragment_wait(NF, 2 * DK, NF, m)));
       {  // read the fragment of mini-step m + AHEAD (past the end: the next step's first V fragments)
         constexpr int mm = m + AHEAD;
-        if constexpr (mm < DK) fr[mm & 7] = load_rows(v_ev, v_od, std::integral_constant<int, mm>{});
-        else if constexpr (mm < 2 * DK) fr[mm & 7] = load_rows(k_ev, k_od, std::integral_constant<int, mm - DK>{});
-        else if constexpr (mm < NF) fr[mm & 7] = load_t(t_lo, t_hi, std::integral_constant<int, mm - 2 * DK>{});
-        else fr[mm & 7] = load_rows(n_ev, n_od, std::integral_constant<int, mm - NF>{});
+        if constexpr (mm < DK) fr[mm % RING] = load_rows(v_ev, v_od, std::integral_constant<int, mm>{});
+        else if constexpr (mm < 2 * DK) fr[mm % RING] = load_rows(k_ev, k_od, std::integral_constant<int, mm - DK>{});
+        else if constexpr (mm < NF) fr[mm % RING] = load_t(t_lo, t_hi, std::integral_constant<int, mm - 2 * DK>{});
+        else fr[mm % RING] = load_rows(n_ev, n_od, std::integral_constant<int, mm - NF>{});
       }
-      const bf16x8 fa = fr[m & 7];
+      const bf16x8 fa = fr[m % RING];
       // dP^T and S^T are kept in vector registers, the Q / dO fragments in accumulation registers (opaque MFMAs, see
       // bwd_dkv_pipe_kernel); dP^T is first read three mini-steps after its last MFMA, S^T in the next step
       auto mma = [&](auto u_c) __attribute__((always_inline)) {
@@ -1473,19 +1486,26 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_pipe_kernel(DqParams p, int num
       };
       constexpr std::integral_constant<int, 0> c0{};
       constexpr std::integral_constant<int, 1> c1{};
-      // exponentials: pair j in mini-step 6 + j (the first six mini-steps are left to the MFMAs alone: measured 1 %
-      // faster than starting with mini-step 0, and faster than starting with 2, 4 or 8); dS: pairs 0 .. 11 in
-      // mini-steps 10 .. 21, then two per mini-step
+      // scores e0 .. e1 - 1 (two per pair) and pairs s0 .. s1 - 1 of dS belong to this mini-step, the first half of each
+      // after its first MFMA
+      constexpr int e0 = 2 * exp_done(m - 1), e1 = 2 * exp_done(m), em = e0 + (e1 - e0 + 1) / 2;
+      constexpr int s0 = ds_done(m - 1), s1 = ds_done(m), sm = s0 + (s1 - s0 + 1) / 2;
+      static_assert(s1 <= exp_done(m - 1), "a pair's exponentials come before its dS");
+      auto exp_range = [&](auto lo_c, auto hi_c) __attribute__((always_inline)) {
+        static_for<decltype(lo_c)::value, decltype(hi_c)::value>([&](auto i_c) __attribute__((always_inline)) {
+          constexpr int i = decltype(i_c)::value;
+          exp_half(std::integral_constant<int, i / 2>{}, std::integral_constant<int, i % 2>{});
+        });
+      };
       mma(c0);
-      if constexpr (m >= 6 && m < 22) exp_half(std::integral_constant<int, m - 6>{}, c0);
-      if constexpr (m >= 10 && m < 22) ds_pair(std::integral_constant<int, m - 10>{});
-      if constexpr (m >= 22) ds_pair(std::integral_constant<int, 12 + 2 * (m - 22)>{});
+      exp_range(std::integral_constant<int, e0>{}, std::integral_constant<int, em>{});
+      static_for<s0, sm>(ds_pair);
       __builtin_amdgcn_sched_barrier(0);
       mma(c1);
-      if constexpr (m >= 6 && m < 22) exp_half(std::integral_constant<int, m - 6>{}, c1);
+      exp_range(std::integral_constant<int, em>{}, std::integral_constant<int, e1>{});
       if constexpr (m >= 3 && m < 3 + 2 * PER && ((m - 3) & 1) == 0) dma_piece((m - 3) >> 1);
-      if constexpr (m >= 22) ds_pair(std::integral_constant<int, 13 + 2 * (m - 22)>{});
-      if constexpr (m == 12) {  // bookkeeping for the next step (this step's copies have been issued)
+      static_for<sm, s1>(ds_pair);
+      if constexpr (m == BOOK) {  // bookkeeping for the next step (this step's copies have been issued)
         dma_advance();
         sV = sK;
       }
@@ -1571,7 +1591,9 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_pipe_kernel(DqParams p, int num
 // dQ rows of the items whose walks were cut: the sum of their partial results, in the order of the pieces, times the
 // scale.  One workgroup per (whole item, inner index), each of its 8 waves one unit of 32 rows in the layout in which
 // the pipelined kernel held it.  Bound by the reads of the partial results (128 KB per block and piece).
+template <int D>
 __global__ __launch_bounds__(512) void bwd_dq_merge_kernel(DqParams p, const DqItem* __restrict__ cut) {
+  constexpr int NQ = D / 8;  // accumulator quarters
   const int lane = threadIdx.x & 63, l32 = lane & 31, hh = lane >> 5;
   const int unit = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int inner_n = p.num_kv_heads * p.head_splits, inner = blockIdx.x % inner_n;
@@ -1582,17 +1604,17 @@ __global__ __launch_bounds__(512) void bwd_dq_merge_kernel(DqParams p, const DqI
   if (r >= it.q_rows) return;
   const int64_t step = (int64_t)inner_n * kPartRowFloats;
   const float* src = p.parts + (int64_t)it.part * step + (int64_t)inner * kPartRowFloats + unit * 4096 + lane * 4;
-  f32x4 s[16];
+  f32x4 s[NQ];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) s[i] = *reinterpret_cast<const f32x4*>(src + i * 256);
+  for (int i = 0; i < NQ; ++i) s[i] = *reinterpret_cast<const f32x4*>(src + i * 256);
   for (int k = 1; k < it.kv_tile0; ++k) {  // kv_tile0: number of pieces
     src += step;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) s[i] += *reinterpret_cast<const f32x4*>(src + i * 256);
+    for (int i = 0; i < NQ; ++i) s[i] += *reinterpret_cast<const f32x4*>(src + i * 256);
   }
-  __bf16* op = p.dq + (int64_t)(it.q_row0 + r) * p.num_q_heads * 128 + (int64_t)head * 128 + 4 * hh;
+  __bf16* op = p.dq + (int64_t)(it.q_row0 + r) * p.num_q_heads * D + (int64_t)head * D + 4 * hh;
 #pragma unroll
-  for (int i = 0; i < 16; ++i)
+  for (int i = 0; i < NQ; ++i)
     *reinterpret_cast<bf16x4*>(op + 8 * i) = pack4(s[i][0] * p.scale, s[i][1] * p.scale, s[i][2] * p.scale, s[i][3] * p.scale);
 }
 
@@ -1631,7 +1653,7 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
                        P.q_tiles, d->total_q, d->num_q_heads, lse2p, dsp);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  if constexpr (D != 128) {  // the head_dim 128 dQ kernel reads K^T from its K tiles
+  if constexpr (!pipelined(D)) {  // the pipelined dQ kernel reads K^T from its K tiles
     if ((e = launch_transpose(a.k, d->num_kv_heads, D, 32, kjobs, (int)P.kjobs.size(), P.kv32_tiles, kt, stream)) != hipSuccess) return e;
   }
 
@@ -1664,7 +1686,7 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
     p.clock_log = clock_log(1);
     const int64_t blocks = (int64_t)P.dq_items.size() * d->num_kv_heads * p.head_splits;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    if constexpr (D == 128) {
+    if constexpr (pipelined(D)) {
       // ring slots of a K and a V tile, then the staging tiles of the four waves (64 rows each)
       const size_t smem = (size_t)2 * (DQ_PIPE_DIST + 3) * 32 * D * 2 + (size_t)4 * 64 * D * 2;
       static const hipError_t attr = raise_smem_limit(&bwd_dq_pipe_kernel<D>, smem);
@@ -1672,7 +1694,7 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
       hipLaunchKernelGGL((bwd_dq_pipe_kernel<D>), dim3((unsigned)persistent_grid(blocks)), dim3(256), smem, stream, p, (int)blocks);
       if (P.n_dq_cut > 0) {
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        hipLaunchKernelGGL(bwd_dq_merge_kernel, dim3((unsigned)(P.n_dq_cut * d->num_kv_heads * p.head_splits)), dim3(512), 0, stream, p,
+        hipLaunchKernelGGL((bwd_dq_merge_kernel<D>), dim3((unsigned)(P.n_dq_cut * d->num_kv_heads * p.head_splits)), dim3(512), 0, stream, p,
                            reinterpret_cast<const DqItem*>(ws + P.dq_cut_off));
       }
     } else {
@@ -1703,7 +1725,7 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
     ProfileEvents pe = profile_events();
     profile_events() = ProfileEvents{};
-    if constexpr (D == 128) {
+    if constexpr (pipelined(D)) {
       // ring slots of two 32-row operand tiles, 2 P hand-over slots, one slot of LSE and D rows per ring slot
       constexpr int NS = DKV_PIPE_DIST + 5;
       const size_t smem = (size_t)2 * NS * 32 * D * 2 + 2 * 4096 * 2 + 2 * NS * 64 * sizeof(float);
@@ -1809,6 +1831,7 @@ std::vector<char> bwd_blob(const BwdPlan& P) {
 
 hipError_t launch_bwd(const chunk_attn_desc* d, const BwdArgs& a, const BwdPlan& P, hipStream_t stream) {
   return d->head_dim == 128 ? launch_bwd_t<128>(d, a, P, stream)
+         : d->head_dim == 96 ? launch_bwd_t<96>(d, a, P, stream)
          : d->head_dim == 256 ? launch_bwd_t<256>(d, a, P, stream) : launch_bwd_t<64>(d, a, P, stream);
 }
 

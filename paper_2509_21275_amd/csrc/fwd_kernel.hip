@@ -34,8 +34,10 @@ namespace chunk_attn {
 // (O_s unnormalised, m_s the reference maximum, l_s the sum), M the largest m_s.  Each of the 8 waves takes one unit of
 // 32 rows in the layout in which the pipelined kernel held it.  Bound by the reads of the partial results (128 KB per
 // block and piece, mostly out of the caches they were just written to).
+template <int D>
 __device__ __forceinline__ void fwd_merge_parts(const FwdParams& p, const FwdItem& it, int kvh, int hs, int inner, int inner_n,
                                                 int unit, int lane) {
+  constexpr int NQ = D / 8;  // accumulator quarters
   const int l32 = lane & 31, hh = lane >> 5;
   const int w = unit >> 1;  // wave of the pipelined kernel
   const int head = kvh * p.group + hs * p.heads_per_wg + w % p.heads_per_wg;
@@ -46,14 +48,14 @@ __device__ __forceinline__ void fwd_merge_parts(const FwdParams& p, const FwdIte
   float m = ml[0], l = 0.f;
   for (int s = 1; s < it.whole; ++s) m = fmaxf(m, ml[s * step]);
   for (int s = 0; s < it.whole; ++s) l += ml[s * step + 1] * __builtin_amdgcn_exp2f(ml[s * step] - m);
-  f32x4 o[16];
+  f32x4 o[NQ];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < NQ; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
   const float* src = part0 + unit * 4096 + lane * 4;
   for (int s = 0; s < it.whole; ++s, src += step) {
     const float f = __builtin_amdgcn_exp2f(ml[s * step] - m);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
+    for (int i = 0; i < NQ; ++i) {
       const f32x4 v = *reinterpret_cast<const f32x4*>(src + i * 256);
 #pragma unroll
       for (int e = 0; e < 4; ++e) o[i][e] += v[e] * f;
@@ -61,9 +63,9 @@ __device__ __forceinline__ void fwd_merge_parts(const FwdParams& p, const FwdIte
   }
   if (r >= it.q_rows) return;
   const float inv = 1.0f / l;
-  __bf16* op = p.o + (int64_t)(it.q_row0 + r) * p.num_q_heads * 128 + (int64_t)head * 128 + 4 * hh;
+  __bf16* op = p.o + (int64_t)(it.q_row0 + r) * p.num_q_heads * D + (int64_t)head * D + 4 * hh;
 #pragma unroll
-  for (int i = 0; i < 16; ++i)
+  for (int i = 0; i < NQ; ++i)
     *reinterpret_cast<bf16x4*>(op + 8 * i) = pack4(o[i][0] * inv, o[i][1] * inv, o[i][2] * inv, o[i][3] * inv);
   if (hh == 0) p.lse[(int64_t)head * p.total_q + it.q_row0 + r] = (m + log2f(l)) * 0.6931471805599453f;
 }
@@ -78,7 +80,7 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
   constexpr int DB = D / 32;   // 32-row blocks of O^T
   constexpr int KT = BN * D;   // elements per K tile and per V^T image
   constexpr int WR = 32 * QB;  // query rows per wave
-  constexpr bool IMG = D != 128;  // V arrives as a transposed image; else as rows, two chunk-major tiles of 32
+  constexpr bool IMG = !pipelined(D);  // V arrives as a transposed image; else as rows, two chunk-major tiles of 32
 
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   __bf16* Ks = reinterpret_cast<__bf16*>(smem);  // [2][BN][D]  swizzled rows
@@ -95,7 +97,7 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
   const int kvh = inner % p.num_kv_heads, hs = inner / p.num_kv_heads;
   if constexpr (!IMG) {  // second pass: only what the pipelined kernel left to do
     if (p.redo[blockIdx.x] == 0) {
-      if (it.part >= 0) fwd_merge_parts(p, it, kvh, hs, inner, inner_n, wave, lane);
+      if (it.part >= 0) fwd_merge_parts<D>(p, it, kvh, hs, inner, inner_n, wave, lane);
       return;
     }
   }
@@ -118,8 +120,10 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
   // Per-lane source offsets of the global->LDS copies (elements).  A K tile is 64 rows x KC chunks; copy
   // instruction i of wave w fills LDS chunks [(WAVES i + w) 64, +64), so the lane fetches the chunk that the
   // swizzle puts there.  The V^T image is copied linearly.
-  constexpr int NK = BN * KC / NT, NV = KT / 8 / NT;
-  static_assert(NK >= 1 && NV >= 1, "every thread copies at least one chunk of each tile");
+  // (head_dim 96: 12 copies of 64 chunks for 8 waves, so the second round is half a round)
+  constexpr int PIECES = BN * KC / 64, NK = (PIECES + WAVES - 1) / WAVES, NV = NK;
+  static_assert(KT == BN * KC * 8, "a V tile has as many chunks as a K tile");
+  auto has_piece = [&](int i) { return PIECES % WAVES == 0 || i * WAVES + wave < PIECES; };
   unsigned k_src[NK];
   int k_row[NK];
 #pragma unroll
@@ -134,12 +138,13 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
     __bf16* kdst = Ks + buf * KT;
     if (last_row >= BN - 1) {
 #pragma unroll
-      for (int i = 0; i < NK; ++i) dma16(ksrc + k_src[i], kdst + (i * WAVES + wave) * 512);
+      for (int i = 0; i < NK; ++i)
+        if (has_piece(i)) dma16(ksrc + k_src[i], kdst + (i * WAVES + wave) * 512);
     } else {
 #pragma unroll
       for (int i = 0; i < NK; ++i) {
         const unsigned off = k_src[i] - (unsigned)((k_row[i] - min(k_row[i], last_row)) * (int)kv_stride);
-        dma16(ksrc + off, kdst + (i * WAVES + wave) * 512);
+        if (has_piece(i)) dma16(ksrc + off, kdst + (i * WAVES + wave) * 512);
       }
     }
     __bf16* vdst = Vs + buf * KT;
@@ -154,7 +159,7 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
       for (int i = 0; i < NV; ++i) {
         const int x = (i * WAVES + wave) * 64 + lane, xt = x % (32 * KC);  // slot, slot in its 32-row tile
         const int row = x / (32 * KC) * 32 + ((xt & 31) ^ (((xt >> 5) & 3) << 2));
-        dma16(vsrc + (int64_t)min(row, last_row) * kv_stride + (xt >> 5) * 8, vdst + (i * WAVES + wave) * 512);
+        if (has_piece(i)) dma16(vsrc + (int64_t)min(row, last_row) * kv_stride + (xt >> 5) * 8, vdst + (i * WAVES + wave) * 512);
       }
     }
   };
@@ -205,15 +210,15 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
   ones[0] = (__bf16)1.0f; ones[1] = (__bf16)1.0f;
 
   // One loop body for both LDS buffers: the operand addresses are toggled between the buffers with an XOR
-  // (the buffers are KT elements = a power of two bytes apart), so the accumulators are carried by a single
-  // loop and never pass through a conditional.
-  static_assert((KT & (KT - 1)) == 0, "buffer pitch must be a power of two");
+  // (the buffers are KT elements = a power of two bytes apart; else the buffer's offset is added), so the accumulators are
+  // carried by a single loop and never pass through a conditional.
+  constexpr bool TOGGLE = (KT & (KT - 1)) == 0;
   int buf = 0;
   for (int t = 0; t < nt_wg; ++t) {
     if (t + 1 < nt_wg) dma_tile(t + 1, buf ^ 1);
 
     if (t < nt_w) {
-      const __bf16* Kt = Ks;
+      const __bf16* Kt = Ks + (TOGGLE ? 0 : buf * KT);
       const __bf16* Vt = Vs;
       // ---- S^T = K Q^T : [64 keys] x [32 QB queries]; every K fragment feeds QB products ----
       f32x16 s0[QB], s1[QB];
@@ -299,21 +304,21 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
         const unsigned lo_addr = vt_lo + buf * (KT * 2), hi_addr = vt_hi + buf * (KT * 2);
         static_for<0, 4>([&](auto ks_c) __attribute__((always_inline)) {
           constexpr int ks = decltype(ks_c)::value;
-          s16x4 lo[4], hi[4];
-          static_assert(IMG || DB == 4, "four blocks of O^T");
-          static_for<0, 4>([&](auto db_c) __attribute__((always_inline)) {
+          s16x4 lo[DB], hi[DB];
+          static_for<0, DB>([&](auto db_c) __attribute__((always_inline)) {
             constexpr int db = decltype(db_c)::value;
             constexpr int off = ((ks >> 1) * (32 * D) + (ks & 1) * (16 * 8) + db * (4 * 32 * 8)) * 2;
             lo[db] = lds_asm_read_tr<off>(lo_addr);
             hi[db] = lds_asm_read_tr<off>(hi_addr);
           });
-          asm volatile("s_waitcnt lgkmcnt(0)"
-                       : "+v"(lo[0]), "+v"(lo[1]), "+v"(lo[2]), "+v"(lo[3]), "+v"(hi[0]), "+v"(hi[1]), "+v"(hi[2]), "+v"(hi[3]));
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-          for (int db = 0; db < 4; ++db) {
+          for (int db = 0; db < DB; ++db) asm volatile("" : "+v"(lo[db]), "+v"(hi[db]));  // (after the wait, in this order)
+#pragma unroll
+          for (int db = 0; db < DB; ++db) {
             const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo[db], hi[db], 0, 1, 2, 3, 4, 5, 6, 7));
 #pragma unroll
-            for (int qb = 0; qb < QB; ++qb) oacc[qb][db % DB] = mfma32(a, pf[qb][ks], oacc[qb][db % DB]);
+            for (int qb = 0; qb < QB; ++qb) oacc[qb][db] = mfma32(a, pf[qb][ks], oacc[qb][db]);
           }
         });
       }
@@ -321,9 +326,9 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
 
     buf ^= 1;
 #pragma unroll
-    for (int ks = 0; ks < DK; ++ks) k_off[ks] ^= KT;
+    for (int ks = 0; ks < DK; ++ks) k_off[ks] ^= TOGGLE ? KT : 0;
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) v_off[ks] ^= KT;
+    for (int ks = 0; ks < 4; ++ks) v_off[ks] ^= TOGGLE ? KT : 0;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
   }
@@ -352,15 +357,15 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
 }
 
 // ------------------------------------------------------------------------------------------------
-// Pipelined forward for head_dim 128: one wave per SIMD, 64 query rows per wave (two 32-row "units"), keys
+// Pipelined forward for head_dim 128 and 96: one wave per SIMD, 64 query rows per wave (two 32-row "units"), keys
 // streamed in stages of 32.
 //
 // A wave issues at most one instruction every four cycles and an MFMA holds the matrix pipe for 32, so the loop
 // is laid out instruction by instruction.  In step t a wave runs
 //     O^T += V(t-1)^T P^T(t-1)        S^T(t+1) = K(t+1) Q^T        (matrix pipe)
 //     P^T(t) = exp2(S^T(t) c - m c) and its row sums                (vector pipe)
-// as 16 mini-steps of one LDS operand fragment and the two MFMAs it feeds (one per unit), each MFMA followed by
-// the vector work of one score.  K and V tiles are copied global->LDS into a ring of DIST + 3 slots, stored
+// as 16 (head_dim 96: 12) mini-steps of one LDS operand fragment and the two MFMAs it feeds (one per unit), each MFMA
+// followed by its share of the vector work of 32 scores.  K and V tiles are copied global->LDS into a ring of DIST + 3 slots, stored
 // chunk-major; V^T is read from the V tile itself with the LDS transpose read.  Fragments are fetched four
 // mini-steps ahead with opaque LDS reads and explicit lgkmcnt waits; S^T lives in vector registers, where the
 // vector work reads it directly, the Q fragments and O^T in accumulation registers (tiles.hpp).
@@ -381,9 +386,11 @@ __global__ __launch_bounds__(256, 1) void fwd_pipe_kernel(FwdParams p, int num_b
   constexpr int NS = DIST + 3; // ring slots: stages t - 1 .. t + 1 in use, t + 2 .. t + 1 + DIST on their way
   constexpr int NF = 2 * DB + DK;      // operand fragments (mini-steps) per step: V^T, then K rows
   constexpr int AHEAD = 4;             // fragments in flight
+  constexpr int RING = NF % 8 == 0 ? 8 : 6;  // registers of the fragment ring: a step starts where the ring does
   constexpr int NP = BN * KC / 64;     // 64-slot pieces per tile
   constexpr int PER = 2 * NP / NW;     // global->LDS copies per wave and stage
-  static_assert(D == 128 && NF == 16 && PER == 4, "the mini-step schedule below is written for head_dim 128");
+  constexpr int BOOK = NF - 4;         // mini-step of the bookkeeping, behind the last copy
+  static_assert(2 * NP % NW == 0 && NF % RING == 0 && RING > AHEAD && 3 + 2 * (PER - 1) < BOOK, "the schedule of a step");
 
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   lds_bf16* const L = (lds_bf16*)smem;
@@ -455,10 +462,11 @@ __global__ __launch_bounds__(256, 1) void fwd_pipe_kernel(FwdParams p, int num_b
   int d_t = 0, d_slot = 0;   // stage to copy next (clamped to the last one) and its slot
   int64_t d_off = 0;         // element offset of its first row
   auto dma_piece = [&](int i) __attribute__((always_inline)) {
-    const int piece = i * NW + wave;  // wave-uniform; i < NP / NW: a piece of K, else of V
+    const int piece = i * NW + wave;  // wave-uniform; the first NP are pieces of K, the others of V
+    const bool of_k = NP % NW == 0 ? i < NP / NW : piece < NP;
     const unsigned voff = d_t == nt - 1 ? v_last[i] : v_full[i];
-    const char* base = reinterpret_cast<const char*>((i < NP / NW ? Kg : Vg) + d_off);
-    lds_bf16* dst = L + (i < NP / NW ? K_OFF + piece * 512 : V_OFF + (piece - NP) * 512) + d_slot * KT;
+    const char* base = reinterpret_cast<const char*>((of_k ? Kg : Vg) + d_off);
+    lds_bf16* dst = L + (of_k ? K_OFF + piece * 512 : V_OFF + (piece - NP) * 512) + d_slot * KT;
     dma16(base + voff, dst);
   };
   auto dma_advance = [&]() __attribute__((always_inline)) {
@@ -543,7 +551,7 @@ __global__ __launch_bounds__(256, 1) void fwd_pipe_kernel(FwdParams p, int num_b
 #pragma unroll
         for (int i = 0; i < 8; ++i) f[b][u][ks][i] = (__bf16)0.0f;
   const float c = p.scale_log2;
-  bf16x8 fr[8];  // ring of operand fragments
+  bf16x8 fr[RING];  // ring of operand fragments
 
   // S^T(0) = K(0) Q^T and the reference maximum of each row; then the first fragments of step 0 (zeros)
   float mc[2], l_run[2];
@@ -554,7 +562,9 @@ __global__ __launch_bounds__(256, 1) void fwd_pipe_kernel(FwdParams p, int num_b
       const unsigned sT = (NS - 1) * SLOT;
       static_for<0, AHEAD>([&](auto m_c) __attribute__((always_inline)) { fr[decltype(m_c)::value] = load_t(t_lo0 + sT, t_hi0 + sT, m_c); });
     }
-    asm volatile("s_waitcnt lgkmcnt(%8)" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]) : "n"(2 * AHEAD));
+    asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(2 * AHEAD) : "memory");
+#pragma unroll
+    for (int ks = 0; ks < DK; ++ks) asm volatile("" : "+v"(a[ks]));  // (after the wait, in this order)
 #pragma unroll
     for (int ks = 0; ks < DK; ++ks)
 #pragma unroll
@@ -582,13 +592,8 @@ __global__ __launch_bounds__(256, 1) void fwd_pipe_kernel(FwdParams p, int num_b
   bool risk = false;
   const float big = __builtin_amdgcn_exp2f(p.ref_limit);
 
-  // In program order mini-step m reads fragment m + 4: two instructions for the transposed fragments (0 .. 7 of this
-  // step, 0 .. 3 of the next), one for the rows fragments (8 .. 15).  lgkm_wait(m) = number of LDS instructions between
-  // the read of fragment m and the start of mini-step m, where the wait stands.
-  auto lgkm_wait = [](int m) {
-    constexpr int tab[16] = {6, 6, 6, 6, 6, 5, 4, 3, 3, 3, 3, 3, 3, 4, 5, 6};
-    return tab[m];
-  };
+  // In program order mini-step m reads fragment m + 4: the transposed fragments (0 .. 2 DB - 1 of this step, 0 .. 3 of the
+  // next) take two instructions, the rows fragments one.
   int sV = 0;  // slot of stage t
   auto step = [&](int t, f32x16 (&cur)[2], f32x16 (&nxt)[2], bf16x8 (&f_old)[2][2], bf16x8 (&f_new)[2][2],
                   auto masked_c) __attribute__((always_inline)) {
@@ -630,18 +635,26 @@ __global__ __launch_bounds__(256, 1) void fwd_pipe_kernel(FwdParams p, int num_b
       e_hold[q] = __builtin_amdgcn_exp2f(tt);
       asm volatile("" : "+v"(e_hold[q]));
     };
+    // the 32 scores' vector work, spread evenly over the step's 2 NF MFMAs: scores [done(k - 1), done(k)) after MFMA k
+    auto vec_after = [&](auto k_c) __attribute__((always_inline)) {
+      constexpr int k = decltype(k_c)::value, lo = 32 * k / (2 * NF), hi = 32 * (k + 1) / (2 * NF);
+      static_for<lo, hi>([&](auto x_c) __attribute__((always_inline)) {
+        constexpr int x = decltype(x_c)::value;
+        vec_half(std::integral_constant<int, x / 2>{}, std::integral_constant<int, x % 2>{});
+      });
+    };
     asm volatile("s_nop 7" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
     static_for<0, NF>([&](auto m_c) __attribute__((always_inline)) {
       constexpr int m = decltype(m_c)::value;
-      asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(fr[m & 7]) : "n"(lgkm_wait(m)));
+      asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(fr[m % RING]) : "n"(fragment_wait(NF, 0, 2 * DB, m)));
       {  // read the fragment of mini-step m + AHEAD (past the end: the next step's first transposed fragments)
         constexpr int mm = m + AHEAD;
-        if constexpr (mm < 2 * DB) fr[mm & 7] = load_t(t_lo, t_hi, std::integral_constant<int, mm>{});
-        else if constexpr (mm < NF) fr[mm & 7] = load_rows(k_ev, k_od, std::integral_constant<int, mm - 2 * DB>{});
-        else fr[mm & 7] = load_t(n_lo, n_hi, std::integral_constant<int, mm - NF>{});
+        if constexpr (mm < 2 * DB) fr[mm % RING] = load_t(t_lo, t_hi, std::integral_constant<int, mm>{});
+        else if constexpr (mm < NF) fr[mm % RING] = load_rows(k_ev, k_od, std::integral_constant<int, mm - 2 * DB>{});
+        else fr[mm % RING] = load_t(n_lo, n_hi, std::integral_constant<int, mm - NF>{});
       }
-      const bf16x8 fa = fr[m & 7];
+      const bf16x8 fa = fr[m % RING];
       auto mma = [&](auto u_c) __attribute__((always_inline)) {
         constexpr int u = decltype(u_c)::value;
         if constexpr (m < 2 * DB) {
@@ -659,12 +672,12 @@ __global__ __launch_bounds__(256, 1) void fwd_pipe_kernel(FwdParams p, int num_b
       constexpr std::integral_constant<int, 0> c0{};
       constexpr std::integral_constant<int, 1> c1{};
       mma(c0);
-      vec_half(m_c, c0);
+      vec_after(std::integral_constant<int, 2 * m>{});
       __builtin_amdgcn_sched_barrier(0);
       mma(c1);
-      vec_half(m_c, c1);
+      vec_after(std::integral_constant<int, 2 * m + 1>{});
       if constexpr (m >= 3 && m < 3 + 2 * PER && ((m - 3) & 1) == 0) dma_piece((m - 3) >> 1);
-      if constexpr (m == 12) {  // bookkeeping for the next step (this step's copies have been issued)
+      if constexpr (m == BOOK) {  // bookkeeping for the next step (this step's copies have been issued)
         dma_advance();
         sV = sK;
       }
@@ -780,23 +793,30 @@ static hipError_t launch_fwd_t(const FwdParams& p, int num_blocks, hipStream_t s
   return hipGetLastError();
 }
 
+template <int D>
+static hipError_t launch_fwd_pipe(const FwdParams& p, int num_blocks, int num_wholes, hipStream_t stream) {
+  // ring slots of a K and a V tile, then the staging tiles of the four waves (64 rows each)
+  const size_t smem = (size_t)2 * (FWD_PIPE_DIST + 3) * 32 * D * 2 + (size_t)4 * 64 * D * 2;
+  static const hipError_t attr = raise_smem_limit(&fwd_pipe_kernel<D>, smem);
+  if (attr != hipSuccess) return attr;
+  hipLaunchKernelGGL((fwd_pipe_kernel<D>), dim3(persistent_grid(num_blocks)), dim3(256), smem, stream, p, num_blocks);
+  hipError_t e;
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  // Second pass over the whole items, 8 waves of 32 rows: a workgroup returns at once unless its flag is raised (the item
+  // is recomputed) or its item was cut (its pieces are put together).
+  return launch_fwd_t<D, 8>(p, num_wholes, stream);
+}
+
 hipError_t launch_fwd(const FwdParams& p, int head_dim, int num_blocks, int num_wholes, const TileJob* vjobs, int num_vjobs,
                       hipStream_t stream) {
-  hipError_t e;
-  if (head_dim != 128) {
+  if (!pipelined(head_dim)) {
+    hipError_t e;
     if ((e = launch_transpose(p.v, p.num_kv_heads, head_dim, 64, vjobs, num_vjobs, p.total_kv_tiles, const_cast<__bf16*>(p.vt),
                               stream)) != hipSuccess) return e;
     return head_dim == 256 ? launch_fwd_t<256, 4>(p, num_blocks, stream) : launch_fwd_t<64, 4>(p, num_blocks, stream);
   }
-  // ring slots of a K and a V tile, then the staging tiles of the four waves (64 rows each)
-  const size_t smem = (size_t)2 * (FWD_PIPE_DIST + 3) * 32 * 128 * 2 + (size_t)4 * 64 * 128 * 2;
-  static const hipError_t attr = raise_smem_limit(&fwd_pipe_kernel<128>, smem);
-  if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL((fwd_pipe_kernel<128>), dim3(persistent_grid(num_blocks)), dim3(256), smem, stream, p, num_blocks);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  // Second pass over the whole items, 8 waves of 32 rows: a workgroup returns at once unless its flag is raised (the item
-  // is recomputed) or its item was cut (its pieces are put together).
-  return launch_fwd_t<128, 8>(p, num_wholes, stream);
+  return head_dim == 96 ? launch_fwd_pipe<96>(p, num_blocks, num_wholes, stream)
+                        : launch_fwd_pipe<128>(p, num_blocks, num_wholes, stream);
 }
 
 }  // namespace chunk_attn

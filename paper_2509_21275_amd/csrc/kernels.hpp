@@ -40,9 +40,11 @@ struct FwdParams {
 // over as many query heads of one group as divide both (so that the key/value tiles they stream are shared).
 // forward: 4 waves; for head_dim 128 each wave owns two 32-row query blocks (fwd_pipe_kernel; its second pass,
 // fwd_kernel with 8 waves of one block, covers the same rows per workgroup)
+// head dimensions that the software-pipelined kernels are instantiated for
+constexpr bool pipelined(int head_dim) { return head_dim == 96 || head_dim == 128; }
 inline int fwd_waves(int) { return 4; }
-inline int fwd_qblocks(int head_dim) { return head_dim == 128 ? 2 : 1; }
-inline int dq_waves(int head_dim) { return head_dim == 128 ? 8 : 4; }
+inline int fwd_qblocks(int head_dim) { return pipelined(head_dim) ? 2 : 1; }
+inline int dq_waves(int head_dim) { return pipelined(head_dim) ? 8 : 4; }
 inline int heads_per_wg(int group, int waves) {
   int h = 1;
   while (h * 2 <= waves && group % (h * 2) == 0) h *= 2;
@@ -63,8 +65,8 @@ inline int persistent_grid(int64_t blocks) {
 }
 constexpr int kBlockQueues = 8;  // counters per kernel that claims its blocks
 constexpr int kCus = 256;        // compute units of an MI355X (plans that must not depend on where they are made)
-// A partial result of one block (256 rows of head_dim 128) in the order in which the kernels hold it: [8 units of 32
-// rows][16 accumulator quarters][64 lanes][4] float32; for the forward then [8 units][32 rows] {reference maximum, sum}.
+// A partial result of one block (256 rows of head_dim 128, or fewer) in the order in which the kernels hold it: [8 units of 32
+// rows][up to 16 accumulator quarters][64 lanes][4] float32; for the forward then [8 units][32 rows] {reference maximum, sum}.
 constexpr int kPartRowFloats = 8 * 16 * 64 * 4;
 constexpr int kPartFloats = kPartRowFloats + 8 * 32 * 2;
 

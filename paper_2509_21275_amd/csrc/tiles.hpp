@@ -24,11 +24,16 @@ __device__ __forceinline__ int swz(int row, int c) {
     // 256-byte rows: rotate by a 4x4 bit-transposed row index; conflict-free for 16 consecutive rows
     const int f = ((row & 3) << 2) | ((row >> 2) & 3);
     return (c + f) & 15;
+  } else if constexpr (CHUNKS == 12) {
+    // 192-byte rows: four consecutive rows start on bank groups 0, 12, 8 and 4 (of 16); rotated by 0 .. 3 for the four
+    // rows after them, and so on (a rotation past the row's end is a step of 4 groups, which keeps that set)
+    const int x = c + ((row >> 2) & 3);
+    return x >= 12 ? x - 12 : x;
   } else if constexpr (CHUNKS == 8) {
     // 128-byte rows: two rows share a 256-byte bank line, so the permutation changes every other row
     return c ^ ((row >> 1) & 7);
   } else {
-    static_assert(CHUNKS == 4, "tiles have 4, 8, 16 or 32 chunks per row");
+    static_assert(CHUNKS == 4, "tiles have 4, 8, 12, 16 or 32 chunks per row");
     // 64-byte rows: four rows share a bank line
     return c ^ ((row >> 2) & 3);
   }
@@ -41,6 +46,9 @@ __device__ __forceinline__ int unswz(int row, int pc) {
   } else if constexpr (CHUNKS == 16) {
     const int f = ((row & 3) << 2) | ((row >> 2) & 3);
     return (pc - f) & 15;
+  } else if constexpr (CHUNKS == 12) {
+    const int x = pc - ((row >> 2) & 3);
+    return x < 0 ? x + 12 : x;
   } else if constexpr (CHUNKS == 8) {
     return pc ^ ((row >> 1) & 7);
   } else {
@@ -182,6 +190,23 @@ __device__ __forceinline__ void lds_asm_write16(unsigned addr, bf16x8 v) {
 }
 __device__ __forceinline__ unsigned lds_addr(const lds_bf16* p) { return (unsigned)(uintptr_t)p; }
 __device__ __forceinline__ unsigned lds_addr(const lds_f32* p) { return (unsigned)(uintptr_t)p; }
+
+// How a software-pipelined step spreads `n` pieces of vector work over its mini-steps first .. last - 1: the number done by the
+// end of mini-step m (those of one mini-step are split between its two MFMAs, the first half, rounded up, after the first).
+__host__ __device__ constexpr int spread(int n, int first, int last, int m) {
+  return m < first ? 0 : m >= last - 1 ? n : n * (m - first + 1) / (last - first);
+}
+// LDS instructions issued between the read of fragment m and the start of mini-step m, where the wait for it stands: the
+// reads of the three fragments after it (fragments are read four mini-steps ahead).  Of a step's `nf` fragments those from
+// t_first to t_last - 1 are transposed, two instructions each; the ones past the end are the next step's first.
+__host__ __device__ constexpr int fragment_wait(int nf, int t_first, int t_last, int m) {
+  int n = 0;
+  for (int k = m + 1; k <= m + 3; ++k) n += k % nf >= t_first && k % nf < t_last ? 2 : 1;
+  return n;
+}
+static_assert(fragment_wait(16, 0, 8, 0) == 6 && fragment_wait(16, 0, 8, 5) == 5 && fragment_wait(16, 0, 8, 12) == 3 &&
+              fragment_wait(16, 0, 8, 13) == 4 && fragment_wait(24, 16, 24, 12) == 3 && fragment_wait(24, 16, 24, 15) == 6 &&
+              fragment_wait(24, 16, 24, 21) == 5, "worked out by hand");
 
 template <int I, int N, class F>
 __device__ __forceinline__ void static_for(F&& f) {

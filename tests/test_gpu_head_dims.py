@@ -1,5 +1,4 @@
-"""Head dimensions other than the benchmark's 64 and 128: 256 (kernels of its own) and 96 (run as 128 on zero-padded
-copies held in the workspace), through the C ABI against the fp64 oracle: scaled replicas of the five workloads, the
+"""Head dimensions other than the benchmark's 64 and 128: 256 and 96, through the C ABI against the fp64 oracle: scaled replicas of the five workloads, the
 slice-by-slice accumulation of a split sequence in bf16 and float32 buffers, untouched / zeroed rows outside the key
 ranges, workspace sizes, bit-reproducibility."""
 import dataclasses
@@ -82,7 +81,7 @@ def test_rows_outside_key_ranges(oracle_mod, d):
 
 
 def test_padded_head_needs_a_larger_workspace_and_says_so():
-    """head_dim 96 keeps zero-padded copies of its operands in the workspace: the sizes reported cover them, and a
+    """The sizes reported for head_dim 96 cover zero-padded copies of the operands, and a
     workspace sized for head_dim 128 alone is refused before anything is launched."""
     segs = synth.packed_chunk([300, 200])
     d96 = ca.make_desc(segs, 8, 2, 96, 500, 500, 96 ** -0.5)
@@ -98,3 +97,30 @@ def test_padded_head_needs_a_larger_workspace_and_says_so():
         ca.chunk_attn_fwd(d96, q, kv, kv, o, lse, ws)
     assert e.value.code == ca.WORKSPACE_TOO_SMALL
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("name,segs,Hq,Hkv", [
+    ("tiny_walks", [(0, 32, 0, 32), (32, 33, 32, 33), (65, 64, 65, 64), (129, 1, 129, 129), (130, 95, 258, 95)], 2, 2),
+    ("many_contexts", [(0, 40, 0, 127), (40, 40, 127, 128), (80, 40, 255, 129), (120, 200, 384, 513)], 8, 2),
+    ("two_way_walks", [(0, 1500, 0, 1500 + 200), (1500, 90, 1700, 90)], 64, 64),
+    ("gqa3_odd_group", [(0, 65, 0, 193)], 6, 2),
+    ("gqa8", [(0, 96, 0, 640), (96, 160, 640, 160)], 16, 2),
+])
+def test_pipelined_kernels_of_head_dim_96(oracle_mod, name, segs, Hq, Hkv):
+    """Edges of the software-pipelined kernels' head_dim 96 instantiations (walks of one to three stages, key blocks of 127
+    to 129 rows, both walk directions, head splits), against the oracle and against head_dim 128 on zero-padded inputs: the
+    same sums in the same order up to the order inside a matrix instruction, so two bf16 roundings apart at most."""
+    tq, tkv = max(s[0] + s[1] for s in segs), max(s[2] + s[3] for s in segs)
+    case = synth.ChunkCase(f"{name}_d96", [synth.Seg(*s) for s in segs], tq, tkv, Hq, Hkv, 96, 500 + len(name))
+    q, k, v, do = make_inputs(case)
+    got = run_gpu(case, q, k, v, do)
+    orc = oracle_mod.Oracle(case.segs, q.cpu(), k.cpu(), v.cpu(), do.cpu(), case.scale)
+    O, LSE = orc.forward(); dQ, dK, dV = orc.backward()
+    errs = [rel_err(a, b) for a, b in zip(got, (O, LSE, dQ, dK, dV))]
+    print(case.name, errs, flush=True)
+    assert errs[0] <= TOL_O and errs[1] <= 1e-4 and max(errs[2:]) <= TOL_GRAD
+    wide = dataclasses.replace(case, head_dim=128)
+    ref = run_gpu(wide, *(torch.nn.functional.pad(x, (0, 32)) for x in (q, k, v, do)), scale=case.scale)
+    for a, b in zip(got, ref):
+        b = b if b.dim() == 2 else b[..., :96]
+        assert rel_err(a, b.double().cpu().numpy()) <= 2.0 ** -7

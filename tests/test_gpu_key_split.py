@@ -1,4 +1,4 @@
-"""Chunks with few query rows and long key walks, whose work items the head_dim 128 forward and dQ kernels cut into pieces:
+"""Chunks with few query rows and long key walks, whose work items the head_dim 128 and 96 forward and dQ kernels cut into pieces:
 against the fp64 oracle (2e-2 for O, 5e-2 for the gradients, as everywhere), against the uncut run (a workspace
 without room for partial results; both are bf16 roundings of float32 sums in different orders, so they differ by about one
 rounding: 2^-7 of the largest value), and bit for bit between the workspace and the static forward."""
@@ -31,14 +31,15 @@ def _lse_err(lse, want):
     return float(abs(lse.double().cpu().numpy() - want).max())
 
 
-def _case(name, segs, hq, hk):
+def _case(name, segs, hq, hk, d=128):
     tq, tkv = max(s[0] + s[1] for s in segs), max(s[2] + s[3] for s in segs) + 3
-    return synth.ChunkCase(name, [synth.Seg(*s) for s in segs], tq, tkv, hq, hk, 128, 900 + len(name))
+    return synth.ChunkCase(name, [synth.Seg(*s) for s in segs], tq, tkv, hq, hk, d, 900 + len(name))
 
 
+@pytest.mark.parametrize("d", [128, 96])
 @pytest.mark.parametrize("name,segs,hq,hk", CASES, ids=[c[0] for c in CASES])
-def test_cut_walks(oracle_mod, name, segs, hq, hk):
-    case = _case(name, segs, hq, hk)
+def test_cut_walks(oracle_mod, name, segs, hq, hk, d):
+    case = _case(name, segs, hq, hk, d)
     q, k, v, do = make_inputs(case)
     o, lse, dq, dk, dv = run_gpu(case, q, k, v, do)
     orc = oracle_mod.Oracle(case.segs, q.cpu(), k.cpu(), v.cpu(), do.cpu(), case.scale)
@@ -46,7 +47,7 @@ def test_cut_walks(oracle_mod, name, segs, hq, hk):
     assert rel_err(o, O) <= TOL_O and rel_err(lse, LSE) <= 1e-4
     assert max(rel_err(dq, dQ), rel_err(dk, dK), rel_err(dv, dV)) <= TOL_GRAD
 
-    desc = ca.make_desc(case.segs, hq, hk, 128, case.total_q, case.total_kv, case.scale)
+    desc = ca.make_desc(case.segs, hq, hk, d, case.total_q, case.total_kv, case.scale)
     o2 = torch.full_like(o, float("nan")); lse2 = torch.full_like(lse, float("nan"))
     ca.chunk_attn_fwd_static(desc, q, k, v, o2, lse2)
     assert torch.equal(o, o2) and torch.equal(lse, lse2)
@@ -66,9 +67,10 @@ def test_cut_walks(oracle_mod, name, segs, hq, hk):
     assert rel_err(o, o2.double().cpu().numpy()) <= 2.0 ** -7 and rel_err(lse, lse2.double().cpu().numpy()) <= 1e-5
 
 
-def test_cut_walks_that_take_the_second_pass(oracle_mod):
+@pytest.mark.parametrize("d", [128, 96])
+def test_cut_walks_that_take_the_second_pass(oracle_mod, d):
     """Every piece raises its item's flag: the whole items are recomputed, not put together."""
-    case = _case(*CASES[6])
+    case = _case(*CASES[6], d)
     q, k, v, _ = make_inputs(case)
     ca.chunk_attn_test_set_fwd_rescale_limit(-1e30)
     try:
