@@ -152,7 +152,8 @@ inline size_t padded_bytes(int64_t rows, int heads, size_t elem) { return align_
 // transposed V images or, for head_dim 128, the partial results of items whose walks are cut.
 struct FwdLayout {
   int tile_rows;
-  KeySplit split;  // head_dim 128: how the walks are cut
+  bool pipe;       // the pipelined kernel runs (head_dim 96 and 128, and 64 from a number of blocks on)
+  KeySplit split;  // pipelined kernel: how the walks are cut
   size_t n_items, n_wholes, wholes_off, jobs_off, flags_off, blob_bytes, vt_off, total;
   int64_t blocks, whole_blocks;
   int64_t kv_tiles;
@@ -170,10 +171,14 @@ void layout_fwd(const chunk_attn_desc* desc, FwdLayout& L, bool with_plan, bool 
   const chunk_attn_desc wide = widened(desc), *d = &wide;
   const int group = d->num_q_heads / d->num_kv_heads;
   const int inner = d->num_kv_heads * (group / heads_per_wg(group, fwd_waves(d->head_dim)));
-  const bool pipe = pipelined(d->head_dim);
-  L.tile_rows = tile_rows(group, fwd_waves(d->head_dim)) * fwd_qblocks(d->head_dim);
-  L.n_wholes = 0;
-  for (int t = 0; t < d->num_segments; ++t) L.n_wholes += (d->segments[t].q_len + L.tile_rows - 1) / L.tile_rows;
+  L.tile_rows = 2 * tile_rows(group, fwd_waves(d->head_dim));  // two 32-row blocks per wave
+  Walks walks = count_walks(d, L.tile_rows);
+  const bool pipe = L.pipe = pipelined(d->head_dim) || (d->head_dim == 64 && pipe_pays(walks, inner));
+  if (!pipe) {
+    L.tile_rows /= 2;
+    walks = count_walks(d, L.tile_rows);
+  }
+  L.n_wholes = (size_t)walks.items;
   L.kv_tiles = count_tiles(d, true, 64);
   const size_t image_bytes = align_up((size_t)L.kv_tiles * d->num_kv_heads * d->head_dim * 64 * sizeof(__bf16));
   L.whole_blocks = (int64_t)L.n_wholes * inner;
@@ -184,7 +189,7 @@ void layout_fwd(const chunk_attn_desc* desc, FwdLayout& L, bool with_plan, bool 
     L.n_items = n_items;
     L.wholes_off = n_items == L.n_wholes ? 0 : align_up(n_items * sizeof(FwdItem));
     L.jobs_off = align_up(L.wholes_off + L.n_wholes * sizeof(FwdItem));
-    L.flags_off = align_up(L.jobs_off + (pipe ? 0 : (size_t)L.kv_tiles * sizeof(TileJob)));
+    L.flags_off = align_up(L.jobs_off + (d->head_dim <= 128 ? 0 : (size_t)L.kv_tiles * sizeof(TileJob)));
     L.blob_bytes = L.flags_off + ((size_t)L.whole_blocks + kBlockQueues) * sizeof(int32_t);
     L.vt_off = align_up(L.blob_bytes);
   };
@@ -193,7 +198,7 @@ void layout_fwd(const chunk_attn_desc* desc, FwdLayout& L, bool with_plan, bool 
   const size_t uncut_total = L.vt_off + image_bytes;
   if (pipe && may_cut) {
     const size_t limit = std::max(uncut_total, kStaticScratchBytes);
-    L.split = choose_key_split(d, L.tile_rows, inner, kCus, (int64_t)((limit - L.vt_off) / part_bytes));
+    L.split = choose_key_split(d, L.tile_rows, inner, d->head_dim == 64 ? 2 * kCus : kCus, (int64_t)((limit - L.vt_off) / part_bytes));
     if (L.split.target > 0) {
       place((size_t)L.split.pieces);
       if (L.vt_off + align_up((size_t)L.split.parts * part_bytes) > limit) {  // (the longer item list takes room, too)
@@ -209,7 +214,7 @@ void layout_fwd(const chunk_attn_desc* desc, FwdLayout& L, bool with_plan, bool 
   if (!with_plan) return;
   L.wholes = plan_fwd(d, L.tile_rows);
   L.items = cut_items(L.wholes, L.split.target);
-  if (!pipe) L.jobs = tile_jobs(d, true, 64, nullptr);
+  if (d->head_dim > 128) L.jobs = tile_jobs(d, true, 64, nullptr);
 }
 
 // ---- the forward that allocates nothing (chunk_attn_fwd_static) ----
@@ -535,7 +540,7 @@ int chunk_attn_fwd(const chunk_attn_desc* desc, const void* q, const void* k, co
   p.head_splits = p.group / p.heads_per_wg;
   p.total_q = desc->total_q;
   p.scale_log2 = desc->softmax_scale * 1.4426950408889634f;
-  p.redo = pipelined(desc->head_dim) ? reinterpret_cast<int32_t*>(ws + L.flags_off) : nullptr;
+  p.redo = L.pipe ? reinterpret_cast<int32_t*>(ws + L.flags_off) : nullptr;
   p.taken = reinterpret_cast<int32_t*>(ws + L.flags_off) + L.whole_blocks;
   p.clock_log = clock_log(0);
   p.ref_limit = g_fwd_rescale_limit.load();
@@ -544,7 +549,7 @@ int chunk_attn_fwd(const chunk_attn_desc* desc, const void* q, const void* k, co
   ProfileEvents pe = profile_events();
   profile_events() = ProfileEvents{};
   if (pe.start && (e = hipEventRecord(pe.start, stream)) != hipSuccess) return hip_fail(e, "event record");
-  e = launch_fwd(p, desc->head_dim, (int)blocks, (int)L.whole_blocks, reinterpret_cast<const TileJob*>(ws + L.jobs_off),
+  e = launch_fwd(p, desc->head_dim, L.pipe, (int)blocks, (int)L.whole_blocks, reinterpret_cast<const TileJob*>(ws + L.jobs_off),
                  (int)L.jobs.size(), stream);
   if (e != hipSuccess) return hip_fail(e, "forward launch");
   if (pe.stop && (e = hipEventRecord(pe.stop, stream)) != hipSuccess) return hip_fail(e, "event record");
@@ -570,7 +575,7 @@ int chunk_attn_fwd_static(const chunk_attn_desc* desc, const void* q, const void
   for (int t = 0; t < desc->num_segments; ++t) segs.seg[t] = desc->segments[t];
   hipLaunchKernelGGL(plan_fwd_static_kernel, dim3(1), dim3(256), 0, stream, segs, desc->num_segments, L.tile_rows,
                      reinterpret_cast<FwdItem*>(ws + L.wholes_off), (int)L.n_wholes, reinterpret_cast<FwdItem*>(ws),
-                     L.split.target, reinterpret_cast<TileJob*>(ws + L.jobs_off), pipelined(desc->head_dim) ? 0 : (int)L.kv_tiles,
+                     L.split.target, reinterpret_cast<TileJob*>(ws + L.jobs_off), desc->head_dim <= 128 ? 0 : (int)L.kv_tiles,
                      reinterpret_cast<int32_t*>(ws + L.flags_off), (int)L.whole_blocks + kBlockQueues);
   if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "schedule kernel launch");
 
@@ -592,11 +597,11 @@ int chunk_attn_fwd_static(const chunk_attn_desc* desc, const void* q, const void
   p.head_splits = p.group / p.heads_per_wg;
   p.total_q = desc->total_q;
   p.scale_log2 = desc->softmax_scale * 1.4426950408889634f;
-  p.redo = pipelined(desc->head_dim) ? reinterpret_cast<int32_t*>(ws + L.flags_off) : nullptr;
+  p.redo = L.pipe ? reinterpret_cast<int32_t*>(ws + L.flags_off) : nullptr;
   p.taken = reinterpret_cast<int32_t*>(ws + L.flags_off) + L.whole_blocks;
   p.clock_log = clock_log(0);
   p.ref_limit = g_fwd_rescale_limit.load();
-  e = launch_fwd(p, desc->head_dim, (int)L.blocks, (int)L.whole_blocks, reinterpret_cast<const TileJob*>(ws + L.jobs_off),
+  e = launch_fwd(p, desc->head_dim, L.pipe, (int)L.blocks, (int)L.whole_blocks, reinterpret_cast<const TileJob*>(ws + L.jobs_off),
                  (int)L.kv_tiles, stream);
   if (e != hipSuccess) return hip_fail(e, "forward launch");
   return CHUNK_ATTN_OK;

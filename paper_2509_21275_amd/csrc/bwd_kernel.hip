@@ -1146,6 +1146,9 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(DkvParams p, int n
       step(g, x[0], x[1], f[0], f[1]);
       step(g + 1, x[1], x[0], f[1], f[0]);
     }
+    // the last step's reads ahead are nobody's operands; their registers stay taken until they have arrived
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(fr[i]));
     // every copy of this wave has landed (the last ones rewrote a slot nobody reads): once all waves have met at the
     // barrier that hands out the next block, the ring may be filled again
     __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
@@ -1183,7 +1186,424 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(DkvParams p, int n
 }
 
 // ------------------------------------------------------------------------------------------------
-// bwd_dq_pipe (head_dim 128 and 96)
+// bwd_dkv_narrow_pipe (head_dim 64)
+//
+// With half the head dimension a wave has the registers for all four contractions of its 64 keys (K and V fragments, dK^T and
+// dV^T accumulators: 192 accumulation registers), so there are no wave roles and no hand-over: a workgroup is two waves,
+// 128 keys, two workgroups per CU, one wave per SIMD.  Stage n is the n-th (head, 32-row query tile) of the walk, as in
+// bwd_dkv_pipe_kernel; in step g a wave runs
+//     dP(g) = dO V^T     dV^T += dO^T P(g-1)     dK^T += Q^T dS(g-1)     S(g+1) = Q K^T        (matrix pipe)
+//     P(g) = exp2(S(g) c - LSE)  and, once dP(g) is complete,  dS(g) = P(g) (dP(g) - D)         (vector)
+// as 16 mini-steps of one LDS operand fragment and the two MFMAs it feeds (one per 32-key block), each MFMA followed by its
+// share of the vector work.  Stages live in a ring of DIST + 3 slots (3 in use, DIST on their way).  Scores that a query
+// does not see, and whole stages past the end of the walk, are set to -inf in a rarely taken branch before their step.
+// The step is bound by what a single wave can issue: 32 MFMAs hold the matrix pipe for 1024 cycles, next to about 770
+// cycles of vector work and 32 LDS reads.  Against bwd_dkv_kernel (32 keys per wave, two roles, one MFMA per fragment):
+// packed 64K chunk, 32/8 heads, 6.28 -> 3.99 ms.
+// ------------------------------------------------------------------------------------------------
+template <int D>
+__global__ __launch_bounds__(128, 1) void bwd_dkv_narrow_pipe_kernel(DkvParams p, int num_blocks) {
+  constexpr int NW = 2;        // waves
+  constexpr int BM = 32;       // query rows per stage
+  constexpr int KC = D / 8;    // 16-byte chunks per operand row
+  constexpr int DK = D / 16;   // k-steps over the head dimension
+  constexpr int DB = D / 32;   // 32-row blocks of dK^T / dV^T
+  constexpr int QT = BM * D;   // elements per operand tile
+  constexpr int DIST = 3;      // stages copied ahead
+  constexpr int NS = DIST + 3; // ring slots: stages g - 1 .. g + 1 in use, g + 2 .. g + 1 + DIST on their way
+  constexpr int NF = 2 * DK + 4 * DB;  // fragments (mini-steps) per step: dO rows, dO^T, Q^T, Q rows
+  constexpr int T0 = DK, T1 = DK + 4 * DB;  // of which transposed
+  constexpr int AHEAD = 4, RING = 8;   // fragments in flight, registers of the fragment ring
+  constexpr int NP = BM * KC / 64;     // 64-slot pieces per tile
+  constexpr int PER = 2 * NP / NW;     // pieces per wave and stage
+  constexpr int CPS = PER + 1;         // copies per wave and stage: its pieces and one set of row values (LSE or D)
+  constexpr int RV = 64;               // floats per slot of the LSE / D rows (32 used; a whole wave copies them)
+  constexpr int EXP0 = 0, EXP1 = 9, DS0 = 7;  // mini-steps of the vector work (spread); dP(g) is complete after mini-step 3
+  constexpr int D_READ = 2, LSE_READ = NF - 3;  // mini-steps that read the D rows of this stage / the LSE rows of the next
+  constexpr int BOOK = NF - 2;
+  static_assert(D == 64 && NF == 16 && NF % RING == 0 && PER % 2 == 0 && 3 + 2 * PER < BOOK, "the schedule of a step");
+  // LDS instructions issued between the read of fragment m and the start of mini-step m (fragment_wait and the row values)
+  auto lds_wait = [](int m) constexpr {
+    int n = fragment_wait(NF, T0, T1, m);
+    for (int i = m - 4; i < m; ++i) {
+      const int k = (i + NF) % NF;
+      if (k == D_READ || k == LSE_READ) n += 4;
+    }
+    return m == 0 && n > 2 ? 2 : n;  // mini-step 0 also waits for the LSE rows: two fragments have been read since
+  };
+  static_assert(LSE_READ == NF - 3 && DS0 >= D_READ + 5, "the row values have arrived when they are first used");
+
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  lds_bf16* const L = (lds_bf16*)smem;
+  constexpr int Q_OFF = 0;                 // [NS][QT]  Q rows of stage n in slot n % NS (chunk-major)
+  constexpr int G_OFF = Q_OFF + NS * QT;   // [NS][QT]  dO rows
+  constexpr int R_OFF = G_OFF + NS * QT;   // [NS][RV] floats LSE rows, then [NS][RV] floats D rows
+  lds_f32* const lse_s = (lds_f32*)(L + R_OFF);
+  lds_f32* const dsum_s = lse_s + NS * RV;
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, hh = lane >> 5;
+
+  // persistent, as bwd_dkv_pipe_kernel
+  __shared__ int next_block;
+  const int xcd = xcd_of_this_wave();
+  auto start_in_step = [&](int b) __attribute__((always_inline)) {
+    if (b >= 0 && p.items[b / p.num_kv_heads].in_step) wait_for_earlier_groups(p.ended, b, p.side_by_side);
+  };
+  int blk = 0;
+  if (wave == 0) {
+    blk = block_claim_finish(p.taken, num_blocks, xcd, block_claim_issue(p.taken, xcd));
+    start_in_step(blk);
+  }
+  blk = broadcast_from_wave0(&next_block, blk);
+  while (blk >= 0) {
+  const int kvh = blk % p.num_kv_heads;
+  const DkvItem it = p.items[blk / p.num_kv_heads];
+  const int G = p.group;
+  const int64_t q_stride = (int64_t)p.num_q_heads * D, kv_stride = (int64_t)p.num_kv_heads * D;
+  const float c = p.scale_log2;
+
+  // the slots the prologue does not fill: slot NS - 1 (stage -1) is read in step 0
+  {
+    bf16x8 z;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) z[i] = (__bf16)0.0f;
+    for (int x = tid; x < (NS - DIST - 1) * QT / 8; x += NW * 64) {
+      lds_store8(L + Q_OFF + (DIST + 1) * QT + x * 8, z);
+      lds_store8(L + G_OFF + (DIST + 1) * QT + x * 8, z);
+    }
+  }
+
+  const int nqt = it.n_qt - it.qt_first;
+  const int n_iter = nqt * G;
+
+  // ---- staging (see bwd_dkv_pipe_kernel): copy i of a wave is piece (i % (PER / 2)) * 2 + wave of Q (i < PER / 2) or of dO ----
+  unsigned v_full[PER / 2], v_last[PER / 2];
+  {
+    const int last_row = it.q_len - 1 - (it.n_qt - 1) * BM;
+#pragma unroll
+    for (int i = 0; i < PER / 2; ++i) {
+      const int x = (i * NW + wave) * 64 + lane;
+      const int off = (x >> 5) * 8, row = (x & 31) ^ (((x >> 5) & 3) << 2);
+      v_full[i] = (unsigned)(row * (int)q_stride + off) * 2u;
+      v_last[i] = (unsigned)(min(row, last_row) * (int)q_stride + off) * 2u;
+    }
+  }
+  const bool down = it.reverse != 0;
+  const int qt_start = down ? it.n_qt - 1 : it.qt_first;
+  const int64_t roff0 = (int64_t)(it.q_row_seg + qt_start * BM) * q_stride + (int64_t)(kvh * G) * D;
+  const int64_t rv_first = ((int64_t)(kvh * G) * p.total_q_tiles + it.q_tile0) * 64 + qt_start * BM;
+  const char* d_q = reinterpret_cast<const char*>(p.q + roff0);
+  const char* d_g = reinterpret_cast<const char*>(p.d_o + roff0);
+  const char* d_r = reinterpret_cast<const char*>((wave ? p.dsp : p.lse2p) + rv_first);
+  const int64_t head_bytes = (int64_t)D * 2;
+  const int64_t head_rows_bytes = p.total_q_tiles * 64 * 4;
+  const int64_t tile_bytes = (down ? -1 : 1) * (int64_t)BM * q_stride * 2 - (G - 1) * head_bytes;
+  const int64_t tile_rows_bytes = (down ? -1 : 1) * (int64_t)BM * 4 - (G - 1) * head_rows_bytes;
+  int d_heads = G, d_tiles = nqt;
+  const int d_ragged = down ? nqt : 1;
+  unsigned d_slot = 0;  // element offset of the ring slot inside the Q / dO rings (slot index x QT)
+  const unsigned lane4 = (unsigned)lane * 4u;
+  lds_f32* const rows_dst = wave ? dsum_s : lse_s;
+  auto dma_rows = [&]() __attribute__((always_inline)) { dma4(d_r + lane4, rows_dst + d_slot / (QT / RV)); };
+  auto dma_piece = [&](int i) __attribute__((always_inline)) {
+    const bool of_q = i < PER / 2;
+    const int k = i % (PER / 2);
+    const unsigned voff = d_tiles == d_ragged ? v_last[k] : v_full[k];
+    lds_bf16* dst = L + (of_q ? Q_OFF : G_OFF) + (k * NW + wave) * 512 + d_slot;
+    dma16((of_q ? d_q : d_g) + voff, dst);
+  };
+  auto dma_advance = [&]() __attribute__((always_inline)) {
+    if (d_heads > 1) {
+      --d_heads;
+      d_q += head_bytes; d_g += head_bytes; d_r += head_rows_bytes;
+    } else {  // on to the next query tile; after the last stage, stay on it
+      const bool more = d_tiles > 1;
+      d_tiles -= more ? 1 : 0;
+      d_heads = more ? G : 1;
+      const int64_t tb = more ? tile_bytes : 0, tr = more ? tile_rows_bytes : 0;
+      d_q += tb; d_g += tb; d_r += tr;
+    }
+    d_slot = d_slot == (unsigned)((NS - 1) * QT) ? 0u : d_slot + (unsigned)QT;
+  };
+
+  // byte addresses of this lane's operand reads inside slot 0 of the Q ring; the dO ring is a constant further
+  unsigned ev0, od0, lo0, hi0;
+  {
+    const int j = lane & 15, cl = 2 * ((lane >> 4) & 1) + ((j & 3) >> 1), r0 = 4 * hh + (j >> 2);
+    ev0 = lds_addr(L + Q_OFF + cm_elem(l32, hh));
+    od0 = lds_addr(L + Q_OFF + cm_elem(l32, 2 + hh));
+    lo0 = lds_addr(L + Q_OFF + cm_elem(r0, cl) + 4 * (j & 1));
+    hi0 = lds_addr(L + Q_OFF + cm_elem(r0 + 8, cl) + 4 * (j & 1));
+  }
+  const unsigned lse0 = lds_addr(lse_s + 4 * hh);
+  constexpr unsigned SLOT = QT * 2;               // bytes per ring slot
+  constexpr int DO_RING = (G_OFF - Q_OFF) * 2;    // bytes from the Q ring to the dO ring
+  constexpr int D_ROWS = NS * RV * 4;             // bytes from the LSE rows to the D rows
+  auto load_rows = [&](unsigned ev_addr, unsigned od_addr, auto ks_c, auto ring_c) __attribute__((always_inline)) {
+    constexpr int ks = decltype(ks_c)::value;
+    constexpr int off = (ks >> 1) * (4 * 32 * 8) * 2 + decltype(ring_c)::value;
+    return lds_asm_read16<off>((ks & 1) ? od_addr : ev_addr);
+  };
+  auto load_t = [&](unsigned lo_addr, unsigned hi_addr, auto m_c, auto ring_c) __attribute__((always_inline)) {
+    constexpr int m = decltype(m_c)::value;  // ks2 * DB + db
+    constexpr int off = ((m / DB) * (16 * 8) + (m % DB) * (4 * 32 * 8)) * 2 + decltype(ring_c)::value;
+    const s16x4 lo = lds_asm_read_tr<off>(lo_addr);
+    const s16x4 hi = lds_asm_read_tr<off>(hi_addr);
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
+  constexpr std::integral_constant<int, 0> in_q{};
+  constexpr std::integral_constant<int, DO_RING> in_do{};
+
+  // K and V fragments (B operands): lane holds X[key = 64 wave + 32 kb + l32][16 ks + 8 hh ..+7]
+  bf16x8 kf[2][DK], vf[2][DK];
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb) {
+    const int64_t grow = it.kv_row0 + min(64 * wave + 32 * kb + l32, it.kv_rows - 1);
+    const int64_t off = grow * kv_stride + (int64_t)kvh * D + 8 * hh;
+#pragma unroll
+    for (int ks = 0; ks < DK; ++ks) {
+      kf[kb][ks] = *reinterpret_cast<const bf16x8*>(p.k + off + 16 * ks);
+      vf[kb][ks] = *reinterpret_cast<const bf16x8*>(p.v + off + 16 * ks);
+    }
+  }
+  // prologue: the copies of stages 0 .. DIST
+#pragma unroll
+  for (int s = 0; s <= DIST; ++s) {
+    dma_rows();
+#pragma unroll
+    for (int i = 0; i < PER; ++i) dma_piece(i);
+    dma_advance();
+  }
+  __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0), visible to the compiler
+  wg_barrier();
+
+  const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  f32x16 dk[2][DB], dv[2][DB];  // dK^T, dV^T: [D] x [32 keys of block kb]
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+    for (int db = 0; db < DB; ++db) dk[kb][db] = dv[kb][db] = zero16;
+  f32x16 x[2][2];       // S: [buffer][key block]
+  f32x16 dp[2];         // dP: [key block]
+  bf16x8 fp[2][2][2], fs[2][2][2];  // P and dS as B operands: [buffer][key block][k-step]
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) fp[b][kb][ks][i] = fs[b][kb][ks][i] = (__bf16)0.0f;
+  bf16x8 fr[RING];
+  f32x4 rl[4], rd[4];   // LSE and -D of rows 8 g4 + 4 hh + 0..3
+
+  // S(0), then the LSE rows of stage 0 and the first fragments of step 0 (dO rows of stage 0)
+  {
+    bf16x8 a[DK];
+    static_for<0, DK>([&](auto k_c) __attribute__((always_inline)) { a[decltype(k_c)::value] = load_rows(ev0, od0, k_c, in_q); });
+    static_for<0, 4>([&](auto g_c) __attribute__((always_inline)) { rl[decltype(g_c)::value] = lds_asm_read16f<32 * decltype(g_c)::value>(lse0); });
+    static_for<0, AHEAD>([&](auto k_c) __attribute__((always_inline)) { fr[decltype(k_c)::value] = load_rows(ev0, od0, k_c, in_do); });
+    asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(AHEAD) : "memory");
+#pragma unroll
+    for (int ks = 0; ks < DK; ++ks) asm volatile("" : "+v"(a[ks]));  // (after the wait, in this order)
+#pragma unroll
+    for (int g4 = 0; g4 < 4; ++g4) asm volatile("" : "+v"(rl[g4]));
+#pragma unroll
+    for (int ks = 0; ks < DK; ++ks)
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) {
+        f32x16& d_ = x[0][kb];
+        const bf16x8& b_ = kf[kb][ks];
+        if (ks == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d_) : "v"(a[ks]), "a"(b_));
+        else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d_) : "v"(a[ks]), "a"(b_));
+      }
+    mfma_settle();
+  }
+
+  // key index of this lane's column of block 0 relative to the context: query i of the segment sees the column of block kb
+  // iff i >= jrel + 32 kb
+  const int jrel = it.j0 + 64 * wave + l32 - it.ctx;
+  const int jrel_hi = it.j0 + 64 * wave + 63 - it.ctx;  // of the wave's last key
+  int s_cur = 0;        // slot of stage g
+  int s_qt = qt_start;  // query tile of stage g
+  int s_heads = G;      // heads of that tile still to come, counting stage g's
+
+  auto step = [&](int g, f32x16 (&cur)[2], f32x16 (&nxt)[2], bf16x8 (&p_old)[2][2], bf16x8 (&p_new)[2][2], bf16x8 (&s_old)[2][2],
+                  bf16x8 (&s_new)[2][2]) __attribute__((always_inline)) {
+    const int s_nxt = s_cur == NS - 1 ? 0 : s_cur + 1, s_prv = s_cur == 0 ? NS - 1 : s_cur - 1;
+    const unsigned c_ev = ev0 + s_cur * SLOT, c_od = od0 + s_cur * SLOT, n_ev = ev0 + s_nxt * SLOT, n_od = od0 + s_nxt * SLOT;
+    const unsigned t_lo = lo0 + s_prv * SLOT, t_hi = hi0 + s_prv * SLOT;
+    const unsigned r_cur = lse0 + s_cur * (RV * 4), r_nxt = lse0 + s_nxt * (RV * 4);
+    // entry (query 8 (i / 4) + 4 hh + i % 4 of the tile, column of block kb) is visible iff 8 (i / 4) + i % 4 >= lim + 32 kb
+    const bool valid = g < n_iter;
+    if (__builtin_expect(!valid || s_qt * BM < jrel_hi, 0)) {
+      const int lim = valid ? jrel - s_qt * BM - 4 * hh : 0x40000000;
+      asm volatile("s_nop 15\n\ts_nop 7" : "+v"(cur[0]), "+v"(cur[1]));  // S(g) has been written
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (8 * (i >> 2) + (i & 3) < lim + 32 * kb) cur[kb][i] = -INFINITY;
+    }
+    float pf[2][16];             // P(g)
+    unsigned pw[2][8], sw[2][8]; // P(g), dS(g), packed pairs
+    auto pack_p = [&](int j) __attribute__((always_inline)) {  // (one pair late: an exponential cannot be used by the next instruction)
+      bf16x2 w;
+      w[0] = (__bf16)pf[j >> 3][2 * (j & 7)]; w[1] = (__bf16)pf[j >> 3][2 * (j & 7) + 1];
+      unsigned wu = __builtin_bit_cast(unsigned, w);
+      asm volatile("" : "+v"(wu));
+      pw[j >> 3][j & 7] = wu;
+    };
+    auto exp_half = [&](auto x_c) __attribute__((always_inline)) {
+      constexpr int j = decltype(x_c)::value / 2, q = decltype(x_c)::value % 2, kb = j >> 3, i = 2 * (j & 7) + q;
+      if constexpr (j > 0 && q == 0) pack_p(j - 1);
+      pf[kb][i] = __builtin_amdgcn_exp2f(cur[kb][i] * c - rl[i >> 2][i & 3]);
+      asm volatile("" : "+v"(pf[kb][i]));
+    };
+    auto ds_pair = [&](auto j_c) __attribute__((always_inline)) {
+      constexpr int j = decltype(j_c)::value, kb = j >> 3, i = 2 * (j & 7);
+      bf16x2 w;
+      w[0] = (__bf16)(pf[kb][i] * (dp[kb][i] + rd[i >> 2][i & 3]));
+      w[1] = (__bf16)(pf[kb][i + 1] * (dp[kb][i + 1] + rd[i >> 2][(i & 3) + 1]));
+      unsigned wu = __builtin_bit_cast(unsigned, w);
+      asm volatile("" : "+v"(wu));
+      sw[kb][j & 7] = wu;
+    };
+    asm volatile("s_nop 7" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<0, NF>([&](auto m_c) __attribute__((always_inline)) {
+      constexpr int m = decltype(m_c)::value;
+      if constexpr (m == 0)
+        asm volatile("s_waitcnt lgkmcnt(%5)" : "+v"(fr[0]), "+v"(rl[0]), "+v"(rl[1]), "+v"(rl[2]), "+v"(rl[3]) : "n"(lds_wait(0)));
+      else if constexpr (m == DS0)
+        asm volatile("s_waitcnt lgkmcnt(%5)" : "+v"(fr[m % RING]), "+v"(rd[0]), "+v"(rd[1]), "+v"(rd[2]), "+v"(rd[3]) : "n"(lds_wait(m)));
+      else
+        asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(fr[m % RING]) : "n"(lds_wait(m)));
+      {  // read the fragment of mini-step m + AHEAD (past the end: the next step's dO rows)
+        constexpr int mm = m + AHEAD;
+        if constexpr (mm < T0) fr[mm % RING] = load_rows(c_ev, c_od, std::integral_constant<int, mm>{}, in_do);
+        else if constexpr (mm < T0 + 2 * DB) fr[mm % RING] = load_t(t_lo, t_hi, std::integral_constant<int, mm - T0>{}, in_do);
+        else if constexpr (mm < T1) fr[mm % RING] = load_t(t_lo, t_hi, std::integral_constant<int, mm - T0 - 2 * DB>{}, in_q);
+        else if constexpr (mm < NF) fr[mm % RING] = load_rows(n_ev, n_od, std::integral_constant<int, mm - T1>{}, in_q);
+        else fr[mm % RING] = load_rows(n_ev, n_od, std::integral_constant<int, mm - NF>{}, in_do);
+      }
+      const bf16x8 fa = fr[m % RING];
+      auto mma = [&](auto kb_c) __attribute__((always_inline)) {
+        constexpr int kb = decltype(kb_c)::value;
+        const bf16x8& a_ = fa;  // (named references: variables used only inside an asm statement are not captured)
+        if constexpr (m < T0) {
+          f32x16& d_ = dp[kb];
+          const bf16x8& b_ = vf[kb][m];
+          if (m == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d_) : "v"(a_), "a"(b_));
+          else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d_) : "v"(a_), "a"(b_));
+        } else if constexpr (m < T0 + 2 * DB) {
+          constexpr int ks = (m - T0) / DB, db = (m - T0) % DB;
+          dv[kb][db] = mfma32(fa, p_old[kb][ks], dv[kb][db]);
+        } else if constexpr (m < T1) {
+          constexpr int ks = (m - T0 - 2 * DB) / DB, db = (m - T0 - 2 * DB) % DB;
+          dk[kb][db] = mfma32(fa, s_old[kb][ks], dk[kb][db]);
+        } else {
+          constexpr int ks = m - T1;
+          f32x16& d_ = nxt[kb];
+          const bf16x8& b_ = kf[kb][ks];
+          if (ks == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d_) : "v"(a_), "a"(b_));
+          else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d_) : "v"(a_), "a"(b_));
+        }
+      };
+      constexpr int e0 = 2 * spread(16, EXP0, EXP1, m - 1), e1 = 2 * spread(16, EXP0, EXP1, m), em = e0 + (e1 - e0 + 1) / 2;
+      constexpr int s0 = spread(16, DS0, NF, m - 1), s1 = spread(16, DS0, NF, m), sm = s0 + (s1 - s0 + 1) / 2;
+      static_assert(2 * s1 <= e0 || e0 == 32, "a pair's exponentials come before its dS");
+      mma(std::integral_constant<int, 0>{});
+      static_for<e0, em>(exp_half);
+      static_for<s0, sm>(ds_pair);
+      if constexpr (m == D_READ) {
+        rd[0] = lds_asm_read16f<D_ROWS>(r_cur);
+        rd[1] = lds_asm_read16f<D_ROWS + 32>(r_cur);
+        rd[2] = lds_asm_read16f<D_ROWS + 64>(r_cur);
+        rd[3] = lds_asm_read16f<D_ROWS + 96>(r_cur);
+      }
+      if constexpr (m == LSE_READ) {
+        rl[0] = lds_asm_read16f<0>(r_nxt);
+        rl[1] = lds_asm_read16f<32>(r_nxt);
+        rl[2] = lds_asm_read16f<64>(r_nxt);
+        rl[3] = lds_asm_read16f<96>(r_nxt);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      mma(std::integral_constant<int, 1>{});
+      static_for<em, e1>(exp_half);
+      static_for<sm, s1>(ds_pair);
+      if constexpr (m == EXP1 - 1) pack_p(15);
+      if constexpr (m >= 3 && m < 3 + 2 * PER && ((m - 3) & 1) == 0) dma_piece((m - 3) >> 1);
+      if constexpr (m == 3 + 2 * PER) dma_rows();
+      if constexpr (m == BOOK) {  // bookkeeping for the next step (this step's copies have been issued)
+        dma_advance();
+        s_cur = s_nxt;
+        if (--s_heads == 0) {
+          s_heads = G;
+          s_qt += down ? -1 : 1;
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        const u32x4 pv = {pw[kb][4 * ks], pw[kb][4 * ks + 1], pw[kb][4 * ks + 2], pw[kb][4 * ks + 3]};
+        const u32x4 sv = {sw[kb][4 * ks], sw[kb][4 * ks + 1], sw[kb][4 * ks + 2], sw[kb][4 * ks + 3]};
+        p_new[kb][ks] = __builtin_bit_cast(bf16x8, pv);
+        s_new[kb][ks] = __builtin_bit_cast(bf16x8, sv);
+      }
+    // stage g + 2 must have landed; the copies of the DIST - 1 stages after it may still be in flight
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((DIST - 1) * CPS) : "memory");
+    wg_barrier();
+  };
+  // the last products are those of stage n - 1 in step n; a pair of steps may run one past that, which contributes nothing
+  int pending_claim = 0;
+  const int claim_at = max(0, n_iter - 3) & ~1;  // the step pair before which wave 0 claims the next block
+  for (int g = 0; g <= n_iter; g += 2) {
+    if (g == claim_at && wave == 0) pending_claim = block_claim_issue(p.taken, xcd);
+    step(g, x[0], x[1], fp[0], fp[1], fs[0], fs[1]);
+    step(g + 1, x[1], x[0], fp[1], fp[0], fs[1], fs[0]);
+  }
+  // the last step's reads ahead are nobody's operands; their registers stay taken until they have arrived
+#pragma unroll
+  for (int i = 0; i < 4; ++i) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(fr[i]), "+v"(rl[i]));
+  // every copy of this wave has landed: once both waves have met at the barrier that hands out the next block, the ring
+  // may be filled again
+  __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
+
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb) {
+    const int kr = 64 * wave + 32 * kb + l32;
+    if (kr < it.kv_rows) {
+      const int64_t off = ((int64_t)it.kv_row0 + kr) * kv_stride + (int64_t)kvh * D;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int64_t e = off + 32 * db + 8 * g + 4 * hh;
+          dkv_store4(p, p.dv, e, dv[kb][db][4 * g], dv[kb][db][4 * g + 1], dv[kb][db][4 * g + 2], dv[kb][db][4 * g + 3]);
+          dkv_store4(p, p.dk, e, dk[kb][db][4 * g] * p.scale, dk[kb][db][4 * g + 1] * p.scale, dk[kb][db][4 * g + 2] * p.scale,
+                     dk[kb][db][4 * g + 3] * p.scale);
+        }
+    }
+  }
+  // on to the next block; the stores of the epilogue are not waited for here
+  int nb = 0;
+  if (wave == 0) {
+    if (lane == 0) __hip_atomic_fetch_add(p.ended + (blk & 7), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    nb = block_claim_finish(p.taken, num_blocks, xcd, pending_claim);
+    start_in_step(nb);
+  }
+  blk = broadcast_from_wave0(&next_block, nb);
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
+// bwd_dq_pipe (head_dim 128, 96 and, with long walks, 64)
 //
 // The dQ kernel in the style of bwd_dkv_pipe_kernel: one wave per SIMD, a workgroup of 4 waves, each wave
 // owning two 32-row query blocks ("units": the workgroup's 8 units are the same (head, row block) pairs the
@@ -1191,7 +1611,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(DkvParams p, int n
 // the t-th 32-key tile of the segment; in step t a wave runs
 //     dP^T(t) = V(t) dO^T        S^T(t+1) = K(t+1) Q^T        dQ^T += K(t-1)^T dS^T(t-1)      (matrix pipe)
 //     P^T(t) = exp2(S^T(t) c - LSE)  and, once dP^T(t) is complete,  dS^T(t) = P^T(t) (dP^T(t) - D)   (vector)
-// as 24 (head_dim 96: 18) mini-steps of one LDS operand fragment and the two MFMAs it feeds (one per unit), each MFMA followed
+// as 24 (head_dim 96: 18, 64: 12) mini-steps of one LDS operand fragment and the two MFMAs it feeds (one per unit), each MFMA followed
 // by its share of the vector work.  K^T is read from the K tile itself with the LDS transpose read (tiles
 // are stored chunk-major as in the dK/dV kernels), so no transposed image of K is needed.  K and V tiles
 // live in a ring of DIST + 3 slots.  Steps whose tile needs the causal mask (the last one or two of the
@@ -1212,12 +1632,12 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_pipe_kernel(DqParams p, int num
   constexpr int RING = NF % 8 == 0 ? 8 : 6;  // registers of the fragment ring: a step starts where the ring does
   constexpr int NP = BN * KC / 64;     // 64-slot pieces per tile
   constexpr int PER = 2 * NP / NW;     // global->LDS copies per wave and stage
-  constexpr int BOOK = 12;             // mini-step of the bookkeeping, behind the last copy
+  constexpr int BOOK = D == 64 ? 8 : 12;  // mini-step of the bookkeeping, behind the last copy
   // Vector work of a step: the 16 pairs' exponentials in mini-steps EXP0 .. EXP1 - 1, their dS from DS0 on (dP^T is
   // complete two mini-steps before), spread evenly.  head_dim 128: one pair of exponentials per mini-step from 6 on (the first
   // six are left to the MFMAs alone: measured 1 % faster than starting with 0, and faster than starting with 2, 4 or
   // 8), dS one pair per mini-step from 10 on and two in the last two.
-  constexpr int EXP0 = D == 128 ? 6 : 4, EXP1 = D == 128 ? 22 : 16, DS0 = DK + 2;
+  constexpr int EXP0 = D == 128 ? 6 : D == 96 ? 4 : 2, EXP1 = D == 128 ? 22 : D == 96 ? 16 : 9, DS0 = DK + 2;
   auto exp_done = [](int m) constexpr { return spread(16, EXP0, EXP1, m); };
   auto ds_done = [](int m) constexpr { return D == 128 && m < 22 ? spread(12, DS0, 22, m) : D == 128 ? 12 + 2 * (m - 21) : spread(16, DS0, NF, m); };
   static_assert(2 * NP % NW == 0 && NF % RING == 0 && RING > AHEAD && 3 + 2 * (PER - 1) < BOOK && BOOK < NF, "the schedule of a step");
@@ -1539,6 +1959,9 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_pipe_kernel(DqParams p, int num
     step(t + 1, x[1], x[0], f[1], f[0], std::true_type{});
   }
 
+  // the last step's reads ahead are nobody's operands; their registers stay taken until they have arrived
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(fr[i]));
   // every copy of this wave has landed (the last ones rewrote a slot nobody reads): after the barrier below the next
   // block may fill the ring again
   __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
@@ -1628,6 +2051,12 @@ size_t n_dkv_blocks(const chunk_attn_desc* d) {
   return n;
 }
 
+// Key blocks from which on head_dim 64 runs bwd_dkv_narrow_pipe_kernel: two blocks per CU.  With fewer of them half of the chip's
+// SIMDs would have no wave, and bwd_dkv_kernel, which puts eight waves on a block, ends earlier.  Measured backward, one and the
+// other kernel (8 key/value heads): 256 blocks 61 / 74 us and (32 query heads) 148 / 174, 512 blocks 150 / 141, 1024 blocks
+// of 256-token sequences 228 / 227, 1024 blocks of 2048-token sequences 811 / 696, 2048 blocks 7573 / 6451.
+constexpr int64_t kMinDkvPipeBlocks64 = 2 * kCus;
+
 // Raises a kernel's dynamic-LDS limit; callers keep the result in a function-local static, so that it happens once per
 // process and is safe from several threads.
 template <class K>
@@ -1653,7 +2082,7 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
                        P.q_tiles, d->total_q, d->num_q_heads, lse2p, dsp);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  if constexpr (!pipelined(D)) {  // the pipelined dQ kernel reads K^T from its K tiles
+  if (!P.dq_pipe) {  // the pipelined dQ kernel reads K^T from its K tiles
     if ((e = launch_transpose(a.k, d->num_kv_heads, D, 32, kjobs, (int)P.kjobs.size(), P.kv32_tiles, kt, stream)) != hipSuccess) return e;
   }
 
@@ -1679,30 +2108,37 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
     p.items = reinterpret_cast<const DqItem*>(ws + P.dq_items_off);
     p.total_kv32_tiles = P.kv32_tiles; p.total_q_tiles = P.q_tiles;
     p.num_q_heads = d->num_q_heads; p.num_kv_heads = d->num_kv_heads; p.group = group;
-    p.heads_per_wg = heads_per_wg(group, dq_waves(D)); p.head_splits = group / p.heads_per_wg;
+    p.heads_per_wg = heads_per_wg(group, P.dq_waves); p.head_splits = group / p.heads_per_wg;
     p.scale = d->softmax_scale; p.scale_log2 = d->softmax_scale * kLog2e;
     p.parts = reinterpret_cast<float*>(ws + P.fdq_off);  // (the one-pass backward's dQ tiles: only one of the two runs)
     p.taken = reinterpret_cast<int32_t*>(ws + P.queues_off);
     p.clock_log = clock_log(1);
     const int64_t blocks = (int64_t)P.dq_items.size() * d->num_kv_heads * p.head_splits;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    if constexpr (pipelined(D)) {
-      // ring slots of a K and a V tile, then the staging tiles of the four waves (64 rows each)
-      const size_t smem = (size_t)2 * (DQ_PIPE_DIST + 3) * 32 * D * 2 + (size_t)4 * 64 * D * 2;
-      static const hipError_t attr = raise_smem_limit(&bwd_dq_pipe_kernel<D>, smem);
-      if (attr != hipSuccess) return attr;
-      hipLaunchKernelGGL((bwd_dq_pipe_kernel<D>), dim3((unsigned)persistent_grid(blocks)), dim3(256), smem, stream, p, (int)blocks);
-      if (P.n_dq_cut > 0) {
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        hipLaunchKernelGGL((bwd_dq_merge_kernel<D>), dim3((unsigned)(P.n_dq_cut * d->num_kv_heads * p.head_splits)), dim3(512), 0, stream, p,
-                           reinterpret_cast<const DqItem*>(ws + P.dq_cut_off));
+    if constexpr (D <= 128) {
+      if (P.dq_pipe) {
+        // ring slots of a K and a V tile, then the staging tiles of the four waves (64 rows each)
+        const size_t smem = (size_t)2 * (DQ_PIPE_DIST + 3) * 32 * D * 2 + (size_t)4 * 64 * D * 2;
+        static const hipError_t attr = raise_smem_limit(&bwd_dq_pipe_kernel<D>, smem);
+        if (attr != hipSuccess) return attr;
+        hipLaunchKernelGGL((bwd_dq_pipe_kernel<D>), dim3((unsigned)persistent_grid(blocks)), dim3(256), smem, stream, p, (int)blocks);
+        if constexpr (pipelined(D)) {
+          if (P.n_dq_cut > 0) {
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+            hipLaunchKernelGGL((bwd_dq_merge_kernel<D>), dim3((unsigned)(P.n_dq_cut * d->num_kv_heads * p.head_splits)), dim3(512), 0,
+                               stream, p, reinterpret_cast<const DqItem*>(ws + P.dq_cut_off));
+          }
+        }
       }
-    } else {
-      const size_t smem = (size_t)9 * 32 * D * 2;  // 3 stages of K, V and K^T tiles
-      constexpr int DQW = 4;
-      static const hipError_t attr = raise_smem_limit(&bwd_dq_kernel<D, DQW>, smem);
-      if (attr != hipSuccess) return attr;
-      hipLaunchKernelGGL((bwd_dq_kernel<D, DQW>), dim3((unsigned)blocks), dim3(DQW * 64), smem, stream, p);
+    }
+    if constexpr (!pipelined(D)) {
+      if (!P.dq_pipe) {
+        const size_t smem = (size_t)9 * 32 * D * 2;  // 3 stages of K, V and K^T tiles
+        constexpr int DQW = 4;
+        static const hipError_t attr = raise_smem_limit(&bwd_dq_kernel<D, DQW>, smem);
+        if (attr != hipSuccess) return attr;
+        hipLaunchKernelGGL((bwd_dq_kernel<D, DQW>), dim3((unsigned)blocks), dim3(DQW * 64), smem, stream, p);
+      }
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
@@ -1734,13 +2170,26 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
       if (pe.start && (e = hipEventRecord(pe.start, stream)) != hipSuccess) return e;
       hipLaunchKernelGGL((bwd_dkv_pipe_kernel<D>), dim3((unsigned)persistent_grid(blocks)), dim3(256), smem, stream, p, (int)blocks);
     } else {
-      // 4 ring slots of two 32-row operand tiles, 2 P hand-over slots, 4 slots of LSE and D rows
-      constexpr int KB = (D > 128 ? 64 : DKV_KEYS) / 32;   // as dkv_keys(D)
-      const size_t smem = (size_t)8 * 32 * D * 2 + 2 * KB * 1024 * 2 + 2 * 4 * 64 * sizeof(float);
-      static const hipError_t attr = raise_smem_limit(&bwd_dkv_kernel<D, KB>, smem);
-      if (attr != hipSuccess) return attr;
-      if (pe.start && (e = hipEventRecord(pe.start, stream)) != hipSuccess) return e;
-      hipLaunchKernelGGL((bwd_dkv_kernel<D, KB>), dim3((unsigned)blocks), dim3(KB * 128), smem, stream, p);
+      if constexpr (D == 64) {
+        if (P.dkv_pipe) {
+          // 6 ring slots of two 32-row operand tiles and their LSE and D rows
+          const size_t smem = (size_t)2 * 6 * 32 * D * 2 + 2 * 6 * 64 * sizeof(float);
+          static const hipError_t attr = raise_smem_limit(&bwd_dkv_narrow_pipe_kernel<D>, smem);
+          if (attr != hipSuccess) return attr;
+          if (pe.start && (e = hipEventRecord(pe.start, stream)) != hipSuccess) return e;
+          hipLaunchKernelGGL((bwd_dkv_narrow_pipe_kernel<D>), dim3((unsigned)persistent_grid(blocks, 2)), dim3(128), smem, stream, p,
+                             (int)blocks);
+        }
+      }
+      if (!P.dkv_pipe) {
+        // 4 ring slots of two 32-row operand tiles, 2 P hand-over slots, 4 slots of LSE and D rows
+        constexpr int KB = (D > 128 ? 64 : DKV_KEYS) / 32;   // as dkv_keys(D)
+        const size_t smem = (size_t)8 * 32 * D * 2 + 2 * KB * 1024 * 2 + 2 * 4 * 64 * sizeof(float);
+        static const hipError_t attr = raise_smem_limit(&bwd_dkv_kernel<D, KB>, smem);
+        if (attr != hipSuccess) return attr;
+        if (pe.start && (e = hipEventRecord(pe.start, stream)) != hipSuccess) return e;
+        hipLaunchKernelGGL((bwd_dkv_kernel<D, KB>), dim3((unsigned)blocks), dim3(KB * 128), smem, stream, p);
+      }
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (pe.stop && (e = hipEventRecord(pe.stop, stream)) != hipSuccess) return e;
@@ -1753,8 +2202,15 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
 void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, bool may_cut) {
   P = BwdPlan{};
   const int group = d->num_q_heads / d->num_kv_heads;
-  const int dq_rows = tile_rows(group, dq_waves(d->head_dim));
   const bool pipe = d->head_dim == 128;
+  P.dq_waves = pipe ? 8 : 4;
+  P.dq_pipe = P.dkv_pipe = pipe;
+  if (d->head_dim == 64) {
+    P.dq_pipe = pipe_pays(count_walks(d, tile_rows(group, 8)), d->num_kv_heads * (group / heads_per_wg(group, 8)));
+    if (P.dq_pipe) P.dq_waves = 8;
+    P.dkv_pipe = (int64_t)n_dkv_blocks(d) * d->num_kv_heads >= kMinDkvPipeBlocks64;
+  }
+  const int dq_rows = tile_rows(group, P.dq_waves);
   P.q_tiles = count_tiles(d, false, 64);
   P.kv32_tiles = count_tiles(d, true, 32);
   P.qt32_tiles = count_tiles(d, false, 32);
@@ -1763,7 +2219,7 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, bool may_c
   P.fused = d->head_dim == 128 && bwd_mode() == 2;
   size_t n_dq = 0, n_dkv = 0;
   if (pipe && may_cut && !P.fused) {
-    const int inner = d->num_kv_heads * (group / heads_per_wg(group, dq_waves(d->head_dim)));
+    const int inner = d->num_kv_heads * (group / heads_per_wg(group, P.dq_waves));
     P.split = choose_key_split(d, dq_rows, inner, kCus, (int64_t)(dq_tile_bytes / ((size_t)inner * kPartRowFloats * sizeof(float))));
   }
   if (with_plan) {
@@ -1778,7 +2234,7 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, bool may_c
       P.dkv_items = plan_dkv(d, dkv_keys(d->head_dim), side_by_side);
     }
     P.qjobs = tile_jobs(d, false, 64, nullptr);
-    if (!pipe) P.kjobs = tile_jobs(d, true, 32, nullptr);
+    if (!P.dq_pipe) P.kjobs = tile_jobs(d, true, 32, nullptr);
   }
   // the layout does not depend on which backward runs: item counts follow from the segment table
   for (int t = 0; t < d->num_segments; ++t) {

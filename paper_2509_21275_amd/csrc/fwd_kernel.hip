@@ -11,10 +11,11 @@
 //
 // Two kernels:
 //   fwd_kernel       online softmax with a lazily moved reference maximum, one 32-row query block per wave,
-//                    two waves per SIMD, tiles of 64 keys (K row-major, V as the pre-transposed image of
-//                    transpose_kernel.hip, double-buffered).  Used for head_dim 64 and 256, and for head_dim 128
-//                    (V read transposed from row tiles, no image) as the second pass below.
-//   fwd_pipe_kernel  head_dim 128: one wave per SIMD with 64 query rows, software pipelined over stages of 32
+//                    two waves per SIMD or more, tiles of 64 keys (K row-major, V as rows that are read transposed or,
+//                    for head_dim 256, as the pre-transposed image of transpose_kernel.hip, double-buffered).  Used
+//                    for head_dim 256, for 64 unless its walks are long (pipe_pays), and as the second pass below.
+//                    head_dim 64 without the image and its launch: four sequences of 1024, 32/8 heads, 51 -> 42 us.
+//   fwd_pipe_kernel  head_dim 96 and 128, and 64 with two workgroups per CU: one wave per SIMD with 64 query rows, software pipelined over stages of 32
 //                    keys, reference maximum fixed by the first stage; rows whose scores outgrow it are
 //                    flagged and recomputed by fwd_kernel, launched right after.  Where a chunk has too few items for
 //                    the chip their walks are cut into pieces (plan.hpp); the pieces leave float32 partial results, which
@@ -80,7 +81,7 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
   constexpr int DB = D / 32;   // 32-row blocks of O^T
   constexpr int KT = BN * D;   // elements per K tile and per V^T image
   constexpr int WR = 32 * QB;  // query rows per wave
-  constexpr bool IMG = !pipelined(D);  // V arrives as a transposed image; else as rows, two chunk-major tiles of 32
+  constexpr bool IMG = D > 128;  // V arrives as a transposed image; else as rows, two chunk-major tiles of 32
 
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   __bf16* Ks = reinterpret_cast<__bf16*>(smem);  // [2][BN][D]  swizzled rows
@@ -96,7 +97,7 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
   const FwdItem it = (IMG ? p.items : p.wholes)[blockIdx.x / inner_n];
   const int kvh = inner % p.num_kv_heads, hs = inner / p.num_kv_heads;
   if constexpr (!IMG) {  // second pass: only what the pipelined kernel left to do
-    if (p.redo[blockIdx.x] == 0) {
+    if (p.redo != nullptr && p.redo[blockIdx.x] == 0) {
       if (it.part >= 0) fwd_merge_parts<D>(p, it, kvh, hs, inner, inner_n, wave, lane);
       return;
     }
@@ -232,6 +233,21 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
           s1[qb] = mfma32(a1, qf[qb][ks], ks == 0 ? zero16 : s1[qb]);
         }
       }
+      // head_dim 64: the V^T fragments are read here, so that they arrive while the exponentials are computed
+      s16x4 v_lo[4][DB], v_hi[4][DB];
+      auto read_vt = [&](auto ks_c) __attribute__((always_inline)) {
+        static_for<0, DB>([&](auto db_c) __attribute__((always_inline)) {
+          constexpr int ks = decltype(ks_c)::value, db = decltype(db_c)::value;
+          constexpr int off = ((ks >> 1) * (32 * D) + (ks & 1) * (16 * 8) + db * (4 * 32 * 8)) * 2;
+          v_lo[ks][db] = lds_asm_read_tr<off>(vt_lo + buf * (KT * 2));
+          v_hi[ks][db] = lds_asm_read_tr<off>(vt_hi + buf * (KT * 2));
+        });
+      };
+      if constexpr (D == 64) {
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<0, 4>(read_vt);
+        __builtin_amdgcn_sched_barrier(0);
+      }
       bf16x8 pf[QB][4];
 #pragma unroll
       for (int qb = 0; qb < QB; ++qb) {
@@ -301,22 +317,14 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
           }
         }
       } else {
-        const unsigned lo_addr = vt_lo + buf * (KT * 2), hi_addr = vt_hi + buf * (KT * 2);
         static_for<0, 4>([&](auto ks_c) __attribute__((always_inline)) {
           constexpr int ks = decltype(ks_c)::value;
-          s16x4 lo[DB], hi[DB];
-          static_for<0, DB>([&](auto db_c) __attribute__((always_inline)) {
-            constexpr int db = decltype(db_c)::value;
-            constexpr int off = ((ks >> 1) * (32 * D) + (ks & 1) * (16 * 8) + db * (4 * 32 * 8)) * 2;
-            lo[db] = lds_asm_read_tr<off>(lo_addr);
-            hi[db] = lds_asm_read_tr<off>(hi_addr);
-          });
-          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-          for (int db = 0; db < DB; ++db) asm volatile("" : "+v"(lo[db]), "+v"(hi[db]));  // (after the wait, in this order)
+          if constexpr (D != 64) read_vt(ks_c);
+          if constexpr (D != 64 || ks == 0) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
           for (int db = 0; db < DB; ++db) {
-            const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo[db], hi[db], 0, 1, 2, 3, 4, 5, 6, 7));
+            asm volatile("" : "+v"(v_lo[ks][db]), "+v"(v_hi[ks][db]));  // (after the wait, in this order)
+            const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(v_lo[ks][db], v_hi[ks][db], 0, 1, 2, 3, 4, 5, 6, 7));
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) oacc[qb][db] = mfma32(a, pf[qb][ks], oacc[qb][db]);
           }
@@ -357,14 +365,14 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
 }
 
 // ------------------------------------------------------------------------------------------------
-// Pipelined forward for head_dim 128 and 96: one wave per SIMD, 64 query rows per wave (two 32-row "units"), keys
+// Pipelined forward for head_dim 128, 96 and 64: one wave per SIMD (64: two), 64 query rows per wave (two 32-row "units"), keys
 // streamed in stages of 32.
 //
 // A wave issues at most one instruction every four cycles and an MFMA holds the matrix pipe for 32, so the loop
 // is laid out instruction by instruction.  In step t a wave runs
 //     O^T += V(t-1)^T P^T(t-1)        S^T(t+1) = K(t+1) Q^T        (matrix pipe)
 //     P^T(t) = exp2(S^T(t) c - m c) and its row sums                (vector pipe)
-// as 16 (head_dim 96: 12) mini-steps of one LDS operand fragment and the two MFMAs it feeds (one per unit), each MFMA
+// as 16 (head_dim 96: 12, 64: 8) mini-steps of one LDS operand fragment and the two MFMAs it feeds (one per unit), each MFMA
 // followed by its share of the vector work of 32 scores.  K and V tiles are copied global->LDS into a ring of DIST + 3 slots, stored
 // chunk-major; V^T is read from the V tile itself with the LDS transpose read.  Fragments are fetched four
 // mini-steps ahead with opaque LDS reads and explicit lgkmcnt waits; S^T lives in vector registers, where the
@@ -375,7 +383,7 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
 // the step that masks in the vector work.
 // ------------------------------------------------------------------------------------------------
 template <int D>
-__global__ __launch_bounds__(256, 1) void fwd_pipe_kernel(FwdParams p, int num_blocks) {
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void fwd_pipe_kernel(FwdParams p, int num_blocks) {
   constexpr int NW = 4;        // waves
   constexpr int BN = 32;       // key rows per stage
   constexpr int KC = D / 8;    // 16-byte chunks per K / V row
@@ -385,11 +393,11 @@ __global__ __launch_bounds__(256, 1) void fwd_pipe_kernel(FwdParams p, int num_b
   constexpr int DIST = FWD_PIPE_DIST;  // stages copied ahead
   constexpr int NS = DIST + 3; // ring slots: stages t - 1 .. t + 1 in use, t + 2 .. t + 1 + DIST on their way
   constexpr int NF = 2 * DB + DK;      // operand fragments (mini-steps) per step: V^T, then K rows
-  constexpr int AHEAD = 4;             // fragments in flight
-  constexpr int RING = NF % 8 == 0 ? 8 : 6;  // registers of the fragment ring: a step starts where the ring does
+  constexpr int AHEAD = D == 64 ? 3 : 4;  // fragments in flight
+  constexpr int RING = D == 64 ? 4 : NF % 8 == 0 ? 8 : 6;  // registers of the fragment ring: a step starts where the ring does
   constexpr int NP = BN * KC / 64;     // 64-slot pieces per tile
   constexpr int PER = 2 * NP / NW;     // global->LDS copies per wave and stage
-  constexpr int BOOK = NF - 4;         // mini-step of the bookkeeping, behind the last copy
+  constexpr int BOOK = D == 64 ? NF - 2 : NF - 4;  // mini-step of the bookkeeping, behind the last copy
   static_assert(2 * NP % NW == 0 && NF % RING == 0 && RING > AHEAD && 3 + 2 * (PER - 1) < BOOK, "the schedule of a step");
 
   extern __shared__ __attribute__((aligned(1024))) char smem[];
@@ -448,23 +456,34 @@ __global__ __launch_bounds__(256, 1) void fwd_pipe_kernel(FwdParams p, int num_b
   // ---- staging: the 2 NP pieces of a stage (NP of K, then NP of V) are dealt to the waves round robin; a piece is
   // 64 consecutive slots of a chunk-major tile = two chunk columns of 32 rows.  Past the last stage the last one is
   // copied again. ----
-  unsigned v_full[PER], v_last[PER];  // byte offset of the lane's chunk from the tile's first row: full tile, last tile
-  {
-    const int last_row = n_wg - 1 - (nt - 1) * BN;  // rows past the last key repeat it (masked)
+  // byte offset of the lane's chunk from the tile's first row: full tile, last tile (rows past the last key repeat it,
+  // masked; head_dim 64, short of registers, computes it when it comes to the last tile)
+  const int last_row = n_wg - 1 - (nt - 1) * BN;
+  auto chunk_off = [&](int i, int ln, int max_row) __attribute__((always_inline)) {
+    const int x = ((i * NW + wave) % NP) * 64 + ln;
+    const int off = (x >> 5) * 8, row = (x & 31) ^ (((x >> 5) & 3) << 2);
+    return (unsigned)(min(row, max_row) * (int)kv_stride + off) * 2u;
+  };
+  unsigned v_full[PER], v_last[PER];
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int x = ((i * NW + wave) % NP) * 64 + lane;
-      const int off = (x >> 5) * 8, row = (x & 31) ^ (((x >> 5) & 3) << 2);
-      v_full[i] = (unsigned)(row * (int)kv_stride + off) * 2u;
-      v_last[i] = (unsigned)(min(row, last_row) * (int)kv_stride + off) * 2u;
-    }
+  for (int i = 0; i < PER; ++i) {
+    v_full[i] = chunk_off(i, lane, BN);
+    v_last[i] = D == 64 ? 0 : chunk_off(i, lane, last_row);
   }
   int d_t = 0, d_slot = 0;   // stage to copy next (clamped to the last one) and its slot
   int64_t d_off = 0;         // element offset of its first row
   auto dma_piece = [&](int i) __attribute__((always_inline)) {
     const int piece = i * NW + wave;  // wave-uniform; the first NP are pieces of K, the others of V
     const bool of_k = NP % NW == 0 ? i < NP / NW : piece < NP;
-    const unsigned voff = d_t == nt - 1 ? v_last[i] : v_full[i];
+    unsigned voff = d_t == nt - 1 ? v_last[i] : v_full[i];
+    if constexpr (D == 64) {
+      voff = v_full[i];
+      if (__builtin_expect(d_t == nt - 1, 0)) {
+        int ln = threadIdx.x & 63;
+        asm volatile("" : "+v"(ln));  // (computed here and not ahead of the loop)
+        voff = chunk_off(i, ln, last_row);
+      }
+    }
     const char* base = reinterpret_cast<const char*>((of_k ? Kg : Vg) + d_off);
     lds_bf16* dst = L + (of_k ? K_OFF + piece * 512 : V_OFF + (piece - NP) * 512) + d_slot * KT;
     dma16(base + voff, dst);
@@ -592,7 +611,7 @@ __global__ __launch_bounds__(256, 1) void fwd_pipe_kernel(FwdParams p, int num_b
   bool risk = false;
   const float big = __builtin_amdgcn_exp2f(p.ref_limit);
 
-  // In program order mini-step m reads fragment m + 4: the transposed fragments (0 .. 2 DB - 1 of this step, 0 .. 3 of the
+  // In program order mini-step m reads fragment m + AHEAD: the transposed fragments (0 .. 2 DB - 1 of this step, 0 .. AHEAD - 1 of the
   // next) take two instructions, the rows fragments one.
   int sV = 0;  // slot of stage t
   auto step = [&](int t, f32x16 (&cur)[2], f32x16 (&nxt)[2], bf16x8 (&f_old)[2][2], bf16x8 (&f_new)[2][2],
@@ -647,7 +666,7 @@ __global__ __launch_bounds__(256, 1) void fwd_pipe_kernel(FwdParams p, int num_b
     __builtin_amdgcn_sched_barrier(0);
     static_for<0, NF>([&](auto m_c) __attribute__((always_inline)) {
       constexpr int m = decltype(m_c)::value;
-      asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(fr[m % RING]) : "n"(fragment_wait(NF, 0, 2 * DB, m)));
+      asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(fr[m % RING]) : "n"(fragment_wait(NF, 0, 2 * DB, m, AHEAD)));
       {  // read the fragment of mini-step m + AHEAD (past the end: the next step's first transposed fragments)
         constexpr int mm = m + AHEAD;
         if constexpr (mm < 2 * DB) fr[mm % RING] = load_t(t_lo, t_hi, std::integral_constant<int, mm>{});
@@ -714,6 +733,9 @@ __global__ __launch_bounds__(256, 1) void fwd_pipe_kernel(FwdParams p, int num_b
     step(t, x[0], x[1], f[0], f[1], std::true_type{});
     step(t + 1, x[1], x[0], f[1], f[0], std::true_type{});
   }
+  // the last step's reads ahead are nobody's operands; their registers stay taken until they have arrived
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(fr[i]));
   // every copy of this wave has landed (the last ones rewrote a slot nobody reads): after the barrier below the next
   // block may fill the ring again
   __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
@@ -799,7 +821,7 @@ static hipError_t launch_fwd_pipe(const FwdParams& p, int num_blocks, int num_wh
   const size_t smem = (size_t)2 * (FWD_PIPE_DIST + 3) * 32 * D * 2 + (size_t)4 * 64 * D * 2;
   static const hipError_t attr = raise_smem_limit(&fwd_pipe_kernel<D>, smem);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL((fwd_pipe_kernel<D>), dim3(persistent_grid(num_blocks)), dim3(256), smem, stream, p, num_blocks);
+  hipLaunchKernelGGL((fwd_pipe_kernel<D>), dim3(persistent_grid(num_blocks, D == 64 ? 2 : 1)), dim3(256), smem, stream, p, num_blocks);
   hipError_t e;
   if ((e = hipGetLastError()) != hipSuccess) return e;
   // Second pass over the whole items, 8 waves of 32 rows: a workgroup returns at once unless its flag is raised (the item
@@ -807,16 +829,18 @@ static hipError_t launch_fwd_pipe(const FwdParams& p, int num_blocks, int num_wh
   return launch_fwd_t<D, 8>(p, num_wholes, stream);
 }
 
-hipError_t launch_fwd(const FwdParams& p, int head_dim, int num_blocks, int num_wholes, const TileJob* vjobs, int num_vjobs,
-                      hipStream_t stream) {
-  if (!pipelined(head_dim)) {
+hipError_t launch_fwd(const FwdParams& p, int head_dim, bool pipe, int num_blocks, int num_wholes, const TileJob* vjobs,
+                      int num_vjobs, hipStream_t stream) {
+  if (head_dim == 256) {
     hipError_t e;
     if ((e = launch_transpose(p.v, p.num_kv_heads, head_dim, 64, vjobs, num_vjobs, p.total_kv_tiles, const_cast<__bf16*>(p.vt),
                               stream)) != hipSuccess) return e;
-    return head_dim == 256 ? launch_fwd_t<256, 4>(p, num_blocks, stream) : launch_fwd_t<64, 4>(p, num_blocks, stream);
+    return launch_fwd_t<256, 4>(p, num_blocks, stream);
   }
-  return head_dim == 96 ? launch_fwd_pipe<96>(p, num_blocks, num_wholes, stream)
-                        : launch_fwd_pipe<128>(p, num_blocks, num_wholes, stream);
+  if (!pipe) return launch_fwd_t<64, 4>(p, num_blocks, stream);
+  return head_dim == 64 ? launch_fwd_pipe<64>(p, num_blocks, num_wholes, stream)
+         : head_dim == 96 ? launch_fwd_pipe<96>(p, num_blocks, num_wholes, stream)
+                          : launch_fwd_pipe<128>(p, num_blocks, num_wholes, stream);
 }
 
 }  // namespace chunk_attn

@@ -40,11 +40,9 @@ struct FwdParams {
 // over as many query heads of one group as divide both (so that the key/value tiles they stream are shared).
 // forward: 4 waves; for head_dim 128 each wave owns two 32-row query blocks (fwd_pipe_kernel; its second pass,
 // fwd_kernel with 8 waves of one block, covers the same rows per workgroup)
-// head dimensions that the software-pipelined kernels are instantiated for
+// head dimensions that always run the software-pipelined kernels (64 does from a size on, pipe_pays)
 constexpr bool pipelined(int head_dim) { return head_dim == 96 || head_dim == 128; }
 inline int fwd_waves(int) { return 4; }
-inline int fwd_qblocks(int head_dim) { return pipelined(head_dim) ? 2 : 1; }
-inline int dq_waves(int head_dim) { return pipelined(head_dim) ? 8 : 4; }
 inline int heads_per_wg(int group, int waves) {
   int h = 1;
   while (h * 2 <= waves && group % (h * 2) == 0) h *= 2;
@@ -54,14 +52,14 @@ inline int heads_per_wg(int group, int waves) {
 inline int dkv_keys(int head_dim) { return head_dim > 128 ? 64 : DKV_KEYS; }
 inline int tile_rows(int group, int waves) { return 32 * (waves / heads_per_wg(group, waves)); }
 
-// Workgroups launched by a kernel whose workgroups claim their blocks themselves (device_common.hpp): one per CU of the
+// Workgroups launched by a kernel whose workgroups claim their blocks themselves (device_common.hpp): one (`per_cu`) per CU of the
 // current device, and never more than there are blocks.
-inline int persistent_grid(int64_t blocks) {
+inline int persistent_grid(int64_t blocks, int per_cu = 1) {
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
       cus <= 0)
     cus = 256;
-  return (int)std::max<int64_t>(1, std::min<int64_t>(blocks, cus));
+  return (int)std::max<int64_t>(1, std::min<int64_t>(blocks, (int64_t)cus * per_cu));
 }
 constexpr int kBlockQueues = 8;  // counters per kernel that claims its blocks
 constexpr int kCus = 256;        // compute units of an MI355X (plans that must not depend on where they are made)
@@ -69,6 +67,13 @@ constexpr int kCus = 256;        // compute units of an MI355X (plans that must 
 // rows][up to 16 accumulator quarters][64 lanes][4] float32; for the forward then [8 units][32 rows] {reference maximum, sum}.
 constexpr int kPartRowFloats = 8 * 16 * 64 * 4;
 constexpr int kPartFloats = kPartRowFloats + 8 * 32 * 2;
+
+// Whether a query-stationary kernel of head_dim 64 runs as the pipelined one: its workgroups start and end more slowly than
+// the other kernel's, which has three or four of them on a CU, so it needs two blocks per CU and walks of 64 stages on
+// average.  Measured, other -> pipelined, 32/8 heads: 8192 queries on 32768 keys (906 stages) forward 2086 -> 1934 us,
+// backward 6355 -> 6065; four sequences of 4096 (64) 349 -> 340, 1166 -> 1130; eight of 2048 (34) 206 -> 209, 672 -> 661;
+// sixteen of 1024 (18) 128 -> 147, 403 -> 417; 128 blocks of 1008 stages 460 -> 541, 1085 -> 1132.
+inline bool pipe_pays(const Walks& w, int inner) { return w.items * inner >= 2 * kCus && w.stages >= 64 * w.items; }
 
 // Events armed by chunk_attn_profile_events for the calling thread (null when disarmed).
 struct ProfileEvents {
@@ -101,6 +106,8 @@ struct BwdPlan {
   size_t lse2p_off = 0, dsp_off = 0, kt_off = 0, total = 0;
   // one-pass backward (head_dim 128): its items and workgroup order travel at the end of the blob; then the per-wave
   // progress counters and the status word (cleared by a kernel on every call) and the float32 dQ tiles
+  bool dq_pipe = false, dkv_pipe = false;  // the pipelined kernels run (head_dim 96 and 128 always, 256 never)
+  int dq_waves = 0;                        // 32-row units of a dQ workgroup
   bool fused = false;
   FusedPlan fplan;
   int64_t qt32_tiles = 0;
@@ -124,9 +131,10 @@ std::vector<char> bwd_blob(const BwdPlan& plan);
 // Enqueues the backward kernels; the blob must already be on its way to the workspace on `stream`.
 hipError_t launch_bwd(const chunk_attn_desc* d, const BwdArgs& a, const BwdPlan& plan, hipStream_t stream);
 
-// The forward kernels of one call over `num_blocks` blocks (items x inner) cut from `num_wholes`.  `vjobs` (device) lists
-// the 64-row tiles of V whose transposed images p.vt receives (head_dim 64 and 256).
-hipError_t launch_fwd(const FwdParams& p, int head_dim, int num_blocks, int num_wholes, const TileJob* vjobs, int num_vjobs,
+// The forward kernels of one call over `num_blocks` blocks (items x inner) cut from `num_wholes`: the pipelined kernel and its
+// second pass, or fwd_kernel alone (head_dim 256, and 64 unless `pipe`).  `vjobs` (device) lists the 64-row tiles of V whose
+// transposed images p.vt receives (head_dim 256).
+hipError_t launch_fwd(const FwdParams& p, int head_dim, bool pipe, int num_blocks, int num_wholes, const TileJob* vjobs, int num_vjobs,
                       hipStream_t stream);
 
 // Transposed tile images (width 64 or 32 rows) of x[rows][num_heads][head_dim]:

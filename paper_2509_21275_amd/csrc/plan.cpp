@@ -128,6 +128,18 @@ std::vector<DqItem> plan_dq(const chunk_attn_desc* d, int tile_rows) {
   return items;
 }
 
+Walks count_walks(const chunk_attn_desc* d, int tile_rows) {
+  Walks w;
+  for (int t = 0; t < d->num_segments; ++t) {
+    const chunk_attn_seg& s = d->segments[t];
+    for (int32_t i0 = 0; i0 < s.q_len; i0 += tile_rows) {
+      ++w.items;
+      w.stages += walk_stages(s.kv_len - s.q_len + i0 + 1, std::min<int32_t>(tile_rows, s.q_len - i0));
+    }
+  }
+  return w;
+}
+
 // The estimate, in stages (one 32-key step of a workgroup, about a microsecond).  A block costs its walk plus kStart
 // for filling the pipeline and writing its rows; a piece kPart more for its float32 rows (twice the bytes).  The blocks of
 // queue 0 (every eighth one) are dealt, longest first, to an eighth of the compute units as they become free.  Putting

@@ -127,6 +127,11 @@ CHUNK_ATTN_HD inline int piece_count(int stages, int n0, int target) {
   return n < 1 ? 1 : n;
 }
 CHUNK_ATTN_HD inline int walk_stages(int n0, int q_rows) { return (n0 + q_rows - 1 + kStageKeys - 1) / kStageKeys; }
+// Query-stationary items of a chunk and the stages they walk together.
+struct Walks {
+  int64_t items = 0, stages = 0;
+};
+Walks count_walks(const chunk_attn_desc* d, int tile_rows);
 struct KeySplit {
   int target = 0;      // argument of piece_count; 0: nothing is cut
   int64_t pieces = 0;  // items to run (pieces and whole items)

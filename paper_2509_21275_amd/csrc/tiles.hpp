@@ -197,11 +197,11 @@ __host__ __device__ constexpr int spread(int n, int first, int last, int m) {
   return m < first ? 0 : m >= last - 1 ? n : n * (m - first + 1) / (last - first);
 }
 // LDS instructions issued between the read of fragment m and the start of mini-step m, where the wait for it stands: the
-// reads of the three fragments after it (fragments are read four mini-steps ahead).  Of a step's `nf` fragments those from
+// reads of the fragments after it (fragments are read `ahead` mini-steps ahead).  Of a step's `nf` fragments those from
 // t_first to t_last - 1 are transposed, two instructions each; the ones past the end are the next step's first.
-__host__ __device__ constexpr int fragment_wait(int nf, int t_first, int t_last, int m) {
+__host__ __device__ constexpr int fragment_wait(int nf, int t_first, int t_last, int m, int ahead = 4) {
   int n = 0;
-  for (int k = m + 1; k <= m + 3; ++k) n += k % nf >= t_first && k % nf < t_last ? 2 : 1;
+  for (int k = m + 1; k < m + ahead; ++k) n += k % nf >= t_first && k % nf < t_last ? 2 : 1;
   return n;
 }
 static_assert(fragment_wait(16, 0, 8, 0) == 6 && fragment_wait(16, 0, 8, 5) == 5 && fragment_wait(16, 0, 8, 12) == 3 &&

@@ -55,8 +55,7 @@ hipError_t launch_transpose(const __bf16* x, int num_heads, int head_dim, int wi
   if (num_jobs == 0) return hipSuccess;
   const int64_t blocks = (int64_t)num_jobs * num_heads;
   if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-  if (head_dim == 64 && width == 64) launch_t<64, 64>(x, num_heads, jobs, blocks, total_tiles, out, stream);
-  else if (head_dim == 64 && width == 32) launch_t<64, 32>(x, num_heads, jobs, blocks, total_tiles, out, stream);
+  if (head_dim == 64 && width == 32) launch_t<64, 32>(x, num_heads, jobs, blocks, total_tiles, out, stream);
   else if (head_dim == 256 && width == 64) launch_t<256, 64>(x, num_heads, jobs, blocks, total_tiles, out, stream);
   else if (head_dim == 256 && width == 32) launch_t<256, 32>(x, num_heads, jobs, blocks, total_tiles, out, stream);
   else return hipErrorInvalidValue;

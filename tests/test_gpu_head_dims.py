@@ -124,3 +124,53 @@ def test_pipelined_kernels_of_head_dim_96(oracle_mod, name, segs, Hq, Hkv):
     for a, b in zip(got, ref):
         b = b if b.dim() == 2 else b[..., :96]
         assert rel_err(a, b.double().cpu().numpy()) <= 2.0 ** -7
+
+
+@pytest.mark.parametrize("name,segs,Hq,Hkv", [
+    # 64 key/value heads: enough blocks for the pipelined kernels of head_dim 64 on short chunks
+    ("dkv_ragged", [(0, 1000, 0, 1000), (1000, 33, 1000, 160)], 64, 64),          # 10 key blocks x 64, walks of 34 stages
+    ("dkv_groups_and_gaps", [(0, 130, 3, 900), (130, 1, 910, 129), (131, 95, 1041, 127)], 128, 64),
+    ("all_pipelined", [(0, 1100, 0, 2600)], 64, 64),                              # 5 x 64 query items of 54 .. 82 stages
+    ("all_pipelined_gqa4", [(0, 2050, 0, 4000)], 64, 16),
+])
+def test_pipelined_kernels_of_head_dim_64(oracle_mod, name, segs, Hq, Hkv):
+    """Chunks with enough blocks (and, for forward and dQ, long enough walks) for head_dim 64's pipelined kernels: ragged key
+    blocks and query tiles, rows outside key ranges, accumulation; against the oracle on one head group of each end.  (LSE:
+    the forward that is not pipelined sums the probabilities as rounded to bf16, 2^-9 of the sum at most.)"""
+    tq, tkv = max(s[0] + s[1] for s in segs), max(s[2] + s[3] for s in segs) + 2
+    case = synth.ChunkCase(f"{name}_d64", [synth.Seg(*s) for s in segs], tq, tkv, Hq, Hkv, 64, 700 + len(name))
+    q, k, v, do = make_inputs(case)
+    got = run_gpu(case, q, k, v, do)
+    again = run_gpu(case, q, k, v, do)
+    assert all(torch.equal(a, b) for a, b in zip(got, again))
+    init = torch.full_like(k, 3.0)
+    acc = run_gpu(case, q, k, v, do, accumulate=True, dk_init=init, dv_init=init)
+    cov = np.zeros(tkv, dtype=bool)
+    for s in segs:
+        cov[s[2]:s[2] + s[3]] = True
+    o, lse, dq, dk, dv = got
+    assert torch.all(dk.cpu()[~cov] == 0) and torch.all(acc[3].cpu()[~cov] == 3.0) and torch.all(acc[4].cpu()[~cov] == 3.0)
+    G = Hq // Hkv
+    for h in (0, Hkv - 1):
+        qs = slice(h * G, (h + 1) * G)
+        orc = oracle_mod.Oracle(case.segs, q[:, qs].cpu().contiguous(), k[:, h:h + 1].cpu().contiguous(), v[:, h:h + 1].cpu().contiguous(),
+                                do[:, qs].cpu().contiguous(), case.scale)
+        O, LSE = orc.forward(); dQ, dK, dV = orc.backward()
+        errs = (rel_err(o[:, qs], O), float(np.abs(lse[qs].double().cpu().numpy() - LSE).max()), rel_err(dq[:, qs], dQ), rel_err(dk[:, h:h + 1], dK), rel_err(dv[:, h:h + 1], dV))
+        print(case.name, h, errs, flush=True)
+        assert errs[0] <= TOL_O and errs[1] <= 2.0 ** -9 + 1e-4 and max(errs[2:]) <= TOL_GRAD
+        assert rel_err(acc[3][:, h:h + 1].cpu()[cov], dK[cov] + 3.0) <= TOL_GRAD and rel_err(acc[4][:, h:h + 1].cpu()[cov], dV[cov] + 3.0) <= TOL_GRAD
+
+
+def test_second_pass_of_head_dim_64(oracle_mod):
+    """The pipelined forward of head_dim 64 with every item sent to its second pass (probabilities rounded to bf16 are summed
+    there: 2^-9 of the sum at most, as much in its logarithm)."""
+    case = synth.ChunkCase("redo_d64", [synth.Seg(0, 1100, 0, 2600)], 1100, 2600, 64, 64, 64, 77)
+    q, k, v, _ = make_inputs(case)
+    ca.chunk_attn_test_set_fwd_rescale_limit(-1e30)
+    try:
+        o, lse = run_gpu(case, q, k, v, backward=False)
+    finally:
+        ca.chunk_attn_test_set_fwd_rescale_limit(60.0)
+    O, LSE = oracle_mod.Oracle(case.segs, q[:, 5:6].cpu().contiguous(), k[:, 5:6].cpu().contiguous(), v[:, 5:6].cpu().contiguous(), None, case.scale).forward()
+    assert rel_err(o[:, 5:6], O) <= TOL_O and float(np.abs(lse[5:6].double().cpu().numpy() - LSE).max()) <= 2.0 ** -9 + 1e-4
