@@ -1603,6 +1603,437 @@ __global__ __launch_bounds__(128, 1) void bwd_dkv_narrow_pipe_kernel(DkvParams p
 }
 
 // ------------------------------------------------------------------------------------------------
+// bwd_dkv_wide_pipe (head_dim 256)
+//
+// One wave per SIMD, a workgroup of 4 waves covers 64 keys.  A dK^T or dV^T accumulator for 64 keys takes 256 registers, so the
+// waves have three roles: wave 0, 1 (score waves, 32 keys each, K and V fragments in accumulation registers) run in step g
+//     dP(g) = dO V^T     S(g+1) = Q K^T     P(g) = exp2(S(g) c - LSE),  dS(g) = P(g) (dP(g) - D)
+// and hand P(g) and dS(g) (bf16) over through LDS; wave 2 runs dV^T += dO^T P(g-1), wave 3 dK^T += Q^T dS(g-1), both for all
+// 64 keys.  Every wave has 32 MFMAs per step; a fragment of the gradient waves feeds two of them, one of the score waves one
+// (for both to feed two, S and dP would have to sit in different waves, and Q or dO wait two steps longer in an LDS that
+// has no room for it).  Stage n is the n-th (head, 32-row query tile) of the walk.  LDS is full: five stages of Q (g - 1 and
+// g + 1 in use in step g, g in between, g + 2 and g + 3 on their way) and four of dO (g - 1 and g in use, g + 1 and g + 2 on
+// their way), so that every copy has more than a step to land.  (With four of each, copies had to land within their step and
+// the waves waited for them more than half of the time.)  That leaves room for one P and one dS, so a step has a second
+// barrier in its middle, between the gradient waves' reads of the hand-over and the score waves' next stores; and the score
+// waves do not read ahead over the end of a step, but begin it with exponentials while their first fragments arrive.
+// Against bwd_dkv_kernel (the same split as for head_dim 64, 32 keys per wave, no pipelining): packed 64K chunk, 32/8 heads,
+// 23.8 -> 16.2 ms.
+// ------------------------------------------------------------------------------------------------
+template <int D>
+__global__ __launch_bounds__(256, 1) void bwd_dkv_wide_pipe_kernel(DkvParams p, int num_blocks) {
+  constexpr int NW = 4;        // waves
+  constexpr int BM = 32;       // query rows per stage
+  constexpr int KC = D / 8;    // 16-byte chunks per operand row
+  constexpr int DK = D / 16;   // k-steps over the head dimension
+  constexpr int DB = D / 32;   // 32-row blocks of dK^T / dV^T
+  constexpr int QT = BM * D;   // elements per operand tile
+  constexpr int NSQ = 5, NSG = 4;  // ring slots of Q and dO
+  constexpr int NP = BM * KC / 64;     // 64-slot pieces per tile
+  constexpr int AHEAD = 4, RING = 8;   // fragments in flight, registers of the fragment ring
+  constexpr int PS = 2 * 2 * 64 * 8;   // elements of P or dS of a stage: 2 key blocks x 2 k-steps x 64 lanes x 8
+  constexpr int RV = 64;               // floats per slot of the LSE / D rows (32 used; a whole wave copies them)
+  constexpr int PER_A = 2, PER_W = NP - PER_A;  // pieces a score wave / a gradient wave copies per stage
+  static_assert(D == 256 && PER_A % 2 == 0 && PER_W <= 2 * DB, "the schedule of a step");
+
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  lds_bf16* const L = (lds_bf16*)smem;
+  constexpr int Q_OFF = 0;                 // [NSQ][QT]  Q rows of stage n in slot n % NSQ (chunk-major)
+  constexpr int G_OFF = Q_OFF + NSQ * QT;  // [NSG][QT]  dO rows
+  constexpr int P_OFF = G_OFF + NSG * QT;  // [PS]       P hand-over
+  constexpr int S_OFF = P_OFF + PS;        // [PS]       dS hand-over
+  constexpr int R_OFF = S_OFF + PS;        // [NSQ][RV] floats LSE rows, then [NSG][RV] floats D rows
+  lds_f32* const lse_s = (lds_f32*)(L + R_OFF);
+  lds_f32* const dsum_s = lse_s + NSQ * RV;
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, hh = lane >> 5;
+
+  // persistent, as bwd_dkv_pipe_kernel
+  __shared__ int next_block;
+  const int xcd = xcd_of_this_wave();
+  auto start_in_step = [&](int b) __attribute__((always_inline)) {
+    if (b >= 0 && p.items[b / p.num_kv_heads].in_step) wait_for_earlier_groups(p.ended, b, p.side_by_side);
+  };
+  int blk = 0;
+  if (wave == 0) {
+    blk = block_claim_finish(p.taken, num_blocks, xcd, block_claim_issue(p.taken, xcd));
+    start_in_step(blk);
+  }
+  blk = broadcast_from_wave0(&next_block, blk);
+  while (blk >= 0) {
+  int pending_claim = 0;
+  const int kvh = blk % p.num_kv_heads;
+  const DkvItem it = p.items[blk / p.num_kv_heads];
+  const int G = p.group;
+  const int64_t q_stride = (int64_t)p.num_q_heads * D, kv_stride = (int64_t)p.num_kv_heads * D;
+  const float c = p.scale_log2;
+
+  // what step 0 reads of stage -1: the rings' last slots and the hand-over
+  {
+    bf16x8 z;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) z[i] = (__bf16)0.0f;
+    for (int x = tid; x < QT / 8; x += NW * 64) {
+      lds_store8(L + Q_OFF + (NSQ - 1) * QT + x * 8, z);
+      lds_store8(L + G_OFF + (NSG - 1) * QT + x * 8, z);
+    }
+    for (int x = tid; x < 2 * PS / 8; x += NW * 64) lds_store8(L + P_OFF + x * 8, z);
+  }
+
+  const int n_iter = (it.n_qt - it.qt_first) * G;  // stages
+
+  // ---- staging: waves 0 and 3 copy Q (wave 0 also the LSE rows), waves 1 and 2 dO (wave 1 also the D rows); the NP pieces of
+  // a tile (a piece is two chunk columns of 32 rows) are dealt unevenly, PER_A to the score wave.  Past the last stage the
+  // last one is copied again. ----
+  const bool score_wave = wave < 2;
+  const bool of_q = wave == 0 || wave == 3;
+  const int first_piece = score_wave ? 0 : PER_A;
+  unsigned v_full[2], v_last[2];  // byte offset of the lane's chunk of an even / odd piece, without the piece's columns
+  {
+    const int last_row = it.q_len - 1 - (it.n_qt - 1) * BM;
+#pragma unroll
+    for (int par = 0; par < 2; ++par) {
+      const int row = l32 ^ (((2 * par + hh) & 3) << 2);
+      v_full[par] = (unsigned)(row * (int)q_stride + hh * 8) * 2u;
+      v_last[par] = (unsigned)(min(row, last_row) * (int)q_stride + hh * 8) * 2u;
+    }
+  }
+  const bool down = it.reverse != 0;
+  const int qt_start = down ? it.n_qt - 1 : it.qt_first;
+  const int64_t rv_first = ((int64_t)(kvh * G) * p.total_q_tiles + it.q_tile0) * 64 + qt_start * BM;
+  const char* d_x = reinterpret_cast<const char*>((of_q ? p.q : p.d_o) + (int64_t)(it.q_row_seg + qt_start * BM) * q_stride + (int64_t)(kvh * G) * D) +
+                    first_piece * 32;
+  const char* d_r = reinterpret_cast<const char*>((wave ? p.dsp : p.lse2p) + rv_first);
+  const int64_t head_bytes = (int64_t)D * 2;
+  const int64_t head_rows_bytes = p.total_q_tiles * 64 * 4;
+  const int64_t tile_bytes = (down ? -1 : 1) * (int64_t)BM * q_stride * 2 - (G - 1) * head_bytes;  // from the last head to the first, next tile
+  const int64_t tile_rows_bytes = (down ? -1 : 1) * (int64_t)BM * 4 - (G - 1) * head_rows_bytes;
+  int d_heads = G, d_tiles = it.n_qt - it.qt_first;
+  const int d_ragged = down ? d_tiles : 1;  // d_tiles while the segment's last query tile is the one to copy
+  lds_bf16* const ring = L + (of_q ? Q_OFF : G_OFF) + first_piece * 512;
+  const unsigned ring_end = (unsigned)(((of_q ? NSQ : NSG) - 1) * QT);
+  unsigned d_slot = 0;  // element offset of the slot inside the ring (slot index x QT)
+  const unsigned lane4 = (unsigned)lane * 4u;
+  lds_f32* const rows_dst = wave ? dsum_s : lse_s;
+  auto dma_rows = [&]() __attribute__((always_inline)) { dma4(d_r + lane4, rows_dst + d_slot / (QT / RV)); };
+  auto dma_piece = [&](int i) __attribute__((always_inline)) {  // (the first piece of every wave is even)
+    const unsigned voff = d_tiles == d_ragged ? v_last[i & 1] : v_full[i & 1];
+    dma16(d_x + i * 32 + voff, ring + i * 512 + d_slot);
+  };
+  auto dma_advance = [&]() __attribute__((always_inline)) {
+    if (d_heads > 1) {
+      --d_heads;
+      d_x += head_bytes; d_r += head_rows_bytes;
+    } else {  // on to the next query tile; after the last stage, stay on it
+      const bool more = d_tiles > 1;
+      d_tiles -= more ? 1 : 0;
+      d_heads = more ? G : 1;
+      d_x += more ? tile_bytes : 0;
+      d_r += more ? tile_rows_bytes : 0;
+    }
+    d_slot = d_slot == ring_end ? 0u : d_slot + (unsigned)QT;
+  };
+  const int ahead = of_q ? 3 : 2;  // stages copied before step 0
+  constexpr unsigned SLOT = QT * 2;  // bytes per ring slot
+  const int claim_at = max(0, n_iter - 3) & ~1;  // the step pair before which wave 0 claims the next block
+
+  if (score_wave) {
+    // ================= score waves: 32 keys, S, P, dP, dS =================
+    bf16x8 kf[DK], vf[DK];  // B operands: lane holds X[key = 32 wave + l32][16 ks + 8 hh ..+7]
+    {
+      const int64_t off = ((int64_t)it.kv_row0 + min(32 * wave + l32, it.kv_rows - 1)) * kv_stride + (int64_t)kvh * D + 8 * hh;
+#pragma unroll
+      for (int ks = 0; ks < DK; ++ks) {
+        kf[ks] = *reinterpret_cast<const bf16x8*>(p.k + off + 16 * ks);
+        vf[ks] = *reinterpret_cast<const bf16x8*>(p.v + off + 16 * ks);
+      }
+    }
+    for (int s = 0; s < ahead; ++s) {
+      dma_rows();
+#pragma unroll
+      for (int i = 0; i < PER_A; ++i) dma_piece(i);
+      dma_advance();
+    }
+    __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0), visible to the compiler
+    wg_barrier();
+
+    constexpr int NF = 2 * DK;  // fragments (mini-steps of one MFMA): dO rows of stage g, Q rows of stage g + 1
+    // vector work: exponentials 0 .. EXP_PRE - 1 before the first mini-step, the others spread over mini-steps EXP0 .. EXP1 - 1,
+    // the pairs of dS over DS0 .. DS1 - 1; dP(g) is complete after mini-step DK - 1
+    constexpr int EXP_PRE = 6, EXP0 = 0, EXP1 = 14, DS0 = 19, DS1 = 28;
+    constexpr int P_WRITE = 16, S_WRITE0 = 24, S_WRITE1 = 28, D_READ = 4, LSE_READ = 20;
+    static_assert(spread(8, DS0, DS1, S_WRITE0 - 1) >= 4 && spread(8, DS0, DS1, S_WRITE1 - 1) == 8 && DS0 >= DK + 3, "dS before its stores");
+    // LDS instructions of mini-step k after its fragment read, and the wait for fragment m: the instructions issued between
+    // its read (four mini-steps before; those of 0 .. 3 at the start of the step) and mini-step m
+    auto extra = [](int k) constexpr {
+      return (k == P_WRITE || k == P_WRITE + 1 || k == S_WRITE0 || k == S_WRITE1 || (k >= D_READ && k < D_READ + 4) ||
+              (k >= LSE_READ && k < LSE_READ + 4)) ? 1 : 0;
+    };
+    auto lds_wait = [extra](int m) constexpr {
+      int n = NF - 1 - m < AHEAD - 1 ? NF - 1 - m : AHEAD - 1;
+      for (int i = m < AHEAD ? 0 : m - AHEAD; i < m; ++i) n += extra(i);
+      return n;
+    };
+
+    const unsigned ev0 = lds_addr(L + Q_OFF + cm_elem(l32, hh)), od0 = lds_addr(L + Q_OFF + cm_elem(l32, 2 + hh));
+    constexpr int DO_RING = (G_OFF - Q_OFF) * 2;  // bytes from the Q ring to the dO ring: added to the address
+    const unsigned lse0 = lds_addr(lse_s + 4 * hh);
+    constexpr int D_ROWS = NSQ * RV * 4;
+    const unsigned hand0 = lds_addr(L + P_OFF + wave * 1024 + lane * 8);
+    auto load_rows = [&](unsigned ev_addr, unsigned od_addr, auto ks_c) __attribute__((always_inline)) {
+      constexpr int ks = decltype(ks_c)::value;
+      return lds_asm_read16<(ks >> 1) * (4 * 32 * 8) * 2>((ks & 1) ? od_addr : ev_addr);
+    };
+    f32x16 x[2], dp;
+    f32x4 rl[4], rd[4];  // LSE and -D of rows 8 g4 + 4 hh + 0..3
+    bf16x8 fr[RING];
+    {  // S(0), the LSE rows of stage 0
+      static_for<0, 2>([&](auto half_c) __attribute__((always_inline)) {
+        constexpr int k0 = decltype(half_c)::value * (DK / 2);
+        bf16x8 a[DK / 2];
+        static_for<0, DK / 2>([&](auto k_c) __attribute__((always_inline)) {
+          a[decltype(k_c)::value] = load_rows(ev0, od0, std::integral_constant<int, k0 + decltype(k_c)::value>{});
+        });
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int k = 0; k < DK / 2; ++k) asm volatile("" : "+v"(a[k]));  // (after the wait, in this order)
+#pragma unroll
+        for (int k = 0; k < DK / 2; ++k) {
+          f32x16& d_ = x[0];
+          const bf16x8& b_ = kf[k0 + k];
+          if (k0 + k == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d_) : "v"(a[k]), "a"(b_));
+          else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d_) : "v"(a[k]), "a"(b_));
+        }
+      });
+      static_for<0, 4>([&](auto g_c) __attribute__((always_inline)) { rl[decltype(g_c)::value] = lds_asm_read16f<32 * decltype(g_c)::value>(lse0); });
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+      for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(rl[i]));
+      mfma_settle();
+    }
+    // key index of this lane's column relative to the context: query i of the segment sees it iff i >= jrel
+    const int jrel = it.j0 + 32 * wave + l32 - it.ctx, jrel_hi = it.j0 + 32 * wave + 31 - it.ctx;
+    int s_g = 0, s_q = 1;              // slots of dO of stage g and of Q of stage g + 1
+    int s_qt = qt_start, s_heads = G;  // query tile of stage g; heads of the tile still to come
+
+    auto step = [&](int g, f32x16& cur, f32x16& nxt) __attribute__((always_inline)) {
+      const unsigned g_ev = ev0 + DO_RING + s_g * SLOT, g_od = od0 + DO_RING + s_g * SLOT;
+      const unsigned q_ev = ev0 + s_q * SLOT, q_od = od0 + s_q * SLOT;
+      const unsigned r_cur = lse0 + s_g * (RV * 4), r_nxt = lse0 + s_q * (RV * 4);
+      // entry (query 8 (i / 4) + 4 hh + i % 4 of the tile, the lane's key) is visible iff 8 (i / 4) + i % 4 >= lim
+      const bool valid = g < n_iter;
+      if (__builtin_expect(!valid || s_qt * BM < jrel_hi, 0)) {
+        const int lim = valid ? jrel - s_qt * BM - 4 * hh : 0x40000000;
+        asm volatile("s_nop 15\n\ts_nop 7" : "+v"(cur));  // S(g) has been written
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (8 * (i >> 2) + (i & 3) < lim) cur[i] = -INFINITY;
+      }
+      float pf[16];             // P(g)
+      unsigned pw[8], sw[8];    // P(g), dS(g), packed pairs
+      auto pack_p = [&](int j) __attribute__((always_inline)) {  // (one pair late, see bwd_dkv_narrow_pipe_kernel)
+        bf16x2 w;
+        w[0] = (__bf16)pf[2 * j]; w[1] = (__bf16)pf[2 * j + 1];
+        unsigned wu = __builtin_bit_cast(unsigned, w);
+        asm volatile("" : "+v"(wu));
+        pw[j] = wu;
+      };
+      auto exp_one = [&](auto i_c) __attribute__((always_inline)) {
+        constexpr int i = decltype(i_c)::value;
+        if constexpr (i > 0 && i % 2 == 0) pack_p(i / 2 - 1);
+        pf[i] = __builtin_amdgcn_exp2f(cur[i] * c - rl[i >> 2][i & 3]);
+        asm volatile("" : "+v"(pf[i]));
+      };
+      auto ds_pair = [&](auto j_c) __attribute__((always_inline)) {
+        constexpr int j = decltype(j_c)::value, i = 2 * j;
+        bf16x2 w;
+        w[0] = (__bf16)(pf[i] * (dp[i] + rd[i >> 2][i & 3]));
+        w[1] = (__bf16)(pf[i + 1] * (dp[i + 1] + rd[i >> 2][(i & 3) + 1]));
+        unsigned wu = __builtin_bit_cast(unsigned, w);
+        asm volatile("" : "+v"(wu));
+        sw[j] = wu;
+      };
+      auto frag_of = [](const unsigned* w) __attribute__((always_inline)) {
+        const u32x4 v = {w[0], w[1], w[2], w[3]};
+        return __builtin_bit_cast(bf16x8, v);
+      };
+      asm volatile("s_nop 15\n\ts_nop 7" ::: "memory");  // S(g) has been written
+      static_for<0, AHEAD>([&](auto k_c) __attribute__((always_inline)) { fr[decltype(k_c)::value] = load_rows(g_ev, g_od, k_c); });
+      __builtin_amdgcn_sched_barrier(0);
+      static_for<0, EXP_PRE>(exp_one);
+      __builtin_amdgcn_sched_barrier(0);
+      static_for<0, NF>([&](auto m_c) __attribute__((always_inline)) {
+        constexpr int m = decltype(m_c)::value;
+        if constexpr (m == DS0)
+          asm volatile("s_waitcnt lgkmcnt(%5)" : "+v"(fr[m % RING]), "+v"(rd[0]), "+v"(rd[1]), "+v"(rd[2]), "+v"(rd[3]) : "n"(lds_wait(m)));
+        else
+          asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(fr[m % RING]) : "n"(lds_wait(m)));
+        {  // read the fragment of mini-step m + AHEAD
+          constexpr int mm = m + AHEAD;
+          if constexpr (mm < DK) fr[mm % RING] = load_rows(g_ev, g_od, std::integral_constant<int, mm>{});
+          else if constexpr (mm < NF) fr[mm % RING] = load_rows(q_ev, q_od, std::integral_constant<int, mm - DK>{});
+        }
+        const bf16x8 fa = fr[m % RING];
+        {
+          const bf16x8& a_ = fa;  // (named references: variables used only inside an asm statement are not captured)
+          if constexpr (m < DK) {
+            const bf16x8& b_ = vf[m];
+            f32x16& d_ = dp;
+            if (m == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d_) : "v"(a_), "a"(b_));
+            else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d_) : "v"(a_), "a"(b_));
+          } else {
+            const bf16x8& b_ = kf[m - DK];
+            f32x16& d_ = nxt;
+            if (m == DK) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d_) : "v"(a_), "a"(b_));
+            else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d_) : "v"(a_), "a"(b_));
+          }
+        }
+        static_for<EXP_PRE + spread(16 - EXP_PRE, EXP0, EXP1, m - 1), EXP_PRE + spread(16 - EXP_PRE, EXP0, EXP1, m)>(exp_one);
+        static_for<spread(8, DS0, DS1, m - 1), spread(8, DS0, DS1, m)>(ds_pair);
+        if constexpr (m == EXP1) pack_p(7);
+        if constexpr (m == P_WRITE) {
+          wg_barrier();  // the gradient waves have read the hand-over of stage g - 1
+          lds_asm_write16<0>(hand0, frag_of(pw));
+        }
+        if constexpr (m == P_WRITE + 1) lds_asm_write16<1024>(hand0, frag_of(pw + 4));
+        if constexpr (m == S_WRITE0) lds_asm_write16<(S_OFF - P_OFF) * 2>(hand0, frag_of(sw));
+        if constexpr (m == S_WRITE1) lds_asm_write16<(S_OFF - P_OFF) * 2 + 1024>(hand0, frag_of(sw + 4));
+        if constexpr (m >= D_READ && m < D_READ + 4) rd[m - D_READ] = lds_asm_read16f<D_ROWS + 32 * (m - D_READ)>(r_cur);
+        if constexpr (m >= LSE_READ && m < LSE_READ + 4) rl[m - LSE_READ] = lds_asm_read16f<32 * (m - LSE_READ)>(r_nxt);
+        if constexpr (m < 2 * PER_A && m % 2 == 1) dma_piece(m / 2);
+        if constexpr (m == 2 * PER_A + 1) dma_rows();
+        if constexpr (m == 2 * PER_A + 4) {  // bookkeeping for the next step (this step's copies have been issued)
+          dma_advance();
+          s_g = (s_g + 1) & (NSG - 1);
+          s_q = s_q == NSQ - 1 ? 0 : s_q + 1;
+          if (--s_heads == 0) {
+            s_heads = G;
+            s_qt += down ? -1 : 1;
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      // this wave's copies of the step before have landed (those of this step may still be in flight); its hand-over has
+      // been stored
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(PER_A + 1) : "memory");
+      wg_barrier();
+    };
+    for (int g = 0; g <= n_iter; g += 2) {
+      if (g == claim_at && wave == 0) pending_claim = block_claim_issue(p.taken, xcd);
+      step(g, x[0], x[1]);
+      step(g + 1, x[1], x[0]);
+    }
+    __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
+  } else {
+    // ================= gradient waves: dV^T += dO^T P (wave 2), dK^T += Q^T dS (wave 3), 64 keys =================
+    const bool of_k = wave == 3;
+    for (int s = 0; s < ahead; ++s) {
+#pragma unroll
+      for (int i = 0; i < PER_W; ++i) dma_piece(i);
+      dma_advance();
+    }
+    __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0), visible to the compiler
+    wg_barrier();
+
+    constexpr int NF = 2 * DB;  // fragments (mini-steps of two MFMAs): the transposed tile of stage g - 1
+    unsigned lo0, hi0;
+    {
+      const int j = lane & 15, cl = 2 * ((lane >> 4) & 1) + ((j & 3) >> 1), r0 = 4 * hh + (j >> 2);
+      lo0 = lds_addr(L + (of_k ? Q_OFF : G_OFF) + cm_elem(r0, cl) + 4 * (j & 1));
+      hi0 = lds_addr(L + (of_k ? Q_OFF : G_OFF) + cm_elem(r0 + 8, cl) + 4 * (j & 1));
+    }
+    const unsigned hand0 = lds_addr(L + (of_k ? S_OFF : P_OFF) + lane * 8);
+    auto load_t = [&](unsigned lo_addr, unsigned hi_addr, auto m_c) __attribute__((always_inline)) {
+      constexpr int m = decltype(m_c)::value;  // ks2 * DB + db
+      constexpr int off = ((m / DB) * (16 * 8) + (m % DB) * (4 * 32 * 8)) * 2;
+      const s16x4 lo = lds_asm_read_tr<off>(lo_addr);
+      const s16x4 hi = lds_asm_read_tr<off>(hi_addr);
+      return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    f32x16 acc[2][DB];  // [D] x [32 keys of block kb]
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int db = 0; db < DB; ++db) acc[kb][db] = zero16;
+    bf16x8 fr[RING], b[2][2];  // fragment ring; P or dS of stage g - 1: [key block][k-step]
+    const int last_slot = (of_k ? NSQ : NSG) - 1;
+    int s_prv = last_slot;     // slot of stage g - 1
+    static_for<0, AHEAD>([&](auto m_c) __attribute__((always_inline)) { fr[decltype(m_c)::value] = load_t(lo0 + last_slot * SLOT, hi0 + last_slot * SLOT, m_c); });
+
+    auto step = [&]() __attribute__((always_inline)) {
+      const int s_cur = s_prv == last_slot ? 0 : s_prv + 1;
+      const unsigned t_lo = lo0 + s_prv * SLOT, t_hi = hi0 + s_prv * SLOT, n_lo = lo0 + s_cur * SLOT, n_hi = hi0 + s_cur * SLOT;
+      b[0][0] = lds_asm_read16<0>(hand0);
+      b[0][1] = lds_asm_read16<1024>(hand0);
+      b[1][0] = lds_asm_read16<2048>(hand0);
+      b[1][1] = lds_asm_read16<3072>(hand0);
+      __builtin_amdgcn_sched_barrier(0);
+      static_for<0, NF>([&](auto m_c) __attribute__((always_inline)) {
+        constexpr int m = decltype(m_c)::value;
+        if constexpr (m == 0)
+          asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(fr[0]), "+v"(fr[1]), "+v"(fr[2]), "+v"(fr[3]), "+v"(b[0][0]), "+v"(b[0][1]), "+v"(b[1][0]), "+v"(b[1][1]));
+        else
+          asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(fr[m % RING]) : "n"(2 * (AHEAD - 1)));
+        {  // read the fragment of mini-step m + AHEAD (past the end: stage g's first)
+          constexpr int mm = m + AHEAD;
+          if constexpr (mm < NF) fr[mm % RING] = load_t(t_lo, t_hi, std::integral_constant<int, mm>{});
+          else fr[mm % RING] = load_t(n_lo, n_hi, std::integral_constant<int, mm - NF>{});
+        }
+        const bf16x8 fa = fr[m % RING];
+        constexpr int ks = m / DB, db = m % DB;
+        acc[0][db] = mfma32(fa, b[0][ks], acc[0][db]);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (m < PER_W) dma_piece(m);
+        acc[1][db] = mfma32(fa, b[1][ks], acc[1][db]);
+        if constexpr (m == NF / 2 - 1) wg_barrier();  // the hand-over has been read: it may be overwritten
+        if constexpr (m == NF - 2) {
+          dma_advance();
+          s_prv = s_cur;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      // this wave's copies of the step before have landed
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER_W) : "memory");
+      wg_barrier();
+    };
+    for (int g = 0; g <= n_iter; g += 2) {
+      step();
+      step();
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(fr[i]));
+    __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
+    __bf16* const out = of_k ? p.dk : p.dv;
+    const float f = of_k ? p.scale : 1.0f;
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+      const int kr = 32 * kb + l32;
+      if (kr < it.kv_rows) {
+        const int64_t off = ((int64_t)it.kv_row0 + kr) * kv_stride + (int64_t)kvh * D;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int g = 0; g < 4; ++g)
+            dkv_store4(p, out, off + 32 * db + 8 * g + 4 * hh, acc[kb][db][4 * g] * f, acc[kb][db][4 * g + 1] * f,
+                       acc[kb][db][4 * g + 2] * f, acc[kb][db][4 * g + 3] * f);
+      }
+    }
+  }
+  // on to the next block; the stores of the epilogue are not waited for here
+  int nb = 0;
+  if (wave == 0) {
+    if (lane == 0) __hip_atomic_fetch_add(p.ended + (blk & 7), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    nb = block_claim_finish(p.taken, num_blocks, xcd, pending_claim);
+    start_in_step(nb);
+  }
+  blk = broadcast_from_wave0(&next_block, nb);
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
 // bwd_dq_pipe (head_dim 128, 96 and, with long walks, 64)
 //
 // The dQ kernel in the style of bwd_dkv_pipe_kernel: one wave per SIMD, a workgroup of 4 waves, each wave
@@ -2051,11 +2482,16 @@ size_t n_dkv_blocks(const chunk_attn_desc* d) {
   return n;
 }
 
-// Key blocks from which on head_dim 64 runs bwd_dkv_narrow_pipe_kernel: two blocks per CU.  With fewer of them half of the chip's
-// SIMDs would have no wave, and bwd_dkv_kernel, which puts eight waves on a block, ends earlier.  Measured backward, one and the
-// other kernel (8 key/value heads): 256 blocks 61 / 74 us and (32 query heads) 148 / 174, 512 blocks 150 / 141, 1024 blocks
-// of 256-token sequences 228 / 227, 1024 blocks of 2048-token sequences 811 / 696, 2048 blocks 7573 / 6451.
-constexpr int64_t kMinDkvPipeBlocks64 = 2 * kCus;
+// Key blocks from which on head_dim 64 and 256 run their pipelined dK/dV kernels: two blocks per CU.  Fewer blocks end earlier
+// in bwd_dkv_kernel (head_dim 64: eight waves on a block instead of two; 256: its blocks start and end faster).
+// Measured backward, bwd_dkv_kernel / pipelined (8 key/value heads), head_dim 64: 256 blocks 61 / 74 us and (32 query heads)
+// 148 / 174, 512 blocks 150 / 141, 1024 blocks of 256-token sequences 228 / 227, of 2048-token sequences 811 / 696, 2048 blocks
+// 7573 / 6451; head_dim 256: 128 blocks 80 / 84, 256 blocks 127 / 127 and (32 query heads) 184 / 167, 312 short ones 169 / 173,
+// 512 blocks 173 / 161 and 508 / 405, 4096 blocks 35161 / 26922.
+constexpr int64_t kMinDkvPipeBlocks = 2 * kCus;
+
+// workgroups of the pipelined dK/dV kernels on a CU
+constexpr int dkv_per_cu(int head_dim) { return head_dim == 64 ? 2 : 1; }
 
 // Raises a kernel's dynamic-LDS limit; callers keep the result in a function-local static, so that it happens once per
 // process and is safe from several threads.
@@ -2154,7 +2590,7 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
     p.out_f32 = a.dkv_f32 ? 1 : 0;
     p.taken = reinterpret_cast<int32_t*>(ws + P.queues_off) + kBlockQueues;
     p.ended = p.taken + kBlockQueues;
-    p.side_by_side = std::max(1, persistent_grid(0x7fffffff) / kBlockQueues);
+    p.side_by_side = std::max(1, persistent_grid(0x7fffffff, dkv_per_cu(D)) / kBlockQueues);
     p.clock_log = clock_log(2);
     static_assert(DKV_KEYS == 128, "the head_dim 64 and 128 kernels cover 128 keys per workgroup");
     const int64_t blocks = (int64_t)P.dkv_items.size() * d->num_kv_heads;
@@ -2177,8 +2613,18 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
           static const hipError_t attr = raise_smem_limit(&bwd_dkv_narrow_pipe_kernel<D>, smem);
           if (attr != hipSuccess) return attr;
           if (pe.start && (e = hipEventRecord(pe.start, stream)) != hipSuccess) return e;
-          hipLaunchKernelGGL((bwd_dkv_narrow_pipe_kernel<D>), dim3((unsigned)persistent_grid(blocks, 2)), dim3(128), smem, stream, p,
+          hipLaunchKernelGGL((bwd_dkv_narrow_pipe_kernel<D>), dim3((unsigned)persistent_grid(blocks, dkv_per_cu(D))), dim3(128), smem, stream, p,
                              (int)blocks);
+        }
+      }
+      if constexpr (D == 256) {
+        if (P.dkv_pipe) {
+          // 5 + 4 ring slots of 32-row Q and dO tiles with their LSE and D rows, a P and a dS hand-over slot
+          const size_t smem = (size_t)9 * 32 * D * 2 + 2 * 2048 * 2 + 9 * 64 * sizeof(float);
+          static const hipError_t attr = raise_smem_limit(&bwd_dkv_wide_pipe_kernel<D>, smem);
+          if (attr != hipSuccess) return attr;
+          if (pe.start && (e = hipEventRecord(pe.start, stream)) != hipSuccess) return e;
+          hipLaunchKernelGGL((bwd_dkv_wide_pipe_kernel<D>), dim3((unsigned)persistent_grid(blocks)), dim3(256), smem, stream, p, (int)blocks);
         }
       }
       if (!P.dkv_pipe) {
@@ -2208,8 +2654,8 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, bool may_c
   if (d->head_dim == 64) {
     P.dq_pipe = pipe_pays(count_walks(d, tile_rows(group, 8)), d->num_kv_heads * (group / heads_per_wg(group, 8)));
     if (P.dq_pipe) P.dq_waves = 8;
-    P.dkv_pipe = (int64_t)n_dkv_blocks(d) * d->num_kv_heads >= kMinDkvPipeBlocks64;
   }
+  if (!pipe) P.dkv_pipe = (int64_t)n_dkv_blocks(d) * d->num_kv_heads >= kMinDkvPipeBlocks;
   const int dq_rows = tile_rows(group, P.dq_waves);
   P.q_tiles = count_tiles(d, false, 64);
   P.kv32_tiles = count_tiles(d, true, 32);
@@ -2228,9 +2674,9 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, bool may_c
     } else {
       P.dq_items = plan_dq(d, dq_rows);
       if (P.split.target > 0) P.dq_items = cut_items(P.dq_items, P.split.target, &P.dq_cut);
-      // head_dim 128: the pipelined kernel walks either way; the key blocks of one key/value head that run at the same time
-      // are the workgroups of the launch (one per CU) over the number of key/value heads
-      const int side_by_side = d->head_dim == 128 ? std::max(1, persistent_grid(0x7fffffff) / d->num_kv_heads) : 0;
+      // the pipelined kernels walk either way; the key blocks of one key/value head that run at the same time are the
+      // workgroups of the launch over the number of key/value heads
+      const int side_by_side = P.dkv_pipe ? std::max(1, persistent_grid(0x7fffffff, dkv_per_cu(d->head_dim)) / d->num_kv_heads) : 0;
       P.dkv_items = plan_dkv(d, dkv_keys(d->head_dim), side_by_side);
     }
     P.qjobs = tile_jobs(d, false, 64, nullptr);

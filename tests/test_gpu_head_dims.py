@@ -174,3 +174,36 @@ def test_second_pass_of_head_dim_64(oracle_mod):
         ca.chunk_attn_test_set_fwd_rescale_limit(60.0)
     O, LSE = oracle_mod.Oracle(case.segs, q[:, 5:6].cpu().contiguous(), k[:, 5:6].cpu().contiguous(), v[:, 5:6].cpu().contiguous(), None, case.scale).forward()
     assert rel_err(o[:, 5:6], O) <= TOL_O and float(np.abs(lse[5:6].double().cpu().numpy() - LSE).max()) <= 2.0 ** -9 + 1e-4
+
+
+@pytest.mark.parametrize("name,segs,Hq,Hkv", [
+    # enough 64-key blocks for the pipelined dK/dV kernel of head_dim 256, both walk directions among them
+    ("ragged", [(0, 700, 0, 700), (700, 33, 700, 160)], 64, 64),
+    ("groups_and_gaps", [(0, 130, 3, 900), (130, 1, 910, 129), (131, 63, 1041, 127)], 64, 32),
+    ("context_blocks_in_groups", [(0, 65, 0, 65 + 70 * 64)], 16, 8),
+])
+def test_pipelined_dkv_of_head_dim_256(oracle_mod, name, segs, Hq, Hkv):
+    """Ragged key blocks and query tiles, walks of one stage upwards, rows outside key ranges, accumulation, float32 buffers;
+    against the oracle on one head group of each end."""
+    tq, tkv = max(s[0] + s[1] for s in segs), max(s[2] + s[3] for s in segs) + 2
+    case = synth.ChunkCase(f"{name}_d256", [synth.Seg(*s) for s in segs], tq, tkv, Hq, Hkv, 256, 800 + len(name))
+    q, k, v, do = make_inputs(case)
+    _, _, _, dk, dv = run_gpu(case, q, k, v, do)
+    again = run_gpu(case, q, k, v, do)
+    assert torch.equal(dk, again[3]) and torch.equal(dv, again[4])
+    init = torch.full(k.shape, 3.0, device=k.device)
+    acc = run_gpu(case, q, k, v, do, accumulate=True, dk_init=init, dv_init=init, f32kv=True)
+    cov = np.zeros(tkv, dtype=bool)
+    for s in segs:
+        cov[s[2]:s[2] + s[3]] = True
+    assert torch.all(dk.cpu()[~cov] == 0) and torch.all(dv.cpu()[~cov] == 0)
+    assert torch.all(acc[3].cpu()[~cov] == 3.0) and torch.all(acc[4].cpu()[~cov] == 3.0)
+    G = Hq // Hkv
+    for h in (0, Hkv - 1):
+        qs = slice(h * G, (h + 1) * G)
+        orc = oracle_mod.Oracle(case.segs, q[:, qs].cpu().contiguous(), k[:, h:h + 1].cpu().contiguous(), v[:, h:h + 1].cpu().contiguous(),
+                                do[:, qs].cpu().contiguous(), case.scale)
+        orc.forward()
+        _, dK, dV = orc.backward()
+        assert max(rel_err(dk[:, h:h + 1], dK), rel_err(dv[:, h:h + 1], dV)) <= TOL_GRAD
+        assert rel_err(acc[3][:, h:h + 1].cpu()[cov], dK[cov] + 3.0) <= TOL_GRAD and rel_err(acc[4][:, h:h + 1].cpu()[cov], dV[cov] + 3.0) <= TOL_GRAD
