@@ -531,6 +531,7 @@ int chunk_attn_fwd(const chunk_attn_desc* desc, const void* q, const void* k, co
   p.vt = vt;
   p.items = reinterpret_cast<const FwdItem*>(ws);
   p.wholes = reinterpret_cast<const FwdItem*>(ws + L.wholes_off);
+  p.cut = L.split.target > 0;
   p.parts = reinterpret_cast<float*>(ws + L.vt_off);
   p.total_kv_tiles = L.kv_tiles;
   p.num_q_heads = desc->num_q_heads;
@@ -588,6 +589,7 @@ int chunk_attn_fwd_static(const chunk_attn_desc* desc, const void* q, const void
   p.vt = reinterpret_cast<__bf16*>(ws + L.vt_off);
   p.items = reinterpret_cast<const FwdItem*>(ws);
   p.wholes = reinterpret_cast<const FwdItem*>(ws + L.wholes_off);
+  p.cut = L.split.target > 0;
   p.parts = reinterpret_cast<float*>(ws + L.vt_off);
   p.total_kv_tiles = L.kv_tiles;
   p.num_q_heads = desc->num_q_heads;

@@ -331,6 +331,7 @@ struct DkvParams {
   int32_t* taken;       // 8 block-queue counters of the pipelined kernel (zero before the launch)
   int32_t* ended;       // per queue, the blocks that have ended (zero before the launch)
   int32_t side_by_side; // blocks of a queue that run at the same time (DkvItem::in_step)
+  float* parts;         // partial results of pieces (bwd_dkv_pipe_kernel), kPartRowFloats per (slot, key/value head)
   unsigned long long* clock_log;  // null, or where the pipelined kernel's workgroups log their clocks
 };
 
@@ -707,7 +708,8 @@ static_assert(DkvLdsOrder<0, 16, 8>::wait(0) == 6 && DkvLdsOrder<0, 16, 8>::wait
 // every MFMA result of a kernel this size in accumulation registers (one extra move per element), so those
 // MFMAs are written as opaque instructions.
 // ------------------------------------------------------------------------------------------------
-template <int D>
+// (CUT: some items are pieces; see fwd_pipe_kernel)
+template <int D, bool CUT>
 __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(DkvParams p, int num_blocks) {
   constexpr int NW = 4;        // waves
   constexpr int BM = 32;       // query rows per stage
@@ -1154,6 +1156,17 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(DkvParams p, int n
     __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
 
     // ---- epilogue: dV = dV^T (role A), dK = scale * dK^T (role B), written (or added) as bf16 ----
+    if (CUT && it.part >= 0) {  // a piece: the accumulators as they are, put together by bwd_dkv_merge_kernel
+      float* const out = p.parts + ((int64_t)it.part * p.num_kv_heads + kvh) * kPartRowFloats + (4 * ROLE + 2 * pair) * 4096 + lane * 4;
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int g = 0; g < 4; ++g)
+            *reinterpret_cast<f32x4*>(out + kb * 4096 + (db * 4 + g) * 256) =
+                f32x4{acc[kb][db][4 * g], acc[kb][db][4 * g + 1], acc[kb][db][4 * g + 2], acc[kb][db][4 * g + 3]};
+    } else
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
       const int kr = 64 * pair + 32 * kb + l32;
@@ -2048,7 +2061,8 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_wide_pipe_kernel(DkvParams p, 
 // live in a ring of DIST + 3 slots.  Steps whose tile needs the causal mask (the last one or two of the
 // walk) or lies past the end run a second variant of the step that masks in the vector work.
 // ------------------------------------------------------------------------------------------------
-template <int D>
+// (CUT: some items are pieces; see fwd_pipe_kernel)
+template <int D, bool CUT>
 __global__ __launch_bounds__(256, 1) void bwd_dq_pipe_kernel(DqParams p, int num_blocks) {
   constexpr int NW = 4;        // waves
   constexpr int BN = 32;       // key rows per stage
@@ -2111,7 +2125,8 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_pipe_kernel(DqParams p, int num
     row0[u] = (unit / p.heads_per_wg) * 32;
   }
 
-  const int n_wg = min(it.n0 + it.q_rows - 1, it.keys);  // keys the last valid row sees of the item's range
+  const int n_last = it.n0 + it.q_rows - 1;                // keys the last valid row sees ...
+  const int n_wg = CUT ? min(n_last, it.keys) : n_last;  // ... of the item's range
   const int nt = (n_wg + BN - 1) / BN;       // stages
 
   const int64_t q_stride = (int64_t)p.num_q_heads * D, kv_stride = (int64_t)p.num_kv_heads * D;
@@ -2403,7 +2418,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_pipe_kernel(DqParams p, int num
   int lane_e = lane;
   asm volatile("" : "+v"(lane_e));
   const int l32_e = lane_e & 31, hh_e = lane_e >> 5;
-  if (it.part >= 0) {  // a piece: dQ^T as it is, put together by bwd_dq_merge_kernel
+  if (CUT && it.part >= 0) {  // a piece: dQ^T as it is, put together by bwd_dq_merge_kernel
     float* const out = p.parts + ((int64_t)it.part * inner_n + inner) * kPartRowFloats + wave * (2 * 4096) + lane_e * 4;
 #pragma unroll
     for (int u = 0; u < 2; ++u)
@@ -2470,6 +2485,33 @@ __global__ __launch_bounds__(512) void bwd_dq_merge_kernel(DqParams p, const DqI
 #pragma unroll
   for (int i = 0; i < NQ; ++i)
     *reinterpret_cast<bf16x4*>(op + 8 * i) = pack4(s[i][0] * p.scale, s[i][1] * p.scale, s[i][2] * p.scale, s[i][3] * p.scale);
+}
+
+// The same for the dK and dV rows of key blocks whose walks were cut (in_step: number of pieces).
+template <int D>
+__global__ __launch_bounds__(512) void bwd_dkv_merge_kernel(DkvParams p, const DkvItem* __restrict__ cut) {
+  constexpr int NQ = D / 8;  // accumulator quarters
+  const int lane = threadIdx.x & 63, l32 = lane & 31, hh = lane >> 5;
+  const int unit = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int kvh = blockIdx.x % p.num_kv_heads;
+  const DkvItem it = cut[blockIdx.x / p.num_kv_heads];
+  const int kr = (unit & 3) * 32 + l32;
+  if (kr >= it.kv_rows) return;
+  const int64_t step = (int64_t)p.num_kv_heads * kPartRowFloats;
+  const float* src = p.parts + (int64_t)it.part * step + (int64_t)kvh * kPartRowFloats + unit * 4096 + lane * 4;
+  f32x4 s[NQ];
+#pragma unroll
+  for (int i = 0; i < NQ; ++i) s[i] = *reinterpret_cast<const f32x4*>(src + i * 256);
+  for (int k = 1; k < it.in_step; ++k) {
+    src += step;
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) s[i] += *reinterpret_cast<const f32x4*>(src + i * 256);
+  }
+  __bf16* const out = unit < 4 ? p.dv : p.dk;
+  const float f = unit < 4 ? 1.0f : p.scale;
+  const int64_t off = ((int64_t)it.kv_row0 + kr) * p.num_kv_heads * D + (int64_t)kvh * D + 4 * hh;
+#pragma unroll
+  for (int i = 0; i < NQ; ++i) dkv_store4(p, out, off + 8 * i, s[i][0] * f, s[i][1] * f, s[i][2] * f, s[i][3] * f);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -2555,11 +2597,16 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
       if (P.dq_pipe) {
         // ring slots of a K and a V tile, then the staging tiles of the four waves (64 rows each)
         const size_t smem = (size_t)2 * (DQ_PIPE_DIST + 3) * 32 * D * 2 + (size_t)4 * 64 * D * 2;
-        static const hipError_t attr = raise_smem_limit(&bwd_dq_pipe_kernel<D>, smem);
-        if (attr != hipSuccess) return attr;
-        hipLaunchKernelGGL((bwd_dq_pipe_kernel<D>), dim3((unsigned)persistent_grid(blocks)), dim3(256), smem, stream, p, (int)blocks);
+        if (P.n_dq_cut == 0) {
+          static const hipError_t attr = raise_smem_limit(&bwd_dq_pipe_kernel<D, false>, smem);
+          if (attr != hipSuccess) return attr;
+          hipLaunchKernelGGL((bwd_dq_pipe_kernel<D, false>), dim3((unsigned)persistent_grid(blocks)), dim3(256), smem, stream, p, (int)blocks);
+        }
         if constexpr (pipelined(D)) {
           if (P.n_dq_cut > 0) {
+            static const hipError_t attr = raise_smem_limit(&bwd_dq_pipe_kernel<D, true>, smem);
+            if (attr != hipSuccess) return attr;
+            hipLaunchKernelGGL((bwd_dq_pipe_kernel<D, true>), dim3((unsigned)persistent_grid(blocks)), dim3(256), smem, stream, p, (int)blocks);
             if ((e = hipGetLastError()) != hipSuccess) return e;
             hipLaunchKernelGGL((bwd_dq_merge_kernel<D>), dim3((unsigned)(P.n_dq_cut * d->num_kv_heads * p.head_splits)), dim3(512), 0,
                                stream, p, reinterpret_cast<const DqItem*>(ws + P.dq_cut_off));
@@ -2590,6 +2637,7 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
     p.out_f32 = a.dkv_f32 ? 1 : 0;
     p.taken = reinterpret_cast<int32_t*>(ws + P.queues_off) + kBlockQueues;
     p.ended = p.taken + kBlockQueues;
+    p.parts = reinterpret_cast<float*>(ws + P.fdq_off);  // (as for dQ, whose partial results have been put together by then)
     p.side_by_side = std::max(1, persistent_grid(0x7fffffff, dkv_per_cu(D)) / kBlockQueues);
     p.clock_log = clock_log(2);
     static_assert(DKV_KEYS == 128, "the head_dim 64 and 128 kernels cover 128 keys per workgroup");
@@ -2601,10 +2649,19 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
       // ring slots of two 32-row operand tiles, 2 P hand-over slots, one slot of LSE and D rows per ring slot
       constexpr int NS = DKV_PIPE_DIST + 5;
       const size_t smem = (size_t)2 * NS * 32 * D * 2 + 2 * 4096 * 2 + 2 * NS * 64 * sizeof(float);
-      static const hipError_t attr = raise_smem_limit(&bwd_dkv_pipe_kernel<D>, smem);
-      if (attr != hipSuccess) return attr;
       if (pe.start && (e = hipEventRecord(pe.start, stream)) != hipSuccess) return e;
-      hipLaunchKernelGGL((bwd_dkv_pipe_kernel<D>), dim3((unsigned)persistent_grid(blocks)), dim3(256), smem, stream, p, (int)blocks);
+      if (P.n_dkv_cut == 0) {
+        static const hipError_t attr = raise_smem_limit(&bwd_dkv_pipe_kernel<D, false>, smem);
+        if (attr != hipSuccess) return attr;
+        hipLaunchKernelGGL((bwd_dkv_pipe_kernel<D, false>), dim3((unsigned)persistent_grid(blocks)), dim3(256), smem, stream, p, (int)blocks);
+      } else {
+        static const hipError_t attr = raise_smem_limit(&bwd_dkv_pipe_kernel<D, true>, smem);
+        if (attr != hipSuccess) return attr;
+        hipLaunchKernelGGL((bwd_dkv_pipe_kernel<D, true>), dim3((unsigned)persistent_grid(blocks)), dim3(256), smem, stream, p, (int)blocks);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        hipLaunchKernelGGL((bwd_dkv_merge_kernel<D>), dim3((unsigned)(P.n_dkv_cut * d->num_kv_heads)), dim3(512), 0, stream, p,
+                           reinterpret_cast<const DkvItem*>(ws + P.dkv_cut_off));
+      }
     } else {
       if constexpr (D == 64) {
         if (P.dkv_pipe) {
@@ -2667,6 +2724,8 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, bool may_c
   if (pipe && may_cut && !P.fused) {
     const int inner = d->num_kv_heads * (group / heads_per_wg(group, P.dq_waves));
     P.split = choose_key_split(d, dq_rows, inner, kCus, (int64_t)(dq_tile_bytes / ((size_t)inner * kPartRowFloats * sizeof(float))));
+    P.dkv_split = choose_tile_split(d, dkv_keys(d->head_dim), kCus,
+                                    (int64_t)(dq_tile_bytes / ((size_t)d->num_kv_heads * kPartRowFloats * sizeof(float))));
   }
   if (with_plan) {
     if (P.fused) {
@@ -2677,7 +2736,8 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, bool may_c
       // the pipelined kernels walk either way; the key blocks of one key/value head that run at the same time are the
       // workgroups of the launch over the number of key/value heads
       const int side_by_side = P.dkv_pipe ? std::max(1, persistent_grid(0x7fffffff, dkv_per_cu(d->head_dim)) / d->num_kv_heads) : 0;
-      P.dkv_items = plan_dkv(d, dkv_keys(d->head_dim), side_by_side);
+      P.dkv_items = plan_dkv(d, dkv_keys(d->head_dim), P.dkv_split.target > 0 ? 0 : side_by_side);
+      if (P.dkv_split.target > 0) P.dkv_items = cut_items(P.dkv_items, P.dkv_split.target, &P.dkv_cut);
     }
     P.qjobs = tile_jobs(d, false, 64, nullptr);
     if (!P.dq_pipe) P.kjobs = tile_jobs(d, true, 32, nullptr);
@@ -2689,10 +2749,12 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, bool may_c
   }
   // (cut walks: the pieces, then the whole items that were cut, of which there are at most as many as items)
   P.n_dq_cut = P.dq_cut.size();
+  P.n_dkv_cut = P.dkv_cut.size();
   P.dq_items_off = 0;
   P.dq_cut_off = P.split.target > 0 ? up256((size_t)P.split.pieces * sizeof(DqItem)) : 0;
   P.dkv_items_off = P.dq_cut_off + up256(n_dq * sizeof(DqItem));
-  P.qjobs_off = P.dkv_items_off + up256(n_dkv * sizeof(DkvItem));
+  P.dkv_cut_off = P.dkv_items_off + (P.dkv_split.target > 0 ? up256((size_t)P.dkv_split.pieces * sizeof(DkvItem)) : 0);
+  P.qjobs_off = P.dkv_cut_off + up256(n_dkv * sizeof(DkvItem));
   P.kjobs_off = P.qjobs_off + up256((size_t)P.q_tiles * sizeof(TileJob));
   P.fitems_off = P.kjobs_off + (pipe ? 0 : up256((size_t)P.kv32_tiles * sizeof(TileJob)));
   // the workspace is sized for either backward (the mode may change between the size query and the call): the one-pass
@@ -2721,6 +2783,7 @@ std::vector<char> bwd_blob(const BwdPlan& P) {
   std::memcpy(blob.data() + P.dq_items_off, P.dq_items.data(), P.dq_items.size() * sizeof(DqItem));
   std::memcpy(blob.data() + P.dq_cut_off, P.dq_cut.data(), P.dq_cut.size() * sizeof(DqItem));
   std::memcpy(blob.data() + P.dkv_items_off, P.dkv_items.data(), P.dkv_items.size() * sizeof(DkvItem));
+  std::memcpy(blob.data() + P.dkv_cut_off, P.dkv_cut.data(), P.dkv_cut.size() * sizeof(DkvItem));
   std::memcpy(blob.data() + P.qjobs_off, P.qjobs.data(), P.qjobs.size() * sizeof(TileJob));
   std::memcpy(blob.data() + P.kjobs_off, P.kjobs.data(), P.kjobs.size() * sizeof(TileJob));
   if (P.fused) {

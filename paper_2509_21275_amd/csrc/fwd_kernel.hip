@@ -81,6 +81,7 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
   constexpr int DB = D / 32;   // 32-row blocks of O^T
   constexpr int KT = BN * D;   // elements per K tile and per V^T image
   constexpr int WR = 32 * QB;  // query rows per wave
+  if (p.redo != nullptr && !p.cut && p.redo[blockIdx.x] == 0) return;  // second pass with nothing to do
   constexpr bool IMG = D > 128;  // V arrives as a transposed image; else as rows, two chunk-major tiles of 32
 
   extern __shared__ __attribute__((aligned(1024))) char smem[];
@@ -382,7 +383,9 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
 // Steps whose stage needs the causal mask (the last few of the walk) or lies past the end run a second variant of
 // the step that masks in the vector work.
 // ------------------------------------------------------------------------------------------------
-template <int D>
+// CUT: some items are pieces.  A kernel of its own, because the few registers and instructions it takes lengthen every block of
+// the other one (chunk of 256-token sequences: dQ, which has the same split, 171 -> 178 us, forward 142 -> 144).
+template <int D, bool CUT>
 __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void fwd_pipe_kernel(FwdParams p, int num_blocks) {
   constexpr int NW = 4;        // waves
   constexpr int BN = 32;       // key rows per stage
@@ -435,7 +438,8 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void fwd_pipe_kernel(FwdParam
   const int head = kvh * p.group + hs * p.heads_per_wg + wave % p.heads_per_wg;
   const int wave_row0 = (wave / p.heads_per_wg) * 64;  // the wave's units are rows wave_row0 + 32 u .. + 31 of `head`
 
-  const int n_wg = min(it.n0 + it.q_rows - 1, it.keys);  // keys the last valid row sees of the item's range
+  const int n_last = it.n0 + it.q_rows - 1;                // keys the last valid row sees ...
+  const int n_wg = CUT ? min(n_last, it.keys) : n_last;  // ... of the item's range
   const int nt = (n_wg + BN - 1) / BN;       // stages
 
   const int64_t q_stride = (int64_t)p.num_q_heads * D, kv_stride = (int64_t)p.num_kv_heads * D;
@@ -740,14 +744,14 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void fwd_pipe_kernel(FwdParam
   // block may fill the ring again
   __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
   if (__any(risk) && lane == 0) {
-    p.redo[it.whole * inner_n + inner] = 1;
+    p.redo[CUT ? it.whole * inner_n + inner : blk] = 1;
   }
 
   // ---- epilogue: O = O^T / l, LSE = ln(l) + m scale ----
   // (through the wave's staging tile: the lane that holds four values of a row writes them there, then every lane
   // moves one 16-byte chunk of a row to global memory, four whole rows per instruction; one unit after the other, so
   // that few values are in flight at a time)
-  if (it.part >= 0) {  // a piece: O^T as it is, the reference maximum and the sum of each row
+  if (CUT && it.part >= 0) {  // a piece: O^T as it is, the reference maximum and the sum of each row
     float* const out = p.parts + ((int64_t)it.part * inner_n + inner) * kPartFloats;
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
@@ -815,15 +819,21 @@ static hipError_t launch_fwd_t(const FwdParams& p, int num_blocks, hipStream_t s
   return hipGetLastError();
 }
 
+template <int D, bool CUT>
+static hipError_t launch_fwd_items(const FwdParams& p, int num_blocks, size_t smem, hipStream_t stream) {
+  static const hipError_t attr = raise_smem_limit(&fwd_pipe_kernel<D, CUT>, smem);
+  if (attr != hipSuccess) return attr;
+  hipLaunchKernelGGL((fwd_pipe_kernel<D, CUT>), dim3(persistent_grid(num_blocks, D == 64 ? 2 : 1)), dim3(256), smem, stream, p, num_blocks);
+  return hipGetLastError();
+}
+
 template <int D>
 static hipError_t launch_fwd_pipe(const FwdParams& p, int num_blocks, int num_wholes, hipStream_t stream) {
   // ring slots of a K and a V tile, then the staging tiles of the four waves (64 rows each)
   const size_t smem = (size_t)2 * (FWD_PIPE_DIST + 3) * 32 * D * 2 + (size_t)4 * 64 * D * 2;
-  static const hipError_t attr = raise_smem_limit(&fwd_pipe_kernel<D>, smem);
-  if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL((fwd_pipe_kernel<D>), dim3(persistent_grid(num_blocks, D == 64 ? 2 : 1)), dim3(256), smem, stream, p, num_blocks);
   hipError_t e;
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if ((e = p.cut ? launch_fwd_items<D, true>(p, num_blocks, smem, stream) : launch_fwd_items<D, false>(p, num_blocks, smem, stream)) !=
+      hipSuccess) return e;
   // Second pass over the whole items, 8 waves of 32 rows: a workgroup returns at once unless its flag is raised (the item
   // is recomputed) or its item was cut (its pieces are put together).
   return launch_fwd_t<D, 8>(p, num_wholes, stream);

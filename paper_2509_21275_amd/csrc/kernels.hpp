@@ -22,6 +22,7 @@ struct FwdParams {
   const __bf16* vt;         // transposed V images [Hkv][total_kv_tiles][D][64]
   const FwdItem* items;
   const FwdItem* wholes;    // head_dim 128: the items before cutting (= items if none was cut)
+  bool cut;                 // some of the items are pieces
   float* parts;             // head_dim 128: partial results of the pieces, kPartFloats per (slot, inner index)
   int64_t total_kv_tiles;
   int32_t num_q_heads, num_kv_heads, group;  // group = Hq / Hkv
@@ -67,6 +68,7 @@ constexpr int kCus = 256;        // compute units of an MI355X (plans that must 
 // rows][up to 16 accumulator quarters][64 lanes][4] float32; for the forward then [8 units][32 rows] {reference maximum, sum}.
 constexpr int kPartRowFloats = 8 * 16 * 64 * 4;
 constexpr int kPartFloats = kPartRowFloats + 8 * 32 * 2;
+// (a partial result of a dK/dV block of 128 keys has the same size: units 0 .. 3 are dV, 4 .. 7 dK of 32 keys each)
 
 // Whether a query-stationary kernel of head_dim 64 runs as the pipelined one: its workgroups start and end more slowly than
 // the other kernel's, which has three or four of them on a CU, so it needs two blocks per CU and walks of 64 stages on
@@ -92,17 +94,19 @@ struct BwdArgs {
 };
 
 // Host-side plan of one backward call and the layout of its workspace:
-// [dQ items | dQ items that were cut | dK/dV items | 64-row query-tile jobs | 32-row key-tile jobs] (one uploaded blob), then
+// [dQ items | dQ items that were cut | dK/dV items | dK/dV items that were cut | 64-row query-tile jobs | 32-row key-tile jobs] (one uploaded blob), then
 // the LSE and D arrays padded to 64-row tiles and the transposed images of K (32-row tiles; not for head_dim 128).
 struct BwdPlan {
   KeySplit split;                // head_dim 128: how the dQ walks are cut
   std::vector<DqItem> dq_items;  // with the pieces of walks that are cut
   std::vector<DqItem> dq_cut;    // the whole items that were cut
+  KeySplit dkv_split;            // the same for the dK/dV walks
+  std::vector<DkvItem> dkv_cut;
   std::vector<DkvItem> dkv_items;
   std::vector<TileJob> qjobs, kjobs;
   int64_t q_tiles = 0, kv32_tiles = 0;
-  size_t n_dq_cut = 0;
-  size_t dq_items_off = 0, dq_cut_off = 0, dkv_items_off = 0, qjobs_off = 0, kjobs_off = 0, queues_off = 0, blob_bytes = 0;
+  size_t n_dq_cut = 0, n_dkv_cut = 0;
+  size_t dq_items_off = 0, dq_cut_off = 0, dkv_items_off = 0, dkv_cut_off = 0, qjobs_off = 0, kjobs_off = 0, queues_off = 0, blob_bytes = 0;
   size_t lse2p_off = 0, dsp_off = 0, kt_off = 0, total = 0;
   // one-pass backward (head_dim 128): its items and workgroup order travel at the end of the blob; then the per-wave
   // progress counters and the status word (cleared by a kernel on every call) and the float32 dQ tiles
@@ -124,7 +128,7 @@ constexpr size_t kClockLogEntries = 4 * 1024;
 unsigned long long* clock_log(int which);
 hipError_t launch_bwd_fused(const chunk_attn_desc* d, const BwdArgs& a, const BwdPlan& plan, const float* lse2p, const float* dsp,
                             hipStream_t stream);
-// Fills the offsets (and, if with_plan, the schedules) for a validated descriptor.  `may_cut`: false: no dQ walk is cut.
+// Fills the offsets (and, if with_plan, the schedules) for a validated descriptor.  `may_cut`: false: no walk is cut.
 void bwd_layout(const chunk_attn_desc* d, BwdPlan& plan, bool with_plan, bool may_cut = true);
 // The host image of the blob at the start of the workspace.
 std::vector<char> bwd_blob(const BwdPlan& plan);

@@ -140,31 +140,25 @@ Walks count_walks(const chunk_attn_desc* d, int tile_rows) {
   return w;
 }
 
-// The estimate, in stages (one 32-key step of a workgroup, about a microsecond).  A block costs its walk plus kStart
-// for filling the pipeline and writing its rows; a piece kPart more for its float32 rows (twice the bytes).  The blocks of
-// queue 0 (every eighth one) are dealt, longest first, to an eighth of the compute units as they become free.  Putting
-// the pieces together costs kMerge and the time to read the partial results.  A cut has to win 5 % of the uncut time.
+// The estimate behind both kinds of cut, in steps of a workgroup (about a microsecond each).  A block costs its steps plus
+// kStart for filling the pipeline and writing its rows; a piece kPart more for its float32 rows (twice the bytes).  The
+// blocks of queue 0 (every eighth one) are dealt, longest first, to an eighth of the compute units as they become free.
+// Putting the pieces together costs kMerge and the time to read the partial results.  A cut has to win 5 % of the uncut time.
+// `pieces(walk, target)` and `steps(walk, n, k)` (steps of piece k of n) describe a walk, `longest` is the longest one's length
+// in the units of a target, `shortest` what a piece has at least.
 // Measured, uncut -> cut (head_dim 128, 32/8 heads): 1024 queries on 32768 keys, 128 blocks of 1024 stages in two pieces each:
 // forward 744 -> 472 us + 12 us to put them together, dQ 959 -> 625 + 12 us (not half: 128 busy compute units hold a
 // higher clock than 256); 203 queries on 1704 keys next to 611 short rows: forward 48 -> 28 + 6 us.  Chunks the estimate
 // leaves alone (8192 queries on 32768 keys: 1024 equal blocks) run as before.
-KeySplit choose_key_split(const chunk_attn_desc* d, int tile_rows, int inner, int cus, int64_t max_parts) {
+// dK/dV: two slices of 3193 and 4999 queries of one sequence, 512 and 320 blocks, 1367 -> 1280 us for both.
+constexpr int64_t kMaxCutBlocks = 1024;  // from four blocks per compute unit on they even out by themselves
+template <class Walk, class Pieces, class Steps>
+static KeySplit choose_cut(const std::vector<Walk>& walks, int longest, int shortest, int inner, int cus, int64_t max_parts,
+                           Pieces pieces, Steps steps) {
   constexpr int kStart = 12, kPart = 6, kMerge = 6;
-  constexpr int64_t kMaxBlocks = 1024;     // from four blocks per compute unit on they even out by themselves
-  constexpr int64_t kPartsPerStage = 32;   // partial results (128 KB per block) read per stage
-  struct Walk { int stages, n0; };
-  std::vector<Walk> walks;
-  for (int t = 0; t < d->num_segments; ++t) {
-    const chunk_attn_seg& s = d->segments[t];
-    for (int32_t i0 = 0; i0 < s.q_len; i0 += tile_rows) {
-      const int32_t n0 = s.kv_len - s.q_len + i0 + 1, rows = std::min<int32_t>(tile_rows, s.q_len - i0);
-      walks.push_back(Walk{walk_stages(n0, rows), n0});
-      if ((int64_t)walks.size() * inner >= kMaxBlocks) return KeySplit{};
-    }
-  }
-  int longest = 0;
-  for (const Walk& w : walks) longest = std::max(longest, w.stages);
+  constexpr int64_t kPartsPerStep = 32;  // partial results (128 KB per block) read per step
   const int workers = std::max(1, cus / 8);
+  const auto later = [](int64_t a, int64_t b) { return a > b; };
   std::vector<int> cost;
   std::vector<int64_t> free_at;
   auto estimate = [&](KeySplit& k) -> int64_t {
@@ -172,41 +166,102 @@ KeySplit choose_key_split(const chunk_attn_desc* d, int tile_rows, int inner, in
     k.pieces = k.parts = 0;
     int64_t block = 0;
     for (const Walk& w : walks) {
-      const int n = piece_count(w.stages, w.n0, k.target);
+      const int n = pieces(w, k.target);
       k.pieces += n;
       if (n > 1) k.parts += n;
       for (int i = 0; i < n; ++i) {
-        const int len = (i + 1 < n ? piece_begin(w.stages, n, i + 1) : w.stages) - piece_begin(w.stages, n, i);
-        const int64_t end = block + inner;   // blocks block .. end - 1; those divisible by 8 are queue 0's
-        for (int64_t b = (block + 7) / 8 * 8; b < end; b += 8) cost.push_back(len + kStart + (n > 1 ? kPart : 0));
+        const int64_t end = block + inner;  // blocks block .. end - 1; those divisible by 8 are queue 0's
+        for (int64_t b = (block + 7) / 8 * 8; b < end; b += 8) cost.push_back(steps(w, n, i) + kStart + (n > 1 ? kPart : 0));
         block = end;
       }
     }
-    std::sort(cost.begin(), cost.end(), [](int a, int b) { return a > b; });
+    std::sort(cost.begin(), cost.end(), later);
     free_at.assign(workers, 0);  // a heap, earliest first
     int64_t last = 0;
     for (int c : cost) {
-      std::pop_heap(free_at.begin(), free_at.end(), [](int64_t a, int64_t b) { return a > b; });
+      std::pop_heap(free_at.begin(), free_at.end(), later);
       free_at.back() += c;
       last = std::max(last, free_at.back());
-      std::push_heap(free_at.begin(), free_at.end(), [](int64_t a, int64_t b) { return a > b; });
+      std::push_heap(free_at.begin(), free_at.end(), later);
     }
-    return last + (k.parts > 0 ? kMerge + k.parts * inner / kPartsPerStage : 0);
+    return last + (k.parts > 0 ? kMerge + k.parts * inner / kPartsPerStep : 0);
   };
   KeySplit best;
   int64_t best_time = estimate(best);
   best_time -= best_time / 20;
-  for (int n = 2; n <= 16 && longest / n >= kMinPieceStages; ++n) {
+  for (int n = 2; n <= 16 && longest / n >= shortest; ++n) {
     KeySplit k;
     k.target = (longest + n - 1) / n;
     const int64_t time = estimate(k);
-    if (k.pieces * inner > 2 * kMaxBlocks) break;
+    if (k.pieces * inner > 2 * kMaxCutBlocks) break;
     if (k.parts > 0 && k.parts <= max_parts && time < best_time) {
       best = k;
       best_time = time;
     }
   }
   return best;
+}
+
+KeySplit choose_key_split(const chunk_attn_desc* d, int tile_rows, int inner, int cus, int64_t max_parts) {
+  struct Walk { int stages, n0; };
+  std::vector<Walk> walks;
+  int longest = 0;
+  for (int t = 0; t < d->num_segments; ++t) {
+    const chunk_attn_seg& s = d->segments[t];
+    for (int32_t i0 = 0; i0 < s.q_len; i0 += tile_rows) {
+      const int32_t n0 = s.kv_len - s.q_len + i0 + 1, rows = std::min<int32_t>(tile_rows, s.q_len - i0);
+      walks.push_back(Walk{walk_stages(n0, rows), n0});
+      longest = std::max(longest, walks.back().stages);
+      if ((int64_t)walks.size() * inner >= kMaxCutBlocks) return KeySplit{};
+    }
+  }
+  return choose_cut(
+      walks, longest, kMinPieceStages, inner, cus, max_parts, [](const Walk& w, int target) { return piece_count(w.stages, w.n0, target); },
+      [](const Walk& w, int n, int k) { return (k + 1 < n ? piece_begin(w.stages, n, k + 1) : w.stages) - piece_begin(w.stages, n, k); });
+}
+
+KeySplit choose_tile_split(const chunk_attn_desc* d, int keys, int cus, int64_t max_parts) {
+  const int group = d->num_q_heads / d->num_kv_heads;
+  std::vector<int> walks;  // query tiles per key block
+  int longest = 0;
+  for (int t = 0; t < d->num_segments; ++t) {
+    const chunk_attn_seg& s = d->segments[t];
+    const int32_t C = s.kv_len - s.q_len, n_qt = (s.q_len + 31) / 32;
+    for (int32_t j0 = 0; j0 < s.kv_len; j0 += keys) {
+      walks.push_back(n_qt - std::max<int32_t>(0, j0 - C) / 32);
+      longest = std::max(longest, walks.back());
+      if ((int64_t)walks.size() * d->num_kv_heads >= kMaxCutBlocks) return KeySplit{};
+    }
+  }
+  return choose_cut(
+      walks, longest, (2 * kMinPieceStages + group - 1) / group, d->num_kv_heads, cus, max_parts,
+      [](int tiles, int target) { return tile_piece_count(tiles, target); },
+      [&](int tiles, int n, int k) { return ((int)((int64_t)tiles * (k + 1) / n) - (int)((int64_t)tiles * k / n)) * group; });
+}
+
+std::vector<DkvItem> cut_items(const std::vector<DkvItem>& wholes, int target, std::vector<DkvItem>* cut) {
+  std::vector<DkvItem> items;
+  int32_t part = 0;
+  for (const DkvItem& whole : wholes) {
+    const int tiles = whole.n_qt - whole.qt_first, n = tile_piece_count(tiles, target);
+    if (n > 1) {
+      cut->push_back(whole);
+      cut->back().part = part;
+      cut->back().in_step = n;
+    }
+    for (int k = 0; k < n; ++k) {
+      DkvItem it = whole;
+      it.qt_first = whole.qt_first + (int)((int64_t)tiles * k / n);
+      it.n_qt = whole.qt_first + (int)((int64_t)tiles * (k + 1) / n);
+      it.part = n > 1 ? part++ : -1;
+      items.push_back(it);
+    }
+  }
+  std::stable_sort(items.begin(), items.end(), [](const DkvItem& a, const DkvItem& b) {
+    const int la = a.n_qt - a.qt_first, lb = b.n_qt - b.qt_first;
+    return la != lb ? la > lb : a.q_row_seg != b.q_row_seg ? a.q_row_seg < b.q_row_seg : a.qt_first < b.qt_first;
+  });
+  return items;
 }
 
 std::vector<FwdItem> cut_items(std::vector<FwdItem>& wholes, int target) {
@@ -314,6 +369,7 @@ std::vector<DkvItem> plan_dkv(const chunk_attn_desc* d, int keys, int side_by_si
       it.qt_first = std::max<int32_t>(0, j0 - C) / 32;  // query i sees key j0 iff i >= j0 - C
       it.n_qt = n_qt;
       it.q_tile0 = q_tile0;
+      it.part = -1;
       items.push_back(it);
     }
     q_tile0 += (s.q_len + 63) / 64;

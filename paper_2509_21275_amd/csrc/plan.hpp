@@ -66,7 +66,9 @@ struct DkvItem {
   int32_t q_tile0;    // index of the segment's first 64-row tile in the padded per-row arrays (LSE, D)
   int32_t reverse;    // 1: the kernel walks the query tiles from the segment's last one down to qt_first (plan_dkv)
   int32_t in_step;    // 1: started only when the blocks of the groups before it (of `side_by_side` blocks) have ended (plan_dkv)
-  int32_t pad1;
+  int32_t part;       // head_dim 96 and 128: slot among the partial results, -1 if the item is not a piece of a cut walk (a piece
+                      // walks the query tiles qt_first .. n_qt - 1 of its own).  A whole item that was cut: its first slot
+                      // (its number of pieces is in in_step)
 };
 
 // Work item of the one-pass backward kernel (head_dim 128): a DkvItem plus what the kernel needs to add its share of dQ
@@ -140,6 +142,13 @@ struct KeySplit {
 // The cut that ends first by the estimate of plan.cpp, given that each item is run for `inner` (key/value head, head
 // split) pairs on `cus` compute units; at most `max_parts` partial results.
 KeySplit choose_key_split(const chunk_attn_desc* d, int tile_rows, int inner, int cus, int64_t max_parts);
+// The same for the walks of key-stationary items (`keys` keys each) over the query tiles, `group` steps per tile; `target` is
+// in tiles (tile_piece_count).
+inline int tile_piece_count(int tiles, int target) { return target > 0 ? (tiles + target - 1) / target : 1; }
+KeySplit choose_tile_split(const chunk_attn_desc* d, int keys, int cus, int64_t max_parts);
+// The key-stationary items to run for such a cut, longest walk first, of equal ones those that walk the same tiles side by
+// side; `cut` receives the whole items that were cut.
+std::vector<DkvItem> cut_items(const std::vector<DkvItem>& wholes, int target, std::vector<DkvItem>* cut);
 // The items to run for a cut: pieces of one item are consecutive.  In `wholes`, items that were cut get the number of their
 // pieces and their first slot.
 std::vector<FwdItem> cut_items(std::vector<FwdItem>& wholes, int target);

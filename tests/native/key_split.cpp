@@ -3,6 +3,7 @@
 //   * the first key of a piece is visible to the item's first row, every piece but the last is visible whole to every row;
 //   * slots of partial results are handed out in order, to pieces of cut items only;
 //   * choose_key_split counts what cut_items makes, respects its limit, cuts chunks with few long walks and no others.
+#include <algorithm>
 #include <cstdio>
 #include <random>
 
@@ -67,6 +68,43 @@ static int one(const std::vector<chunk_attn_seg>& segs, int heads, int kv_heads,
     int64_t sum = 0;
     for (const auto& c : cut) { REQUIRE(c.kv_tile0 > 1 && c.part == sum); sum += c.kv_tile0; }
     REQUIRE(sum == parts);
+  }
+  for (int target : {0, 1, 2, 5, 100000}) {  // key-stationary: every piece a run of its walk's query tiles
+    const auto w = plan_dkv(&d, 128);
+    std::vector<DkvItem> cut;
+    const auto items = cut_items(w, target, &cut);
+    size_t n_items = 0;
+    int32_t part = 0;
+    for (const auto& whole : w) {
+      std::vector<DkvItem> mine;
+      for (const auto& it : items) if (it.kv_row0 == whole.kv_row0) mine.push_back(it);
+      std::sort(mine.begin(), mine.end(), [](const DkvItem& a, const DkvItem& b) { return a.qt_first < b.qt_first; });
+      int next = whole.qt_first;
+      for (const auto& it : mine) {
+        REQUIRE(it.qt_first == next && it.n_qt > it.qt_first && it.q_len == whole.q_len && it.q_tile0 == whole.q_tile0);
+        REQUIRE(it.part == (mine.size() > 1 ? part : -1) && !it.reverse && !it.in_step);
+        if (mine.size() > 1) ++part;
+        next = it.n_qt;
+      }
+      REQUIRE(next == whole.n_qt);
+      n_items += mine.size();
+    }
+    REQUIRE(n_items == items.size());
+    int32_t sum = 0;
+    for (const auto& c : cut) { REQUIRE(c.in_step > 1 && c.part == sum); sum += c.in_step; }
+    REQUIRE(sum == part);
+    for (size_t i = 1; i < items.size(); ++i) REQUIRE(items[i].n_qt - items[i].qt_first <= items[i - 1].n_qt - items[i - 1].qt_first);
+  }
+  for (int64_t limit : {(int64_t)0, (int64_t)5, (int64_t)1 << 40}) {
+    const KeySplit k = choose_tile_split(&d, 128, 256, limit);
+    REQUIRE(k.parts <= limit);
+    if (k.target > 0) {
+      std::vector<DkvItem> cut;
+      const auto items = cut_items(plan_dkv(&d, 128), k.target, &cut);
+      int64_t parts = 0;
+      for (const auto& c : cut) parts += c.in_step;
+      REQUIRE(k.pieces == (int64_t)items.size() && k.parts == parts && parts > 0);
+    }
   }
   for (int64_t limit : {(int64_t)0, (int64_t)3, (int64_t)1 << 40}) {
     const KeySplit k = choose_key_split(&d, rows, inner, 256, limit);

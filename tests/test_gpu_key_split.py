@@ -1,4 +1,4 @@
-"""Chunks with few query rows and long key walks, whose work items the head_dim 128 and 96 forward and dQ kernels cut into pieces:
+"""Chunks with few query rows and long key walks, whose work items the head_dim 128 and 96 kernels cut into pieces:
 against the fp64 oracle (2e-2 for O, 5e-2 for the gradients, as everywhere), against the uncut run (a workspace
 without room for partial results; both are bf16 roundings of float32 sums in different orders, so they differ by about one
 rounding: 2^-7 of the largest value), and bit for bit between the workspace and the static forward."""
@@ -18,6 +18,7 @@ CASES = [  # name, segments, query heads, key/value heads
     ("one_key_past_a_stage", [(0, 65, 0, 1025 + 64)], 16, 2),
     ("mha_256_row_items", [(0, 257, 0, 2000)], 3, 3),
     ("causal_from_the_start", [(0, 1900, 0, 1900)], 2, 1),
+    ("key_blocks_cut_too", [(0, 700, 0, 1100)], 8, 2),
     ("cut_and_uncut_items", [(0, 130, 3, 1630), (130, 70, 1640, 70), (200, 1, 1710, 900), (201, 300, 2612, 300)], 6, 2),
 ]
 
@@ -70,7 +71,7 @@ def test_cut_walks(oracle_mod, name, segs, hq, hk, d):
 @pytest.mark.parametrize("d", [128, 96])
 def test_cut_walks_that_take_the_second_pass(oracle_mod, d):
     """Every piece raises its item's flag: the whole items are recomputed, not put together."""
-    case = _case(*CASES[6], d)
+    case = _case(*CASES[7], d)
     q, k, v, _ = make_inputs(case)
     ca.chunk_attn_test_set_fwd_rescale_limit(-1e30)
     try:
@@ -92,3 +93,25 @@ def test_piece_whose_scores_outgrow_its_first_stage(oracle_mod):
     o, lse = run_gpu(case, q, k, v, backward=False)
     O, LSE = oracle_mod.Oracle(case.segs, q.cpu(), k.cpu(), v.cpu(), None, case.scale).forward()
     assert rel_err(o, O) <= TOL_O and _lse_err(lse, LSE) <= TOL_LSE_SECOND_PASS
+
+
+@pytest.mark.parametrize("d", [128, 96])
+@pytest.mark.parametrize("f32kv", [False, True])
+def test_cut_key_blocks_accumulate(oracle_mod, f32kv, d):
+    """dK / dV of key blocks whose walks over the queries were cut, added to what the buffers hold; rows outside every key
+    range stay as they are; the same bits on a second run."""
+    segs = [(0, 1100, 5, 1400), (1100, 77, 1410, 77)]
+    case = _case("cut_accumulate", segs, 6, 2, d)
+    q, k, v, do = make_inputs(case)
+    init = torch.full(k.shape, 3.0, device=q.device, dtype=torch.float32 if f32kv else torch.bfloat16)
+    got = run_gpu(case, q, k, v, do, accumulate=True, dk_init=init, dv_init=init, f32kv=f32kv)
+    again = run_gpu(case, q, k, v, do, accumulate=True, dk_init=init, dv_init=init, f32kv=f32kv)
+    assert all(torch.equal(a, b) for a, b in zip(got, again))
+    cov = torch.zeros(case.total_kv, dtype=torch.bool)
+    for s in segs:
+        cov[s[2]:s[2] + s[3]] = True
+    orc = oracle_mod.Oracle(case.segs, q.cpu(), k.cpu(), v.cpu(), do.cpu(), case.scale)
+    orc.forward()
+    _, dK, dV = orc.backward()
+    for g, w in ((got[3], dK), (got[4], dV)):
+        assert torch.all(g.cpu()[~cov] == 3.0) and rel_err(g.cpu()[cov], w[cov.numpy()] + 3.0) <= TOL_GRAD
