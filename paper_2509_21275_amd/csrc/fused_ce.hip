@@ -3,12 +3,16 @@
 // HBM-bound by construction: one workgroup of 512 threads owns one row of logits at a time, loads it once (16 bytes per
 // lane and load, consecutive lanes consecutive chunks: fully coalesced), reduces the maximum and the sum of
 // exponentials across the workgroup, and stores the gradient over the logits.  Algorithmic traffic: 4 bytes per logit.
-// The exponential of an element is evaluated twice (for the sum and for the gradient) rather than kept.  The sum is
-// taken while the row arrives, against the running maximum of the thread's own chunks (moved once per group of chunks),
-// and the threads' (maximum, sum) pairs are merged once per row: one exchange through LDS, and only the gradient's
-// vector work is left between the last load and the first store.  Workgroups walk the rows with a grid stride.
-// Measured on 4096 rows of 151936 logits: 538 us, 4.6 TB/s (a copy of the same bytes by the runtime: 5.2 TB/s); with the row
-// read three times, as rows beyond 131072 logits were before the LDS part existed, 780 us.
+// The exponential of an element is evaluated twice (for the sum and for the gradient) rather than kept: the vector work of
+// a row is several times shorter than the time HBM needs to deliver it.  Workgroups walk the rows with a grid stride.
+//
+// Two kernels.  Rows of up to 131072 logits (fused_ce_kernel) stay in 128 registers per lane; maximum and sum are two passes
+// over them.  Longer rows (fused_ce_long_kernel) take more registers and LDS; with one workgroup per compute unit nothing
+// hides the vector work between the last load and the first store, so the sum is taken while the row arrives, against the
+// running maximum of the thread's own chunks (moved once per group of chunks), and the threads' (maximum, sum) pairs are
+// merged once per row.  Measured: 4096 rows of 151936 logits 538 us, 4.6 TB/s (a copy of the same bytes by the runtime: 5.2
+// TB/s; with three passes over memory, as such rows took before: 780 us), 2048 of 200064 539 -> 391 us.  On shorter rows the
+// one-pass sum is the slower one (16384 rows of 8000: 119 -> 148 us; 256 of 64000: 14.1 -> 15.0).
 #include <hip/hip_runtime.h>
 
 #include "../../include/fused_ce.h"
@@ -32,12 +36,86 @@ __device__ __forceinline__ float wave_sum(float x) {
   return x;
 }
 
-// NCH: 16-byte chunks per thread kept in registers, NL: further ones kept in LDS (a row has at most
+// NCH: 16-byte chunks per thread (a row has at most 512 * 8 * NCH logits; 32 chunks = 128 registers is what fits)
+template <int NCH>
+__global__ __launch_bounds__(kThreads) void fused_ce_kernel(__bf16* __restrict__ logits, const int32_t* __restrict__ targets,
+                                                            float* __restrict__ loss, int64_t rows, int vocab,
+                                                            int64_t row_stride, float grad_scale) {
+  __shared__ float red[2][kThreads / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n_chunks = vocab / 8;
+  for (int64_t row = blockIdx.x; row < rows; row += gridDim.x) {
+    __bf16* const z = logits + row * row_stride;
+    const int y = targets[row];
+    const bool ignored = y < 0 || y >= vocab;
+    const float zy = ignored ? 0.f : (float)z[y];  // read before the row is overwritten (every thread: one cached load)
+    bf16x8 v[NCH];
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+      const int ch = c * kThreads + tid;
+      if (ch < n_chunks) v[c] = *reinterpret_cast<const bf16x8*>(z + (int64_t)ch * 8);
+    }
+    // Between the three passes the row is kept as it was loaded (packed bf16): the opaque statements stop the compiler
+    // from keeping a widened fp32 copy of the whole row alive, which would not fit the register file.
+    float mx = -INFINITY;
+#pragma unroll
+    for (int c = 0; c < NCH; ++c)
+      if (c * kThreads + tid < n_chunks) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) mx = fmaxf(mx, (float)v[c][e]);
+      }
+    mx = wave_max(mx);
+    if (lane == 0) red[0][wave] = mx;
+    __syncthreads();
+    mx = red[0][0];
+#pragma unroll
+    for (int w = 1; w < kThreads / 64; ++w) mx = fmaxf(mx, red[0][w]);
+    const float m2 = mx * kLog2e;
+    float sum = 0.f;
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) asm volatile("" : "+v"(v[c]));
+#pragma unroll
+    for (int c = 0; c < NCH; ++c)
+      if (c * kThreads + tid < n_chunks) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) sum += __builtin_amdgcn_exp2f((float)v[c][e] * kLog2e - m2);
+      }
+    sum = wave_sum(sum);
+    if (lane == 0) red[1][wave] = sum;
+    __syncthreads();
+    sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < kThreads / 64; ++w) sum += red[1][w];
+    const float lse2 = m2 + __builtin_amdgcn_logf(sum);  // log2 of the sum of exponentials
+    if (tid == 0) loss[row] = ignored ? 0.f : lse2 * kLn2 - zy;
+    const float scale = ignored ? 0.f : grad_scale;
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) asm volatile("" : "+v"(v[c]));
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+      const int ch = c * kThreads + tid;
+      if (ch < n_chunks) {
+        const int d = y - ch * 8;  // position of the target inside this chunk, if it is there
+        bf16x8 g;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          float pe = __builtin_amdgcn_exp2f((float)v[c][e] * kLog2e - lse2);
+          if (d == e) pe -= 1.0f;
+          g[e] = (__bf16)(pe * scale);
+        }
+        *reinterpret_cast<bf16x8*>(z + (int64_t)ch * 8) = g;
+      }
+    }
+    __syncthreads();  // red[] is reused by the next row
+  }
+}
+
+// Longer rows, up to 262144 logits.  NCH: 16-byte chunks per thread kept in registers, NL: further ones kept in LDS (a row has at most
 // 512 * 8 * (NCH + NL) logits).  A compute unit has 512 KB of registers and 160 KB of LDS and a row of 262144 logits takes
 // 512 KB, so the longest rows need both: chunks past the NCH-th are copied global -> LDS (wave w's chunk c in 1 KB at
 // c * 8 + w; each lane reads back what its own wave copied, so no barrier is needed).
 template <int NCH, int NL>
-__global__ __launch_bounds__(kThreads) void fused_ce_kernel(__bf16* __restrict__ logits, const int32_t* __restrict__ targets,
+__global__ __launch_bounds__(kThreads) void fused_ce_long_kernel(__bf16* __restrict__ logits, const int32_t* __restrict__ targets,
                                                             float* __restrict__ loss, int64_t rows, int vocab,
                                                             int64_t row_stride, float grad_scale) {
   constexpr int NW = kThreads / 64;
@@ -112,7 +190,7 @@ __global__ __launch_bounds__(kThreads) void fused_ce_kernel(__bf16* __restrict__
     }
     if constexpr (NL > 0) {
       __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's copies have landed
-#pragma unroll 1
+#pragma unroll 3
       for (int c0 = 0; c0 < NL; c0 += GRP) {
         if ((NCH + c0) * kThreads >= n_chunks) break;
         bf16x8 g[GRP];
@@ -175,16 +253,19 @@ __global__ __launch_bounds__(kThreads) void fused_ce_kernel(__bf16* __restrict__
 template <int NCH, int NL = 0>
 hipError_t launch(void* logits, const int32_t* targets, float* loss, int64_t rows, int vocab, int64_t row_stride,
                   float grad_scale, hipStream_t stream) {
-  constexpr size_t smem = (size_t)NL * kThreads * 16;
-  if constexpr (NL > 0) {
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&fused_ce_kernel<NCH, NL>),
+  // two workgroups per compute unit when the registers allow it, rows dealt round robin
+  const dim3 grid((unsigned)(rows < 512 ? rows : 512));
+  if constexpr (NCH <= 32) {
+    hipLaunchKernelGGL((fused_ce_kernel<NCH>), grid, dim3(kThreads), 0, stream, (__bf16*)logits, targets, loss, rows, vocab,
+                       row_stride, grad_scale);
+  } else {
+    constexpr size_t smem = (size_t)NL * kThreads * 16;
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&fused_ce_long_kernel<NCH, NL>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (attr != hipSuccess) return attr;
+    hipLaunchKernelGGL((fused_ce_long_kernel<NCH, NL>), grid, dim3(kThreads), smem, stream, (__bf16*)logits, targets, loss, rows,
+                       vocab, row_stride, grad_scale);
   }
-  // two workgroups per compute unit when the registers allow it, rows dealt round robin
-  const int64_t grid = rows < 512 ? rows : 512;
-  hipLaunchKernelGGL((fused_ce_kernel<NCH, NL>), dim3((unsigned)grid), dim3(kThreads), smem, stream, (__bf16*)logits, targets,
-                     loss, rows, vocab, row_stride, grad_scale);
   return hipGetLastError();
 }
 
