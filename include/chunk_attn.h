@@ -85,7 +85,7 @@ typedef struct {
 /*
  * Scratch sizes (bytes) for a descriptor: *fwd_bytes for chunk_attn_fwd, *bwd_bytes for
  * chunk_attn_bwd (the tile schedules, the row sums D_i = <dO_i, O_i>, transposed tile images
- * of operands (head_dim 64 and 256) or float32 partial results (96 and 128); for head_dim 96
+ * of V (head_dim 64 and 256) or float32 partial results (96 and 128); for head_dim 96
  * also room for zero-padded copies of the tensors, 128 wide).  Either output pointer may be NULL.  Validates the descriptor.
  */
 int chunk_attn_workspace_bytes(const chunk_attn_desc* desc, size_t* fwd_bytes, size_t* bwd_bytes);

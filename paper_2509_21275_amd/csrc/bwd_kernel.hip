@@ -8,7 +8,6 @@
 //
 //   bwd_pre   D_i = <dO_i, O_i> and LSE_i log2(e) per (head, row), stored in arrays padded to 64-row
 //             tiles per segment (+inf / 0 in the padding, so padded rows yield P = 0);
-//   transpose (transpose_kernel.hip) of K into 32-row tile images, for the dQ kernel;
 //   bwd_dq    query-stationary, like the forward: S^T = K Q^T and dP^T = V dO^T per 32-key tile,
 //             dS^T = P^T (dP^T - D), dQ^T += K^T dS^T with dS^T fed back from the accumulator registers;
 //   bwd_dkv   key-stationary: one workgroup per 128 keys of one key/value head, walking the query heads of
@@ -82,12 +81,11 @@ __global__ __launch_bounds__(256) void zero_fill_kernel(u32x4* __restrict__ p, i
 // ------------------------------------------------------------------------------------------------
 struct DqParams {
   const __bf16 *q, *k, *v, *d_o;
-  const __bf16* kt;      // transposed K images [Hkv][total_kv32_tiles][D][32]
   const float* lse2p;    // [Hq][total_q_tiles * 64]
   const float* dsp;
   __bf16* dq;
   const DqItem* items;
-  int64_t total_kv32_tiles, total_q_tiles;
+  int64_t total_q_tiles;
   int32_t num_q_heads, num_kv_heads, group, heads_per_wg, head_splits;
   float scale, scale_log2;
   float* parts;          // partial results of pieces (pipelined kernel), kPartRowFloats per (slot, inner index)
@@ -95,6 +93,9 @@ struct DqParams {
   unsigned long long* clock_log;  // null, or where the pipelined kernel's workgroups log their clocks
 };
 
+// (head_dim 64 unless its walks are long, and 256.)  K^T is read transposed out of the K tile; with an image of K made by a
+// launch before, as this kernel had it, the backward of four sequences of 1024, 32/8 heads, took 144 us instead of 141, of
+// 64 of 256 220 instead of 211, and at head_dim 256 the packed 64K chunk 41.2 ms (forward included) instead of 40.2.
 template <int D, int WAVES>
 __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void bwd_dq_kernel(DqParams p) {
   constexpr int NTH = WAVES * 64;  // threads
@@ -107,9 +108,8 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void bwd_dq_ke
   constexpr int NS = 3;        // LDS stages: tiles are fetched NS - 1 iterations ahead
 
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  __bf16* Ks = reinterpret_cast<__bf16*>(smem);  // [NS][BN][D]
+  __bf16* Ks = reinterpret_cast<__bf16*>(smem);  // [NS][BN][D]  chunk-major; K^T is read from it, too
   __bf16* Vs = Ks + NS * KT;                     // [NS][BN][D]
-  __bf16* Ts = Vs + NS * KT;                     // [NS][D][BN]  K^T image
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -134,37 +134,30 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void bwd_dq_ke
   const int64_t q_stride = (int64_t)p.num_q_heads * D, kv_stride = (int64_t)p.num_kv_heads * D;
   const __bf16* __restrict__ Kg = p.k + (int64_t)it.kv_row0 * kv_stride + (int64_t)kvh * D;
   const __bf16* __restrict__ Vg = p.v + (int64_t)it.kv_row0 * kv_stride + (int64_t)kvh * D;
-  const __bf16* __restrict__ Timg = p.kt + ((int64_t)kvh * p.total_kv32_tiles + it.kv_tile0) * KT;
 
-  constexpr int NK = BN * KC / NTH, NT = KT / 8 / NTH;
-  static_assert(NK >= 1 && NT >= 1, "every thread copies at least one chunk of each tile");
+  constexpr int NK = BN * KC / NTH;
+  static_assert(NK >= 1, "every thread copies at least one chunk of each tile");
   unsigned k_src[NK];
   int k_row[NK];
 #pragma unroll
   for (int i = 0; i < NK; ++i) {
     const int x = (i * WAVES + wave) * 64 + lane;
-    k_row[i] = x / KC;
-    k_src[i] = (unsigned)(k_row[i] * (int)kv_stride + unswz<KC>(k_row[i], x % KC) * 8);
+    k_row[i] = (x & 31) ^ (((x >> 5) & 3) << 2);
+    k_src[i] = (unsigned)(k_row[i] * (int)kv_stride + (x >> 5) * 8);
   }
-  // One tile is copied by NK + NT pieces per lane (piece i < NK: a K and a V chunk; else a K^T image chunk), so
-  // that the copies can be issued between MFMAs instead of in one burst.
+  // One tile is copied by NK pieces per lane (a K and a V chunk each), so that the copies can be issued between MFMAs
+  // instead of in one burst.
   auto dma_piece = [&](int t, int buf, int i) {
-    if (i < NK) {
-      const int64_t toff = (int64_t)(BN * t) * kv_stride;  // wave-uniform
-      const int last_row = n_wg - 1 - BN * t;
-      unsigned off = k_src[i];
-      if (last_row < BN - 1) off -= (unsigned)((k_row[i] - min(k_row[i], last_row)) * (int)kv_stride);
-      dma16(Kg + toff + off, Ks + buf * KT + (i * WAVES + wave) * 512);
-      dma16(Vg + toff + off, Vs + buf * KT + (i * WAVES + wave) * 512);
-    } else {
-      const int j = i - NK;
-      const __bf16* tsrc = Timg + (int64_t)t * KT;
-      dma16(tsrc + (unsigned)(((j * WAVES + wave) * 64 + lane) * 8), Ts + buf * KT + (j * WAVES + wave) * 512);
-    }
+    const int64_t toff = (int64_t)(BN * t) * kv_stride;  // wave-uniform
+    const int last_row = n_wg - 1 - BN * t;
+    unsigned off = k_src[i];
+    if (last_row < BN - 1) off -= (unsigned)((k_row[i] - min(k_row[i], last_row)) * (int)kv_stride);
+    dma16(Kg + toff + off, Ks + buf * KT + (i * WAVES + wave) * 512);
+    dma16(Vg + toff + off, Vs + buf * KT + (i * WAVES + wave) * 512);
   };
   auto dma_tile = [&](int t, int buf) {
 #pragma unroll
-    for (int i = 0; i < NK + NT; ++i) dma_piece(t, buf, i);
+    for (int i = 0; i < NK; ++i) dma_piece(t, buf, i);
   };
 
   // Q and dO fragments (B operands): lane holds X[row = l32][16 ks + 8 hh ..+7]
@@ -193,15 +186,19 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void bwd_dq_ke
   for (int db = 0; db < DB; ++db) dq[db] = zero16;
   const float c = p.scale_log2;
 
-  int k_off[DK], t_off[2];
-#pragma unroll
-  for (int ks = 0; ks < DK; ++ks) k_off[ks] = tile_elem<KC>(l32, 2 * ks + hh);
-#pragma unroll
-  for (int ks = 0; ks < 2; ++ks) t_off[ks] = tile_elem<4>(l32, 2 * ks + hh);
+  // (addresses inside a tile as in the pipelined kernels)
+  const int x_off[2] = {cm_elem(l32, hh), cm_elem(l32, 2 + hh)};
+  auto k_off = [&](int ks) { return x_off[ks & 1] + (ks >> 1) * (4 * 32 * 8); };
+  unsigned t_lo, t_hi;
+  {
+    const int j = lane & 15, cl = 2 * ((lane >> 4) & 1) + ((j & 3) >> 1), r0 = 4 * hh + (j >> 2);
+    t_lo = lds_addr((lds_bf16*)Ks + cm_elem(r0, cl) + 4 * (j & 1));
+    t_hi = lds_addr((lds_bf16*)Ks + cm_elem(r0 + 8, cl) + 4 * (j & 1));
+  }
 
-  // wait until at most `tiles_in_flight` later tiles are still being copied (each is NK * 2 + NT copies per lane)
+  // wait until at most `tiles_in_flight` later tiles are still being copied (each is 2 NK copies per lane)
   auto wait_tiles = [&](int tiles_in_flight) {
-    constexpr int PER = 2 * NK + NT;
+    constexpr int PER = 2 * NK;
     if (tiles_in_flight <= 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER) : "memory");
   };
@@ -216,12 +213,11 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void bwd_dq_ke
     if (t < nt_w) {
       const __bf16* Kt = Ks + buf * KT;
       const __bf16* Vt = Vs + buf * KT;
-      const __bf16* Tt = Ts + buf * KT;
       // The loop body is laid out as stages separated by scheduling fences: each stage issues the LDS reads
       // of the next stage's operands together with the MFMAs of the current one, so the reads' latency is
       // covered by matrix work instead of stalling every MFMA on the read issued just before it.
-      auto ldk = [&](int ks) { return *reinterpret_cast<const bf16x8*>(Kt + k_off[ks]); };
-      auto ldv = [&](int ks) { return *reinterpret_cast<const bf16x8*>(Vt + k_off[ks]); };
+      auto ldk = [&](int ks) { return *reinterpret_cast<const bf16x8*>(Kt + k_off(ks)); };
+      auto ldv = [&](int ks) { return *reinterpret_cast<const bf16x8*>(Vt + k_off(ks)); };
       // ---- S^T = K Q^T, dP^T = V dO^T : [32 keys] x [32 queries] ----
       f32x16 s, dp;
       bf16x8 ak[2][2], av[2][2];  // [parity of the k-step pair][step in the pair]
@@ -236,18 +232,19 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void bwd_dq_ke
         }
         s = mfma32(ak[cur][0], qf[2 * g], g == 0 ? zero16 : s);
         dp = mfma32(av[cur][0], gf[2 * g], g == 0 ? zero16 : dp);
-        if (prefetch && g < NK + NT) dma_piece(t + NS - 1, (buf + NS - 1) % NS, g);
+        if (prefetch && g < NK) dma_piece(t + NS - 1, (buf + NS - 1) % NS, g);
         s = mfma32(ak[cur][1], qf[2 * g + 1], s);
         dp = mfma32(av[cur][1], gf[2 * g + 1], dp);
         __builtin_amdgcn_sched_barrier(0);
       }
       // operands of dQ^T += K^T dS^T, fetched while the exponentials are computed
-      bf16x8 at[2][DB];
-#pragma unroll
-      for (int db = 0; db < DB; ++db) {
-        at[0][db] = *reinterpret_cast<const bf16x8*>(Tt + t_off[0] + db * 32 * BN);
-        at[1][db] = *reinterpret_cast<const bf16x8*>(Tt + t_off[1] + db * 32 * BN);
-      }
+      s16x4 a_lo[2 * DB], a_hi[2 * DB];  // k-step m / DB, block m % DB
+      static_for<0, 2 * DB>([&](auto m_c) __attribute__((always_inline)) {
+        constexpr int m = decltype(m_c)::value;
+        constexpr int off = (buf * KT + (m / DB) * (16 * 8) + (m % DB) * (4 * 32 * 8)) * 2;
+        a_lo[m] = lds_asm_read_tr<off>(t_lo);
+        a_hi[m] = lds_asm_read_tr<off>(t_hi);
+      });
       // ---- P = exp2(S c - LSE), dS = P (dP - D); masked keys give P = 0 ----
       float pe[16];
 #pragma unroll
@@ -267,10 +264,13 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void bwd_dq_ke
       const bf16x8 f1 = pack8(ds[8], ds[9], ds[10], ds[11], ds[12], ds[13], ds[14], ds[15]);
       __builtin_amdgcn_sched_barrier(0);
       // ---- dQ^T += K^T dS^T : [D] x [32 queries], contraction over the 32 keys ----
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-      for (int db = 0; db < DB; ++db) dq[db] = mfma32(at[0][db], f0, dq[db]);
-#pragma unroll
-      for (int db = 0; db < DB; ++db) dq[db] = mfma32(at[1][db], f1, dq[db]);
+      for (int m = 0; m < 2 * DB; ++m) {
+        asm volatile("" : "+v"(a_lo[m]), "+v"(a_hi[m]));  // (after the wait, in this order)
+        const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(a_lo[m], a_hi[m], 0, 1, 2, 3, 4, 5, 6, 7));
+        dq[m % DB] = mfma32(a, m < DB ? f0 : f1, dq[m % DB]);
+      }
     }
     // tile t + 1 must have landed; tiles t + 2 .. may still be in flight
     wait_tiles(min(nt_wg - 1, t + NS - 1) - (t + 1));
@@ -2546,10 +2546,8 @@ template <int D>
 hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPlan& P, hipStream_t stream) {
   char* ws = a.workspace;
   const TileJob* qjobs = reinterpret_cast<const TileJob*>(ws + P.qjobs_off);
-  const TileJob* kjobs = reinterpret_cast<const TileJob*>(ws + P.kjobs_off);
   float* lse2p = reinterpret_cast<float*>(ws + P.lse2p_off);
   float* dsp = reinterpret_cast<float*>(ws + P.dsp_off);
-  __bf16* kt = reinterpret_cast<__bf16*>(ws + P.kt_off);
   hipError_t e;
 
   // pre-pass: D, scaled LSE, transposed operand images
@@ -2560,10 +2558,6 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
                        P.q_tiles, d->total_q, d->num_q_heads, lse2p, dsp);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  if (!P.dq_pipe) {  // the pipelined dQ kernel reads K^T from its K tiles
-    if ((e = launch_transpose(a.k, d->num_kv_heads, D, 32, kjobs, (int)P.kjobs.size(), P.kv32_tiles, kt, stream)) != hipSuccess) return e;
-  }
-
   if (!a.accumulate) {  // rows no segment covers receive no gradient
     for (const auto& gap : uncovered_kv_ranges(d)) {
       const int esz = a.dkv_f32 ? 4 : 2;  // bytes per element of dK / dV
@@ -2582,9 +2576,9 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
   }
   {  // dQ
     DqParams p;
-    p.q = a.q; p.k = a.k; p.v = a.v; p.d_o = a.d_o; p.kt = kt; p.lse2p = lse2p; p.dsp = dsp; p.dq = a.dq;
+    p.q = a.q; p.k = a.k; p.v = a.v; p.d_o = a.d_o; p.lse2p = lse2p; p.dsp = dsp; p.dq = a.dq;
     p.items = reinterpret_cast<const DqItem*>(ws + P.dq_items_off);
-    p.total_kv32_tiles = P.kv32_tiles; p.total_q_tiles = P.q_tiles;
+    p.total_q_tiles = P.q_tiles;
     p.num_q_heads = d->num_q_heads; p.num_kv_heads = d->num_kv_heads; p.group = group;
     p.heads_per_wg = heads_per_wg(group, P.dq_waves); p.head_splits = group / p.heads_per_wg;
     p.scale = d->softmax_scale; p.scale_log2 = d->softmax_scale * kLog2e;
@@ -2616,7 +2610,7 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
     }
     if constexpr (!pipelined(D)) {
       if (!P.dq_pipe) {
-        const size_t smem = (size_t)9 * 32 * D * 2;  // 3 stages of K, V and K^T tiles
+        const size_t smem = (size_t)6 * 32 * D * 2;  // 3 stages of K and V tiles
         constexpr int DQW = 4;
         static const hipError_t attr = raise_smem_limit(&bwd_dq_kernel<D, DQW>, smem);
         if (attr != hipSuccess) return attr;
@@ -2715,7 +2709,6 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, bool may_c
   if (!pipe) P.dkv_pipe = (int64_t)n_dkv_blocks(d) * d->num_kv_heads >= kMinDkvPipeBlocks;
   const int dq_rows = tile_rows(group, P.dq_waves);
   P.q_tiles = count_tiles(d, false, 64);
-  P.kv32_tiles = count_tiles(d, true, 32);
   P.qt32_tiles = count_tiles(d, false, 32);
   // head_dim 128: room for dQ tiles in float32, for the one-pass backward or for the partial results of cut dQ walks
   const size_t dq_tile_bytes = pipe ? (size_t)fused_num_bufs(d, dkv_keys(128)) * d->num_q_heads * P.qt32_tiles * 4096 * sizeof(float) : 0;
@@ -2740,7 +2733,6 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, bool may_c
       if (P.dkv_split.target > 0) P.dkv_items = cut_items(P.dkv_items, P.dkv_split.target, &P.dkv_cut);
     }
     P.qjobs = tile_jobs(d, false, 64, nullptr);
-    if (!P.dq_pipe) P.kjobs = tile_jobs(d, true, 32, nullptr);
   }
   // the layout does not depend on which backward runs: item counts follow from the segment table
   for (int t = 0; t < d->num_segments; ++t) {
@@ -2755,8 +2747,7 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, bool may_c
   P.dkv_items_off = P.dq_cut_off + up256(n_dq * sizeof(DqItem));
   P.dkv_cut_off = P.dkv_items_off + (P.dkv_split.target > 0 ? up256((size_t)P.dkv_split.pieces * sizeof(DkvItem)) : 0);
   P.qjobs_off = P.dkv_cut_off + up256(n_dkv * sizeof(DkvItem));
-  P.kjobs_off = P.qjobs_off + up256((size_t)P.q_tiles * sizeof(TileJob));
-  P.fitems_off = P.kjobs_off + (pipe ? 0 : up256((size_t)P.kv32_tiles * sizeof(TileJob)));
+  P.fitems_off = P.qjobs_off + up256((size_t)P.q_tiles * sizeof(TileJob));
   // the workspace is sized for either backward (the mode may change between the size query and the call): the one-pass
   // backward has one item per (key block, key/value head) and at most 8 x that many workgroup slots
   const size_t n_fused = d->head_dim == 128 ? n_dkv_blocks(d) * (size_t)d->num_kv_heads : 0;
@@ -2771,10 +2762,8 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, bool may_c
   P.fprog_bytes = up256(n_fused * 4 * sizeof(unsigned)) + 256 + kFusedSinkBytes;
   P.lse2p_off = P.fprog_off + P.fprog_bytes;
   P.dsp_off = P.lse2p_off + up256(row_slots * sizeof(float));
-  P.kt_off = P.dsp_off + up256(row_slots * sizeof(float));
-  // transposed K images only for head_dim 64 (the head_dim 128 dQ kernel reads K^T from its K tiles)
-  // (256 bytes remain in any case: the dK/dV kernels copy the LSE / D rows 64 at a time, up to 32 past a segment's last)
-  P.fdq_off = P.kt_off + (d->head_dim == 128 ? 256 : up256((size_t)d->num_kv_heads * P.kv32_tiles * 32 * d->head_dim * sizeof(__bf16)));
+  // (256 bytes remain: the dK/dV kernels copy the LSE / D rows 64 at a time, up to 32 past a segment's last)
+  P.fdq_off = P.dsp_off + up256(row_slots * sizeof(float)) + 256;
   P.total = P.fdq_off + dq_tile_bytes;
 }
 
@@ -2785,7 +2774,6 @@ std::vector<char> bwd_blob(const BwdPlan& P) {
   std::memcpy(blob.data() + P.dkv_items_off, P.dkv_items.data(), P.dkv_items.size() * sizeof(DkvItem));
   std::memcpy(blob.data() + P.dkv_cut_off, P.dkv_cut.data(), P.dkv_cut.size() * sizeof(DkvItem));
   std::memcpy(blob.data() + P.qjobs_off, P.qjobs.data(), P.qjobs.size() * sizeof(TileJob));
-  std::memcpy(blob.data() + P.kjobs_off, P.kjobs.data(), P.kjobs.size() * sizeof(TileJob));
   if (P.fused) {
     std::memcpy(blob.data() + P.fitems_off, P.fplan.items.data(), P.fplan.items.size() * sizeof(FusedItem));
     std::memcpy(blob.data() + P.forder_off, P.fplan.order.data(), P.fplan.order.size() * sizeof(int32_t));

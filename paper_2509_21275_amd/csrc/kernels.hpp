@@ -94,8 +94,8 @@ struct BwdArgs {
 };
 
 // Host-side plan of one backward call and the layout of its workspace:
-// [dQ items | dQ items that were cut | dK/dV items | dK/dV items that were cut | 64-row query-tile jobs | 32-row key-tile jobs] (one uploaded blob), then
-// the LSE and D arrays padded to 64-row tiles and the transposed images of K (32-row tiles; not for head_dim 128).
+// [dQ items | dQ items that were cut | dK/dV items | dK/dV items that were cut | 64-row query-tile jobs] (one uploaded blob), then the
+// LSE and D arrays padded to 64-row tiles.
 struct BwdPlan {
   KeySplit split;                // head_dim 128: how the dQ walks are cut
   std::vector<DqItem> dq_items;  // with the pieces of walks that are cut
@@ -103,11 +103,11 @@ struct BwdPlan {
   KeySplit dkv_split;            // the same for the dK/dV walks
   std::vector<DkvItem> dkv_cut;
   std::vector<DkvItem> dkv_items;
-  std::vector<TileJob> qjobs, kjobs;
-  int64_t q_tiles = 0, kv32_tiles = 0;
+  std::vector<TileJob> qjobs;
+  int64_t q_tiles = 0;
   size_t n_dq_cut = 0, n_dkv_cut = 0;
-  size_t dq_items_off = 0, dq_cut_off = 0, dkv_items_off = 0, dkv_cut_off = 0, qjobs_off = 0, kjobs_off = 0, queues_off = 0, blob_bytes = 0;
-  size_t lse2p_off = 0, dsp_off = 0, kt_off = 0, total = 0;
+  size_t dq_items_off = 0, dq_cut_off = 0, dkv_items_off = 0, dkv_cut_off = 0, qjobs_off = 0, queues_off = 0, blob_bytes = 0;
+  size_t lse2p_off = 0, dsp_off = 0, total = 0;
   // one-pass backward (head_dim 128): its items and workgroup order travel at the end of the blob; then the per-wave
   // progress counters and the status word (cleared by a kernel on every call) and the float32 dQ tiles
   bool dq_pipe = false, dkv_pipe = false;  // the pipelined kernels run (head_dim 96 and 128 always, 256 never)

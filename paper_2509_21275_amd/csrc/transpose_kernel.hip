@@ -1,11 +1,11 @@
-// Pre-pass that prepares transposed operand tiles.
+// Pre-pass that prepares transposed operand tiles (V for the head_dim 256 forward).
 //
-// For X[rows][H][D] (bf16) and a list of W-row tiles (W = 64 or 32), writes for every (head, tile) an "image"
+// For X[rows][H][D] (bf16) and a list of W-row tiles, writes for every (head, tile) an "image"
 // T[D][W] with T[c][p] = X[row0 + cperm(p)][head][c] (zero past the tile's valid rows), already in
-// the swizzled chunk order in which the attention kernels keep it in LDS.  The attention kernels then
-// fetch an image with a linear global->LDS copy and read MFMA operands whose contraction index runs
-// along X's row index (V^T for O += P V, K^T for dQ += dS K, Q^T and dO^T for dK, dV) with plain
-// 16-byte LDS reads.  Cost: one read and one write of X, negligible next to the attention itself.
+// the swizzled chunk order in which the attention kernels keep it in LDS.  The attention kernel then
+// fetches an image with a linear global->LDS copy and reads MFMA operands whose contraction index runs
+// along X's row index (V^T for O += P V) with plain 16-byte LDS reads.  Cost: one read and one write of X,
+// negligible next to the attention itself at this head dimension.
 #include "kernels.hpp"
 #include "tiles.hpp"
 
@@ -55,10 +55,8 @@ hipError_t launch_transpose(const __bf16* x, int num_heads, int head_dim, int wi
   if (num_jobs == 0) return hipSuccess;
   const int64_t blocks = (int64_t)num_jobs * num_heads;
   if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-  if (head_dim == 64 && width == 32) launch_t<64, 32>(x, num_heads, jobs, blocks, total_tiles, out, stream);
-  else if (head_dim == 256 && width == 64) launch_t<256, 64>(x, num_heads, jobs, blocks, total_tiles, out, stream);
-  else if (head_dim == 256 && width == 32) launch_t<256, 32>(x, num_heads, jobs, blocks, total_tiles, out, stream);
-  else return hipErrorInvalidValue;
+  if (head_dim != 256 || width != 64) return hipErrorInvalidValue;
+  launch_t<256, 64>(x, num_heads, jobs, blocks, total_tiles, out, stream);
   return hipGetLastError();
 }
 
