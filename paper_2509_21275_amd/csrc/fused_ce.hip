@@ -10,7 +10,7 @@
 // over them.  Longer rows (fused_ce_long_kernel) take more registers and LDS; with one workgroup per compute unit nothing
 // hides the vector work between the last load and the first store, so the sum is taken while the row arrives, against the
 // running maximum of the thread's own chunks (moved once per group of chunks), and the threads' (maximum, sum) pairs are
-// merged once per row.  Measured: 4096 rows of 151936 logits 538 us, 4.6 TB/s (a copy of the same bytes by the runtime: 5.2
+// merged once per row.  Measured: 4096 rows of 151936 logits 538 us, 4.6 TB/s (a copy of the same bytes by the runtime: 5.5
 // TB/s; with three passes over memory, as such rows took before: 780 us), 2048 of 200064 539 -> 391 us.  On shorter rows the
 // one-pass sum is the slower one (16384 rows of 8000: 119 -> 148 us; 256 of 64000: 14.1 -> 15.0).
 #include <hip/hip_runtime.h>
