@@ -161,20 +161,28 @@ static KeySplit choose_cut(const std::vector<Walk>& walks, int longest, int shor
   const auto later = [](int64_t a, int64_t b) { return a > b; };
   std::vector<int> cost;
   std::vector<int64_t> free_at;
-  auto estimate = [&](KeySplit& k) -> int64_t {
+  int64_t total = 0;  // work of queue 0
+  // `limit`: a cut that cannot end before it is not followed to its end (the result is then some time not below it)
+  auto estimate = [&](KeySplit& k, int64_t limit) -> int64_t {
     cost.clear();
     k.pieces = k.parts = 0;
-    int64_t block = 0;
+    int64_t block = 0, sum = 0;
     for (const Walk& w : walks) {
       const int n = pieces(w, k.target);
       k.pieces += n;
       if (n > 1) k.parts += n;
       for (int i = 0; i < n; ++i) {
         const int64_t end = block + inner;  // blocks block .. end - 1; those divisible by 8 are queue 0's
-        for (int64_t b = (block + 7) / 8 * 8; b < end; b += 8) cost.push_back(steps(w, n, i) + kStart + (n > 1 ? kPart : 0));
+        for (int64_t b = (block + 7) / 8 * 8; b < end; b += 8) {
+          cost.push_back(steps(w, n, i) + kStart + (n > 1 ? kPart : 0));
+          sum += cost.back();
+        }
         block = end;
       }
     }
+    const int64_t merge = k.parts > 0 ? kMerge + k.parts * inner / kPartsPerStep : 0;
+    total = sum;
+    if (sum / workers + merge >= limit) return limit;
     std::sort(cost.begin(), cost.end(), later);
     free_at.assign(workers, 0);  // a heap, earliest first
     int64_t last = 0;
@@ -184,15 +192,16 @@ static KeySplit choose_cut(const std::vector<Walk>& walks, int longest, int shor
       last = std::max(last, free_at.back());
       std::push_heap(free_at.begin(), free_at.end(), later);
     }
-    return last + (k.parts > 0 ? kMerge + k.parts * inner / kPartsPerStep : 0);
+    return last + merge;
   };
   KeySplit best;
-  int64_t best_time = estimate(best);
+  int64_t best_time = estimate(best, INT64_MAX);
   best_time -= best_time / 20;
+  if (total / workers >= best_time) return best;  // as even as it can get: pieces only add to the work
   for (int n = 2; n <= 16 && longest / n >= shortest; ++n) {
     KeySplit k;
     k.target = (longest + n - 1) / n;
-    const int64_t time = estimate(k);
+    const int64_t time = estimate(k, best_time);
     if (k.pieces * inner > 2 * kMaxCutBlocks) break;
     if (k.parts > 0 && k.parts <= max_parts && time < best_time) {
       best = k;
