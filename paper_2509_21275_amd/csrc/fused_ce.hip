@@ -202,9 +202,10 @@ __global__ __launch_bounds__(kThreads) void fused_ce_long_kernel(__bf16* __restr
         count_group(g);
       }
     }
-    // merge: the wave's 64 pairs, then the workgroup's 8
+    // merge: the wave's 64 pairs, then the workgroup's 8.  A share whose maximum is -inf has the sum 0, or NaN if a NaN was
+    // among its logits (the maximum passes over it), which the row's loss has to show: it is taken as it is.
     const float wm = wave_max(mx);
-    sum *= mx == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mx - wm);
+    sum = mx == -INFINITY ? sum : sum * __builtin_amdgcn_exp2f(mx - wm);
     sum = wave_sum(sum);
     if (lane == 0) {
       red_m[set][wave] = wm;
@@ -217,7 +218,7 @@ __global__ __launch_bounds__(kThreads) void fused_ce_long_kernel(__bf16* __restr
     sum = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w)
-      sum += red_m[set][w] == -INFINITY ? 0.f : red_s[set][w] * __builtin_amdgcn_exp2f(red_m[set][w] - bm);
+      sum += red_m[set][w] == -INFINITY ? red_s[set][w] : red_s[set][w] * __builtin_amdgcn_exp2f(red_m[set][w] - bm);
     const float lse2 = bm + __builtin_amdgcn_logf(sum);  // log2 of the sum of exponentials
     if (tid == 0) loss[row] = ignored ? 0.f : lse2 * kLn2 - zy;
     const float scale = ignored ? 0.f : grad_scale;

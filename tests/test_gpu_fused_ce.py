@@ -79,3 +79,27 @@ def test_edges_of_the_register_and_lds_variants(vocab):
     got = dev.cpu().double().numpy()
     assert np.abs(loss.cpu().double().numpy() - want_loss).max() <= 2e-4 * max(1.0, np.abs(want_loss).max())
     assert np.all(np.abs(got - want_grad) <= 2.0 ** -8 * np.abs(want_grad) + 2.0 ** -8 * scale * 1e-3)
+
+
+@pytest.mark.parametrize("vocab", [4096, 131072, 131080, 163840, 163848, 262136])
+def test_a_nan_logit_is_not_lost(vocab):
+    """A NaN makes its row's loss and gradient NaN, also where every other logit of the threads around it is -inf (their maximum
+    is then -inf, and the sum that holds the NaN must not be taken for empty); the other rows are as without it."""
+    from paper_2509_21275_amd.fused_ce import fused_ce_inplace
+    g = torch.Generator(device="cpu").manual_seed(vocab + 1)
+    rows = 5
+    buf = (torch.randn((rows, vocab), generator=g) * 2.0).to(torch.bfloat16)
+    targets = torch.full((rows,), 8, dtype=torch.int32)
+    buf[1, 17] = float("nan")                       # among finite logits
+    buf[2, 16:] = float("-inf")                     # the only finite logits are the first two chunks' ...
+    buf[2, vocab - 3] = float("nan")                # ... the NaN is in the last chunk
+    buf[3, 16:] = float("-inf")
+    keep = [0, 3, 4]
+    want_loss, want_grad = orc.cross_entropy(buf[keep].double().numpy(), targets[keep].numpy(), 0.5)
+    dev, loss = buf.cuda(), torch.zeros((rows,), device="cuda")
+    fused_ce_inplace(dev, targets.cuda(), loss, 0.5)
+    torch.cuda.synchronize()
+    got_loss, got = loss.cpu().double().numpy(), dev.cpu().double().numpy()
+    assert np.isnan(got_loss[[1, 2]]).all() and np.isnan(got[1]).all() and np.isnan(got[2]).all()
+    assert np.abs(got_loss[keep] - want_loss).max() <= 2e-4 * max(1.0, np.abs(want_loss).max())
+    assert np.all(np.abs(got[keep] - want_grad) <= 2.0 ** -8 * np.abs(want_grad) + 2.0 ** -8 * 0.5 * 1e-3)
