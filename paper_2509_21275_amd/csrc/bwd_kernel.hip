@@ -2714,7 +2714,7 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, bool may_c
   const size_t dq_tile_bytes = pipe ? (size_t)fused_num_bufs(d, dkv_keys(128)) * d->num_q_heads * P.qt32_tiles * 4096 * sizeof(float) : 0;
   P.fused = d->head_dim == 128 && bwd_mode() == 2;
   size_t n_dq = 0, n_dkv = 0;
-  if (pipe && may_cut && !P.fused) {
+  if (pipe && may_cut) {  // (in either mode: the pieces are part of the layout, whose size must not depend on the mode)
     const int inner = d->num_kv_heads * (group / heads_per_wg(group, P.dq_waves));
     P.split = choose_key_split(d, dq_rows, inner, kCus, (int64_t)(dq_tile_bytes / ((size_t)inner * kPartRowFloats * sizeof(float))));
     P.dkv_split = choose_tile_split(d, dkv_keys(d->head_dim), kCus,
@@ -2734,7 +2734,7 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, bool may_c
     }
     P.qjobs = tile_jobs(d, false, 64, nullptr);
   }
-  // the layout does not depend on which backward runs: item counts follow from the segment table
+  // the layout does not depend on which backward runs: item and piece counts follow from the segment table
   for (int t = 0; t < d->num_segments; ++t) {
     n_dq += (d->segments[t].q_len + dq_rows - 1) / dq_rows;
     n_dkv += (d->segments[t].kv_len + dkv_keys(d->head_dim) - 1) / dkv_keys(d->head_dim);

@@ -75,6 +75,24 @@ def test_head_dimensions(ca):
     assert "64, 96, 128 or 256" in ca.chunk_attn_strerror(ca.UNSUPPORTED)
 
 
+@pytest.mark.parametrize("segs,Hq,Hkv,dim", [
+    ([(0, 1024, 0, 32768)], 32, 8, 128), ([(0, 1024, 0, 32768)], 32, 8, 96),   # dQ walks are cut
+    ([(0, 4999, 0, 4999)], 32, 8, 128), ([(0, 1100, 5, 1400), (1100, 77, 1410, 77)], 6, 2, 96),  # dK/dV walks are cut
+    ([(0, 300, 0, 300)], 32, 8, 128), ([(0, 300, 0, 700)], 8, 2, 64),
+])
+def test_workspace_size_does_not_depend_on_the_backward_mode(ca, segs, Hq, Hkv, dim):
+    """The mode may change between the size query and the call (include/chunk_attn.h)."""
+    d, lib = desc(ca, segs, Hq=Hq, Hkv=Hkv, d=dim), ctypes.CDLL(ca.LIB_PATH)
+    try:
+        sizes = []
+        for mode in (0, 1, 2):
+            assert lib.chunk_attn_test_set_bwd_mode(mode) == ca.OK
+            sizes.append(ca.chunk_attn_workspace_bytes(d))
+    finally:
+        lib.chunk_attn_test_set_bwd_mode(0)
+    assert sizes[0] == sizes[1] == sizes[2]
+
+
 @pytest.mark.parametrize("segs,kw,code", [
     ([(0, 0, 0, 4)], {"tq": 4}, "BAD_SEGMENT"),                        # empty query range
     ([(0, 8, 0, 4)], {}, "BAD_SEGMENT"),                          # fewer keys than queries
