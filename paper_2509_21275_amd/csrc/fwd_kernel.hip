@@ -14,7 +14,9 @@
 //                    two waves per SIMD or more, tiles of 64 keys (K row-major, V as rows that are read transposed or,
 //                    for head_dim 256, as the pre-transposed image of transpose_kernel.hip, double-buffered).  Used
 //                    for head_dim 256, for 64 unless its walks are long (pipe_pays), and as the second pass below.
-//                    head_dim 64 without the image and its launch: four sequences of 1024, 32/8 heads, 51 -> 42 us.
+//                    head_dim 64 without the image and its launch: four sequences of 1024, 32/8 heads, 51 -> 42 us; 1024
+//                    queries on 32768 keys 447 -> 447 us, 2048 on 18432, 8/2 heads, 253 -> 256 (with V in chunk-major
+//                    tiles, whose copies touch four times the cache lines: 460 - 480 and 264).
 //   fwd_pipe_kernel  head_dim 96 and 128, and 64 with two workgroups per CU: one wave per SIMD with 64 query rows, software pipelined over stages of 32
 //                    keys, reference maximum fixed by the first stage; rows whose scores outgrow it are
 //                    flagged and recomputed by fwd_kernel, launched right after.  Where a chunk has too few items for
@@ -82,11 +84,12 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
   constexpr int KT = BN * D;   // elements per K tile and per V^T image
   constexpr int WR = 32 * QB;  // query rows per wave
   if (p.redo != nullptr && !p.cut && p.redo[blockIdx.x] == 0) return;  // second pass with nothing to do
-  constexpr bool IMG = D > 128;  // V arrives as a transposed image; else as rows, two chunk-major tiles of 32
+  constexpr bool IMG = D > 128;   // V arrives as a transposed image; else as rows:
+  constexpr bool ROWS = D == 64;  // a row-major tile like K's (row_elem) for head_dim 64, else two chunk-major tiles of 32
 
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   __bf16* Ks = reinterpret_cast<__bf16*>(smem);  // [2][BN][D]  swizzled rows
-  __bf16* Vs = Ks + 2 * KT;                      // [2][D][BN]  transposed image
+  __bf16* Vs = Ks + 2 * KT;                      // [2][D][BN]  transposed image, or [2][BN][D]
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, kept in a scalar register
@@ -132,12 +135,16 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
   for (int i = 0; i < NK; ++i) {
     const int x = (i * WAVES + wave) * 64 + lane;
     k_row[i] = x / KC;
-    k_src[i] = (unsigned)(k_row[i] * (int)kv_stride + unswz<KC>(k_row[i], x % KC) * 8);
+    int c = x % KC;
+    if constexpr (ROWS) c ^= row_swz(k_row[i]);
+    else c = unswz<KC>(k_row[i], c);
+    k_src[i] = (unsigned)(k_row[i] * (int)kv_stride + c * 8);
   }
   auto dma_tile = [&](int t, int buf) {
     const __bf16* ksrc = Kg + (int64_t)(BN * t) * kv_stride;  // wave-uniform
     const int last_row = n_wg - 1 - BN * t;                   // rows past it are clamped (last tile only)
     __bf16* kdst = Ks + buf * KT;
+    __bf16* vdst = Vs + buf * KT;
     if (last_row >= BN - 1) {
 #pragma unroll
       for (int i = 0; i < NK; ++i)
@@ -149,12 +156,19 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
         if (has_piece(i)) dma16(ksrc + off, kdst + (i * WAVES + wave) * 512);
       }
     }
-    __bf16* vdst = Vs + buf * KT;
     if constexpr (IMG) {
       const __bf16* vsrc = Vimg + (int64_t)t * KT;            // wave-uniform
 #pragma unroll
       for (int i = 0; i < NV; ++i)
         dma16(vsrc + (unsigned)(((i * WAVES + wave) * 64 + lane) * 8), vdst + (i * WAVES + wave) * 512);
+    } else if constexpr (ROWS) {
+      const __bf16* vsrc = Vimg + (int64_t)(BN * t) * kv_stride;
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        unsigned off = k_src[i];
+        if (last_row < BN - 1) off -= (unsigned)((k_row[i] - min(k_row[i], last_row)) * (int)kv_stride);
+        dma16(vsrc + off, vdst + (i * WAVES + wave) * 512);
+      }
     } else {
       const __bf16* vsrc = Vimg + (int64_t)(BN * t) * kv_stride;
 #pragma unroll
@@ -197,14 +211,22 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
   // each tile is a constant offset away; the buffer index is a compile-time constant of the unrolled loop.
   int k_off[DK], v_off[4];
 #pragma unroll
-  for (int ks = 0; ks < DK; ++ks) k_off[ks] = tile_elem<KC>(l32, 2 * ks + hh);
+  for (int ks = 0; ks < DK; ++ks) {
+    if constexpr (ROWS) k_off[ks] = row_elem(l32, 2 * ks + hh);
+    else k_off[ks] = tile_elem<KC>(l32, 2 * ks + hh);
+  }
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) v_off[ks] = tile_elem<8>(l32, 2 * ks + hh);
   unsigned vt_lo = 0, vt_hi = 0;  // byte addresses of the transposed reads (as in the pipelined kernel) in buffer 0
   if constexpr (!IMG) {
     const int j = lane & 15, cl = 2 * ((lane >> 4) & 1) + ((j & 3) >> 1), r0 = 4 * hh + (j >> 2);
-    vt_lo = lds_addr((lds_bf16*)Vs + cm_elem(r0, cl) + 4 * (j & 1));
-    vt_hi = lds_addr((lds_bf16*)Vs + cm_elem(r0 + 8, cl) + 4 * (j & 1));
+    if constexpr (ROWS) {
+      vt_lo = lds_addr((lds_bf16*)Vs + row_elem(r0, cl) + 4 * (j & 1));
+      vt_hi = lds_addr((lds_bf16*)Vs + row_elem(r0 + 8, cl) + 4 * (j & 1));
+    } else {
+      vt_lo = lds_addr((lds_bf16*)Vs + cm_elem(r0, cl) + 4 * (j & 1));
+      vt_hi = lds_addr((lds_bf16*)Vs + cm_elem(r0 + 8, cl) + 4 * (j & 1));
+    }
   }
 
   const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -239,9 +261,14 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
       auto read_vt = [&](auto ks_c) __attribute__((always_inline)) {
         static_for<0, DB>([&](auto db_c) __attribute__((always_inline)) {
           constexpr int ks = decltype(ks_c)::value, db = decltype(db_c)::value;
-          constexpr int off = ((ks >> 1) * (32 * D) + (ks & 1) * (16 * 8) + db * (4 * 32 * 8)) * 2;
-          v_lo[ks][db] = lds_asm_read_tr<off>(vt_lo + buf * (KT * 2));
-          v_hi[ks][db] = lds_asm_read_tr<off>(vt_hi + buf * (KT * 2));
+          if constexpr (ROWS) {  // (chunks 4 .. 7 of a row: the other half of its 128 bytes)
+            v_lo[ks][db] = lds_asm_read_tr<ks * (16 * D) * 2>((vt_lo ^ (db * 64)) + buf * (KT * 2));
+            v_hi[ks][db] = lds_asm_read_tr<ks * (16 * D) * 2>((vt_hi ^ (db * 64)) + buf * (KT * 2));
+          } else {
+            constexpr int off = ((ks >> 1) * (32 * D) + (ks & 1) * (16 * 8) + db * (4 * 32 * 8)) * 2;
+            v_lo[ks][db] = lds_asm_read_tr<off>(vt_lo + buf * (KT * 2));
+            v_hi[ks][db] = lds_asm_read_tr<off>(vt_hi + buf * (KT * 2));
+          }
         });
       };
       if constexpr (D == 64) {

@@ -161,6 +161,14 @@ __host__ __device__ __forceinline__ int cperm(int p) {
 // per-lane base plus constants.  cm_elem: element offset of (row r, chunk c).
 __device__ __forceinline__ int cm_elem(int r, int c) { return (c * 32 + (r ^ ((c & 3) << 2))) * 8; }
 
+// Row-major tile of 128-byte rows (head_dim 64) that serves both kinds of read as well: a copy instruction then fetches eight
+// whole rows, where a chunk-major tile's fetches 32 bytes of each of 32 rows, four times the cache lines; a kernel with few
+// copies in flight waits for that.  Chunk c of row r sits at position c ^ row_swz(r), bits 1 .. 3 of the row index reversed:
+// 16 consecutive rows of one chunk, and four consecutive rows of four chunks, fall on all banks once.  Rows r + 16 share it,
+// and chunk c ^ 4 is 64 bytes away (in either direction).
+__device__ __forceinline__ int row_swz(int r) { return ((r >> 3) & 1) | ((r >> 1) & 2) | ((r & 2) << 1); }
+__device__ __forceinline__ int row_elem(int r, int c) { return (r * 8 + (c ^ row_swz(r))) * 8; }
+
 // LDS accesses as opaque instructions, for the software-pipelined kernels.  The compiler makes a wave wait for ALL of its
 // outstanding global->LDS copies before an LDS read it cannot tell apart from their destinations (the
 // transpose read in particular), which would serialise the copies of later stages with the reads of the

@@ -162,6 +162,30 @@ def test_pipelined_kernels_of_head_dim_64(oracle_mod, name, segs, Hq, Hkv):
         assert rel_err(acc[3][:, h:h + 1].cpu()[cov], dK[cov] + 3.0) <= TOL_GRAD and rel_err(acc[4][:, h:h + 1].cpu()[cov], dV[cov] + 3.0) <= TOL_GRAD
 
 
+@pytest.mark.parametrize("d", [64, 256])
+@pytest.mark.parametrize("Hq,Hkv", [(2, 2), (4, 1), (6, 2)])
+def test_tile_edges_of_the_kernels_for_short_walks(oracle_mod, d, Hq, Hkv):
+    """Head dimensions 64 and 256 below the pipelined kernels' sizes: key counts on both sides of the 32- and 64-row tiles the
+    forward and dQ kernels read rows and transposed operands from, contexts that are and are not whole tiles, single rows.
+    (LSE: these forwards sum the probabilities as rounded to bf16, 2^-9 of the sum at most.)"""
+    lens = [(1, 1), (31, 31), (32, 32), (33, 33), (63, 64), (64, 65), (65, 65), (1, 96), (2, 128), (40, 129), (95, 191), (129, 193)]
+    segs, tq, tkv = [], 0, 0
+    for n, keys in lens:
+        segs.append((tq, n, tkv, keys))
+        tq, tkv = tq + n, tkv + keys
+    case = synth.ChunkCase(f"tile_edges_d{d}", [synth.Seg(*s) for s in segs], tq, tkv, Hq, Hkv, d, 610 + Hq)
+    q, k, v, do = make_inputs(case)
+    o, lse, dq, dk, dv = run_gpu(case, q, k, v, do)
+    orc = oracle_mod.Oracle(case.segs, q.cpu(), k.cpu(), v.cpu(), do.cpu(), case.scale)
+    O, LSE = orc.forward(); dQ, dK, dV = orc.backward()
+    assert float(np.abs(lse.double().cpu().numpy() - LSE).max()) <= 2.0 ** -9 + 1e-4
+    for q0, n, k0, keys in segs:  # per sequence: an error in a short one does not drown in the others
+        assert rel_err(o[q0:q0 + n], O[q0:q0 + n]) <= TOL_O
+        if keys > 1:  # (one query on one key: its dQ and dK are zero up to rounding)
+            assert rel_err(dq[q0:q0 + n], dQ[q0:q0 + n]) <= TOL_GRAD and rel_err(dk[k0:k0 + keys], dK[k0:k0 + keys]) <= TOL_GRAD
+        assert rel_err(dv[k0:k0 + keys], dV[k0:k0 + keys]) <= TOL_GRAD
+
+
 def test_second_pass_of_head_dim_64(oracle_mod):
     """The pipelined forward of head_dim 64 with every item sent to its second pass (probabilities rounded to bf16 are summed
     there: 2^-9 of the sum at most, as much in its logarithm)."""
