@@ -96,6 +96,11 @@ struct DqParams {
 // (head_dim 64 unless its walks are long, and 256.)  K^T is read transposed out of the K tile; with an image of K made by a
 // launch before, as this kernel had it, the backward of four sequences of 1024, 32/8 heads, took 144 us instead of 141, of
 // 64 of 256 220 instead of 211, and at head_dim 256 the packed 64K chunk 41.2 ms (forward included) instead of 40.2.
+// With one wave per SIMD a tile's chain of products, exponentials and products is what a step takes, and the transposed
+// reads (twice as many instructions as an image takes) lengthen it unless they are issued behind the last products of S^T and
+// dP^T and the second half of dS is made behind the first half's products.  Backward with an image / with the reads in one
+// burst behind the products / as they are now: head_dim 64, 128 queries on 16384 keys, 8/8 heads, 314 / 334 / 293 us, 512
+// queries, 32/8 heads, 476 / 484 / 450; head_dim 256, 64 queries on 8192 keys, 8/8 heads, 413 / 427 / 388.
 template <int D, int WAVES>
 __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void bwd_dq_kernel(DqParams p) {
   constexpr int NTH = WAVES * 64;  // threads
@@ -222,28 +227,38 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void bwd_dq_ke
       f32x16 s, dp;
       bf16x8 ak[2][2], av[2][2];  // [parity of the k-step pair][step in the pair]
       ak[0][0] = ldk(0); av[0][0] = ldv(0); ak[0][1] = ldk(1); av[0][1] = ldv(1);
+      // operands of dQ^T += K^T dS^T (k-step m / DB, block m % DB), fetched between the last products of S^T and dP^T: a
+      // quarter behind each, where the wave has nothing else to issue
+      s16x4 a_lo[2 * DB], a_hi[2 * DB];
+      auto read_kt = [&](auto quarter_c) __attribute__((always_inline)) {
+        constexpr int quarter = decltype(quarter_c)::value;
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<quarter * (DB / 2), (quarter + 1) * (DB / 2)>([&](auto m_c) __attribute__((always_inline)) {
+          constexpr int m = decltype(m_c)::value;
+          constexpr int off = (buf * KT + (m / DB) * (16 * 8) + (m % DB) * (4 * 32 * 8)) * 2;
+          a_lo[m] = lds_asm_read_tr<off>(t_lo);
+          a_hi[m] = lds_asm_read_tr<off>(t_hi);
+        });
+        __builtin_amdgcn_sched_barrier(0);
+      };
       __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int g = 0; g < DK / 2; ++g) {
-        const int cur = g & 1, nxt = cur ^ 1;
-        if (g + 1 < DK / 2) {
+      static_for<0, DK / 2>([&](auto g_c) __attribute__((always_inline)) {
+        constexpr int g = decltype(g_c)::value, cur = g & 1, nxt = cur ^ 1;
+        constexpr bool last = g == DK / 2 - 1;
+        if constexpr (!last) {
           ak[nxt][0] = ldk(2 * g + 2); av[nxt][0] = ldv(2 * g + 2);
           ak[nxt][1] = ldk(2 * g + 3); av[nxt][1] = ldv(2 * g + 3);
         }
         s = mfma32(ak[cur][0], qf[2 * g], g == 0 ? zero16 : s);
+        if constexpr (last) read_kt(std::integral_constant<int, 0>{});
         dp = mfma32(av[cur][0], gf[2 * g], g == 0 ? zero16 : dp);
-        if (prefetch && g < NK) dma_piece(t + NS - 1, (buf + NS - 1) % NS, g);
+        if constexpr (last) read_kt(std::integral_constant<int, 1>{});
+        if (g < NK && prefetch) dma_piece(t + NS - 1, (buf + NS - 1) % NS, g);
         s = mfma32(ak[cur][1], qf[2 * g + 1], s);
+        if constexpr (last) read_kt(std::integral_constant<int, 2>{});
         dp = mfma32(av[cur][1], gf[2 * g + 1], dp);
+        if constexpr (last) read_kt(std::integral_constant<int, 3>{});
         __builtin_amdgcn_sched_barrier(0);
-      }
-      // operands of dQ^T += K^T dS^T, fetched while the exponentials are computed
-      s16x4 a_lo[2 * DB], a_hi[2 * DB];  // k-step m / DB, block m % DB
-      static_for<0, 2 * DB>([&](auto m_c) __attribute__((always_inline)) {
-        constexpr int m = decltype(m_c)::value;
-        constexpr int off = (buf * KT + (m / DB) * (16 * 8) + (m % DB) * (4 * 32 * 8)) * 2;
-        a_lo[m] = lds_asm_read_tr<off>(t_lo);
-        a_hi[m] = lds_asm_read_tr<off>(t_hi);
       });
       // ---- P = exp2(S c - LSE), dS = P (dP - D); masked keys give P = 0 ----
       float pe[16];
@@ -257,19 +272,22 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void bwd_dq_ke
           if (j >= lim) pe[i] = 0.f;
         }
       }
-      float ds[16];
-#pragma unroll
-      for (int i = 0; i < 16; ++i) ds[i] = pe[i] * (dp[i] + dsum);
-      const bf16x8 f0 = pack8(ds[0], ds[1], ds[2], ds[3], ds[4], ds[5], ds[6], ds[7]);
-      const bf16x8 f1 = pack8(ds[8], ds[9], ds[10], ds[11], ds[12], ds[13], ds[14], ds[15]);
-      __builtin_amdgcn_sched_barrier(0);
-      // ---- dQ^T += K^T dS^T : [D] x [32 queries], contraction over the 32 keys ----
+      // ---- dQ^T += K^T dS^T : [D] x [32 queries], contraction over the 32 keys, the second 16 keys' dS while the first 16's
+      // products run ----
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-      for (int m = 0; m < 2 * DB; ++m) {
-        asm volatile("" : "+v"(a_lo[m]), "+v"(a_hi[m]));  // (after the wait, in this order)
-        const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(a_lo[m], a_hi[m], 0, 1, 2, 3, 4, 5, 6, 7));
-        dq[m % DB] = mfma32(a, m < DB ? f0 : f1, dq[m % DB]);
+      for (int h = 0; h < 2; ++h) {
+        float ds[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) ds[i] = pe[8 * h + i] * (dp[8 * h + i] + dsum);
+        const bf16x8 f = pack8(ds[0], ds[1], ds[2], ds[3], ds[4], ds[5], ds[6], ds[7]);
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+          const int m = h * DB + db;
+          asm volatile("" : "+v"(a_lo[m]), "+v"(a_hi[m]));  // (after the wait, in this order)
+          const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(a_lo[m], a_hi[m], 0, 1, 2, 3, 4, 5, 6, 7));
+          dq[db] = mfma32(a, f, dq[db]);
+        }
       }
     }
     // tile t + 1 must have landed; tiles t + 2 .. may still be in flight
