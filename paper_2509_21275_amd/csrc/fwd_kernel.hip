@@ -15,8 +15,12 @@
 //                    for head_dim 256, as the pre-transposed image of transpose_kernel.hip, double-buffered).  Used
 //                    for head_dim 256, for 64 unless its walks are long (pipe_pays), and as the second pass below.
 //                    head_dim 64 without the image and its launch: four sequences of 1024, 32/8 heads, 51 -> 42 us; 1024
-//                    queries on 32768 keys 447 -> 447 us, 2048 on 18432, 8/2 heads, 253 -> 256 (with V in chunk-major
-//                    tiles, whose copies touch four times the cache lines: 460 - 480 and 264).
+//                    queries on 32768 keys 447 -> 390 us, 2048 on 18432, 8/2 heads, 253 -> 219.  (With one workgroup per
+//                    compute unit a tile's chain of copies, reads and products is what a step takes.  V in chunk-major
+//                    tiles, whose copies touch four times the cache lines: 460 - 490 and 264; rows, but all transposed
+//                    reads in one burst behind the products and the rows of a full tile clamped like the last one's:
+//                    447 - 469 and 256.  168 registers, so that three workgroups share a CU: with two more, 64 sequences
+//                    of 256 took 83 us instead of 74.)
 //   fwd_pipe_kernel  head_dim 96 and 128, and 64 with two workgroups per CU: one wave per SIMD with 64 query rows, software pipelined over stages of 32
 //                    keys, reference maximum fixed by the first stage; rows whose scores outgrow it are
 //                    flagged and recomputed by fwd_kernel, launched right after.  Where a chunk has too few items for
@@ -74,7 +78,7 @@ __device__ __forceinline__ void fwd_merge_parts(const FwdParams& p, const FwdIte
 }
 
 template <int D, int WAVES>
-__global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kernel(FwdParams p) {
+__global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : D == 64 && WAVES == 4 ? 3 : 8 / WAVES) void fwd_kernel(FwdParams p) {
   constexpr int QB = 1;        // 32-row query blocks per wave
   constexpr int NT = WAVES * 64;  // threads
   constexpr int BN = 64;       // key rows per LDS tile
@@ -127,7 +131,7 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
   // swizzle puts there.  The V^T image is copied linearly.
   // (head_dim 96: 12 copies of 64 chunks for 8 waves, so the second round is half a round)
   constexpr int PIECES = BN * KC / 64, NK = (PIECES + WAVES - 1) / WAVES, NV = NK;
-  static_assert(KT == BN * KC * 8, "a V tile has as many chunks as a K tile");
+  static_assert(KT == BN * KC * 8 && (!ROWS || PIECES % WAVES == 0), "a V tile has as many chunks as a K tile");
   auto has_piece = [&](int i) { return PIECES % WAVES == 0 || i * WAVES + wave < PIECES; };
   unsigned k_src[NK];
   int k_row[NK];
@@ -145,15 +149,23 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
     const int last_row = n_wg - 1 - BN * t;                   // rows past it are clamped (last tile only)
     __bf16* kdst = Ks + buf * KT;
     __bf16* vdst = Vs + buf * KT;
+    auto copy = [&](int i, unsigned off) __attribute__((always_inline)) {
+      if (has_piece(i)) dma16(ksrc + off, kdst + (i * WAVES + wave) * 512);
+      if constexpr (ROWS) dma16(Vimg + (int64_t)(BN * t) * kv_stride + off, vdst + (i * WAVES + wave) * 512);
+    };
     if (last_row >= BN - 1) {
 #pragma unroll
-      for (int i = 0; i < NK; ++i)
-        if (has_piece(i)) dma16(ksrc + k_src[i], kdst + (i * WAVES + wave) * 512);
+      for (int i = 0; i < NK; ++i) copy(i, k_src[i]);
     } else {
 #pragma unroll
       for (int i = 0; i < NK; ++i) {
-        const unsigned off = k_src[i] - (unsigned)((k_row[i] - min(k_row[i], last_row)) * (int)kv_stride);
-        if (has_piece(i)) dma16(ksrc + off, kdst + (i * WAVES + wave) * 512);
+        int row = k_row[i];
+        if constexpr (ROWS) {  // (computed here, and not kept for the length of the loop)
+          int ln = threadIdx.x & 63;
+          asm volatile("" : "+v"(ln));
+          row = ((i * WAVES + wave) * 64 + ln) / KC;
+        }
+        copy(i, k_src[i] - (unsigned)((row - min(row, last_row)) * (int)kv_stride));
       }
     }
     if constexpr (IMG) {
@@ -161,15 +173,7 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
 #pragma unroll
       for (int i = 0; i < NV; ++i)
         dma16(vsrc + (unsigned)(((i * WAVES + wave) * 64 + lane) * 8), vdst + (i * WAVES + wave) * 512);
-    } else if constexpr (ROWS) {
-      const __bf16* vsrc = Vimg + (int64_t)(BN * t) * kv_stride;
-#pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        unsigned off = k_src[i];
-        if (last_row < BN - 1) off -= (unsigned)((k_row[i] - min(k_row[i], last_row)) * (int)kv_stride);
-        dma16(vsrc + off, vdst + (i * WAVES + wave) * 512);
-      }
-    } else {
+    } else if constexpr (!ROWS) {
       const __bf16* vsrc = Vimg + (int64_t)(BN * t) * kv_stride;
 #pragma unroll
       for (int i = 0; i < NV; ++i) {
@@ -222,7 +226,6 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
     const int j = lane & 15, cl = 2 * ((lane >> 4) & 1) + ((j & 3) >> 1), r0 = 4 * hh + (j >> 2);
     if constexpr (ROWS) {
       vt_lo = lds_addr((lds_bf16*)Vs + row_elem(r0, cl) + 4 * (j & 1));
-      vt_hi = lds_addr((lds_bf16*)Vs + row_elem(r0 + 8, cl) + 4 * (j & 1));
     } else {
       vt_lo = lds_addr((lds_bf16*)Vs + cm_elem(r0, cl) + 4 * (j & 1));
       vt_hi = lds_addr((lds_bf16*)Vs + cm_elem(r0 + 8, cl) + 4 * (j & 1));
@@ -244,26 +247,13 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
     if (t < nt_w) {
       const __bf16* Kt = Ks + (TOGGLE ? 0 : buf * KT);
       const __bf16* Vt = Vs;
-      // ---- S^T = K Q^T : [64 keys] x [32 QB queries]; every K fragment feeds QB products ----
-      f32x16 s0[QB], s1[QB];
-#pragma unroll
-      for (int ks = 0; ks < DK; ++ks) {
-        const bf16x8 a0 = *reinterpret_cast<const bf16x8*>(Kt + k_off[ks]);
-        const bf16x8 a1 = *reinterpret_cast<const bf16x8*>(Kt + k_off[ks] + 32 * D);
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-          s0[qb] = mfma32(a0, qf[qb][ks], ks == 0 ? zero16 : s0[qb]);
-          s1[qb] = mfma32(a1, qf[qb][ks], ks == 0 ? zero16 : s1[qb]);
-        }
-      }
-      // head_dim 64: the V^T fragments are read here, so that they arrive while the exponentials are computed
       s16x4 v_lo[4][DB], v_hi[4][DB];
       auto read_vt = [&](auto ks_c) __attribute__((always_inline)) {
         static_for<0, DB>([&](auto db_c) __attribute__((always_inline)) {
           constexpr int ks = decltype(ks_c)::value, db = decltype(db_c)::value;
           if constexpr (ROWS) {  // (chunks 4 .. 7 of a row: the other half of its 128 bytes)
             v_lo[ks][db] = lds_asm_read_tr<ks * (16 * D) * 2>((vt_lo ^ (db * 64)) + buf * (KT * 2));
-            v_hi[ks][db] = lds_asm_read_tr<ks * (16 * D) * 2>((vt_hi ^ (db * 64)) + buf * (KT * 2));
+            v_hi[ks][db] = lds_asm_read_tr<(ks * 16 + 8) * D * 2>((vt_lo ^ (db * 64 + 16)) + buf * (KT * 2));  // eight rows on
           } else {
             constexpr int off = ((ks >> 1) * (32 * D) + (ks & 1) * (16 * 8) + db * (4 * 32 * 8)) * 2;
             v_lo[ks][db] = lds_asm_read_tr<off>(vt_lo + buf * (KT * 2));
@@ -271,10 +261,48 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void fwd_kerne
           }
         });
       };
-      if constexpr (D == 64) {
+      // ---- S^T = K Q^T : [64 keys] x [32 QB queries]; every K fragment feeds QB products ----
+      f32x16 s0[QB], s1[QB];
+      auto ldk = [&](int ks, int half) {  // (ROWS: chunks 2 ks + hh are an XOR apart, so that one address is kept)
+        return *reinterpret_cast<const bf16x8*>(Kt + (ROWS ? k_off[0] ^ (16 * ks) : k_off[ks]) + half * (32 * D));
+      };
+      auto mma_s = [&](int ks, bf16x8 a, f32x16 (&d)[QB]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) d[qb] = mfma32(a, qf[qb][ks], ks == 0 ? zero16 : d[qb]);
+      };
+      if constexpr (ROWS) {
+        // the K fragments first, the second half while the first one's products run; a quarter of the V^T fragments behind each
+        // of the last four products, where the wave has nothing else to issue: they arrive while the exponentials are computed
+        bf16x8 a[4][2];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) a[x >> 1][x & 1] = ldk(x >> 1, x & 1);
         __builtin_amdgcn_sched_barrier(0);
-        static_for<0, 4>(read_vt);
+#pragma unroll
+        for (int x = 4; x < 8; ++x) a[x >> 1][x & 1] = ldk(x >> 1, x & 1);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+          mma_s(ks, a[ks][0], s0);
+          mma_s(ks, a[ks][1], s1);
+        }
         __builtin_amdgcn_sched_barrier(0);
+        static_for<2, 4>([&](auto ks_c) __attribute__((always_inline)) {
+          constexpr int ks = decltype(ks_c)::value;
+          mma_s(ks, a[ks][0], s0);
+          __builtin_amdgcn_sched_barrier(0);
+          read_vt(std::integral_constant<int, 2 * ks - 4>{});
+          __builtin_amdgcn_sched_barrier(0);
+          mma_s(ks, a[ks][1], s1);
+          __builtin_amdgcn_sched_barrier(0);
+          read_vt(std::integral_constant<int, 2 * ks - 3>{});
+          __builtin_amdgcn_sched_barrier(0);
+        });
+      } else {
+#pragma unroll
+        for (int ks = 0; ks < DK; ++ks) {
+          const bf16x8 a0 = ldk(ks, 0), a1 = ldk(ks, 1);
+          mma_s(ks, a0, s0);
+          mma_s(ks, a1, s1);
+        }
       }
       bf16x8 pf[QB][4];
 #pragma unroll
