@@ -234,6 +234,19 @@ int chunk_attn_test_set_bwd_mode(int mode);
  */
 int chunk_attn_test_bwd_status_offset(const chunk_attn_desc* desc, size_t* offset);
 
+/*
+ * Test hook: which kernels chunk_attn_fwd and chunk_attn_bwd choose for `desc` (given workspaces of the reported sizes), as
+ * a sum of the bits below.  Decided on the host from the descriptor alone (and, for the last bit, the backward mode).
+ */
+#define CHUNK_ATTN_ROUTE_FWD_PIPELINED 1 /* software-pipelined forward and its second pass */
+#define CHUNK_ATTN_ROUTE_FWD_CUT 2       /* some of its walks over the keys are cut into pieces */
+#define CHUNK_ATTN_ROUTE_DQ_PIPELINED 4
+#define CHUNK_ATTN_ROUTE_DQ_CUT 8
+#define CHUNK_ATTN_ROUTE_DKV_PIPELINED 16
+#define CHUNK_ATTN_ROUTE_DKV_CUT 32      /* some of its walks over the query tiles are cut */
+#define CHUNK_ATTN_ROUTE_ONE_PASS 64     /* one-pass backward instead of the dQ and dK/dV kernels */
+int chunk_attn_test_routes(const chunk_attn_desc* desc, int32_t* routes);
+
 /* Static description of an error code; for CHUNK_ATTN_HIP_ERROR includes the last HIP error text. */
 const char* chunk_attn_strerror(int code);
 

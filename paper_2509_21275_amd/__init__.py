@@ -264,6 +264,19 @@ def chunk_attn_test_set_bwd_mode(mode: int) -> None:
         raise ChunkAttnError(rc)
 
 
+ROUTE_FWD_PIPELINED, ROUTE_FWD_CUT, ROUTE_DQ_PIPELINED, ROUTE_DQ_CUT, ROUTE_DKV_PIPELINED, ROUTE_DKV_CUT, ROUTE_ONE_PASS = \
+    (1 << i for i in range(7))
+
+
+def chunk_attn_test_routes(desc) -> int:
+    """Test hook: the kernels the library chooses for a chunk, as a sum of ROUTE_* bits (host only)."""
+    out = ctypes.c_int32(0)
+    rc = _lib.chunk_attn_test_routes(ctypes.byref(desc), ctypes.byref(out))
+    if rc != 0:
+        raise ChunkAttnError(rc)
+    return out.value
+
+
 def chunk_attn_test_bwd_status(desc, workspace) -> int:
     """Test hook: the status word the one-pass backward left in `workspace` (synchronises the device)."""
     import torch

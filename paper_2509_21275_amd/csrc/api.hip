@@ -452,6 +452,25 @@ int chunk_attn_test_bwd_status_offset(const chunk_attn_desc* desc, size_t* offse
   return CHUNK_ATTN_OK;
 }
 
+int chunk_attn_test_routes(const chunk_attn_desc* desc, int32_t* routes) {
+  const int rc = validate(desc);
+  if (rc != CHUNK_ATTN_OK) return rc;
+  if (!routes) return CHUNK_ATTN_INVALID_ARG;
+  FwdLayout L;
+  layout_fwd(desc, L, false);
+  const chunk_attn_desc w = widened(desc);
+  BwdPlan P;
+  bwd_layout(&w, P, false);
+  *routes = (L.pipe ? CHUNK_ATTN_ROUTE_FWD_PIPELINED : 0) | (L.split.target > 0 ? CHUNK_ATTN_ROUTE_FWD_CUT : 0);
+  if (P.fused) {
+    *routes |= CHUNK_ATTN_ROUTE_ONE_PASS;
+    return CHUNK_ATTN_OK;
+  }
+  *routes |= (P.dq_pipe ? CHUNK_ATTN_ROUTE_DQ_PIPELINED : 0) | (P.split.target > 0 ? CHUNK_ATTN_ROUTE_DQ_CUT : 0) |
+             (P.dkv_pipe ? CHUNK_ATTN_ROUTE_DKV_PIPELINED : 0) | (P.dkv_split.target > 0 ? CHUNK_ATTN_ROUTE_DKV_CUT : 0);
+  return CHUNK_ATTN_OK;
+}
+
 int chunk_attn_test_set_fwd_rescale_limit(float log2_growth) {
   g_fwd_rescale_limit.store(log2_growth);
   return CHUNK_ATTN_OK;

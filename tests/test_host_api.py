@@ -93,6 +93,33 @@ def test_workspace_size_does_not_depend_on_the_backward_mode(ca, segs, Hq, Hkv, 
     assert sizes[0] == sizes[1] == sizes[2]
 
 
+def packed(*lens):
+    segs, at = [], 0
+    for n in lens:
+        segs.append((at, n, at, n))
+        at += n
+    return segs
+
+
+@pytest.mark.parametrize("segs,Hq,Hkv,dim,fwd,dq,dkv", [
+    # "": the plain kernel, "p": pipelined, "pc": pipelined with cut walks
+    ([(0, 8192, 0, 32768)], 32, 8, 128, "p", "p", "p"),           # enough blocks: nothing is cut
+    ([(0, 1024, 0, 32768)], 32, 8, 128, "pc", "pc", "p"),
+    ([(0, 4999, 0, 4999)], 32, 8, 128, "p", "p", "pc"),
+    ([(0, 1024, 0, 32768)], 32, 8, 96, "pc", "pc", "p"),
+    (packed(*[4096] * 4), 32, 8, 64, "p", "p", "p"),
+    (packed(256, 512, 128, 128), 8, 8, 64, "", "", ""),
+    (packed(*[4096] * 4), 32, 8, 256, "", "", "p"),
+    (packed(256, 512, 128, 128), 8, 8, 256, "", "", ""),
+])
+def test_routes(ca, segs, Hq, Hkv, dim, fwd, dq, dkv):
+    """Which kernels a chunk runs; the tests on the GPU assert with the same hook that they reach the path they are named for."""
+    bits = {"": 0, "p": 1, "pc": 3}
+    d = desc(ca, segs, Hq=Hq, Hkv=Hkv, d=dim)
+    assert ca.chunk_attn_test_routes(d) == bits[fwd] | bits[dq] << 2 | bits[dkv] << 4
+    assert (ca.ROUTE_FWD_CUT, ca.ROUTE_DQ_PIPELINED, ca.ROUTE_DKV_PIPELINED, ca.ROUTE_ONE_PASS) == (2, 4, 16, 64)
+
+
 @pytest.mark.parametrize("segs,kw,code", [
     ([(0, 0, 0, 4)], {"tq": 4}, "BAD_SEGMENT"),                        # empty query range
     ([(0, 8, 0, 4)], {}, "BAD_SEGMENT"),                          # fewer keys than queries
