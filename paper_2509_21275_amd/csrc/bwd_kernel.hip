@@ -1276,17 +1276,14 @@ __global__ __launch_bounds__(128, 1) void bwd_dkv_narrow_pipe_kernel(DkvParams p
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hh = lane >> 5;
 
-  // persistent, as bwd_dkv_pipe_kernel
+  // Persistent, as bwd_dkv_pipe_kernel, but no block waits for the groups before it (DkvItem::in_step is for head_dim 96 and
+  // 128).  Half the head dimension leaves too little to gain from the L2: with the waits and the counting of ended blocks the
+  // backward of 1024 queries on 32768 keys, 32/8 heads, took 1139 us instead of 1041, of 64 sequences of 64, 8/8 heads, 57
+  // instead of 38; 16384 queries on 65536 keys 23.7 ms instead of 23.4.
   __shared__ int next_block;
   const int xcd = xcd_of_this_wave();
-  auto start_in_step = [&](int b) __attribute__((always_inline)) {
-    if (b >= 0 && p.items[b / p.num_kv_heads].in_step) wait_for_earlier_groups(p.ended, b, p.side_by_side);
-  };
   int blk = 0;
-  if (wave == 0) {
-    blk = block_claim_finish(p.taken, num_blocks, xcd, block_claim_issue(p.taken, xcd));
-    start_in_step(blk);
-  }
+  if (wave == 0) blk = block_claim_finish(p.taken, num_blocks, xcd, block_claim_issue(p.taken, xcd));
   blk = broadcast_from_wave0(&next_block, blk);
   while (blk >= 0) {
   const int kvh = blk % p.num_kv_heads;
@@ -1624,11 +1621,7 @@ __global__ __launch_bounds__(128, 1) void bwd_dkv_narrow_pipe_kernel(DkvParams p
   }
   // on to the next block; the stores of the epilogue are not waited for here
   int nb = 0;
-  if (wave == 0) {
-    if (lane == 0) __hip_atomic_fetch_add(p.ended + (blk & 7), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    nb = block_claim_finish(p.taken, num_blocks, xcd, pending_claim);
-    start_in_step(nb);
-  }
+  if (wave == 0) nb = block_claim_finish(p.taken, num_blocks, xcd, pending_claim);
   blk = broadcast_from_wave0(&next_block, nb);
   }
 }
@@ -1681,17 +1674,13 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_wide_pipe_kernel(DkvParams p, 
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hh = lane >> 5;
 
-  // persistent, as bwd_dkv_pipe_kernel
+  // Persistent, as bwd_dkv_pipe_kernel, but no block waits for the groups before it (DkvItem::in_step is for head_dim 96 and
+  // 128): that cost 1024 queries on 32768 keys, 32/8 heads, 3796 us of backward instead of 3684, gained nothing on 8192
+  // (25.6 and 25.8 ms) and cost chunks of 64-token sequences a tenth.
   __shared__ int next_block;
   const int xcd = xcd_of_this_wave();
-  auto start_in_step = [&](int b) __attribute__((always_inline)) {
-    if (b >= 0 && p.items[b / p.num_kv_heads].in_step) wait_for_earlier_groups(p.ended, b, p.side_by_side);
-  };
   int blk = 0;
-  if (wave == 0) {
-    blk = block_claim_finish(p.taken, num_blocks, xcd, block_claim_issue(p.taken, xcd));
-    start_in_step(blk);
-  }
+  if (wave == 0) blk = block_claim_finish(p.taken, num_blocks, xcd, block_claim_issue(p.taken, xcd));
   blk = broadcast_from_wave0(&next_block, blk);
   while (blk >= 0) {
   int pending_claim = 0;
@@ -2055,11 +2044,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_wide_pipe_kernel(DkvParams p, 
   }
   // on to the next block; the stores of the epilogue are not waited for here
   int nb = 0;
-  if (wave == 0) {
-    if (lane == 0) __hip_atomic_fetch_add(p.ended + (blk & 7), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    nb = block_claim_finish(p.taken, num_blocks, xcd, pending_claim);
-    start_in_step(nb);
-  }
+  if (wave == 0) nb = block_claim_finish(p.taken, num_blocks, xcd, pending_claim);
   blk = broadcast_from_wave0(&next_block, nb);
   }
 }
