@@ -2527,13 +2527,20 @@ size_t n_dkv_blocks(const chunk_attn_desc* d) {
   return n;
 }
 
-// Key blocks from which on head_dim 64 and 256 run their pipelined dK/dV kernels: two blocks per CU.  Fewer blocks end earlier
-// in bwd_dkv_kernel (head_dim 64: eight waves on a block instead of two; 256: its blocks start and end faster).
-// Measured backward, bwd_dkv_kernel / pipelined (8 key/value heads), head_dim 64: 256 blocks 61 / 74 us and (32 query heads)
-// 148 / 174, 512 blocks 150 / 141, 1024 blocks of 256-token sequences 228 / 227, of 2048-token sequences 811 / 696, 2048 blocks
-// 7573 / 6451; head_dim 256: 128 blocks 80 / 84, 256 blocks 127 / 127 and (32 query heads) 184 / 167, 312 short ones 169 / 173,
-// 512 blocks 173 / 161 and 508 / 405, 4096 blocks 35161 / 26922.
-constexpr int64_t kMinDkvPipeBlocks = 2 * kCus;
+// Whether head_dim 64 and 256 run their pipelined dK/dV kernels, given the walks of one key/value head.  Those kernels' blocks
+// start and end more slowly than bwd_dkv_kernel's, which has several of them on a CU, so they need two blocks per CU and
+//   64:  24 stages for each of the 512 workgroups that run at a time,
+//   256: walks of 14 stages on average.
+// Measured backward, bwd_dkv_kernel / pipelined, head_dim 64 (stages per workgroup): 64 sequences of 64, 8/8 heads (2) 28 / 38
+// us; 64 of 128, 32/8 (16) 83 / 86; 64 of 256, 8/8 (12) 77 / 78; 32 of 256, 32/8 (24) 106 / 101; 128 of 128, 32/8 (32) 170 /
+// 175; 64 of 256 (48) 217 / 202; 16 of 1024 (144) 478 / 390; 128 queries on 16384 keys (32) 325 / 320, 512 (126) 450 / 407.
+// Head_dim 256 (stages per block): 64 sequences of 64, 8/8 heads (2) 73 / 90; 64 of 256 (5) 334 / 346; 128 of 64, 32/8 (8)
+// 320 / 345; 64 of 128 (12) 381 / 389; 32 of 200 (16) 365 / 322; 64 of 256 (20) 915 / 794; 512 queries on 4096 keys, 8/8
+// (15) 257 / 258, on 8192 490 / 483.
+bool dkv_pipe_pays(const chunk_attn_desc* d, const Walks& w) {
+  const int64_t blocks = w.items * d->num_kv_heads, stages = w.stages * d->num_kv_heads;
+  return blocks >= 2 * kCus && stages >= (d->head_dim == 64 ? 24 * 2 * kCus : 14 * blocks);
+}
 
 // workgroups of the pipelined dK/dV kernels on a CU
 constexpr int dkv_per_cu(int head_dim) { return head_dim == 64 ? 2 : 1; }
@@ -2709,7 +2716,7 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, bool may_c
     P.dq_pipe = pipe_pays(count_walks(d, tile_rows(group, 8)), d->num_kv_heads * (group / heads_per_wg(group, 8)));
     if (P.dq_pipe) P.dq_waves = 8;
   }
-  if (!pipe) P.dkv_pipe = (int64_t)n_dkv_blocks(d) * d->num_kv_heads >= kMinDkvPipeBlocks;
+  if (!pipe) P.dkv_pipe = dkv_pipe_pays(d, count_dkv_walks(d, dkv_keys(d->head_dim)));
   const int dq_rows = tile_rows(group, P.dq_waves);
   P.q_tiles = count_tiles(d, false, 64);
   P.qt32_tiles = count_tiles(d, false, 32);

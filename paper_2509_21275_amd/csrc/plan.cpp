@@ -140,6 +140,20 @@ Walks count_walks(const chunk_attn_desc* d, int tile_rows) {
   return w;
 }
 
+Walks count_dkv_walks(const chunk_attn_desc* d, int keys) {
+  Walks w;
+  for (int t = 0; t < d->num_segments; ++t) {
+    const chunk_attn_seg& s = d->segments[t];
+    const int32_t C = s.kv_len - s.q_len, n_qt = (s.q_len + 31) / 32;
+    for (int32_t j0 = 0; j0 < s.kv_len; j0 += keys) {
+      ++w.items;
+      w.stages += n_qt - std::max<int32_t>(0, j0 - C) / 32;
+    }
+  }
+  w.stages *= d->num_q_heads / d->num_kv_heads;
+  return w;
+}
+
 // The estimate behind both kinds of cut, in steps of a workgroup (about a microsecond each).  A block costs its steps plus
 // kStart for filling the pipeline and writing its rows; a piece kPart more for its float32 rows (twice the bytes).  The
 // blocks of queue 0 (every eighth one) are dealt, longest first, to an eighth of the compute units as they become free.

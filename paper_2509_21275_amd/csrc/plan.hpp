@@ -135,6 +135,8 @@ struct Walks {
   int64_t items = 0, stages = 0;
 };
 Walks count_walks(const chunk_attn_desc* d, int tile_rows);
+// The same for the key-stationary items (`keys` keys each) of one key/value head; a stage is a 32-row query tile of one head.
+Walks count_dkv_walks(const chunk_attn_desc* d, int keys);
 struct KeySplit {
   int target = 0;      // argument of piece_count; 0: nothing is cut
   int64_t pieces = 0;  // items to run (pieces and whole items)

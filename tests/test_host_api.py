@@ -111,6 +111,11 @@ def packed(*lens):
     (packed(256, 512, 128, 128), 8, 8, 64, "", "", ""),
     (packed(*[4096] * 4), 32, 8, 256, "", "", "p"),
     (packed(256, 512, 128, 128), 8, 8, 256, "", "", ""),
+    # many key blocks, but too little to walk for the pipelined dK/dV kernels
+    (packed(*[70] * 64), 8, 8, 64, "", "", ""), (packed(*[128] * 64), 32, 8, 64, "", "", ""),
+    (packed(*[256] * 64), 32, 8, 64, "", "", "p"), ([(0, 512, 0, 16896)], 8, 8, 64, "", "", "p"),
+    (packed(*[70] * 64), 8, 8, 256, "", "", ""), ([(0, 64, 0, 4160)], 32, 8, 256, "", "", ""),
+    (packed(*[200] * 32), 32, 8, 256, "", "", "p"),
 ])
 def test_routes(ca, segs, Hq, Hkv, dim, fwd, dq, dkv):
     """Which kernels a chunk runs; the tests on the GPU assert with the same hook that they reach the path they are named for."""
