@@ -282,9 +282,16 @@ __global__ __launch_bounds__(256) void plan_fwd_static_kernel(StaticSegs segs, i
       it.n0 = s.kv_len - s.q_len + i0 + 1;
       it.kv_tile0 = job0[t];
       it.keys = s.kv_len;
-      stages = walk_stages(it.n0, it.q_rows);
-      n = piece_count(stages, it.n0, target);
+      if (target <= 0) {  // nothing is cut: no pieces to number
+        it.whole = x;
+        it.part = -1;
+        items[x] = it;
+      } else {
+        stages = walk_stages(it.n0, it.q_rows);
+        n = piece_count(stages, it.n0, target);
+      }
     }
+    if (target <= 0) continue;
     int item = n, part = n > 1 ? n : 0;  // inclusive sums over the items up to this one
     for (int o = 1; o < 64; o *= 2) {
       const int a = __shfl_up(item, o), b = __shfl_up(part, o);
@@ -319,7 +326,7 @@ __global__ __launch_bounds__(256) void plan_fwd_static_kernel(StaticSegs segs, i
       p.part = n > 1 ? part + k : -1;
       items[item + k] = p;
     }
-    if (x < n_wholes && target > 0) {
+    if (x < n_wholes) {
       it.whole = n;
       it.part = n > 1 ? part : -1;
       wholes[x] = it;
