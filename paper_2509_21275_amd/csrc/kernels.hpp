@@ -71,11 +71,21 @@ constexpr int kPartFloats = kPartRowFloats + 8 * 32 * 2;
 // (a partial result of a dK/dV block of 128 keys has the same size: units 0 .. 3 are dV, 4 .. 7 dK of 32 keys each)
 
 // Whether a query-stationary kernel of head_dim 64 runs as the pipelined one: its workgroups start and end more slowly than
-// the other kernel's, which has three or four of them on a CU, so it needs two blocks per CU and walks of 64 stages on
-// average.  Measured, other -> pipelined, 32/8 heads: 8192 queries on 32768 keys (906 stages) forward 2086 -> 1934 us,
-// backward 6355 -> 6065; four sequences of 4096 (64) 349 -> 340, 1166 -> 1130; eight of 2048 (34) 206 -> 209, 672 -> 661;
-// sixteen of 1024 (18) 128 -> 147, 403 -> 417; 128 blocks of 1008 stages 460 -> 541, 1085 -> 1132.
-inline bool pipe_pays(const Walks& w, int inner) { return w.items * inner >= 2 * kCus && w.stages >= 64 * w.items; }
+// the other kernel's, which has three of them on a CU, and it puts twice the rows on a block.  So it needs two blocks per CU,
+// walks of 100 stages on average (64 from four blocks per CU on and 45 from eight: more blocks even out better), and no walk
+// that alone takes longer than the 512 workgroups' even share of all (but for a tenth).  Between three and four blocks per CU
+// the second round is nearly as long as with four, and the other kernel's smaller blocks fill the chip better.
+// Measured forward, other -> pipelined, 32/8 heads unless noted (blocks, mean and longest walk): 8192 queries on 16384 keys
+// (1024, 384, 512) 906 -> 859 us; four sequences of 4096 (2048, 65, 128) 390 -> 377; ten of 3000 (3760, 47) 473 -> 450; eight
+// of 2048 (2048, 34) 203 -> 210; 16 of 1024 (2048, 18) 128 -> 148; 4096 queries on 8192 keys (512, 193, 256) 243 -> 253; 5000
+// on 6000 (632, 110, 188) 180 -> 190; 64/8: 2048 on 16384 (512, 480, 512) 568 -> 526, 3000 on 19000 (752, 548, 594) 956 -> 822,
+// 3600 on 13000 (900, 350, 406) 713 -> 777; 8/8: three sequences of 6000 (576, 98, 188) 158 -> 194, four of 4096 (512, 68,
+// 128) 120 -> 137.  dQ is less sensitive: the same rule serves it.
+inline bool pipe_pays(const Walks& w, int inner) {
+  const int64_t blocks = w.items * inner, mean = blocks >= 8 * kCus ? 45 : blocks >= 4 * kCus ? 64 : 100;
+  if (blocks < 2 * kCus || (blocks > 3 * kCus && blocks < 4 * kCus)) return false;
+  return w.stages >= mean * w.items && 10 * w.stages * inner >= 9 * 2 * kCus * w.longest;
+}
 
 // Events armed by chunk_attn_profile_events for the calling thread (null when disarmed).
 struct ProfileEvents {

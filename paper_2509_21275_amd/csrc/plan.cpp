@@ -133,8 +133,10 @@ Walks count_walks(const chunk_attn_desc* d, int tile_rows) {
   for (int t = 0; t < d->num_segments; ++t) {
     const chunk_attn_seg& s = d->segments[t];
     for (int32_t i0 = 0; i0 < s.q_len; i0 += tile_rows) {
+      const int64_t stages = walk_stages(s.kv_len - s.q_len + i0 + 1, std::min<int32_t>(tile_rows, s.q_len - i0));
       ++w.items;
-      w.stages += walk_stages(s.kv_len - s.q_len + i0 + 1, std::min<int32_t>(tile_rows, s.q_len - i0));
+      w.stages += stages;
+      w.longest = std::max(w.longest, stages);
     }
   }
   return w;
@@ -142,15 +144,16 @@ Walks count_walks(const chunk_attn_desc* d, int tile_rows) {
 
 Walks count_dkv_walks(const chunk_attn_desc* d, int keys) {
   Walks w;
+  const int group = d->num_q_heads / d->num_kv_heads;
   for (int t = 0; t < d->num_segments; ++t) {
     const chunk_attn_seg& s = d->segments[t];
     const int32_t C = s.kv_len - s.q_len, n_qt = (s.q_len + 31) / 32;
+    w.longest = std::max<int64_t>(w.longest, (int64_t)n_qt * group);
     for (int32_t j0 = 0; j0 < s.kv_len; j0 += keys) {
       ++w.items;
-      w.stages += n_qt - std::max<int32_t>(0, j0 - C) / 32;
+      w.stages += (int64_t)(n_qt - std::max<int32_t>(0, j0 - C) / 32) * group;
     }
   }
-  w.stages *= d->num_q_heads / d->num_kv_heads;
   return w;
 }
 

@@ -130,9 +130,10 @@ CHUNK_ATTN_HD inline int piece_count(int stages, int n0, int target) {
   return n < 1 ? 1 : n;
 }
 CHUNK_ATTN_HD inline int walk_stages(int n0, int q_rows) { return (n0 + q_rows - 1 + kStageKeys - 1) / kStageKeys; }
-// Query-stationary items of a chunk and the stages they walk together.
+// Items of a chunk and the stages they walk together.
 struct Walks {
   int64_t items = 0, stages = 0;
+  int64_t longest = 0;  // stages of the longest walk
 };
 Walks count_walks(const chunk_attn_desc* d, int tile_rows);
 // The same for the key-stationary items (`keys` keys each) of one key/value head; a stage is a 32-row query tile of one head.

@@ -111,6 +111,10 @@ def packed(*lens):
     (packed(256, 512, 128, 128), 8, 8, 64, "", "", ""),
     (packed(*[4096] * 4), 32, 8, 256, "", "", "p"),
     (packed(256, 512, 128, 128), 8, 8, 256, "", "", ""),
+    # head dimension 64: blocks enough for the pipelined forward and dQ, but too few for their longest walk or their mean one
+    (packed(*[6000] * 3), 8, 8, 64, "", "", "p"), ([(0, 5000, 0, 6000)], 32, 8, 64, "", "", ""),
+    ([(0, 2048, 0, 16384)], 64, 8, 64, "p", "p", "p"), (packed(*[3000] * 10), 32, 8, 64, "p", "p", "p"),
+    (packed(*[2048] * 8), 32, 8, 64, "", "", "p"),
     # many key blocks, but too little to walk for the pipelined dK/dV kernels
     (packed(*[70] * 64), 8, 8, 64, "", "", ""), (packed(*[128] * 64), 32, 8, 64, "", "", ""),
     (packed(*[256] * 64), 32, 8, 64, "", "", "p"), ([(0, 512, 0, 16896)], 8, 8, 64, "", "", "p"),
