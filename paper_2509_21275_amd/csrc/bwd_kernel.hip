@@ -2529,17 +2529,23 @@ size_t n_dkv_blocks(const chunk_attn_desc* d) {
 
 // Whether head_dim 64 and 256 run their pipelined dK/dV kernels, given the walks of one key/value head.  Those kernels' blocks
 // start and end more slowly than bwd_dkv_kernel's, which has several of them on a CU, so they need two blocks per CU and
-//   64:  24 stages for each of the 512 workgroups that run at a time,
+//   64:  24 stages for each of the 512 workgroups that run at a time, and below three blocks per CU walks that are nearly equal
+//        or belong to several sequences, none with more than a quarter of the blocks (one or two long causal sequences
+//        put long walks on the same CU, which then ends last),
 //   256: walks of 14 stages on average.
 // Measured backward, bwd_dkv_kernel / pipelined, head_dim 64 (stages per workgroup): 64 sequences of 64, 8/8 heads (2) 28 / 38
 // us; 64 of 128, 32/8 (16) 83 / 86; 64 of 256, 8/8 (12) 77 / 78; 32 of 256, 32/8 (24) 106 / 101; 128 of 128, 32/8 (32) 170 /
 // 175; 64 of 256 (48) 217 / 202; 16 of 1024 (144) 478 / 390; 128 queries on 16384 keys (32) 325 / 320, 512 (126) 450 / 407.
+// Causal sequences with 512 blocks, 32/8 heads: eight of 1024 265 / 215, four of 2048 438 / 365, two of 4096 604 / 647, one of
+// 8192 1099 / 1222; 8/2: four of 8192 1554 / 1233, two of 16384 2256 / 2414; with 768 blocks: three of 4096 1028 / 811.
 // Head_dim 256 (stages per block): 64 sequences of 64, 8/8 heads (2) 73 / 90; 64 of 256 (5) 334 / 346; 128 of 64, 32/8 (8)
 // 320 / 345; 64 of 128 (12) 381 / 389; 32 of 200 (16) 365 / 322; 64 of 256 (20) 915 / 794; 512 queries on 4096 keys, 8/8
 // (15) 257 / 258, on 8192 490 / 483.
 bool dkv_pipe_pays(const chunk_attn_desc* d, const Walks& w) {
   const int64_t blocks = w.items * d->num_kv_heads, stages = w.stages * d->num_kv_heads;
-  return blocks >= 2 * kCus && stages >= (d->head_dim == 64 ? 24 * 2 * kCus : 14 * blocks);
+  if (blocks < 2 * kCus) return false;
+  if (d->head_dim != 64) return stages >= 14 * blocks;
+  return stages >= 24 * 2 * kCus && (blocks >= 3 * kCus || 4 * w.largest <= w.items || 10 * stages >= 9 * 2 * kCus * w.longest);
 }
 
 // workgroups of the pipelined dK/dV kernels on a CU

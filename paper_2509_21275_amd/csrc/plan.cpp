@@ -132,6 +132,7 @@ Walks count_walks(const chunk_attn_desc* d, int tile_rows) {
   Walks w;
   for (int t = 0; t < d->num_segments; ++t) {
     const chunk_attn_seg& s = d->segments[t];
+    w.largest = std::max<int64_t>(w.largest, (s.q_len + tile_rows - 1) / tile_rows);
     for (int32_t i0 = 0; i0 < s.q_len; i0 += tile_rows) {
       const int64_t stages = walk_stages(s.kv_len - s.q_len + i0 + 1, std::min<int32_t>(tile_rows, s.q_len - i0));
       ++w.items;
@@ -149,6 +150,7 @@ Walks count_dkv_walks(const chunk_attn_desc* d, int keys) {
     const chunk_attn_seg& s = d->segments[t];
     const int32_t C = s.kv_len - s.q_len, n_qt = (s.q_len + 31) / 32;
     w.longest = std::max<int64_t>(w.longest, (int64_t)n_qt * group);
+    w.largest = std::max<int64_t>(w.largest, (s.kv_len + keys - 1) / keys);
     for (int32_t j0 = 0; j0 < s.kv_len; j0 += keys) {
       ++w.items;
       w.stages += (int64_t)(n_qt - std::max<int32_t>(0, j0 - C) / 32) * group;

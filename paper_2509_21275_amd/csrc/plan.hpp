@@ -134,6 +134,7 @@ CHUNK_ATTN_HD inline int walk_stages(int n0, int q_rows) { return (n0 + q_rows -
 struct Walks {
   int64_t items = 0, stages = 0;
   int64_t longest = 0;  // stages of the longest walk
+  int64_t largest = 0;  // items of the sequence that has most
 };
 Walks count_walks(const chunk_attn_desc* d, int tile_rows);
 // The same for the key-stationary items (`keys` keys each) of one key/value head; a stage is a 32-row query tile of one head.
