@@ -106,7 +106,9 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : D == 64 && WAVES == 4 ? 3
   const int kvh = inner % p.num_kv_heads, hs = inner / p.num_kv_heads;
   if constexpr (!IMG) {  // second pass: only what the pipelined kernel left to do
     if (p.redo != nullptr && p.redo[blockIdx.x] == 0) {
-      if (it.part >= 0) fwd_merge_parts<D>(p, it, kvh, hs, inner, inner_n, wave, lane);
+      if constexpr (pipelined(D)) {
+        if (it.part >= 0) fwd_merge_parts<D>(p, it, kvh, hs, inner, inner_n, wave, lane);
+      }
       return;
     }
   }
@@ -887,8 +889,9 @@ static hipError_t launch_fwd_pipe(const FwdParams& p, int num_blocks, int num_wh
   // ring slots of a K and a V tile, then the staging tiles of the four waves (64 rows each)
   const size_t smem = (size_t)2 * (FWD_PIPE_DIST + 3) * 32 * D * 2 + (size_t)4 * 64 * D * 2;
   hipError_t e;
-  if ((e = p.cut ? launch_fwd_items<D, true>(p, num_blocks, smem, stream) : launch_fwd_items<D, false>(p, num_blocks, smem, stream)) !=
-      hipSuccess) return e;
+  if constexpr (pipelined(D)) e = p.cut ? launch_fwd_items<D, true>(p, num_blocks, smem, stream) : launch_fwd_items<D, false>(p, num_blocks, smem, stream);
+  else e = launch_fwd_items<D, false>(p, num_blocks, smem, stream);
+  if (e != hipSuccess) return e;
   // Second pass over the whole items, 8 waves of 32 rows: a workgroup returns at once unless its flag is raised (the item
   // is recomputed) or its item was cut (its pieces are put together).
   return launch_fwd_t<D, 8>(p, num_wholes, stream);

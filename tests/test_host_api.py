@@ -115,6 +115,8 @@ def packed(*lens):
     (packed(*[6000] * 3), 8, 8, 64, "", "", "p"), ([(0, 5000, 0, 6000)], 32, 8, 64, "", "", ""),
     ([(0, 2048, 0, 16384)], 64, 8, 64, "p", "p", "p"), (packed(*[3000] * 10), 32, 8, 64, "p", "p", "p"),
     (packed(*[2048] * 8), 32, 8, 64, "", "", "p"),
+    # (no walk of head dimension 64 is cut)
+    ([(0, 3032, 0, 51484)], 64, 64, 64, "p", "p", "p"),
     # one or two long causal sequences that barely fill the chip
     (packed(4096, 4096), 32, 8, 64, "p", "p", ""), (packed(8192), 8, 8, 64, "", "", ""), (packed(16384, 16384), 8, 2, 64, "p", "p", ""),
     (packed(*[2048] * 4), 32, 8, 64, "", "", "p"), (packed(*[4096] * 3), 32, 8, 64, "p", "p", "p"), ([(0, 1024, 0, 8192)], 32, 8, 64, "", "", "p"),
