@@ -177,52 +177,76 @@ static KeySplit choose_cut(const std::vector<Walk>& walks, int longest, int shor
   constexpr int kStart = 12, kPart = 6, kMerge = 6;
   constexpr int64_t kPartsPerStep = 32;  // partial results (128 KB per block) read per step
   const int workers = std::max(1, cus / 8);
-  const auto later = [](int64_t a, int64_t b) { return a > b; };
   std::vector<int> cost;
   std::vector<int64_t> free_at;
-  int64_t total = 0;  // work of queue 0
-  // `limit`: a cut that cannot end before it is not followed to its end (the result is then some time not below it)
-  auto estimate = [&](KeySplit& k, int64_t limit) -> int64_t {
-    cost.clear();
+  int64_t total = 0;    // work of queue 0 ...
+  int largest = 0;      // ... and its longest block
+  // blocks of queue 0 among the `inner` ones that start at block b: those divisible by 8
+  auto in_queue = [&](int64_t b) { return (b + inner + 7) / 8 - (b + 7) / 8; };
+  auto count_pieces = [&](KeySplit& k) {
     k.pieces = k.parts = 0;
-    int64_t block = 0, sum = 0;
     for (const Walk& w : walks) {
       const int n = pieces(w, k.target);
       k.pieces += n;
       if (n > 1) k.parts += n;
-      for (int i = 0; i < n; ++i) {
-        const int64_t end = block + inner;  // blocks block .. end - 1; those divisible by 8 are queue 0's
-        for (int64_t b = (block + 7) / 8 * 8; b < end; b += 8) {
-          cost.push_back(steps(w, n, i) + kStart + (n > 1 ? kPart : 0));
-          sum += cost.back();
-        }
-        block = end;
+    }
+  };
+  auto count_work = [&](const KeySplit& k) {
+    total = largest = 0;
+    int64_t block = 0;
+    for (const Walk& w : walks) {
+      const int n = pieces(w, k.target);
+      for (int i = 0; i < n; ++i, block += inner) {
+        const int64_t q = in_queue(block);
+        if (q == 0) continue;
+        const int c = steps(w, n, i) + kStart + (n > 1 ? kPart : 0);
+        total += q * c;
+        largest = std::max(largest, c);
       }
     }
-    const int64_t merge = k.parts > 0 ? kMerge + k.parts * inner / kPartsPerStep : 0;
-    total = sum;
-    if (sum / workers + merge >= limit) return limit;
-    std::sort(cost.begin(), cost.end(), later);
+  };
+  auto merge_time = [&](const KeySplit& k) { return k.parts > 0 ? kMerge + k.parts * inner / kPartsPerStep : 0; };
+  auto simulate = [&](const KeySplit& k) -> int64_t {
+    cost.clear();
+    int64_t block = 0;
+    for (const Walk& w : walks) {
+      const int n = pieces(w, k.target);
+      for (int i = 0; i < n; ++i, block += inner) cost.insert(cost.end(), in_queue(block), steps(w, n, i) + kStart + (n > 1 ? kPart : 0));
+    }
+    std::sort(cost.begin(), cost.end(), [](int a, int b) { return a > b; });
     free_at.assign(workers, 0);  // a heap, earliest first
     int64_t last = 0;
     for (int c : cost) {
-      std::pop_heap(free_at.begin(), free_at.end(), later);
-      free_at.back() += c;
-      last = std::max(last, free_at.back());
-      std::push_heap(free_at.begin(), free_at.end(), later);
+      const int64_t end = free_at[0] + c;
+      last = std::max(last, end);
+      int at = 0;  // the earliest one takes the block and sinks to its place
+      for (int child; (child = 2 * at + 1) < workers; at = child) {
+        if (child + 1 < workers && free_at[child + 1] < free_at[child]) ++child;
+        if (free_at[child] >= end) break;
+        free_at[at] = free_at[child];
+      }
+      free_at[at] = end;
     }
-    return last + merge;
+    return last + merge_time(k);
   };
   KeySplit best;
-  int64_t best_time = estimate(best, INT64_MAX);
+  count_pieces(best);
+  count_work(best);
+  int64_t best_time = simulate(best);
   best_time -= best_time / 20;
   if (total / workers >= best_time) return best;  // as even as it can get: pieces only add to the work
+  // The choice is part of every call, so a candidate that cannot win is not followed further: one with too many partial
+  // results, or whose work shared evenly, or longest block alone, already takes as long as the best so far.
   for (int n = 2; n <= 16 && longest / n >= shortest; ++n) {
     KeySplit k;
     k.target = (longest + n - 1) / n;
-    const int64_t time = estimate(k, best_time);
+    count_pieces(k);
     if (k.pieces * inner > 2 * kMaxCutBlocks) break;
-    if (k.parts > 0 && k.parts <= max_parts && time < best_time) {
+    if (k.parts == 0 || k.parts > max_parts) continue;
+    count_work(k);
+    if (std::max<int64_t>(total / workers, largest) + merge_time(k) >= best_time) continue;
+    const int64_t time = simulate(k);
+    if (time < best_time) {
       best = k;
       best_time = time;
     }
@@ -264,7 +288,7 @@ KeySplit choose_tile_split(const chunk_attn_desc* d, int keys, int cus, int64_t 
   return choose_cut(
       walks, longest, (2 * kMinPieceStages + group - 1) / group, d->num_kv_heads, cus, max_parts,
       [](int tiles, int target) { return tile_piece_count(tiles, target); },
-      [&](int tiles, int n, int k) { return ((int)((int64_t)tiles * (k + 1) / n) - (int)((int64_t)tiles * k / n)) * group; });
+      [&](int tiles, int n, int k) { return (share_begin(tiles, n, k + 1) - share_begin(tiles, n, k)) * group; });
 }
 
 std::vector<DkvItem> cut_items(const std::vector<DkvItem>& wholes, int target, std::vector<DkvItem>* cut) {
@@ -279,8 +303,8 @@ std::vector<DkvItem> cut_items(const std::vector<DkvItem>& wholes, int target, s
     }
     for (int k = 0; k < n; ++k) {
       DkvItem it = whole;
-      it.qt_first = whole.qt_first + (int)((int64_t)tiles * k / n);
-      it.n_qt = whole.qt_first + (int)((int64_t)tiles * (k + 1) / n);
+      it.qt_first = whole.qt_first + share_begin(tiles, n, k);
+      it.n_qt = whole.qt_first + share_begin(tiles, n, k + 1);
       it.part = n > 1 ? part++ : -1;
       items.push_back(it);
     }

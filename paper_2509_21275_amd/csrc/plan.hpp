@@ -118,8 +118,11 @@ std::vector<DqItem> plan_dq(const chunk_attn_desc* d, int tile_rows);
 // pieces that run on different compute units, write float32 partial results and are put together afterwards.
 constexpr int kStageKeys = 32;
 constexpr int kMinPieceStages = 8;  // below that a piece's start and end cost more than its walk
+// First of `n` units of piece k of `pieces` (unsigned 32-bit: fewer than 2^26 units, as 2^31 rows make, and at most 17 pieces;
+// a 64-bit division takes several times as long, on the host and even more on the device).
+CHUNK_ATTN_HD inline int share_begin(int n, int pieces, int k) { return (int)((unsigned)n * (unsigned)k / (unsigned)pieces); }
 // First stage of piece k of a walk of `stages` stages cut into `pieces`.  Even: the kernels take steps two at a time.
-CHUNK_ATTN_HD inline int piece_begin(int stages, int pieces, int k) { return (int)((int64_t)stages * k / pieces) & ~1; }
+CHUNK_ATTN_HD inline int piece_begin(int stages, int pieces, int k) { return share_begin(stages, pieces, k) & ~1; }
 // Pieces of a walk whose first row sees n0 keys, for a cut into pieces of about `target` stages (0: none are cut).  The
 // last piece begins with a key that every row sees (the rows of a piece need one to begin with).
 CHUNK_ATTN_HD inline int piece_count(int stages, int n0, int target) {
