@@ -1936,8 +1936,8 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_wide_pipe_kernel(DkvParams p, 
         __builtin_amdgcn_sched_barrier(0);
       });
       // this wave's copies of the step before have landed (those of this step may still be in flight); its hand-over has
-      // been stored
-      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(PER_A + 1) : "memory");
+      // been stored and the LSE rows of the next step have arrived
+      asm volatile("s_waitcnt vmcnt(%4) lgkmcnt(0)" : "+v"(rl[0]), "+v"(rl[1]), "+v"(rl[2]), "+v"(rl[3]) : "n"(PER_A + 1) : "memory");
       wg_barrier();
     };
     for (int g = 0; g <= n_iter; g += 2) {

@@ -1,0 +1,49 @@
+"""LDS reads written as instructions (lds_asm_read*) are invisible to the compiler: a register they fill may be used only after
+an s_waitcnt that covers the read, and only naming the register in that statement (or in an empty one behind it) keeps the
+compiler from moving the use in front of it.  This looks at the source of every pipelined step: each array that a
+read fills is an operand of a wait in the same step."""
+import os
+import re
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2509_21275_amd", "csrc")
+
+
+def lambda_bodies(text, name):
+    """Bodies of the lambdas `auto name = [&](...) ... { ... };`"""
+    for m in re.finditer(r"auto %s = \[&\]" % name, text):
+        at = text.index("{", m.end())
+        depth, i = 0, at
+        while True:
+            depth += {"{": 1, "}": -1}.get(text[i], 0)
+            i += 1
+            if depth == 0:
+                break
+        yield text[at:i], text.count("\n", 0, at) + 1
+
+
+def statements(body):
+    """Operand texts of the asm statements that wait for LDS reads or stand for one that did (empty, tying registers)."""
+    for m in re.finditer(r'asm volatile\("((?:[^"\\]|\\.)*)"', body):
+        end, depth = m.start() + len("asm volatile"), 0
+        while True:
+            depth += {"(": 1, ")": -1}.get(body[end], 0)
+            end += 1
+            if depth == 0:
+                break
+        if "lgkmcnt" in m.group(1) or m.group(1) == "":
+            yield body[m.end():end]
+
+
+@pytest.mark.parametrize("source", ["fwd_kernel.hip", "bwd_kernel.hip", "bwd_fused_kernel.hip"])
+def test_every_array_read_in_a_step_is_tied_to_a_wait(source):
+    text = open(os.path.join(CSRC, source)).read()
+    steps = list(lambda_bodies(text, "step"))
+    found = 0
+    for body, line in steps:
+        filled = set(re.findall(r"\b(\w+)(?:\[[^=;]*\])? = (?:lds_asm_read\w*|load_\w+)\b", body))
+        found += len(filled)
+        tied = set(re.findall(r'"\+v"\((\w+)', " ".join(statements(body))))
+        assert filled <= tied, f"{source}:{line}: {sorted(filled - tied)} read from LDS, but no wait names them"
+    assert found >= 1
