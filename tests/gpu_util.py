@@ -40,6 +40,13 @@ def run_gpu(case, q, k, v, do=None, accumulate=False, dk_init=None, dv_init=None
     return o, lse, dq, dk, dv
 
 
+def routes(case):
+    """Which kernels the library chooses for a case (ROUTE_* bits)."""
+    import paper_2509_21275_amd as ca
+    return ca.chunk_attn_test_routes(ca.make_desc(case.segs, case.num_q_heads, case.num_kv_heads, case.head_dim, case.total_q,
+                                                  case.total_kv, case.scale))
+
+
 def rel_err(gpu, ref):
     """max |gpu - ref| / max |ref| over the compared elements (one ratio per tensor)."""
     g = gpu.detach().double().cpu().numpy() if isinstance(gpu, torch.Tensor) else np.asarray(gpu, dtype=np.float64)

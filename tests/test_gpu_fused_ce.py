@@ -103,3 +103,32 @@ def test_a_nan_logit_is_not_lost(vocab):
     assert np.isnan(got_loss[[1, 2]]).all() and np.isnan(got[1]).all() and np.isnan(got[2]).all()
     assert np.abs(got_loss[keep] - want_loss).max() <= 2e-4 * max(1.0, np.abs(want_loss).max())
     assert np.all(np.abs(got[keep] - want_grad) <= 2.0 ** -8 * np.abs(want_grad) + 2.0 ** -8 * 0.5 * 1e-3)
+
+
+@pytest.mark.parametrize("rows,vocab", [(1100, 131080), (1100, 163848), (600, 262136), (1100, 4096)])
+def test_workgroups_that_run_several_rows(rows, vocab):
+    """More rows than workgroups (512): a workgroup's next row refills its registers and LDS and reuses its partial results,
+    twice where there are more than 1024 rows.  Maxima and targets differ from row to row; rows around the multiples of 512
+    and a few others against the oracle, all losses against PyTorch in float64."""
+    from paper_2509_21275_amd.fused_ce import fused_ce_inplace
+    g = torch.Generator(device="cuda").manual_seed(rows + vocab)
+    buf = torch.randn((rows, vocab), generator=g, device="cuda", dtype=torch.bfloat16)
+    buf += torch.linspace(-30.0, 30.0, rows, device="cuda").to(torch.bfloat16)[torch.randperm(rows, generator=g, device="cuda")].view(-1, 1)
+    targets = torch.randint(0, vocab, (rows,), generator=g, device="cuda", dtype=torch.int32)
+    targets[torch.arange(7, rows, 97, device="cuda")] = -1
+    check = [r for r in (0, 1, 7, 255, 510, 511, 512, 513, 1022, 1023, 1024, 1025, rows - 2, rows - 1) if r < rows]
+    kept = buf[check].cpu().double().numpy()
+    want_all = torch.empty(rows, dtype=torch.float64, device="cuda")
+    for r0 in range(0, rows, 64):
+        z = buf[r0:r0 + 64].double()
+        y = targets[r0:r0 + 64].long()
+        want_all[r0:r0 + 64] = torch.where(y < 0, torch.zeros((), dtype=torch.float64, device="cuda"),
+                                           torch.logsumexp(z, 1) - z.gather(1, y.clamp(min=0).view(-1, 1)).view(-1))
+    loss = torch.full((rows,), float("nan"), device="cuda")
+    fused_ce_inplace(buf, targets, loss, 0.5)
+    torch.cuda.synchronize()
+    assert float((loss.double() - want_all).abs().max()) <= 2e-4 * max(1.0, float(want_all.abs().max()))
+    want_loss, want_grad = orc.cross_entropy(kept, targets[check].cpu().numpy(), 0.5)
+    got = buf[check].cpu().double().numpy()
+    assert np.abs(loss[check].cpu().double().numpy() - want_loss).max() <= 2e-4 * max(1.0, np.abs(want_loss).max())
+    assert np.all(np.abs(got - want_grad) <= 2.0 ** -8 * np.abs(want_grad) + 2.0 ** -8 * 0.5 * 1e-3)

@@ -9,7 +9,7 @@ import torch
 
 import synth
 import paper_2509_21275_amd as ca
-from gpu_util import TOL_GRAD, TOL_O, make_inputs, rel_err, run_gpu
+from gpu_util import TOL_GRAD, TOL_O, make_inputs, rel_err, routes, run_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -126,19 +126,25 @@ def test_pipelined_kernels_of_head_dim_96(oracle_mod, name, segs, Hq, Hkv):
         assert rel_err(a, b.double().cpu().numpy()) <= 2.0 ** -7
 
 
-@pytest.mark.parametrize("name,segs,Hq,Hkv", [
-    # 64 key/value heads: enough blocks for the pipelined kernels of head_dim 64 on short chunks
-    ("dkv_ragged", [(0, 1000, 0, 1000), (1000, 33, 1000, 160)], 64, 64),          # 10 key blocks x 64, walks of 34 stages
-    ("dkv_groups_and_gaps", [(0, 130, 3, 900), (130, 1, 910, 129), (131, 95, 1041, 127)], 128, 64),
-    ("all_pipelined", [(0, 1100, 0, 2600)], 64, 64),                              # 5 x 64 query items of 54 .. 82 stages
-    ("all_pipelined_gqa4", [(0, 2050, 0, 4000)], 64, 16),
+ALL_PIPELINED = ca.ROUTE_FWD_PIPELINED | ca.ROUTE_DQ_PIPELINED | ca.ROUTE_DKV_PIPELINED
+
+
+@pytest.mark.parametrize("name,segs,Hq,Hkv,want", [
+    # many heads: enough blocks for the pipelined kernels of head_dim 64 on short chunks
+    ("dkv_ragged", [(0, 1000, 0, 1000), (1000, 33, 1000, 160)], 128, 128, ca.ROUTE_DKV_PIPELINED),
+    ("dkv_groups_and_gaps", [(0, 130, 3, 900), (130, 1, 910, 129), (131, 95, 1041, 127)], 512, 256, ca.ROUTE_DKV_PIPELINED),
+    ("all_pipelined", [(0, 300, 0, 4000)], 256, 256, ALL_PIPELINED),
+    ("all_pipelined_ragged", [(0, 290, 0, 3900), (290, 30, 3903, 70)], 512, 512, ALL_PIPELINED),
+    ("all_pipelined_gqa4", [(0, 500, 0, 3600)], 256, 64, ALL_PIPELINED),
+    ("all_pipelined_gqa8", [(0, 500, 0, 3700)], 512, 64, ALL_PIPELINED),
 ])
-def test_pipelined_kernels_of_head_dim_64(oracle_mod, name, segs, Hq, Hkv):
+def test_pipelined_kernels_of_head_dim_64(oracle_mod, name, segs, Hq, Hkv, want):
     """Chunks with enough blocks (and, for forward and dQ, long enough walks) for head_dim 64's pipelined kernels: ragged key
     blocks and query tiles, rows outside key ranges, accumulation; against the oracle on one head group of each end.  (LSE:
     the forward that is not pipelined sums the probabilities as rounded to bf16, 2^-9 of the sum at most.)"""
     tq, tkv = max(s[0] + s[1] for s in segs), max(s[2] + s[3] for s in segs) + 2
     case = synth.ChunkCase(f"{name}_d64", [synth.Seg(*s) for s in segs], tq, tkv, Hq, Hkv, 64, 700 + len(name))
+    assert routes(case) == want
     q, k, v, do = make_inputs(case)
     got = run_gpu(case, q, k, v, do)
     again = run_gpu(case, q, k, v, do)
@@ -165,7 +171,7 @@ def test_pipelined_kernels_of_head_dim_64(oracle_mod, name, segs, Hq, Hkv):
 @pytest.mark.parametrize("d", [64, 256])
 @pytest.mark.parametrize("Hq,Hkv", [(2, 2), (4, 1), (6, 2)])
 def test_tile_edges_of_the_kernels_for_short_walks(oracle_mod, d, Hq, Hkv):
-    """Head dimensions 64 and 256 below the pipelined kernels' sizes: key counts on both sides of the 32- and 64-row tiles the
+    """Head dimensions 64 and 256 below the pipelined kernels' sizes (asserted): key counts on both sides of the 32- and 64-row tiles the
     forward and dQ kernels read rows and transposed operands from, contexts that are and are not whole tiles, single rows.
     (LSE: these forwards sum the probabilities as rounded to bf16, 2^-9 of the sum at most.)"""
     lens = [(1, 1), (31, 31), (32, 32), (33, 33), (63, 64), (64, 65), (65, 65), (1, 96), (2, 128), (40, 129), (95, 191), (129, 193)]
@@ -174,6 +180,7 @@ def test_tile_edges_of_the_kernels_for_short_walks(oracle_mod, d, Hq, Hkv):
         segs.append((tq, n, tkv, keys))
         tq, tkv = tq + n, tkv + keys
     case = synth.ChunkCase(f"tile_edges_d{d}", [synth.Seg(*s) for s in segs], tq, tkv, Hq, Hkv, d, 610 + Hq)
+    assert routes(case) == 0
     q, k, v, do = make_inputs(case)
     o, lse, dq, dk, dv = run_gpu(case, q, k, v, do)
     orc = oracle_mod.Oracle(case.segs, q.cpu(), k.cpu(), v.cpu(), do.cpu(), case.scale)
@@ -189,28 +196,50 @@ def test_tile_edges_of_the_kernels_for_short_walks(oracle_mod, d, Hq, Hkv):
 def test_second_pass_of_head_dim_64(oracle_mod):
     """The pipelined forward of head_dim 64 with every item sent to its second pass (probabilities rounded to bf16 are summed
     there: 2^-9 of the sum at most, as much in its logarithm)."""
-    case = synth.ChunkCase("redo_d64", [synth.Seg(0, 1100, 0, 2600)], 1100, 2600, 64, 64, 64, 77)
+    case = synth.ChunkCase("redo_d64", [synth.Seg(0, 290, 0, 3900), synth.Seg(290, 30, 3903, 70)], 320, 3973, 512, 512, 64, 77)
+    assert routes(case) & ca.ROUTE_FWD_PIPELINED
     q, k, v, _ = make_inputs(case)
+    first = run_gpu(case, q, k, v, backward=False)
     ca.chunk_attn_test_set_fwd_rescale_limit(-1e30)
     try:
         o, lse = run_gpu(case, q, k, v, backward=False)
     finally:
         ca.chunk_attn_test_set_fwd_rescale_limit(60.0)
-    O, LSE = oracle_mod.Oracle(case.segs, q[:, 5:6].cpu().contiguous(), k[:, 5:6].cpu().contiguous(), v[:, 5:6].cpu().contiguous(), None, case.scale).forward()
-    assert rel_err(o[:, 5:6], O) <= TOL_O and float(np.abs(lse[5:6].double().cpu().numpy() - LSE).max()) <= 2.0 ** -9 + 1e-4
+    assert not torch.equal(lse, first[1])           # the second pass ran: it sums rounded probabilities
+    for h in (5, 511):
+        O, LSE = oracle_mod.Oracle(case.segs, q[:, h:h + 1].cpu().contiguous(), k[:, h:h + 1].cpu().contiguous(),
+                                   v[:, h:h + 1].cpu().contiguous(), None, case.scale).forward()
+        assert rel_err(o[:, h:h + 1], O) <= TOL_O and float(np.abs(lse[h:h + 1].double().cpu().numpy() - LSE).max()) <= 2.0 ** -9 + 1e-4
+
+
+def test_scores_that_outgrow_their_first_stage_at_head_dim_64(oracle_mod):
+    """Half of the heads have keys whose scores grow past the limit late in the walk: their items alone take the second pass."""
+    case = synth.ChunkCase("late_growth_d64", [synth.Seg(0, 300, 0, 4000)], 300, 4000, 256, 256, 64, 78)
+    assert routes(case) & ca.ROUTE_FWD_PIPELINED
+    q, k, v, _ = make_inputs(case)
+    ramp = torch.zeros((4000, 256, 1), device=q.device)
+    ramp[3000:3400, :128] = torch.linspace(0.0, 3.0, 400, device=q.device).view(-1, 1, 1)   # up to 96 nats
+    q = torch.full_like(q, 4.0)
+    k = (k.float() * 0.05 + ramp).to(torch.bfloat16)
+    o, lse = run_gpu(case, q, k, v, backward=False)
+    for h, tol in ((3, 2.0 ** -9 + 1e-4), (127, 2.0 ** -9 + 1e-4), (128, 1e-4), (255, 1e-4)):
+        O, LSE = oracle_mod.Oracle(case.segs, q[:, h:h + 1].cpu().contiguous(), k[:, h:h + 1].cpu().contiguous(),
+                                   v[:, h:h + 1].cpu().contiguous(), None, case.scale).forward()
+        assert rel_err(o[:, h:h + 1], O) <= TOL_O and float(np.abs(lse[h:h + 1].double().cpu().numpy() - LSE).max()) <= tol
 
 
 @pytest.mark.parametrize("name,segs,Hq,Hkv", [
-    # enough 64-key blocks for the pipelined dK/dV kernel of head_dim 256, both walk directions among them
-    ("ragged", [(0, 700, 0, 700), (700, 33, 700, 160)], 64, 64),
-    ("groups_and_gaps", [(0, 130, 3, 900), (130, 1, 910, 129), (131, 63, 1041, 127)], 64, 32),
-    ("context_blocks_in_groups", [(0, 65, 0, 65 + 70 * 64)], 16, 8),
+    # enough 64-key blocks and stages for the pipelined dK/dV kernel of head_dim 256, both walk directions among them
+    ("ragged", [(0, 1100, 0, 1100), (1100, 33, 1100, 160)], 64, 64),
+    ("groups_and_gaps", [(0, 400, 3, 900), (400, 1, 910, 129), (401, 63, 1041, 127)], 64, 32),
+    ("many_context_blocks", [(0, 250, 0, 250 + 70 * 64)], 16, 8),
 ])
 def test_pipelined_dkv_of_head_dim_256(oracle_mod, name, segs, Hq, Hkv):
     """Ragged key blocks and query tiles, walks of one stage upwards, rows outside key ranges, accumulation, float32 buffers;
     against the oracle on one head group of each end."""
     tq, tkv = max(s[0] + s[1] for s in segs), max(s[2] + s[3] for s in segs) + 2
     case = synth.ChunkCase(f"{name}_d256", [synth.Seg(*s) for s in segs], tq, tkv, Hq, Hkv, 256, 800 + len(name))
+    assert routes(case) == ca.ROUTE_DKV_PIPELINED
     q, k, v, do = make_inputs(case)
     _, _, _, dk, dv = run_gpu(case, q, k, v, do)
     again = run_gpu(case, q, k, v, do)

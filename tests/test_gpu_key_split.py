@@ -1,25 +1,31 @@
 """Chunks with few query rows and long key walks, whose work items the head_dim 128 and 96 kernels cut into pieces:
-against the fp64 oracle (2e-2 for O, 5e-2 for the gradients, as everywhere), against the uncut run (a workspace
-without room for partial results; both are bf16 roundings of float32 sums in different orders, so they differ by about one
-rounding: 2^-7 of the largest value), and bit for bit between the workspace and the static forward."""
+against the fp64 oracle (2e-2 for O, 5e-2 for the gradients, as everywhere), against the uncut run (the same heads among so
+many copies of them that nothing is cut; both are bf16 roundings of float32 sums in different orders, so they differ by about one
+rounding: 2^-7 of the largest value), and bit for bit between the workspace and the static forward and, where the workspace
+has no room for pieces, with the uncut run.  Every case asserts which walks the library cuts."""
+import dataclasses
+
 import pytest
 import torch
 
 import synth
 import paper_2509_21275_amd as ca
-from gpu_util import TOL_GRAD, TOL_O, make_inputs, rel_err, run_gpu
+from gpu_util import TOL_GRAD, TOL_O, make_inputs, rel_err, routes, run_gpu
 
 pytestmark = pytest.mark.gpu
 
-CASES = [  # name, segments, query heads, key/value heads
-    ("one_query", [(0, 1, 0, 1100)], 8, 2),
-    ("ragged_slice", [(0, 203, 0, 1704)], 8, 2),
-    ("walk_ends_on_a_stage", [(0, 64, 0, 1024)], 4, 1),
-    ("one_key_past_a_stage", [(0, 65, 0, 1025 + 64)], 16, 2),
-    ("mha_256_row_items", [(0, 257, 0, 2000)], 3, 3),
-    ("causal_from_the_start", [(0, 1900, 0, 1900)], 2, 1),
-    ("key_blocks_cut_too", [(0, 700, 0, 1100)], 8, 2),
-    ("cut_and_uncut_items", [(0, 130, 3, 1630), (130, 70, 1640, 70), (200, 1, 1710, 900), (201, 300, 2612, 300)], 6, 2),
+FWD, DQ, DKV = ca.ROUTE_FWD_CUT, ca.ROUTE_DQ_CUT, ca.ROUTE_DKV_CUT
+CUT = FWD | DQ | DKV
+CASES = [  # name, segments, query heads, key/value heads, walks that are cut
+    ("one_query", [(0, 1, 0, 1100)], 8, 2, FWD),
+    ("ragged_slice", [(0, 203, 0, 1704)], 8, 2, FWD),
+    ("walk_ends_on_a_stage", [(0, 64, 0, 1024)], 4, 1, FWD),
+    ("one_key_past_a_stage", [(0, 65, 0, 1025 + 64)], 16, 2, FWD),
+    ("mha_256_row_items", [(0, 257, 0, 2000)], 3, 3, FWD),
+    ("causal_from_the_start", [(0, 1900, 0, 1900)], 2, 1, FWD),
+    ("dq_walks", [(0, 300, 0, 4000)], 8, 2, FWD | DQ),
+    ("key_blocks", [(0, 1300, 0, 1300)], 8, 2, FWD | DKV),
+    ("cut_and_uncut_items", [(0, 130, 3, 1630), (130, 70, 1640, 70), (200, 1, 1710, 900), (201, 300, 2612, 300)], 6, 2, FWD),
 ]
 
 
@@ -37,10 +43,36 @@ def _case(name, segs, hq, hk, d=128):
     return synth.ChunkCase(name, [synth.Seg(*s) for s in segs], tq, tkv, hq, hk, d, 900 + len(name))
 
 
+def _uncut(case, q, k, v, do):
+    """Forward and backward of the case as the first heads of a chunk with so many copies of them that no walk is cut."""
+    copies = 2
+    while routes(dataclasses.replace(case, num_q_heads=copies * case.num_q_heads, num_kv_heads=copies * case.num_kv_heads)) & CUT:
+        copies *= 2
+    many = dataclasses.replace(case, num_q_heads=copies * case.num_q_heads, num_kv_heads=copies * case.num_kv_heads)
+    o, lse, dq, dk, dv = run_gpu(many, *(x.repeat(1, copies, 1) for x in (q, k, v, do)))
+    hq, hk = case.num_q_heads, case.num_kv_heads
+    return [x.contiguous() for x in (o[:, :hq], lse[:hq], dq[:, :hq], dk[:, :hk], dv[:, :hk])]
+
+
+def _smallest_workspace(call, size):
+    """Bytes (a multiple of 256, by halving) of the smallest workspace that `call` accepts; refused calls launch nothing."""
+    ws, lo, hi = torch.empty(size, dtype=torch.uint8, device="cuda"), 0, size
+    while hi - lo > 256:
+        mid = (lo + hi) // 512 * 256
+        try:
+            call(ws[:mid])
+            hi = mid
+        except ca.ChunkAttnError as e:
+            assert e.code == ca.WORKSPACE_TOO_SMALL
+            lo = mid
+    return ws[:hi]
+
+
 @pytest.mark.parametrize("d", [128, 96])
-@pytest.mark.parametrize("name,segs,hq,hk", CASES, ids=[c[0] for c in CASES])
-def test_cut_walks(oracle_mod, name, segs, hq, hk, d):
+@pytest.mark.parametrize("name,segs,hq,hk,cut", CASES, ids=[c[0] for c in CASES])
+def test_cut_walks(oracle_mod, name, segs, hq, hk, cut, d):
     case = _case(name, segs, hq, hk, d)
+    assert routes(case) & CUT == cut
     q, k, v, do = make_inputs(case)
     o, lse, dq, dk, dv = run_gpu(case, q, k, v, do)
     orc = oracle_mod.Oracle(case.segs, q.cpu(), k.cpu(), v.cpu(), do.cpu(), case.scale)
@@ -53,25 +85,41 @@ def test_cut_walks(oracle_mod, name, segs, hq, hk, d):
     ca.chunk_attn_fwd_static(desc, q, k, v, o2, lse2)
     assert torch.equal(o, o2) and torch.equal(lse, lse2)
 
-    # the largest workspace with which nothing is cut: found by halving (calls with less are refused without a launch)
-    lo, hi = 0, ca.chunk_attn_workspace_bytes(desc)[0]
-    ws = torch.empty(hi, dtype=torch.uint8, device=q.device)
-    while hi - lo > 256:
-        mid = (lo + hi) // 512 * 256
-        try:
-            ca.chunk_attn_fwd(desc, q, k, v, o2, lse2, ws[:mid])
-            hi = mid
-        except ca.ChunkAttnError:
-            lo = mid
+    uncut = _uncut(case, q, k, v, do)
+    for got, want, tol in zip((o, lse, dq, dk, dv), uncut, (2.0 ** -7, 1e-5, 2.0 ** -7, 2.0 ** -7, 2.0 ** -7)):
+        assert rel_err(got, want.double().cpu().numpy()) <= tol
+
+
+@pytest.mark.parametrize("name,segs,hq,hk,cut", [c for c in CASES if c[0] in ("ragged_slice", "dq_walks", "key_blocks", "causal_from_the_start")],
+                         ids=["ragged_slice", "causal_from_the_start", "dq_walks", "key_blocks"])
+def test_workspace_without_room_for_pieces(name, segs, hq, hk, cut):
+    """Forward and backward accept a workspace of the uncut layout's size and then run uncut: the uncut run's bits.  (At
+    head_dim 96 the reported sizes have room for pieces anyway.)"""
+    case = _case(name, segs, hq, hk)
+    q, k, v, do = make_inputs(case)
+    o, lse, dq, dk, dv = _uncut(case, q, k, v, do)
+    desc = ca.make_desc(case.segs, hq, hk, 128, case.total_q, case.total_kv, case.scale)
+    fwd, bwd = ca.chunk_attn_workspace_bytes(desc)
+    o2, lse2, dq2, dk2, dv2 = (torch.full_like(x, float("nan")) for x in (o, lse, dq, dk, dv))
+    ws = _smallest_workspace(lambda w: ca.chunk_attn_fwd(desc, q, k, v, o2, lse2, w), fwd)
+    assert ws.numel() < fwd
     o2.fill_(float("nan")); lse2.fill_(float("nan"))
-    ca.chunk_attn_fwd(desc, q, k, v, o2, lse2, ws[:hi])
-    assert rel_err(o, o2.double().cpu().numpy()) <= 2.0 ** -7 and rel_err(lse, lse2.double().cpu().numpy()) <= 1e-5
+    ca.chunk_attn_fwd(desc, q, k, v, o2, lse2, ws)
+    assert torch.equal(o, o2) and torch.equal(lse, lse2)
+    ws = _smallest_workspace(lambda w: ca.chunk_attn_bwd(desc, q, k, v, o, do, lse, dq2, dk2, dv2, 0, w), bwd)
+    assert (ws.numel() < bwd) == bool(cut & (DQ | DKV))
+    for x in (dq2, dk2, dv2):
+        x.fill_(float("nan"))
+    ca.chunk_attn_bwd(desc, q, k, v, o, do, lse, dq2, dk2, dv2, 0, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(dq, dq2) and torch.equal(dk, dk2) and torch.equal(dv, dv2)
 
 
 @pytest.mark.parametrize("d", [128, 96])
 def test_cut_walks_that_take_the_second_pass(oracle_mod, d):
     """Every piece raises its item's flag: the whole items are recomputed, not put together."""
-    case = _case(*CASES[7], d)
+    case = _case(*CASES[-1][:4], d)
+    assert routes(case) & FWD
     q, k, v, _ = make_inputs(case)
     ca.chunk_attn_test_set_fwd_rescale_limit(-1e30)
     try:
@@ -85,6 +133,7 @@ def test_cut_walks_that_take_the_second_pass(oracle_mod, d):
 def test_piece_whose_scores_outgrow_its_first_stage(oracle_mod):
     """Only a later piece's scores grow past the limit: its flag alone sends the item to the second pass."""
     n, case = 1500, _case("late_growth", [(0, 64, 0, 1500)], 8, 2)
+    assert routes(case) & FWD
     q, k, v, _ = make_inputs(case)
     ramp = torch.zeros(k.shape[0], device=q.device)
     ramp[n - 400: n] = torch.linspace(0.0, 3.0, 400, device=q.device)
@@ -102,6 +151,7 @@ def test_cut_key_blocks_accumulate(oracle_mod, f32kv, d):
     range stay as they are; the same bits on a second run."""
     segs = [(0, 1100, 5, 1400), (1100, 77, 1410, 77)]
     case = _case("cut_accumulate", segs, 6, 2, d)
+    assert routes(case) & DKV
     q, k, v, do = make_inputs(case)
     init = torch.full(k.shape, 3.0, device=q.device, dtype=torch.float32 if f32kv else torch.bfloat16)
     got = run_gpu(case, q, k, v, do, accumulate=True, dk_init=init, dv_init=init, f32kv=f32kv)
