@@ -70,7 +70,7 @@ typedef struct {
 typedef struct {
   int32_t num_q_heads;  /* Hq > 0 */
   int32_t num_kv_heads; /* Hkv > 0, divides Hq */
-  int32_t head_dim;     /* 64, 96, 128 or 256 (a workspace for 96 is sized as one for 128 plus padded copies) */
+  int32_t head_dim;     /* 64, 96, 128 or 256 */
   int32_t total_q;      /* rows of q / o / d_o / dq */
   int32_t total_kv;     /* rows of k / v / dk / dv */
   int32_t num_segments; /* >= 1 */
@@ -84,9 +84,13 @@ typedef struct {
 
 /*
  * Scratch sizes (bytes) for a descriptor: *fwd_bytes for chunk_attn_fwd, *bwd_bytes for
- * chunk_attn_bwd (the tile schedules, the row sums D_i = <dO_i, O_i>, transposed tile images
- * of V (head_dim 64 and 256) or float32 partial results (96 and 128); for head_dim 96
- * also room for zero-padded copies of the tensors, 128 wide).  Either output pointer may be NULL.  Validates the descriptor.
+ * chunk_attn_bwd.  Forward: the tile schedule, then room for transposed tile images of V (made for head_dim 256 only) or for
+ * the float32 partial results of walks that are cut (96 and 128; up to 16 MiB where the images would be smaller).  Backward:
+ * the schedules, the row sums D_i = <dO_i, O_i> and, for 96 and 128, float32 tiles of dQ or partial results.  For 96 both also
+ * have room for zero-padded copies of the tensors, 128 wide.  Some of that room is used by no kernel of the default mode
+ * and kept so that the sizes stay what callers know.  A chunk whose walks would be cut also runs in a somewhat smaller
+ * workspace, one that holds its uncut schedule: nothing is cut then, and the results are other roundings of the same sums.
+ * Either output pointer may be NULL.  Validates the descriptor.
  */
 int chunk_attn_workspace_bytes(const chunk_attn_desc* desc, size_t* fwd_bytes, size_t* bwd_bytes);
 
@@ -112,7 +116,7 @@ int chunk_attn_fwd(const chunk_attn_desc* desc, const void* q, const void* k, co
  * segment table, which travels as a kernel argument).  Its scratch memory is a fixed array of
  * 16 MiB inside the library, one copy per GPU, held until the process ends.
  * Limits: at most 64 segments, and a forward scratch need (chunk_attn_workspace_bytes' *fwd_bytes:
- * the schedule plus one transposed copy of V) of at most 16 MiB, else CHUNK_ATTN_TOO_LARGE and
+ * the schedule plus room for one transposed copy of V) of at most 16 MiB, else CHUNK_ATTN_TOO_LARGE and
  * nothing is launched.  All calls on one GPU share that GPU's array: calls that may overlap on
  * one GPU (different streams, different threads) race and must be serialised by the caller.
  */
@@ -176,7 +180,7 @@ int chunk_attn_profile_events(void* start_event, void* stop_event);
 int chunk_attn_shutdown(void);
 
 /*
- * Test hook (not part of the method): the head_dim 128 forward keeps the softmax reference
+ * Test hook (not part of the method): the pipelined forward (head_dim 96 and 128, and 64 for large chunks) keeps the softmax reference
  * maximum of a row fixed after its first key tile and recomputes, in a second pass with a moving
  * maximum, the rows whose later scores exceed it by more than 2^log2_growth (default 60; any
  * reference gives the same softmax).  A very negative value sends every row through the second
@@ -203,8 +207,8 @@ int chunk_attn_measure_mfma_rate_on(int milliseconds, int workgroups, void* scra
                                     double* tflops);
 
 /*
- * Measurement hook (not part of the method): the clock the three pipelined kernels (forward, dQ, dK/dV; head_dim 64,
- * 96 and 128) actually run at.  `device_buffer`: DEVICE memory, 8-byte aligned, at least CHUNK_ATTN_CLOCK_LOG_BYTES
+ * Measurement hook (not part of the method): the clock the three pipelined kernels (forward, dQ, dK/dV of head_dim 96
+ * and 128; forward and dQ of 64 where they run pipelined) actually run at.  `device_buffer`: DEVICE memory, 8-byte aligned, at least CHUNK_ATTN_CLOCK_LOG_BYTES
  * (else CHUNK_ATTN_WORKSPACE_TOO_SMALL; CHUNK_ATTN_INVALID_ARG if misaligned), owned by the caller and kept alive until
  * the hook is switched off with a null pointer.  While it is set, every workgroup of those kernels writes four 64-bit
  * values when it starts and when it has run out of work: section k of the buffer (k = 0 forward, 1 dQ, 2 dK/dV; 4096

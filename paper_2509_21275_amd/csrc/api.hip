@@ -123,7 +123,7 @@ struct StagingRing {
 };
 StagingRing g_ring;
 
-// log2 growth of a row's maximum past the first key tile's at which the head_dim 128 forward hands the row to its
+// log2 growth of a row's maximum past the first key tile's at which the pipelined forward hands the row to its
 // rescaling second pass: bf16 probabilities and fp32 sums hold 2^60 with room to spare
 std::atomic<float> g_fwd_rescale_limit{60.0f};
 
@@ -149,7 +149,7 @@ inline chunk_attn_desc widened(const chunk_attn_desc* d) {
 inline size_t padded_bytes(int64_t rows, int heads, size_t elem) { return align_up((size_t)rows * heads * kPaddedDim * elem); }
 
 // Forward workspace: [work items | transpose jobs | redo flags (zero)] (uploaded as one blob) then the
-// transposed V images or, for head_dim 128, the partial results of items whose walks are cut.
+// transposed V images (head_dim 256) or, for 96 and 128, the partial results of items whose walks are cut.
 struct FwdLayout {
   int tile_rows;
   bool pipe;       // the pipelined kernel runs (head_dim 96 and 128, and 64 from a number of blocks on)
@@ -164,9 +164,10 @@ struct FwdLayout {
 // Scratch memory of the forward that allocates nothing (chunk_attn_fwd_static), below.
 constexpr size_t kStaticScratchBytes = (size_t)16 << 20;
 
-// `may_cut`: false: no walk is cut whatever the chunk.  Partial results take the place of V images, which the pipelined
-// kernels do not need (the room for them stays part of the size), or up to the static forward's scratch memory where the
-// images would be smaller; the cut is a function of the chunk alone, so that every entry point gives the same bits.
+// `may_cut`: false: no walk is cut whatever the chunk.  Partial results take the place of V images, which only head_dim 256
+// makes (the room for them stays part of the other sizes, as callers may know them), or up to the static forward's scratch memory where
+// the images would be smaller.  The cut is a function of the chunk alone, so that both entry points give the same bits; a workspace
+// too small for it, which older sizes may be, runs uncut.
 void layout_fwd(const chunk_attn_desc* desc, FwdLayout& L, bool with_plan, bool may_cut = true) {
   const chunk_attn_desc wide = widened(desc), *d = &wide;
   const int group = d->num_q_heads / d->num_kv_heads;

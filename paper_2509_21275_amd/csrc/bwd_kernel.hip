@@ -2566,7 +2566,7 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
   float* dsp = reinterpret_cast<float*>(ws + P.dsp_off);
   hipError_t e;
 
-  // pre-pass: D, scaled LSE, transposed operand images
+  // pre-pass: D, scaled LSE
   {
     const int64_t blocks = (int64_t)P.qjobs.size() * d->num_q_heads;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;

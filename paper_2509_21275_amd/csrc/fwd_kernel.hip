@@ -21,11 +21,11 @@
 //                    reads in one burst behind the products and the rows of a full tile clamped like the last one's:
 //                    447 - 469 and 256.  168 registers, so that three workgroups share a CU: with two more, 64 sequences
 //                    of 256 took 83 us instead of 74.)
-//   fwd_pipe_kernel  head_dim 96 and 128, and 64 with two workgroups per CU: one wave per SIMD with 64 query rows, software pipelined over stages of 32
-//                    keys, reference maximum fixed by the first stage; rows whose scores outgrow it are
-//                    flagged and recomputed by fwd_kernel, launched right after.  Where a chunk has too few items for
-//                    the chip their walks are cut into pieces (plan.hpp); the pieces leave float32 partial results, which
-//                    the second pass puts together.
+//   fwd_pipe_kernel  head_dim 96 and 128, and 64 with two workgroups per CU: one wave per SIMD with 64 query rows, software
+//                    pipelined over stages of 32 keys, reference maximum fixed by the first stage; rows whose scores
+//                    outgrow it are flagged and recomputed by fwd_kernel, launched right after.  Where a chunk of 96 or
+//                    128 has too few items for the chip their walks are cut into pieces (plan.hpp); the pieces leave
+//                    float32 partial results, which the second pass puts together.
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -80,7 +80,6 @@ __device__ __forceinline__ void fwd_merge_parts(const FwdParams& p, const FwdIte
 template <int D, int WAVES>
 __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : D == 64 && WAVES == 4 ? 3 : 8 / WAVES) void fwd_kernel(FwdParams p) {
   constexpr int QB = 1;        // 32-row query blocks per wave
-  constexpr int NT = WAVES * 64;  // threads
   constexpr int BN = 64;       // key rows per LDS tile
   constexpr int KC = D / 8;    // 16-byte chunks per K row
   constexpr int DK = D / 16;   // k-steps of S^T = K Q^T

@@ -19,18 +19,18 @@ struct FwdParams {
   const __bf16* v;
   __bf16* o;
   float* lse;
-  const __bf16* vt;         // transposed V images [Hkv][total_kv_tiles][D][64]
+  const __bf16* vt;         // head_dim 256: transposed V images [Hkv][total_kv_tiles][D][64]
   const FwdItem* items;
-  const FwdItem* wholes;    // head_dim 128: the items before cutting (= items if none was cut)
-  bool cut;                 // some of the items are pieces
-  float* parts;             // head_dim 128: partial results of the pieces, kPartFloats per (slot, inner index)
+  const FwdItem* wholes;    // the items before cutting (= items if none was cut)
+  bool cut;                 // some of the items are pieces (head_dim 96 and 128)
+  float* parts;             // partial results of the pieces, kPartFloats per (slot, inner index)
   int64_t total_kv_tiles;
   int32_t num_q_heads, num_kv_heads, group;  // group = Hq / Hkv
   int32_t heads_per_wg;                      // query heads of one group handled by one workgroup (a power of two)
   int32_t head_splits;                       // group / heads_per_wg
   int32_t total_q;
   float scale_log2;                          // softmax scale * log2(e)
-  int32_t* redo;                             // head_dim 128: redo flag per (whole item, inner index)
+  int32_t* redo;                             // pipelined forward: redo flag per (whole item, inner index); else null
   float ref_limit;                           // log2 growth of the row maximum past the first tile's that raises the flag
   int32_t* taken;                            // 8 block-queue counters of the pipelined forward (zero before the launch)
   unsigned long long* clock_log;             // null, or where the pipelined forward's workgroups log their clocks
@@ -39,8 +39,8 @@ struct FwdParams {
 // rows of query tile per forward work item for a given head layout
 // Shape of a query-stationary workgroup (forward and dQ kernels): `waves` waves of 32 query rows each, spread
 // over as many query heads of one group as divide both (so that the key/value tiles they stream are shared).
-// forward: 4 waves; for head_dim 128 each wave owns two 32-row query blocks (fwd_pipe_kernel; its second pass,
-// fwd_kernel with 8 waves of one block, covers the same rows per workgroup)
+// forward: 4 waves; in the pipelined kernel each wave owns two 32-row query blocks (its second pass, fwd_kernel with 8 waves
+// of one block, covers the same rows per workgroup)
 // head dimensions that always run the software-pipelined kernels (64 does from a size on, pipe_pays)
 constexpr bool pipelined(int head_dim) { return head_dim == 96 || head_dim == 128; }
 inline int fwd_waves(int) { return 4; }
@@ -64,7 +64,7 @@ inline int persistent_grid(int64_t blocks, int per_cu = 1) {
 }
 constexpr int kBlockQueues = 8;  // counters per kernel that claims its blocks
 constexpr int kCus = 256;        // compute units of an MI355X (plans that must not depend on where they are made)
-// A partial result of one block (256 rows of head_dim 128, or fewer) in the order in which the kernels hold it: [8 units of 32
+// A partial result of one block (256 rows of head_dim 96 or 128, or fewer) in the order in which the kernels hold it: [8 units of 32
 // rows][up to 16 accumulator quarters][64 lanes][4] float32; for the forward then [8 units][32 rows] {reference maximum, sum}.
 constexpr int kPartRowFloats = 8 * 16 * 64 * 4;
 constexpr int kPartFloats = kPartRowFloats + 8 * 32 * 2;
@@ -107,7 +107,7 @@ struct BwdArgs {
 // [dQ items | dQ items that were cut | dK/dV items | dK/dV items that were cut | 64-row query-tile jobs] (one uploaded blob), then the
 // LSE and D arrays padded to 64-row tiles.
 struct BwdPlan {
-  KeySplit split;                // head_dim 128: how the dQ walks are cut
+  KeySplit split;                // head_dim 96 and 128: how the dQ walks are cut
   std::vector<DqItem> dq_items;  // with the pieces of walks that are cut
   std::vector<DqItem> dq_cut;    // the whole items that were cut
   KeySplit dkv_split;            // the same for the dK/dV walks
@@ -118,10 +118,11 @@ struct BwdPlan {
   size_t n_dq_cut = 0, n_dkv_cut = 0;
   size_t dq_items_off = 0, dq_cut_off = 0, dkv_items_off = 0, dkv_cut_off = 0, qjobs_off = 0, queues_off = 0, blob_bytes = 0;
   size_t lse2p_off = 0, dsp_off = 0, total = 0;
+  // (head_dim 96 and 128 always; dQ: 64 where pipe_pays, 256 never; dK/dV: 64 and 256 where dkv_pipe_pays)
+  bool dq_pipe = false, dkv_pipe = false;  // the pipelined kernels run
+  int dq_waves = 0;                        // 32-row units of a dQ workgroup
   // one-pass backward (head_dim 128): its items and workgroup order travel at the end of the blob; then the per-wave
   // progress counters and the status word (cleared by a kernel on every call) and the float32 dQ tiles
-  bool dq_pipe = false, dkv_pipe = false;  // the pipelined kernels run (head_dim 96 and 128 always, 256 never)
-  int dq_waves = 0;                        // 32-row units of a dQ workgroup
   bool fused = false;
   FusedPlan fplan;
   int64_t qt32_tiles = 0;

@@ -33,7 +33,7 @@ struct FwdItem {
   int32_t kv_row0;   // first key row of the segment (global)
   int32_t n0;        // keys visible to the tile's first row: C + i0 + 1; row r sees n0 + r
   int32_t kv_tile0;  // index of the transposed image of the segment's first 64-key tile
-  // head_dim 128, whose walks over the keys may be cut into pieces (choose_key_split):
+  // head_dim 96 and 128, whose walks over the keys may be cut into pieces (choose_key_split; 64 and 256: one piece each):
   int32_t keys;      // keys of the item's own range: it sees min(n0 + r, keys) of them
   int32_t whole;     // a piece: index of the whole item.  A whole item: number of its pieces (1: not cut)
   int32_t part;      // a piece: its slot among the partial results, -1 if it is the whole item.  A whole item: its first slot
@@ -45,11 +45,11 @@ struct DqItem {
   int32_t q_rows;    // valid rows in the tile (>= 1)
   int32_t kv_row0;   // first key row of the segment (global)
   int32_t n0;        // keys visible to the tile's first row
-  int32_t kv_tile0;  // index of the transposed image of the segment's first 32-key tile
+  int32_t kv_tile0;  // index of the segment's first 32-key tile (a whole item that was cut: the number of its pieces)
   int32_t q_slot0;   // slot of the tile's first row in the padded per-row arrays (LSE, D)
-  int32_t keys;      // head_dim 128: keys of the item's own range, as in FwdItem
-  int32_t part;      // head_dim 128: slot among the partial results, -1 if the item is not a piece (whole items that were cut:
-                     // the first slot; their number of pieces is in kv_tile0)
+  int32_t keys;      // head_dim 96 and 128: keys of the item's own range, as in FwdItem
+  int32_t part;      // head_dim 96 and 128: slot among the partial results, -1 if the item is not a piece (whole items that
+                     // were cut: the first slot)
 };
 
 // Work item of the dK/dV kernel: up to 128 consecutive key rows of one segment and the 32-row query tiles

@@ -56,8 +56,8 @@ def test_valid_descriptors(ca):
 
 
 def test_head_dimensions(ca):
-    """64, 96, 128 and 256 are accepted; 96 runs as 128 on zero-padded copies kept in the workspace, so its workspace
-    is that of 128 plus the copies (Q, K, V, O for the forward; Q, K, V, O, dO, dQ and float32-sized dK, dV for the
+    """64, 96, 128 and 256 are accepted; a workspace for 96 has the size of one for 128 plus zero-padded copies
+    of the tensors, which the one-pass backward runs on (Q, K, V, O for the forward; Q, K, V, O, dO, dQ and float32-sized dK, dV for the
     backward)."""
     segs = [(0, 300, 0, 500), (300, 212, 500, 212)]
     sizes = {}
