@@ -72,7 +72,7 @@ def cpu_baseline():
 def recorded_traffic():
     """HBM-side bytes per launch of the dominant kernel, as measured by the two rocprofv3 counter runs that are
     summarised under profiles/ (this script cannot run the profiler on itself).  None if no summary is there."""
-    path = os.path.join(ROOT, "profiles", "bwd_dkv_pipe_kernel_bench_workload_hbm_traffic.md")
+    path = os.path.join(ROOT, "profiles", "bwd_pipe_kernel_bench_workload_hbm_traffic.md")
     try:
         for line in open(path):
             if line.startswith("traffic_bytes_per_launch:"):
@@ -257,19 +257,19 @@ def main():
         ci = calls.index(c)
         fw, bw = call_ms[(ci, "fwd")], call_ms[(ci, "bwd")]
         per_call.append({"call": c["name"], "pairs_per_head": c["pairs"], "fwd_kernel_ms": round(f, 4),
-                         "bwd_dkv_kernel_ms": round(b, 4),
+                         "bwd_kernel_ms": round(b, 4),
                          "fwd_tflops": round(c["fwd_flops"] / f / 1e9, 1),
-                         "bwd_dkv_kernel_tflops": round(0.8 * c["bwd_flops"] / b / 1e9, 1),
+                         "bwd_kernel_tflops": round(c["bwd_flops"] / b / 1e9, 1),
                          "fwd_call_ms": round(fw, 4), "bwd_call_ms": round(bw, 4),
                          "fwd_bwd_tflops": round((c["fwd_flops"] + c["bwd_flops"]) / (fw + bw) / 1e9, 1)})
     evpool.close()
     bwd_flops = sum(c["bwd_flops"] for c in calls)
     fwd_flops = sum(c["fwd_flops"] for c in calls)
     n_launch = len(calls)
-    # The dominant kernel is the dK/dV kernel of the backward.  It computes four contractions per unmasked
-    # (query, key) pair and query head -- S, dP, dV, dK -- i.e. 8 * head_dim flops, 0.8 of the backward's 10 * head_dim.
-    dkv_flops = 0.8 * bwd_flops
-    achieved = dkv_flops / (bwd_k_ms * 1e-3) / 1e12
+    # The dominant kernel is the backward's: its dQ and dK/dV blocks are one launch.  Counted are the backward's five
+    # contractions, 10 * head_dim flops per unmasked (query, key) pair and query head (S and dP, computed for both kinds of
+    # block, once).
+    achieved = bwd_flops / (bwd_k_ms * 1e-3) / 1e12
 
     # the two workloads the target names, each by itself (whole calls, all kernels)
     def shape_row(names):
@@ -298,7 +298,7 @@ def main():
         "target": {"pct_of_bf16_mfma_peak": 50.0, "met": bool(value >= 0.5 * PEAK_BF16_TFLOPS)},
         "pct_of_measured_clock_peak": round(100.0 * value / measured_peak, 2),
         "per_shape": per_shape,
-        "roofline": {"kernel": "bwd_dkv_pipe_kernel<128>", "bound": "mfma", "achieved": round(achieved, 2),
+        "roofline": {"kernel": "bwd_pipe_kernel<128>", "bound": "mfma", "achieved": round(achieved, 2),
                      "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": round(achieved / PEAK_BF16_TFLOPS, 4),
                      "measured_clock_peak": round(measured_peak, 1),
                      "frac_of_measured_clock_peak": round(achieved / measured_peak, 4),
@@ -307,7 +307,7 @@ def main():
                                                       if kernel_clock_mhz["dkv"] else None),
                      "traffic": recorded_traffic(), "launches_per_step": n_launch,
                      "avg_launch_ms": round(bwd_k_ms / n_launch, 4),
-                     "flops_per_launch_avg": dkv_flops / n_launch,
+                     "flops_per_launch_avg": bwd_flops / n_launch,
                      "fwd_kernel": {"kernel": "fwd_pipe_kernel<128>", "achieved": round(fwd_flops / (fwd_k_ms * 1e-3) / 1e12, 2),
                                     "frac": round(fwd_flops / (fwd_k_ms * 1e-3) / 1e12 / PEAK_BF16_TFLOPS, 4),
                                     "avg_launch_ms": round(fwd_k_ms / n_launch, 4)}},

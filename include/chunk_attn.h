@@ -166,7 +166,7 @@ int64_t chunk_attn_pair_count(const chunk_attn_desc* desc);
  * Measurement hook (not part of the method): arms one pair of hipEvent_t (passed as void*) for the
  * calling thread.  The next chunk_attn_fwd or chunk_attn_bwd call on this thread records `start`
  * immediately before and `stop` immediately after its main kernel (the forward kernel, resp. the
- * dK/dV/dQ kernel of the backward) on that call's stream, then disarms.  Pass NULLs to disarm.
+ * dQ and dK/dV kernel of the backward, the dK/dV kernel alone for head_dim 64 and 256) on that call's stream, then disarms.  Pass NULLs to disarm.
  * The caller owns the events.  Always returns CHUNK_ATTN_OK.
  */
 int chunk_attn_profile_events(void* start_event, void* stop_event);
@@ -207,7 +207,7 @@ int chunk_attn_measure_mfma_rate_on(int milliseconds, int workgroups, void* scra
                                     double* tflops);
 
 /*
- * Measurement hook (not part of the method): the clock the three pipelined kernels (forward, dQ, dK/dV of head_dim 96
+ * Measurement hook (not part of the method): the clock the pipelined kernels (forward, and the dQ and dK/dV blocks of the backward, of head_dim 96
  * and 128; forward and dQ of 64 where they run pipelined) actually run at.  `device_buffer`: DEVICE memory, 8-byte aligned, at least CHUNK_ATTN_CLOCK_LOG_BYTES
  * (else CHUNK_ATTN_WORKSPACE_TOO_SMALL; CHUNK_ATTN_INVALID_ARG if misaligned), owned by the caller and kept alive until
  * the hook is switched off with a null pointer.  While it is set, every workgroup of those kernels writes four 64-bit

@@ -25,7 +25,7 @@
 // the accumulator's register order), which makes every load and store of the walk one contiguous kilobyte;
 // dq_convert_kernel turns the tiles into bf16 rows afterwards.
 //
-// Per step (stage n = n-th (head, query tile) of the walk) a wave runs, software pipelined as in bwd_dkv_pipe_kernel,
+// Per step (stage n = n-th (head, query tile) of the walk) a wave runs, software pipelined as in dkv_pipe_blocks (bwd_kernel.hip),
 //     role A:  S(g) = Q K^T           P(g-1) = exp2(S(g-1) c - LSE)       dV^T += dO^T P(g-2)
 //     role B:  dP(g-2) = dO V^T       dS(g-3) = P(g-3) (dP(g-3) - D)      dK^T += Q^T dS(g-4)    dS(g-4) -> LDS
 //     all:     dQ^T(g-5) = K^T dS^T(g-5)   (8 MFMAs on the wave's 32 rows of the head dimension), load the tile of g-5,
@@ -215,7 +215,7 @@ __global__ __launch_bounds__(256, 1) void bwd_fused_pipe_kernel(FusedParams p) {
   const int nqt = it.n_qt - it.qt_first;
   const int n_iter = nqt * G;  // stages: (query tile, head in group), the heads of a tile one after the other
 
-  // ---- staging of Q / dO / LSE / D, as in bwd_dkv_pipe_kernel ----
+  // ---- staging of Q / dO / LSE / D, as in dkv_pipe_blocks ----
   unsigned v_full[PER], v_last[PER];
   {
     const int last_row = it.q_len - 1 - (it.n_qt - 1) * BM;
@@ -262,7 +262,7 @@ __global__ __launch_bounds__(256, 1) void bwd_fused_pipe_kernel(FusedParams p) {
     d_slot = d_slot == (unsigned)((NS - 1) * QT) ? 0u : d_slot + (unsigned)QT;
   };
 
-  // ---- per-lane operand addresses (elements) inside a tile, as in bwd_dkv_pipe_kernel ----
+  // ---- per-lane operand addresses (elements) inside a tile, as in dkv_pipe_blocks ----
   int x_off[2];
 #pragma unroll
   for (int par = 0; par < 2; ++par) x_off[par] = cm_elem(l32, 2 * par + hh);

@@ -349,7 +349,7 @@ struct DkvParams {
   int32_t* taken;       // 8 block-queue counters of the pipelined kernel (zero before the launch)
   int32_t* ended;       // per queue, the blocks that have ended (zero before the launch)
   int32_t side_by_side; // blocks of a queue that run at the same time (DkvItem::in_step)
-  float* parts;         // partial results of pieces (bwd_dkv_pipe_kernel), kPartRowFloats per (slot, key/value head)
+  float* parts;         // partial results of pieces (dkv_pipe_blocks), kPartRowFloats per (slot, key/value head)
   unsigned long long* clock_log;  // null, or where the pipelined kernel's workgroups log their clocks
 };
 
@@ -658,7 +658,7 @@ __global__ __launch_bounds__(KB * 128, D > 128 ? 1 : 4 / KB) void bwd_dkv_kernel
   }
 }
 
-// LDS instructions of one step of bwd_dkv_pipe_kernel in program order, per wave role, and the waits that follow from
+// LDS instructions of one step of dkv_pipe_blocks in program order, per wave role, and the waits that follow from
 // it.  Mini-step m issues the read of fragment m + 4 (two instructions for a transposed fragment: the first NT of a step;
 // fragments past the end are the next step's first ones), then E0(m) instructions after its first MFMA and E1(m) after
 // its second: role A spreads its four hand-over stores and four row-value reads over mini-steps 0 .. 3 (issued in one go
@@ -699,7 +699,7 @@ static_assert(DkvLdsOrder<0, 16, 8>::wait(0) == 6 && DkvLdsOrder<0, 16, 8>::wait
               DkvLdsOrder<0, 16, 8>::wait(7) == 4 && DkvLdsOrder<0, 16, 8>::wait(8) == 3 && DkvLdsOrder<0, 16, 8>::wait(15) == 6, "role A");
 
 // ------------------------------------------------------------------------------------------------
-// bwd_dkv_pipe (head_dim 128 and 96)
+// dkv_pipe_blocks (head_dim 128 and 96): the dK/dV blocks of bwd_pipe_kernel
 //
 // Same work split as bwd_dkv_kernel, laid out for one wave per SIMD: a workgroup of 4 waves covers 128
 // keys; each wave owns 64 keys (two 32-key blocks), waves 0, 1 in role A (S, P, dV^T), waves 2, 3 in role B
@@ -728,7 +728,7 @@ static_assert(DkvLdsOrder<0, 16, 8>::wait(0) == 6 && DkvLdsOrder<0, 16, 8>::wait
 // ------------------------------------------------------------------------------------------------
 // (CUT: some items are pieces; see fwd_pipe_kernel)
 template <int D, bool CUT>
-__global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(DkvParams p, int num_blocks) {
+__device__ __forceinline__ void dkv_pipe_blocks(const DkvParams& p, const int num_blocks) {
   constexpr int NW = 4;        // waves
   constexpr int BM = 32;       // query rows per stage
   constexpr int KC = D / 8;    // 16-byte chunks per operand row
@@ -763,7 +763,9 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(DkvParams p, int n
   lds_f32* const dsum_s = lse_s + NS * RV;
   constexpr int LDS_ELEMS = R_OFF + 2 * NS * RV * 2;  // in bf16 units
 
-  const int tid = threadIdx.x, lane = tid & 63;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int role = wave >> 1, pair = wave & 1;
   const int l32 = lane & 31, hh = lane >> 5;
@@ -772,7 +774,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(DkvParams p, int n
   // (device_common.hpp) until none is left.  The next block is claimed before the current one's last few steps: early
   // enough for the answer to arrive by the time it is needed, and not earlier (that would fix the order of the blocks
   // before it is known which workgroup is free first).
-  __shared__ int next_block;
+  int* const next_block = (int*)((__bf16*)smem + LDS_ELEMS);
   const int xcd = xcd_of_this_wave();
   clock_log_stamp(p.clock_log, 0);
   int blk = 0;
@@ -784,7 +786,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(DkvParams p, int n
     blk = block_claim_finish(p.taken, num_blocks, xcd, block_claim_issue(p.taken, xcd));
     start_in_step(blk);
   }
-  blk = broadcast_from_wave0(&next_block, blk);
+  blk = broadcast_from_wave0(next_block, blk);
   while (blk >= 0) {
   int pending_claim = 0;
   const int kvh = blk % p.num_kv_heads;
@@ -1211,7 +1213,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(DkvParams p, int n
     nb = block_claim_finish(p.taken, num_blocks, xcd, pending_claim);
     start_in_step(nb);
   }
-  blk = broadcast_from_wave0(&next_block, nb);
+  blk = broadcast_from_wave0(next_block, nb);
   }
   clock_log_stamp(p.clock_log, 1);
 }
@@ -1222,7 +1224,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(DkvParams p, int n
 // With half the head dimension a wave has the registers for all four contractions of its 64 keys (K and V fragments, dK^T and
 // dV^T accumulators: 192 accumulation registers), so there are no wave roles and no hand-over: a workgroup is two waves,
 // 128 keys, two workgroups per CU, one wave per SIMD.  Stage n is the n-th (head, 32-row query tile) of the walk, as in
-// bwd_dkv_pipe_kernel; in step g a wave runs
+// dkv_pipe_blocks; in step g a wave runs
 //     dP(g) = dO V^T     dV^T += dO^T P(g-1)     dK^T += Q^T dS(g-1)     S(g+1) = Q K^T        (matrix pipe)
 //     P(g) = exp2(S(g) c - LSE)  and, once dP(g) is complete,  dS(g) = P(g) (dP(g) - D)         (vector)
 // as 16 mini-steps of one LDS operand fragment and the two MFMAs it feeds (one per 32-key block), each MFMA followed by its
@@ -1276,7 +1278,7 @@ __global__ __launch_bounds__(128, 1) void bwd_dkv_narrow_pipe_kernel(DkvParams p
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hh = lane >> 5;
 
-  // Persistent, as bwd_dkv_pipe_kernel, but no block waits for the groups before it (DkvItem::in_step is for head_dim 96 and
+  // Persistent, as dkv_pipe_blocks, but no block waits for the groups before it (DkvItem::in_step is for head_dim 96 and
   // 128).  Half the head dimension leaves too little to gain from the L2: with the waits and the counting of ended blocks the
   // backward of 1024 queries on 32768 keys, 32/8 heads, took 1139 us instead of 1041, of 64 sequences of 64, 8/8 heads, 57
   // instead of 38; 16384 queries on 65536 keys 23.7 ms instead of 23.4.
@@ -1306,7 +1308,7 @@ __global__ __launch_bounds__(128, 1) void bwd_dkv_narrow_pipe_kernel(DkvParams p
   const int nqt = it.n_qt - it.qt_first;
   const int n_iter = nqt * G;
 
-  // ---- staging (see bwd_dkv_pipe_kernel): copy i of a wave is piece (i % (PER / 2)) * 2 + wave of Q (i < PER / 2) or of dO ----
+  // ---- staging (see dkv_pipe_blocks): copy i of a wave is piece (i % (PER / 2)) * 2 + wave of Q (i < PER / 2) or of dO ----
   unsigned v_full[PER / 2], v_last[PER / 2];
   {
     const int last_row = it.q_len - 1 - (it.n_qt - 1) * BM;
@@ -1674,7 +1676,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_wide_pipe_kernel(DkvParams p, 
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hh = lane >> 5;
 
-  // Persistent, as bwd_dkv_pipe_kernel, but no block waits for the groups before it (DkvItem::in_step is for head_dim 96 and
+  // Persistent, as dkv_pipe_blocks, but no block waits for the groups before it (DkvItem::in_step is for head_dim 96 and
   // 128): that cost 1024 queries on 32768 keys, 32/8 heads, 3796 us of backward instead of 3684, gained nothing on 8192
   // (25.6 and 25.8 ms) and cost chunks of 64-token sequences a tenth.
   __shared__ int next_block;
@@ -2050,9 +2052,9 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_wide_pipe_kernel(DkvParams p, 
 }
 
 // ------------------------------------------------------------------------------------------------
-// bwd_dq_pipe (head_dim 128, 96 and, with long walks, 64)
+// dq_pipe_blocks: the dQ blocks of bwd_pipe_kernel (head_dim 128 and 96) and, with long walks, of head_dim 64
 //
-// The dQ kernel in the style of bwd_dkv_pipe_kernel: one wave per SIMD, a workgroup of 4 waves, each wave
+// dQ in the style of dkv_pipe_blocks: one wave per SIMD, a workgroup of 4 waves, each wave
 // owning two 32-row query blocks ("units": the workgroup's 8 units are the same (head, row block) pairs the
 // 8 waves of bwd_dq_kernel take), so that every K / V fragment read from LDS feeds two MFMAs.  Stage t is
 // the t-th 32-key tile of the segment; in step t a wave runs
@@ -2066,7 +2068,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_wide_pipe_kernel(DkvParams p, 
 // ------------------------------------------------------------------------------------------------
 // (CUT: some items are pieces; see fwd_pipe_kernel)
 template <int D, bool CUT>
-__global__ __launch_bounds__(256, 1) void bwd_dq_pipe_kernel(DqParams p, int num_blocks) {
+__device__ __forceinline__ void dq_pipe_blocks(const DqParams& p, const int num_blocks) {
   constexpr int NW = 4;        // waves
   constexpr int BN = 32;       // key rows per stage
   constexpr int KC = D / 8;    // 16-byte chunks per K / V row
@@ -2100,7 +2102,9 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_pipe_kernel(DqParams p, int num
   // the next block, between the last read of one block and the first write of the next.
   constexpr int ST_OFF = V_OFF + NS * KT;
 
-  const int tid = threadIdx.x, lane = tid & 63;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hh = lane >> 5;
   int* const next_block = (int*)((__bf16*)smem + ST_OFF);
@@ -2332,7 +2336,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_pipe_kernel(DqParams p, int num
       }
       const bf16x8 fa = fr[m % RING];
       // dP^T and S^T are kept in vector registers, the Q / dO fragments in accumulation registers (opaque MFMAs, see
-      // bwd_dkv_pipe_kernel); dP^T is first read three mini-steps after its last MFMA, S^T in the next step
+      // dkv_pipe_blocks); dP^T is first read three mini-steps after its last MFMA, S^T in the next step
       auto mma = [&](auto u_c) __attribute__((always_inline)) {
         constexpr int u = decltype(u_c)::value;
         const bf16x8& a_ = fa;  // (named references: variables used only inside an asm statement are not captured)
@@ -2459,6 +2463,45 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_pipe_kernel(DqParams p, int num
   }
   clock_log_stamp(p.clock_log, 1);
 }
+
+// ------------------------------------------------------------------------------------------------
+// bwd_pipe (head_dim 128 and 96): the dQ and the dK/dV blocks of a chunk in one launch
+//
+// The two kinds of block need nothing of each other, so a workgroup that finds no more blocks of one kind goes on to the other:
+// small chunks run both kinds side by side on compute units that one kind alone would leave idle, and no chunk ends twice.  The kind
+// with the longer walks goes first (`dq_phase`: the phase of dQ), so that long blocks do not start last.  Both kinds fill
+// the LDS and a wave's registers, whatever the order.  Forward and backward, two launches -> one: 557 causal tokens, 32/8 heads,
+// 123 -> 96 us; two slices of 3193 and 4999 queries (backwards only) 1886 -> 1801; long chunks are as fast either way (packed
+// 64K chunk, 8192 queries on 32768 keys: within 0.3 %).
+// The parameters of a phase are read when it starts, from the kernel arguments through a pointer the compiler cannot see
+// through: held by value for both phases they took 118 spilled scalar registers.
+// ------------------------------------------------------------------------------------------------
+struct BwdPipeParams {
+  DqParams dq;
+  DkvParams dkv;
+  int32_t dq_blocks, dkv_blocks, dq_phase;
+};
+template <int D, bool CUT>
+__global__ __launch_bounds__(256, 1) void bwd_pipe_kernel(BwdPipeParams) {
+  typedef const __attribute__((address_space(4))) BwdPipeParams* args_ptr;
+  for (int phase = 0; phase < 2; ++phase) {
+    if (phase > 0) wg_barrier();  // every wave has read that no block of the other kind is left: the LDS may be written again
+    args_ptr args = (args_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    if (phase == args->dq_phase) {
+      DqParams p;
+      __builtin_memcpy(&p, (const void*)&args->dq, sizeof(p));
+      dq_pipe_blocks<D, CUT>(p, args->dq_blocks);
+    } else {
+      DkvParams p;
+      __builtin_memcpy(&p, (const void*)&args->dkv, sizeof(p));
+      dkv_pipe_blocks<D, CUT>(p, args->dkv_blocks);
+    }
+  }
+}
+
+// head_dim 64, where dQ is pipelined
+__global__ __launch_bounds__(256, 1) void bwd_dq_pipe_kernel(DqParams p, int num_blocks) { dq_pipe_blocks<64, false>(p, num_blocks); }
 
 // dQ rows of the items whose walks were cut: the sum of their partial results, in the order of the pieces, times the
 // scale.  One workgroup per (whole item, inner index), each of its 8 waves one unit of 32 rows in the layout in which
@@ -2590,123 +2633,116 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
   if constexpr (D == 128) {
     if (P.fused) return launch_bwd_fused(d, a, P, lse2p, dsp, stream);
   }
-  {  // dQ
-    DqParams p;
-    p.q = a.q; p.k = a.k; p.v = a.v; p.d_o = a.d_o; p.lse2p = lse2p; p.dsp = dsp; p.dq = a.dq;
-    p.items = reinterpret_cast<const DqItem*>(ws + P.dq_items_off);
-    p.total_q_tiles = P.q_tiles;
-    p.num_q_heads = d->num_q_heads; p.num_kv_heads = d->num_kv_heads; p.group = group;
-    p.heads_per_wg = heads_per_wg(group, P.dq_waves); p.head_splits = group / p.heads_per_wg;
-    p.scale = d->softmax_scale; p.scale_log2 = d->softmax_scale * kLog2e;
-    p.parts = reinterpret_cast<float*>(ws + P.fdq_off);  // (the one-pass backward's dQ tiles: only one of the two runs)
-    p.taken = reinterpret_cast<int32_t*>(ws + P.queues_off);
-    p.clock_log = clock_log(1);
-    const int64_t blocks = (int64_t)P.dq_items.size() * d->num_kv_heads * p.head_splits;
-    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    if constexpr (D <= 128) {
-      if (P.dq_pipe) {
-        // ring slots of a K and a V tile, then the staging tiles of the four waves (64 rows each)
-        const size_t smem = (size_t)2 * (DQ_PIPE_DIST + 3) * 32 * D * 2 + (size_t)4 * 64 * D * 2;
-        if (P.n_dq_cut == 0) {
-          static const hipError_t attr = raise_smem_limit(&bwd_dq_pipe_kernel<D, false>, smem);
-          if (attr != hipSuccess) return attr;
-          hipLaunchKernelGGL((bwd_dq_pipe_kernel<D, false>), dim3((unsigned)persistent_grid(blocks)), dim3(256), smem, stream, p, (int)blocks);
-        }
-        if constexpr (pipelined(D)) {
-          if (P.n_dq_cut > 0) {
-            static const hipError_t attr = raise_smem_limit(&bwd_dq_pipe_kernel<D, true>, smem);
-            if (attr != hipSuccess) return attr;
-            hipLaunchKernelGGL((bwd_dq_pipe_kernel<D, true>), dim3((unsigned)persistent_grid(blocks)), dim3(256), smem, stream, p, (int)blocks);
-            if ((e = hipGetLastError()) != hipSuccess) return e;
-            hipLaunchKernelGGL((bwd_dq_merge_kernel<D>), dim3((unsigned)(P.n_dq_cut * d->num_kv_heads * p.head_splits)), dim3(512), 0,
-                               stream, p, reinterpret_cast<const DqItem*>(ws + P.dq_cut_off));
-          }
-        }
-      }
-    }
-    if constexpr (!pipelined(D)) {
-      if (!P.dq_pipe) {
-        const size_t smem = (size_t)6 * 32 * D * 2;  // 3 stages of K and V tiles
-        constexpr int DQW = 4;
-        static const hipError_t attr = raise_smem_limit(&bwd_dq_kernel<D, DQW>, smem);
-        if (attr != hipSuccess) return attr;
-        hipLaunchKernelGGL((bwd_dq_kernel<D, DQW>), dim3((unsigned)blocks), dim3(DQW * 64), smem, stream, p);
-      }
+  DqParams pq;
+  pq.q = a.q; pq.k = a.k; pq.v = a.v; pq.d_o = a.d_o; pq.lse2p = lse2p; pq.dsp = dsp; pq.dq = a.dq;
+  pq.items = reinterpret_cast<const DqItem*>(ws + P.dq_items_off);
+  pq.total_q_tiles = P.q_tiles;
+  pq.num_q_heads = d->num_q_heads; pq.num_kv_heads = d->num_kv_heads; pq.group = group;
+  pq.heads_per_wg = heads_per_wg(group, P.dq_waves); pq.head_splits = group / pq.heads_per_wg;
+  pq.scale = d->softmax_scale; pq.scale_log2 = d->softmax_scale * kLog2e;
+  pq.parts = reinterpret_cast<float*>(ws + P.dq_parts_off);
+  pq.taken = reinterpret_cast<int32_t*>(ws + P.queues_off);
+  pq.clock_log = clock_log(1);
+  const int64_t dq_blocks = (int64_t)P.dq_items.size() * d->num_kv_heads * pq.head_splits;
+  DkvParams pk;
+  pk.q = a.q; pk.k = a.k; pk.v = a.v; pk.d_o = a.d_o; pk.lse2p = lse2p; pk.dsp = dsp;
+  pk.dk = a.dk; pk.dv = a.dv;
+  pk.items = reinterpret_cast<const DkvItem*>(ws + P.dkv_items_off);
+  pk.total_q_tiles = P.q_tiles;
+  pk.num_q_heads = d->num_q_heads; pk.num_kv_heads = d->num_kv_heads; pk.group = group;
+  pk.scale = d->softmax_scale; pk.scale_log2 = d->softmax_scale * kLog2e;
+  pk.accumulate = a.accumulate ? 1 : 0;
+  pk.out_f32 = a.dkv_f32 ? 1 : 0;
+  pk.taken = reinterpret_cast<int32_t*>(ws + P.queues_off) + kBlockQueues;
+  pk.ended = pk.taken + kBlockQueues;
+  pk.parts = reinterpret_cast<float*>(ws + P.fdq_off);
+  pk.side_by_side = std::max(1, persistent_grid(0x7fffffff, dkv_per_cu(D)) / kBlockQueues);
+  pk.clock_log = clock_log(2);
+  static_assert(DKV_KEYS == 128, "the head_dim 64 and 128 kernels cover 128 keys per workgroup");
+  const int64_t dkv_blocks = (int64_t)P.dkv_items.size() * d->num_kv_heads;
+  if (dq_blocks > 0x7fffffff || dkv_blocks > 0x7fffffff) return hipErrorInvalidValue;
+  ProfileEvents pe = profile_events();
+  profile_events() = ProfileEvents{};
+
+  if constexpr (pipelined(D)) {
+    // dQ: ring slots of a K and a V tile, then the staging tiles of the four waves (64 rows each).  dK/dV: ring slots of two 32-row
+    // operand tiles, 2 P hand-over slots, one slot of LSE and D rows per ring slot, the word that announces the next block
+    constexpr int NS = DKV_PIPE_DIST + 5;
+    constexpr size_t dq_smem = (size_t)2 * (DQ_PIPE_DIST + 3) * 32 * D * 2 + (size_t)4 * 64 * D * 2;
+    constexpr size_t dkv_smem = (size_t)2 * NS * 32 * D * 2 + 2 * 4096 * 2 + 2 * NS * 64 * sizeof(float) + 16;
+    constexpr size_t smem = dq_smem > dkv_smem ? dq_smem : dkv_smem;
+    BwdPipeParams p;
+    p.dq = pq;
+    p.dkv = pk;
+    p.dq_blocks = (int)dq_blocks;
+    p.dkv_blocks = (int)dkv_blocks;
+    p.dq_phase = P.dq_first ? 0 : 1;
+    const dim3 grid((unsigned)persistent_grid(dq_blocks + dkv_blocks));
+    if (pe.start && (e = hipEventRecord(pe.start, stream)) != hipSuccess) return e;
+    if (P.n_dq_cut == 0 && P.n_dkv_cut == 0) {
+      static const hipError_t attr = raise_smem_limit(&bwd_pipe_kernel<D, false>, smem);
+      if (attr != hipSuccess) return attr;
+      hipLaunchKernelGGL((bwd_pipe_kernel<D, false>), grid, dim3(256), smem, stream, p);
+    } else {
+      static const hipError_t attr = raise_smem_limit(&bwd_pipe_kernel<D, true>, smem);
+      if (attr != hipSuccess) return attr;
+      hipLaunchKernelGGL((bwd_pipe_kernel<D, true>), grid, dim3(256), smem, stream, p);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  {  // dK, dV
-    DkvParams p;
-    p.q = a.q; p.k = a.k; p.v = a.v; p.d_o = a.d_o; p.lse2p = lse2p; p.dsp = dsp;
-    p.dk = a.dk; p.dv = a.dv;
-    p.items = reinterpret_cast<const DkvItem*>(ws + P.dkv_items_off);
-    p.total_q_tiles = P.q_tiles;
-    p.num_q_heads = d->num_q_heads; p.num_kv_heads = d->num_kv_heads; p.group = group;
-    p.scale = d->softmax_scale; p.scale_log2 = d->softmax_scale * kLog2e;
-    p.accumulate = a.accumulate ? 1 : 0;
-    p.out_f32 = a.dkv_f32 ? 1 : 0;
-    p.taken = reinterpret_cast<int32_t*>(ws + P.queues_off) + kBlockQueues;
-    p.ended = p.taken + kBlockQueues;
-    p.parts = reinterpret_cast<float*>(ws + P.fdq_off);  // (as for dQ, whose partial results have been put together by then)
-    p.side_by_side = std::max(1, persistent_grid(0x7fffffff, dkv_per_cu(D)) / kBlockQueues);
-    p.clock_log = clock_log(2);
-    static_assert(DKV_KEYS == 128, "the head_dim 64 and 128 kernels cover 128 keys per workgroup");
-    const int64_t blocks = (int64_t)P.dkv_items.size() * d->num_kv_heads;
-    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    ProfileEvents pe = profile_events();
-    profile_events() = ProfileEvents{};
-    if constexpr (pipelined(D)) {
-      // ring slots of two 32-row operand tiles, 2 P hand-over slots, one slot of LSE and D rows per ring slot
-      constexpr int NS = DKV_PIPE_DIST + 5;
-      const size_t smem = (size_t)2 * NS * 32 * D * 2 + 2 * 4096 * 2 + 2 * NS * 64 * sizeof(float);
-      if (pe.start && (e = hipEventRecord(pe.start, stream)) != hipSuccess) return e;
-      if (P.n_dkv_cut == 0) {
-        static const hipError_t attr = raise_smem_limit(&bwd_dkv_pipe_kernel<D, false>, smem);
-        if (attr != hipSuccess) return attr;
-        hipLaunchKernelGGL((bwd_dkv_pipe_kernel<D, false>), dim3((unsigned)persistent_grid(blocks)), dim3(256), smem, stream, p, (int)blocks);
-      } else {
-        static const hipError_t attr = raise_smem_limit(&bwd_dkv_pipe_kernel<D, true>, smem);
-        if (attr != hipSuccess) return attr;
-        hipLaunchKernelGGL((bwd_dkv_pipe_kernel<D, true>), dim3((unsigned)persistent_grid(blocks)), dim3(256), smem, stream, p, (int)blocks);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        hipLaunchKernelGGL((bwd_dkv_merge_kernel<D>), dim3((unsigned)(P.n_dkv_cut * d->num_kv_heads)), dim3(512), 0, stream, p,
-                           reinterpret_cast<const DkvItem*>(ws + P.dkv_cut_off));
-      }
+    if (P.n_dq_cut > 0)
+      hipLaunchKernelGGL((bwd_dq_merge_kernel<D>), dim3((unsigned)(P.n_dq_cut * d->num_kv_heads * pq.head_splits)), dim3(512), 0,
+                         stream, pq, reinterpret_cast<const DqItem*>(ws + P.dq_cut_off));
+    if (P.n_dkv_cut > 0)
+      hipLaunchKernelGGL((bwd_dkv_merge_kernel<D>), dim3((unsigned)(P.n_dkv_cut * d->num_kv_heads)), dim3(512), 0, stream, pk,
+                         reinterpret_cast<const DkvItem*>(ws + P.dkv_cut_off));
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  } else {
+    if (D == 64 && P.dq_pipe) {
+      const size_t smem = (size_t)2 * (DQ_PIPE_DIST + 3) * 32 * D * 2 + (size_t)4 * 64 * D * 2;
+      static const hipError_t attr = raise_smem_limit(&bwd_dq_pipe_kernel, smem);
+      if (attr != hipSuccess) return attr;
+      hipLaunchKernelGGL(bwd_dq_pipe_kernel, dim3((unsigned)persistent_grid(dq_blocks)), dim3(256), smem, stream, pq, (int)dq_blocks);
     } else {
-      if constexpr (D == 64) {
-        if (P.dkv_pipe) {
-          // 6 ring slots of two 32-row operand tiles and their LSE and D rows
-          const size_t smem = (size_t)2 * 6 * 32 * D * 2 + 2 * 6 * 64 * sizeof(float);
-          static const hipError_t attr = raise_smem_limit(&bwd_dkv_narrow_pipe_kernel<D>, smem);
-          if (attr != hipSuccess) return attr;
-          if (pe.start && (e = hipEventRecord(pe.start, stream)) != hipSuccess) return e;
-          hipLaunchKernelGGL((bwd_dkv_narrow_pipe_kernel<D>), dim3((unsigned)persistent_grid(blocks, dkv_per_cu(D))), dim3(128), smem, stream, p,
-                             (int)blocks);
-        }
-      }
-      if constexpr (D == 256) {
-        if (P.dkv_pipe) {
-          // 5 + 4 ring slots of 32-row Q and dO tiles with their LSE and D rows, a P and a dS hand-over slot
-          const size_t smem = (size_t)9 * 32 * D * 2 + 2 * 2048 * 2 + 9 * 64 * sizeof(float);
-          static const hipError_t attr = raise_smem_limit(&bwd_dkv_wide_pipe_kernel<D>, smem);
-          if (attr != hipSuccess) return attr;
-          if (pe.start && (e = hipEventRecord(pe.start, stream)) != hipSuccess) return e;
-          hipLaunchKernelGGL((bwd_dkv_wide_pipe_kernel<D>), dim3((unsigned)persistent_grid(blocks)), dim3(256), smem, stream, p, (int)blocks);
-        }
-      }
-      if (!P.dkv_pipe) {
-        // 4 ring slots of two 32-row operand tiles, 2 P hand-over slots, 4 slots of LSE and D rows
-        constexpr int KB = (D > 128 ? 64 : DKV_KEYS) / 32;   // as dkv_keys(D)
-        const size_t smem = (size_t)8 * 32 * D * 2 + 2 * KB * 1024 * 2 + 2 * 4 * 64 * sizeof(float);
-        static const hipError_t attr = raise_smem_limit(&bwd_dkv_kernel<D, KB>, smem);
+      const size_t smem = (size_t)6 * 32 * D * 2;  // 3 stages of K and V tiles
+      constexpr int DQW = 4;
+      static const hipError_t attr = raise_smem_limit(&bwd_dq_kernel<D, DQW>, smem);
+      if (attr != hipSuccess) return attr;
+      hipLaunchKernelGGL((bwd_dq_kernel<D, DQW>), dim3((unsigned)dq_blocks), dim3(DQW * 64), smem, stream, pq);
+    }
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if constexpr (D == 64) {
+      if (P.dkv_pipe) {
+        // 6 ring slots of two 32-row operand tiles and their LSE and D rows
+        const size_t smem = (size_t)2 * 6 * 32 * D * 2 + 2 * 6 * 64 * sizeof(float);
+        static const hipError_t attr = raise_smem_limit(&bwd_dkv_narrow_pipe_kernel<D>, smem);
         if (attr != hipSuccess) return attr;
         if (pe.start && (e = hipEventRecord(pe.start, stream)) != hipSuccess) return e;
-        hipLaunchKernelGGL((bwd_dkv_kernel<D, KB>), dim3((unsigned)blocks), dim3(KB * 128), smem, stream, p);
+        hipLaunchKernelGGL((bwd_dkv_narrow_pipe_kernel<D>), dim3((unsigned)persistent_grid(dkv_blocks, dkv_per_cu(D))), dim3(128), smem, stream, pk,
+                           (int)dkv_blocks);
       }
     }
+    if constexpr (D == 256) {
+      if (P.dkv_pipe) {
+        // 5 + 4 ring slots of 32-row Q and dO tiles with their LSE and D rows, a P and a dS hand-over slot
+        const size_t smem = (size_t)9 * 32 * D * 2 + 2 * 2048 * 2 + 9 * 64 * sizeof(float);
+        static const hipError_t attr = raise_smem_limit(&bwd_dkv_wide_pipe_kernel<D>, smem);
+        if (attr != hipSuccess) return attr;
+        if (pe.start && (e = hipEventRecord(pe.start, stream)) != hipSuccess) return e;
+        hipLaunchKernelGGL((bwd_dkv_wide_pipe_kernel<D>), dim3((unsigned)persistent_grid(dkv_blocks)), dim3(256), smem, stream, pk, (int)dkv_blocks);
+      }
+    }
+    if (!P.dkv_pipe) {
+      // 4 ring slots of two 32-row operand tiles, 2 P hand-over slots, 4 slots of LSE and D rows
+      constexpr int KB = (D > 128 ? 64 : DKV_KEYS) / 32;   // as dkv_keys(D)
+      const size_t smem = (size_t)8 * 32 * D * 2 + 2 * KB * 1024 * 2 + 2 * 4 * 64 * sizeof(float);
+      static const hipError_t attr = raise_smem_limit(&bwd_dkv_kernel<D, KB>, smem);
+      if (attr != hipSuccess) return attr;
+      if (pe.start && (e = hipEventRecord(pe.start, stream)) != hipSuccess) return e;
+      hipLaunchKernelGGL((bwd_dkv_kernel<D, KB>), dim3((unsigned)dkv_blocks), dim3(KB * 128), smem, stream, pk);
+    }
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (pe.stop && (e = hipEventRecord(pe.stop, stream)) != hipSuccess) return e;
   }
+  if (pe.stop && (e = hipEventRecord(pe.stop, stream)) != hipSuccess) return e;
   return hipSuccess;
 }
 
@@ -2780,7 +2816,11 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, bool may_c
   P.dsp_off = P.lse2p_off + up256(row_slots * sizeof(float));
   // (256 bytes remain: the dK/dV kernels copy the LSE / D rows 64 at a time, up to 32 past a segment's last)
   P.fdq_off = P.dsp_off + up256(row_slots * sizeof(float)) + 256;
-  P.total = P.fdq_off + dq_tile_bytes;
+  // partial results of cut walks: those of dK/dV, then those of dQ (both kinds of block run in one launch)
+  P.dq_parts_off = P.fdq_off + up256((size_t)P.dkv_split.parts * d->num_kv_heads * kPartRowFloats * sizeof(float));
+  const size_t dq_part_bytes = P.split.parts > 0 ? (size_t)P.split.parts * d->num_kv_heads * (group / heads_per_wg(group, P.dq_waves)) * kPartRowFloats * sizeof(float) : 0;
+  P.total = std::max(P.fdq_off + dq_tile_bytes, P.dq_parts_off + dq_part_bytes);
+  P.dq_first = count_walks(d, dq_rows).longest > count_dkv_walks(d, dkv_keys(d->head_dim)).longest;
 }
 
 std::vector<char> bwd_blob(const BwdPlan& P) {
