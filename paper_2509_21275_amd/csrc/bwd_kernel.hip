@@ -1176,7 +1176,7 @@ __device__ __forceinline__ void dkv_pipe_blocks(const DkvParams& p, const int nu
     __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
 
     // ---- epilogue: dV = dV^T (role A), dK = scale * dK^T (role B), written (or added) as bf16 ----
-    if (CUT && it.part >= 0) {  // a piece: the accumulators as they are, put together by bwd_dkv_merge_kernel
+    if (CUT && it.part >= 0) {  // a piece: the accumulators as they are, put together by bwd_merge_kernel
       float* const out = p.parts + ((int64_t)it.part * p.num_kv_heads + kvh) * kPartRowFloats + (4 * ROLE + 2 * pair) * 4096 + lane * 4;
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
@@ -2425,7 +2425,7 @@ __device__ __forceinline__ void dq_pipe_blocks(const DqParams& p, const int num_
   int lane_e = lane;
   asm volatile("" : "+v"(lane_e));
   const int l32_e = lane_e & 31, hh_e = lane_e >> 5;
-  if (CUT && it.part >= 0) {  // a piece: dQ^T as it is, put together by bwd_dq_merge_kernel
+  if (CUT && it.part >= 0) {  // a piece: dQ^T as it is, put together by bwd_merge_kernel
     float* const out = p.parts + ((int64_t)it.part * inner_n + inner) * kPartRowFloats + wave * (2 * 4096) + lane_e * 4;
 #pragma unroll
     for (int u = 0; u < 2; ++u)
@@ -2503,61 +2503,64 @@ __global__ __launch_bounds__(256, 1) void bwd_pipe_kernel(BwdPipeParams) {
 // head_dim 64, where dQ is pipelined
 __global__ __launch_bounds__(256, 1) void bwd_dq_pipe_kernel(DqParams p, int num_blocks) { dq_pipe_blocks<64, false>(p, num_blocks); }
 
-// dQ rows of the items whose walks were cut: the sum of their partial results, in the order of the pieces, times the
-// scale.  One workgroup per (whole item, inner index), each of its 8 waves one unit of 32 rows in the layout in which
-// the pipelined kernel held it.  Bound by the reads of the partial results (128 KB per block and piece).
+// Puts the pieces of cut walks together: dQ rows = scale x the sum of their partial results in the order of the pieces, dK and dV
+// rows likewise.  A workgroup takes one unit of 32 rows of a whole item (the layout in which the pipelined kernel held it), each of
+// its 4 waves a quarter of the accumulator; first the dQ units, then the dK/dV units.  Bound by the latency of reading the partial
+// results (128 KB per block and piece, most of it written on another XCD).  A workgroup per whole block, its 8 waves a unit
+// each, and a launch per kind took 8 - 26 us each: 557 causal tokens, 32/8 heads, 10.3 us, now 5.0; 918 queries on 4182 keys,
+// 8/2 heads, 11.8 (dQ) and 26 (dK/dV), now 12.6 together.
 template <int D>
-__global__ __launch_bounds__(512) void bwd_dq_merge_kernel(DqParams p, const DqItem* __restrict__ cut) {
-  constexpr int NQ = D / 8;  // accumulator quarters
+__global__ __launch_bounds__(256) void bwd_merge_kernel(DqParams pq, const DqItem* __restrict__ dq_cut, int dq_units, DkvParams pk,
+                                                        const DkvItem* __restrict__ dkv_cut) {
+  constexpr int NQ = D / 8 / 4;  // accumulator quarters per wave
   const int lane = threadIdx.x & 63, l32 = lane & 31, hh = lane >> 5;
-  const int unit = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int inner_n = p.num_kv_heads * p.head_splits, inner = blockIdx.x % inner_n;
-  const DqItem it = cut[blockIdx.x / inner_n];
-  const int kvh = inner % p.num_kv_heads, hs = inner / p.num_kv_heads;
-  const int head = kvh * p.group + hs * p.heads_per_wg + unit % p.heads_per_wg;
-  const int r = (unit / p.heads_per_wg) * 32 + l32;
-  if (r >= it.q_rows) return;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool is_dq = (int)blockIdx.x < dq_units;
+  const int x = is_dq ? blockIdx.x : blockIdx.x - dq_units;
+  const int unit = x & 7, block = x >> 3;
+  const int inner_n = is_dq ? pq.num_kv_heads * pq.head_splits : pk.num_kv_heads, inner = block % inner_n;
+  int part, pieces, row, rows, head = 0;
+  int64_t row0;
+  if (is_dq) {
+    const DqItem it = dq_cut[block / inner_n];
+    part = it.part;
+    pieces = it.kv_tile0;
+    head = inner % pq.num_kv_heads * pq.group + inner / pq.num_kv_heads * pq.heads_per_wg + unit % pq.heads_per_wg;
+    row = (unit / pq.heads_per_wg) * 32 + l32;
+    rows = it.q_rows;
+    row0 = it.q_row0;
+  } else {
+    const DkvItem it = dkv_cut[block / inner_n];
+    part = it.part;
+    pieces = it.in_step;
+    row = (unit & 3) * 32 + l32;
+    rows = it.kv_rows;
+    row0 = it.kv_row0;
+  }
+  if (row >= rows) return;
   const int64_t step = (int64_t)inner_n * kPartRowFloats;
-  const float* src = p.parts + (int64_t)it.part * step + (int64_t)inner * kPartRowFloats + unit * 4096 + lane * 4;
+  const float* src = (is_dq ? pq.parts : pk.parts) + part * step + (int64_t)inner * kPartRowFloats + unit * 4096 + wave * (NQ * 256) + lane * 4;
   f32x4 s[NQ];
 #pragma unroll
   for (int i = 0; i < NQ; ++i) s[i] = *reinterpret_cast<const f32x4*>(src + i * 256);
-  for (int k = 1; k < it.kv_tile0; ++k) {  // kv_tile0: number of pieces
-    src += step;
+#pragma unroll 4
+  for (int k = 1; k < pieces; ++k) {
 #pragma unroll
-    for (int i = 0; i < NQ; ++i) s[i] += *reinterpret_cast<const f32x4*>(src + i * 256);
+    for (int i = 0; i < NQ; ++i) s[i] += *reinterpret_cast<const f32x4*>(src + k * step + i * 256);
   }
-  __bf16* op = p.dq + (int64_t)(it.q_row0 + r) * p.num_q_heads * D + (int64_t)head * D + 4 * hh;
+  const int col = wave * (NQ * 8) + 4 * hh;
+  if (is_dq) {
+    __bf16* op = pq.dq + ((row0 + row) * pq.num_q_heads + head) * D + col;
 #pragma unroll
-  for (int i = 0; i < NQ; ++i)
-    *reinterpret_cast<bf16x4*>(op + 8 * i) = pack4(s[i][0] * p.scale, s[i][1] * p.scale, s[i][2] * p.scale, s[i][3] * p.scale);
-}
-
-// The same for the dK and dV rows of key blocks whose walks were cut (in_step: number of pieces).
-template <int D>
-__global__ __launch_bounds__(512) void bwd_dkv_merge_kernel(DkvParams p, const DkvItem* __restrict__ cut) {
-  constexpr int NQ = D / 8;  // accumulator quarters
-  const int lane = threadIdx.x & 63, l32 = lane & 31, hh = lane >> 5;
-  const int unit = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int kvh = blockIdx.x % p.num_kv_heads;
-  const DkvItem it = cut[blockIdx.x / p.num_kv_heads];
-  const int kr = (unit & 3) * 32 + l32;
-  if (kr >= it.kv_rows) return;
-  const int64_t step = (int64_t)p.num_kv_heads * kPartRowFloats;
-  const float* src = p.parts + (int64_t)it.part * step + (int64_t)kvh * kPartRowFloats + unit * 4096 + lane * 4;
-  f32x4 s[NQ];
+    for (int i = 0; i < NQ; ++i)
+      *reinterpret_cast<bf16x4*>(op + 8 * i) = pack4(s[i][0] * pq.scale, s[i][1] * pq.scale, s[i][2] * pq.scale, s[i][3] * pq.scale);
+  } else {
+    __bf16* const out = unit < 4 ? pk.dv : pk.dk;
+    const float f = unit < 4 ? 1.0f : pk.scale;
+    const int64_t off = ((row0 + row) * pk.num_kv_heads + inner) * D + col;
 #pragma unroll
-  for (int i = 0; i < NQ; ++i) s[i] = *reinterpret_cast<const f32x4*>(src + i * 256);
-  for (int k = 1; k < it.in_step; ++k) {
-    src += step;
-#pragma unroll
-    for (int i = 0; i < NQ; ++i) s[i] += *reinterpret_cast<const f32x4*>(src + i * 256);
+    for (int i = 0; i < NQ; ++i) dkv_store4(pk, out, off + 8 * i, s[i][0] * f, s[i][1] * f, s[i][2] * f, s[i][3] * f);
   }
-  __bf16* const out = unit < 4 ? p.dv : p.dk;
-  const float f = unit < 4 ? 1.0f : p.scale;
-  const int64_t off = ((int64_t)it.kv_row0 + kr) * p.num_kv_heads * D + (int64_t)kvh * D + 4 * hh;
-#pragma unroll
-  for (int i = 0; i < NQ; ++i) dkv_store4(p, out, off + 8 * i, s[i][0] * f, s[i][1] * f, s[i][2] * f, s[i][3] * f);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -2689,11 +2692,10 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
       hipLaunchKernelGGL((bwd_pipe_kernel<D, true>), grid, dim3(256), smem, stream, p);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (P.n_dq_cut > 0)
-      hipLaunchKernelGGL((bwd_dq_merge_kernel<D>), dim3((unsigned)(P.n_dq_cut * d->num_kv_heads * pq.head_splits)), dim3(512), 0,
-                         stream, pq, reinterpret_cast<const DqItem*>(ws + P.dq_cut_off));
-    if (P.n_dkv_cut > 0)
-      hipLaunchKernelGGL((bwd_dkv_merge_kernel<D>), dim3((unsigned)(P.n_dkv_cut * d->num_kv_heads)), dim3(512), 0, stream, pk,
+    const int64_t dq_units = 8 * (int64_t)P.n_dq_cut * d->num_kv_heads * pq.head_splits, dkv_units = 8 * (int64_t)P.n_dkv_cut * d->num_kv_heads;
+    if (dq_units + dkv_units > 0)  // (cut chunks have few blocks: choose_key_split, choose_tile_split)
+      hipLaunchKernelGGL((bwd_merge_kernel<D>), dim3((unsigned)(dq_units + dkv_units)), dim3(256), 0, stream, pq,
+                         reinterpret_cast<const DqItem*>(ws + P.dq_cut_off), (int)dq_units, pk,
                          reinterpret_cast<const DkvItem*>(ws + P.dkv_cut_off));
     if ((e = hipGetLastError()) != hipSuccess) return e;
   } else {
@@ -2785,6 +2787,10 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, bool may_c
       if (P.dkv_split.target > 0) P.dkv_items = cut_items(P.dkv_items, P.dkv_split.target, &P.dkv_cut);
     }
     P.qjobs = tile_jobs(d, false, 64, nullptr);
+    int dq_longest = 0, dkv_longest = 0;
+    for (const DqItem& it : P.dq_items) dq_longest = std::max(dq_longest, (std::min(it.n0 + it.q_rows - 1, it.keys) + kStageKeys - 1) / kStageKeys);
+    for (const DkvItem& it : P.dkv_items) dkv_longest = std::max(dkv_longest, (it.n_qt - it.qt_first) * group);
+    P.dq_first = dq_longest > dkv_longest;
   }
   // the layout does not depend on which backward runs: item and piece counts follow from the segment table
   for (int t = 0; t < d->num_segments; ++t) {
@@ -2820,7 +2826,6 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, bool may_c
   P.dq_parts_off = P.fdq_off + up256((size_t)P.dkv_split.parts * d->num_kv_heads * kPartRowFloats * sizeof(float));
   const size_t dq_part_bytes = P.split.parts > 0 ? (size_t)P.split.parts * d->num_kv_heads * (group / heads_per_wg(group, P.dq_waves)) * kPartRowFloats * sizeof(float) : 0;
   P.total = std::max(P.fdq_off + dq_tile_bytes, P.dq_parts_off + dq_part_bytes);
-  P.dq_first = count_walks(d, dq_rows).longest > count_dkv_walks(d, dkv_keys(d->head_dim)).longest;
 }
 
 std::vector<char> bwd_blob(const BwdPlan& P) {
