@@ -112,8 +112,8 @@ int chunk_attn_fwd(const chunk_attn_desc* desc, const void* q, const void* k, co
  * chunk_attn_fwd for callers that cannot allocate device memory or pass a workspace: code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same inputs, outputs and
  * results as chunk_attn_fwd; the call allocates nothing, on the host side of the runtime or the
- * device (no hipMalloc / hipFree / pinned buffers: the schedule is built by a small kernel from the
- * segment table, which travels as a kernel argument).  Its scratch memory is a fixed array of
+ * device (no hipMalloc / hipFree / pinned buffers: a short schedule travels as a kernel argument, a longer one is
+ * built by a small kernel from the segment table, which does).  Its scratch memory is a fixed array of
  * 16 MiB inside the library, one copy per GPU, held until the process ends.
  * Limits: at most 64 segments, and a forward scratch need (chunk_attn_workspace_bytes' *fwd_bytes:
  * the schedule plus room for one transposed copy of V) of at most 16 MiB, else CHUNK_ATTN_TOO_LARGE and
@@ -181,10 +181,9 @@ int chunk_attn_shutdown(void);
 
 /*
  * Test hook (not part of the method): the pipelined forward (head_dim 96 and 128, and 64 for large chunks) keeps the softmax reference
- * maximum of a row fixed after its first key tile and recomputes, in a second pass with a moving
- * maximum, the rows whose later scores exceed it by more than 2^log2_growth (default 60; any
- * reference gives the same softmax).  A very negative value sends every row through the second
- * pass.  Process-wide.  Always returns CHUNK_ATTN_OK.
+ * maximum of a row fixed after its first key tile and takes a block again, with the maximum over
+ * all its keys, if the later scores of a row exceed it by more than 2^log2_growth (default 60; any
+ * reference gives the same softmax).  A very negative value makes every block be taken twice.  Process-wide.  Always returns CHUNK_ATTN_OK.
  */
 int chunk_attn_test_set_fwd_rescale_limit(float log2_growth);
 
@@ -242,7 +241,7 @@ int chunk_attn_test_bwd_status_offset(const chunk_attn_desc* desc, size_t* offse
  * Test hook: which kernels chunk_attn_fwd and chunk_attn_bwd choose for `desc` (given workspaces of the reported sizes), as
  * a sum of the bits below.  Decided on the host from the descriptor alone (and, for the last bit, the backward mode).
  */
-#define CHUNK_ATTN_ROUTE_FWD_PIPELINED 1 /* software-pipelined forward and its second pass */
+#define CHUNK_ATTN_ROUTE_FWD_PIPELINED 1 /* software-pipelined forward */
 #define CHUNK_ATTN_ROUTE_FWD_CUT 2       /* some of its walks over the keys are cut into pieces */
 #define CHUNK_ATTN_ROUTE_DQ_PIPELINED 4
 #define CHUNK_ATTN_ROUTE_DQ_CUT 8

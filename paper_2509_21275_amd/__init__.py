@@ -201,7 +201,7 @@ def chunk_attn_shutdown() -> None:
 
 
 def chunk_attn_test_set_fwd_rescale_limit(log2_growth: float) -> None:
-    """Test hook: growth of a row's maximum (log2) past which the pipelined forward takes its second pass."""
+    """Test hook: growth of a row's maximum (log2) past which the pipelined forward takes a block again."""
     _lib.chunk_attn_test_set_fwd_rescale_limit(ctypes.c_float(log2_growth))
 
 

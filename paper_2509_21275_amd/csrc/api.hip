@@ -26,6 +26,20 @@ int hip_fail(hipError_t e, const char* what) {
   return CHUNK_ATTN_HIP_ERROR;
 }
 
+// Schedules reach the device as kernel arguments where they are small (the forward's items with the forward itself, the backward's
+// blob with its pre-pass, a forward blob with a launch of its own), else through pinned staging buffers.
+struct InlineBlob {
+  uint4 data[kInlineBlob / 16];
+};
+__global__ __launch_bounds__(256) void upload_inline_kernel(InlineBlob blob, uint4* dst, int n16) {
+  if ((int)threadIdx.x < n16) dst[threadIdx.x] = blob.data[threadIdx.x];
+}
+static_assert(kInlineBlob <= 256 * 16, "one workgroup copies it");
+__global__ __launch_bounds__(256) void upload_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst, int n16) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n16) dst[i] = src[i];
+}
+
 // Pinned staging buffers for the schedule uploads.  A buffer is reused only after the copy that read it has
 // completed; while the GPU is still busy with earlier calls the pool grows (up to kMaxBytes) instead of making the
 // caller wait, so that the host can plan and enqueue ahead of the GPU.  Buffers come in power-of-two sizes and are
@@ -43,7 +57,9 @@ struct StagingRing {
   size_t next = 0, total = 0;
   std::mutex mu;
 
-  // Copies `bytes` from src into pinned memory and enqueues the upload to `dst` on `stream`.
+  // Copies `bytes` (a multiple of 16) from src into pinned memory and enqueues the upload to `dst` on `stream`: a small kernel that reads
+  // the pinned memory, which takes 3 us where the runtime's copy takes 4 (by a kernel, and 5 until the next one starts) to 20
+  // (by a copy engine, from 16 KB on).
   hipError_t upload(void* dst, const void* src, size_t bytes, hipStream_t stream) {
     std::lock_guard<std::mutex> lock(mu);
     hipError_t e;
@@ -70,7 +86,7 @@ struct StagingRing {
     }
     if (!s && total + want <= kMaxBytes) {  // grow
       Slot n;
-      if ((e = hipHostMalloc(&n.host, want, hipHostMallocDefault)) != hipSuccess) return e;
+      if ((e = hipHostMalloc(&n.host, want, hipHostMallocPortable | hipHostMallocMapped)) != hipSuccess) return e;
       n.cap = want;
       if ((e = hipEventCreateWithFlags(&n.ev, hipEventDisableTiming)) != hipSuccess) return e;
       total += want;
@@ -93,13 +109,18 @@ struct StagingRing {
         total -= s->cap;
         s->host = nullptr;
         s->cap = 0;
-        if ((e = hipHostMalloc(&s->host, want, hipHostMallocDefault)) != hipSuccess) return e;
+        if ((e = hipHostMalloc(&s->host, want, hipHostMallocPortable | hipHostMallocMapped)) != hipSuccess) return e;
         s->cap = want;
         total += want;
       }
     }
     std::memcpy(s->host, src, bytes);
-    if ((e = hipMemcpyAsync(dst, s->host, bytes, hipMemcpyHostToDevice, stream)) != hipSuccess) return e;
+    void* from = nullptr;
+    if ((e = hipHostGetDevicePointer(&from, s->host, 0)) != hipSuccess) return e;
+    const int n16 = (int)(bytes / 16);
+    hipLaunchKernelGGL(upload_kernel, dim3((unsigned)((n16 + 255) / 256)), dim3(256), 0, stream, static_cast<const uint4*>(from),
+                       static_cast<uint4*>(dst), n16);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = hipEventRecord(s->ev, stream)) != hipSuccess) return e;
     s->in_flight = true;
     return hipSuccess;
@@ -123,8 +144,16 @@ struct StagingRing {
 };
 StagingRing g_ring;
 
-// log2 growth of a row's maximum past the first key tile's at which the pipelined forward hands the row to its
-// rescaling second pass: bf16 probabilities and fp32 sums hold 2^60 with room to spare
+hipError_t upload_schedule(void* dst, const std::vector<char>& blob, hipStream_t stream) {
+  if (blob.size() > kInlineBlob) return g_ring.upload(dst, blob.data(), blob.size(), stream);
+  InlineBlob a;
+  std::memcpy(a.data, blob.data(), blob.size());
+  hipLaunchKernelGGL(upload_inline_kernel, dim3(1), dim3(256), 0, stream, a, static_cast<uint4*>(dst), (int)(blob.size() / 16));
+  return hipGetLastError();
+}
+
+// log2 growth of a row's maximum past the first key tile's at which the pipelined forward takes the row's block again with
+// the true maximum: bf16 probabilities and fp32 sums hold 2^60 with room to spare
 std::atomic<float> g_fwd_rescale_limit{60.0f};
 
 std::atomic<int> g_bwd_mode{0};
@@ -148,21 +177,31 @@ inline chunk_attn_desc widened(const chunk_attn_desc* d) {
 }
 inline size_t padded_bytes(int64_t rows, int heads, size_t elem) { return align_up((size_t)rows * heads * kPaddedDim * elem); }
 
-// Forward workspace: [work items | transpose jobs | redo flags (zero)] (uploaded as one blob) then the
-// transposed V images (head_dim 256) or, for 96 and 128, the partial results of items whose walks are cut.
+// Forward workspace: [work items | whole items that were cut | transpose jobs | block-queue counters (zero)] (uploaded as one blob, unless
+// the kernel arguments carry the items) then the transposed V images (head_dim 256) or, for 96 and 128, the partial results of items
+// whose walks are cut.
 struct FwdLayout {
   int tile_rows;
   bool pipe;       // the pipelined kernel runs (head_dim 96 and 128, and 64 from a number of blocks on)
   KeySplit split;  // pipelined kernel: how the walks are cut
-  size_t n_items, n_wholes, wholes_off, jobs_off, flags_off, blob_bytes, vt_off, total;
-  int64_t blocks, whole_blocks;
+  size_t n_items, n_wholes, wholes_off, jobs_off, queues_off, blob_bytes, vt_off, total;
+  int64_t blocks;
   int64_t kv_tiles;
-  std::vector<FwdItem> items, wholes;
+  std::vector<FwdItem> items, cut;  // what runs, and the whole items that were cut
   std::vector<TileJob> jobs;
 };
 
 // Scratch memory of the forward that allocates nothing (chunk_attn_fwd_static), below.
 constexpr size_t kStaticScratchBytes = (size_t)16 << 20;
+
+// The lists of a layout whose sizes are known.
+void fill_fwd_lists(const chunk_attn_desc* d, FwdLayout& L) {
+  std::vector<FwdItem> wholes = plan_fwd(d, L.tile_rows);
+  L.items = cut_items(wholes, L.split.target);
+  for (const FwdItem& w : wholes)
+    if (w.part >= 0) L.cut.push_back(w);
+  if (d->head_dim > 128) L.jobs = tile_jobs(d, true, 64, nullptr);
+}
 
 // `may_cut`: false: no walk is cut whatever the chunk.  Partial results take the place of V images, which only head_dim 256
 // makes (the room for them stays part of the other sizes, as callers may know them), or up to the static forward's scratch memory where
@@ -182,16 +221,15 @@ void layout_fwd(const chunk_attn_desc* desc, FwdLayout& L, bool with_plan, bool 
   L.n_wholes = (size_t)walks.items;
   L.kv_tiles = count_tiles(d, true, 64);
   const size_t image_bytes = align_up((size_t)L.kv_tiles * d->num_kv_heads * d->head_dim * 64 * sizeof(__bf16));
-  L.whole_blocks = (int64_t)L.n_wholes * inner;
   const size_t part_bytes = (size_t)inner * kPartFloats * sizeof(float);
   // the fixed part of a layout with n items to run: [items | whole items, if any was cut | V tile jobs, if V images are
-  // made | a redo flag per whole block and the block-queue counters of the pipelined kernel (all zero)]
+  // made | the block-queue counters of the pipelined kernel (zero)]
   auto place = [&](size_t n_items) {
     L.n_items = n_items;
-    L.wholes_off = n_items == L.n_wholes ? 0 : align_up(n_items * sizeof(FwdItem));
-    L.jobs_off = align_up(L.wholes_off + L.n_wholes * sizeof(FwdItem));
-    L.flags_off = align_up(L.jobs_off + (d->head_dim <= 128 ? 0 : (size_t)L.kv_tiles * sizeof(TileJob)));
-    L.blob_bytes = L.flags_off + ((size_t)L.whole_blocks + kBlockQueues) * sizeof(int32_t);
+    L.wholes_off = n_items * sizeof(FwdItem);
+    L.jobs_off = L.wholes_off + (n_items == L.n_wholes ? 0 : L.n_wholes * sizeof(FwdItem));
+    L.queues_off = L.jobs_off + (d->head_dim <= 128 ? 0 : (size_t)L.kv_tiles * sizeof(TileJob));
+    L.blob_bytes = L.queues_off + kBlockQueues * sizeof(int32_t);
     L.vt_off = align_up(L.blob_bytes);
   };
   L.split = KeySplit{};
@@ -214,10 +252,7 @@ void layout_fwd(const chunk_attn_desc* desc, FwdLayout& L, bool with_plan, bool 
   L.total = std::max(uncut_total, L.vt_off + align_up((size_t)L.split.parts * part_bytes));
   if (is_narrow(desc))  // (as much as with padded copies of Q, K, V and O)
     L.total = std::max(L.total, uncut_total + 2 * padded_bytes(d->total_q, d->num_q_heads, 2) + 2 * padded_bytes(d->total_kv, d->num_kv_heads, 2));
-  if (!with_plan) return;
-  L.wholes = plan_fwd(d, L.tile_rows);
-  L.items = cut_items(L.wholes, L.split.target);
-  if (d->head_dim > 128) L.jobs = tile_jobs(d, true, 64, nullptr);
+  if (with_plan) fill_fwd_lists(desc, L);
 }
 
 // ---- the forward that allocates nothing (chunk_attn_fwd_static) ----
@@ -246,13 +281,14 @@ hipError_t static_scratch(char** out) {
 }
 
 // The forward's schedule made on the device from a segment table passed by value: work items in segment order (their
-// order does not change any result) and the pieces of those that are cut, the 64-row tiles of V, and the redo flags cleared.
+// order does not change any result) and the pieces of those that are cut, the 64-row tiles of V, and the block-queue counters cleared.
+// (Short lists of items travel as kernel arguments of the forward itself instead: fwd_inline.)
 struct StaticSegs {
   chunk_attn_seg seg[kStaticMaxSegments];
 };
 __global__ __launch_bounds__(256) void plan_fwd_static_kernel(StaticSegs segs, int n_seg, int tile_rows, FwdItem* wholes,
                                                               int n_wholes, FwdItem* items, int target, TileJob* jobs,
-                                                              int n_jobs, int32_t* flags, int n_flags) {
+                                                              int n_jobs, int32_t* queues) {
   __shared__ int item0[kStaticMaxSegments + 1], job0[kStaticMaxSegments + 1];
   __shared__ int wave_items[4], wave_parts[4];
   if (threadIdx.x == 0) {
@@ -286,7 +322,6 @@ __global__ __launch_bounds__(256) void plan_fwd_static_kernel(StaticSegs segs, i
       it.kv_tile0 = job0[t];
       it.keys = s.kv_len;
       if (target <= 0) {  // nothing is cut: no pieces to number
-        it.whole = x;
         it.part = -1;
         items[x] = it;
       } else {
@@ -325,7 +360,6 @@ __global__ __launch_bounds__(256) void plan_fwd_static_kernel(StaticSegs segs, i
       p.kv_row0 += b;
       p.n0 -= b;
       p.keys = (k + 1 < n ? piece_begin(stages, n, k + 1) * kStageKeys : it.keys) - b;
-      p.whole = x;
       p.part = n > 1 ? part + k : -1;
       items[item + k] = p;
     }
@@ -342,7 +376,7 @@ __global__ __launch_bounds__(256) void plan_fwd_static_kernel(StaticSegs segs, i
     const int r = (x - job0[t]) * 64;
     jobs[x] = TileJob{s.kv_start + r, min(64, s.kv_len - r), x, 0};
   }
-  for (int x = threadIdx.x; x < n_flags; x += 256) flags[x] = 0;
+  if (threadIdx.x < kBlockQueues) queues[threadIdx.x] = 0;
 }
 
 // dst[row][0 .. out_chunks) = src[row][0 .. in_chunks) followed by zero chunks
@@ -404,6 +438,51 @@ NarrowBwdLayout narrow_bwd_layout(const chunk_attn_desc* d, size_t inner_bytes) 
   return N;
 }
 
+// Whether the forward's kernel arguments carry its items: there is room for them, and no block is claimed through a counter in device
+// memory, which would have to be cleared first (head_dim 256 also needs its list of V tiles there).  Saves the launch that
+// would bring them, 3 us and as much of host time.  Forward and backward of 557 causal tokens, 32/8 heads, without any upload by the
+// runtime, with workgroups that find their block without a counter, and without the forward's second launch: 92 -> 73 us; 439
+// tokens, 8/2 heads, 87 -> 68; the static forward of 1501 + 203 keys next to 611 short rows 41 -> 30 us.
+bool fwd_inline(const FwdLayout& L, int head_dim) {
+  return head_dim <= 128 && L.n_items <= (size_t)kInlineItems && (!L.pipe || L.blocks <= persistent_grid(L.blocks, fwd_per_cu(head_dim)));
+}
+
+// Parameters and lists of a forward whose scratch memory is `ws`.
+FwdParams fwd_params(const chunk_attn_desc* desc, const FwdLayout& L, char* ws, bool items_inline, const void* q, const void* k, const void* v,
+                     void* o, float* lse) {
+  FwdParams p;
+  p.q = static_cast<const __bf16*>(q);
+  p.k = static_cast<const __bf16*>(k);
+  p.v = static_cast<const __bf16*>(v);
+  p.o = static_cast<__bf16*>(o);
+  p.lse = lse;
+  p.vt = reinterpret_cast<const __bf16*>(ws + L.vt_off);
+  p.items = items_inline ? nullptr : reinterpret_cast<const FwdItem*>(ws);
+  p.wholes = items_inline ? nullptr : reinterpret_cast<const FwdItem*>(ws + L.wholes_off);
+  p.parts = reinterpret_cast<float*>(ws + L.vt_off);
+  p.total_kv_tiles = L.kv_tiles;
+  p.num_q_heads = desc->num_q_heads;
+  p.num_kv_heads = desc->num_kv_heads;
+  p.group = desc->num_q_heads / desc->num_kv_heads;
+  p.heads_per_wg = heads_per_wg(p.group, fwd_waves(desc->head_dim));
+  p.head_splits = p.group / p.heads_per_wg;
+  p.total_q = desc->total_q;
+  p.scale_log2 = desc->softmax_scale * 1.4426950408889634f;
+  p.taken = reinterpret_cast<int32_t*>(ws + L.queues_off);
+  p.clock_log = clock_log(0);
+  p.ref_limit = g_fwd_rescale_limit.load();
+  return p;
+}
+FwdLists fwd_lists(const FwdLayout& L) {
+  FwdLists l;
+  l.num_blocks = (int)L.blocks;
+  l.num_items = (int)L.n_items;
+  l.num_wholes = (int)L.cut.size();
+  l.num_vjobs = (int)L.jobs.size();
+  l.items = L.items.data();
+  l.wholes = L.cut.data();
+  return l;
+}
 }  // namespace
 
 namespace chunk_attn {
@@ -538,49 +617,28 @@ int chunk_attn_fwd(const chunk_attn_desc* desc, const void* q, const void* k, co
     return CHUNK_ATTN_INVALID_ARG;  // the kernels move rows in 16-byte pieces
   FwdLayout L;
   layout_fwd(desc, L, true);
-  if (workspace_bytes < L.total) layout_fwd(desc, L, true, false);  // too small for partial results: nothing is cut
+  if (workspace_bytes < L.total) {  // too small for partial results: nothing is cut
+    L = FwdLayout{};
+    layout_fwd(desc, L, true, false);
+  }
   if (workspace_bytes < L.total) return CHUNK_ATTN_WORKSPACE_TOO_SMALL;
+  if (L.blocks > 0x7fffffff) return CHUNK_ATTN_UNSUPPORTED;
   hipStream_t stream = static_cast<hipStream_t>(stream_v);
   char* ws = static_cast<char*>(workspace);
-
-  std::vector<char> blob(L.blob_bytes, 0);
-  std::memcpy(blob.data() + L.wholes_off, L.wholes.data(), L.wholes.size() * sizeof(FwdItem));
-  std::memcpy(blob.data(), L.items.data(), L.items.size() * sizeof(FwdItem));
-  std::memcpy(blob.data() + L.jobs_off, L.jobs.data(), L.jobs.size() * sizeof(TileJob));
-  hipError_t e = g_ring.upload(ws, blob.data(), blob.size(), stream);
-  if (e != hipSuccess) return hip_fail(e, "schedule upload");
-  __bf16* vt = reinterpret_cast<__bf16*>(ws + L.vt_off);
-
-  FwdParams p;
-  p.q = static_cast<const __bf16*>(q);
-  p.k = static_cast<const __bf16*>(k);
-  p.v = static_cast<const __bf16*>(v);
-  p.o = static_cast<__bf16*>(o);
-  p.lse = lse;
-  p.vt = vt;
-  p.items = reinterpret_cast<const FwdItem*>(ws);
-  p.wholes = reinterpret_cast<const FwdItem*>(ws + L.wholes_off);
-  p.cut = L.split.target > 0;
-  p.parts = reinterpret_cast<float*>(ws + L.vt_off);
-  p.total_kv_tiles = L.kv_tiles;
-  p.num_q_heads = desc->num_q_heads;
-  p.num_kv_heads = desc->num_kv_heads;
-  p.group = desc->num_q_heads / desc->num_kv_heads;
-  p.heads_per_wg = heads_per_wg(p.group, fwd_waves(desc->head_dim));
-  p.head_splits = p.group / p.heads_per_wg;
-  p.total_q = desc->total_q;
-  p.scale_log2 = desc->softmax_scale * 1.4426950408889634f;
-  p.redo = L.pipe ? reinterpret_cast<int32_t*>(ws + L.flags_off) : nullptr;
-  p.taken = reinterpret_cast<int32_t*>(ws + L.flags_off) + L.whole_blocks;
-  p.clock_log = clock_log(0);
-  p.ref_limit = g_fwd_rescale_limit.load();
-  const int64_t blocks = L.blocks;
-  if (blocks > 0x7fffffff) return CHUNK_ATTN_UNSUPPORTED;
+  const bool items_inline = fwd_inline(L, desc->head_dim);
+  hipError_t e;
+  if (!items_inline) {
+    std::vector<char> blob(L.blob_bytes, 0);
+    std::memcpy(blob.data(), L.items.data(), L.items.size() * sizeof(FwdItem));
+    std::memcpy(blob.data() + L.wholes_off, L.cut.data(), L.cut.size() * sizeof(FwdItem));
+    std::memcpy(blob.data() + L.jobs_off, L.jobs.data(), L.jobs.size() * sizeof(TileJob));
+    if ((e = upload_schedule(ws, blob, stream)) != hipSuccess) return hip_fail(e, "schedule upload");
+  }
+  const FwdParams p = fwd_params(desc, L, ws, items_inline, q, k, v, o, lse);
   ProfileEvents pe = profile_events();
   profile_events() = ProfileEvents{};
   if (pe.start && (e = hipEventRecord(pe.start, stream)) != hipSuccess) return hip_fail(e, "event record");
-  e = launch_fwd(p, desc->head_dim, L.pipe, (int)blocks, (int)L.whole_blocks, reinterpret_cast<const TileJob*>(ws + L.jobs_off),
-                 (int)L.jobs.size(), stream);
+  e = launch_fwd(p, desc->head_dim, L.pipe, fwd_lists(L), reinterpret_cast<const TileJob*>(ws + L.jobs_off), stream);
   if (e != hipSuccess) return hip_fail(e, "forward launch");
   if (pe.stop && (e = hipEventRecord(pe.stop, stream)) != hipSuccess) return hip_fail(e, "event record");
   return CHUNK_ATTN_OK;
@@ -601,39 +659,22 @@ int chunk_attn_fwd_static(const chunk_attn_desc* desc, const void* q, const void
   char* ws = nullptr;
   hipError_t e = static_scratch(&ws);
   if (e != hipSuccess) return hip_fail(e, "address of the static scratch buffer");
-  StaticSegs segs;
-  for (int t = 0; t < desc->num_segments; ++t) segs.seg[t] = desc->segments[t];
-  hipLaunchKernelGGL(plan_fwd_static_kernel, dim3(1), dim3(256), 0, stream, segs, desc->num_segments, L.tile_rows,
-                     reinterpret_cast<FwdItem*>(ws + L.wholes_off), (int)L.n_wholes, reinterpret_cast<FwdItem*>(ws),
-                     L.split.target, reinterpret_cast<TileJob*>(ws + L.jobs_off), desc->head_dim <= 128 ? 0 : (int)L.kv_tiles,
-                     reinterpret_cast<int32_t*>(ws + L.flags_off), (int)L.whole_blocks + kBlockQueues);
-  if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "schedule kernel launch");
-
-  FwdParams p;
-  p.q = static_cast<const __bf16*>(q);
-  p.k = static_cast<const __bf16*>(k);
-  p.v = static_cast<const __bf16*>(v);
-  p.o = static_cast<__bf16*>(o);
-  p.lse = lse;
-  p.vt = reinterpret_cast<__bf16*>(ws + L.vt_off);
-  p.items = reinterpret_cast<const FwdItem*>(ws);
-  p.wholes = reinterpret_cast<const FwdItem*>(ws + L.wholes_off);
-  p.cut = L.split.target > 0;
-  p.parts = reinterpret_cast<float*>(ws + L.vt_off);
-  p.total_kv_tiles = L.kv_tiles;
-  p.num_q_heads = desc->num_q_heads;
-  p.num_kv_heads = desc->num_kv_heads;
-  p.group = desc->num_q_heads / desc->num_kv_heads;
-  p.heads_per_wg = heads_per_wg(p.group, fwd_waves(desc->head_dim));
-  p.head_splits = p.group / p.heads_per_wg;
-  p.total_q = desc->total_q;
-  p.scale_log2 = desc->softmax_scale * 1.4426950408889634f;
-  p.redo = L.pipe ? reinterpret_cast<int32_t*>(ws + L.flags_off) : nullptr;
-  p.taken = reinterpret_cast<int32_t*>(ws + L.flags_off) + L.whole_blocks;
-  p.clock_log = clock_log(0);
-  p.ref_limit = g_fwd_rescale_limit.load();
-  e = launch_fwd(p, desc->head_dim, L.pipe, (int)L.blocks, (int)L.whole_blocks, reinterpret_cast<const TileJob*>(ws + L.jobs_off),
-                 (int)L.kv_tiles, stream);
+  const bool items_inline = fwd_inline(L, desc->head_dim);
+  if (items_inline) fill_fwd_lists(desc, L);
+  const FwdParams p = fwd_params(desc, L, ws, items_inline, q, k, v, o, lse);
+  FwdLists lists = fwd_lists(L);
+  if (!items_inline) {
+    lists.num_wholes = L.split.target > 0 ? (int)L.n_wholes : 0;  // (with those that were not cut among them)
+    lists.num_vjobs = desc->head_dim <= 128 ? 0 : (int)L.kv_tiles;
+    StaticSegs segs;
+    for (int t = 0; t < desc->num_segments; ++t) segs.seg[t] = desc->segments[t];
+    hipLaunchKernelGGL(plan_fwd_static_kernel, dim3(1), dim3(256), 0, stream, segs, desc->num_segments, L.tile_rows,
+                       reinterpret_cast<FwdItem*>(ws + L.wholes_off), (int)L.n_wholes, reinterpret_cast<FwdItem*>(ws),
+                       L.split.target, reinterpret_cast<TileJob*>(ws + L.jobs_off), lists.num_vjobs,
+                       reinterpret_cast<int32_t*>(ws + L.queues_off));
+    if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "schedule kernel launch");
+  }
+  e = launch_fwd(p, desc->head_dim, L.pipe, lists, reinterpret_cast<const TileJob*>(ws + L.jobs_off), stream);
   if (e != hipSuccess) return hip_fail(e, "forward launch");
   return CHUNK_ATTN_OK;
 }
@@ -694,9 +735,10 @@ int bwd_any(const chunk_attn_desc* desc, const void* q, const void* k, const voi
   a.dkv_f32 = dkv_f32;
   a.workspace = static_cast<char*>(workspace);
   const std::vector<char> blob = bwd_blob(P);
-  hipError_t e = g_ring.upload(a.workspace, blob.data(), blob.size(), stream);
-  if (e != hipSuccess) return hip_fail(e, "schedule upload");
-  e = launch_bwd(desc, a, P, stream);
+  hipError_t e = hipSuccess;
+  if (blob.size() > kInlineBlob && (e = g_ring.upload(a.workspace, blob.data(), blob.size(), stream)) != hipSuccess)
+    return hip_fail(e, "schedule upload");
+  e = launch_bwd(desc, a, P, blob, stream);  // (its pre-pass brings a smaller one along)
   if (e != hipSuccess) return hip_fail(e, "backward launch");
   return CHUNK_ATTN_OK;
 }

@@ -37,16 +37,39 @@ constexpr float kLog2e = 1.4426950408889634f;
 // ------------------------------------------------------------------------------------------------
 // bwd_pre: one workgroup per (64-row query tile, head); D / 8 threads per row (head_dim 96: 16, of which 12 read), one
 // 16-byte chunk of O and of dO each, so that a wave reads whole rows (the kernel is bound by memory: it reads O and dO once).
+// Its arguments may carry the call's schedule, which the first workgroup then copies into the workspace for the kernels behind it.
 // ------------------------------------------------------------------------------------------------
+struct BwdPreArgs {
+  const __bf16 *o, *d_o;
+  const float* lse;
+  const TileJob* jobs;  // null: in the blob
+  float *lse2p, *dsp;
+  int64_t total_q_tiles;
+  int32_t total_q, num_q_heads;
+  u32x4* blob_dst;
+  int32_t blob_n16, jobs_off;  // the blob's size in units of 16 bytes (0: it is not here) and the place of the jobs in it
+  u32x4 blob[kInlineBlob / 16];
+};
 template <int D>
-__global__ __launch_bounds__(256) void bwd_pre_kernel(const __bf16* __restrict__ o, const __bf16* __restrict__ d_o,
-                                                      const float* __restrict__ lse, const TileJob* __restrict__ jobs,
-                                                      int64_t total_q_tiles, int total_q, int num_q_heads,
-                                                      float* __restrict__ lse2p, float* __restrict__ dsp) {
+__global__ __launch_bounds__(256) void bwd_pre_kernel(BwdPreArgs) {
+  typedef const __attribute__((address_space(4))) BwdPreArgs* args_ptr;
+  typedef const __attribute__((address_space(4))) TileJob* job_ptr;
+  const args_ptr args = (args_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+  const __bf16* const o = args->o;
+  const __bf16* const d_o = args->d_o;
+  const float* const lse = args->lse;
+  float* const lse2p = args->lse2p;
+  float* const dsp = args->dsp;
+  const int64_t total_q_tiles = args->total_q_tiles;
+  const int total_q = args->total_q, num_q_heads = args->num_q_heads;
+  if (blockIdx.x == 0 && (int)threadIdx.x < args->blob_n16) args->blob_dst[threadIdx.x] = args->blob[threadIdx.x];
   constexpr int TPR = D == 96 ? 16 : D / 8;  // threads per row
   constexpr int RPP = 256 / TPR;     // rows per pass
   const int head = blockIdx.x % num_q_heads;
-  const TileJob job = jobs[blockIdx.x / num_q_heads];
+  const job_ptr jobs = args->jobs != nullptr ? (job_ptr)(uintptr_t)args->jobs
+                                             : (job_ptr)((const __attribute__((address_space(4))) char*)args->blob + args->jobs_off);
+  TileJob job;
+  __builtin_memcpy(&job, (const void*)(jobs + blockIdx.x / num_q_heads), sizeof(job));
   const int part = threadIdx.x % TPR;
 #pragma unroll
   for (int pass = 0; pass < 64 / RPP; ++pass) {
@@ -90,6 +113,7 @@ struct DqParams {
   float scale, scale_log2;
   float* parts;          // partial results of pieces (pipelined kernel), kPartRowFloats per (slot, inner index)
   int32_t* taken;        // 8 block-queue counters of the pipelined kernel (zero before the launch)
+  int32_t num_blocks;
   unsigned long long* clock_log;  // null, or where the pipelined kernel's workgroups log their clocks
 };
 
@@ -351,6 +375,7 @@ struct DkvParams {
   int32_t side_by_side; // blocks of a queue that run at the same time (DkvItem::in_step)
   float* parts;         // partial results of pieces (dkv_pipe_blocks), kPartRowFloats per (slot, key/value head)
   unsigned long long* clock_log;  // null, or where the pipelined kernel's workgroups log their clocks
+  int32_t num_blocks;
 };
 
 // Four consecutive elements of a dK / dV row: stored, or added to what is there, as bf16 or as fp32.
@@ -727,8 +752,27 @@ static_assert(DkvLdsOrder<0, 16, 8>::wait(0) == 6 && DkvLdsOrder<0, 16, 8>::wait
 // MFMAs are written as opaque instructions.
 // ------------------------------------------------------------------------------------------------
 // (CUT: some items are pieces; see fwd_pipe_kernel)
+// Kernel arguments read anew, through a pointer the compiler cannot see through, wherever a block needs them: held in scalar registers for
+// the length of a kernel they push out values that the steps use (one v_readlane per use).
+template <class P>
+__device__ __forceinline__ P fresh(const __attribute__((address_space(4))) P* args) {
+  asm volatile("" : "+s"(args));
+  P p;
+  __builtin_memcpy(&p, (const void*)args, sizeof(p));
+  return p;
+}
+// Element x (the same for all lanes) of a list that nothing writes while the kernel runs, in scalar registers.
+template <class T>
+__device__ __forceinline__ T load_uniform(const T* list, int x) {
+  T v;
+  __builtin_memcpy(&v, (const void*)((const __attribute__((address_space(4))) T*)(uintptr_t)list + x), sizeof(v));
+  return v;
+}
+template <class P>
+using ArgsPtr = const __attribute__((address_space(4))) P*;
+
 template <int D, bool CUT>
-__device__ __forceinline__ void dkv_pipe_blocks(const DkvParams& p, const int num_blocks) {
+__device__ __forceinline__ void dkv_pipe_blocks(const ArgsPtr<DkvParams> args, const int mine) {
   constexpr int NW = 4;        // waves
   constexpr int BM = 32;       // query rows per stage
   constexpr int KC = D / 8;    // 16-byte chunks per operand row
@@ -776,21 +820,26 @@ __device__ __forceinline__ void dkv_pipe_blocks(const DkvParams& p, const int nu
   // before it is known which workgroup is free first).
   int* const next_block = (int*)((__bf16*)smem + LDS_ELEMS);
   const int xcd = xcd_of_this_wave();
-  clock_log_stamp(p.clock_log, 0);
-  int blk = 0;
+  clock_log_stamp(fresh(args).clock_log, 0);
+  int blk = mine;
   // blocks that walk the same rows as the others of their group wait for the groups before them (DkvItem::in_step)
   auto start_in_step = [&](int b) __attribute__((always_inline)) {
-    if (b >= 0 && p.items[b / p.num_kv_heads].in_step) wait_for_earlier_groups(p.ended, b, p.side_by_side);
+    const DkvParams p = fresh(args);
+    if (b >= 0 && load_uniform(p.items, b / p.num_kv_heads).in_step) wait_for_earlier_groups(p.ended, b, p.side_by_side);
   };
-  if (wave == 0) {
-    blk = block_claim_finish(p.taken, num_blocks, xcd, block_claim_issue(p.taken, xcd));
-    start_in_step(blk);
+  if (mine == kClaimBlocks) {
+    if (wave == 0) {
+      const DkvParams p = fresh(args);
+      blk = block_claim_finish(p.taken, p.num_blocks, xcd, block_claim_issue(p.taken, xcd));
+      start_in_step(blk);
+    }
+    blk = broadcast_from_wave0(next_block, blk);
   }
-  blk = broadcast_from_wave0(next_block, blk);
   while (blk >= 0) {
   int pending_claim = 0;
+  const DkvParams p = fresh(args);
   const int kvh = blk % p.num_kv_heads;
-  const DkvItem it = p.items[blk / p.num_kv_heads];
+  const DkvItem it = load_uniform(p.items, blk / p.num_kv_heads);
   const int G = p.group;
   const int64_t q_stride = (int64_t)p.num_q_heads * D, kv_stride = (int64_t)p.num_kv_heads * D;
   const float c = p.scale_log2;
@@ -1164,7 +1213,7 @@ __device__ __forceinline__ void dkv_pipe_blocks(const DkvParams& p, const int nu
     const int n_steps = n_iter + 4;
     const int claim_at = max(0, n_steps - 4) & ~1;  // the step pair before which wave 0 claims the next block
     for (int g = 0; g < n_steps; g += 2) {
-      if (g == claim_at && wave == 0) pending_claim = block_claim_issue(p.taken, xcd);
+      if (g == claim_at && wave == 0 && mine == kClaimBlocks) pending_claim = block_claim_issue(fresh(args).taken, xcd);
       step(g, x[0], x[1], f[0], f[1]);
       step(g + 1, x[1], x[0], f[1], f[0]);
     }
@@ -1176,6 +1225,8 @@ __device__ __forceinline__ void dkv_pipe_blocks(const DkvParams& p, const int nu
     __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
 
     // ---- epilogue: dV = dV^T (role A), dK = scale * dK^T (role B), written (or added) as bf16 ----
+    const DkvParams p = fresh(args);
+    const int64_t kv_stride = (int64_t)p.num_kv_heads * D;
     if (CUT && it.part >= 0) {  // a piece: the accumulators as they are, put together by bwd_merge_kernel
       float* const out = p.parts + ((int64_t)it.part * p.num_kv_heads + kvh) * kPartRowFloats + (4 * ROLE + 2 * pair) * 4096 + lane * 4;
 #pragma unroll
@@ -1206,16 +1257,18 @@ __device__ __forceinline__ void dkv_pipe_blocks(const DkvParams& p, const int nu
   };
   if (role == 0) body(std::integral_constant<int, 0>{});
   else body(std::integral_constant<int, 1>{});
+  if (mine != kClaimBlocks) break;
   // on to the next block; the stores of the epilogue are not waited for here
   int nb = 0;
   if (wave == 0) {
+    const DkvParams p = fresh(args);
     if (lane == 0) __hip_atomic_fetch_add(p.ended + (blk & 7), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    nb = block_claim_finish(p.taken, num_blocks, xcd, pending_claim);
+    nb = block_claim_finish(p.taken, p.num_blocks, xcd, pending_claim);
     start_in_step(nb);
   }
   blk = broadcast_from_wave0(next_block, nb);
   }
-  clock_log_stamp(p.clock_log, 1);
+  clock_log_stamp(fresh(args).clock_log, 1);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -2068,7 +2121,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_wide_pipe_kernel(DkvParams p, 
 // ------------------------------------------------------------------------------------------------
 // (CUT: some items are pieces; see fwd_pipe_kernel)
 template <int D, bool CUT>
-__device__ __forceinline__ void dq_pipe_blocks(const DqParams& p, const int num_blocks) {
+__device__ __forceinline__ void dq_pipe_blocks(const ArgsPtr<DqParams> args, const int mine) {
   constexpr int NW = 4;        // waves
   constexpr int BN = 32;       // key rows per stage
   constexpr int KC = D / 8;    // 16-byte chunks per K / V row
@@ -2114,16 +2167,20 @@ __device__ __forceinline__ void dq_pipe_blocks(const DqParams& p, const int num_
   // enough for the answer to arrive by the time it is needed, and not earlier (that would fix the order of the blocks
   // before it is known which workgroup is free first).
   const int xcd = xcd_of_this_wave();
-  clock_log_stamp(p.clock_log, 0);
-  int blk = 0;
-  if (wave == 0) blk = block_claim_finish(p.taken, num_blocks, xcd, block_claim_issue(p.taken, xcd));
-  blk = broadcast_from_wave0(next_block, blk);
+  clock_log_stamp(fresh(args).clock_log, 0);
+  int blk = mine;
+  if (mine == kClaimBlocks) {
+    const DqParams p = fresh(args);
+    if (wave == 0) blk = block_claim_finish(p.taken, p.num_blocks, xcd, block_claim_issue(p.taken, xcd));
+    blk = broadcast_from_wave0(next_block, blk);
+  }
   while (blk >= 0) {
   wg_barrier();  // every wave has read the announcement: the staging area may be written again
+  const DqParams p = fresh(args);
   const int inner_n = p.num_kv_heads * p.head_splits;
-  const int inner = blk % inner_n;
-  const DqItem it = p.items[blk / inner_n];
-  const int kvh = inner % p.num_kv_heads, hs = inner / p.num_kv_heads;
+  const int inner = __builtin_amdgcn_readfirstlane(blk % inner_n);
+  const DqItem it = load_uniform(p.items, __builtin_amdgcn_readfirstlane(blk / inner_n));
+  const int kvh = __builtin_amdgcn_readfirstlane(inner % p.num_kv_heads), hs = inner / p.num_kv_heads;
   int head[2], row0[2];  // of the wave's two units
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
@@ -2166,19 +2223,21 @@ __device__ __forceinline__ void dq_pipe_blocks(const DqParams& p, const int num_
     }
   }
   int d_t = 0, d_slot = 0;   // stage to copy next (clamped to the last one) and its slot
-  int64_t d_off = 0;         // element offset of its first row
+  const char* d_k = reinterpret_cast<const char*>(Kg);  // its first row in K and in V (running pointers stay in scalar registers)
+  const char* d_v = reinterpret_cast<const char*>(Vg);
   auto dma_piece = [&](int i) __attribute__((always_inline)) {
     const int piece = i * NW + wave;  // wave-uniform; the first NP are pieces of K, the others of V
     const bool of_k = NP % NW == 0 ? i < NP / NW : piece < NP;
     const unsigned voff = d_t == nt - 1 ? v_last[i] : v_full[i];
-    const char* base = reinterpret_cast<const char*>((of_k ? Kg : Vg) + d_off);
+    const char* base = of_k ? d_k : d_v;
     lds_bf16* dst = L + (of_k ? K_OFF + piece * 512 : V_OFF + (piece - NP) * 512) + d_slot * KT;
     dma16(base + voff, dst);
   };
   auto dma_advance = [&]() __attribute__((always_inline)) {
     if (d_t + 1 < nt) {
       ++d_t;
-      d_off += BN * kv_stride;
+      d_k += BN * kv_stride * 2;
+      d_v += BN * kv_stride * 2;
     }
     d_slot = d_slot == NS - 1 ? 0 : d_slot + 1;
   };
@@ -2406,7 +2465,7 @@ __device__ __forceinline__ void dq_pipe_blocks(const DqParams& p, const int num_
     step(t + 1, x[1], x[0], f[1], f[0], std::false_type{});
   }
   int pending_claim = 0;
-  if (wave == 0) pending_claim = block_claim_issue(p.taken, xcd);
+  if (wave == 0 && mine == kClaimBlocks) pending_claim = block_claim_issue(fresh(args).taken, xcd);
   for (; t <= nt; t += 2) {
     step(t, x[0], x[1], f[0], f[1], std::true_type{});
     step(t + 1, x[1], x[0], f[1], f[0], std::true_type{});
@@ -2425,8 +2484,10 @@ __device__ __forceinline__ void dq_pipe_blocks(const DqParams& p, const int num_
   int lane_e = lane;
   asm volatile("" : "+v"(lane_e));
   const int l32_e = lane_e & 31, hh_e = lane_e >> 5;
+  const DqParams pe = fresh(args);
+  const int64_t q_stride_e = (int64_t)pe.num_q_heads * D;
   if (CUT && it.part >= 0) {  // a piece: dQ^T as it is, put together by bwd_merge_kernel
-    float* const out = p.parts + ((int64_t)it.part * inner_n + inner) * kPartRowFloats + wave * (2 * 4096) + lane_e * 4;
+    float* const out = pe.parts + ((int64_t)it.part * (pe.num_kv_heads * pe.head_splits) + inner) * kPartRowFloats + wave * (2 * 4096) + lane_e * 4;
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -2442,26 +2503,30 @@ __device__ __forceinline__ void dq_pipe_blocks(const DqParams& p, const int num_
     for (int db = 0; db < DB; ++db)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        const bf16x4 v = pack4(dq[u][db][4 * g] * p.scale, dq[u][db][4 * g + 1] * p.scale, dq[u][db][4 * g + 2] * p.scale,
-                               dq[u][db][4 * g + 3] * p.scale);
+        const bf16x4 v = pack4(dq[u][db][4 * g] * pe.scale, dq[u][db][4 * g + 1] * pe.scale, dq[u][db][4 * g + 2] * pe.scale,
+                               dq[u][db][4 * g + 3] * pe.scale);
         *(__attribute__((address_space(3))) bf16x4*)(stage + tile_elem<KC>(32 * u + l32_e, 4 * db + g) + 4 * hh_e) = v;
       }
-    __bf16* obase = p.dq + (int64_t)(it.q_row0 + row0[u]) * q_stride + (int64_t)head[u] * D;
+    __bf16* obase = pe.dq + (int64_t)(it.q_row0 + row0[u]) * q_stride_e + (int64_t)head[u] * D;
 #pragma unroll 2
     for (int i = 0; i < 32 * KC / 64; ++i) {
       const int x = (u * 32 * KC / 64 + i) * 64 + lane_e;
       const int row = x / KC, c = unswz<KC>(row, x % KC);  // row of the staging tile: 32 u + row of the unit
       const bf16x8 v = lds_load8(stage + x * 8);
       const int ru = row - 32 * u;
-      if (row0[u] + ru < it.q_rows) *reinterpret_cast<bf16x8*>(obase + (int64_t)ru * q_stride + c * 8) = v;
+      if (row0[u] + ru < it.q_rows) *reinterpret_cast<bf16x8*>(obase + (int64_t)ru * q_stride_e + c * 8) = v;
     }
   }
+  if (mine != kClaimBlocks) break;
   // on to the next block; the stores above are not waited for here
   int nb = 0;
-  if (wave == 0) nb = block_claim_finish(p.taken, num_blocks, xcd, pending_claim);
+  if (wave == 0) {
+    const DqParams pc = fresh(args);
+    nb = block_claim_finish(pc.taken, pc.num_blocks, xcd, pending_claim);
+  }
   blk = broadcast_from_wave0(next_block, nb);
   }
-  clock_log_stamp(p.clock_log, 1);
+  clock_log_stamp(fresh(args).clock_log, 1);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -2473,13 +2538,11 @@ __device__ __forceinline__ void dq_pipe_blocks(const DqParams& p, const int num_
 // the LDS and a wave's registers, whatever the order.  Forward and backward, two launches -> one: 557 causal tokens, 32/8 heads,
 // 123 -> 96 us; two slices of 3193 and 4999 queries (backwards only) 1886 -> 1801; long chunks are as fast either way (packed
 // 64K chunk, 8192 queries on 32768 keys: within 0.3 %).
-// The parameters of a phase are read when it starts, from the kernel arguments through a pointer the compiler cannot see
-// through: held by value for both phases they took 118 spilled scalar registers.
 // ------------------------------------------------------------------------------------------------
 struct BwdPipeParams {
   DqParams dq;
   DkvParams dkv;
-  int32_t dq_blocks, dkv_blocks, dq_phase;
+  int32_t dq_phase;
 };
 template <int D, bool CUT>
 __global__ __launch_bounds__(256, 1) void bwd_pipe_kernel(BwdPipeParams) {
@@ -2488,20 +2551,22 @@ __global__ __launch_bounds__(256, 1) void bwd_pipe_kernel(BwdPipeParams) {
     if (phase > 0) wg_barrier();  // every wave has read that no block of the other kind is left: the LDS may be written again
     args_ptr args = (args_ptr)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(args));
-    if (phase == args->dq_phase) {
-      DqParams p;
-      __builtin_memcpy(&p, (const void*)&args->dq, sizeof(p));
-      dq_pipe_blocks<D, CUT>(p, args->dq_blocks);
-    } else {
-      DkvParams p;
-      __builtin_memcpy(&p, (const void*)&args->dkv, sizeof(p));
-      dkv_pipe_blocks<D, CUT>(p, args->dkv_blocks);
+    const bool is_dq = phase == args->dq_phase;
+    int mine = kClaimBlocks;
+    if (args->dq.num_blocks + args->dkv.num_blocks <= (int)gridDim.x) {  // a workgroup per block: nothing to claim
+      const int first = args->dq_phase == 0 ? args->dq.num_blocks : args->dkv.num_blocks;
+      mine = phase == 0 ? ((int)blockIdx.x < first ? (int)blockIdx.x : -1) : (int)blockIdx.x - first;
     }
+    if (is_dq) dq_pipe_blocks<D, CUT>(&args->dq, mine);
+    else dkv_pipe_blocks<D, CUT>(&args->dkv, mine);
+    if (mine >= 0) break;
   }
 }
 
 // head_dim 64, where dQ is pipelined
-__global__ __launch_bounds__(256, 1) void bwd_dq_pipe_kernel(DqParams p, int num_blocks) { dq_pipe_blocks<64, false>(p, num_blocks); }
+__global__ __launch_bounds__(256, 1) void bwd_dq_pipe_kernel(DqParams) {
+  dq_pipe_blocks<64, false>((ArgsPtr<DqParams>)__builtin_amdgcn_kernarg_segment_ptr(), kClaimBlocks);
+}
 
 // Puts the pieces of cut walks together: dQ rows = scale x the sum of their partial results in the order of the pieces, dK and dV
 // rows likewise.  A workgroup takes one unit of 32 rows of a whole item (the layout in which the pipelined kernel held it), each of
@@ -2605,9 +2670,8 @@ hipError_t raise_smem_limit(K kernel, size_t smem) {
 }
 
 template <int D>
-hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPlan& P, hipStream_t stream) {
+hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPlan& P, const std::vector<char>& blob, hipStream_t stream) {
   char* ws = a.workspace;
-  const TileJob* qjobs = reinterpret_cast<const TileJob*>(ws + P.qjobs_off);
   float* lse2p = reinterpret_cast<float*>(ws + P.lse2p_off);
   float* dsp = reinterpret_cast<float*>(ws + P.dsp_off);
   hipError_t e;
@@ -2616,8 +2680,18 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
   {
     const int64_t blocks = (int64_t)P.qjobs.size() * d->num_q_heads;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((bwd_pre_kernel<D>), dim3((unsigned)blocks), dim3(256), 0, stream, a.o, a.d_o, a.lse, qjobs,
-                       P.q_tiles, d->total_q, d->num_q_heads, lse2p, dsp);
+    const bool carry = blob.size() <= kInlineBlob;
+    BwdPreArgs p;
+    p.o = a.o; p.d_o = a.d_o; p.lse = a.lse;
+    p.jobs = carry ? nullptr : reinterpret_cast<const TileJob*>(ws + P.qjobs_off);
+    p.lse2p = lse2p; p.dsp = dsp;
+    p.total_q_tiles = P.q_tiles; p.total_q = d->total_q; p.num_q_heads = d->num_q_heads;
+    p.blob_dst = reinterpret_cast<u32x4*>(ws);
+    p.blob_n16 = carry ? (int)(blob.size() / 16) : 0;
+    p.jobs_off = (int)P.qjobs_off;
+    if (carry) std::memcpy(p.blob, blob.data(), blob.size());
+    static_assert(kInlineBlob <= 256 * 16, "one workgroup copies it");
+    hipLaunchKernelGGL((bwd_pre_kernel<D>), dim3((unsigned)blocks), dim3(256), 0, stream, p);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if (!a.accumulate) {  // rows no segment covers receive no gradient
@@ -2664,6 +2738,8 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
   static_assert(DKV_KEYS == 128, "the head_dim 64 and 128 kernels cover 128 keys per workgroup");
   const int64_t dkv_blocks = (int64_t)P.dkv_items.size() * d->num_kv_heads;
   if (dq_blocks > 0x7fffffff || dkv_blocks > 0x7fffffff) return hipErrorInvalidValue;
+  pq.num_blocks = (int)dq_blocks;
+  pk.num_blocks = (int)dkv_blocks;
   ProfileEvents pe = profile_events();
   profile_events() = ProfileEvents{};
 
@@ -2677,8 +2753,6 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
     BwdPipeParams p;
     p.dq = pq;
     p.dkv = pk;
-    p.dq_blocks = (int)dq_blocks;
-    p.dkv_blocks = (int)dkv_blocks;
     p.dq_phase = P.dq_first ? 0 : 1;
     const dim3 grid((unsigned)persistent_grid(dq_blocks + dkv_blocks));
     if (pe.start && (e = hipEventRecord(pe.start, stream)) != hipSuccess) return e;
@@ -2703,7 +2777,7 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
       const size_t smem = (size_t)2 * (DQ_PIPE_DIST + 3) * 32 * D * 2 + (size_t)4 * 64 * D * 2;
       static const hipError_t attr = raise_smem_limit(&bwd_dq_pipe_kernel, smem);
       if (attr != hipSuccess) return attr;
-      hipLaunchKernelGGL(bwd_dq_pipe_kernel, dim3((unsigned)persistent_grid(dq_blocks)), dim3(256), smem, stream, pq, (int)dq_blocks);
+      hipLaunchKernelGGL(bwd_dq_pipe_kernel, dim3((unsigned)persistent_grid(dq_blocks)), dim3(256), smem, stream, pq);
     } else {
       const size_t smem = (size_t)6 * 32 * D * 2;  // 3 stages of K and V tiles
       constexpr int DQW = 4;
@@ -2797,23 +2871,25 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, bool may_c
     n_dq += (d->segments[t].q_len + dq_rows - 1) / dq_rows;
     n_dkv += (d->segments[t].kv_len + dkv_keys(d->head_dim) - 1) / dkv_keys(d->head_dim);
   }
-  // (cut walks: the pieces, then the whole items that were cut, of which there are at most as many as items)
-  P.n_dq_cut = P.dq_cut.size();
-  P.n_dkv_cut = P.dkv_cut.size();
+  // (cut walks: the pieces, then the whole items that were cut)
+  auto up16 = [](size_t x) { return (x + 15) / 16 * 16; };
+  P.n_dq_cut = n_dq - (size_t)(P.split.target > 0 ? P.split.pieces - P.split.parts : (int64_t)n_dq);
+  P.n_dkv_cut = n_dkv - (size_t)(P.dkv_split.target > 0 ? P.dkv_split.pieces - P.dkv_split.parts : (int64_t)n_dkv);
   P.dq_items_off = 0;
-  P.dq_cut_off = P.split.target > 0 ? up256((size_t)P.split.pieces * sizeof(DqItem)) : 0;
-  P.dkv_items_off = P.dq_cut_off + up256(n_dq * sizeof(DqItem));
-  P.dkv_cut_off = P.dkv_items_off + (P.dkv_split.target > 0 ? up256((size_t)P.dkv_split.pieces * sizeof(DkvItem)) : 0);
-  P.qjobs_off = P.dkv_cut_off + up256(n_dkv * sizeof(DkvItem));
-  P.fitems_off = P.qjobs_off + up256((size_t)P.q_tiles * sizeof(TileJob));
+  P.dq_cut_off = up16((P.split.target > 0 ? (size_t)P.split.pieces : n_dq) * sizeof(DqItem));
+  P.dkv_items_off = P.dq_cut_off + up16(P.n_dq_cut * sizeof(DqItem));
+  P.dkv_cut_off = P.dkv_items_off + up16((P.dkv_split.target > 0 ? (size_t)P.dkv_split.pieces : n_dkv) * sizeof(DkvItem));
+  P.qjobs_off = P.dkv_cut_off + up16(P.n_dkv_cut * sizeof(DkvItem));
+  // block-queue counters of the dQ and of the dK/dV kernel (zero in the blob): dQ queues, dK/dV queues, dK/dV blocks ended
+  P.queues_off = P.qjobs_off + up16((size_t)P.q_tiles * sizeof(TileJob));
+  P.fitems_off = P.queues_off + up16(3 * kBlockQueues * sizeof(int32_t));
   // the workspace is sized for either backward (the mode may change between the size query and the call): the one-pass
   // backward has one item per (key block, key/value head) and at most 8 x that many workgroup slots
   const size_t n_fused = d->head_dim == 128 ? n_dkv_blocks(d) * (size_t)d->num_kv_heads : 0;
-  P.forder_off = P.fitems_off + up256(n_fused * sizeof(FusedItem));
-  P.q32jobs_off = P.forder_off + up256(n_fused * kNumXcd * sizeof(int32_t));
-  // block-queue counters of the dQ and of the dK/dV kernel (zero in the blob)
-  P.queues_off = P.q32jobs_off + (d->head_dim == 128 ? up256((size_t)P.qt32_tiles * sizeof(DqTileJob)) : 0);
-  P.blob_bytes = P.queues_off + up256(3 * kBlockQueues * sizeof(int32_t));  // dQ queues, dK/dV queues, dK/dV blocks ended
+  P.forder_off = P.fitems_off + up16(n_fused * sizeof(FusedItem));
+  P.q32jobs_off = P.forder_off + up16(n_fused * kNumXcd * sizeof(int32_t));
+  P.blob_bytes = up256(P.q32jobs_off + (d->head_dim == 128 ? (size_t)P.qt32_tiles * sizeof(DqTileJob) : 0));
+  P.upload_bytes = P.fused ? P.blob_bytes : P.fitems_off;
   const size_t row_slots = (size_t)d->num_q_heads * P.q_tiles * 64;
   P.fprog_off = P.blob_bytes;
   // progress counters, then the status word (its own 256 bytes), then a scratch tile
@@ -2829,7 +2905,7 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, bool may_c
 }
 
 std::vector<char> bwd_blob(const BwdPlan& P) {
-  std::vector<char> blob(P.blob_bytes);
+  std::vector<char> blob(P.upload_bytes);
   std::memcpy(blob.data() + P.dq_items_off, P.dq_items.data(), P.dq_items.size() * sizeof(DqItem));
   std::memcpy(blob.data() + P.dq_cut_off, P.dq_cut.data(), P.dq_cut.size() * sizeof(DqItem));
   std::memcpy(blob.data() + P.dkv_items_off, P.dkv_items.data(), P.dkv_items.size() * sizeof(DkvItem));
@@ -2843,10 +2919,10 @@ std::vector<char> bwd_blob(const BwdPlan& P) {
   return blob;
 }
 
-hipError_t launch_bwd(const chunk_attn_desc* d, const BwdArgs& a, const BwdPlan& P, hipStream_t stream) {
-  return d->head_dim == 128 ? launch_bwd_t<128>(d, a, P, stream)
-         : d->head_dim == 96 ? launch_bwd_t<96>(d, a, P, stream)
-         : d->head_dim == 256 ? launch_bwd_t<256>(d, a, P, stream) : launch_bwd_t<64>(d, a, P, stream);
+hipError_t launch_bwd(const chunk_attn_desc* d, const BwdArgs& a, const BwdPlan& P, const std::vector<char>& blob, hipStream_t stream) {
+  return d->head_dim == 128 ? launch_bwd_t<128>(d, a, P, blob, stream)
+         : d->head_dim == 96 ? launch_bwd_t<96>(d, a, P, blob, stream)
+         : d->head_dim == 256 ? launch_bwd_t<256>(d, a, P, blob, stream) : launch_bwd_t<64>(d, a, P, blob, stream);
 }
 
 }  // namespace chunk_attn

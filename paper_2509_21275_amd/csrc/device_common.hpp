@@ -94,6 +94,7 @@ __device__ __forceinline__ void clock_log_stamp(unsigned long long* log, int end
 // have not started, and only the blocks taken over lose their L2 neighbourhood.  `taken` (device, 8 counters, zero when
 // the kernel starts) counts the claims per queue; an index past the end of a queue means it is empty.  No workgroup
 // ever waits for another one.
+constexpr int kClaimBlocks = -2;  // in the place of a block index (-1: none): the blocks are claimed through the counters
 __device__ __forceinline__ int xcd_of_this_wave() { return __builtin_amdgcn_s_getreg((3 << 11) | (0 << 6) | 20) & 7; }
 __device__ __forceinline__ int block_queue_len(int total, int x) { return total > x ? (total - x + 7) >> 3 : 0; }
 // Claim of the next block of queue x, issued by lane 0 without waiting for the answer (the caller reads `idx` later).

@@ -11,9 +11,9 @@
 //
 // Two kernels:
 //   fwd_kernel       online softmax with a lazily moved reference maximum, one 32-row query block per wave,
-//                    two waves per SIMD or more, tiles of 64 keys (K row-major, V as rows that are read transposed or,
+//                    tiles of 64 keys (K row-major, V as rows that are read transposed or,
 //                    for head_dim 256, as the pre-transposed image of transpose_kernel.hip, double-buffered).  Used
-//                    for head_dim 256, for 64 unless its walks are long (pipe_pays), and as the second pass below.
+//                    for head_dim 256, and for 64 unless its walks are long (pipe_pays).
 //                    head_dim 64 without the image and its launch: four sequences of 1024, 32/8 heads, 51 -> 42 us; 1024
 //                    queries on 32768 keys 447 -> 390 us, 2048 on 18432, 8/2 heads, 253 -> 219.  (With one workgroup per
 //                    compute unit a tile's chain of copies, reads and products is what a step takes.  V in chunk-major
@@ -22,10 +22,12 @@
 //                    447 - 469 and 256.  168 registers, so that three workgroups share a CU: with two more, 64 sequences
 //                    of 256 took 83 us instead of 74.)
 //   fwd_pipe_kernel  head_dim 96 and 128, and 64 with two workgroups per CU: one wave per SIMD with 64 query rows, software
-//                    pipelined over stages of 32 keys, reference maximum fixed by the first stage; rows whose scores
-//                    outgrow it are flagged and recomputed by fwd_kernel, launched right after.  Where a chunk of 96 or
+//                    pipelined over stages of 32 keys, reference maximum fixed by the first stage; a block with a row whose scores
+//                    outgrow it is taken a second time, with the true maxima (as a second launch that found out which
+//                    blocks to recompute this cost every call 4 us).  Where a chunk of 96 or
 //                    128 has too few items for the chip their walks are cut into pieces (plan.hpp); the pieces leave
-//                    float32 partial results, which the second pass puts together.
+//                    float32 partial results, which fwd_merge_kernel puts together.
+#include <cstring>
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -37,48 +39,79 @@
 
 namespace chunk_attn {
 
-// Puts the pieces of one block together: O = sum_s 2^(m_s - M) O_s / l, l = sum_s 2^(m_s - M) l_s over its partial results
-// (O_s unnormalised, m_s the reference maximum, l_s the sum), M the largest m_s.  Each of the 8 waves takes one unit of
-// 32 rows in the layout in which the pipelined kernel held it.  Bound by the reads of the partial results (128 KB per
-// block and piece, mostly out of the caches they were just written to).
+// The kernels read their arguments from the kernel argument segment, where a list of items may follow the parameters.
+typedef const __attribute__((address_space(4))) FwdArgs* FwdArgsPtr;
+__device__ __forceinline__ FwdArgsPtr fwd_args() { return (FwdArgsPtr)__builtin_amdgcn_kernarg_segment_ptr(); }
+__device__ __forceinline__ FwdParams load_params(const __attribute__((address_space(4))) FwdParams* src) {
+  FwdParams p;
+  __builtin_memcpy(&p, (const void*)src, sizeof(p));
+  return p;
+}
+// Item x of the list in device memory, or of the one behind the parameters.  (Through the constant address space, so that the item
+// comes in scalar registers either way: nothing writes the lists while a kernel runs.)
+__device__ __forceinline__ FwdItem load_item(const FwdItem* list, const __attribute__((address_space(4))) FwdItem* inline_list, int x) {
+  typedef const __attribute__((address_space(4))) FwdItem* item_ptr;
+  const item_ptr items = list != nullptr ? (item_ptr)(uintptr_t)list : inline_list;
+  FwdItem it;
+  __builtin_memcpy(&it, (const void*)(items + x), sizeof(it));
+  return it;
+}
+
+// Puts the pieces of cut walks together: O = sum_s 2^(m_s - M) O_s / l, l = sum_s 2^(m_s - M) l_s over the partial results of a
+// whole item (O_s unnormalised, m_s the reference maximum, l_s the sum), M the largest m_s.  A workgroup takes one unit of 32 rows in
+// the layout in which the pipelined kernel held it, each of its 4 waves a quarter of the accumulator.  Bound by the latency of
+// reading the partial results (128 KB per block and piece, most of it written on another XCD); one workgroup of 8 waves per block, a unit
+// each, took 10 us (203 queries on 1704 keys next to 611 short rows, 32/8 heads; now 5).
 template <int D>
-__device__ __forceinline__ void fwd_merge_parts(const FwdParams& p, const FwdItem& it, int kvh, int hs, int inner, int inner_n,
-                                                int unit, int lane) {
-  constexpr int NQ = D / 8;  // accumulator quarters
-  const int l32 = lane & 31, hh = lane >> 5;
+__global__ __launch_bounds__(256) void fwd_merge_kernel(FwdMergeArgs) {
+  constexpr int NQ = D / 8 / 4;  // accumulator quarters per wave
+  typedef const __attribute__((address_space(4))) FwdMergeArgs* args_ptr;
+  const args_ptr args = (args_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+  const FwdParams p = load_params(&args->p);
+  const int lane = threadIdx.x & 63, l32 = lane & 31, hh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int unit = blockIdx.x & 7, block = blockIdx.x >> 3;
+  const int inner_n = p.num_kv_heads * p.head_splits, inner = block % inner_n;
+  const FwdItem it = load_item(p.wholes, args->wholes, block / inner_n);
+  if (it.part < 0) return;  // not cut
+  const int kvh = inner % p.num_kv_heads, hs = inner / p.num_kv_heads;
   const int w = unit >> 1;  // wave of the pipelined kernel
   const int head = kvh * p.group + hs * p.heads_per_wg + w % p.heads_per_wg;
   const int r = (w / p.heads_per_wg) * 64 + 32 * (unit & 1) + l32;
+  if (r >= it.q_rows) return;
   const int64_t step = (int64_t)inner_n * kPartFloats;
   const float* const part0 = p.parts + (int64_t)it.part * step + (int64_t)inner * kPartFloats;
   const float* const ml = part0 + kPartRowFloats + (unit * 32 + l32) * 2;
   float m = ml[0], l = 0.f;
+#pragma unroll 4
   for (int s = 1; s < it.whole; ++s) m = fmaxf(m, ml[s * step]);
-  for (int s = 0; s < it.whole; ++s) l += ml[s * step + 1] * __builtin_amdgcn_exp2f(ml[s * step] - m);
   f32x4 o[NQ];
 #pragma unroll
   for (int i = 0; i < NQ; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const float* src = part0 + unit * 4096 + lane * 4;
-  for (int s = 0; s < it.whole; ++s, src += step) {
-    const float f = __builtin_amdgcn_exp2f(ml[s * step] - m);
+  const float* const src = part0 + unit * 4096 + wave * (NQ * 256) + lane * 4;
+#pragma unroll 4
+  for (int s = 0; s < it.whole; ++s) {
+    const f32x2 v2 = *reinterpret_cast<const f32x2*>(ml + s * step);
+    const float f = __builtin_amdgcn_exp2f(v2[0] - m);
+    l += v2[1] * f;
 #pragma unroll
     for (int i = 0; i < NQ; ++i) {
-      const f32x4 v = *reinterpret_cast<const f32x4*>(src + i * 256);
+      const f32x4 v = *reinterpret_cast<const f32x4*>(src + s * step + i * 256);
 #pragma unroll
       for (int e = 0; e < 4; ++e) o[i][e] += v[e] * f;
     }
   }
-  if (r >= it.q_rows) return;
   const float inv = 1.0f / l;
-  __bf16* op = p.o + (int64_t)(it.q_row0 + r) * p.num_q_heads * D + (int64_t)head * D + 4 * hh;
+  __bf16* op = p.o + (int64_t)(it.q_row0 + r) * p.num_q_heads * D + (int64_t)head * D + wave * (NQ * 8) + 4 * hh;
 #pragma unroll
   for (int i = 0; i < NQ; ++i)
     *reinterpret_cast<bf16x4*>(op + 8 * i) = pack4(o[i][0] * inv, o[i][1] * inv, o[i][2] * inv, o[i][3] * inv);
-  if (hh == 0) p.lse[(int64_t)head * p.total_q + it.q_row0 + r] = (m + log2f(l)) * 0.6931471805599453f;
+  if (wave == 0 && hh == 0) p.lse[(int64_t)head * p.total_q + it.q_row0 + r] = (m + log2f(l)) * 0.6931471805599453f;
 }
 
-template <int D, int WAVES>
-__global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : D == 64 && WAVES == 4 ? 3 : 8 / WAVES) void fwd_kernel(FwdParams p) {
+template <int D>
+__global__ __launch_bounds__(256, D > 128 ? 1 : 3) void fwd_kernel(FwdArgs) {
+  constexpr int WAVES = 4;
   constexpr int QB = 1;        // 32-row query blocks per wave
   constexpr int BN = 64;       // key rows per LDS tile
   constexpr int KC = D / 8;    // 16-byte chunks per K row
@@ -86,9 +119,10 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : D == 64 && WAVES == 4 ? 3
   constexpr int DB = D / 32;   // 32-row blocks of O^T
   constexpr int KT = BN * D;   // elements per K tile and per V^T image
   constexpr int WR = 32 * QB;  // query rows per wave
-  if (p.redo != nullptr && !p.cut && p.redo[blockIdx.x] == 0) return;  // second pass with nothing to do
-  constexpr bool IMG = D > 128;   // V arrives as a transposed image; else as rows:
-  constexpr bool ROWS = D == 64;  // a row-major tile like K's (row_elem) for head_dim 64, else two chunk-major tiles of 32
+  constexpr bool ROWS = D == 64;  // V arrives as a row-major tile like K's (row_elem); else (IMG) as a transposed image
+  constexpr bool IMG = !ROWS;
+  const FwdArgsPtr args = fwd_args();
+  const FwdParams p = load_params(&args->p);
 
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   __bf16* Ks = reinterpret_cast<__bf16*>(smem);  // [2][BN][D]  swizzled rows
@@ -101,16 +135,8 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : D == 64 && WAVES == 4 ? 3
 
   const int inner_n = p.num_kv_heads * p.head_splits;
   const int inner = blockIdx.x % inner_n;
-  const FwdItem it = (IMG ? p.items : p.wholes)[blockIdx.x / inner_n];
+  const FwdItem it = load_item(p.items, args->items, blockIdx.x / inner_n);
   const int kvh = inner % p.num_kv_heads, hs = inner / p.num_kv_heads;
-  if constexpr (!IMG) {  // second pass: only what the pipelined kernel left to do
-    if (p.redo != nullptr && p.redo[blockIdx.x] == 0) {
-      if constexpr (pipelined(D)) {
-        if (it.part >= 0) fwd_merge_parts<D>(p, it, kvh, hs, inner, inner_n, wave, lane);
-      }
-      return;
-    }
-  }
   const int head = kvh * p.group + hs * p.heads_per_wg + wave % p.heads_per_wg;
   const int wave_row0 = (wave / p.heads_per_wg) * WR;  // first tile-local row of this wave
 
@@ -130,10 +156,8 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : D == 64 && WAVES == 4 ? 3
   // Per-lane source offsets of the global->LDS copies (elements).  A K tile is 64 rows x KC chunks; copy
   // instruction i of wave w fills LDS chunks [(WAVES i + w) 64, +64), so the lane fetches the chunk that the
   // swizzle puts there.  The V^T image is copied linearly.
-  // (head_dim 96: 12 copies of 64 chunks for 8 waves, so the second round is half a round)
   constexpr int PIECES = BN * KC / 64, NK = (PIECES + WAVES - 1) / WAVES, NV = NK;
-  static_assert(KT == BN * KC * 8 && (!ROWS || PIECES % WAVES == 0), "a V tile has as many chunks as a K tile");
-  auto has_piece = [&](int i) { return PIECES % WAVES == 0 || i * WAVES + wave < PIECES; };
+  static_assert(KT == BN * KC * 8 && PIECES % WAVES == 0, "a V tile has as many chunks as a K tile");
   unsigned k_src[NK];
   int k_row[NK];
 #pragma unroll
@@ -151,7 +175,7 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : D == 64 && WAVES == 4 ? 3
     __bf16* kdst = Ks + buf * KT;
     __bf16* vdst = Vs + buf * KT;
     auto copy = [&](int i, unsigned off) __attribute__((always_inline)) {
-      if (has_piece(i)) dma16(ksrc + off, kdst + (i * WAVES + wave) * 512);
+      dma16(ksrc + off, kdst + (i * WAVES + wave) * 512);
       if constexpr (ROWS) dma16(Vimg + (int64_t)(BN * t) * kv_stride + off, vdst + (i * WAVES + wave) * 512);
     };
     if (last_row >= BN - 1) {
@@ -174,14 +198,6 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : D == 64 && WAVES == 4 ? 3
 #pragma unroll
       for (int i = 0; i < NV; ++i)
         dma16(vsrc + (unsigned)(((i * WAVES + wave) * 64 + lane) * 8), vdst + (i * WAVES + wave) * 512);
-    } else if constexpr (!ROWS) {
-      const __bf16* vsrc = Vimg + (int64_t)(BN * t) * kv_stride;
-#pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        const int x = (i * WAVES + wave) * 64 + lane, xt = x % (32 * KC);  // slot, slot in its 32-row tile
-        const int row = x / (32 * KC) * 32 + ((xt & 31) ^ (((xt >> 5) & 3) << 2));
-        if (has_piece(i)) dma16(vsrc + (int64_t)min(row, last_row) * kv_stride + (xt >> 5) * 8, vdst + (i * WAVES + wave) * 512);
-      }
     }
   };
 
@@ -222,15 +238,10 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : D == 64 && WAVES == 4 ? 3
   }
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) v_off[ks] = tile_elem<8>(l32, 2 * ks + hh);
-  unsigned vt_lo = 0, vt_hi = 0;  // byte addresses of the transposed reads (as in the pipelined kernel) in buffer 0
+  unsigned vt_lo = 0;  // byte addresses of the transposed reads (as in the pipelined kernel) in buffer 0
   if constexpr (!IMG) {
     const int j = lane & 15, cl = 2 * ((lane >> 4) & 1) + ((j & 3) >> 1), r0 = 4 * hh + (j >> 2);
-    if constexpr (ROWS) {
-      vt_lo = lds_addr((lds_bf16*)Vs + row_elem(r0, cl) + 4 * (j & 1));
-    } else {
-      vt_lo = lds_addr((lds_bf16*)Vs + cm_elem(r0, cl) + 4 * (j & 1));
-      vt_hi = lds_addr((lds_bf16*)Vs + cm_elem(r0 + 8, cl) + 4 * (j & 1));
-    }
+    vt_lo = lds_addr((lds_bf16*)Vs + row_elem(r0, cl) + 4 * (j & 1));
   }
 
   const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -238,28 +249,22 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : D == 64 && WAVES == 4 ? 3
   ones[0] = (__bf16)1.0f; ones[1] = (__bf16)1.0f;
 
   // One loop body for both LDS buffers: the operand addresses are toggled between the buffers with an XOR
-  // (the buffers are KT elements = a power of two bytes apart; else the buffer's offset is added), so the accumulators are
+  // (the buffers are KT elements = a power of two bytes apart), so the accumulators are
   // carried by a single loop and never pass through a conditional.
-  constexpr bool TOGGLE = (KT & (KT - 1)) == 0;
   int buf = 0;
   for (int t = 0; t < nt_wg; ++t) {
     if (t + 1 < nt_wg) dma_tile(t + 1, buf ^ 1);
 
     if (t < nt_w) {
-      const __bf16* Kt = Ks + (TOGGLE ? 0 : buf * KT);
+      const __bf16* Kt = Ks;
       const __bf16* Vt = Vs;
       s16x4 v_lo[4][DB], v_hi[4][DB];
       auto read_vt = [&](auto ks_c) __attribute__((always_inline)) {
         static_for<0, DB>([&](auto db_c) __attribute__((always_inline)) {
           constexpr int ks = decltype(ks_c)::value, db = decltype(db_c)::value;
-          if constexpr (ROWS) {  // (chunks 4 .. 7 of a row: the other half of its 128 bytes)
-            v_lo[ks][db] = lds_asm_read_tr<ks * (16 * D) * 2>((vt_lo ^ (db * 64)) + buf * (KT * 2));
-            v_hi[ks][db] = lds_asm_read_tr<(ks * 16 + 8) * D * 2>((vt_lo ^ (db * 64 + 16)) + buf * (KT * 2));  // eight rows on
-          } else {
-            constexpr int off = ((ks >> 1) * (32 * D) + (ks & 1) * (16 * 8) + db * (4 * 32 * 8)) * 2;
-            v_lo[ks][db] = lds_asm_read_tr<off>(vt_lo + buf * (KT * 2));
-            v_hi[ks][db] = lds_asm_read_tr<off>(vt_hi + buf * (KT * 2));
-          }
+          // (chunks 4 .. 7 of a row: the other half of its 128 bytes)
+          v_lo[ks][db] = lds_asm_read_tr<ks * (16 * D) * 2>((vt_lo ^ (db * 64)) + buf * (KT * 2));
+          v_hi[ks][db] = lds_asm_read_tr<(ks * 16 + 8) * D * 2>((vt_lo ^ (db * 64 + 16)) + buf * (KT * 2));  // eight rows on
         });
       };
       // ---- S^T = K Q^T : [64 keys] x [32 QB queries]; every K fragment feeds QB products ----
@@ -376,8 +381,7 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : D == 64 && WAVES == 4 ? 3
       } else {
         static_for<0, 4>([&](auto ks_c) __attribute__((always_inline)) {
           constexpr int ks = decltype(ks_c)::value;
-          if constexpr (D != 64) read_vt(ks_c);
-          if constexpr (D != 64 || ks == 0) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+          if constexpr (ks == 0) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
           for (int db = 0; db < DB; ++db) {
             asm volatile("" : "+v"(v_lo[ks][db]), "+v"(v_hi[ks][db]));  // (after the wait, in this order)
@@ -391,9 +395,9 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : D == 64 && WAVES == 4 ? 3
 
     buf ^= 1;
 #pragma unroll
-    for (int ks = 0; ks < DK; ++ks) k_off[ks] ^= TOGGLE ? KT : 0;
+    for (int ks = 0; ks < DK; ++ks) k_off[ks] ^= KT;
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) v_off[ks] ^= TOGGLE ? KT : 0;
+    for (int ks = 0; ks < 4; ++ks) v_off[ks] ^= KT;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
   }
@@ -434,15 +438,18 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : D == 64 && WAVES == 4 ? 3
 // chunk-major; V^T is read from the V tile itself with the LDS transpose read.  Fragments are fetched four
 // mini-steps ahead with opaque LDS reads and explicit lgkmcnt waits; S^T lives in vector registers, where the
 // vector work reads it directly, the Q fragments and O^T in accumulation registers (tiles.hpp).
-// The reference maximum of the softmax is fixed by the first stage, so O^T is never rescaled in the loop; a row
-// whose later scores outgrow it raises the workgroup's redo flag and the item is recomputed by fwd_kernel.
+// The reference maximum of the softmax is fixed by the first stage, so O^T is never rescaled in the loop; with a row
+// whose later scores outgrow it the workgroup takes the block again, the maximum over all stages first.
 // Steps whose stage needs the causal mask (the last few of the walk) or lies past the end run a second variant of
 // the step that masks in the vector work.
 // ------------------------------------------------------------------------------------------------
 // CUT: some items are pieces.  A kernel of its own, because the few registers and instructions it takes lengthen every block of
 // the other one (chunk of 256-token sequences: dQ, which has the same split, 171 -> 178 us, forward 142 -> 144).
 template <int D, bool CUT>
-__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void fwd_pipe_kernel(FwdParams p, int num_blocks) {
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void fwd_pipe_kernel(FwdArgs) {
+  const FwdArgsPtr args = fwd_args();
+  const FwdParams p = load_params(&args->p);
+  const int num_blocks = args->num_blocks;
   constexpr int NW = 4;        // waves
   constexpr int BN = 32;       // key rows per stage
   constexpr int KC = D / 8;    // 16-byte chunks per K / V row
@@ -482,14 +489,20 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void fwd_pipe_kernel(FwdParam
   // before it is known which workgroup is free first).
   const int xcd = xcd_of_this_wave();
   clock_log_stamp(p.clock_log, 0);
-  int blk = 0;
-  if (wave == 0) blk = block_claim_finish(p.taken, num_blocks, xcd, block_claim_issue(p.taken, xcd));
-  blk = broadcast_from_wave0(next_block, blk);
+  // (As many workgroups as blocks: block b is workgroup b's, and the counters are not looked at.)
+  const bool direct = num_blocks <= (int)gridDim.x;
+  int blk = blockIdx.x;
+  if (!direct) {
+    if (wave == 0) blk = block_claim_finish(p.taken, num_blocks, xcd, block_claim_issue(p.taken, xcd));
+    blk = broadcast_from_wave0(next_block, blk);
+  }
+  bool again = false;  // the block is taken a second time, with every row's true maximum
+  int pending_claim = 0;
   while (blk >= 0) {
   wg_barrier();  // every wave has read the announcement: the staging area may be written again
   const int inner_n = p.num_kv_heads * p.head_splits;
   const int inner = blk % inner_n;
-  const FwdItem it = p.items[blk / inner_n];
+  const FwdItem it = load_item(p.items, args->items, blk / inner_n);
   const int kvh = inner % p.num_kv_heads, hs = inner / p.num_kv_heads;
   const int head = kvh * p.group + hs * p.heads_per_wg + wave % p.heads_per_wg;
   const int wave_row0 = (wave / p.heads_per_wg) * 64;  // the wave's units are rows wave_row0 + 32 u .. + 31 of `head`
@@ -611,6 +624,16 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void fwd_pipe_kernel(FwdParam
   for (int u = 0; u < 2; ++u)
 #pragma unroll
     for (int ks = 0; ks < DK; ++ks) qf[u][ks] = lds_chunk<KC>(stage, 32 * u + l32, 2 * ks + hh);
+  // Once Q has been read, the staging tile's first word says whether some wave has seen a row outgrow its reference maximum:
+  // one word per wave, written by any and read by its own wave only, as the others may by then write their rows of O.
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (in this order: the compiler takes the word and the rows for unrelated)
+  *(volatile int*)stage = 0;
+  // (the fragments settle in their accumulation registers here: an opaque MFMA must not follow a write to one of its operands)
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int ks = 0; ks < DK; ++ks) asm volatile("" : "+a"(qf[u][ks]));
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   wg_barrier();
 
   const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -667,6 +690,28 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void fwd_pipe_kernel(FwdParam
       mc[u] = max_halves(mx) * c;
       l_run[u] = 0.f;
     }
+  }
+  if (__builtin_expect(again, 0)) {  // the maximum over all stages: S^T as in the loop, K read from global memory
+    float mx[2] = {-INFINITY, -INFINITY};
+    for (int s = 0; s < nt; ++s) {
+      const __bf16* kr = Kg + (int64_t)min(BN * s + l32, n_wg - 1) * kv_stride + 8 * hh;
+      f32x16 d[2] = {zero16, zero16};
+#pragma unroll
+      for (int ks = 0; ks < DK; ++ks) {
+        const bf16x8 a = *reinterpret_cast<const bf16x8*>(kr + 16 * ks);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) d[u] = mfma32(a, qf[u][ks], d[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int lim = it.n0 + wave_row0 + 32 * u + l32 - BN * s;
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (8 * (i >> 2) + 4 * hh + (i & 3) < lim) mx[u] = fmaxf(mx[u], d[u][i]);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) mc[u] = max_halves(mx[u]) * c;
   }
   bool risk = false;
   const float big = __builtin_amdgcn_exp2f(p.ref_limit);
@@ -787,10 +832,15 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void fwd_pipe_kernel(FwdParam
     step(t, x[0], x[1], f[0], f[1], std::false_type{});
     step(t + 1, x[1], x[0], f[1], f[0], std::false_type{});
   }
-  int pending_claim = 0;
-  if (wave == 0) pending_claim = block_claim_issue(p.taken, xcd);
+  if (wave == 0 && !again && !direct) pending_claim = block_claim_issue(p.taken, xcd);
   for (; t <= nt; t += 2) {
     step(t, x[0], x[1], f[0], f[1], std::true_type{});
+    // (the scores of stages up to nt - 1 have been looked at by the first of the last two steps; the barrier that ends the
+    // second one publishes the word)
+    if (__builtin_expect(__any(risk), 0)) {
+#pragma unroll
+      for (int w = 0; w < NW; ++w) *(volatile int*)((__bf16*)smem + ST_OFF + w * (ST_ROWS * D)) = 1;
+    }
     step(t + 1, x[1], x[0], f[1], f[0], std::true_type{});
   }
   // the last step's reads ahead are nobody's operands; their registers stay taken until they have arrived
@@ -799,9 +849,12 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void fwd_pipe_kernel(FwdParam
   // every copy of this wave has landed (the last ones rewrote a slot nobody reads): after the barrier below the next
   // block may fill the ring again
   __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
-  if (__any(risk) && lane == 0) {
-    p.redo[CUT ? it.whole * inner_n + inner : blk] = 1;
+  const bool outgrown = __builtin_amdgcn_readfirstlane(*(volatile int*)stage) != 0;
+  if (__builtin_expect(outgrown && !again, 0)) {  // (the same for all waves; the barrier at the head of the loop comes before the next copies)
+    again = true;
+    continue;
   }
+  again = false;
 
   // ---- epilogue: O = O^T / l, LSE = ln(l) + m scale ----
   // (through the wave's staging tile: the lane that holds four values of a row writes them there, then every lane
@@ -852,6 +905,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void fwd_pipe_kernel(FwdParam
       }
     }
   }
+  if (direct) break;
   // on to the next block; the stores above are not waited for here
   int nb = 0;
   if (wave == 0) nb = block_claim_finish(p.taken, num_blocks, xcd, pending_claim);
@@ -866,48 +920,63 @@ static hipError_t raise_smem_limit(K kernel, size_t smem) {
   return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
 }
 
-template <int D, int WAVES>
-static hipError_t launch_fwd_t(const FwdParams& p, int num_blocks, hipStream_t stream) {
+// (the arguments' trailing list of items is only filled, and only read, where the items have no other place)
+static FwdArgs fwd_launch_args(const FwdParams& p, const FwdLists& lists) {
+  FwdArgs a;
+  a.p = p;
+  a.num_blocks = lists.num_blocks;
+  if (p.items == nullptr) std::memcpy(a.items, lists.items, (size_t)lists.num_items * sizeof(FwdItem));
+  return a;
+}
+
+template <int D>
+static hipError_t launch_fwd_t(const FwdArgs& a, hipStream_t stream) {
   const size_t smem = (size_t)4 * 64 * D * 2;
-  static const hipError_t attr = raise_smem_limit(&fwd_kernel<D, WAVES>, smem);
+  static const hipError_t attr = raise_smem_limit(&fwd_kernel<D>, smem);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL((fwd_kernel<D, WAVES>), dim3(num_blocks), dim3(WAVES * 64), smem, stream, p);
+  hipLaunchKernelGGL((fwd_kernel<D>), dim3(a.num_blocks), dim3(256), smem, stream, a);
   return hipGetLastError();
 }
 
 template <int D, bool CUT>
-static hipError_t launch_fwd_items(const FwdParams& p, int num_blocks, size_t smem, hipStream_t stream) {
+static hipError_t launch_fwd_items(const FwdArgs& a, size_t smem, hipStream_t stream) {
   static const hipError_t attr = raise_smem_limit(&fwd_pipe_kernel<D, CUT>, smem);
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL((fwd_pipe_kernel<D, CUT>), dim3(persistent_grid(num_blocks, D == 64 ? 2 : 1)), dim3(256), smem, stream, p, num_blocks);
+  hipLaunchKernelGGL((fwd_pipe_kernel<D, CUT>), dim3(persistent_grid(a.num_blocks, fwd_per_cu(D))), dim3(256), smem, stream, a);
   return hipGetLastError();
 }
 
 template <int D>
-static hipError_t launch_fwd_pipe(const FwdParams& p, int num_blocks, int num_wholes, hipStream_t stream) {
+static hipError_t launch_fwd_pipe(const FwdArgs& a, const FwdLists& lists, hipStream_t stream) {
   // ring slots of a K and a V tile, then the staging tiles of the four waves (64 rows each)
   const size_t smem = (size_t)2 * (FWD_PIPE_DIST + 3) * 32 * D * 2 + (size_t)4 * 64 * D * 2;
-  hipError_t e;
-  if constexpr (pipelined(D)) e = p.cut ? launch_fwd_items<D, true>(p, num_blocks, smem, stream) : launch_fwd_items<D, false>(p, num_blocks, smem, stream);
-  else e = launch_fwd_items<D, false>(p, num_blocks, smem, stream);
-  if (e != hipSuccess) return e;
-  // Second pass over the whole items, 8 waves of 32 rows: a workgroup returns at once unless its flag is raised (the item
-  // is recomputed) or its item was cut (its pieces are put together).
-  return launch_fwd_t<D, 8>(p, num_wholes, stream);
+  if constexpr (pipelined(D)) {
+    if (lists.num_wholes > 0) {
+      const hipError_t e = launch_fwd_items<D, true>(a, smem, stream);
+      if (e != hipSuccess) return e;
+      FwdMergeArgs m;
+      m.p = a.p;
+      if (a.p.wholes == nullptr) std::memcpy(m.wholes, lists.wholes, (size_t)lists.num_wholes * sizeof(FwdItem));
+      const unsigned units = 8u * (unsigned)lists.num_wholes * (unsigned)(a.p.num_kv_heads * a.p.head_splits);
+      hipLaunchKernelGGL((fwd_merge_kernel<D>), dim3(units), dim3(256), 0, stream, m);
+      return hipGetLastError();
+    }
+  }
+  return launch_fwd_items<D, false>(a, smem, stream);
 }
 
-hipError_t launch_fwd(const FwdParams& p, int head_dim, bool pipe, int num_blocks, int num_wholes, const TileJob* vjobs,
-                      int num_vjobs, hipStream_t stream) {
+hipError_t launch_fwd(const FwdParams& p, int head_dim, bool pipe, const FwdLists& lists, const TileJob* vjobs, hipStream_t stream) {
+  const FwdArgs a = fwd_launch_args(p, lists);
   if (head_dim == 256) {
     hipError_t e;
-    if ((e = launch_transpose(p.v, p.num_kv_heads, head_dim, 64, vjobs, num_vjobs, p.total_kv_tiles, const_cast<__bf16*>(p.vt),
+    if ((e = launch_transpose(p.v, p.num_kv_heads, head_dim, 64, vjobs, lists.num_vjobs, p.total_kv_tiles, const_cast<__bf16*>(p.vt),
                               stream)) != hipSuccess) return e;
-    return launch_fwd_t<256, 4>(p, num_blocks, stream);
+    return launch_fwd_t<256>(a, stream);
   }
-  if (!pipe) return launch_fwd_t<64, 4>(p, num_blocks, stream);
-  return head_dim == 64 ? launch_fwd_pipe<64>(p, num_blocks, num_wholes, stream)
-         : head_dim == 96 ? launch_fwd_pipe<96>(p, num_blocks, num_wholes, stream)
-                          : launch_fwd_pipe<128>(p, num_blocks, num_wholes, stream);
+  if (!pipe) return launch_fwd_t<64>(a, stream);
+  return head_dim == 64 ? launch_fwd_pipe<64>(a, lists, stream)
+         : head_dim == 96 ? launch_fwd_pipe<96>(a, lists, stream)
+                          : launch_fwd_pipe<128>(a, lists, stream);
 }
 
 }  // namespace chunk_attn

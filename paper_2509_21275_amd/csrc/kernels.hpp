@@ -20,9 +20,8 @@ struct FwdParams {
   __bf16* o;
   float* lse;
   const __bf16* vt;         // head_dim 256: transposed V images [Hkv][total_kv_tiles][D][64]
-  const FwdItem* items;
-  const FwdItem* wholes;    // the items before cutting (= items if none was cut)
-  bool cut;                 // some of the items are pieces (head_dim 96 and 128)
+  const FwdItem* items;     // null: in the kernel arguments (FwdArgs)
+  const FwdItem* wholes;    // what fwd_merge_kernel goes through: items before cutting (those that were not cut are passed over); or null
   float* parts;             // partial results of the pieces, kPartFloats per (slot, inner index)
   int64_t total_kv_tiles;
   int32_t num_q_heads, num_kv_heads, group;  // group = Hq / Hkv
@@ -30,17 +29,30 @@ struct FwdParams {
   int32_t head_splits;                       // group / heads_per_wg
   int32_t total_q;
   float scale_log2;                          // softmax scale * log2(e)
-  int32_t* redo;                             // pipelined forward: redo flag per (whole item, inner index); else null
-  float ref_limit;                           // log2 growth of the row maximum past the first tile's that raises the flag
-  int32_t* taken;                            // 8 block-queue counters of the pipelined forward (zero before the launch)
+  float ref_limit;                           // log2 growth of the row maximum past the first tile's with which a block is taken again
+  int32_t* taken;                            // 8 block-queue counters of the pipelined forward, zero before the launch (not read
+                                             // if there are no more blocks than workgroups)
   unsigned long long* clock_log;             // null, or where the pipelined forward's workgroups log their clocks
+};
+
+// Kernel arguments with room for a short list of items behind the parameters: a small chunk's schedule then needs no place in device
+// memory and no launch or copy to get there.  (3.6 KB in all; 4 KB are documented for a launch.)
+constexpr int kInlineItems = 104;
+constexpr size_t kInlineBlob = 3584;  // bytes of a schedule that travels as a kernel argument on its way to device memory
+struct FwdArgs {
+  FwdParams p;
+  int32_t num_blocks;
+  FwdItem items[kInlineItems];
+};
+struct FwdMergeArgs {
+  FwdParams p;
+  FwdItem wholes[kInlineItems];
 };
 
 // rows of query tile per forward work item for a given head layout
 // Shape of a query-stationary workgroup (forward and dQ kernels): `waves` waves of 32 query rows each, spread
 // over as many query heads of one group as divide both (so that the key/value tiles they stream are shared).
-// forward: 4 waves; in the pipelined kernel each wave owns two 32-row query blocks (its second pass, fwd_kernel with 8 waves
-// of one block, covers the same rows per workgroup)
+// forward: 4 waves; in the pipelined kernel each wave owns two 32-row query blocks
 // head dimensions that always run the software-pipelined kernels (64 does from a size on, pipe_pays)
 constexpr bool pipelined(int head_dim) { return head_dim == 96 || head_dim == 128; }
 inline int fwd_waves(int) { return 4; }
@@ -104,8 +116,8 @@ struct BwdArgs {
 };
 
 // Host-side plan of one backward call and the layout of its workspace:
-// [dQ items | dQ items that were cut | dK/dV items | dK/dV items that were cut | 64-row query-tile jobs] (one uploaded blob), then the
-// LSE and D arrays padded to 64-row tiles.
+// [dQ items | dQ items that were cut | dK/dV items | dK/dV items that were cut | 64-row query-tile jobs | block-queue counters | items of the
+// one-pass backward, if it runs] (one uploaded blob), then the LSE and D arrays padded to 64-row tiles.
 struct BwdPlan {
   KeySplit split;                // head_dim 96 and 128: how the dQ walks are cut
   std::vector<DqItem> dq_items;  // with the pieces of walks that are cut
@@ -116,7 +128,7 @@ struct BwdPlan {
   std::vector<TileJob> qjobs;
   int64_t q_tiles = 0;
   size_t n_dq_cut = 0, n_dkv_cut = 0;
-  size_t dq_items_off = 0, dq_cut_off = 0, dkv_items_off = 0, dkv_cut_off = 0, qjobs_off = 0, queues_off = 0, blob_bytes = 0;
+  size_t dq_items_off = 0, dq_cut_off = 0, dkv_items_off = 0, dkv_cut_off = 0, qjobs_off = 0, queues_off = 0, upload_bytes = 0, blob_bytes = 0;
   size_t lse2p_off = 0, dsp_off = 0, dq_parts_off = 0, total = 0;
   // (head_dim 96 and 128 always; dQ: 64 where pipe_pays, 256 never; dK/dV: 64 and 256 where dkv_pipe_pays)
   bool dq_pipe = false, dkv_pipe = false;  // the pipelined kernels run
@@ -144,14 +156,22 @@ hipError_t launch_bwd_fused(const chunk_attn_desc* d, const BwdArgs& a, const Bw
 void bwd_layout(const chunk_attn_desc* d, BwdPlan& plan, bool with_plan, bool may_cut = true);
 // The host image of the blob at the start of the workspace.
 std::vector<char> bwd_blob(const BwdPlan& plan);
-// Enqueues the backward kernels; the blob must already be on its way to the workspace on `stream`.
-hipError_t launch_bwd(const chunk_attn_desc* d, const BwdArgs& a, const BwdPlan& plan, hipStream_t stream);
+// Enqueues the backward kernels.  A blob of more than kInlineBlob bytes must already be on its way to the workspace on `stream`.
+hipError_t launch_bwd(const chunk_attn_desc* d, const BwdArgs& a, const BwdPlan& plan, const std::vector<char>& blob, hipStream_t stream);
 
-// The forward kernels of one call over `num_blocks` blocks (items x inner) cut from `num_wholes`: the pipelined kernel and its
-// second pass, or fwd_kernel alone (head_dim 256, and 64 unless `pipe`).  `vjobs` (device) lists the 64-row tiles of V whose
-// transposed images p.vt receives (head_dim 256).
-hipError_t launch_fwd(const FwdParams& p, int head_dim, bool pipe, int num_blocks, int num_wholes, const TileJob* vjobs, int num_vjobs,
-                      hipStream_t stream);
+// The lists of one forward call: `num_blocks` blocks (items x inner); the host copies of the items and of the cut ones among the whole
+// items are read only where the kernel arguments carry them.
+struct FwdLists {
+  int num_blocks = 0, num_items = 0;
+  int num_wholes = 0;  // 0: nothing is cut
+  int num_vjobs = 0;
+  const FwdItem *items = nullptr, *wholes = nullptr;
+};
+// workgroups of the pipelined forward on a CU
+constexpr int fwd_per_cu(int head_dim) { return head_dim == 64 ? 2 : 1; }
+// The pipelined kernel (and the launch that puts cut walks together), or fwd_kernel (head_dim 256, and 64 unless `pipe`).  `vjobs` (device)
+// lists the 64-row tiles of V whose transposed images p.vt receives (head_dim 256).
+hipError_t launch_fwd(const FwdParams& p, int head_dim, bool pipe, const FwdLists& lists, const TileJob* vjobs, hipStream_t stream);
 
 // Transposed tile images (width 64 or 32 rows) of x[rows][num_heads][head_dim]:
 // out[num_heads][total_tiles][head_dim][width].
