@@ -86,7 +86,8 @@ typedef struct {
  * Scratch sizes (bytes) for a descriptor: *fwd_bytes for chunk_attn_fwd, *bwd_bytes for
  * chunk_attn_bwd.  Forward: the tile schedule, then room for transposed tile images of V (made for head_dim 256 only) or for
  * the float32 partial results of walks that are cut (96 and 128; up to 16 MiB where the images would be smaller).  Backward:
- * the schedules, the row sums D_i = <dO_i, O_i> and, for 96 and 128, float32 tiles of dQ or partial results.  For 96 both also
+ * the schedules, the row sums D_i = <dO_i, O_i> and, for 96 and 128, float32 tiles of dQ or partial results, for 64 and 256
+ * partial results of dK / dV walks that are cut (64 MB at most).  For 96 both also
  * have room for zero-padded copies of the tensors, 128 wide.  Some of that room is used by no kernel of the default mode
  * and kept so that the sizes stay what callers know.  A chunk whose walks would be cut also runs in a somewhat smaller
  * workspace, one that holds its uncut schedule: nothing is cut then, and the results are other roundings of the same sums.

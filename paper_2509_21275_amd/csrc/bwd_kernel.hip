@@ -400,7 +400,7 @@ __device__ __forceinline__ void dkv_store4(const DkvParams& p, __bf16* out, int6
 }
 
 
-template <int D, int KB>  // KB: 32-key blocks per workgroup (2 KB waves)
+template <int D, int KB, bool CUT>  // KB: 32-key blocks per workgroup (2 KB waves); CUT: some items are pieces
 __global__ __launch_bounds__(KB * 128, D > 128 ? 1 : 4 / KB) void bwd_dkv_kernel(DkvParams p) {
   constexpr int NW = 2 * KB;   // waves
   constexpr int NTH = NW * 64; // threads
@@ -666,7 +666,14 @@ __global__ __launch_bounds__(KB * 128, D > 128 ? 1 : 4 / KB) void bwd_dkv_kernel
   }
 
   // ---- epilogue: dV = dV^T (wave A), dK = scale * dK^T (wave B), written (or added) as bf16 ----
-  {
+  if (CUT && it.part >= 0) {  // a piece: the accumulators as they are, put together by bwd_merge_kernel
+    float* const out = p.parts + ((int64_t)it.part * p.num_kv_heads + kvh) * kPartRowFloats + wave * part_unit_floats(D) + lane * 4;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<f32x4*>(out + (db * 4 + g) * 256) = f32x4{acc[db][4 * g], acc[db][4 * g + 1], acc[db][4 * g + 2], acc[db][4 * g + 3]};
+  } else {
     const int kr = 32 * kb + l32;
     if (kr < it.kv_rows) {
       const int64_t off = ((int64_t)it.kv_row0 + kr) * kv_stride + (int64_t)kvh * D;
@@ -2578,11 +2585,12 @@ template <int D>
 __global__ __launch_bounds__(256) void bwd_merge_kernel(DqParams pq, const DqItem* __restrict__ dq_cut, int dq_units, DkvParams pk,
                                                         const DkvItem* __restrict__ dkv_cut) {
   constexpr int NQ = D / 8 / 4;  // accumulator quarters per wave
+  constexpr int UNITS = D > 128 ? 4 : 8, KEY_UNITS = UNITS / 2;  // units per block, units of dV (then as many of dK)
   const int lane = threadIdx.x & 63, l32 = lane & 31, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const bool is_dq = (int)blockIdx.x < dq_units;
   const int x = is_dq ? blockIdx.x : blockIdx.x - dq_units;
-  const int unit = x & 7, block = x >> 3;
+  const int unit = x % UNITS, block = x / UNITS;
   const int inner_n = is_dq ? pq.num_kv_heads * pq.head_splits : pk.num_kv_heads, inner = block % inner_n;
   int part, pieces, row, rows, head = 0;
   int64_t row0;
@@ -2598,13 +2606,13 @@ __global__ __launch_bounds__(256) void bwd_merge_kernel(DqParams pq, const DqIte
     const DkvItem it = dkv_cut[block / inner_n];
     part = it.part;
     pieces = it.in_step;
-    row = (unit & 3) * 32 + l32;
+    row = unit % KEY_UNITS * 32 + l32;
     rows = it.kv_rows;
     row0 = it.kv_row0;
   }
   if (row >= rows) return;
   const int64_t step = (int64_t)inner_n * kPartRowFloats;
-  const float* src = (is_dq ? pq.parts : pk.parts) + part * step + (int64_t)inner * kPartRowFloats + unit * 4096 + wave * (NQ * 256) + lane * 4;
+  const float* src = (is_dq ? pq.parts : pk.parts) + part * step + (int64_t)inner * kPartRowFloats + unit * part_unit_floats(D) + wave * (NQ * 256) + lane * 4;
   f32x4 s[NQ];
 #pragma unroll
   for (int i = 0; i < NQ; ++i) s[i] = *reinterpret_cast<const f32x4*>(src + i * 256);
@@ -2620,8 +2628,8 @@ __global__ __launch_bounds__(256) void bwd_merge_kernel(DqParams pq, const DqIte
     for (int i = 0; i < NQ; ++i)
       *reinterpret_cast<bf16x4*>(op + 8 * i) = pack4(s[i][0] * pq.scale, s[i][1] * pq.scale, s[i][2] * pq.scale, s[i][3] * pq.scale);
   } else {
-    __bf16* const out = unit < 4 ? pk.dv : pk.dk;
-    const float f = unit < 4 ? 1.0f : pk.scale;
+    __bf16* const out = unit < KEY_UNITS ? pk.dv : pk.dk;
+    const float f = unit < KEY_UNITS ? 1.0f : pk.scale;
     const int64_t off = ((row0 + row) * pk.num_kv_heads + inner) * D + col;
 #pragma unroll
     for (int i = 0; i < NQ; ++i) dkv_store4(pk, out, off + 8 * i, s[i][0] * f, s[i][1] * f, s[i][2] * f, s[i][3] * f);
@@ -2658,6 +2666,12 @@ bool dkv_pipe_pays(const chunk_attn_desc* d, const Walks& w) {
   if (d->head_dim != 64) return stages >= 14 * blocks;
   return stages >= 24 * 2 * kCus && (blocks >= 3 * kCus || 4 * w.largest <= w.items || 10 * stages >= 9 * 2 * kCus * w.longest);
 }
+
+// The walks of bwd_dkv_kernel's blocks (head_dim 64 and 256) are cut like those of 96 and 128 (choose_tile_split; its step is 0.6 us at 64,
+// 1.4 at 256).  Backward, uncut / cut: head_dim 64, 1185 tokens behind 52, 32/8 heads, 134 / 71 us; 500 tokens, 64/8, 102 / 41; 4096
+// tokens 460 / 329; 6000 741 / 700; 24000 tokens, 8/2, 2829 / 2541; head_dim 256, 2412 tokens, 8/2, 541 / 228; 1024 tokens, 32/8, 246 / 143;
+// 3000 805 / 754.  What the estimate leaves alone (6500 tokens at 64, 3500 at 256) runs as before.
+constexpr int64_t kMaxShortParts = 2 * kCus;  // partial results of such a chunk (64 MB at most)
 
 // workgroups of the pipelined dK/dV kernels on a CU
 constexpr int dkv_per_cu(int head_dim) { return head_dim == 64 ? 2 : 1; }
@@ -2811,10 +2825,19 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
       // 4 ring slots of two 32-row operand tiles, 2 P hand-over slots, 4 slots of LSE and D rows
       constexpr int KB = (D > 128 ? 64 : DKV_KEYS) / 32;   // as dkv_keys(D)
       const size_t smem = (size_t)8 * 32 * D * 2 + 2 * KB * 1024 * 2 + 2 * 4 * 64 * sizeof(float);
-      static const hipError_t attr = raise_smem_limit(&bwd_dkv_kernel<D, KB>, smem);
-      if (attr != hipSuccess) return attr;
       if (pe.start && (e = hipEventRecord(pe.start, stream)) != hipSuccess) return e;
-      hipLaunchKernelGGL((bwd_dkv_kernel<D, KB>), dim3((unsigned)dkv_blocks), dim3(KB * 128), smem, stream, pk);
+      if (P.n_dkv_cut == 0) {
+        static const hipError_t attr = raise_smem_limit(&bwd_dkv_kernel<D, KB, false>, smem);
+        if (attr != hipSuccess) return attr;
+        hipLaunchKernelGGL((bwd_dkv_kernel<D, KB, false>), dim3((unsigned)dkv_blocks), dim3(KB * 128), smem, stream, pk);
+      } else {
+        static const hipError_t attr = raise_smem_limit(&bwd_dkv_kernel<D, KB, true>, smem);
+        if (attr != hipSuccess) return attr;
+        hipLaunchKernelGGL((bwd_dkv_kernel<D, KB, true>), dim3((unsigned)dkv_blocks), dim3(KB * 128), smem, stream, pk);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        hipLaunchKernelGGL((bwd_merge_kernel<D>), dim3((unsigned)(2 * KB * P.n_dkv_cut * d->num_kv_heads)), dim3(256), 0, stream, pq,
+                           static_cast<const DqItem*>(nullptr), 0, pk, reinterpret_cast<const DkvItem*>(ws + P.dkv_cut_off));
+      }
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
@@ -2848,6 +2871,8 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, bool may_c
     P.dkv_split = choose_tile_split(d, dkv_keys(d->head_dim), kCus,
                                     (int64_t)(dq_tile_bytes / ((size_t)d->num_kv_heads * kPartRowFloats * sizeof(float))));
   }
+  if (!pipe && !P.dkv_pipe && may_cut)
+    P.dkv_split = choose_tile_split(d, dkv_keys(d->head_dim), kCus, kMaxShortParts / d->num_kv_heads);
   if (with_plan) {
     if (P.fused) {
       P.fplan = plan_fused(d, dkv_keys(d->head_dim), kNumXcd, fused_num_bufs(d, dkv_keys(d->head_dim)));

@@ -80,7 +80,9 @@ constexpr int kCus = 256;        // compute units of an MI355X (plans that must 
 // rows][up to 16 accumulator quarters][64 lanes][4] float32; for the forward then [8 units][32 rows] {reference maximum, sum}.
 constexpr int kPartRowFloats = 8 * 16 * 64 * 4;
 constexpr int kPartFloats = kPartRowFloats + 8 * 32 * 2;
-// (a partial result of a dK/dV block of 128 keys has the same size: units 0 .. 3 are dV, 4 .. 7 dK of 32 keys each)
+// (a partial result of a dK/dV block has the same size: of 128 keys, units 0 .. 3 are dV, 4 .. 7 dK of 32 keys each; of 64 keys, head_dim
+// 256, two units of dV and two of dK, twice as large; head_dim 64 fills half of each unit)
+constexpr int part_unit_floats(int head_dim) { return head_dim > 128 ? 2 * 4096 : 4096; }
 
 // Whether a query-stationary kernel of head_dim 64 runs as the pipelined one: its workgroups start and end more slowly than
 // the other kernel's, which has three of them on a CU, and it puts twice the rows on a block.  So it needs two blocks per CU,

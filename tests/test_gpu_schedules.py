@@ -38,3 +38,44 @@ def test_schedules_on_both_sides_of_each_line(oracle_mod, n, hq, hk, d):
         o2, lse2 = torch.full_like(o, float("nan")), torch.full_like(lse, float("nan"))
         ca.chunk_attn_fwd_static(ca.make_desc(case.segs, hq, hk, d, case.total_q, case.total_kv, case.scale), q, k, v, o2, lse2)
         assert torch.equal(o, o2) and torch.equal(lse, lse2)
+
+
+@pytest.mark.parametrize("f32kv", [False, True])
+@pytest.mark.parametrize("d,segs,hq,hk", [
+    (64, [(0, 1100, 5, 1400), (1100, 77, 1410, 77)], 6, 2),      # pieces of three query heads per tile, a ragged last block
+    (64, [(0, 1025, 0, 1025)], 2, 2),                          # a last tile and a last block of one row each
+    (256, [(0, 700, 5, 900), (700, 33, 910, 33)], 6, 2),
+    (256, [(0, 1025, 0, 1025)], 1, 1),
+])
+def test_cut_dkv_walks_of_head_dims_64_and_256(oracle_mod, d, segs, hq, hk, f32kv):
+    """Against the oracle, with gradients added to what the buffers hold; a workspace without room for the pieces gives the uncut
+    walks' results, another float32 order of the same sums, rounded once: 2^-7 of the largest value in bf16, 1e-5 in float32."""
+    tq, tkv = max(s[0] + s[1] for s in segs), max(s[2] + s[3] for s in segs) + 3
+    case = synth.ChunkCase("cut_dkv", [synth.Seg(*s) for s in segs], tq, tkv, hq, hk, d, 40 + d)
+    desc = ca.make_desc(case.segs, hq, hk, d, tq, tkv, case.scale)
+    assert ca.chunk_attn_test_routes(desc) & (ca.ROUTE_DKV_CUT | ca.ROUTE_DKV_PIPELINED) == ca.ROUTE_DKV_CUT
+    q, k, v, do = make_inputs(case)
+    init = torch.full(k.shape, 3.0, device=q.device, dtype=torch.float32 if f32kv else torch.bfloat16)
+    got = run_gpu(case, q, k, v, do, accumulate=True, dk_init=init, dv_init=init, f32kv=f32kv)
+    again = run_gpu(case, q, k, v, do, accumulate=True, dk_init=init, dv_init=init, f32kv=f32kv)
+    assert all(torch.equal(a, b) for a, b in zip(got, again))
+    cov = torch.zeros(tkv, dtype=torch.bool)
+    for s in segs:
+        cov[s[2]:s[2] + s[3]] = True
+    orc = oracle_mod.Oracle(case.segs, q.cpu(), k.cpu(), v.cpu(), do.cpu(), case.scale)
+    orc.forward()
+    dQ, dK, dV = orc.backward()
+    assert rel_err(got[2], dQ) <= TOL_GRAD
+    for g, w in ((got[3], dK), (got[4], dV)):
+        assert torch.all(g.cpu()[~cov] == 3.0) and rel_err(g.cpu()[cov], w[cov.numpy()] + 3.0) <= TOL_GRAD
+
+    o, lse = got[:2]
+    dq, dk, dv = torch.empty_like(q), init.clone(), init.clone()
+    size = ca.chunk_attn_workspace_bytes(desc)[1]
+    small = torch.empty(size - 256, dtype=torch.uint8, device=q.device)  # (the pieces take more than that)
+    (ca.chunk_attn_bwd_f32kv if f32kv else ca.chunk_attn_bwd)(desc, q, k, v, o, do, lse, dq, dk, dv, 1, small)
+    torch.cuda.synchronize()
+    assert torch.equal(dq, got[2])
+    for a, b in ((dk, got[3]), (dv, got[4])):
+        assert rel_err(a, b.double().cpu().numpy()) <= (1e-5 if f32kv else 2.0 ** -7)
+        assert not f32kv or not torch.equal(a, b)  # (it did run uncut; bf16 may round both sums alike)
