@@ -84,8 +84,8 @@ typedef struct {
 
 /*
  * Scratch sizes (bytes) for a descriptor: *fwd_bytes for chunk_attn_fwd, *bwd_bytes for
- * chunk_attn_bwd.  Forward: the tile schedule, then room for transposed tile images of V (made for head_dim 256 only) or for
- * the float32 partial results of walks that are cut (96 and 128; up to 16 MiB where the images would be smaller).  Backward:
+ * chunk_attn_bwd.  Forward: the tile schedule, then room as for a transposed copy of V, used by
+ * the float32 partial results of walks that are cut (96 and 128; up to 16 MiB where the copy would be smaller).  Backward:
  * the schedules, the row sums D_i = <dO_i, O_i> and, for 96 and 128, float32 tiles of dQ or partial results, for 64 and 256
  * partial results of dK / dV walks that are cut (64 MB at most).  For 96 both also
  * have room for zero-padded copies of the tensors, 128 wide.  Some of that room is used by no kernel of the default mode
@@ -181,7 +181,7 @@ int chunk_attn_profile_events(void* start_event, void* stop_event);
 int chunk_attn_shutdown(void);
 
 /*
- * Test hook (not part of the method): the pipelined forward (head_dim 96 and 128, and 64 for large chunks) keeps the softmax reference
+ * Test hook (not part of the method): the pipelined forward (head_dim 96, 128 and 256, and 64 for large chunks) keeps the softmax reference
  * maximum of a row fixed after its first key tile and takes a block again, with the maximum over
  * all its keys, if the later scores of a row exceed it by more than 2^log2_growth (default 60; any
  * reference gives the same softmax).  A very negative value makes every block be taken twice.  Process-wide.  Always returns CHUNK_ATTN_OK.
@@ -242,7 +242,7 @@ int chunk_attn_test_bwd_status_offset(const chunk_attn_desc* desc, size_t* offse
  * Test hook: which kernels chunk_attn_fwd and chunk_attn_bwd choose for `desc` (given workspaces of the reported sizes), as
  * a sum of the bits below.  Decided on the host from the descriptor alone (and, for the last bit, the backward mode).
  */
-#define CHUNK_ATTN_ROUTE_FWD_PIPELINED 1 /* software-pipelined forward */
+#define CHUNK_ATTN_ROUTE_FWD_PIPELINED 1 /* software-pipelined forward of head_dim 64, 96 and 128 (256 has one kernel only) */
 #define CHUNK_ATTN_ROUTE_FWD_CUT 2       /* some of its walks over the keys are cut into pieces */
 #define CHUNK_ATTN_ROUTE_DQ_PIPELINED 4
 #define CHUNK_ATTN_ROUTE_DQ_CUT 8

@@ -177,18 +177,15 @@ inline chunk_attn_desc widened(const chunk_attn_desc* d) {
 }
 inline size_t padded_bytes(int64_t rows, int heads, size_t elem) { return align_up((size_t)rows * heads * kPaddedDim * elem); }
 
-// Forward workspace: [work items | whole items that were cut | transpose jobs | block-queue counters (zero)] (uploaded as one blob, unless
-// the kernel arguments carry the items) then the transposed V images (head_dim 256) or, for 96 and 128, the partial results of items
-// whose walks are cut.
+// Forward workspace: [work items | whole items that were cut | block-queue counters (zero)] (uploaded as one blob, unless
+// the kernel arguments carry the items) then, for 96 and 128, the partial results of items whose walks are cut.
 struct FwdLayout {
   int tile_rows;
   bool pipe;       // the pipelined kernel runs (head_dim 96 and 128, and 64 from a number of blocks on)
   KeySplit split;  // pipelined kernel: how the walks are cut
-  size_t n_items, n_wholes, wholes_off, jobs_off, queues_off, blob_bytes, vt_off, total;
+  size_t n_items, n_wholes, wholes_off, queues_off, blob_bytes, parts_off, total;
   int64_t blocks;
-  int64_t kv_tiles;
   std::vector<FwdItem> items, cut;  // what runs, and the whole items that were cut
-  std::vector<TileJob> jobs;
 };
 
 // Scratch memory of the forward that allocates nothing (chunk_attn_fwd_static), below.
@@ -200,13 +197,11 @@ void fill_fwd_lists(const chunk_attn_desc* d, FwdLayout& L) {
   L.items = cut_items(wholes, L.split.target);
   for (const FwdItem& w : wholes)
     if (w.part >= 0) L.cut.push_back(w);
-  if (d->head_dim > 128) L.jobs = tile_jobs(d, true, 64, nullptr);
 }
 
-// `may_cut`: false: no walk is cut whatever the chunk.  Partial results take the place of V images, which only head_dim 256
-// makes (the room for them stays part of the other sizes, as callers may know them), or up to the static forward's scratch memory where
-// the images would be smaller.  The cut is a function of the chunk alone, so that both entry points give the same bits; a workspace
-// too small for it, which older sizes may be, runs uncut.
+// `may_cut`: false: no walk is cut whatever the chunk.  Partial results take the room of a transposed copy of V, or up to the
+// static forward's scratch memory where that is smaller.  The cut is a function of the chunk alone, so that both entry points give the same
+// bits; a workspace too small for it, which older sizes may be, runs uncut.
 void layout_fwd(const chunk_attn_desc* desc, FwdLayout& L, bool with_plan, bool may_cut = true) {
   const chunk_attn_desc wide = widened(desc), *d = &wide;
   const int group = d->num_q_heads / d->num_kv_heads;
@@ -219,37 +214,35 @@ void layout_fwd(const chunk_attn_desc* desc, FwdLayout& L, bool with_plan, bool 
     walks = count_walks(d, L.tile_rows);
   }
   L.n_wholes = (size_t)walks.items;
-  L.kv_tiles = count_tiles(d, true, 64);
-  const size_t image_bytes = align_up((size_t)L.kv_tiles * d->num_kv_heads * d->head_dim * 64 * sizeof(__bf16));
+  // (as much as a transposed copy of V takes, which no kernel makes any more: the sizes stay what callers know)
+  const size_t room = align_up((size_t)count_tiles(d, true, 64) * d->num_kv_heads * d->head_dim * 64 * sizeof(__bf16));
   const size_t part_bytes = (size_t)inner * kPartFloats * sizeof(float);
-  // the fixed part of a layout with n items to run: [items | whole items, if any was cut | V tile jobs, if V images are
-  // made | the block-queue counters of the pipelined kernel (zero)]
+  // the fixed part of a layout with n items to run: [items | whole items, if any was cut | the block-queue counters (zero)]
   auto place = [&](size_t n_items) {
     L.n_items = n_items;
     L.wholes_off = n_items * sizeof(FwdItem);
-    L.jobs_off = L.wholes_off + (n_items == L.n_wholes ? 0 : L.n_wholes * sizeof(FwdItem));
-    L.queues_off = L.jobs_off + (d->head_dim <= 128 ? 0 : (size_t)L.kv_tiles * sizeof(TileJob));
+    L.queues_off = L.wholes_off + (n_items == L.n_wholes ? 0 : L.n_wholes * sizeof(FwdItem));
     L.blob_bytes = L.queues_off + kBlockQueues * sizeof(int32_t);
-    L.vt_off = align_up(L.blob_bytes);
+    L.parts_off = align_up(L.blob_bytes);
   };
   L.split = KeySplit{};
   place(L.n_wholes);
-  const size_t uncut_total = L.vt_off + image_bytes;
+  const size_t uncut_total = L.parts_off + room;
   // (not 64: with the two blocks per CU that pipe_pays asks for its walks are even enough; cut, 3032 queries on 51484 keys,
   // 64/64 heads, took 2587 us instead of 2443)
   if (pipelined(d->head_dim) && may_cut) {
     const size_t limit = std::max(uncut_total, kStaticScratchBytes);
-    L.split = choose_key_split(d, L.tile_rows, inner, kCus, (int64_t)((limit - L.vt_off) / part_bytes));
+    L.split = choose_key_split(d, L.tile_rows, inner, kCus, (int64_t)((limit - L.parts_off) / part_bytes));
     if (L.split.target > 0) {
       place((size_t)L.split.pieces);
-      if (L.vt_off + align_up((size_t)L.split.parts * part_bytes) > limit) {  // (the longer item list takes room, too)
+      if (L.parts_off + align_up((size_t)L.split.parts * part_bytes) > limit) {  // (the longer item list takes room, too)
         L.split = KeySplit{};
         place(L.n_wholes);
       }
     }
   }
   L.blocks = (int64_t)L.n_items * inner;
-  L.total = std::max(uncut_total, L.vt_off + align_up((size_t)L.split.parts * part_bytes));
+  L.total = std::max(uncut_total, L.parts_off + align_up((size_t)L.split.parts * part_bytes));
   if (is_narrow(desc))  // (as much as with padded copies of Q, K, V and O)
     L.total = std::max(L.total, uncut_total + 2 * padded_bytes(d->total_q, d->num_q_heads, 2) + 2 * padded_bytes(d->total_kv, d->num_kv_heads, 2));
   if (with_plan) fill_fwd_lists(desc, L);
@@ -281,26 +274,22 @@ hipError_t static_scratch(char** out) {
 }
 
 // The forward's schedule made on the device from a segment table passed by value: work items in segment order (their
-// order does not change any result) and the pieces of those that are cut, the 64-row tiles of V, and the block-queue counters cleared.
+// order does not change any result) and the pieces of those that are cut, and the block-queue counters cleared.
 // (Short lists of items travel as kernel arguments of the forward itself instead: fwd_inline.)
 struct StaticSegs {
   chunk_attn_seg seg[kStaticMaxSegments];
 };
 __global__ __launch_bounds__(256) void plan_fwd_static_kernel(StaticSegs segs, int n_seg, int tile_rows, FwdItem* wholes,
-                                                              int n_wholes, FwdItem* items, int target, TileJob* jobs,
-                                                              int n_jobs, int32_t* queues) {
-  __shared__ int item0[kStaticMaxSegments + 1], job0[kStaticMaxSegments + 1];
+                                                              int n_wholes, FwdItem* items, int target, int32_t* queues) {
+  __shared__ int item0[kStaticMaxSegments + 1];
   __shared__ int wave_items[4], wave_parts[4];
   if (threadIdx.x == 0) {
-    int ni = 0, nj = 0;
+    int ni = 0;
     for (int t = 0; t < n_seg; ++t) {
       item0[t] = ni;
-      job0[t] = nj;
       ni += (segs.seg[t].q_len + tile_rows - 1) / tile_rows;
-      nj += (segs.seg[t].kv_len + 63) / 64;
     }
     item0[n_seg] = ni;
-    job0[n_seg] = nj;
   }
   __syncthreads();
   // 256 whole items at a time; `items_before` and `parts_before` count the pieces of the items before them
@@ -319,7 +308,6 @@ __global__ __launch_bounds__(256) void plan_fwd_static_kernel(StaticSegs segs, i
       it.q_rows = min(tile_rows, s.q_len - i0);
       it.kv_row0 = s.kv_start;
       it.n0 = s.kv_len - s.q_len + i0 + 1;
-      it.kv_tile0 = job0[t];
       it.keys = s.kv_len;
       if (target <= 0) {  // nothing is cut: no pieces to number
         it.part = -1;
@@ -368,13 +356,6 @@ __global__ __launch_bounds__(256) void plan_fwd_static_kernel(StaticSegs segs, i
       it.part = n > 1 ? part : -1;
       wholes[x] = it;
     }
-  }
-  for (int x = threadIdx.x; x < n_jobs; x += 256) {
-    int t = 0;
-    while (t + 1 < n_seg && job0[t + 1] <= x) ++t;
-    const chunk_attn_seg s = segs.seg[t];
-    const int r = (x - job0[t]) * 64;
-    jobs[x] = TileJob{s.kv_start + r, min(64, s.kv_len - r), x, 0};
   }
   if (threadIdx.x < kBlockQueues) queues[threadIdx.x] = 0;
 }
@@ -439,12 +420,13 @@ NarrowBwdLayout narrow_bwd_layout(const chunk_attn_desc* d, size_t inner_bytes) 
 }
 
 // Whether the forward's kernel arguments carry its items: there is room for them, and no block is claimed through a counter in device
-// memory, which would have to be cleared first (head_dim 256 also needs its list of V tiles there).  Saves the launch that
+// memory, which would have to be cleared first.  Saves the launch that
 // would bring them, 3 us and as much of host time.  Forward and backward of 557 causal tokens, 32/8 heads, without any upload by the
 // runtime, with workgroups that find their block without a counter, and without the forward's second launch: 92 -> 73 us; 439
 // tokens, 8/2 heads, 87 -> 68; the static forward of 1501 + 203 keys next to 611 short rows 41 -> 30 us.
 bool fwd_inline(const FwdLayout& L, int head_dim) {
-  return head_dim <= 128 && L.n_items <= (size_t)kInlineItems && (!L.pipe || L.blocks <= persistent_grid(L.blocks, fwd_per_cu(head_dim)));
+  const bool claims = L.pipe || head_dim == 256;
+  return L.n_items <= (size_t)kInlineItems && (!claims || L.blocks <= persistent_grid(L.blocks, fwd_per_cu(head_dim)));
 }
 
 // Parameters and lists of a forward whose scratch memory is `ws`.
@@ -456,11 +438,9 @@ FwdParams fwd_params(const chunk_attn_desc* desc, const FwdLayout& L, char* ws, 
   p.v = static_cast<const __bf16*>(v);
   p.o = static_cast<__bf16*>(o);
   p.lse = lse;
-  p.vt = reinterpret_cast<const __bf16*>(ws + L.vt_off);
   p.items = items_inline ? nullptr : reinterpret_cast<const FwdItem*>(ws);
   p.wholes = items_inline ? nullptr : reinterpret_cast<const FwdItem*>(ws + L.wholes_off);
-  p.parts = reinterpret_cast<float*>(ws + L.vt_off);
-  p.total_kv_tiles = L.kv_tiles;
+  p.parts = reinterpret_cast<float*>(ws + L.parts_off);
   p.num_q_heads = desc->num_q_heads;
   p.num_kv_heads = desc->num_kv_heads;
   p.group = desc->num_q_heads / desc->num_kv_heads;
@@ -478,7 +458,6 @@ FwdLists fwd_lists(const FwdLayout& L) {
   l.num_blocks = (int)L.blocks;
   l.num_items = (int)L.n_items;
   l.num_wholes = (int)L.cut.size();
-  l.num_vjobs = (int)L.jobs.size();
   l.items = L.items.data();
   l.wholes = L.cut.data();
   return l;
@@ -631,14 +610,13 @@ int chunk_attn_fwd(const chunk_attn_desc* desc, const void* q, const void* k, co
     std::vector<char> blob(L.blob_bytes, 0);
     std::memcpy(blob.data(), L.items.data(), L.items.size() * sizeof(FwdItem));
     std::memcpy(blob.data() + L.wholes_off, L.cut.data(), L.cut.size() * sizeof(FwdItem));
-    std::memcpy(blob.data() + L.jobs_off, L.jobs.data(), L.jobs.size() * sizeof(TileJob));
     if ((e = upload_schedule(ws, blob, stream)) != hipSuccess) return hip_fail(e, "schedule upload");
   }
   const FwdParams p = fwd_params(desc, L, ws, items_inline, q, k, v, o, lse);
   ProfileEvents pe = profile_events();
   profile_events() = ProfileEvents{};
   if (pe.start && (e = hipEventRecord(pe.start, stream)) != hipSuccess) return hip_fail(e, "event record");
-  e = launch_fwd(p, desc->head_dim, L.pipe, fwd_lists(L), reinterpret_cast<const TileJob*>(ws + L.jobs_off), stream);
+  e = launch_fwd(p, desc->head_dim, L.pipe, fwd_lists(L), stream);
   if (e != hipSuccess) return hip_fail(e, "forward launch");
   if (pe.stop && (e = hipEventRecord(pe.stop, stream)) != hipSuccess) return hip_fail(e, "event record");
   return CHUNK_ATTN_OK;
@@ -665,16 +643,14 @@ int chunk_attn_fwd_static(const chunk_attn_desc* desc, const void* q, const void
   FwdLists lists = fwd_lists(L);
   if (!items_inline) {
     lists.num_wholes = L.split.target > 0 ? (int)L.n_wholes : 0;  // (with those that were not cut among them)
-    lists.num_vjobs = desc->head_dim <= 128 ? 0 : (int)L.kv_tiles;
     StaticSegs segs;
     for (int t = 0; t < desc->num_segments; ++t) segs.seg[t] = desc->segments[t];
     hipLaunchKernelGGL(plan_fwd_static_kernel, dim3(1), dim3(256), 0, stream, segs, desc->num_segments, L.tile_rows,
                        reinterpret_cast<FwdItem*>(ws + L.wholes_off), (int)L.n_wholes, reinterpret_cast<FwdItem*>(ws),
-                       L.split.target, reinterpret_cast<TileJob*>(ws + L.jobs_off), lists.num_vjobs,
-                       reinterpret_cast<int32_t*>(ws + L.queues_off));
+                       L.split.target, reinterpret_cast<int32_t*>(ws + L.queues_off));
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "schedule kernel launch");
   }
-  e = launch_fwd(p, desc->head_dim, L.pipe, lists, reinterpret_cast<const TileJob*>(ws + L.jobs_off), stream);
+  e = launch_fwd(p, desc->head_dim, L.pipe, lists, stream);
   if (e != hipSuccess) return hip_fail(e, "forward launch");
   return CHUNK_ATTN_OK;
 }

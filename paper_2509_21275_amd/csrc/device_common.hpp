@@ -146,6 +146,7 @@ __device__ __forceinline__ void wait_for_earlier_groups(const int32_t* ended, in
   }
 }
 __device__ __forceinline__ int broadcast_from_wave0(int* slot, int value) {
+  asm volatile("" ::: "memory");  // (the slot may lie in rows of another type that have just been read)
   if (threadIdx.x == 0) *(volatile int*)slot = value;
   __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
   asm volatile("" ::: "memory");

@@ -9,12 +9,11 @@
 // registers plus one exchange with the lane 32 away, and the bf16 probabilities are already laid out as the
 // B operand of O^T += V^T P^T (device_common.hpp, "C-order").
 //
-// Two kernels:
+// Three kernels:
 //   fwd_kernel       online softmax with a lazily moved reference maximum, one 32-row query block per wave,
-//                    tiles of 64 keys (K row-major, V as rows that are read transposed or,
-//                    for head_dim 256, as the pre-transposed image of transpose_kernel.hip, double-buffered).  Used
-//                    for head_dim 256, and for 64 unless its walks are long (pipe_pays).
-//                    head_dim 64 without the image and its launch: four sequences of 1024, 32/8 heads, 51 -> 42 us; 1024
+//                    tiles of 64 keys (rows, those of V read transposed, double-buffered).  Used for head_dim 64 unless its walks
+//                    are long (pipe_pays).
+//                    V as rows instead of a transposed image made by a launch before: four sequences of 1024, 32/8 heads, 51 -> 42 us; 1024
 //                    queries on 32768 keys 447 -> 390 us, 2048 on 18432, 8/2 heads, 253 -> 219.  (With one workgroup per
 //                    compute unit a tile's chain of copies, reads and products is what a step takes.  V in chunk-major
 //                    tiles, whose copies touch four times the cache lines: 460 - 490 and 264; rows, but all transposed
@@ -27,6 +26,7 @@
 //                    blocks to recompute this cost every call 4 us).  Where a chunk of 96 or
 //                    128 has too few items for the chip their walks are cut into pieces (plan.hpp); the pieces leave
 //                    float32 partial results, which fwd_merge_kernel puts together.
+//   fwd_wide_kernel  head_dim 256: the same with 32 query rows per wave.
 #include <cstring>
 #include <type_traits>
 
@@ -109,24 +109,21 @@ __global__ __launch_bounds__(256) void fwd_merge_kernel(FwdMergeArgs) {
   if (wave == 0 && hh == 0) p.lse[(int64_t)head * p.total_q + it.q_row0 + r] = (m + log2f(l)) * 0.6931471805599453f;
 }
 
-template <int D>
-__global__ __launch_bounds__(256, D > 128 ? 1 : 3) void fwd_kernel(FwdArgs) {
-  constexpr int WAVES = 4;
+__global__ __launch_bounds__(256, 3) void fwd_kernel(FwdArgs) {
+  constexpr int D = 64, WAVES = 4;
   constexpr int QB = 1;        // 32-row query blocks per wave
   constexpr int BN = 64;       // key rows per LDS tile
   constexpr int KC = D / 8;    // 16-byte chunks per K row
   constexpr int DK = D / 16;   // k-steps of S^T = K Q^T
   constexpr int DB = D / 32;   // 32-row blocks of O^T
-  constexpr int KT = BN * D;   // elements per K tile and per V^T image
+  constexpr int KT = BN * D;   // elements per tile
   constexpr int WR = 32 * QB;  // query rows per wave
-  constexpr bool ROWS = D == 64;  // V arrives as a row-major tile like K's (row_elem); else (IMG) as a transposed image
-  constexpr bool IMG = !ROWS;
   const FwdArgsPtr args = fwd_args();
   const FwdParams p = load_params(&args->p);
 
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  __bf16* Ks = reinterpret_cast<__bf16*>(smem);  // [2][BN][D]  swizzled rows
-  __bf16* Vs = Ks + 2 * KT;                      // [2][D][BN]  transposed image, or [2][BN][D]
+  __bf16* Ks = reinterpret_cast<__bf16*>(smem);  // [2][BN][D]  rows (row_elem)
+  __bf16* Vs = Ks + 2 * KT;                      // [2][BN][D]
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, kept in a scalar register
@@ -150,23 +147,20 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 3) void fwd_kernel(FwdArgs) {
 
   const int64_t q_stride = (int64_t)p.num_q_heads * D, kv_stride = (int64_t)p.num_kv_heads * D;
   const __bf16* __restrict__ Kg = p.k + (int64_t)it.kv_row0 * kv_stride + (int64_t)kvh * D;
-  const __bf16* __restrict__ Vimg = IMG ? p.vt + ((int64_t)kvh * p.total_kv_tiles + it.kv_tile0) * KT
-                                        : p.v + (int64_t)it.kv_row0 * kv_stride + (int64_t)kvh * D;
+  const __bf16* __restrict__ Vg = p.v + (int64_t)it.kv_row0 * kv_stride + (int64_t)kvh * D;
 
   // Per-lane source offsets of the global->LDS copies (elements).  A K tile is 64 rows x KC chunks; copy
   // instruction i of wave w fills LDS chunks [(WAVES i + w) 64, +64), so the lane fetches the chunk that the
-  // swizzle puts there.  The V^T image is copied linearly.
-  constexpr int PIECES = BN * KC / 64, NK = (PIECES + WAVES - 1) / WAVES, NV = NK;
-  static_assert(KT == BN * KC * 8 && PIECES % WAVES == 0, "a V tile has as many chunks as a K tile");
+  // swizzle puts there; a V tile likewise.
+  constexpr int PIECES = BN * KC / 64, NK = PIECES / WAVES;
+  static_assert(KT == BN * KC * 8 && PIECES % WAVES == 0, "the pieces of a tile divide evenly among the waves");
   unsigned k_src[NK];
   int k_row[NK];
 #pragma unroll
   for (int i = 0; i < NK; ++i) {
     const int x = (i * WAVES + wave) * 64 + lane;
     k_row[i] = x / KC;
-    int c = x % KC;
-    if constexpr (ROWS) c ^= row_swz(k_row[i]);
-    else c = unswz<KC>(k_row[i], c);
+    const int c = (x % KC) ^ row_swz(k_row[i]);
     k_src[i] = (unsigned)(k_row[i] * (int)kv_stride + c * 8);
   }
   auto dma_tile = [&](int t, int buf) {
@@ -176,7 +170,7 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 3) void fwd_kernel(FwdArgs) {
     __bf16* vdst = Vs + buf * KT;
     auto copy = [&](int i, unsigned off) __attribute__((always_inline)) {
       dma16(ksrc + off, kdst + (i * WAVES + wave) * 512);
-      if constexpr (ROWS) dma16(Vimg + (int64_t)(BN * t) * kv_stride + off, vdst + (i * WAVES + wave) * 512);
+      dma16(Vg + (int64_t)(BN * t) * kv_stride + off, vdst + (i * WAVES + wave) * 512);
     };
     if (last_row >= BN - 1) {
 #pragma unroll
@@ -184,20 +178,12 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 3) void fwd_kernel(FwdArgs) {
     } else {
 #pragma unroll
       for (int i = 0; i < NK; ++i) {
-        int row = k_row[i];
-        if constexpr (ROWS) {  // (computed here, and not kept for the length of the loop)
-          int ln = threadIdx.x & 63;
-          asm volatile("" : "+v"(ln));
-          row = ((i * WAVES + wave) * 64 + ln) / KC;
-        }
+        // (the row is computed here, and not kept for the length of the loop)
+        int ln = threadIdx.x & 63;
+        asm volatile("" : "+v"(ln));
+        const int row = ((i * WAVES + wave) * 64 + ln) / KC;
         copy(i, k_src[i] - (unsigned)((row - min(row, last_row)) * (int)kv_stride));
       }
-    }
-    if constexpr (IMG) {
-      const __bf16* vsrc = Vimg + (int64_t)t * KT;            // wave-uniform
-#pragma unroll
-      for (int i = 0; i < NV; ++i)
-        dma16(vsrc + (unsigned)(((i * WAVES + wave) * 64 + lane) * 8), vdst + (i * WAVES + wave) * 512);
     }
   };
 
@@ -230,16 +216,9 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 3) void fwd_kernel(FwdArgs) {
 
   // LDS operand addresses (elements).  Row l32 and row 32 + l32 share their swizzle, so the second block of
   // each tile is a constant offset away; the buffer index is a compile-time constant of the unrolled loop.
-  int k_off[DK], v_off[4];
-#pragma unroll
-  for (int ks = 0; ks < DK; ++ks) {
-    if constexpr (ROWS) k_off[ks] = row_elem(l32, 2 * ks + hh);
-    else k_off[ks] = tile_elem<KC>(l32, 2 * ks + hh);
-  }
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks) v_off[ks] = tile_elem<8>(l32, 2 * ks + hh);
-  unsigned vt_lo = 0;  // byte addresses of the transposed reads (as in the pipelined kernel) in buffer 0
-  if constexpr (!IMG) {
+  int k_off = row_elem(l32, hh);  // (chunks 2 ks + hh are an XOR apart)
+  unsigned vt_lo;  // byte address of the transposed reads (as in the pipelined kernel) in buffer 0
+  {
     const int j = lane & 15, cl = 2 * ((lane >> 4) & 1) + ((j & 3) >> 1), r0 = 4 * hh + (j >> 2);
     vt_lo = lds_addr((lds_bf16*)Vs + row_elem(r0, cl) + 4 * (j & 1));
   }
@@ -257,7 +236,6 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 3) void fwd_kernel(FwdArgs) {
 
     if (t < nt_w) {
       const __bf16* Kt = Ks;
-      const __bf16* Vt = Vs;
       s16x4 v_lo[4][DB], v_hi[4][DB];
       auto read_vt = [&](auto ks_c) __attribute__((always_inline)) {
         static_for<0, DB>([&](auto db_c) __attribute__((always_inline)) {
@@ -269,47 +247,36 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 3) void fwd_kernel(FwdArgs) {
       };
       // ---- S^T = K Q^T : [64 keys] x [32 QB queries]; every K fragment feeds QB products ----
       f32x16 s0[QB], s1[QB];
-      auto ldk = [&](int ks, int half) {  // (ROWS: chunks 2 ks + hh are an XOR apart, so that one address is kept)
-        return *reinterpret_cast<const bf16x8*>(Kt + (ROWS ? k_off[0] ^ (16 * ks) : k_off[ks]) + half * (32 * D));
-      };
+      auto ldk = [&](int ks, int half) { return *reinterpret_cast<const bf16x8*>(Kt + (k_off ^ (16 * ks)) + half * (32 * D)); };
       auto mma_s = [&](int ks, bf16x8 a, f32x16 (&d)[QB]) __attribute__((always_inline)) {
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) d[qb] = mfma32(a, qf[qb][ks], ks == 0 ? zero16 : d[qb]);
       };
-      if constexpr (ROWS) {
-        // the K fragments first, the second half while the first one's products run; a quarter of the V^T fragments behind each
-        // of the last four products, where the wave has nothing else to issue: they arrive while the exponentials are computed
-        bf16x8 a[4][2];
+      // the K fragments first, the second half while the first one's products run; a quarter of the V^T fragments behind each
+      // of the last four products, where the wave has nothing else to issue: they arrive while the exponentials are computed
+      bf16x8 a[4][2];
 #pragma unroll
-        for (int x = 0; x < 4; ++x) a[x >> 1][x & 1] = ldk(x >> 1, x & 1);
-        __builtin_amdgcn_sched_barrier(0);
+      for (int x = 0; x < 4; ++x) a[x >> 1][x & 1] = ldk(x >> 1, x & 1);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int x = 4; x < 8; ++x) a[x >> 1][x & 1] = ldk(x >> 1, x & 1);
+      for (int x = 4; x < 8; ++x) a[x >> 1][x & 1] = ldk(x >> 1, x & 1);
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-          mma_s(ks, a[ks][0], s0);
-          mma_s(ks, a[ks][1], s1);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        static_for<2, 4>([&](auto ks_c) __attribute__((always_inline)) {
-          constexpr int ks = decltype(ks_c)::value;
-          mma_s(ks, a[ks][0], s0);
-          __builtin_amdgcn_sched_barrier(0);
-          read_vt(std::integral_constant<int, 2 * ks - 4>{});
-          __builtin_amdgcn_sched_barrier(0);
-          mma_s(ks, a[ks][1], s1);
-          __builtin_amdgcn_sched_barrier(0);
-          read_vt(std::integral_constant<int, 2 * ks - 3>{});
-          __builtin_amdgcn_sched_barrier(0);
-        });
-      } else {
-#pragma unroll
-        for (int ks = 0; ks < DK; ++ks) {
-          const bf16x8 a0 = ldk(ks, 0), a1 = ldk(ks, 1);
-          mma_s(ks, a0, s0);
-          mma_s(ks, a1, s1);
-        }
+      for (int ks = 0; ks < 2; ++ks) {
+        mma_s(ks, a[ks][0], s0);
+        mma_s(ks, a[ks][1], s1);
       }
+      __builtin_amdgcn_sched_barrier(0);
+      static_for<2, 4>([&](auto ks_c) __attribute__((always_inline)) {
+        constexpr int ks = decltype(ks_c)::value;
+        mma_s(ks, a[ks][0], s0);
+        __builtin_amdgcn_sched_barrier(0);
+        read_vt(std::integral_constant<int, 2 * ks - 4>{});
+        __builtin_amdgcn_sched_barrier(0);
+        mma_s(ks, a[ks][1], s1);
+        __builtin_amdgcn_sched_barrier(0);
+        read_vt(std::integral_constant<int, 2 * ks - 3>{});
+        __builtin_amdgcn_sched_barrier(0);
+      });
       bf16x8 pf[QB][4];
 #pragma unroll
       for (int qb = 0; qb < QB; ++qb) {
@@ -368,36 +335,21 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 3) void fwd_kernel(FwdArgs) {
         l_run[qb] += ps0 + ps1;
       }
       // ---- O^T += V^T P^T : [D] x [32 QB queries], contraction over the 64 keys; every V^T fragment feeds QB products ----
-      if constexpr (IMG) {
+      static_for<0, 4>([&](auto ks_c) __attribute__((always_inline)) {
+        constexpr int ks = decltype(ks_c)::value;
+        if constexpr (ks == 0) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
+        for (int db = 0; db < DB; ++db) {
+          asm volatile("" : "+v"(v_lo[ks][db]), "+v"(v_hi[ks][db]));  // (after the wait, in this order)
+          const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(v_lo[ks][db], v_hi[ks][db], 0, 1, 2, 3, 4, 5, 6, 7));
 #pragma unroll
-          for (int db = 0; db < DB; ++db) {
-            const bf16x8 a = *reinterpret_cast<const bf16x8*>(Vt + v_off[ks] + db * 32 * 64);
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) oacc[qb][db] = mfma32(a, pf[qb][ks], oacc[qb][db]);
-          }
+          for (int qb = 0; qb < QB; ++qb) oacc[qb][db] = mfma32(a, pf[qb][ks], oacc[qb][db]);
         }
-      } else {
-        static_for<0, 4>([&](auto ks_c) __attribute__((always_inline)) {
-          constexpr int ks = decltype(ks_c)::value;
-          if constexpr (ks == 0) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-          for (int db = 0; db < DB; ++db) {
-            asm volatile("" : "+v"(v_lo[ks][db]), "+v"(v_hi[ks][db]));  // (after the wait, in this order)
-            const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(v_lo[ks][db], v_hi[ks][db], 0, 1, 2, 3, 4, 5, 6, 7));
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) oacc[qb][db] = mfma32(a, pf[qb][ks], oacc[qb][db]);
-          }
-        });
-      }
+      });
     }
 
     buf ^= 1;
-#pragma unroll
-    for (int ks = 0; ks < DK; ++ks) k_off[ks] ^= KT;
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) v_off[ks] ^= KT;
+    k_off ^= KT;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
   }
@@ -914,6 +866,388 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void fwd_pipe_kernel(FwdArgs)
   clock_log_stamp(p.clock_log, 1);
 }
 
+// ------------------------------------------------------------------------------------------------
+// Pipelined forward for head_dim 256: one wave per SIMD, 32 query rows per wave (Q fragments and O^T take 192 accumulation
+// registers; 64 rows would take 384), keys streamed in stages of 32.
+//
+// A step runs the three pieces of fwd_pipe_kernel -- O^T += V(t-1)^T P^T(t-1), S^T(t+1) = K(t+1) Q^T, P^T(t) = exp2(S^T(t) c - m c) -- as
+// 16 mini-steps of one K row fragment and the S MFMA it feeds, one V^T fragment and the O MFMA it feeds, and the vector work of one
+// score.  Every fragment feeds one MFMA only, so a step is bound by what a wave can issue: 48 LDS reads (16 cycles each) and 32 MFMAs
+// (32 each), against half as many reads per MFMA at head_dim 128; the vector work, half of that per MFMA, hides under them.
+// LDS holds four stages of K (t + 1 and, read ahead over the end of the step, t + 2 in use in step t; t + 3 and t + 4 on their way) and
+// five of V (t - 1 and t in use, t + 1 and t + 2 on their way); a copy has more than a step to land.  Q comes in and O goes
+// out through 64 KB of the V ring and behind it, which no stage needs at either end.
+// The reference maximum, blocks that outgrow it and the masked steps as in fwd_pipe_kernel.
+// Against fwd_kernel's scheme, which it replaces here (online softmax, no pipelining, V^T images made by a launch before; 32/8 heads):
+// packed 64K chunk 10.9 -> 8.2 ms, 8192 queries on 32768 keys 10.0 -> 7.2, 64 sequences of 256 329 -> 259 us, 909 queries on 5603 keys 252 -> 175,
+// 148 on 595, 8/2 heads, 39 -> 29.  Two to five fragments read ahead and either order of a mini-step's reads make no difference.
+// ------------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(256, 1) void fwd_wide_kernel(FwdArgs) {
+  constexpr int D = 256;
+  const FwdArgsPtr args = fwd_args();
+  const FwdParams p = load_params(&args->p);
+  const int num_blocks = args->num_blocks;
+  constexpr int NW = 4;        // waves
+  constexpr int BN = 32;       // key rows per stage
+  constexpr int KC = D / 8;    // 16-byte chunks per K / V row
+  constexpr int DK = D / 16;   // k-steps of S^T = K Q^T
+  constexpr int DB = D / 32;   // 32-row blocks of O^T
+  constexpr int KT = BN * D;   // elements per tile
+  constexpr int KS = 4, VS = 5;        // ring slots of K and of V
+  constexpr int NF = DK;               // mini-steps per step
+  constexpr int AHEAD = 3, RING = 4;   // fragments (of each kind) in flight, registers of the fragment rings
+  constexpr int PER = BN * KC / 64 / NW;  // global->LDS copies per wave, tile and stage
+  static_assert(2 * DB == DK && NF % RING == 0 && RING > AHEAD && 1 + PER * 3 < NF, "the schedule of a step");
+
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  lds_bf16* const L = (lds_bf16*)smem;
+  constexpr int K_OFF = 0;               // [KS][KT]  K rows of stage n in slot n % KS (chunk-major)
+  constexpr int V_OFF = K_OFF + KS * KT; // [VS][KT]  V rows of stage n in slot n % VS
+  // [NW][32][D] staging of a wave's 32 rows, rows of swizzled 16-byte chunks: V slots 2 .. 4 and the tile behind them.  Its first word (of
+  // wave 0's tile) doubles as the slot through which wave 0 announces the next block.
+  constexpr int ST_OFF = V_OFF + 2 * KT;
+  constexpr int X_OFF = V_OFF + VS * KT; // the tile behind the V ring: nobody's while the steps run, but for the waves' words
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, hh = lane >> 5;
+  __bf16* const stage = (__bf16*)smem + ST_OFF + wave * KT;
+  int* const next_block = (int*)((__bf16*)smem + ST_OFF);
+  volatile int* const outgrown = (volatile int*)((__bf16*)smem + X_OFF);  // some wave has seen a row outgrow its reference maximum
+
+  const int xcd = xcd_of_this_wave();
+  const bool direct = num_blocks <= (int)gridDim.x;
+  int blk = blockIdx.x;
+  if (!direct) {
+    if (wave == 0) blk = block_claim_finish(p.taken, num_blocks, xcd, block_claim_issue(p.taken, xcd));
+    blk = broadcast_from_wave0(next_block, blk);
+  }
+  bool again = false;  // the block is taken a second time, with every row's true maximum
+  int pending_claim = 0;
+  while (blk >= 0) {
+  wg_barrier();  // every wave has read the announcement: the staging area may be written again
+  const int inner_n = p.num_kv_heads * p.head_splits;
+  const int inner = __builtin_amdgcn_readfirstlane(blk % inner_n);
+  const FwdItem it = load_item(p.items, args->items, __builtin_amdgcn_readfirstlane(blk / inner_n));
+  const int kvh = __builtin_amdgcn_readfirstlane(inner % p.num_kv_heads), hs = inner / p.num_kv_heads;
+  const int head = kvh * p.group + hs * p.heads_per_wg + wave % p.heads_per_wg;
+  const int wave_row0 = (wave / p.heads_per_wg) * 32;  // the wave's rows are wave_row0 .. + 31 of `head`
+  const int n_wg = it.n0 + it.q_rows - 1;              // keys the last valid row sees
+  const int nt = (n_wg + BN - 1) / BN;                 // stages
+
+  const int64_t q_stride = (int64_t)p.num_q_heads * D, kv_stride = (int64_t)p.num_kv_heads * D;
+  const __bf16* __restrict__ Kg = p.k + (int64_t)it.kv_row0 * kv_stride + (int64_t)kvh * D;
+  const __bf16* __restrict__ Vg = p.v + (int64_t)it.kv_row0 * kv_stride + (int64_t)kvh * D;
+
+  // ---- staging: copy i of a wave is piece 4 i + wave of a tile, 64 consecutive slots = two chunk columns of 32 rows.  Past the last
+  // stage the last one is copied again. ----
+  unsigned v_full[PER], v_last[PER];  // byte offset of the lane's chunk from the tile's first row: full tile, last tile
+  {
+    const int last_row = n_wg - 1 - (nt - 1) * BN;  // rows past the last key repeat it (masked)
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int x = (i * NW + wave) * 64 + lane;
+      const int off = (x >> 5) * 8, row = (x & 31) ^ (((x >> 5) & 3) << 2);
+      v_full[i] = (unsigned)(row * (int)kv_stride + off) * 2u;
+      v_last[i] = (unsigned)(min(row, last_row) * (int)kv_stride + off) * 2u;
+    }
+  }
+  struct Stream {  // the next stage to copy, its first row, its slot
+    int t, slot;
+    const char* row;
+  };
+  Stream ks{0, 0, reinterpret_cast<const char*>(Kg)}, vs{0, 0, reinterpret_cast<const char*>(Vg)};
+  auto copy_piece = [&](const Stream& st, int ring, int i) __attribute__((always_inline)) {
+    dma16(st.row + (st.t == nt - 1 ? v_last[i] : v_full[i]), L + ring + st.slot * KT + (i * NW + wave) * 512);
+  };
+  auto advance = [&](Stream& st, int slots) __attribute__((always_inline)) {
+    if (st.t + 1 < nt) {
+      ++st.t;
+      st.row += BN * kv_stride * 2;
+    }
+    st.slot = st.slot == slots - 1 ? 0 : st.slot + 1;
+  };
+
+  // per-lane operand addresses inside a tile (as in fwd_pipe_kernel)
+  int x_off[2], t_off[2];
+#pragma unroll
+  for (int par = 0; par < 2; ++par) x_off[par] = cm_elem(l32, 2 * par + hh);
+  {
+    const int j = lane & 15, grp = (lane >> 4) & 1;
+    const int cl = 2 * grp + ((j & 3) >> 1);
+    const int r0 = 4 * hh + (j >> 2);
+#pragma unroll
+    for (int half = 0; half < 2; ++half) t_off[half] = cm_elem(r0 + 8 * half, cl) + 4 * (j & 1);
+  }
+  const unsigned k_ev0 = lds_addr(L + K_OFF + x_off[0]), k_od0 = lds_addr(L + K_OFF + x_off[1]);
+  const unsigned t_lo0 = lds_addr(L + V_OFF + t_off[0]), t_hi0 = lds_addr(L + V_OFF + t_off[1]);
+  constexpr unsigned SLOT = KT * 2;  // bytes per ring slot
+  auto load_rows = [&](unsigned ev_addr, unsigned od_addr, auto ks_c) __attribute__((always_inline)) {
+    constexpr int k = decltype(ks_c)::value;
+    return lds_asm_read16<(k >> 1) * (4 * 32 * 8) * 2>((k & 1) ? od_addr : ev_addr);
+  };
+  auto load_t = [&](unsigned lo_addr, unsigned hi_addr, auto m_c) __attribute__((always_inline)) {
+    constexpr int m = decltype(m_c)::value;  // ks2 * DB + db
+    constexpr int off = ((m / DB) * (16 * 8) + (m % DB) * (4 * 32 * 8)) * 2;
+    const s16x4 lo = lds_asm_read_tr<off>(lo_addr);
+    const s16x4 hi = lds_asm_read_tr<off>(hi_addr);
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
+
+  // prologue: K of stages 0 .. 3, V of stages 0 and 1, the wave's rows of Q
+#pragma unroll
+  for (int n = 0; n < KS; ++n) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) copy_piece(ks, K_OFF, i);
+    advance(ks, KS);
+  }
+#pragma unroll
+  for (int n = 0; n < 2; ++n) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) copy_piece(vs, V_OFF, i);
+    advance(vs, VS);
+  }
+  {
+    const __bf16* qbase = p.q + (int64_t)it.q_row0 * q_stride + (int64_t)head * D;
+#pragma unroll 4
+    for (int i = 0; i < 32 * KC / 64; ++i) {
+      const int x = i * 64 + lane;
+      const int row = x / KC, c = unswz<KC>(row, x % KC);
+      const int r = min(wave_row0 + row, it.q_rows - 1);  // rows past the tile repeat the last one (never stored)
+      dma16(qbase + (int64_t)r * q_stride + c * 8, stage + i * 512);
+    }
+  }
+  // One wait the compiler can see for everything issued so far: it then has no reason to put full waits for outstanding
+  // loads into the loop.
+  __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
+  // Q fragments (B operands of S^T = K Q^T): lane holds Q[row = l32][16 ks + 8 hh ..+7]
+  bf16x8 qf[DK];
+#pragma unroll
+  for (int k = 0; k < DK; ++k) qf[k] = lds_chunk<KC>(stage, l32, 2 * k + hh);
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (in this order: the compiler takes what is written below and the rows for unrelated)
+  if (wave == 2) {  // V(-1), read in step 0: its slot is this wave's staging tile
+    bf16x8 z;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) z[i] = (__bf16)0.0f;
+    static_assert(ST_OFF + 2 * KT == V_OFF + (VS - 1) * KT, "the slot of V(-1)");
+    for (int x = lane; x < KT / 8; x += 64) lds_store8(L + V_OFF + (VS - 1) * KT + x * 8, z);
+  }
+  if (wave == 3) *outgrown = 0;  // (its staging tile)
+  // (the fragments settle in their accumulation registers here: an opaque MFMA must not follow a write to one of its operands)
+#pragma unroll
+  for (int k = 0; k < DK; ++k) asm volatile("" : "+a"(qf[k]));
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  wg_barrier();
+
+  const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  f32x16 oacc[DB];
+#pragma unroll
+  for (int db = 0; db < DB; ++db) oacc[db] = zero16;
+  f32x16 x[2];       // S^T, two buffers
+  bf16x8 f[2][2];    // P^T as B operands: [buffer][k-step]
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) f[b][k][i] = (__bf16)0.0f;
+  const float c = p.scale_log2;
+  bf16x8 fv[RING], fk[RING];  // rings of V^T and of K fragments
+
+  // S^T(0) = K(0) Q^T and the reference maximum of each row
+  float mc, l_run = 0.f;
+  {
+    bf16x8 a[DK];
+    static_for<0, DK>([&](auto ks_c) __attribute__((always_inline)) { a[decltype(ks_c)::value] = load_rows(k_ev0, k_od0, ks_c); });
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int k = 0; k < DK; ++k) asm volatile("" : "+v"(a[k]));  // (after the wait, in this order)
+    wg_barrier();  // every wave has read K(0): step 0 copies K(4) over it
+#pragma unroll
+    for (int k = 0; k < DK; ++k) {
+      f32x16& d_ = x[0];
+      const bf16x8& b_ = qf[k];
+      if (k == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d_) : "v"(a[k]), "a"(b_));
+      else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d_) : "v"(a[k]), "a"(b_));
+    }
+    mfma_settle();
+    asm volatile("s_nop 15" : "+v"(x[0]));  // the reads below come after the MFMAs have written
+    const int lim = it.n0 + wave_row0 + l32;  // stage 0: visible iff local key index < lim (>= 1)
+    float mx = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      if (8 * (i >> 2) + 4 * hh + (i & 3) < lim) mx = fmaxf(mx, x[0][i]);
+    mc = max_halves(mx) * c;
+  }
+  if (__builtin_expect(again, 0)) {  // the maximum over all stages: S^T as in the loop, K read from global memory
+    float mx = -INFINITY;
+    for (int n = 0; n < nt; ++n) {
+      const __bf16* kr = Kg + (int64_t)min(BN * n + l32, n_wg - 1) * kv_stride + 8 * hh;
+      f32x16 d = zero16;
+#pragma unroll
+      for (int k = 0; k < DK; ++k) d = mfma32(*reinterpret_cast<const bf16x8*>(kr + 16 * k), qf[k], d);
+      const int lim = it.n0 + wave_row0 + l32 - BN * n;
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (8 * (i >> 2) + 4 * hh + (i & 3) < lim) mx = fmaxf(mx, d[i]);
+    }
+    mc = max_halves(mx) * c;
+  }
+  bool risk = false;
+  const float big = __builtin_amdgcn_exp2f(p.ref_limit);
+
+  // the first fragments of step 0: V(-1) (zeros) and K(1)
+  {
+    const unsigned sT = (VS - 1) * SLOT;
+    static_for<0, AHEAD>([&](auto m_c) __attribute__((always_inline)) {
+      constexpr int m = decltype(m_c)::value;
+      fv[m] = load_t(t_lo0 + sT, t_hi0 + sT, m_c);
+      fk[m] = load_rows(k_ev0 + SLOT, k_od0 + SLOT, m_c);
+    });
+  }
+
+  // Mini-step m reads the fragments of mini-step m + AHEAD (past the end: the next step's first ones), three instructions, so that
+  // "the fragments of mini-step m have arrived" is "at most 3 (AHEAD - 1) LDS reads are outstanding" at its start.
+  int sV = 0, sK = 1;  // slots of V(t) and of K(t + 1)
+  auto step = [&](int t, f32x16& cur, f32x16& nxt, bf16x8 (&f_old)[2], bf16x8 (&f_new)[2], auto masked_c) __attribute__((always_inline)) {
+    constexpr bool MASKED = decltype(masked_c)::value;
+    const int sM = sV == 0 ? VS - 1 : sV - 1, sN = sK == KS - 1 ? 0 : sK + 1;  // V(t - 1), K(t + 2)
+    const unsigned t_lo = t_lo0 + sM * SLOT, t_hi = t_hi0 + sM * SLOT, n_lo = t_lo0 + sV * SLOT, n_hi = t_hi0 + sV * SLOT;
+    const unsigned k_ev = k_ev0 + sK * SLOT, k_od = k_od0 + sK * SLOT, n_ev = k_ev0 + sN * SLOT, n_od = k_od0 + sN * SLOT;
+    // MASKED: element i (key 8 (i / 4) + 4 hh + i % 4 of the stage) is visible iff 8 (i / 4) + i % 4 < lim
+    int lim = 0;
+    if (MASKED) lim = t < nt ? it.n0 + wave_row0 + l32 - BN * t - 4 * hh : -0x40000000;
+    unsigned pw[8];  // P^T(t), packed pairs
+    float ps = 0.f;
+    float e_hold[2];
+    // (a pair is converted one mini-step after its exponentials: a transcendental result cannot be consumed by the very next instruction)
+    auto finish_pair = [&](int j) __attribute__((always_inline)) {
+      bf16x2 w;
+      w[0] = (__bf16)e_hold[0]; w[1] = (__bf16)e_hold[1];
+      ps += e_hold[0] + e_hold[1];
+      asm volatile("" : "+v"(ps));
+      unsigned wu = __builtin_bit_cast(unsigned, w);
+      asm volatile("" : "+v"(wu));
+      pw[j] = wu;
+    };
+    asm volatile("s_nop 7" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<0, NF>([&](auto m_c) __attribute__((always_inline)) {
+      constexpr int m = decltype(m_c)::value;
+      asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(fv[m % RING]), "+v"(fk[m % RING]) : "n"(3 * (AHEAD - 1)));
+      {
+        constexpr int mm = m + AHEAD;
+        if constexpr (mm < NF) {
+          fk[mm % RING] = load_rows(k_ev, k_od, std::integral_constant<int, mm>{});
+          fv[mm % RING] = load_t(t_lo, t_hi, std::integral_constant<int, mm>{});
+        } else {
+          fk[mm % RING] = load_rows(n_ev, n_od, std::integral_constant<int, mm - NF>{});
+          fv[mm % RING] = load_t(n_lo, n_hi, std::integral_constant<int, mm - NF>{});
+        }
+      }
+      {
+        const bf16x8& a_ = fk[m % RING];
+        f32x16& d_ = nxt;
+        const bf16x8& b_ = qf[m];
+        if (m == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d_) : "v"(a_), "a"(b_));
+        else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d_) : "v"(a_), "a"(b_));
+      }
+      // K(t + 4) and V(t + 2), one copy in mini-steps 1, 2, 4, 5, 7, 8, 10, 11
+      if constexpr (m % 3 != 0 && m / 3 < PER) {
+        if constexpr (m % 3 == 1) copy_piece(ks, K_OFF, m / 3);
+        else copy_piece(vs, V_OFF, m / 3);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      oacc[m % DB] = mfma32(fv[m % RING], f_old[m / DB], oacc[m % DB]);
+      {  // the vector work of score m
+        if constexpr (m > 0 && m % 2 == 0) finish_pair(m / 2 - 1);
+        float tt = cur[m] * c - mc;
+        if (MASKED) {
+          if (8 * (m >> 2) + (m & 3) >= lim) tt = -INFINITY;
+        }
+        e_hold[m % 2] = __builtin_amdgcn_exp2f(tt);
+        asm volatile("" : "+v"(e_hold[m % 2]));
+      }
+      if constexpr (m == NF - 2) {  // bookkeeping for the next step (this step's copies have been issued)
+        advance(ks, KS);
+        advance(vs, VS);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    finish_pair(7);
+    sV = sV == VS - 1 ? 0 : sV + 1;
+    sK = sN;
+    risk |= !(ps < big);
+    l_run += ps;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      u32x4 v = {pw[4 * k], pw[4 * k + 1], pw[4 * k + 2], pw[4 * k + 3]};
+      f_new[k] = __builtin_bit_cast(bf16x8, v);
+    }
+    // the copies of the step before (K(t + 3), V(t + 1)) must have landed; this step's may still be in flight
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * PER) : "memory");
+    wg_barrier();
+  };
+
+  // (as in fwd_pipe_kernel)
+  const int t_full = min(nt, (it.n0 + wave_row0) / BN) & ~1;
+  int t = 0;
+  for (; t < t_full; t += 2) {
+    step(t, x[0], x[1], f[0], f[1], std::false_type{});
+    step(t + 1, x[1], x[0], f[1], f[0], std::false_type{});
+  }
+  if (wave == 0 && !again && !direct) pending_claim = block_claim_issue(p.taken, xcd);
+  for (; t <= nt; t += 2) {
+    step(t, x[0], x[1], f[0], f[1], std::true_type{});
+    if (__builtin_expect(__any(risk), 0)) *outgrown = 1;
+    step(t + 1, x[1], x[0], f[1], f[0], std::true_type{});
+  }
+  // the last step's reads ahead are nobody's operands; their registers stay taken until they have arrived
+#pragma unroll
+  for (int i = 0; i < RING; ++i) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(fv[i]), "+v"(fk[i]));
+  // every copy of this wave has landed (the last ones rewrote slots nobody reads)
+  __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
+  const bool retake = __builtin_amdgcn_readfirstlane(*outgrown) != 0 && !again;
+  wg_barrier();  // nobody reads the rings, and nobody copies into them, any more: O may be staged there
+  if (__builtin_expect(retake, 0)) {  // (the same for all waves)
+    again = true;
+    continue;
+  }
+  again = false;
+
+  // ---- epilogue: O = O^T / l, LSE = ln(l) + m scale, through the wave's staging tile (as in fwd_pipe_kernel) ----
+  {
+    int lane_e = lane;
+    asm volatile("" : "+v"(lane_e));
+    const int l32_e = lane_e & 31, hh_e = lane_e >> 5;
+    __bf16* obase = p.o + (int64_t)it.q_row0 * q_stride + (int64_t)head * D;
+    const int r = wave_row0 + l32_e;
+    const float l_tot = sum_halves(l_run);
+    const float inv = 1.0f / l_tot;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const bf16x4 v = pack4(oacc[db][4 * g] * inv, oacc[db][4 * g + 1] * inv, oacc[db][4 * g + 2] * inv, oacc[db][4 * g + 3] * inv);
+        *reinterpret_cast<bf16x4*>(stage + tile_elem<KC>(l32_e, 4 * db + g) + 4 * hh_e) = v;
+      }
+    if (r < it.q_rows && hh_e == 0) p.lse[(int64_t)head * p.total_q + it.q_row0 + r] = (mc + log2f(l_tot)) * 0.6931471805599453f;
+#pragma unroll 4
+    for (int i = 0; i < 32 * KC / 64; ++i) {
+      const int y = i * 64 + lane_e;
+      const int row = y / KC, ch = unswz<KC>(row, y % KC);
+      const bf16x8 v = *reinterpret_cast<const bf16x8*>(stage + y * 8);
+      if (wave_row0 + row < it.q_rows) *reinterpret_cast<bf16x8*>(obase + (int64_t)(wave_row0 + row) * q_stride + ch * 8) = v;
+    }
+  }
+  if (direct) break;
+  // on to the next block; the stores above are not waited for here
+  int nb = 0;
+  if (wave == 0) nb = block_claim_finish(p.taken, num_blocks, xcd, pending_claim);
+  blk = broadcast_from_wave0(next_block, nb);
+  }
+}
+
 // The dynamic-LDS limit of a kernel is raised once per process (thread-safe: a function-local static).
 template <class K>
 static hipError_t raise_smem_limit(K kernel, size_t smem) {
@@ -927,15 +1261,6 @@ static FwdArgs fwd_launch_args(const FwdParams& p, const FwdLists& lists) {
   a.num_blocks = lists.num_blocks;
   if (p.items == nullptr) std::memcpy(a.items, lists.items, (size_t)lists.num_items * sizeof(FwdItem));
   return a;
-}
-
-template <int D>
-static hipError_t launch_fwd_t(const FwdArgs& a, hipStream_t stream) {
-  const size_t smem = (size_t)4 * 64 * D * 2;
-  static const hipError_t attr = raise_smem_limit(&fwd_kernel<D>, smem);
-  if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL((fwd_kernel<D>), dim3(a.num_blocks), dim3(256), smem, stream, a);
-  return hipGetLastError();
 }
 
 template <int D, bool CUT>
@@ -965,15 +1290,22 @@ static hipError_t launch_fwd_pipe(const FwdArgs& a, const FwdLists& lists, hipSt
   return launch_fwd_items<D, false>(a, smem, stream);
 }
 
-hipError_t launch_fwd(const FwdParams& p, int head_dim, bool pipe, const FwdLists& lists, const TileJob* vjobs, hipStream_t stream) {
+hipError_t launch_fwd(const FwdParams& p, int head_dim, bool pipe, const FwdLists& lists, hipStream_t stream) {
   const FwdArgs a = fwd_launch_args(p, lists);
   if (head_dim == 256) {
-    hipError_t e;
-    if ((e = launch_transpose(p.v, p.num_kv_heads, head_dim, 64, vjobs, lists.num_vjobs, p.total_kv_tiles, const_cast<__bf16*>(p.vt),
-                              stream)) != hipSuccess) return e;
-    return launch_fwd_t<256>(a, stream);
+    const size_t smem = (size_t)10 * 32 * 256 * 2;  // four slots of K, five of V, and one tile more for the staging
+    static const hipError_t attr = raise_smem_limit(&fwd_wide_kernel, smem);
+    if (attr != hipSuccess) return attr;
+    hipLaunchKernelGGL(fwd_wide_kernel, dim3(persistent_grid(a.num_blocks)), dim3(256), smem, stream, a);
+    return hipGetLastError();
   }
-  if (!pipe) return launch_fwd_t<64>(a, stream);
+  if (!pipe) {
+    const size_t smem = (size_t)4 * 64 * 64 * 2;  // two K tiles, two V tiles
+    static const hipError_t attr = raise_smem_limit(&fwd_kernel, smem);
+    if (attr != hipSuccess) return attr;
+    hipLaunchKernelGGL(fwd_kernel, dim3(a.num_blocks), dim3(256), smem, stream, a);
+    return hipGetLastError();
+  }
   return head_dim == 64 ? launch_fwd_pipe<64>(a, lists, stream)
          : head_dim == 96 ? launch_fwd_pipe<96>(a, lists, stream)
                           : launch_fwd_pipe<128>(a, lists, stream);

@@ -19,11 +19,9 @@ struct FwdParams {
   const __bf16* v;
   __bf16* o;
   float* lse;
-  const __bf16* vt;         // head_dim 256: transposed V images [Hkv][total_kv_tiles][D][64]
   const FwdItem* items;     // null: in the kernel arguments (FwdArgs)
   const FwdItem* wholes;    // what fwd_merge_kernel goes through: items before cutting (those that were not cut are passed over); or null
   float* parts;             // partial results of the pieces, kPartFloats per (slot, inner index)
-  int64_t total_kv_tiles;
   int32_t num_q_heads, num_kv_heads, group;  // group = Hq / Hkv
   int32_t heads_per_wg;                      // query heads of one group handled by one workgroup (a power of two)
   int32_t head_splits;                       // group / heads_per_wg
@@ -166,18 +164,11 @@ hipError_t launch_bwd(const chunk_attn_desc* d, const BwdArgs& a, const BwdPlan&
 struct FwdLists {
   int num_blocks = 0, num_items = 0;
   int num_wholes = 0;  // 0: nothing is cut
-  int num_vjobs = 0;
   const FwdItem *items = nullptr, *wholes = nullptr;
 };
 // workgroups of the pipelined forward on a CU
 constexpr int fwd_per_cu(int head_dim) { return head_dim == 64 ? 2 : 1; }
-// The pipelined kernel (and the launch that puts cut walks together), or fwd_kernel (head_dim 256, and 64 unless `pipe`).  `vjobs` (device)
-// lists the 64-row tiles of V whose transposed images p.vt receives (head_dim 256).
-hipError_t launch_fwd(const FwdParams& p, int head_dim, bool pipe, const FwdLists& lists, const TileJob* vjobs, hipStream_t stream);
-
-// Transposed tile images (width 64 or 32 rows) of x[rows][num_heads][head_dim]:
-// out[num_heads][total_tiles][head_dim][width].
-hipError_t launch_transpose(const __bf16* x, int num_heads, int head_dim, int width, const TileJob* jobs, int num_jobs,
-                            int64_t total_tiles, __bf16* out, hipStream_t stream);
+// head_dim 96 and 128, and 64 if `pipe`: the pipelined kernel (and the launch that puts cut walks together); 256: fwd_wide_kernel; else fwd_kernel.
+hipError_t launch_fwd(const FwdParams& p, int head_dim, bool pipe, const FwdLists& lists, hipStream_t stream);
 
 }  // namespace chunk_attn

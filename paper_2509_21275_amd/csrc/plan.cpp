@@ -81,13 +81,11 @@ static void by_sequence_then_walk(const chunk_attn_desc* d, std::vector<Item>& i
 
 std::vector<FwdItem> plan_fwd(const chunk_attn_desc* d, int tile_rows) {
   std::vector<FwdItem> items;
-  int32_t kv_tile0 = 0;
   for (int t = 0; t < d->num_segments; ++t) {
     const chunk_attn_seg& s = d->segments[t];
     const int32_t C = s.kv_len - s.q_len;
     for (int32_t i0 = 0; i0 < s.q_len; i0 += tile_rows) {
       FwdItem it{};
-      it.kv_tile0 = kv_tile0;
       it.q_row0 = s.q_start + i0;
       it.q_rows = std::min<int32_t>(tile_rows, s.q_len - i0);
       it.kv_row0 = s.kv_start;
@@ -96,7 +94,6 @@ std::vector<FwdItem> plan_fwd(const chunk_attn_desc* d, int tile_rows) {
       it.part = -1;
       items.push_back(it);
     }
-    kv_tile0 += (s.kv_len + 63) / 64;
   }
   by_sequence_then_walk(d, items);
   for (FwdItem& it : items) it.whole = 1;

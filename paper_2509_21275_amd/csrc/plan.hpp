@@ -19,10 +19,10 @@
 
 namespace chunk_attn {
 
-// A tile (64 or 32 rows) of a tensor to be transposed by the pre-pass: rows [src_row0, src_row0 + valid_rows).
+// A tile (64 or 32 rows) of a tensor, for the pre-pass of the backward: rows [src_row0, src_row0 + valid_rows).
 struct TileJob {
   int32_t src_row0, valid_rows;
-  int32_t image;  // index of the output image (per head)
+  int32_t image;  // index of the tile (per head)
   int32_t pad;
 };
 
@@ -32,7 +32,7 @@ struct FwdItem {
   int32_t q_rows;    // valid rows in the tile (>= 1)
   int32_t kv_row0;   // first key row of the segment (global)
   int32_t n0;        // keys visible to the tile's first row: C + i0 + 1; row r sees n0 + r
-  int32_t kv_tile0;  // index of the transposed image of the segment's first 64-key tile
+  int32_t pad;
   // head_dim 96 and 128, whose walks over the keys may be cut into pieces (choose_key_split; 64 and 256: one piece each):
   int32_t keys;      // keys of the item's own range: it sees min(n0 + r, keys) of them
   int32_t whole;     // a piece: index of the whole item (as the host lists them).  A whole item: number of its pieces (1: not cut)

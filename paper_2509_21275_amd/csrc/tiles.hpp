@@ -149,12 +149,6 @@ __device__ __forceinline__ bf16x8 lds_chunk(const __bf16* tile, int row, int c) 
   return *reinterpret_cast<const bf16x8*>(tile + tile_elem<CHUNKS>(row, c));
 }
 
-// Position p (0..63) of a 64-wide transposed tile row holds contraction index cperm(p): the order in which
-// an accumulator tile presents its rows when it is reused as a B operand (device_common.hpp, "C-order").
-__host__ __device__ __forceinline__ int cperm(int p) {
-  return (p & ~15) | ((p & 4) << 1) | ((p & 8) >> 1) | (p & 3);
-}
-
 // Chunk-major tile of 32 rows (rows of Q, dO, K or V: D / 8 chunks of 16 bytes each): chunk c of row r sits at slot
 // c * 32 + (r ^ 4 (c & 3)).  Such a tile serves both as rows (16-byte reads: operand X[row][k]) and transposed
 // (ds_read_b64_tr_b16: operand X^T[column][row]), both kinds of read bank-conflict free and their addresses one

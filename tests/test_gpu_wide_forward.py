@@ -1,0 +1,44 @@
+"""The pipelined forward of head dimension 256 at the edges of its tiles (32 query rows per wave, stages of 32 keys, rings of four
+and five stages), with blocks that are taken a second time because a row outgrows its reference maximum, and with more blocks
+than workgroups, against the fp64 oracle (2e-2, as everywhere; LSE: float32 sums of unrounded probabilities, 1e-4)."""
+import pytest
+import torch
+
+import paper_2509_21275_amd as ca
+import synth
+from gpu_util import TOL_O, make_inputs, rel_err, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(oracle_mod, case, q, k, v):
+    o, lse = run_gpu(case, q, k, v, backward=False)
+    O, LSE = oracle_mod.Oracle(case.segs, q.cpu(), k.cpu(), v.cpu(), None, case.scale).forward()
+    assert rel_err(o, O) <= TOL_O and float(abs(lse.double().cpu().numpy() - LSE).max()) <= 1e-4 * max(1.0, float(abs(LSE).max()))
+
+
+def _case(segs, hq, hk):
+    tq, tkv = max(s[0] + s[1] for s in segs), max(s[2] + s[3] for s in segs) + 3
+    return synth.ChunkCase("wide_forward", [synth.Seg(*s) for s in segs], tq, tkv, hq, hk, 256, 300 + tq)
+
+
+@pytest.mark.parametrize("limit", [60.0, -1e30])
+@pytest.mark.parametrize("q_len,ctx", [(1, 0), (1, 31), (32, 0), (33, 31), (64, 64), (65, 95), (97, 130), (129, 1)])
+@pytest.mark.parametrize("hq,hk", [(4, 1), (6, 2), (3, 3)])  # 4, 1 and 1 heads per workgroup: 32, 128 and 128 rows
+def test_tile_edges(oracle_mod, hq, hk, q_len, ctx, limit):
+    case = _case([(0, q_len, 2, q_len + ctx), (q_len, 40, q_len + ctx + 2, 40)], hq, hk)
+    q, k, v, _ = make_inputs(case)
+    ca.chunk_attn_test_set_fwd_rescale_limit(limit)  # (a very low one: every block is taken twice)
+    try:
+        _check(oracle_mod, case, q, k, v)
+    finally:
+        ca.chunk_attn_test_set_fwd_rescale_limit(60.0)
+
+
+def test_late_growth_and_more_blocks_than_workgroups(oracle_mod):
+    """Some of 288 blocks have scores that grow by more than 2^60 after the first stage."""
+    case = _case([(65 * i, 65, 65 * i, 65) for i in range(12)] + [(780, 33, 780, 400)], 16, 16)
+    q, k, v, _ = make_inputs(case)
+    k[780 + 350:780 + 400] += 3.0
+    q[780:] = q[780:].abs() + 1.0
+    _check(oracle_mod, case, q, k, v)
