@@ -117,7 +117,7 @@ struct DqParams {
   unsigned long long* clock_log;  // null, or where the pipelined kernel's workgroups log their clocks
 };
 
-// (head_dim 64 unless its walks are long, and 256.)  K^T is read transposed out of the K tile; with an image of K made by a
+// (head_dim 64 unless its walks are long, and 256 with short walks.)  K^T is read transposed out of the K tile; with an image of K made by a
 // launch before, as this kernel had it, the backward of four sequences of 1024, 32/8 heads, took 144 us instead of 141, of
 // 64 of 256 220 instead of 211, and at head_dim 256 the packed 64K chunk 41.2 ms (forward included) instead of 40.2.
 // With one wave per SIMD a tile's chain of products, exponentials and products is what a step takes, and the transposed
@@ -985,9 +985,9 @@ __device__ __forceinline__ void dkv_pipe_blocks(const ArgsPtr<DkvParams> args, c
       for (int i = 0; i < PIECES; ++i) dma_piece(i);
       dma_advance();
     }
-    // A wait the compiler can see, for all copies and loads issued so far: without it the compiler's own bookkeeping
-    // of outstanding loads makes it put a full vmcnt(0) wait inside the loop (before role A's first S MFMA).
-    __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
+    // A wait the compiler can see, for the fragments and stage 0 (the later stages are waited for step by step): without it the
+    // compiler's own bookkeeping of outstanding loads makes it put a full vmcnt(0) wait inside the loop (before role A's first S MFMA).
+    wait_all_but<(DIST - 1) * CPS>();
     wg_barrier();
 
     // pipeline state
@@ -2277,13 +2277,17 @@ __device__ __forceinline__ void dq_pipe_blocks(const ArgsPtr<DqParams> args, con
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   };
 
-  // prologue: the copies of stages 0 .. DIST first, then the fragments, so that both travel at the same time
+  // prologue: the copies of stages 0 and 1 first, then the fragments, so that both travel at the same time, then the later
+  // stages, which are waited for step by step
+  auto copy_stages = [&](int n) __attribute__((always_inline)) {
 #pragma unroll
-  for (int s = 0; s <= DIST; ++s) {
+    for (int s = 0; s < n; ++s) {
 #pragma unroll
-    for (int i = 0; i < PER; ++i) dma_piece(i);
-    dma_advance();
-  }
+      for (int i = 0; i < PER; ++i) dma_piece(i);
+      dma_advance();
+    }
+  };
+  copy_stages(2);
   // Q and dO fragments (B operands): lane holds X[row = l32 of the unit][16 ks + 8 hh ..+7]; LSE and D of that row
   bf16x8 qf[2][DK], gf[2][DK];
   float lse2[2], dsum[2];
@@ -2307,9 +2311,10 @@ __device__ __forceinline__ void dq_pipe_blocks(const ArgsPtr<DqParams> args, con
   for (int u = 0; u < 2; ++u)
 #pragma unroll
     for (int i = 0; i < 16; ++i) dneg[u][i] = dsum[u];
-  // One wait the compiler can see for everything issued so far (loads complete in order: the copies have landed when
-  // the fragments have), so that it puts no full waits for outstanding loads into the loop
-  __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
+  copy_stages(DIST - 1);
+  // One wait the compiler can see for the fragments (and the copies before them), so that it puts no full waits for outstanding
+  // loads into the loop
+  wait_all_but<(DIST - 1) * PER>();
   wg_barrier();
 
   const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -2537,6 +2542,367 @@ __device__ __forceinline__ void dq_pipe_blocks(const ArgsPtr<DqParams> args, con
 }
 
 // ------------------------------------------------------------------------------------------------
+// bwd_dq_wide (head_dim 256)
+//
+// dQ in the style of dq_pipe_blocks with 32 query rows per wave (Q and dO fragments and dQ^T take all 256 accumulation registers): in step t
+// a wave runs
+//     dP^T(t) = V(t) dO^T        S^T(t+1) = K(t+1) Q^T        dQ^T += K(t-1)^T dS^T(t-1)      (matrix pipe)
+//     P^T(t) = exp2(S^T(t) c - LSE)  and, once dP^T(t) is complete,  dS^T(t) = P^T(t) (dP^T(t) - D)   (vector)
+// as 48 mini-steps of one operand fragment and the MFMA it feeds.  dP^T and S^T are one accumulator each, so their MFMAs are kept
+// apart: 16 of dP^T alternate with 8 of S^T and 8 of dQ^T, then the other 8 of S^T with the other 8 of dQ^T, next to which dS^T is formed.
+// LDS is full: six stages of K (t - 1, t, t + 1 and, read ahead over the end of the step, t + 2 in use; t + 3 and t + 4 on their way) and
+// four of V (t and t + 1 in use, t + 2 and t + 3 on their way); a copy has more than a step to land.  dQ goes out through the V
+// ring.  As in fwd_wide_kernel every fragment feeds one MFMA, so a step is bound by its 64 LDS reads and 48 MFMAs.
+// Packed 64K chunk, 32/8 heads, backward: 29.4 ms with bwd_dq_kernel, 27.2 with this; 8192 queries on 32768 keys 25.9 -> 24.0 (dq_wide_pays: more).
+// ------------------------------------------------------------------------------------------------
+// mini-step k: what its MFMA adds to (0: dP^T, 1: S^T, 2: dQ^T) and the index of its fragment
+constexpr int wide_kind(int k) { return k < 32 ? (k % 2 == 0 ? 0 : k % 4 == 1 ? 1 : 2) : 1 + k % 2; }
+constexpr int wide_index(int k) { return k < 32 ? (k % 2 == 0 ? k / 2 : k / 4) : 8 + (k - 32) / 2; }
+// LDS instructions issued between the read of fragment k and the start of mini-step k (a transposed fragment takes two)
+constexpr int wide_wait(int k, int ahead) {
+  int n = 0;
+  for (int i = k + 1; i < k + ahead; ++i) n += wide_kind(i % 48) == 2 ? 2 : 1;
+  return n;
+}
+static_assert(wide_kind(0) == 0 && wide_kind(1) == 1 && wide_kind(3) == 2 && wide_kind(30) == 0 && wide_kind(32) == 1 && wide_kind(47) == 2 &&
+              wide_index(1) == 0 && wide_index(3) == 0 && wide_index(5) == 1 && wide_index(29) == 7 && wide_index(30) == 15 && wide_index(31) == 7 &&
+              wide_index(32) == 8 && wide_index(47) == 15 && wide_wait(0, 6) == 6 && wide_wait(32, 6) == 8, "worked out by hand");
+
+__global__ __launch_bounds__(256, 1) void bwd_dq_wide_kernel(DqParams) {
+  constexpr int D = 256;
+  constexpr int NW = 4;        // waves
+  constexpr int BN = 32;       // key rows per stage
+  constexpr int KC = D / 8;    // 16-byte chunks per K / V row
+  constexpr int DK = D / 16;   // k-steps over the head dimension
+  constexpr int DB = D / 32;   // 32-row blocks of dQ^T
+  constexpr int KT = BN * D;   // elements per tile
+  constexpr int KS = 6, VS = 4;           // ring slots of K and of V
+  constexpr int NF = 3 * DK;              // mini-steps per step
+  constexpr int AHEAD = 6, RING = 8;      // fragments in flight, registers of the fragment ring
+  constexpr int PER = BN * KC / 64 / NW;  // global->LDS copies per wave, tile and stage
+  constexpr int EXP0 = 3, DS0 = 33;       // score i's exponential next to MFMA EXP0 + 2 i, pair j of dS next to MFMA DS0 + 2 j
+  constexpr int BOOK = 40;                // mini-step of the bookkeeping, behind the last copy
+  static_assert(NF == 48 && 2 * DB == DK && NF % RING == 0 && RING > AHEAD && 2 + 5 * (2 * PER - 1) < BOOK, "the schedule of a step");
+
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  lds_bf16* const L = (lds_bf16*)smem;
+  constexpr int K_OFF = 0;               // [KS][KT]  K rows of stage n in slot n % KS (chunk-major)
+  constexpr int V_OFF = K_OFF + KS * KT; // [VS][KT]  V rows
+  // the V ring is also the [NW][32][D] staging of dQ on its way out (rows of swizzled 16-byte chunks), whose first word
+  // doubles as the slot through which wave 0 announces the next block
+  constexpr int ST_OFF = V_OFF;
+
+  const ArgsPtr<DqParams> args = (ArgsPtr<DqParams>)__builtin_amdgcn_kernarg_segment_ptr();
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, hh = lane >> 5;
+  int* const next_block = (int*)((__bf16*)smem + ST_OFF);
+
+  const int xcd = xcd_of_this_wave();
+  const bool direct = args->num_blocks <= (int)gridDim.x;
+  int blk = blockIdx.x;
+  if (!direct) {
+    const DqParams p = fresh(args);
+    if (wave == 0) blk = block_claim_finish(p.taken, p.num_blocks, xcd, block_claim_issue(p.taken, xcd));
+    blk = broadcast_from_wave0(next_block, blk);
+  }
+  int pending_claim = 0;
+  while (blk >= 0) {
+  wg_barrier();  // every wave has read the announcement: the V ring may be written again
+  const DqParams p = fresh(args);
+  const int inner_n = p.num_kv_heads * p.head_splits;
+  const int inner = __builtin_amdgcn_readfirstlane(blk % inner_n);
+  const DqItem it = load_uniform(p.items, __builtin_amdgcn_readfirstlane(blk / inner_n));
+  const int kvh = __builtin_amdgcn_readfirstlane(inner % p.num_kv_heads), hs = inner / p.num_kv_heads;
+  const int head = kvh * p.group + hs * p.heads_per_wg + wave % p.heads_per_wg;
+  const int row0 = (wave / p.heads_per_wg) * 32;
+  const int n_wg = it.n0 + it.q_rows - 1;  // keys the last valid row sees
+  const int nt = (n_wg + BN - 1) / BN;     // stages
+
+  const int64_t q_stride = (int64_t)p.num_q_heads * D, kv_stride = (int64_t)p.num_kv_heads * D;
+  const __bf16* __restrict__ Kg = p.k + (int64_t)it.kv_row0 * kv_stride + (int64_t)kvh * D;
+  const __bf16* __restrict__ Vg = p.v + (int64_t)it.kv_row0 * kv_stride + (int64_t)kvh * D;
+
+  {  // K(-1), read in step 0 before anything is copied into its slot
+    bf16x8 z;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) z[i] = (__bf16)0.0f;
+    for (int x = tid; x < KT / 8; x += NW * 64) lds_store8(L + K_OFF + (KS - 1) * KT + x * 8, z);
+  }
+
+  // ---- staging: copy i of a wave is piece 4 i + wave of a tile, 64 consecutive slots = two chunk columns of 32 rows.  Past the last
+  // stage the last one is copied again. ----
+  unsigned v_full[PER], v_last[PER];  // byte offset of the lane's chunk from the tile's first row: full tile, last tile
+  {
+    const int last_row = n_wg - 1 - (nt - 1) * BN;  // rows past the last key repeat it (masked)
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int x = (i * NW + wave) * 64 + lane;
+      const int off = (x >> 5) * 8, row = (x & 31) ^ (((x >> 5) & 3) << 2);
+      v_full[i] = (unsigned)(row * (int)kv_stride + off) * 2u;
+      v_last[i] = (unsigned)(min(row, last_row) * (int)kv_stride + off) * 2u;
+    }
+  }
+  struct Stream {  // the next stage to copy, its slot, its first row
+    int t, slot;
+    const char* row;
+  };
+  Stream ks{0, 0, reinterpret_cast<const char*>(Kg)}, vs{0, 0, reinterpret_cast<const char*>(Vg)};
+  auto copy_piece = [&](const Stream& st, int ring, int i) __attribute__((always_inline)) {
+    dma16(st.row + (st.t == nt - 1 ? v_last[i] : v_full[i]), L + ring + st.slot * KT + (i * NW + wave) * 512);
+  };
+  auto advance = [&](Stream& st, int slots) __attribute__((always_inline)) {
+    if (st.t + 1 < nt) {
+      ++st.t;
+      st.row += BN * kv_stride * 2;
+    }
+    st.slot = st.slot == slots - 1 ? 0 : st.slot + 1;
+  };
+
+  // per-lane operand addresses inside a tile
+  int x_off[2], t_off[2];
+#pragma unroll
+  for (int par = 0; par < 2; ++par) x_off[par] = cm_elem(l32, 2 * par + hh);
+  {
+    const int j = lane & 15, grp = (lane >> 4) & 1;
+    const int cl = 2 * grp + ((j & 3) >> 1);
+    const int r0 = 4 * hh + (j >> 2);
+#pragma unroll
+    for (int half = 0; half < 2; ++half) t_off[half] = cm_elem(r0 + 8 * half, cl) + 4 * (j & 1);
+  }
+  const unsigned k_ev0 = lds_addr(L + K_OFF + x_off[0]), k_od0 = lds_addr(L + K_OFF + x_off[1]);
+  const unsigned v_ev0 = lds_addr(L + V_OFF + x_off[0]), v_od0 = lds_addr(L + V_OFF + x_off[1]);
+  const unsigned t_lo0 = lds_addr(L + K_OFF + t_off[0]), t_hi0 = lds_addr(L + K_OFF + t_off[1]);
+  constexpr unsigned SLOT = KT * 2;  // bytes per ring slot
+  auto load_rows = [&](unsigned ev_addr, unsigned od_addr, auto ks_c) __attribute__((always_inline)) {
+    constexpr int k = decltype(ks_c)::value;
+    return lds_asm_read16<(k >> 1) * (4 * 32 * 8) * 2>((k & 1) ? od_addr : ev_addr);
+  };
+  auto load_t = [&](unsigned lo_addr, unsigned hi_addr, auto m_c) __attribute__((always_inline)) {
+    constexpr int m = decltype(m_c)::value;  // ks2 * DB + db
+    constexpr int off = ((m / DB) * (16 * 8) + (m % DB) * (4 * 32 * 8)) * 2;
+    const s16x4 lo = lds_asm_read_tr<off>(lo_addr);
+    const s16x4 hi = lds_asm_read_tr<off>(hi_addr);
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
+
+  // prologue: K of stages 0 .. 2 and V of stages 0 and 1 first, then the fragments, so that all travel at the same time, then
+  // K(3) and V(2), which step 0 waits for at its end
+  auto copy_tile = [&](Stream& st, int ring, int slots) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) copy_piece(st, ring, i);
+    advance(st, slots);
+  };
+#pragma unroll
+  for (int n = 0; n < 3; ++n) copy_tile(ks, K_OFF, KS);
+#pragma unroll
+  for (int n = 0; n < 2; ++n) copy_tile(vs, V_OFF, VS);
+  // Q and dO fragments (B operands): lane holds X[row = l32][16 ks + 8 hh ..+7]; LSE and D of that row
+  bf16x8 qf[DK], gf[DK];
+  float lse2, dsum;
+  {
+    const int r_own = min(row0 + l32, it.q_rows - 1);  // rows past the tile repeat the last one (never stored)
+    const int64_t off = (int64_t)(it.q_row0 + r_own) * q_stride + (int64_t)head * D + 8 * hh;
+#pragma unroll
+    for (int k = 0; k < DK; ++k) {
+      qf[k] = *reinterpret_cast<const bf16x8*>(p.q + off + 16 * k);
+      gf[k] = *reinterpret_cast<const bf16x8*>(p.d_o + off + 16 * k);
+    }
+    const int64_t slot = (int64_t)head * p.total_q_tiles * 64 + it.q_slot0 + r_own;
+    lse2 = p.lse2p[slot];
+    dsum = p.dsp[slot];
+  }
+  f32x16 dneg;  // -D of the lane's row in every element: the accumulation of dP^T starts from it (as in dq_pipe_blocks)
+#pragma unroll
+  for (int i = 0; i < 16; ++i) dneg[i] = dsum;
+  copy_tile(ks, K_OFF, KS);
+  copy_tile(vs, V_OFF, VS);
+  // One wait the compiler can see for the fragments (and the copies before them), so that it puts no full waits for outstanding
+  // loads into the loop
+  wait_all_but<2 * PER>();
+  // (the fragments settle in their accumulation registers here: an opaque MFMA must not follow a write to one of its operands)
+#pragma unroll
+  for (int k = 0; k < DK; ++k) {
+    asm volatile("" : "+a"(qf[k]));
+    asm volatile("" : "+a"(gf[k]));
+  }
+  wg_barrier();
+
+  const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  f32x16 dq[DB];
+#pragma unroll
+  for (int db = 0; db < DB; ++db) dq[db] = zero16;
+  f32x16 x[2], dp;   // S^T (two buffers), dP^T
+  bf16x8 f[2][2];    // dS^T as B operands: [buffer][k-step]
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) f[b][k][i] = (__bf16)0.0f;
+  const float c = p.scale_log2;
+  bf16x8 fr[RING];  // ring of operand fragments
+
+  {  // S^T(0) = K(0) Q^T
+    bf16x8 a[DK];
+    static_for<0, DK>([&](auto ks_c) __attribute__((always_inline)) { a[decltype(ks_c)::value] = load_rows(k_ev0, k_od0, ks_c); });
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int k = 0; k < DK; ++k) asm volatile("" : "+v"(a[k]));  // (after the wait, in this order)
+#pragma unroll
+    for (int k = 0; k < DK; ++k) {
+      f32x16& d_ = x[0];
+      const bf16x8& b_ = qf[k];
+      if (k == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d_) : "v"(a[k]), "a"(b_));
+      else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d_) : "v"(a[k]), "a"(b_));
+    }
+    mfma_settle();
+  }
+
+  // the fragment of mini-step k of a step whose V(t), K(t + 1) and K(t - 1) lie in slots sV, sK and sT
+  auto load_fragment = [&](auto k_c, int sV, int sK, int sT) __attribute__((always_inline)) {
+    constexpr int k = decltype(k_c)::value, kind = wide_kind(k);
+    constexpr std::integral_constant<int, wide_index(k)> i{};
+    if constexpr (kind == 0) return load_rows(v_ev0 + sV * SLOT, v_od0 + sV * SLOT, i);
+    else if constexpr (kind == 1) return load_rows(k_ev0 + sK * SLOT, k_od0 + sK * SLOT, i);
+    else return load_t(t_lo0 + sT * SLOT, t_hi0 + sT * SLOT, i);
+  };
+  static_for<0, AHEAD>([&](auto k_c) __attribute__((always_inline)) { fr[decltype(k_c)::value] = load_fragment(k_c, 0, 1, KS - 1); });
+
+  int sV = 0, sK = 1, sT = KS - 1;  // slots of V(t), K(t + 1), K(t - 1)
+  auto step = [&](int t, f32x16& cur, f32x16& nxt, bf16x8 (&f_old)[2], bf16x8 (&f_new)[2], auto masked_c) __attribute__((always_inline)) {
+    constexpr bool MASKED = decltype(masked_c)::value;
+    const int nV = sV == VS - 1 ? 0 : sV + 1, nK = sK == KS - 1 ? 0 : sK + 1, nT = sT == KS - 1 ? 0 : sT + 1;  // of the next step
+    // MASKED: element i (key 8 (i / 4) + 4 hh + i % 4 of the tile) is visible iff 8 (i / 4) + i % 4 < lim
+    int lim = 0;
+    if (MASKED) lim = t < nt ? it.n0 + row0 + l32 - BN * t - 4 * hh : -0x40000000;
+    float pf[16];   // P^T(t)
+    unsigned pw[8]; // dS^T(t), packed pairs
+    asm volatile("s_nop 7" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<0, NF>([&](auto k_c) __attribute__((always_inline)) {
+      constexpr int k = decltype(k_c)::value, kind = wide_kind(k), idx = wide_index(k);
+      static_assert(wide_wait(k, AHEAD) <= 15, "lgkmcnt is a 4-bit counter");
+      asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(fr[k % RING]) : "n"(wide_wait(k, AHEAD)));
+      {  // read the fragment of mini-step k + AHEAD (past the end: the next step's first ones)
+        constexpr int kk = k + AHEAD;
+        if constexpr (kk < NF) fr[kk % RING] = load_fragment(std::integral_constant<int, kk>{}, sV, sK, sT);
+        else fr[kk % RING] = load_fragment(std::integral_constant<int, kk - NF>{}, nV, nK, nT);
+      }
+      const bf16x8& a_ = fr[k % RING];
+      if constexpr (kind == 0) {
+        f32x16& d_ = dp;
+        const bf16x8& b_ = gf[idx];
+        const f32x16& n_ = dneg;
+        if (idx == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" : "=&v"(d_) : "v"(a_), "a"(b_), "v"(n_));
+        else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d_) : "v"(a_), "a"(b_));
+      } else if constexpr (kind == 1) {
+        f32x16& d_ = nxt;
+        const bf16x8& b_ = qf[idx];
+        if (idx == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d_) : "v"(a_), "a"(b_));
+        else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d_) : "v"(a_), "a"(b_));
+      } else {
+        dq[idx % DB] = mfma32(a_, f_old[idx / DB], dq[idx % DB]);
+      }
+      if constexpr (k >= EXP0 && (k - EXP0) % 2 == 0 && (k - EXP0) / 2 < 16) {
+        constexpr int i = (k - EXP0) / 2;
+        float tt = cur[i] * c - lse2;
+        if (MASKED) {
+          if (8 * (i >> 2) + (i & 3) >= lim) tt = -INFINITY;
+        }
+        pf[i] = __builtin_amdgcn_exp2f(tt);
+        asm volatile("" : "+v"(pf[i]));  // pinned here (the compiler would gather the vector work elsewhere)
+      }
+      if constexpr (k >= DS0 && (k - DS0) % 2 == 0 && (k - DS0) / 2 < 8) {
+        constexpr int j = (k - DS0) / 2;
+        static_assert(EXP0 + 2 * (2 * j + 1) < k, "a pair's exponentials come before its dS");
+        bf16x2 w;
+        w[0] = (__bf16)(pf[2 * j] * dp[2 * j]);  // dp holds dP - D: its accumulation starts from -D
+        w[1] = (__bf16)(pf[2 * j + 1] * dp[2 * j + 1]);
+        unsigned wu = __builtin_bit_cast(unsigned, w);
+        asm volatile("" : "+v"(wu));
+        pw[j] = wu;
+      }
+      // V(t + 3) and K(t + 4)
+      if constexpr (k >= 2 && (k - 2) % 5 == 0 && (k - 2) / 5 < 2 * PER) {
+        constexpr int i = (k - 2) / 5;
+        if constexpr (i < PER) copy_piece(vs, V_OFF, i);
+        else copy_piece(ks, K_OFF, i - PER);
+      }
+      if constexpr (k == BOOK) {  // bookkeeping for the next step (this step's copies have been issued)
+        advance(ks, KS);
+        advance(vs, VS);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    sV = nV;
+    sK = nK;
+    sT = nT;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      u32x4 v = {pw[4 * k], pw[4 * k + 1], pw[4 * k + 2], pw[4 * k + 3]};
+      f_new[k] = __builtin_bit_cast(bf16x8, v);
+    }
+    // the copies of the step before (V(t + 2), K(t + 3)) must have landed; this step's may still be in flight
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * PER) : "memory");
+    wg_barrier();
+  };
+
+  // (as in dq_pipe_blocks)
+  const int t_full = min(nt, (it.n0 + row0) / BN) & ~1;
+  int t = 0;
+  for (; t < t_full; t += 2) {
+    step(t, x[0], x[1], f[0], f[1], std::false_type{});
+    step(t + 1, x[1], x[0], f[1], f[0], std::false_type{});
+  }
+  if (wave == 0 && !direct) pending_claim = block_claim_issue(fresh(args).taken, xcd);
+  for (; t <= nt; t += 2) {
+    step(t, x[0], x[1], f[0], f[1], std::true_type{});
+    step(t + 1, x[1], x[0], f[1], f[0], std::true_type{});
+  }
+  // the last step's reads ahead are nobody's operands; their registers stay taken until they have arrived
+#pragma unroll
+  for (int i = 0; i < RING; ++i) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(fr[i]));
+  // every copy of this wave has landed (the last ones rewrote slots nobody reads)
+  __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
+  wg_barrier();  // nobody reads the rings, and nobody copies into them, any more: dQ may be staged there
+
+  // ---- epilogue: dQ = scale * dQ^T, through the wave's staging tile (as in dq_pipe_blocks) ----
+  {
+    const DqParams pe = fresh(args);
+    const int64_t q_stride_e = (int64_t)pe.num_q_heads * D;
+    lds_bf16* const stage = L + ST_OFF + wave * KT;
+    int lane_e = lane;
+    asm volatile("" : "+v"(lane_e));
+    const int l32_e = lane_e & 31, hh_e = lane_e >> 5;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const bf16x4 v = pack4(dq[db][4 * g] * pe.scale, dq[db][4 * g + 1] * pe.scale, dq[db][4 * g + 2] * pe.scale, dq[db][4 * g + 3] * pe.scale);
+        *(__attribute__((address_space(3))) bf16x4*)(stage + tile_elem<KC>(l32_e, 4 * db + g) + 4 * hh_e) = v;
+      }
+    __bf16* obase = pe.dq + (int64_t)(it.q_row0 + row0) * q_stride_e + (int64_t)head * D;
+#pragma unroll 4
+    for (int i = 0; i < 32 * KC / 64; ++i) {
+      const int y = i * 64 + lane_e;
+      const int row = y / KC, ch = unswz<KC>(row, y % KC);
+      const bf16x8 v = lds_load8(stage + y * 8);
+      if (row0 + row < it.q_rows) *reinterpret_cast<bf16x8*>(obase + (int64_t)row * q_stride_e + ch * 8) = v;
+    }
+  }
+  if (direct) break;
+  // on to the next block; the stores above are not waited for here
+  int nb = 0;
+  if (wave == 0) {
+    const DqParams pc = fresh(args);
+    nb = block_claim_finish(pc.taken, pc.num_blocks, xcd, pending_claim);
+  }
+  blk = broadcast_from_wave0(next_block, nb);
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
 // bwd_pipe (head_dim 128 and 96): the dQ and the dK/dV blocks of a chunk in one launch
 //
 // The two kinds of block need nothing of each other, so a workgroup that finds no more blocks of one kind goes on to the other:
@@ -2673,6 +3039,12 @@ bool dkv_pipe_pays(const chunk_attn_desc* d, const Walks& w) {
 // 3000 805 / 754.  What the estimate leaves alone (6500 tokens at 64, 3500 at 256) runs as before.
 constexpr int64_t kMaxShortParts = 2 * kCus;  // partial results of such a chunk (64 MB at most)
 
+// Whether head_dim 256 runs bwd_dq_wide_kernel, whose blocks start and end more slowly than bwd_dq_kernel's: from walks of 5.5 stages on
+// average on.  Backward, bwd_dq_kernel / wide (heads, mean walk): 64 sequences of 70, 8/8 (3) 100 / 105 us; of 170 (5) 190 / 197; of 220 (5.5)
+// 283 / 277; four of 256, 8/8 (6) 50 / 49; 148 queries on 595 keys, 8/2 (17) 76 / 72; 32/8 heads: eight sequences of 220 (4) 107 / 111, 64 of 220 (4) 639 / 652,
+// 64 of 256 (4.5) 776 / 760; 1024 causal tokens (16.5) 144 / 135; 909 on 5603 keys (161) 638 / 598.
+bool dq_wide_pays(const Walks& w) { return 2 * w.stages >= 11 * w.items; }
+
 // workgroups of the pipelined dK/dV kernels on a CU
 constexpr int dkv_per_cu(int head_dim) { return head_dim == 64 ? 2 : 1; }
 
@@ -2787,7 +3159,12 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
                          reinterpret_cast<const DkvItem*>(ws + P.dkv_cut_off));
     if ((e = hipGetLastError()) != hipSuccess) return e;
   } else {
-    if (D == 64 && P.dq_pipe) {
+    if (D == 256 && P.dq_wide) {
+      const size_t smem = (size_t)10 * 32 * D * 2;  // six slots of K and four of V
+      static const hipError_t attr = raise_smem_limit(&bwd_dq_wide_kernel, smem);
+      if (attr != hipSuccess) return attr;
+      hipLaunchKernelGGL(bwd_dq_wide_kernel, dim3((unsigned)persistent_grid(dq_blocks)), dim3(256), smem, stream, pq);
+    } else if (D == 64 && P.dq_pipe) {
       const size_t smem = (size_t)2 * (DQ_PIPE_DIST + 3) * 32 * D * 2 + (size_t)4 * 64 * D * 2;
       static const hipError_t attr = raise_smem_limit(&bwd_dq_pipe_kernel, smem);
       if (attr != hipSuccess) return attr;
@@ -2859,6 +3236,7 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, bool may_c
   }
   if (!pipe) P.dkv_pipe = dkv_pipe_pays(d, count_dkv_walks(d, dkv_keys(d->head_dim)));
   const int dq_rows = tile_rows(group, P.dq_waves);
+  if (d->head_dim == 256) P.dq_wide = dq_wide_pays(count_walks(d, dq_rows));
   P.q_tiles = count_tiles(d, false, 64);
   P.qt32_tiles = count_tiles(d, false, 32);
   // head_dim 128: room for dQ tiles in float32, for the one-pass backward or for the partial results of cut dQ walks

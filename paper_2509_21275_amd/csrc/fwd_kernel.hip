@@ -548,13 +548,17 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void fwd_pipe_kernel(FwdArgs)
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   };
 
-  // prologue: the copies of stages 0 .. DIST first, then the Q fragments, so that both travel at the same time
+  // prologue: the copies of stages 0 and 1 first, then the wave's rows of Q, so that both travel at the same time, then the later
+  // stages, which are waited for step by step
+  auto copy_stages = [&](int n) __attribute__((always_inline)) {
 #pragma unroll
-  for (int s = 0; s <= DIST; ++s) {
+    for (int s = 0; s < n; ++s) {
 #pragma unroll
-    for (int i = 0; i < PER; ++i) dma_piece(i);
-    dma_advance();
-  }
+      for (int i = 0; i < PER; ++i) dma_piece(i);
+      dma_advance();
+    }
+  };
+  copy_stages(2);
   // the wave's 64 rows of Q (its two units) into its staging tile: slot x = 16 row + position holds the chunk that
   // belongs there; rows past the tile repeat the last one (never stored)
   {
@@ -567,25 +571,30 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void fwd_pipe_kernel(FwdArgs)
       dma16(qbase + (int64_t)r * q_stride + c * 8, stage + i * 512);
     }
   }
-  // One wait the compiler can see for everything issued so far: it then has no reason to put full waits for outstanding
+  copy_stages(DIST - 1);
+  // One wait the compiler can see for Q (and the copies before it): it then has no reason to put full waits for outstanding
   // loads into the loop.
-  __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
-  // Q fragments (B operands of S^T = K Q^T): lane holds Q[row = l32 of the unit][16 ks + 8 hh ..+7]
+  wait_all_but<(DIST - 1) * PER>();
+  // Q fragments (B operands of S^T = K Q^T): lane holds Q[row = l32 of the unit][16 ks + 8 hh ..+7].  (Opaque reads, as for all that is
+  // read or written while copies are on their way.)
+  const unsigned stage_addr = lds_addr((lds_bf16*)stage);
   bf16x8 qf[2][DK];
 #pragma unroll
   for (int u = 0; u < 2; ++u)
 #pragma unroll
-    for (int ks = 0; ks < DK; ++ks) qf[u][ks] = lds_chunk<KC>(stage, 32 * u + l32, 2 * ks + hh);
+    for (int ks = 0; ks < DK; ++ks) qf[u][ks] = lds_asm_read16<0>(stage_addr + 2 * tile_elem<KC>(32 * u + l32, 2 * ks + hh));
   // Once Q has been read, the staging tile's first word says whether some wave has seen a row outgrow its reference maximum:
   // one word per wave, written by any and read by its own wave only, as the others may by then write their rows of O.
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (in this order: the compiler takes the word and the rows for unrelated)
-  *(volatile int*)stage = 0;
+  lds_asm_write4(stage_addr, 0);
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   // (the fragments settle in their accumulation registers here: an opaque MFMA must not follow a write to one of its operands)
 #pragma unroll
   for (int u = 0; u < 2; ++u)
 #pragma unroll
-    for (int ks = 0; ks < DK; ++ks) asm volatile("" : "+a"(qf[u][ks]));
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    for (int ks = 0; ks < DK; ++ks) {
+      asm volatile("" : "+v"(qf[u][ks]));
+      asm volatile("" : "+a"(qf[u][ks]));
+    }
   wg_barrier();
 
   const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -994,19 +1003,15 @@ __global__ __launch_bounds__(256, 1) void fwd_wide_kernel(FwdArgs) {
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   };
 
-  // prologue: K of stages 0 .. 3, V of stages 0 and 1, the wave's rows of Q
+  // prologue: K of stages 0 .. 2, V of stage 0 and the wave's rows of Q, then K(3) and V(1), which step 0 waits for at its end
+  auto copy_tile = [&](Stream& st, int ring, int slots) __attribute__((always_inline)) {
 #pragma unroll
-  for (int n = 0; n < KS; ++n) {
+    for (int i = 0; i < PER; ++i) copy_piece(st, ring, i);
+    advance(st, slots);
+  };
 #pragma unroll
-    for (int i = 0; i < PER; ++i) copy_piece(ks, K_OFF, i);
-    advance(ks, KS);
-  }
-#pragma unroll
-  for (int n = 0; n < 2; ++n) {
-#pragma unroll
-    for (int i = 0; i < PER; ++i) copy_piece(vs, V_OFF, i);
-    advance(vs, VS);
-  }
+  for (int n = 0; n < 3; ++n) copy_tile(ks, K_OFF, KS);
+  copy_tile(vs, V_OFF, VS);
   {
     const __bf16* qbase = p.q + (int64_t)it.q_row0 * q_stride + (int64_t)head * D;
 #pragma unroll 4
@@ -1017,26 +1022,32 @@ __global__ __launch_bounds__(256, 1) void fwd_wide_kernel(FwdArgs) {
       dma16(qbase + (int64_t)r * q_stride + c * 8, stage + i * 512);
     }
   }
-  // One wait the compiler can see for everything issued so far: it then has no reason to put full waits for outstanding
+  copy_tile(ks, K_OFF, KS);
+  copy_tile(vs, V_OFF, VS);
+  // One wait the compiler can see for Q (and the copies before it): it then has no reason to put full waits for outstanding
   // loads into the loop.
-  __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
-  // Q fragments (B operands of S^T = K Q^T): lane holds Q[row = l32][16 ks + 8 hh ..+7]
+  wait_all_but<2 * PER>();
+  // Q fragments (B operands of S^T = K Q^T): lane holds Q[row = l32][16 ks + 8 hh ..+7].  (Opaque reads, as for all that is read or
+  // written while copies are on their way.)
+  const unsigned stage_addr = lds_addr((lds_bf16*)stage);
   bf16x8 qf[DK];
 #pragma unroll
-  for (int k = 0; k < DK; ++k) qf[k] = lds_chunk<KC>(stage, l32, 2 * k + hh);
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (in this order: the compiler takes what is written below and the rows for unrelated)
+  for (int k = 0; k < DK; ++k) qf[k] = lds_asm_read16<0>(stage_addr + 2 * tile_elem<KC>(l32, 2 * k + hh));
   if (wave == 2) {  // V(-1), read in step 0: its slot is this wave's staging tile
     bf16x8 z;
 #pragma unroll
     for (int i = 0; i < 8; ++i) z[i] = (__bf16)0.0f;
     static_assert(ST_OFF + 2 * KT == V_OFF + (VS - 1) * KT, "the slot of V(-1)");
-    for (int x = lane; x < KT / 8; x += 64) lds_store8(L + V_OFF + (VS - 1) * KT + x * 8, z);
+    static_for<0, KT / 512>([&](auto i_c) __attribute__((always_inline)) { lds_asm_write16<decltype(i_c)::value * 1024>(stage_addr + lane * 16, z); });
   }
-  if (wave == 3) *outgrown = 0;  // (its staging tile)
+  if (wave == 3) lds_asm_write4(lds_addr(L + X_OFF), 0);  // (*outgrown, in its staging tile)
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   // (the fragments settle in their accumulation registers here: an opaque MFMA must not follow a write to one of its operands)
 #pragma unroll
-  for (int k = 0; k < DK; ++k) asm volatile("" : "+a"(qf[k]));
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  for (int k = 0; k < DK; ++k) {
+    asm volatile("" : "+v"(qf[k]));
+    asm volatile("" : "+a"(qf[k]));
+  }
   wg_barrier();
 
   const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};

@@ -130,8 +130,9 @@ struct BwdPlan {
   size_t n_dq_cut = 0, n_dkv_cut = 0;
   size_t dq_items_off = 0, dq_cut_off = 0, dkv_items_off = 0, dkv_cut_off = 0, qjobs_off = 0, queues_off = 0, upload_bytes = 0, blob_bytes = 0;
   size_t lse2p_off = 0, dsp_off = 0, dq_parts_off = 0, total = 0;
-  // (head_dim 96 and 128 always; dQ: 64 where pipe_pays, 256 never; dK/dV: 64 and 256 where dkv_pipe_pays)
+  // (head_dim 96 and 128 always; dQ: 64 where pipe_pays; dK/dV: 64 and 256 where dkv_pipe_pays)
   bool dq_pipe = false, dkv_pipe = false;  // the pipelined kernels run
+  bool dq_wide = false;                    // head_dim 256: bwd_dq_wide_kernel runs
   int dq_waves = 0;                        // 32-row units of a dQ workgroup
   bool dq_first = false;                   // head_dim 96 and 128: the dQ blocks start before the dK/dV blocks
   // one-pass backward (head_dim 128): its items and workgroup order travel at the end of the blob; then the per-wave

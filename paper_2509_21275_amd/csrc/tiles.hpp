@@ -190,6 +190,15 @@ template <int OFF>
 __device__ __forceinline__ void lds_asm_write16(unsigned addr, bf16x8 v) {
   asm volatile("ds_write_b128 %0, %1 offset:%2" : : "v"(addr), "v"(v), "n"(OFF) : "memory");
 }
+__device__ __forceinline__ void lds_asm_write4(unsigned addr, int v) {
+  asm volatile("ds_write_b32 %0, %1" : : "v"(addr), "v"(v) : "memory");
+}
+// A wait the compiler can see for all but the last N vector memory operations (and for all LDS operations).
+template <int N>
+__device__ __forceinline__ void wait_all_but() {
+  static_assert(N >= 0 && N < 64);
+  __builtin_amdgcn_s_waitcnt((N & 15) | (N >> 4) << 14 | 0x0070);
+}
 __device__ __forceinline__ unsigned lds_addr(const lds_bf16* p) { return (unsigned)(uintptr_t)p; }
 __device__ __forceinline__ unsigned lds_addr(const lds_f32* p) { return (unsigned)(uintptr_t)p; }
 

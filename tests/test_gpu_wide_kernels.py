@@ -1,12 +1,12 @@
-"""The pipelined forward of head dimension 256 at the edges of its tiles (32 query rows per wave, stages of 32 keys, rings of four
-and five stages), with blocks that are taken a second time because a row outgrows its reference maximum, and with more blocks
+"""The pipelined forward and dQ kernels of head dimension 256 at the edges of its tiles (32 query rows per wave, stages of 32 keys, rings of four
+to six stages), with blocks that are taken a second time because a row outgrows its reference maximum, and with more blocks
 than workgroups, against the fp64 oracle (2e-2, as everywhere; LSE: float32 sums of unrounded probabilities, 1e-4)."""
 import pytest
 import torch
 
 import paper_2509_21275_amd as ca
 import synth
-from gpu_util import TOL_O, make_inputs, rel_err, run_gpu
+from gpu_util import TOL_GRAD, TOL_O, make_inputs, rel_err, run_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -42,3 +42,22 @@ def test_late_growth_and_more_blocks_than_workgroups(oracle_mod):
     k[780 + 350:780 + 400] += 3.0
     q[780:] = q[780:].abs() + 1.0
     _check(oracle_mod, case, q, k, v)
+
+
+@pytest.mark.parametrize("segs,hq,hk", [
+    ([(0, 1, 2, 201)], 4, 1),                                  # one query
+    ([(0, 33, 2, 203), (33, 32, 205, 224)], 4, 1),              # a full tile and a tile of one row; walks that end on a stage
+    ([(0, 129, 0, 353)], 6, 2),                                # 128-row items, the last of one row
+    ([(0, 97, 1, 497), (97, 1, 498, 161)], 3, 3),
+    ([(65 * i, 65, 260 * i, 255) for i in range(12)], 16, 16),  # 384 dQ blocks: more than workgroups
+])
+def test_dq_of_long_walks(oracle_mod, segs, hq, hk):
+    """Walks of 5.5 stages or more on average, from where the pipelined dQ kernel runs; the same bits on a second run."""
+    case = _case(segs, hq, hk)
+    q, k, v, do = make_inputs(case)
+    got = run_gpu(case, q, k, v, do)
+    assert all(torch.equal(a, b) for a, b in zip(got, run_gpu(case, q, k, v, do)))
+    orc = oracle_mod.Oracle(case.segs, q.cpu(), k.cpu(), v.cpu(), do.cpu(), case.scale)
+    orc.forward()
+    dQ, dK, dV = orc.backward()
+    assert max(rel_err(got[2], dQ), rel_err(got[3], dK), rel_err(got[4], dV)) <= TOL_GRAD
