@@ -86,8 +86,8 @@ typedef struct {
  * Scratch sizes (bytes) for a descriptor: *fwd_bytes for chunk_attn_fwd, *bwd_bytes for
  * chunk_attn_bwd.  Forward: the tile schedule, then room as for a transposed copy of V, used by
  * the float32 partial results of walks that are cut (96 and 128; up to 16 MiB where the copy would be smaller).  Backward:
- * the schedules, the row sums D_i = <dO_i, O_i> and, for 96 and 128, float32 tiles of dQ or partial results, for 64 and 256
- * partial results of dK / dV walks that are cut (64 MB at most).  For 96 both also
+ * the schedules, the row sums D_i = <dO_i, O_i> and, for 96 and 128, float32 tiles of dQ or partial results (128 MB more
+ * than such tiles take, at most), for 64 and 256 partial results of dK / dV walks that are cut (64 MB at most).  For 96 both also
  * have room for zero-padded copies of the tensors, 128 wide.  Some of that room is used by no kernel of the default mode
  * and kept so that the sizes stay what callers know.  A chunk whose walks would be cut also runs in a somewhat smaller
  * workspace, one that holds its uncut schedule: nothing is cut then, and the results are other roundings of the same sums.

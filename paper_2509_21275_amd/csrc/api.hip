@@ -670,7 +670,8 @@ int bwd_any(const chunk_attn_desc* desc, const void* q, const void* k, const voi
   BwdPlan P;
   auto needed = [&]() { return is_narrow(desc) ? narrow_bwd_layout(desc, P.total).total : P.total; };
   bwd_layout(&w, P, true);
-  if (workspace_bytes < needed()) bwd_layout(&w, P, true, false);  // too small for a cut's item lists: nothing is cut
+  if (workspace_bytes < needed()) bwd_layout(&w, P, true, kCutInPlace);  // too small for all partial results: fewer pieces, or
+  if (workspace_bytes < needed()) bwd_layout(&w, P, true, kCutNone);     // none
   if (workspace_bytes < needed()) return CHUNK_ATTN_WORKSPACE_TOO_SMALL;
   if (is_narrow(desc) && P.fused) {  // the one-pass backward: run as head_dim 128 on zero-padded copies
     const NarrowBwdLayout N = narrow_bwd_layout(desc, P.total);

@@ -3224,7 +3224,7 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
 
 }  // namespace
 
-void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, bool may_cut) {
+void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, Cut cut) {
   P = BwdPlan{};
   const int group = d->num_q_heads / d->num_kv_heads;
   const bool pipe = d->head_dim == 128;
@@ -3243,13 +3243,18 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, bool may_c
   const size_t dq_tile_bytes = pipe ? (size_t)fused_num_bufs(d, dkv_keys(128)) * d->num_q_heads * P.qt32_tiles * 4096 * sizeof(float) : 0;
   P.fused = d->head_dim == 128 && bwd_mode() == 2;
   size_t n_dq = 0, n_dkv = 0;
-  if (pipe && may_cut) {  // (in either mode: the pieces are part of the layout, whose size must not depend on the mode)
+  if (pipe && cut > kCutNone) {  // (in either mode: the pieces are part of the layout, whose size must not depend on the mode)
     const int inner = d->num_kv_heads * (group / heads_per_wg(group, P.dq_waves));
-    P.split = choose_key_split(d, dq_rows, inner, kCus, (int64_t)(dq_tile_bytes / ((size_t)inner * kPartRowFloats * sizeof(float))));
-    P.dkv_split = choose_tile_split(d, dkv_keys(d->head_dim), kCus,
-                                    (int64_t)(dq_tile_bytes / ((size_t)d->num_kv_heads * kPartRowFloats * sizeof(float))));
+    // Whether walks are cut is decided for as many partial results as the float32 dQ tiles have room for; into how many pieces, for
+    // all blocks of the launch together and with room for two partial results per compute unit.  Forward + backward, one decision / two: 439
+    // tokens, 8/2 heads, 67 / 56 us; 557 tokens, 32/8, 73 / 68; slices of 918 and 3264 queries, 8/2, 255 / 240; a hybrid chunk of 1742
+    // queries behind 23348 keys with 3732 packed tokens, 8/8, 996 / 945.  (Finer pieces of each kind by itself: 1144 tokens, 32/8, 110 / 122.)
+    const int64_t room = (int64_t)(dq_tile_bytes / ((size_t)kPartRowFloats * sizeof(float)));
+    P.split = choose_key_split(d, dq_rows, inner, kCus, room / inner);
+    P.dkv_split = choose_tile_split(d, dkv_keys(d->head_dim), kCus, room / d->num_kv_heads);
+    if (cut == kCutFine) refine_bwd_split(d, dq_rows, inner, dkv_keys(d->head_dim), kCus, std::max(room, kMaxShortParts), &P.split, &P.dkv_split);
   }
-  if (!pipe && !P.dkv_pipe && may_cut)
+  if (!pipe && !P.dkv_pipe && cut == kCutFine)
     P.dkv_split = choose_tile_split(d, dkv_keys(d->head_dim), kCus, kMaxShortParts / d->num_kv_heads);
   if (with_plan) {
     if (P.fused) {

@@ -153,8 +153,10 @@ constexpr size_t kClockLogEntries = 4 * 1024;
 unsigned long long* clock_log(int which);
 hipError_t launch_bwd_fused(const chunk_attn_desc* d, const BwdArgs& a, const BwdPlan& plan, const float* lse2p, const float* dsp,
                             hipStream_t stream);
-// Fills the offsets (and, if with_plan, the schedules) for a validated descriptor.  `may_cut`: false: no walk is cut.
-void bwd_layout(const chunk_attn_desc* d, BwdPlan& plan, bool with_plan, bool may_cut = true);
+// Fills the offsets (and, if with_plan, the schedules) for a validated descriptor.  kCutInPlace: only where the partial results fit the
+// room that head_dim 96 and 128 keep for dQ tiles anyway (workspaces of that size may be known to callers); kCutNone: no walk is cut.
+enum Cut { kCutNone, kCutInPlace, kCutFine };
+void bwd_layout(const chunk_attn_desc* d, BwdPlan& plan, bool with_plan, Cut cut = kCutFine);
 // The host image of the blob at the start of the workspace.
 std::vector<char> bwd_blob(const BwdPlan& plan);
 // Enqueues the backward kernels.  A blob of more than kInlineBlob bytes must already be on its way to the workspace on `stream`.

@@ -156,21 +156,68 @@ Walks count_dkv_walks(const chunk_attn_desc* d, int keys) {
   return w;
 }
 
-// The estimate behind both kinds of cut, in steps of a workgroup (about a microsecond each).  A block costs its steps plus
+// The estimate behind the cuts, in steps of a workgroup (about a microsecond each).  A block costs its steps plus
 // kStart for filling the pipeline and writing its rows; a piece kPart more for its float32 rows (twice the bytes).  The
-// blocks of queue 0 (every eighth one) are dealt, longest first, to an eighth of the compute units as they become free.
+// blocks of queue 0 (every eighth one of each kind) are dealt, longest first, to an eighth of the compute units as they become free.
 // Putting the pieces together costs kMerge and the time to read the partial results.  A cut has to win 5 % of the uncut time.
-// `pieces(walk, target)` and `steps(walk, n, k)` (steps of piece k of n) describe a walk, `longest` is the longest one's length
-// in the units of a target, `shortest` what a piece has at least.
 // Measured, uncut -> cut (head_dim 128, 32/8 heads): 1024 queries on 32768 keys, 128 blocks of 1024 stages in two pieces each:
-// forward 744 -> 472 us + 12 us to put them together, dQ 959 -> 625 + 12 us (not half: 128 busy compute units hold a
+// forward 744 -> 472 us + 12 us to put them together (not half: 128 busy compute units hold a
 // higher clock than 256); 203 queries on 1704 keys next to 611 short rows: forward 48 -> 28 + 6 us.  Chunks the estimate
 // leaves alone (8192 queries on 32768 keys: 1024 equal blocks) run as before.
-// dK/dV: two slices of 3193 and 4999 queries of one sequence, 512 and 320 blocks, 1367 -> 1280 us for both.
 constexpr int64_t kMaxCutBlocks = 1024;  // from four blocks per compute unit on they even out by themselves
-template <class Walk, class Pieces, class Steps>
-static KeySplit choose_cut(const std::vector<Walk>& walks, int longest, int shortest, int inner, int cus, int64_t max_parts,
-                           Pieces pieces, Steps steps) {
+
+namespace {
+// The walks of one kind of block (query-stationary over 32-key stages, key-stationary over query tiles).
+struct CutKind {
+  struct Walk { int len, n0; };  // length in units (stages or tiles); n0 of a query-stationary one
+  std::vector<Walk> walks;
+  int inner = 1;        // blocks per walk
+  int group = 0;        // > 0: key-stationary, `group` steps per tile
+  int longest = 0;      // units
+  bool many = false;    // kMaxCutBlocks blocks or more: none of these is cut
+  bool whole = false;   // none of these is to be cut
+  int steps_per_unit() const { return group > 0 ? group : 1; }
+  int shortest() const { return group > 0 ? (2 * kMinPieceStages + group - 1) / group : kMinPieceStages; }  // units of a piece, at least
+  int pieces(const Walk& w, int target) const { return group > 0 ? tile_piece_count(w.len, target) : piece_count(w.len, w.n0, target); }
+  int steps(const Walk& w, int n, int k) const {
+    if (group > 0) return (share_begin(w.len, n, k + 1) - share_begin(w.len, n, k)) * group;
+    return (k + 1 < n ? piece_begin(w.len, n, k + 1) : w.len) - piece_begin(w.len, n, k);
+  }
+  void add(int len, int n0) {
+    walks.push_back(Walk{len, n0});
+    longest = std::max(longest, len);
+    many = (int64_t)walks.size() * inner >= kMaxCutBlocks;
+  }
+};
+
+CutKind key_walks(const chunk_attn_desc* d, int tile_rows, int inner) {
+  CutKind k;
+  k.inner = inner;
+  for (int t = 0; t < d->num_segments; ++t) {
+    const chunk_attn_seg& s = d->segments[t];
+    for (int32_t i0 = 0; i0 < s.q_len; i0 += tile_rows) {
+      const int32_t n0 = s.kv_len - s.q_len + i0 + 1;
+      k.add(walk_stages(n0, std::min<int32_t>(tile_rows, s.q_len - i0)), n0);
+    }
+  }
+  return k;
+}
+
+CutKind tile_walks(const chunk_attn_desc* d, int keys) {
+  CutKind k;
+  k.inner = d->num_kv_heads;
+  k.group = d->num_q_heads / d->num_kv_heads;
+  for (int t = 0; t < d->num_segments; ++t) {
+    const chunk_attn_seg& s = d->segments[t];
+    const int32_t C = s.kv_len - s.q_len, n_qt = (s.q_len + 31) / 32;
+    for (int32_t j0 = 0; j0 < s.kv_len; j0 += keys) k.add(n_qt - std::max<int32_t>(0, j0 - C) / 32, 0);
+  }
+  return k;
+}
+
+// The cut of N kinds of block that share the compute units, one split each; at most max_parts[i] partial results of kind i.
+template <int N>
+void choose_cut(const CutKind (&kinds)[N], int cus, const int64_t (&max_parts)[N], KeySplit (&best)[N]) {
   constexpr int kStart = 12, kPart = 6, kMerge = 6;
   constexpr int64_t kPartsPerStep = 32;  // partial results (128 KB per block) read per step
   const int workers = std::max(1, cus / 8);
@@ -178,37 +225,53 @@ static KeySplit choose_cut(const std::vector<Walk>& walks, int longest, int shor
   std::vector<int64_t> free_at;
   int64_t total = 0;    // work of queue 0 ...
   int largest = 0;      // ... and its longest block
+  bool many = false;
   // blocks of queue 0 among the `inner` ones that start at block b: those divisible by 8
-  auto in_queue = [&](int64_t b) { return (b + inner + 7) / 8 - (b + 7) / 8; };
-  auto count_pieces = [&](KeySplit& k) {
-    k.pieces = k.parts = 0;
-    for (const Walk& w : walks) {
-      const int n = pieces(w, k.target);
-      k.pieces += n;
-      if (n > 1) k.parts += n;
-    }
-  };
-  auto count_work = [&](const KeySplit& k) {
-    total = largest = 0;
-    int64_t block = 0;
-    for (const Walk& w : walks) {
-      const int n = pieces(w, k.target);
-      for (int i = 0; i < n; ++i, block += inner) {
-        const int64_t q = in_queue(block);
-        if (q == 0) continue;
-        const int c = steps(w, n, i) + kStart + (n > 1 ? kPart : 0);
-        total += q * c;
-        largest = std::max(largest, c);
+  auto in_queue = [](int64_t b, int inner) { return (b + inner + 7) / 8 - (b + 7) / 8; };
+  auto count_pieces = [&](KeySplit (&k)[N]) {
+    for (int i = 0; i < N; ++i) {
+      k[i].pieces = k[i].parts = 0;
+      for (const auto& w : kinds[i].walks) {
+        const int n = kinds[i].pieces(w, k[i].target);
+        k[i].pieces += n;
+        if (n > 1) k[i].parts += n;
       }
     }
   };
-  auto merge_time = [&](const KeySplit& k) { return k.parts > 0 ? kMerge + k.parts * inner / kPartsPerStep : 0; };
-  auto simulate = [&](const KeySplit& k) -> int64_t {
+  auto count_work = [&](const KeySplit (&k)[N]) {
+    total = largest = 0;
+    for (int i = 0; i < N; ++i) {
+      const CutKind& kind = kinds[i];
+      int64_t block = 0;
+      for (const auto& w : kind.walks) {
+        const int n = kind.pieces(w, k[i].target);
+        for (int x = 0; x < n; ++x, block += kind.inner) {
+          const int64_t q = in_queue(block, kind.inner);
+          if (q == 0) continue;
+          const int c = kind.steps(w, n, x) + kStart + (n > 1 ? kPart : 0);
+          total += q * c;
+          largest = std::max(largest, c);
+        }
+      }
+    }
+  };
+  auto merge_time = [&](const KeySplit (&k)[N]) {
+    int64_t parts = 0;
+    for (int i = 0; i < N; ++i) parts += k[i].parts * kinds[i].inner;
+    return parts > 0 ? kMerge + parts / kPartsPerStep : 0;
+  };
+  // (needs count_work of the same splits)
+  auto estimate = [&](const KeySplit (&k)[N]) -> int64_t {
+    if (many) return std::max<int64_t>(total / workers, largest) + merge_time(k);  // many small blocks fill every gap
     cost.clear();
-    int64_t block = 0;
-    for (const Walk& w : walks) {
-      const int n = pieces(w, k.target);
-      for (int i = 0; i < n; ++i, block += inner) cost.insert(cost.end(), in_queue(block), steps(w, n, i) + kStart + (n > 1 ? kPart : 0));
+    for (int i = 0; i < N; ++i) {
+      const CutKind& kind = kinds[i];
+      int64_t block = 0;
+      for (const auto& w : kind.walks) {
+        const int n = kind.pieces(w, k[i].target);
+        for (int x = 0; x < n; ++x, block += kind.inner)
+          cost.insert(cost.end(), in_queue(block, kind.inner), kind.steps(w, n, x) + kStart + (n > 1 ? kPart : 0));
+      }
     }
     std::sort(cost.begin(), cost.end(), [](int a, int b) { return a > b; });
     free_at.assign(workers, 0);  // a heap, earliest first
@@ -226,66 +289,88 @@ static KeySplit choose_cut(const std::vector<Walk>& walks, int longest, int shor
     }
     return last + merge_time(k);
   };
-  KeySplit best;
+  int longest = 0, shortest = 0x7fffffff;  // steps
+  for (int i = 0; i < N; ++i) {
+    best[i] = KeySplit{};
+    many |= kinds[i].many;
+    if (kinds[i].many || kinds[i].whole) continue;
+    longest = std::max(longest, kinds[i].longest * kinds[i].steps_per_unit());
+    shortest = std::min(shortest, kinds[i].shortest() * kinds[i].steps_per_unit());
+  }
+  if (longest == 0) return;  // nothing that may be cut
   count_pieces(best);
   count_work(best);
-  int64_t best_time = simulate(best);
+  int64_t best_time = estimate(best);
   best_time -= best_time / 20;
-  if (total / workers >= best_time) return best;  // as even as it can get: pieces only add to the work
+  if (total / workers >= best_time) return;  // as even as it can get: pieces only add to the work
   // The choice is part of every call, so a candidate that cannot win is not followed further: one with too many partial
   // results, or whose work shared evenly, or longest block alone, already takes as long as the best so far.
+  bool found = false;
   for (int n = 2; n <= 16 && longest / n >= shortest; ++n) {
-    KeySplit k;
-    k.target = (longest + n - 1) / n;
+    KeySplit k[N];
+    for (int i = 0; i < N; ++i) {
+      const int unit = kinds[i].steps_per_unit(), target = ((longest + n - 1) / n + unit - 1) / unit;
+      if (!kinds[i].many && !kinds[i].whole && kinds[i].longest > target) k[i].target = std::max(target, kinds[i].shortest());
+    }
     count_pieces(k);
-    if (k.pieces * inner > 2 * kMaxCutBlocks) break;
-    if (k.parts == 0 || k.parts > max_parts) continue;
+    int64_t blocks = 0, parts = 0;
+    bool fits = true;
+    for (int i = 0; i < N; ++i) {
+      if (!kinds[i].many) blocks = std::max(blocks, k[i].pieces * kinds[i].inner);
+      parts += k[i].parts;
+      fits &= k[i].parts <= max_parts[i];
+    }
+    if (blocks > 2 * kMaxCutBlocks) break;
+    if (parts == 0 || !fits) continue;
     count_work(k);
     if (std::max<int64_t>(total / workers, largest) + merge_time(k) >= best_time) continue;
-    const int64_t time = simulate(k);
+    const int64_t time = estimate(k);
     if (time < best_time) {
-      best = k;
+      std::copy(k, k + N, best);
       best_time = time;
+      found = true;
     }
   }
-  return best;
+  // a kind whose cut brings nothing stays whole
+  if (N > 1 && found) {
+    for (int i = 0; i < N; ++i) {
+      if (best[i].parts == 0) continue;
+      KeySplit k[N];
+      std::copy(best, best + N, k);
+      k[i].target = 0;
+      count_pieces(k);
+      count_work(k);
+      if (estimate(k) <= best_time + best_time / 50) std::copy(k, k + N, best);
+    }
+  }
+  for (KeySplit& k : best)
+    if (k.parts == 0) k.target = 0;
 }
+}  // namespace
 
 KeySplit choose_key_split(const chunk_attn_desc* d, int tile_rows, int inner, int cus, int64_t max_parts) {
-  struct Walk { int stages, n0; };
-  std::vector<Walk> walks;
-  int longest = 0;
-  for (int t = 0; t < d->num_segments; ++t) {
-    const chunk_attn_seg& s = d->segments[t];
-    for (int32_t i0 = 0; i0 < s.q_len; i0 += tile_rows) {
-      const int32_t n0 = s.kv_len - s.q_len + i0 + 1, rows = std::min<int32_t>(tile_rows, s.q_len - i0);
-      walks.push_back(Walk{walk_stages(n0, rows), n0});
-      longest = std::max(longest, walks.back().stages);
-      if ((int64_t)walks.size() * inner >= kMaxCutBlocks) return KeySplit{};
-    }
-  }
-  return choose_cut(
-      walks, longest, kMinPieceStages, inner, cus, max_parts, [](const Walk& w, int target) { return piece_count(w.stages, w.n0, target); },
-      [](const Walk& w, int n, int k) { return (k + 1 < n ? piece_begin(w.stages, n, k + 1) : w.stages) - piece_begin(w.stages, n, k); });
+  const CutKind kinds[1] = {key_walks(d, tile_rows, inner)};
+  KeySplit best[1];
+  choose_cut<1>(kinds, cus, {max_parts}, best);
+  return best[0];
 }
 
 KeySplit choose_tile_split(const chunk_attn_desc* d, int keys, int cus, int64_t max_parts) {
-  const int group = d->num_q_heads / d->num_kv_heads;
-  std::vector<int> walks;  // query tiles per key block
-  int longest = 0;
-  for (int t = 0; t < d->num_segments; ++t) {
-    const chunk_attn_seg& s = d->segments[t];
-    const int32_t C = s.kv_len - s.q_len, n_qt = (s.q_len + 31) / 32;
-    for (int32_t j0 = 0; j0 < s.kv_len; j0 += keys) {
-      walks.push_back(n_qt - std::max<int32_t>(0, j0 - C) / 32);
-      longest = std::max(longest, walks.back());
-      if ((int64_t)walks.size() * d->num_kv_heads >= kMaxCutBlocks) return KeySplit{};
-    }
-  }
-  return choose_cut(
-      walks, longest, (2 * kMinPieceStages + group - 1) / group, d->num_kv_heads, cus, max_parts,
-      [](int tiles, int target) { return tile_piece_count(tiles, target); },
-      [&](int tiles, int n, int k) { return (share_begin(tiles, n, k + 1) - share_begin(tiles, n, k)) * group; });
+  const CutKind kinds[1] = {tile_walks(d, keys)};
+  KeySplit best[1];
+  choose_cut<1>(kinds, cus, {max_parts}, best);
+  return best[0];
+}
+
+void refine_bwd_split(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int cus, int64_t max_parts, KeySplit* dq, KeySplit* dkv) {
+  CutKind kinds[2] = {key_walks(d, tile_rows, inner), tile_walks(d, keys)};
+  kinds[0].whole = dq->target == 0;
+  kinds[1].whole = dkv->target == 0;
+  if (kinds[0].whole && kinds[1].whole) return;
+  KeySplit best[2];
+  choose_cut<2>(kinds, cus, {max_parts / inner, max_parts / d->num_kv_heads}, best);
+  if (best[0].target > 0) *dq = best[0];
+  if (best[1].target > 0) *dkv = best[1];
 }
 
 std::vector<DkvItem> cut_items(const std::vector<DkvItem>& wholes, int target, std::vector<DkvItem>* cut) {

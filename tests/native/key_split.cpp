@@ -2,7 +2,8 @@
 //   * the pieces of an item are consecutive, begin on even stages, cover its keys once and in order;
 //   * the first key of a piece is visible to the item's first row, every piece but the last is visible whole to every row;
 //   * slots of partial results are handed out in order, to pieces of cut items only;
-//   * choose_key_split counts what cut_items makes, respects its limit, cuts chunks with few long walks and no others.
+//   * choose_key_split and refine_bwd_split count what cut_items makes and respect their limits; choose_key_split cuts chunks with few long
+//     walks and no others.
 #include <algorithm>
 #include <cstdio>
 #include <random>
@@ -105,6 +106,21 @@ static int one(const std::vector<chunk_attn_seg>& segs, int heads, int kv_heads,
       for (const auto& c : cut) parts += c.in_step;
       REQUIRE(k.pieces == (int64_t)items.size() && k.parts == parts && parts > 0);
     }
+  }
+  for (int64_t limit : {(int64_t)3, (int64_t)40, (int64_t)1 << 40}) {  // both kinds of a backward: kinds left whole stay whole
+    const KeySplit q0 = choose_key_split(&d, rows, inner, 256, limit / inner), k0 = choose_tile_split(&d, 128, 256, limit / kv_heads);
+    KeySplit q1 = q0, k1 = k0;
+    refine_bwd_split(&d, rows, inner, 128, 256, 2 * limit, &q1, &k1);
+    REQUIRE((q1.target > 0) == (q0.target > 0) && (k1.target > 0) == (k0.target > 0));
+    REQUIRE(q1.parts * inner <= 2 * limit && k1.parts * kv_heads <= 2 * limit);
+    std::vector<DqItem> qcut;
+    std::vector<DkvItem> kcut;
+    const auto qi = cut_items(plan_dq(&d, rows), q1.target, &qcut);
+    const auto ki = cut_items(plan_dkv(&d, 128), k1.target, &kcut);
+    int64_t qp = 0, kp = 0;
+    for (const auto& c : qcut) qp += c.kv_tile0;
+    for (const auto& c : kcut) kp += c.in_step;
+    REQUIRE(qp == q1.parts && kp == k1.parts && (q1.target == 0 || q1.pieces == (int64_t)qi.size()) && (k1.target == 0 || k1.pieces == (int64_t)ki.size()));
   }
   for (int64_t limit : {(int64_t)0, (int64_t)3, (int64_t)1 << 40}) {
     const KeySplit k = choose_key_split(&d, rows, inner, 256, limit);
