@@ -126,7 +126,7 @@ struct DqParams {
 // burst behind the products / as they are now: head_dim 64, 128 queries on 16384 keys, 8/8 heads, 314 / 334 / 293 us, 512
 // queries, 32/8 heads, 476 / 484 / 450; head_dim 256, 64 queries on 8192 keys, 8/8 heads, 413 / 427 / 388.
 template <int D, int WAVES>
-__global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void bwd_dq_kernel(DqParams p) {
+__device__ __forceinline__ void dq_block(const DqParams& p, int blk) {
   constexpr int NTH = WAVES * 64;  // threads
   constexpr int BN = 32;       // key rows per LDS tile
   constexpr int KC = D / 8;    // 16-byte chunks per K / V row
@@ -146,8 +146,8 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void bwd_dq_ke
   stagger_wave_priority();
 
   const int inner_n = p.num_kv_heads * p.head_splits;
-  const int inner = blockIdx.x % inner_n;
-  const DqItem it = p.items[blockIdx.x / inner_n];
+  const int inner = blk % inner_n;
+  const DqItem it = p.items[blk / inner_n];
   const int kvh = inner % p.num_kv_heads, hs = inner / p.num_kv_heads;
   const int head = kvh * p.group + hs * p.heads_per_wg + wave % p.heads_per_wg;
   const int wave_row0 = (wave / p.heads_per_wg) * 32;
@@ -342,6 +342,11 @@ __global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void bwd_dq_ke
   }
 }
 
+template <int D, int WAVES>
+__global__ __launch_bounds__(WAVES * 64, D > 128 ? 1 : 8 / WAVES) void bwd_dq_kernel(DqParams p) {
+  dq_block<D, WAVES>(p, blockIdx.x);
+}
+
 // ------------------------------------------------------------------------------------------------
 // bwd_dkv
 //
@@ -401,7 +406,7 @@ __device__ __forceinline__ void dkv_store4(const DkvParams& p, __bf16* out, int6
 
 
 template <int D, int KB, bool CUT>  // KB: 32-key blocks per workgroup (2 KB waves); CUT: some items are pieces
-__global__ __launch_bounds__(KB * 128, D > 128 ? 1 : 4 / KB) void bwd_dkv_kernel(DkvParams p) {
+__device__ __forceinline__ void dkv_block(const DkvParams& p, int blk) {
   constexpr int NW = 2 * KB;   // waves
   constexpr int NTH = NW * 64; // threads
   constexpr int BM = 32;       // query rows per step
@@ -430,8 +435,8 @@ __global__ __launch_bounds__(KB * 128, D > 128 ? 1 : 4 / KB) void bwd_dkv_kernel
   const int role = wave / KB, kb = wave % KB;
   const int l32 = lane & 31, hh = lane >> 5;
 
-  const int kvh = blockIdx.x % p.num_kv_heads;
-  const DkvItem it = p.items[blockIdx.x / p.num_kv_heads];
+  const int kvh = blk % p.num_kv_heads;
+  const DkvItem it = p.items[blk / p.num_kv_heads];
   const int G = p.group;
   const int64_t q_stride = (int64_t)p.num_q_heads * D, kv_stride = (int64_t)p.num_kv_heads * D;
   const float c = p.scale_log2;
@@ -688,6 +693,11 @@ __global__ __launch_bounds__(KB * 128, D > 128 ? 1 : 4 / KB) void bwd_dkv_kernel
         }
     }
   }
+}
+
+template <int D, int KB, bool CUT>
+__global__ __launch_bounds__(KB * 128, D > 128 ? 1 : 4 / KB) void bwd_dkv_kernel(DkvParams p) {
+  dkv_block<D, KB, CUT>(p, blockIdx.x);
 }
 
 // LDS instructions of one step of dkv_pipe_blocks in program order, per wave role, and the waits that follow from
@@ -2568,7 +2578,7 @@ static_assert(wide_kind(0) == 0 && wide_kind(1) == 1 && wide_kind(3) == 2 && wid
               wide_index(1) == 0 && wide_index(3) == 0 && wide_index(5) == 1 && wide_index(29) == 7 && wide_index(30) == 15 && wide_index(31) == 7 &&
               wide_index(32) == 8 && wide_index(47) == 15 && wide_wait(0, 6) == 6 && wide_wait(32, 6) == 8, "worked out by hand");
 
-__global__ __launch_bounds__(256, 1) void bwd_dq_wide_kernel(DqParams) {
+__device__ __forceinline__ void dq_wide_blocks(ArgsPtr<DqParams> args, int mine) {
   constexpr int D = 256;
   constexpr int NW = 4;        // waves
   constexpr int BN = 32;       // key rows per stage
@@ -2592,15 +2602,14 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_wide_kernel(DqParams) {
   // doubles as the slot through which wave 0 announces the next block
   constexpr int ST_OFF = V_OFF;
 
-  const ArgsPtr<DqParams> args = (ArgsPtr<DqParams>)__builtin_amdgcn_kernarg_segment_ptr();
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hh = lane >> 5;
   int* const next_block = (int*)((__bf16*)smem + ST_OFF);
 
   const int xcd = xcd_of_this_wave();
-  const bool direct = args->num_blocks <= (int)gridDim.x;
-  int blk = blockIdx.x;
+  const bool direct = mine != kClaimBlocks;
+  int blk = mine;
   if (!direct) {
     const DqParams p = fresh(args);
     if (wave == 0) blk = block_claim_finish(p.taken, p.num_blocks, xcd, block_claim_issue(p.taken, xcd));
@@ -2902,6 +2911,11 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_wide_kernel(DqParams) {
   }
 }
 
+__global__ __launch_bounds__(256, 1) void bwd_dq_wide_kernel(DqParams) {
+  const ArgsPtr<DqParams> args = (ArgsPtr<DqParams>)__builtin_amdgcn_kernarg_segment_ptr();
+  dq_wide_blocks(args, args->num_blocks <= (int)gridDim.x ? (int)blockIdx.x : kClaimBlocks);
+}
+
 // ------------------------------------------------------------------------------------------------
 // bwd_pipe (head_dim 128 and 96): the dQ and the dK/dV blocks of a chunk in one launch
 //
@@ -2933,6 +2947,22 @@ __global__ __launch_bounds__(256, 1) void bwd_pipe_kernel(BwdPipeParams) {
     if (is_dq) dq_pipe_blocks<D, CUT>(&args->dq, mine);
     else dkv_pipe_blocks<D, CUT>(&args->dkv, mine);
     if (mine >= 0) break;
+  }
+}
+
+// The same for small chunks of head_dim 64 and 256, a workgroup per block: the dK/dV blocks, then the dQ blocks.  Each kind is a chain of
+// launch, first copies and a walk of a few stages on a part of the compute units, and neither waits for the other here.  At 64 a dQ block
+// takes four of the eight waves; the others end at once (a barrier waits for the waves that are left).  Only chunks whose
+// blocks all find a compute unit of their own (short_joins).
+template <int D, int KB, bool CUT, bool WIDE>
+__global__ __launch_bounds__(KB * 128, D > 128 ? 1 : 4 / KB) void bwd_short_kernel(BwdPipeParams p) {
+  const int blk = (int)blockIdx.x - p.dkv.num_blocks;
+  if (blk < 0) {
+    dkv_block<D, KB, CUT>(p.dkv, blockIdx.x);
+  } else if constexpr (WIDE) {
+    dq_wide_blocks(&((ArgsPtr<BwdPipeParams>)__builtin_amdgcn_kernarg_segment_ptr())->dq, blk);
+  } else if (threadIdx.x < 256) {
+    dq_block<D, 4>(p.dq, blk);
   }
 }
 
@@ -3044,6 +3074,11 @@ constexpr int64_t kMaxShortParts = 2 * kCus;  // partial results of such a chunk
 // 283 / 277; four of 256, 8/8 (6) 50 / 49; 148 queries on 595 keys, 8/2 (17) 76 / 72; 32/8 heads: eight sequences of 220 (4) 107 / 111, 64 of 220 (4) 639 / 652,
 // 64 of 256 (4.5) 776 / 760; 1024 causal tokens (16.5) 144 / 135; 909 on 5603 keys (161) 638 / 598.
 bool dq_wide_pays(const Walks& w) { return 2 * w.stages >= 11 * w.items; }
+
+// Whether a chunk of head_dim 64 or 256 runs its dQ and dK/dV blocks in one launch (bwd_short_kernel): if each has a compute unit to itself.
+// Backward, two launches / one: head_dim 64, four sequences of 256, 8/8 heads, 22.7 / 16.8 us; 1024 tokens 49.4 / 30.6; 300 queries on 3300 keys
+// 70.1 / 58.2; 500 tokens, 32/8, 36.7 / 25.2; head_dim 256, 512 tokens, 8/8, 65 / 38; 148 queries on 595 keys, 8/2, 71 / 42; 1000 tokens, 8/2 (cut), 97 / 66.
+bool short_joins(const BwdPlan& P, int64_t blocks) { return !P.dq_pipe && !P.dkv_pipe && blocks <= kCus; }
 
 // workgroups of the pipelined dK/dV kernels on a CU
 constexpr int dkv_per_cu(int head_dim) { return head_dim == 64 ? 2 : 1; }
@@ -3159,7 +3194,31 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
                          reinterpret_cast<const DkvItem*>(ws + P.dkv_cut_off));
     if ((e = hipGetLastError()) != hipSuccess) return e;
   } else {
-    if (D == 256 && P.dq_wide) {
+    constexpr int KB = (D > 128 ? 64 : DKV_KEYS) / 32;  // as dkv_keys(D)
+    // 4 ring slots of two 32-row operand tiles, 2 P hand-over slots, 4 slots of LSE and D rows
+    constexpr size_t dkv_smem = (size_t)8 * 32 * D * 2 + 2 * KB * 1024 * 2 + 2 * 4 * 64 * sizeof(float);
+    const bool joint = short_joins(P, dq_blocks + dkv_blocks);
+    if (joint) {
+      BwdPipeParams p;
+      p.dq = pq;
+      p.dkv = pk;
+      p.dq_phase = 1;
+      const dim3 grid((unsigned)(dq_blocks + dkv_blocks));
+      auto run = [&](auto cut_c, auto wide_c) {
+        constexpr bool CUT = decltype(cut_c)::value, WIDE = decltype(wide_c)::value;
+        constexpr size_t dq_smem = (size_t)(WIDE ? 10 : 6) * 32 * D * 2, smem = dq_smem > dkv_smem ? dq_smem : dkv_smem;  // (as below)
+        static const hipError_t attr = raise_smem_limit(&bwd_short_kernel<D, KB, CUT, WIDE>, smem);
+        if (attr != hipSuccess) return attr;
+        hipError_t err;
+        if (pe.start && (err = hipEventRecord(pe.start, stream)) != hipSuccess) return err;
+        hipLaunchKernelGGL((bwd_short_kernel<D, KB, CUT, WIDE>), grid, dim3(KB * 128), smem, stream, p);
+        return hipGetLastError();
+      };
+      const std::bool_constant<D == 256> wide;
+      if (P.n_dkv_cut == 0) e = P.dq_wide ? run(std::false_type{}, wide) : run(std::false_type{}, std::false_type{});
+      else e = P.dq_wide ? run(std::true_type{}, wide) : run(std::true_type{}, std::false_type{});
+      if (e != hipSuccess) return e;
+    } else if (D == 256 && P.dq_wide) {
       const size_t smem = (size_t)10 * 32 * D * 2;  // six slots of K and four of V
       static const hipError_t attr = raise_smem_limit(&bwd_dq_wide_kernel, smem);
       if (attr != hipSuccess) return attr;
@@ -3198,24 +3257,22 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
         hipLaunchKernelGGL((bwd_dkv_wide_pipe_kernel<D>), dim3((unsigned)persistent_grid(dkv_blocks)), dim3(256), smem, stream, pk, (int)dkv_blocks);
       }
     }
-    if (!P.dkv_pipe) {
-      // 4 ring slots of two 32-row operand tiles, 2 P hand-over slots, 4 slots of LSE and D rows
-      constexpr int KB = (D > 128 ? 64 : DKV_KEYS) / 32;   // as dkv_keys(D)
-      const size_t smem = (size_t)8 * 32 * D * 2 + 2 * KB * 1024 * 2 + 2 * 4 * 64 * sizeof(float);
+    if (!joint && !P.dkv_pipe) {
       if (pe.start && (e = hipEventRecord(pe.start, stream)) != hipSuccess) return e;
       if (P.n_dkv_cut == 0) {
-        static const hipError_t attr = raise_smem_limit(&bwd_dkv_kernel<D, KB, false>, smem);
+        static const hipError_t attr = raise_smem_limit(&bwd_dkv_kernel<D, KB, false>, dkv_smem);
         if (attr != hipSuccess) return attr;
-        hipLaunchKernelGGL((bwd_dkv_kernel<D, KB, false>), dim3((unsigned)dkv_blocks), dim3(KB * 128), smem, stream, pk);
+        hipLaunchKernelGGL((bwd_dkv_kernel<D, KB, false>), dim3((unsigned)dkv_blocks), dim3(KB * 128), dkv_smem, stream, pk);
       } else {
-        static const hipError_t attr = raise_smem_limit(&bwd_dkv_kernel<D, KB, true>, smem);
+        static const hipError_t attr = raise_smem_limit(&bwd_dkv_kernel<D, KB, true>, dkv_smem);
         if (attr != hipSuccess) return attr;
-        hipLaunchKernelGGL((bwd_dkv_kernel<D, KB, true>), dim3((unsigned)dkv_blocks), dim3(KB * 128), smem, stream, pk);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        hipLaunchKernelGGL((bwd_merge_kernel<D>), dim3((unsigned)(2 * KB * P.n_dkv_cut * d->num_kv_heads)), dim3(256), 0, stream, pq,
-                           static_cast<const DqItem*>(nullptr), 0, pk, reinterpret_cast<const DkvItem*>(ws + P.dkv_cut_off));
+        hipLaunchKernelGGL((bwd_dkv_kernel<D, KB, true>), dim3((unsigned)dkv_blocks), dim3(KB * 128), dkv_smem, stream, pk);
       }
     }
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (P.n_dkv_cut > 0)
+      hipLaunchKernelGGL((bwd_merge_kernel<D>), dim3((unsigned)(2 * KB * P.n_dkv_cut * d->num_kv_heads)), dim3(256), 0, stream, pq,
+                         static_cast<const DqItem*>(nullptr), 0, pk, reinterpret_cast<const DkvItem*>(ws + P.dkv_cut_off));
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if (pe.stop && (e = hipEventRecord(pe.stop, stream)) != hipSuccess) return e;

@@ -40,6 +40,25 @@ def test_schedules_on_both_sides_of_each_line(oracle_mod, n, hq, hk, d):
         assert torch.equal(o, o2) and torch.equal(lse, lse2)
 
 
+@pytest.mark.parametrize("d,n,rows,hq,hk", [
+    # blocks of both kinds before any dK/dV walk is cut
+    (256, 10, 200, 4, 4), (256, 11, 200, 4, 4),  # 240, 264; 5.5 stages per dQ walk: the pipelined dQ kernel
+    (256, 8, 65, 24, 6), (256, 9, 65, 24, 6),    # 240, 270; dQ items of 32 rows and four heads, the last of one row
+    (64, 18, 129, 8, 2), (64, 19, 129, 8, 2),    # 252, 266; the same at 64
+    (64, 1, 1, 1, 1), (256, 1, 1, 1, 1),         # one row
+])
+def test_dq_and_dkv_blocks_in_one_launch_and_in_two(oracle_mod, d, n, rows, hq, hk):
+    """Head dimensions 64 and 256 run both kinds of block in one launch up to 256 of them; the same bits on a second run."""
+    case = synth.ChunkCase("joint", synth.packed_chunk([rows] * n), n * rows, n * rows, hq, hk, d, 90 + n)
+    q, k, v, do = make_inputs(case)
+    got = run_gpu(case, q, k, v, do)
+    assert all(torch.equal(a, b) for a, b in zip(got, run_gpu(case, q, k, v, do)))
+    orc = oracle_mod.Oracle(case.segs, q.cpu(), k.cpu(), v.cpu(), do.cpu(), case.scale)
+    orc.forward()
+    dQ, dK, dV = orc.backward()
+    assert max(rel_err(got[2], dQ), rel_err(got[3], dK), rel_err(got[4], dV)) <= TOL_GRAD
+
+
 @pytest.mark.parametrize("f32kv", [False, True])
 @pytest.mark.parametrize("d,segs,hq,hk", [
     (64, [(0, 1100, 5, 1400), (1100, 77, 1410, 77)], 6, 2),      # pieces of three query heads per tile, a ragged last block
