@@ -167,7 +167,7 @@ int64_t chunk_attn_pair_count(const chunk_attn_desc* desc);
  * Measurement hook (not part of the method): arms one pair of hipEvent_t (passed as void*) for the
  * calling thread.  The next chunk_attn_fwd or chunk_attn_bwd call on this thread records `start`
  * immediately before and `stop` immediately after its main kernel (the forward kernel, resp. the
- * dQ and dK/dV kernel of the backward; the dK/dV kernel alone for head_dim 64 and 256, small chunks aside) on that call's
+ * dQ and dK/dV kernel of the backward; the dK/dV kernel alone for head_dim 64 and 256 where it is a launch of its own) on that call's
  * stream, then disarms.  Pass NULLs to disarm.
  * The caller owns the events.  Always returns CHUNK_ATTN_OK.
  */

@@ -2950,15 +2950,16 @@ __global__ __launch_bounds__(256, 1) void bwd_pipe_kernel(BwdPipeParams) {
   }
 }
 
-// The same for small chunks of head_dim 64 and 256, a workgroup per block: the dK/dV blocks, then the dQ blocks.  Each kind is a chain of
-// launch, first copies and a walk of a few stages on a part of the compute units, and neither waits for the other here.  At 64 a dQ block
-// takes four of the eight waves; the others end at once (a barrier waits for the waves that are left).  Only chunks whose
-// blocks all find a compute unit of their own (short_joins).
+// The same for chunks of head_dim 64 and 256 that are too small or too short for the pipelined dK/dV kernels, a workgroup per block.  Each kind by
+// itself is a launch, first copies and walks that leave compute units idle at their end; neither waits for the other here.  At 64 a
+// dQ block takes four of the eight waves; the others end at once (a barrier waits for the waves that are left).  Figures: short_joins.
 template <int D, int KB, bool CUT, bool WIDE>
 __global__ __launch_bounds__(KB * 128, D > 128 ? 1 : 4 / KB) void bwd_short_kernel(BwdPipeParams p) {
-  const int blk = (int)blockIdx.x - p.dkv.num_blocks;
-  if (blk < 0) {
-    dkv_block<D, KB, CUT>(p.dkv, blockIdx.x);
+  const int first = p.dq_phase == 0 ? p.dq.num_blocks : p.dkv.num_blocks;
+  const bool second = (int)blockIdx.x >= first;
+  const int blk = second ? (int)blockIdx.x - first : (int)blockIdx.x;
+  if (second == (p.dq_phase == 0)) {
+    dkv_block<D, KB, CUT>(p.dkv, blk);
   } else if constexpr (WIDE) {
     dq_wide_blocks(&((ArgsPtr<BwdPipeParams>)__builtin_amdgcn_kernarg_segment_ptr())->dq, blk);
   } else if (threadIdx.x < 256) {
@@ -3075,10 +3076,14 @@ constexpr int64_t kMaxShortParts = 2 * kCus;  // partial results of such a chunk
 // 64 of 256 (4.5) 776 / 760; 1024 causal tokens (16.5) 144 / 135; 909 on 5603 keys (161) 638 / 598.
 bool dq_wide_pays(const Walks& w) { return 2 * w.stages >= 11 * w.items; }
 
-// Whether a chunk of head_dim 64 or 256 runs its dQ and dK/dV blocks in one launch (bwd_short_kernel): if each has a compute unit to itself.
-// Backward, two launches / one: head_dim 64, four sequences of 256, 8/8 heads, 22.7 / 16.8 us; 1024 tokens 49.4 / 30.6; 300 queries on 3300 keys
-// 70.1 / 58.2; 500 tokens, 32/8, 36.7 / 25.2; head_dim 256, 512 tokens, 8/8, 65 / 38; 148 queries on 595 keys, 8/2, 71 / 42; 1000 tokens, 8/2 (cut), 97 / 66.
-bool short_joins(const BwdPlan& P, int64_t blocks) { return !P.dq_pipe && !P.dkv_pipe && blocks <= kCus; }
+// Whether a chunk of head_dim 64 or 256 runs its dQ and dK/dV blocks in one launch (bwd_short_kernel): where neither kind is pipelined with
+// blocks of its own shape, as long as one grid holds both.  The kind with the longer walks goes first; at 64, dQ if they are equal.  (A dQ block
+// of 64 holds the place of eight waves in that launch, which the other kind going on under it outweighs.)
+// Backward, two launches / one: head_dim 64, four sequences of 256, 8/8 heads, 22.7 / 16.5 us; 1024 tokens 49.4 / 30.9; 3000 tokens 102 / 72; 1185
+// tokens behind 52, 32/8, 67 / 48; 24 sequences of 200, 64/8, 142 / 125; 64 of 256, 8/8, 77.9 / 75.7 (dK/dV first 79.5); 128 of 256 143.5 / 143.4; 16
+// times 64 queries on 2000 keys 91 / 67 (dK/dV first 99); head_dim 256, 512 tokens, 8/8, 65 / 38; 148 queries on 595 keys, 8/2, 71 / 42; 1500
+// tokens, 64/8, 394 / 366; 300 queries on 3000 keys, 32/8, 231 / 162; 128 sequences of 128, 32/8, 733 / 700; 40 of 150, 8/8, 122 / 109 (dQ first 113).
+bool short_joins(const BwdPlan& P, int64_t blocks, int threads) { return !P.dq_pipe && !P.dkv_pipe && blocks * threads < (int64_t)1 << 32; }
 
 // workgroups of the pipelined dK/dV kernels on a CU
 constexpr int dkv_per_cu(int head_dim) { return head_dim == 64 ? 2 : 1; }
@@ -3197,12 +3202,12 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
     constexpr int KB = (D > 128 ? 64 : DKV_KEYS) / 32;  // as dkv_keys(D)
     // 4 ring slots of two 32-row operand tiles, 2 P hand-over slots, 4 slots of LSE and D rows
     constexpr size_t dkv_smem = (size_t)8 * 32 * D * 2 + 2 * KB * 1024 * 2 + 2 * 4 * 64 * sizeof(float);
-    const bool joint = short_joins(P, dq_blocks + dkv_blocks);
+    const bool joint = short_joins(P, dq_blocks + dkv_blocks, KB * 128);
     if (joint) {
       BwdPipeParams p;
       p.dq = pq;
       p.dkv = pk;
-      p.dq_phase = 1;
+      p.dq_phase = P.dq_first ? 0 : 1;
       const dim3 grid((unsigned)(dq_blocks + dkv_blocks));
       auto run = [&](auto cut_c, auto wide_c) {
         constexpr bool CUT = decltype(cut_c)::value, WIDE = decltype(wide_c)::value;
@@ -3329,7 +3334,7 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, Cut cut) {
     int dq_longest = 0, dkv_longest = 0;
     for (const DqItem& it : P.dq_items) dq_longest = std::max(dq_longest, (std::min(it.n0 + it.q_rows - 1, it.keys) + kStageKeys - 1) / kStageKeys);
     for (const DkvItem& it : P.dkv_items) dkv_longest = std::max(dkv_longest, (it.n_qt - it.qt_first) * group);
-    P.dq_first = dq_longest > dkv_longest;
+    P.dq_first = dq_longest > dkv_longest || (d->head_dim == 64 && dq_longest == dkv_longest);  // (64: short_joins)
   }
   // the layout does not depend on which backward runs: item and piece counts follow from the segment table
   for (int t = 0; t < d->num_segments; ++t) {

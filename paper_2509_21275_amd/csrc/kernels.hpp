@@ -134,7 +134,7 @@ struct BwdPlan {
   bool dq_pipe = false, dkv_pipe = false;  // the pipelined kernels run
   bool dq_wide = false;                    // head_dim 256: bwd_dq_wide_kernel runs
   int dq_waves = 0;                        // 32-row units of a dQ workgroup
-  bool dq_first = false;                   // head_dim 96 and 128: the dQ blocks start before the dK/dV blocks
+  bool dq_first = false;                   // both kinds in one launch: the dQ blocks start before the dK/dV blocks
   // one-pass backward (head_dim 128): its items and workgroup order travel at the end of the blob; then the per-wave
   // progress counters and the status word (cleared by a kernel on every call) and the float32 dQ tiles
   bool fused = false;

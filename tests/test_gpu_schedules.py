@@ -40,16 +40,18 @@ def test_schedules_on_both_sides_of_each_line(oracle_mod, n, hq, hk, d):
         assert torch.equal(o, o2) and torch.equal(lse, lse2)
 
 
-@pytest.mark.parametrize("d,n,rows,hq,hk", [
-    # blocks of both kinds before any dK/dV walk is cut
-    (256, 10, 200, 4, 4), (256, 11, 200, 4, 4),  # 240, 264; 5.5 stages per dQ walk: the pipelined dQ kernel
-    (256, 8, 65, 24, 6), (256, 9, 65, 24, 6),    # 240, 270; dQ items of 32 rows and four heads, the last of one row
-    (64, 18, 129, 8, 2), (64, 19, 129, 8, 2),    # 252, 266; the same at 64
-    (64, 1, 1, 1, 1), (256, 1, 1, 1, 1),         # one row
+@pytest.mark.parametrize("d,n,rows,ctx,hq,hk", [
+    (256, 10, 200, 0, 4, 4), (256, 11, 200, 0, 4, 4),  # 240 and 264 blocks; 5.5 stages per dQ walk: the pipelined dQ kernel
+    (256, 8, 65, 0, 24, 6), (256, 9, 65, 0, 24, 6),    # 240, 270; dQ items of 32 rows and four heads, the last of one row
+    (64, 18, 129, 0, 8, 2), (64, 19, 129, 0, 8, 2),    # 252, 266; the same at 64
+    (64, 5, 33, 700, 3, 3), (256, 5, 33, 700, 3, 3),   # dQ has the longer walks and goes first
+    (64, 40, 129, 0, 8, 8), (64, 1, 1, 0, 1, 1), (256, 1, 1, 0, 1, 1),
 ])
-def test_dq_and_dkv_blocks_in_one_launch_and_in_two(oracle_mod, d, n, rows, hq, hk):
-    """Head dimensions 64 and 256 run both kinds of block in one launch up to 256 of them; the same bits on a second run."""
-    case = synth.ChunkCase("joint", synth.packed_chunk([rows] * n), n * rows, n * rows, hq, hk, d, 90 + n)
+def test_dq_and_dkv_blocks_in_one_launch(oracle_mod, d, n, rows, ctx, hq, hk):
+    """The unpipelined dK/dV kernels of head dimensions 64 and 256 share their launch with dQ; the same bits on a second run."""
+    segs = [synth.Seg(rows * i, rows, (rows + ctx) * i, rows + ctx) for i in range(n)]
+    case = synth.ChunkCase("joint", segs, n * rows, n * (rows + ctx), hq, hk, d, 90 + n)
+    assert not ca.chunk_attn_test_routes(ca.make_desc(segs, hq, hk, d, case.total_q, case.total_kv, case.scale)) & (ca.ROUTE_DQ_PIPELINED | ca.ROUTE_DKV_PIPELINED)
     q, k, v, do = make_inputs(case)
     got = run_gpu(case, q, k, v, do)
     assert all(torch.equal(a, b) for a, b in zip(got, run_gpu(case, q, k, v, do)))
