@@ -886,10 +886,12 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void fwd_pipe_kernel(FwdArgs)
 // LDS holds four stages of K (t + 1 and, read ahead over the end of the step, t + 2 in use in step t; t + 3 and t + 4 on their way) and
 // five of V (t - 1 and t in use, t + 1 and t + 2 on their way); a copy has more than a step to land.  Q comes in and O goes
 // out through 64 KB of the V ring and behind it, which no stage needs at either end.
-// The reference maximum, blocks that outgrow it and the masked steps as in fwd_pipe_kernel.
+// Blocks that outgrow their reference maximum and the masked steps as in fwd_pipe_kernel; the maximum is that of two stages, and O and LSE
+// have a sum of probabilities each (2-norm error of O, 1000 causal tokens, 8/2 heads, scores of 1 / 4 / 8 nats: 2.02e-3 / 1.83e-3 / 1.70e-3, with a
+// moving maximum 2.02 / 1.80 / 1.66; with one stage and one sum 2.07 / 2.23 / 2.22.  The two cost long walks 1.8 %, short ones nothing).
 // Against fwd_kernel's scheme, which it replaces here (online softmax, no pipelining, V^T images made by a launch before; 32/8 heads):
-// packed 64K chunk 10.9 -> 8.2 ms, 8192 queries on 32768 keys 10.0 -> 7.2, 64 sequences of 256 329 -> 259 us, 909 queries on 5603 keys 252 -> 175,
-// 148 on 595, 8/2 heads, 39 -> 29.  Two to five fragments read ahead and either order of a mini-step's reads make no difference.
+// packed 64K chunk 10.9 -> 8.3 ms, 8192 queries on 32768 keys 10.0 -> 7.5, 64 sequences of 256 342 -> 244 us, 909 queries on 5603 keys 256 -> 169,
+// 148 on 595, 8/2 heads, 43 -> 25.  Two to five fragments read ahead and either order of a mini-step's reads make no difference.
 // ------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256, 1) void fwd_wide_kernel(FwdArgs) {
   constexpr int D = 256;
@@ -1065,29 +1067,39 @@ __global__ __launch_bounds__(256, 1) void fwd_wide_kernel(FwdArgs) {
   const float c = p.scale_log2;
   bf16x8 fv[RING], fk[RING];  // rings of V^T and of K fragments
 
-  // S^T(0) = K(0) Q^T and the reference maximum of each row
-  float mc, l_run = 0.f;
+  // S^T(0) = K(0) Q^T and the reference maximum of each row, over stages 0 and 1 (S^T(1) is formed for that alone, and again in step 0): the
+  // largest probability is the one whose rounding matters most, and it is exact where the maximum is the reference.
+  // Two sums: O is divided by the sum of the probabilities as they are rounded to bf16 for the product with V, so that a dominant
+  // one's rounding cancels; LSE takes the unrounded sum.
+  float mc, l_run = 0.f, l_rnd = 0.f;
+  bf16x2 ones;
+  ones[0] = (__bf16)1.0f; ones[1] = (__bf16)1.0f;
   {
     bf16x8 a[DK];
-    static_for<0, DK>([&](auto ks_c) __attribute__((always_inline)) { a[decltype(ks_c)::value] = load_rows(k_ev0, k_od0, ks_c); });
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-    for (int k = 0; k < DK; ++k) asm volatile("" : "+v"(a[k]));  // (after the wait, in this order)
-    wg_barrier();  // every wave has read K(0): step 0 copies K(4) over it
+    for (int n = 1; n >= 0; --n) {
+      static_for<0, DK>([&](auto ks_c) __attribute__((always_inline)) { a[decltype(ks_c)::value] = load_rows(k_ev0 + n * SLOT, k_od0 + n * SLOT, ks_c); });
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-    for (int k = 0; k < DK; ++k) {
-      f32x16& d_ = x[0];
-      const bf16x8& b_ = qf[k];
-      if (k == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d_) : "v"(a[k]), "a"(b_));
-      else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d_) : "v"(a[k]), "a"(b_));
+      for (int k = 0; k < DK; ++k) asm volatile("" : "+v"(a[k]));  // (after the wait, in this order)
+      if (n == 0) wg_barrier();  // every wave has read K(0): step 0 copies K(4) over it
+#pragma unroll
+      for (int k = 0; k < DK; ++k) {
+        f32x16& d_ = x[n];
+        const bf16x8& b_ = qf[k];
+        if (k == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d_) : "v"(a[k]), "a"(b_));
+        else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d_) : "v"(a[k]), "a"(b_));
+      }
     }
     mfma_settle();
-    asm volatile("s_nop 15" : "+v"(x[0]));  // the reads below come after the MFMAs have written
-    const int lim = it.n0 + wave_row0 + l32;  // stage 0: visible iff local key index < lim (>= 1)
+    asm volatile("s_nop 15" : "+v"(x[0]), "+v"(x[1]));  // the reads below come after the MFMAs have written
+    const int lim = it.n0 + wave_row0 + l32;  // visible iff key index < lim (>= 1)
     float mx = -INFINITY;
 #pragma unroll
-    for (int i = 0; i < 16; ++i)
-      if (8 * (i >> 2) + 4 * hh + (i & 3) < lim) mx = fmaxf(mx, x[0][i]);
+    for (int n = 0; n < 2; ++n)
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (BN * n + 8 * (i >> 2) + 4 * hh + (i & 3) < lim) mx = fmaxf(mx, x[n][i]);
     mc = max_halves(mx) * c;
   }
   if (__builtin_expect(again, 0)) {  // the maximum over all stages: S^T as in the loop, K read from global memory
@@ -1129,7 +1141,7 @@ __global__ __launch_bounds__(256, 1) void fwd_wide_kernel(FwdArgs) {
     int lim = 0;
     if (MASKED) lim = t < nt ? it.n0 + wave_row0 + l32 - BN * t - 4 * hh : -0x40000000;
     unsigned pw[8];  // P^T(t), packed pairs
-    float ps = 0.f;
+    float ps = 0.f, pr = 0.f;
     float e_hold[2];
     // (a pair is converted one mini-step after its exponentials: a transcendental result cannot be consumed by the very next instruction)
     auto finish_pair = [&](int j) __attribute__((always_inline)) {
@@ -1137,6 +1149,8 @@ __global__ __launch_bounds__(256, 1) void fwd_wide_kernel(FwdArgs) {
       w[0] = (__bf16)e_hold[0]; w[1] = (__bf16)e_hold[1];
       ps += e_hold[0] + e_hold[1];
       asm volatile("" : "+v"(ps));
+      pr = __builtin_amdgcn_fdot2_f32_bf16(w, ones, pr, false);
+      asm volatile("" : "+v"(pr));
       unsigned wu = __builtin_bit_cast(unsigned, w);
       asm volatile("" : "+v"(wu));
       pw[j] = wu;
@@ -1190,6 +1204,7 @@ __global__ __launch_bounds__(256, 1) void fwd_wide_kernel(FwdArgs) {
     sK = sN;
     risk |= !(ps < big);
     l_run += ps;
+    l_rnd += pr;
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
       u32x4 v = {pw[4 * k], pw[4 * k + 1], pw[4 * k + 2], pw[4 * k + 3]};
@@ -1234,7 +1249,7 @@ __global__ __launch_bounds__(256, 1) void fwd_wide_kernel(FwdArgs) {
     __bf16* obase = p.o + (int64_t)it.q_row0 * q_stride + (int64_t)head * D;
     const int r = wave_row0 + l32_e;
     const float l_tot = sum_halves(l_run);
-    const float inv = 1.0f / l_tot;
+    const float inv = 1.0f / sum_halves(l_rnd);
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll

@@ -1,6 +1,8 @@
 """The pipelined forward and dQ kernels of head dimension 256 at the edges of its tiles (32 query rows per wave, stages of 32 keys, rings of four
 to six stages), with blocks that are taken a second time because a row outgrows its reference maximum, and with more blocks
 than workgroups, against the fp64 oracle (2e-2, as everywhere; LSE: float32 sums of unrounded probabilities, 1e-4)."""
+import math
+
 import pytest
 import torch
 
@@ -42,6 +44,29 @@ def test_late_growth_and_more_blocks_than_workgroups(oracle_mod):
     k[780 + 350:780 + 400] += 3.0
     q[780:] = q[780:].abs() + 1.0
     _check(oracle_mod, case, q, k, v)
+
+
+@pytest.mark.parametrize("limit", [60.0, -1e30])
+@pytest.mark.parametrize("d", [256, 64])
+def test_rounding_of_the_probabilities_cancels_in_the_quotient(d, limit):
+    """V is one everywhere, so that every row of O is one.  All keys but the first have the same probability relative to it, 0.5018, which bf16
+    rounds to 0.5: divided by a sum of unrounded probabilities, O would be 0.9964 for many keys, 0.9961 in bf16.  Divided by the sum of what
+    is multiplied with V it is one up to float32 sums of a few hundred terms, which is one in bf16.  LSE takes the unrounded sum at 256,
+    the rounded one at 64 (2^-9 of it, as the sum's terms)."""
+    n, ctx, hq, hk = 70, 300, 4, 2
+    q = torch.zeros((n, hq, d), dtype=torch.bfloat16, device="cuda")
+    k = torch.zeros((n + ctx, hk, d), dtype=torch.bfloat16, device="cuda")
+    q[..., 0], k[1:, :, 0] = 1.0, -1.0
+    v = torch.ones_like(k)
+    case = synth.ChunkCase("ones", [synth.Seg(0, n, 0, n + ctx)], n, n + ctx, hq, hk, d, 0)
+    ca.chunk_attn_test_set_fwd_rescale_limit(limit)
+    try:
+        o, lse = run_gpu(case, q, k, v, scale=0.68955, backward=False)
+    finally:
+        ca.chunk_attn_test_set_fwd_rescale_limit(60.0)
+    assert torch.all(o == 1.0)
+    want = torch.log(1.0 + torch.arange(ctx, ctx + n, dtype=torch.float64) * math.exp(-0.68955))
+    assert float((lse.double().cpu() - want).abs().max()) <= (1e-5 if d == 256 else 2.0 ** -8)
 
 
 @pytest.mark.parametrize("segs,hq,hk", [
