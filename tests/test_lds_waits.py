@@ -4,8 +4,12 @@ compiler from moving the use in front of it.  This looks at the source of every 
 read fills is an operand of a wait in the same step."""
 import os
 import re
+import shutil
+import subprocess
 
 import pytest
+
+from paper_2509_21275_amd.build import FLAGS
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2509_21275_amd", "csrc")
 
@@ -47,3 +51,21 @@ def test_every_array_read_in_a_step_is_tied_to_a_wait(source):
         tied = set(re.findall(r'"\+v"\((\w+)', " ".join(statements(body))))
         assert filled <= tied, f"{source}:{line}: {sorted(filled - tied)} read from LDS, but no wait names them"
     assert found >= 1
+
+
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+
+@pytest.mark.skipif(shutil.which(HIPCC) is None, reason="needs hipcc")
+def test_unpipelined_dkv_steps_wait_for_their_reads_one_by_one(tmp_path):
+    """Each of bwd_dkv_kernel's four unrolled steps starts its vector work on the first of its reads while five later ones are still
+    out.  (The compiler places these waits; it waits for all reads at once where it has lost count of them.)"""
+    out = str(tmp_path / "bwd.s")
+    r = subprocess.run([HIPCC, *FLAGS, "-x", "hip", "--cuda-device-only", "-S", os.path.join(CSRC, "bwd_kernel.hip"), "-o", out],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    text = open(out).read()
+    for name in ("bwd_dkv_kernelILi64ELi4ELb0", "bwd_dkv_kernelILi64ELi4ELb1", "bwd_short_kernelILi64ELi4ELb0", "bwd_short_kernelILi64ELi4ELb1"):
+        at = re.search(r"^\S*%s\S*:" % name, text, re.M).end()
+        body = text[at:text.index(".Lfunc_end", at)]
+        assert body.count("lgkmcnt(5)") >= 4, name
