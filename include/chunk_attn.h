@@ -90,7 +90,8 @@ typedef struct {
  * than such tiles take, at most), for 64 and 256 partial results of dK / dV walks that are cut (64 MB at most).  For 96 both also
  * have room for zero-padded copies of the tensors, 128 wide.  Some of that room is used by no kernel of the default mode
  * and kept so that the sizes stay what callers know.  A chunk whose walks would be cut also runs in a somewhat smaller
- * workspace, one that holds its uncut schedule: nothing is cut then, and the results are other roundings of the same sums.
+ * workspace: one that holds its uncut schedule and, for the backward of 96 and 128, the tiles of dQ.  There fewer walks or none are
+ * cut, and the results are other roundings of the same sums.
  * Either output pointer may be NULL.  Validates the descriptor.
  */
 int chunk_attn_workspace_bytes(const chunk_attn_desc* desc, size_t* fwd_bytes, size_t* bwd_bytes);

@@ -2944,6 +2944,7 @@ __global__ __launch_bounds__(256, 1) void bwd_pipe_kernel(BwdPipeParams) {
     args_ptr args = (args_ptr)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(args));
     const bool is_dq = phase == args->dq_phase;
+    if ((is_dq ? args->dq.num_blocks : args->dkv.num_blocks) == 0) continue;  // (this launch has blocks of the other kind only)
     int mine = kClaimBlocks;
     if (args->dq.num_blocks + args->dkv.num_blocks <= (int)gridDim.x) {  // a workgroup per block: nothing to claim
       const int first = args->dq_phase == 0 ? args->dq.num_blocks : args->dkv.num_blocks;
@@ -3181,28 +3182,40 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
     constexpr size_t dq_smem = (size_t)2 * (DQ_PIPE_DIST + 3) * 32 * D * 2 + (size_t)4 * 64 * D * 2;
     constexpr size_t dkv_smem = (size_t)2 * NS * 32 * D * 2 + 2 * 4096 * 2 + 2 * NS * 64 * sizeof(float) + 16;
     constexpr size_t smem = dq_smem > dkv_smem ? dq_smem : dkv_smem;
-    BwdPipeParams p;
-    p.dq = pq;
-    p.dkv = pk;
-    p.dq_phase = P.dq_first ? 0 : 1;
-    const dim3 grid((unsigned)persistent_grid(dq_blocks + dkv_blocks));
     if (pe.start && (e = hipEventRecord(pe.start, stream)) != hipSuccess) return e;
-    if (P.n_dq_cut == 0 && P.n_dkv_cut == 0) {
-      static const hipError_t attr = raise_smem_limit(&bwd_pipe_kernel<D, false>, smem);
-      if (attr != hipSuccess) return attr;
-      hipLaunchKernelGGL((bwd_pipe_kernel<D, false>), grid, dim3(256), smem, stream, p);
-    } else {
+    // the blocks of one kind or of both, then their pieces put together
+    auto run = [&](bool dq, bool dkv) {
+      BwdPipeParams p;
+      p.dq = pq;
+      p.dkv = pk;
+      p.dq_phase = P.dq_first ? 0 : 1;
+      if (!dq) p.dq.num_blocks = 0;
+      if (!dkv) p.dkv.num_blocks = 0;
+      const size_t n_dq_cut = dq ? P.n_dq_cut : 0, n_dkv_cut = dkv ? P.n_dkv_cut : 0;
+      const dim3 grid((unsigned)persistent_grid((int64_t)p.dq.num_blocks + p.dkv.num_blocks));
+      if (n_dq_cut == 0 && n_dkv_cut == 0) {
+        static const hipError_t attr = raise_smem_limit(&bwd_pipe_kernel<D, false>, smem);
+        if (attr != hipSuccess) return attr;
+        hipLaunchKernelGGL((bwd_pipe_kernel<D, false>), grid, dim3(256), smem, stream, p);
+        return hipGetLastError();
+      }
       static const hipError_t attr = raise_smem_limit(&bwd_pipe_kernel<D, true>, smem);
       if (attr != hipSuccess) return attr;
       hipLaunchKernelGGL((bwd_pipe_kernel<D, true>), grid, dim3(256), smem, stream, p);
-    }
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    const int64_t dq_units = 8 * (int64_t)P.n_dq_cut * d->num_kv_heads * pq.head_splits, dkv_units = 8 * (int64_t)P.n_dkv_cut * d->num_kv_heads;
-    if (dq_units + dkv_units > 0)  // (cut chunks have few blocks: choose_key_split, choose_tile_split)
+      const hipError_t err = hipGetLastError();
+      if (err != hipSuccess) return err;
+      const int64_t dq_units = 8 * (int64_t)n_dq_cut * d->num_kv_heads * pq.head_splits, dkv_units = 8 * (int64_t)n_dkv_cut * d->num_kv_heads;
+      // (cut chunks have few blocks: choose_key_split, choose_tile_split)
       hipLaunchKernelGGL((bwd_merge_kernel<D>), dim3((unsigned)(dq_units + dkv_units)), dim3(256), 0, stream, pq,
                          reinterpret_cast<const DqItem*>(ws + P.dq_cut_off), (int)dq_units, pk,
                          reinterpret_cast<const DkvItem*>(ws + P.dkv_cut_off));
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+      return hipGetLastError();
+    };
+    if (P.in_turn) {
+      if ((e = run(true, false)) != hipSuccess || (e = run(false, true)) != hipSuccess) return e;
+    } else if ((e = run(true, true)) != hipSuccess) {
+      return e;
+    }
   } else {
     constexpr int KB = (D > 128 ? 64 : DKV_KEYS) / 32;  // as dkv_keys(D)
     // 4 ring slots of two 32-row operand tiles, 2 P hand-over slots, 4 slots of LSE and D rows
@@ -3373,9 +3386,12 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, Cut cut) {
   P.dsp_off = P.lse2p_off + up256(row_slots * sizeof(float));
   // (256 bytes remain: the dK/dV kernels copy the LSE / D rows 64 at a time, up to 32 past a segment's last)
   P.fdq_off = P.dsp_off + up256(row_slots * sizeof(float)) + 256;
-  // partial results of cut walks: those of dK/dV, then those of dQ (both kinds of block run in one launch)
+  // partial results of cut walks: those of dK/dV, then those of dQ, as both kinds of block run in one launch; where the room is
+  // that of the dQ tiles and too small for both, each kind has all of it in turn, in a launch of its own
   P.dq_parts_off = P.fdq_off + up256((size_t)P.dkv_split.parts * d->num_kv_heads * kPartRowFloats * sizeof(float));
   const size_t dq_part_bytes = P.split.parts > 0 ? (size_t)P.split.parts * d->num_kv_heads * (group / heads_per_wg(group, P.dq_waves)) * kPartRowFloats * sizeof(float) : 0;
+  P.in_turn = cut == kCutInPlace && P.dkv_split.parts > 0 && P.split.parts > 0 && P.dq_parts_off + dq_part_bytes > P.fdq_off + dq_tile_bytes;
+  if (P.in_turn) P.dq_parts_off = P.fdq_off;
   P.total = std::max(P.fdq_off + dq_tile_bytes, P.dq_parts_off + dq_part_bytes);
 }
 

@@ -135,6 +135,7 @@ struct BwdPlan {
   bool dq_wide = false;                    // head_dim 256: bwd_dq_wide_kernel runs
   int dq_waves = 0;                        // 32-row units of a dQ workgroup
   bool dq_first = false;                   // both kinds in one launch: the dQ blocks start before the dK/dV blocks
+  bool in_turn = false;                    // head_dim 96 and 128: a launch per kind, whose partial results take the same place
   // one-pass backward (head_dim 128): its items and workgroup order travel at the end of the blob; then the per-wave
   // progress counters and the status word (cleared by a kernel on every call) and the float32 dQ tiles
   bool fused = false;
@@ -153,8 +154,8 @@ constexpr size_t kClockLogEntries = 4 * 1024;
 unsigned long long* clock_log(int which);
 hipError_t launch_bwd_fused(const chunk_attn_desc* d, const BwdArgs& a, const BwdPlan& plan, const float* lse2p, const float* dsp,
                             hipStream_t stream);
-// Fills the offsets (and, if with_plan, the schedules) for a validated descriptor.  kCutInPlace: only where the partial results fit the
-// room that head_dim 96 and 128 keep for dQ tiles anyway (workspaces of that size may be known to callers); kCutNone: no walk is cut.
+// Fills the offsets (and, if with_plan, the schedules) for a validated descriptor.  kCutInPlace: only where the partial results of each kind fit
+// the room that head_dim 96 and 128 keep for dQ tiles anyway (workspaces of that size may be known to callers); kCutNone: no walk is cut.
 enum Cut { kCutNone, kCutInPlace, kCutFine };
 void bwd_layout(const chunk_attn_desc* d, BwdPlan& plan, bool with_plan, Cut cut = kCutFine);
 // The host image of the blob at the start of the workspace.

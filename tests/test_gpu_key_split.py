@@ -115,6 +115,42 @@ def test_workspace_without_room_for_pieces(name, segs, hq, hk, cut):
     assert torch.equal(dq, dq2) and torch.equal(dk, dk2) and torch.equal(dv, dv2)
 
 
+@pytest.mark.parametrize("segs,hq,hk", [
+    ([(0, 2049, 0, 2049)], 8, 2),     # room for 130 partial results; 110 of dQ blocks and 124 of dK/dV blocks
+    ([(0, 467, 0, 467), (467, 916, 467, 916)], 8, 2),
+    ([(0, 1350, 0, 1350), (1350, 129, 1350, 129), (1479, 85, 1479, 85)], 32, 8),
+])
+def test_workspace_with_room_for_one_kind_of_pieces(oracle_mod, segs, hq, hk):
+    """The uncut layout keeps room for float32 dQ tiles.  With a little more for the longer lists, walks of both kinds are cut if the partial
+    results of each kind fit that room, in turn if they do not fit it together: other float32 sums than those of the uncut run, within
+    1e-5 of them, and the same bits on a second run."""
+    case = _case("in_turn", segs, hq, hk)
+    q, k, v, do = make_inputs(case)
+    o, lse = run_gpu(case, q, k, v, backward=False)
+    desc = ca.make_desc(case.segs, hq, hk, 128, case.total_q, case.total_kv, case.scale)
+    dq, dk, dv = torch.empty_like(q), torch.empty_like(k, dtype=torch.float32), torch.empty_like(v, dtype=torch.float32)
+
+    def run(ws):
+        for x in (dq, dk, dv, ws):
+            x.view(torch.uint8).fill_(0xff)
+        ca.chunk_attn_bwd_f32kv(desc, q, k, v, o, do, lse, dq, dk, dv, 0, ws)
+        return [x.clone() for x in (dq, dk, dv)]
+
+    full = ca.chunk_attn_workspace_bytes(desc)[1]
+    uncut = _smallest_workspace(lambda w: ca.chunk_attn_bwd_f32kv(desc, q, k, v, o, do, lse, dq, dk, dv, 0, w), full)
+    small = torch.empty(uncut.numel() + 65536, dtype=torch.uint8, device=q.device)
+    assert small.numel() < full
+    want, got, again = run(uncut), run(small), run(small)
+    assert all(torch.equal(a, b) for a, b in zip(got, again))
+    assert not torch.equal(got[1], want[1]) and not torch.equal(got[2], want[2]) and not torch.equal(got[0], want[0])
+    for a, b, tol in zip(got, want, (2.0 ** -7, 1e-5, 1e-5)):
+        assert rel_err(a, b.double().cpu().numpy()) <= tol
+    orc = oracle_mod.Oracle(case.segs, q.cpu(), k.cpu(), v.cpu(), do.cpu(), case.scale)
+    orc.forward()
+    for g, w in zip(got, orc.backward()):
+        assert rel_err(g, w) <= TOL_GRAD
+
+
 @pytest.mark.parametrize("d", [128, 96])
 def test_cut_walks_that_take_the_second_pass(oracle_mod, d):
     """Every piece raises its item's flag: the whole items are recomputed, not put together."""
