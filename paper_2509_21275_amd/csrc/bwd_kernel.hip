@@ -376,8 +376,6 @@ struct DkvParams {
   int32_t accumulate;
   int32_t out_f32;      // dk / dv point to fp32 arrays of the same shape
   int32_t* taken;       // 8 block-queue counters of the pipelined kernel (zero before the launch)
-  int32_t* ended;       // per queue, the blocks that have ended (zero before the launch)
-  int32_t side_by_side; // blocks of a queue that run at the same time (DkvItem::in_step)
   float* parts;         // partial results of pieces (dkv_pipe_blocks), kPartRowFloats per (slot, key/value head)
   unsigned long long* clock_log;  // null, or where the pipelined kernel's workgroups log their clocks
   int32_t num_blocks;
@@ -839,21 +837,17 @@ __device__ __forceinline__ void dkv_pipe_blocks(const ArgsPtr<DkvParams> args, c
   // The workgroup is persistent: it claims one block (128 keys of one key/value head) after the other
   // (device_common.hpp) until none is left.  The next block is claimed before the current one's last few steps: early
   // enough for the answer to arrive by the time it is needed, and not earlier (that would fix the order of the blocks
-  // before it is known which workgroup is free first).
+  // before it is known which workgroup is free first).  Blocks that walk the same rows do not wait for each other: that gained the L2
+  // something while every workgroup ran blocks of this kind; with those of dQ between them it saves no traffic (16384 queries on 131072 keys, 64/8
+  // heads, 39 - 48 GB with it, 37 - 49 without) and workgroups stand idle (873 queries on 5197 keys, 32/8, whole walks, backward 323 / 238 us).
   int* const next_block = (int*)((__bf16*)smem + LDS_ELEMS);
   const int xcd = xcd_of_this_wave();
   clock_log_stamp(fresh(args).clock_log, 0);
   int blk = mine;
-  // blocks that walk the same rows as the others of their group wait for the groups before them (DkvItem::in_step)
-  auto start_in_step = [&](int b) __attribute__((always_inline)) {
-    const DkvParams p = fresh(args);
-    if (b >= 0 && load_uniform(p.items, b / p.num_kv_heads).in_step) wait_for_earlier_groups(p.ended, b, p.side_by_side);
-  };
   if (mine == kClaimBlocks) {
     if (wave == 0) {
       const DkvParams p = fresh(args);
       blk = block_claim_finish(p.taken, p.num_blocks, xcd, block_claim_issue(p.taken, xcd));
-      start_in_step(blk);
     }
     blk = broadcast_from_wave0(next_block, blk);
   }
@@ -1284,9 +1278,7 @@ __device__ __forceinline__ void dkv_pipe_blocks(const ArgsPtr<DkvParams> args, c
   int nb = 0;
   if (wave == 0) {
     const DkvParams p = fresh(args);
-    if (lane == 0) __hip_atomic_fetch_add(p.ended + (blk & 7), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     nb = block_claim_finish(p.taken, p.num_blocks, xcd, pending_claim);
-    start_in_step(nb);
   }
   blk = broadcast_from_wave0(next_block, nb);
   }
@@ -1353,10 +1345,7 @@ __global__ __launch_bounds__(128, 1) void bwd_dkv_narrow_pipe_kernel(DkvParams p
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hh = lane >> 5;
 
-  // Persistent, as dkv_pipe_blocks, but no block waits for the groups before it (DkvItem::in_step is for head_dim 96 and
-  // 128).  Half the head dimension leaves too little to gain from the L2: with the waits and the counting of ended blocks the
-  // backward of 1024 queries on 32768 keys, 32/8 heads, took 1139 us instead of 1041, of 64 sequences of 64, 8/8 heads, 57
-  // instead of 38; 16384 queries on 65536 keys 23.7 ms instead of 23.4.
+  // Persistent, as dkv_pipe_blocks.
   __shared__ int next_block;
   const int xcd = xcd_of_this_wave();
   int blk = 0;
@@ -1751,9 +1740,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_wide_pipe_kernel(DkvParams p, 
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hh = lane >> 5;
 
-  // Persistent, as dkv_pipe_blocks, but no block waits for the groups before it (DkvItem::in_step is for head_dim 96 and
-  // 128): that cost 1024 queries on 32768 keys, 32/8 heads, 3796 us of backward instead of 3684, gained nothing on 8192
-  // (25.6 and 25.8 ms) and cost chunks of 64-token sequences a tenth.
+  // Persistent, as dkv_pipe_blocks.
   __shared__ int next_block;
   const int xcd = xcd_of_this_wave();
   int blk = 0;
@@ -3000,7 +2987,7 @@ __global__ __launch_bounds__(256) void bwd_merge_kernel(DqParams pq, const DqIte
   if (is_dq) {
     const DqItem it = dq_cut[block / inner_n];
     part = it.part;
-    pieces = it.kv_tile0;
+    pieces = it.pieces;
     head = inner % pq.num_kv_heads * pq.group + inner / pq.num_kv_heads * pq.heads_per_wg + unit % pq.heads_per_wg;
     row = (unit / pq.heads_per_wg) * 32 + l32;
     rows = it.q_rows;
@@ -3008,7 +2995,7 @@ __global__ __launch_bounds__(256) void bwd_merge_kernel(DqParams pq, const DqIte
   } else {
     const DkvItem it = dkv_cut[block / inner_n];
     part = it.part;
-    pieces = it.in_step;
+    pieces = it.pieces;
     row = unit % KEY_UNITS * 32 + l32;
     rows = it.kv_rows;
     row0 = it.kv_row0;
@@ -3163,9 +3150,7 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
   pk.accumulate = a.accumulate ? 1 : 0;
   pk.out_f32 = a.dkv_f32 ? 1 : 0;
   pk.taken = reinterpret_cast<int32_t*>(ws + P.queues_off) + kBlockQueues;
-  pk.ended = pk.taken + kBlockQueues;
   pk.parts = reinterpret_cast<float*>(ws + P.fdq_off);
-  pk.side_by_side = std::max(1, persistent_grid(0x7fffffff, dkv_per_cu(D)) / kBlockQueues);
   pk.clock_log = clock_log(2);
   static_assert(DKV_KEYS == 128, "the head_dim 64 and 128 kernels cover 128 keys per workgroup");
   const int64_t dkv_blocks = (int64_t)P.dkv_items.size() * d->num_kv_heads;
@@ -3368,9 +3353,9 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, Cut cut) {
   P.dkv_items_off = P.dq_cut_off + up16(P.n_dq_cut * sizeof(DqItem));
   P.dkv_cut_off = P.dkv_items_off + up16((P.dkv_split.target > 0 ? (size_t)P.dkv_split.pieces : n_dkv) * sizeof(DkvItem));
   P.qjobs_off = P.dkv_cut_off + up16(P.n_dkv_cut * sizeof(DkvItem));
-  // block-queue counters of the dQ and of the dK/dV kernel (zero in the blob): dQ queues, dK/dV queues, dK/dV blocks ended
+  // block-queue counters of the dQ and of the dK/dV kernel (zero in the blob)
   P.queues_off = P.qjobs_off + up16((size_t)P.q_tiles * sizeof(TileJob));
-  P.fitems_off = P.queues_off + up16(3 * kBlockQueues * sizeof(int32_t));
+  P.fitems_off = P.queues_off + up16(2 * kBlockQueues * sizeof(int32_t));
   // the workspace is sized for either backward (the mode may change between the size query and the call): the one-pass
   // backward has one item per (key block, key/value head) and at most 8 x that many workgroup slots
   const size_t n_fused = d->head_dim == 128 ? n_dkv_blocks(d) * (size_t)d->num_kv_heads : 0;

@@ -102,7 +102,7 @@ std::vector<FwdItem> plan_fwd(const chunk_attn_desc* d, int tile_rows) {
 
 std::vector<DqItem> plan_dq(const chunk_attn_desc* d, int tile_rows) {
   std::vector<DqItem> items;
-  int32_t kv_tile0 = 0, q_tile0 = 0;
+  int32_t q_tile0 = 0;
   for (int t = 0; t < d->num_segments; ++t) {
     const chunk_attn_seg& s = d->segments[t];
     const int32_t C = s.kv_len - s.q_len;
@@ -112,13 +112,11 @@ std::vector<DqItem> plan_dq(const chunk_attn_desc* d, int tile_rows) {
       it.q_rows = std::min<int32_t>(tile_rows, s.q_len - i0);
       it.kv_row0 = s.kv_start;
       it.n0 = C + i0 + 1;
-      it.kv_tile0 = kv_tile0;
       it.q_slot0 = q_tile0 * 64 + i0;
       it.keys = s.kv_len;
       it.part = -1;
       items.push_back(it);
     }
-    kv_tile0 += (s.kv_len + 31) / 32;
     q_tile0 += (s.q_len + 63) / 64;
   }
   by_sequence_then_walk(d, items);
@@ -381,7 +379,7 @@ std::vector<DkvItem> cut_items(const std::vector<DkvItem>& wholes, int target, s
     if (n > 1) {
       cut->push_back(whole);
       cut->back().part = part;
-      cut->back().in_step = n;
+      cut->back().pieces = n;
     }
     for (int k = 0; k < n; ++k) {
       DkvItem it = whole;
@@ -428,7 +426,7 @@ std::vector<DqItem> cut_items(const std::vector<DqItem>& wholes, int target, std
     if (n > 1) {
       cut->push_back(whole);
       cut->back().part = part;
-      cut->back().kv_tile0 = n;
+      cut->back().pieces = n;
     }
     for (int k = 0; k < n; ++k) {
       const int b = piece_begin(stages, n, k) * kStageKeys;
@@ -455,20 +453,12 @@ std::vector<DqItem> cut_items(const std::vector<DqItem>& wholes, int target, std
 //   * the shortest quarter is kept for the end, longest first, walking upwards: small items for the workgroups to
 //     even out what their unequal speeds have left.
 // The result holds indices into the input order; reverse[i] is the direction of input block i.
-// in_step[i]: block i is one of the equal walks at the front.  The workgroups that run them drift apart over many blocks
-// (left alone their speeds differ by up to 2 %), until they no longer find each other's rows in the L2; the kernel
-// therefore starts such a block only when the blocks of the groups of `width` before it have ended.
-void side_by_side_order(const std::vector<DkvItem>& blocks, int width, std::vector<int>& order, std::vector<char>& reverse,
-                        std::vector<char>& in_step) {
+void side_by_side_order(const std::vector<DkvItem>& blocks, int width, std::vector<int>& order, std::vector<char>& reverse) {
   const int n = (int)blocks.size();
   order.clear();
   reverse.assign(n, 0);
-  in_step.assign(n, 0);
   int lo = 0;
-  while (lo < n && blocks[lo].qt_first == 0 && blocks[lo].j0 + blocks[lo].kv_rows <= blocks[lo].ctx) {
-    in_step[lo] = 1;
-    order.push_back(lo++);
-  }
+  while (lo < n && blocks[lo].qt_first == 0 && blocks[lo].j0 + blocks[lo].kv_rows <= blocks[lo].ctx) order.push_back(lo++);
   int hi = n - (n - lo) / 4;
   const int tail = hi;
   while (lo < hi) {
@@ -516,16 +506,15 @@ std::vector<DkvItem> plan_dkv(const chunk_attn_desc* d, int keys, int side_by_si
   out.reserve(items.size());
   std::vector<DkvItem> seq;
   std::vector<int> order;
-  std::vector<char> reverse, in_step;
+  std::vector<char> reverse;
   for (size_t i = 0; i < items.size();) {
     size_t e = i;
     while (e < items.size() && items[e].q_row_seg == items[i].q_row_seg && items[e].kv_row0 - items[e].j0 == items[i].kv_row0 - items[i].j0) ++e;
     seq.assign(items.begin() + i, items.begin() + e);
-    side_by_side_order(seq, side_by_side, order, reverse, in_step);
+    side_by_side_order(seq, side_by_side, order, reverse);
     for (int k : order) {
       out.push_back(seq[k]);
       out.back().reverse = reverse[k];
-      out.back().in_step = in_step[k];
     }
     i = e;
   }

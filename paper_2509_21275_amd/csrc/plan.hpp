@@ -45,7 +45,7 @@ struct DqItem {
   int32_t q_rows;    // valid rows in the tile (>= 1)
   int32_t kv_row0;   // first key row of the segment (global)
   int32_t n0;        // keys visible to the tile's first row
-  int32_t kv_tile0;  // index of the segment's first 32-key tile (a whole item that was cut: the number of its pieces)
+  int32_t pieces;    // a whole item that was cut: the number of its pieces
   int32_t q_slot0;   // slot of the tile's first row in the padded per-row arrays (LSE, D)
   int32_t keys;      // head_dim 96 and 128: keys of the item's own range, as in FwdItem
   int32_t part;      // head_dim 96 and 128: slot among the partial results, -1 if the item is not a piece (whole items that
@@ -65,11 +65,9 @@ struct DkvItem {
   int32_t n_qt;       // number of 32-row query tiles of the segment
   int32_t q_tile0;    // index of the segment's first 64-row tile in the padded per-row arrays (LSE, D)
   int32_t reverse;    // 1: the kernel walks the query tiles from the segment's last one down to qt_first (plan_dkv)
-  int32_t in_step;    // 1: started only when the blocks of the groups before it (of `side_by_side` blocks) have ended (plan_dkv;
-                      // head_dim 96 and 128)
-  int32_t part;       // head_dim 96 and 128: slot among the partial results, -1 if the item is not a piece of a cut walk (a piece
-                      // walks the query tiles qt_first .. n_qt - 1 of its own).  A whole item that was cut: its first slot
-                      // (its number of pieces is in in_step)
+  int32_t pieces;     // a whole item that was cut: the number of its pieces
+  int32_t part;       // slot among the partial results, -1 if the item is not a piece of a cut walk (a piece walks the query tiles
+                      // qt_first .. n_qt - 1 of its own).  A whole item that was cut: its first slot
 };
 
 // Work item of the one-pass backward kernel (head_dim 128): a DkvItem plus what the kernel needs to add its share of dQ

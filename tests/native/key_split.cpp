@@ -67,7 +67,7 @@ static int one(const std::vector<chunk_attn_seg>& segs, int heads, int kv_heads,
     std::vector<DqItem> cut;
     if (check(q, cut_items(q, target, &cut), target, &parts)) return 1;
     int64_t sum = 0;
-    for (const auto& c : cut) { REQUIRE(c.kv_tile0 > 1 && c.part == sum); sum += c.kv_tile0; }
+    for (const auto& c : cut) { REQUIRE(c.pieces > 1 && c.part == sum); sum += c.pieces; }
     REQUIRE(sum == parts);
   }
   for (int target : {0, 1, 2, 5, 100000}) {  // key-stationary: every piece a run of its walk's query tiles
@@ -83,7 +83,7 @@ static int one(const std::vector<chunk_attn_seg>& segs, int heads, int kv_heads,
       int next = whole.qt_first;
       for (const auto& it : mine) {
         REQUIRE(it.qt_first == next && it.n_qt > it.qt_first && it.q_len == whole.q_len && it.q_tile0 == whole.q_tile0);
-        REQUIRE(it.part == (mine.size() > 1 ? part : -1) && !it.reverse && !it.in_step);
+        REQUIRE(it.part == (mine.size() > 1 ? part : -1) && !it.reverse);
         if (mine.size() > 1) ++part;
         next = it.n_qt;
       }
@@ -92,7 +92,7 @@ static int one(const std::vector<chunk_attn_seg>& segs, int heads, int kv_heads,
     }
     REQUIRE(n_items == items.size());
     int32_t sum = 0;
-    for (const auto& c : cut) { REQUIRE(c.in_step > 1 && c.part == sum); sum += c.in_step; }
+    for (const auto& c : cut) { REQUIRE(c.pieces > 1 && c.part == sum); sum += c.pieces; }
     REQUIRE(sum == part);
     for (size_t i = 1; i < items.size(); ++i) REQUIRE(items[i].n_qt - items[i].qt_first <= items[i - 1].n_qt - items[i - 1].qt_first);
   }
@@ -103,7 +103,7 @@ static int one(const std::vector<chunk_attn_seg>& segs, int heads, int kv_heads,
       std::vector<DkvItem> cut;
       const auto items = cut_items(plan_dkv(&d, 128), k.target, &cut);
       int64_t parts = 0;
-      for (const auto& c : cut) parts += c.in_step;
+      for (const auto& c : cut) parts += c.pieces;
       REQUIRE(k.pieces == (int64_t)items.size() && k.parts == parts && parts > 0);
     }
   }
@@ -118,8 +118,8 @@ static int one(const std::vector<chunk_attn_seg>& segs, int heads, int kv_heads,
     const auto qi = cut_items(plan_dq(&d, rows), q1.target, &qcut);
     const auto ki = cut_items(plan_dkv(&d, 128), k1.target, &kcut);
     int64_t qp = 0, kp = 0;
-    for (const auto& c : qcut) qp += c.kv_tile0;
-    for (const auto& c : kcut) kp += c.in_step;
+    for (const auto& c : qcut) qp += c.pieces;
+    for (const auto& c : kcut) kp += c.pieces;
     REQUIRE(qp == q1.parts && kp == k1.parts && (q1.target == 0 || q1.pieces == (int64_t)qi.size()) && (k1.target == 0 || k1.pieces == (int64_t)ki.size()));
   }
   for (int64_t limit : {(int64_t)0, (int64_t)3, (int64_t)1 << 40}) {
