@@ -162,6 +162,13 @@ Walks count_dkv_walks(const chunk_attn_desc* d, int keys) {
 // forward 744 -> 472 us + 12 us to put them together (not half: 128 busy compute units hold a
 // higher clock than 256); 203 queries on 1704 keys next to 611 short rows: forward 48 -> 28 + 6 us.  Chunks the estimate
 // leaves alone (8192 queries on 32768 keys: 1024 equal blocks) run as before.
+// Both kinds of block of a backward in one launch (N = 2, refine_bwd_split) are dealt in the order in which that launch starts them, and
+// a dQ stage counts as 5/4 of a dK/dV step; what runs is the cut with the least time, no cut included.  75 chunks on which this differs from the kinds' own
+// cuts with finer pieces, which ran whatever the estimate said of them: backward 6.3 % less in the mean, none more by 1 % (both counted alike 6.2
+// % and one 5 % more, 3/2 4.9 %; dealt longest first whatever the kind 5.9 % and one 8 % more; without the kinds' own cuts among the candidates 5.7 %),
+// 40 others 7.7 % less, two of them 3 % more:
+// 483 queries on 2437 keys, 32/8 heads, 106 -> 85 us; 3823 on 9114, 8/2, 463 -> 382; 3467 on 4302, 8/8, 177 -> 146; 11561 on 11582, 32/8, 3154.
+constexpr int kJointStep = 4;
 constexpr int64_t kMaxCutBlocks = 1024;  // from four blocks per compute unit on they even out by themselves
 
 namespace {
@@ -174,6 +181,7 @@ struct CutKind {
   int longest = 0;      // units
   bool many = false;    // kMaxCutBlocks blocks or more: none of these is cut
   bool whole = false;   // none of these is to be cut
+  int cost = 1;         // of a step, in units of the estimate
   int steps_per_unit() const { return group > 0 ? group : 1; }
   int shortest() const { return group > 0 ? (2 * kMinPieceStages + group - 1) / group : kMinPieceStages; }  // units of a piece, at least
   int pieces(const Walk& w, int target) const { return group > 0 ? tile_piece_count(w.len, target) : piece_count(w.len, w.n0, target); }
@@ -214,9 +222,11 @@ CutKind tile_walks(const chunk_attn_desc* d, int keys) {
 }
 
 // The cut of N kinds of block that share the compute units, one split each; at most max_parts[i] partial results of kind i.
+// `first` (or null): a cut to look at besides those into equal shares.
 template <int N>
-void choose_cut(const CutKind (&kinds)[N], int cus, const int64_t (&max_parts)[N], KeySplit (&best)[N]) {
-  constexpr int kStart = 12, kPart = 6, kMerge = 6;
+void choose_cut(const CutKind (&kinds)[N], int cus, const int64_t (&max_parts)[N], KeySplit (&best)[N], const KeySplit* first = nullptr) {
+  constexpr int kUnit = N > 1 ? kJointStep : 1;  // a step
+  constexpr int kStart = 12 * kUnit, kPart = 6 * kUnit, kMerge = 6 * kUnit;
   constexpr int64_t kPartsPerStep = 32;  // partial results (128 KB per block) read per step
   const int workers = std::max(1, cus / 8);
   std::vector<int> cost;
@@ -246,7 +256,7 @@ void choose_cut(const CutKind (&kinds)[N], int cus, const int64_t (&max_parts)[N
         for (int x = 0; x < n; ++x, block += kind.inner) {
           const int64_t q = in_queue(block, kind.inner);
           if (q == 0) continue;
-          const int c = kind.steps(w, n, x) + kStart + (n > 1 ? kPart : 0);
+          const int c = kind.steps(w, n, x) * kind.cost + kStart + (n > 1 ? kPart : 0);
           total += q * c;
           largest = std::max(largest, c);
         }
@@ -256,22 +266,33 @@ void choose_cut(const CutKind (&kinds)[N], int cus, const int64_t (&max_parts)[N
   auto merge_time = [&](const KeySplit (&k)[N]) {
     int64_t parts = 0;
     for (int i = 0; i < N; ++i) parts += k[i].parts * kinds[i].inner;
-    return parts > 0 ? kMerge + parts / kPartsPerStep : 0;
+    return parts > 0 ? kMerge + parts * kUnit / kPartsPerStep : 0;
+  };
+  auto longest_steps = [&](int i, const KeySplit (&k)[N]) {
+    int most = 0;
+    for (const auto& w : kinds[i].walks) {
+      const int n = kinds[i].pieces(w, k[i].target);
+      for (int x = 0; x < n; ++x) most = std::max(most, kinds[i].steps(w, n, x));
+    }
+    return most;
   };
   // (needs count_work of the same splits)
   auto estimate = [&](const KeySplit (&k)[N]) -> int64_t {
     if (many) return std::max<int64_t>(total / workers, largest) + merge_time(k);  // many small blocks fill every gap
     cost.clear();
-    for (int i = 0; i < N; ++i) {
+    const bool swap = N > 1 && longest_steps(0, k) <= longest_steps(N - 1, k);  // the kind with the longer walks starts first (bwd_layout)
+    for (int j = 0; j < N; ++j) {
+      const int i = swap ? N - 1 - j : j;
       const CutKind& kind = kinds[i];
+      const size_t first = cost.size();
       int64_t block = 0;
       for (const auto& w : kind.walks) {
         const int n = kind.pieces(w, k[i].target);
         for (int x = 0; x < n; ++x, block += kind.inner)
-          cost.insert(cost.end(), in_queue(block, kind.inner), kind.steps(w, n, x) + kStart + (n > 1 ? kPart : 0));
+          cost.insert(cost.end(), in_queue(block, kind.inner), kind.steps(w, n, x) * kind.cost + kStart + (n > 1 ? kPart : 0));
       }
+      std::sort(cost.begin() + first, cost.end(), [](int a, int b) { return a > b; });
     }
-    std::sort(cost.begin(), cost.end(), [](int a, int b) { return a > b; });
     free_at.assign(workers, 0);  // a heap, earliest first
     int64_t last = 0;
     for (int c : cost) {
@@ -304,6 +325,21 @@ void choose_cut(const CutKind (&kinds)[N], int cus, const int64_t (&max_parts)[N
   // The choice is part of every call, so a candidate that cannot win is not followed further: one with too many partial
   // results, or whose work shared evenly, or longest block alone, already takes as long as the best so far.
   bool found = false;
+  auto consider = [&](KeySplit (&k)[N]) {  // (pieces counted)
+    count_work(k);
+    if (std::max<int64_t>(total / workers, largest) + merge_time(k) >= best_time) return;
+    const int64_t time = estimate(k);
+    if (time >= best_time) return;
+    std::copy(k, k + N, best);
+    best_time = time;
+    found = true;
+  };
+  if (first) {
+    KeySplit k[N];
+    std::copy(first, first + N, k);
+    count_pieces(k);
+    consider(k);
+  }
   for (int n = 2; n <= 16 && longest / n >= shortest; ++n) {
     KeySplit k[N];
     for (int i = 0; i < N; ++i) {
@@ -320,14 +356,7 @@ void choose_cut(const CutKind (&kinds)[N], int cus, const int64_t (&max_parts)[N
     }
     if (blocks > 2 * kMaxCutBlocks) break;
     if (parts == 0 || !fits) continue;
-    count_work(k);
-    if (std::max<int64_t>(total / workers, largest) + merge_time(k) >= best_time) continue;
-    const int64_t time = estimate(k);
-    if (time < best_time) {
-      std::copy(k, k + N, best);
-      best_time = time;
-      found = true;
-    }
+    consider(k);
   }
   // a kind whose cut brings nothing stays whole
   if (N > 1 && found) {
@@ -365,10 +394,13 @@ void refine_bwd_split(const chunk_attn_desc* d, int tile_rows, int inner, int ke
   kinds[0].whole = dq->target == 0;
   kinds[1].whole = dkv->target == 0;
   if (kinds[0].whole && kinds[1].whole) return;
+  kinds[0].cost = 5;  // 48 MFMAs per wave and stage, against 32 per step of dK/dV: not 3 : 2, as other costs of a step are alike
+  kinds[1].cost = kJointStep;
+  const KeySplit alone[2] = {*dq, *dkv};
   KeySplit best[2];
-  choose_cut<2>(kinds, cus, {max_parts / inner, max_parts / d->num_kv_heads}, best);
-  if (best[0].target > 0) *dq = best[0];
-  if (best[1].target > 0) *dkv = best[1];
+  choose_cut<2>(kinds, cus, {max_parts / inner, max_parts / d->num_kv_heads}, best, alone);
+  *dq = best[0];
+  *dkv = best[1];
 }
 
 std::vector<DkvItem> cut_items(const std::vector<DkvItem>& wholes, int target, std::vector<DkvItem>* cut) {

@@ -152,9 +152,9 @@ KeySplit choose_key_split(const chunk_attn_desc* d, int tile_rows, int inner, in
 // in tiles (tile_piece_count).
 inline int tile_piece_count(int tiles, int target) { return target > 0 ? (tiles + target - 1) / target : 1; }
 KeySplit choose_tile_split(const chunk_attn_desc* d, int keys, int cus, int64_t max_parts);
-// Both kinds of item of a backward that runs them in one launch, on the same compute units: chooses the pieces of the kinds that are cut
-// anew, with all blocks counted and room for `max_parts` partial results of blocks of either kind.  (Each kind by itself has room for
-// fewer, and its pieces may crowd out the other kind's blocks.)
+// Both kinds of item of a backward that runs them in one launch, on the same compute units: chooses the pieces of the kinds that are cut by
+// themselves (`dq` and `dkv` as they come) anew, or none, with all blocks counted and room for `max_parts` partial results of blocks of either kind.
+// (Each kind by itself has room for fewer, and its pieces may crowd out the other kind's blocks.)
 void refine_bwd_split(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int cus, int64_t max_parts, KeySplit* dq, KeySplit* dkv);
 // The key-stationary items to run for such a cut, longest walk first, of equal ones those that walk the same tiles side by
 // side; `cut` receives the whole items that were cut.

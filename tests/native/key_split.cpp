@@ -107,11 +107,11 @@ static int one(const std::vector<chunk_attn_seg>& segs, int heads, int kv_heads,
       REQUIRE(k.pieces == (int64_t)items.size() && k.parts == parts && parts > 0);
     }
   }
-  for (int64_t limit : {(int64_t)3, (int64_t)40, (int64_t)1 << 40}) {  // both kinds of a backward: kinds left whole stay whole
+  for (int64_t limit : {(int64_t)3, (int64_t)40, (int64_t)1 << 40}) {  // both kinds of a backward: kinds that are whole by themselves stay whole
     const KeySplit q0 = choose_key_split(&d, rows, inner, 256, limit / inner), k0 = choose_tile_split(&d, 128, 256, limit / kv_heads);
     KeySplit q1 = q0, k1 = k0;
     refine_bwd_split(&d, rows, inner, 128, 256, 2 * limit, &q1, &k1);
-    REQUIRE((q1.target > 0) == (q0.target > 0) && (k1.target > 0) == (k0.target > 0));
+    REQUIRE((q1.target == 0 || q0.target > 0) && (k1.target == 0 || k0.target > 0));
     REQUIRE(q1.parts * inner <= 2 * limit && k1.parts * kv_heads <= 2 * limit);
     std::vector<DqItem> qcut;
     std::vector<DkvItem> kcut;
@@ -138,6 +138,24 @@ static int one(const std::vector<chunk_attn_seg>& segs, int heads, int kv_heads,
   return 0;
 }
 
+// What a backward's launch runs is what the estimate for both kinds together finds best: whole walks though one kind by itself would be cut, the cuts
+// of each kind by itself, or others (targets in stages and tiles; 0: whole).
+static int joint(int q, int ctx, int heads, int kv_heads, int dq_alone, int dkv_alone, int dq, int dkv) {
+  chunk_attn_seg s{0, q, 0, ctx + q};
+  chunk_attn_desc d{heads, kv_heads, 128, q, ctx + q, 1, &s, 0.1f};
+  const int group = heads / kv_heads;
+  int h = 1;
+  while (h * 2 <= 8 && group % (h * 2) == 0) h *= 2;
+  const int rows = 256 / h, inner = kv_heads * (group / h);
+  const int64_t room = (int64_t)fused_num_bufs(&d, 128) * heads * ((q + 31) / 32) / 8;  // partial results as large as the float32 dQ tiles
+  KeySplit a = choose_key_split(&d, rows, inner, 256, room / inner), b = choose_tile_split(&d, 128, 256, room / kv_heads);
+  REQUIRE(a.target == dq_alone && b.target == dkv_alone);
+  refine_bwd_split(&d, rows, inner, 128, 256, std::max<int64_t>(room, 512), &a, &b);
+  if (a.target != dq || b.target != dkv) std::printf("%d queries behind %d keys: %d and %d\n", q, ctx, a.target, b.target);
+  REQUIRE(a.target == dq && b.target == dkv && (a.parts > 0) == (dq > 0) && (b.parts > 0) == (dkv > 0));
+  return 0;
+}
+
 int main() {
   std::mt19937 rng(7);
   auto uni = [&](int a, int b) { return std::uniform_int_distribution<int>(a, b)(rng); };
@@ -157,6 +175,7 @@ int main() {
   if (one({{0, 1, 0, 1100}}, 8, 2, 1)) return 1;
   if (one({{0, 8192, 0, 32768}}, 32, 8, 0)) return 1;    // four items per compute unit
   if (one({{0, 100, 0, 100}, {100, 60, 100, 60}}, 8, 8, 0)) return 1;  // walks too short to cut
+  if (joint(483, 1954, 32, 8, 39, 0, 0, 0) || joint(3823, 5291, 8, 2, 143, 60, 143, 60) || joint(6863, 10, 8, 2, 72, 31, 0, 72)) return 1;
   std::printf("ok\n");
   return 0;
 }

@@ -118,7 +118,7 @@ def test_workspace_without_room_for_pieces(name, segs, hq, hk, cut):
 @pytest.mark.parametrize("segs,hq,hk", [
     ([(0, 2049, 0, 2049)], 8, 2),     # room for 130 partial results; 110 of dQ blocks and 124 of dK/dV blocks
     ([(0, 467, 0, 467), (467, 916, 467, 916)], 8, 2),
-    ([(0, 1350, 0, 1350), (1350, 129, 1350, 129), (1479, 85, 1479, 85)], 32, 8),
+    ([(0, 1945, 3, 1951), (1945, 228, 1960, 228), (2173, 185, 2188, 185)], 8, 2),
 ])
 def test_workspace_with_room_for_one_kind_of_pieces(oracle_mod, segs, hq, hk):
     """The uncut layout keeps room for float32 dQ tiles.  With a little more for the longer lists, walks of both kinds are cut if the partial
