@@ -196,6 +196,13 @@ struct CutKind {
   }
 };
 
+// (The choice is part of every call: blocks are counted before walks are listed.)
+bool many_blocks(const chunk_attn_desc* d, bool keys, int rows, int inner) {
+  int64_t n = 0;
+  for (int t = 0; t < d->num_segments; ++t) n += ((keys ? d->segments[t].kv_len : d->segments[t].q_len) + rows - 1) / rows;
+  return n * inner >= kMaxCutBlocks;
+}
+
 CutKind key_walks(const chunk_attn_desc* d, int tile_rows, int inner) {
   CutKind k;
   k.inner = inner;
@@ -376,6 +383,7 @@ void choose_cut(const CutKind (&kinds)[N], int cus, const int64_t (&max_parts)[N
 }  // namespace
 
 KeySplit choose_key_split(const chunk_attn_desc* d, int tile_rows, int inner, int cus, int64_t max_parts) {
+  if (many_blocks(d, false, tile_rows, inner)) return KeySplit{};
   const CutKind kinds[1] = {key_walks(d, tile_rows, inner)};
   KeySplit best[1];
   choose_cut<1>(kinds, cus, {max_parts}, best);
@@ -383,6 +391,7 @@ KeySplit choose_key_split(const chunk_attn_desc* d, int tile_rows, int inner, in
 }
 
 KeySplit choose_tile_split(const chunk_attn_desc* d, int keys, int cus, int64_t max_parts) {
+  if (many_blocks(d, true, keys, d->num_kv_heads)) return KeySplit{};
   const CutKind kinds[1] = {tile_walks(d, keys)};
   KeySplit best[1];
   choose_cut<1>(kinds, cus, {max_parts}, best);
@@ -390,10 +399,10 @@ KeySplit choose_tile_split(const chunk_attn_desc* d, int keys, int cus, int64_t 
 }
 
 void refine_bwd_split(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int cus, int64_t max_parts, KeySplit* dq, KeySplit* dkv) {
+  if (dq->target == 0 && dkv->target == 0) return;
   CutKind kinds[2] = {key_walks(d, tile_rows, inner), tile_walks(d, keys)};
   kinds[0].whole = dq->target == 0;
   kinds[1].whole = dkv->target == 0;
-  if (kinds[0].whole && kinds[1].whole) return;
   kinds[0].cost = 5;  // 48 MFMAs per wave and stage, against 32 per step of dK/dV: not 3 : 2, as other costs of a step are alike
   kinds[1].cost = kJointStep;
   const KeySplit alone[2] = {*dq, *dkv};

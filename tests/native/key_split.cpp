@@ -5,6 +5,7 @@
 //   * choose_key_split and refine_bwd_split count what cut_items makes and respect their limits; choose_key_split cuts chunks with few long
 //     walks and no others.
 #include <algorithm>
+#include <chrono>
 #include <cstdio>
 #include <random>
 
@@ -156,6 +157,22 @@ static int joint(int q, int ctx, int heads, int kv_heads, int dq_alone, int dkv_
   return 0;
 }
 
+// Chunks with more blocks than are ever cut cost a call no list of their walks (of a million blocks here, tens of milliseconds).
+static int many_blocks_take_no_time() {
+  chunk_attn_seg s{0, 1 << 27, 0, 1 << 27};
+  chunk_attn_desc d{8, 8, 128, 1 << 27, 1 << 27, 1, &s, 0.1f};
+  double ms = 1e9;
+  for (int i = 0; i < 5; ++i) {
+    const auto t0 = std::chrono::steady_clock::now();
+    KeySplit q = choose_key_split(&d, 256, 8, 256, 1000), k = choose_tile_split(&d, 128, 256, 1000);
+    refine_bwd_split(&d, 256, 8, 128, 256, 1000, &q, &k);
+    REQUIRE(q.target == 0 && k.target == 0);
+    ms = std::min(ms, std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count());
+  }
+  REQUIRE(ms < 1.0);
+  return 0;
+}
+
 int main() {
   std::mt19937 rng(7);
   auto uni = [&](int a, int b) { return std::uniform_int_distribution<int>(a, b)(rng); };
@@ -176,6 +193,7 @@ int main() {
   if (one({{0, 8192, 0, 32768}}, 32, 8, 0)) return 1;    // four items per compute unit
   if (one({{0, 100, 0, 100}, {100, 60, 100, 60}}, 8, 8, 0)) return 1;  // walks too short to cut
   if (joint(483, 1954, 32, 8, 39, 0, 0, 0) || joint(3823, 5291, 8, 2, 143, 60, 143, 60) || joint(6863, 10, 8, 2, 72, 31, 0, 72)) return 1;
+  if (many_blocks_take_no_time()) return 1;
   std::printf("ok\n");
   return 0;
 }
