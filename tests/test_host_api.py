@@ -104,9 +104,11 @@ def packed(*lens):
 @pytest.mark.parametrize("segs,Hq,Hkv,dim,fwd,dq,dkv", [
     # "": the plain kernel, "p": pipelined, "pc": pipelined with cut walks
     ([(0, 8192, 0, 32768)], 32, 8, 128, "p", "p", "p"),           # enough blocks: nothing is cut
-    ([(0, 1024, 0, 32768)], 32, 8, 128, "pc", "pc", "p"),
-    ([(0, 4999, 0, 4999)], 32, 8, 128, "p", "p", "pc"),
-    ([(0, 1024, 0, 32768)], 32, 8, 96, "pc", "pc", "p"),
+    ([(0, 1024, 0, 32768)], 32, 8, 128, "pc", "p", "p"),           # (of the backward's walks those of one kind fill the gaps of the other's)
+    ([(0, 4999, 0, 4999)], 32, 8, 128, "p", "p", "p"),
+    ([(0, 1024, 0, 32768)], 32, 8, 96, "pc", "p", "p"),
+    ([(0, 300, 0, 4000)], 8, 2, 128, "pc", "pc", "p"), ([(0, 1300, 0, 1300)], 8, 2, 96, "pc", "p", "pc"),
+    ([(0, 3823, 0, 9114)], 8, 2, 128, "p", "pc", "pc"),
     (packed(*[4096] * 4), 32, 8, 64, "p", "p", "p"),
     (packed(256, 512, 128, 128), 8, 8, 64, "", "", ""),
     (packed(*[4096] * 4), 32, 8, 256, "", "", "p"),
