@@ -3,8 +3,9 @@
 //
 // Two reductions are needed -- dQ sums over keys, dK/dV sum over queries -- and a workgroup can keep
 // only one of them in registers.  Float atomics for the other one are far too slow on this chip at the
-// rate an attention backward produces them, so each reduction gets its own kernel and every output
-// element is written exactly once (the result is also bit-reproducible):
+// rate an attention backward produces them, so each reduction gets blocks of its own kind and every output
+// element is written exactly once, or put together from the partial results of a walk that was cut, in a fixed order (the result is
+// also bit-reproducible).  Both kinds of block share a launch (bwd_pipe_kernel, bwd_short_kernel) except in long chunks of head_dim 64 and 256:
 //
 //   bwd_pre   D_i = <dO_i, O_i> and LSE_i log2(e) per (head, row), stored in arrays padded to 64-row
 //             tiles per segment (+inf / 0 in the padding, so padded rows yield P = 0);
@@ -13,7 +14,7 @@
 //   bwd_dkv   key-stationary: one workgroup per 128 keys of one key/value head, walking the query heads of
 //             the group and the 32-row query tiles that see those keys; two wave roles per key block,
 //             S = Q K^T, P, dV^T += dO^T P  and  dP = dO V^T, dS, dK^T += Q^T dS (see the kernel).
-// P is recomputed from the saved log-sum-exp in both kernels.  All operands reach LDS by global->LDS copies.
+// P is recomputed from the saved log-sum-exp in both.  All operands reach LDS by global->LDS copies.
 #include <cstring>
 #include <cstdlib>
 #include <type_traits>
@@ -3333,7 +3334,7 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, Cut cut) {
       P.dkv_items = plan_dkv(d, dkv_keys(d->head_dim), P.dkv_split.target > 0 ? 0 : side_by_side);
       if (P.dkv_split.target > 0) P.dkv_items = cut_items(P.dkv_items, P.dkv_split.target, &P.dkv_cut);
     }
-    P.qjobs = tile_jobs(d, false, 64, nullptr);
+    P.qjobs = query_tile_jobs(d, 64);
     int dq_longest = 0, dkv_longest = 0;
     for (const DqItem& it : P.dq_items) dq_longest = std::max(dq_longest, (std::min(it.n0 + it.q_rows - 1, it.keys) + kStageKeys - 1) / kStageKeys);
     for (const DkvItem& it : P.dkv_items) dkv_longest = std::max(dkv_longest, (it.n_qt - it.qt_first) * group);

@@ -43,17 +43,14 @@ int64_t count_tiles(const chunk_attn_desc* d, bool kv, int width) {
   return n;
 }
 
-std::vector<TileJob> tile_jobs(const chunk_attn_desc* d, bool kv, int width, std::vector<int32_t>* seg_tile0) {
+std::vector<TileJob> query_tile_jobs(const chunk_attn_desc* d, int width) {
   std::vector<TileJob> jobs;
-  if (seg_tile0) seg_tile0->clear();
   for (int t = 0; t < d->num_segments; ++t) {
     const chunk_attn_seg& s = d->segments[t];
-    const int32_t start = kv ? s.kv_start : s.q_start, len = kv ? s.kv_len : s.q_len;
-    if (seg_tile0) seg_tile0->push_back((int32_t)jobs.size());
-    for (int32_t r = 0; r < len; r += width) {
+    for (int32_t r = 0; r < s.q_len; r += width) {
       TileJob j;
-      j.src_row0 = start + r;
-      j.valid_rows = std::min<int32_t>(width, len - r);
+      j.src_row0 = s.q_start + r;
+      j.valid_rows = std::min<int32_t>(width, s.q_len - r);
       j.image = (int32_t)jobs.size();
       j.pad = 0;
       jobs.push_back(j);

@@ -168,9 +168,8 @@ std::vector<DqItem> cut_items(const std::vector<DqItem>& wholes, int target, std
 // of items of one key/value head that run at the same time; the items of a sequence are then ordered, and given a walk
 // direction each, so that those items read the same query rows at about the same time (see plan.cpp).
 std::vector<DkvItem> plan_dkv(const chunk_attn_desc* d, int keys, int side_by_side = 0);
-// `width`-row tiles of every segment's key range (kv = true) or query range (kv = false), in segment order;
-// seg_tile0[t] receives the image index of segment t's first tile.
-std::vector<TileJob> tile_jobs(const chunk_attn_desc* d, bool kv, int width, std::vector<int32_t>* seg_tile0);
+// `width`-row tiles of every segment's query range, in segment order, and the number of such tiles of its key (kv) or query range.
+std::vector<TileJob> query_tile_jobs(const chunk_attn_desc* d, int width);
 int64_t count_tiles(const chunk_attn_desc* d, bool kv, int width);
 // Key-row ranges [begin, end) not covered by any segment (to be zero-filled when not accumulating).
 std::vector<std::pair<int32_t, int32_t>> uncovered_kv_ranges(const chunk_attn_desc* d);

@@ -94,33 +94,6 @@ __device__ __forceinline__ void dma16(const void* gsrc, lds_bf16* lds_wave_base)
                                    (__attribute__((address_space(3))) void*)lds_wave_base, 16, 0, 0);
 }
 
-// DMA a row-major tile of ROWS x (8 CHUNKS) bf16 from global rows `src + min(r, last_row) * row_stride`
-// into a swizzled LDS tile.  Called by all 256 threads of the workgroup.
-template <int ROWS, int CHUNKS>
-__device__ __forceinline__ void dma_rows_tile(const __bf16* src, int64_t row_stride, int last_row, __bf16* lds_tile,
-                                              int wave, int lane) {
-  constexpr int N = ROWS * CHUNKS / 256;  // instructions per thread
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    const int x0 = (i * 4 + wave) * 64;   // wave-uniform first chunk of this instruction
-    const int x = x0 + lane;
-    const int row = x / CHUNKS, pc = x % CHUNKS;
-    const int c = unswz<CHUNKS>(row, pc);
-    dma16(src + (int64_t)min(row, last_row) * row_stride + c * 8, lds_tile + x0 * 8);
-  }
-}
-
-// DMA a contiguous image of BYTES bytes (already in LDS order) into LDS.
-template <int BYTES>
-__device__ __forceinline__ void dma_image(const __bf16* src, __bf16* lds_tile, int wave, int lane) {
-  constexpr int N = BYTES / 16 / 256;
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    const int x0 = (i * 4 + wave) * 64;
-    dma16(src + (int64_t)(x0 + lane) * 8, lds_tile + x0 * 8);
-  }
-}
-
 // Workgroup barrier without the memory fence of __syncthreads(): the fence would wait for every outstanding
 // global->LDS copy, including the ones prefetching later stages.  Callers wait (s_waitcnt vmcnt) for exactly
 // the copies the next stage needs before calling this; LDS reads of the finished stage have completed
@@ -141,12 +114,6 @@ __device__ __forceinline__ void stagger_wave_priority() {
   const unsigned slot = __builtin_amdgcn_s_getreg((3 << 11) | (0 << 6) | 4);
   if (slot & 1) __builtin_amdgcn_s_setprio(3);
   else __builtin_amdgcn_s_setprio(0);
-}
-
-// 8 bf16 of (row, logical chunk c)
-template <int CHUNKS>
-__device__ __forceinline__ bf16x8 lds_chunk(const __bf16* tile, int row, int c) {
-  return *reinterpret_cast<const bf16x8*>(tile + tile_elem<CHUNKS>(row, c));
 }
 
 // Chunk-major tile of 32 rows (rows of Q, dO, K or V: D / 8 chunks of 16 bytes each): chunk c of row r sits at slot
