@@ -173,7 +173,7 @@ def test_pipelined_kernels_of_head_dim_64(oracle_mod, name, segs, Hq, Hkv, want)
 def test_tile_edges_of_the_kernels_for_short_walks(oracle_mod, d, Hq, Hkv):
     """Head dimensions 64 and 256 below the pipelined kernels' sizes (asserted): key counts on both sides of the 32- and 64-row tiles the
     forward and dQ kernels read rows and transposed operands from, contexts that are and are not whole tiles, single rows.
-    (LSE: these forwards sum the probabilities as rounded to bf16, 2^-9 of the sum at most.)"""
+    (LSE: that of 64 sums the probabilities as rounded to bf16, 2^-9 of the sum at most.)"""
     lens = [(1, 1), (31, 31), (32, 32), (33, 33), (63, 64), (64, 65), (65, 65), (1, 96), (2, 128), (40, 129), (95, 191), (129, 193)]
     segs, tq, tkv = [], 0, 0
     for n, keys in lens:
@@ -185,7 +185,7 @@ def test_tile_edges_of_the_kernels_for_short_walks(oracle_mod, d, Hq, Hkv):
     o, lse, dq, dk, dv = run_gpu(case, q, k, v, do)
     orc = oracle_mod.Oracle(case.segs, q.cpu(), k.cpu(), v.cpu(), do.cpu(), case.scale)
     O, LSE = orc.forward(); dQ, dK, dV = orc.backward()
-    assert float(np.abs(lse.double().cpu().numpy() - LSE).max()) <= 2.0 ** -9 + 1e-4
+    assert float(np.abs(lse.double().cpu().numpy() - LSE).max()) <= (2.0 ** -9 + 1e-4 if d == 64 else 1e-4)
     for q0, n, k0, keys in segs:  # per sequence: an error in a short one does not drown in the others
         assert rel_err(o[q0:q0 + n], O[q0:q0 + n]) <= TOL_O
         if keys > 1:  # (one query on one key: its dQ and dK are zero up to rounding)
@@ -194,8 +194,8 @@ def test_tile_edges_of_the_kernels_for_short_walks(oracle_mod, d, Hq, Hkv):
 
 
 def test_second_pass_of_head_dim_64(oracle_mod):
-    """The pipelined forward of head_dim 64 with every item sent to its second pass (probabilities rounded to bf16 are summed
-    there: 2^-9 of the sum at most, as much in its logarithm)."""
+    """The pipelined forward of head_dim 64 with every block taken twice, the second time with the maximum over all keys: other references than
+    with the default limit, so other bits, and LSE as close to the oracle (float32 sums of unrounded probabilities)."""
     case = synth.ChunkCase("redo_d64", [synth.Seg(0, 290, 0, 3900), synth.Seg(290, 30, 3903, 70)], 320, 3973, 512, 512, 64, 77)
     assert routes(case) & ca.ROUTE_FWD_PIPELINED
     q, k, v, _ = make_inputs(case)
@@ -205,15 +205,15 @@ def test_second_pass_of_head_dim_64(oracle_mod):
         o, lse = run_gpu(case, q, k, v, backward=False)
     finally:
         ca.chunk_attn_test_set_fwd_rescale_limit(60.0)
-    assert not torch.equal(lse, first[1])           # the second pass ran: it sums rounded probabilities
+    assert not torch.equal(o, first[0]) and not torch.equal(lse, first[1])
     for h in (5, 511):
         O, LSE = oracle_mod.Oracle(case.segs, q[:, h:h + 1].cpu().contiguous(), k[:, h:h + 1].cpu().contiguous(),
                                    v[:, h:h + 1].cpu().contiguous(), None, case.scale).forward()
-        assert rel_err(o[:, h:h + 1], O) <= TOL_O and float(np.abs(lse[h:h + 1].double().cpu().numpy() - LSE).max()) <= 2.0 ** -9 + 1e-4
+        assert rel_err(o[:, h:h + 1], O) <= TOL_O and float(np.abs(lse[h:h + 1].double().cpu().numpy() - LSE).max()) <= 1e-4
 
 
 def test_scores_that_outgrow_their_first_stage_at_head_dim_64(oracle_mod):
-    """Half of the heads have keys whose scores grow past the limit late in the walk: their items alone take the second pass."""
+    """Half of the heads have keys whose scores grow past the limit late in the walk: their blocks alone are taken again."""
     case = synth.ChunkCase("late_growth_d64", [synth.Seg(0, 300, 0, 4000)], 300, 4000, 256, 256, 64, 78)
     assert routes(case) & ca.ROUTE_FWD_PIPELINED
     q, k, v, _ = make_inputs(case)
@@ -222,10 +222,10 @@ def test_scores_that_outgrow_their_first_stage_at_head_dim_64(oracle_mod):
     q = torch.full_like(q, 4.0)
     k = (k.float() * 0.05 + ramp).to(torch.bfloat16)
     o, lse = run_gpu(case, q, k, v, backward=False)
-    for h, tol in ((3, 2.0 ** -9 + 1e-4), (127, 2.0 ** -9 + 1e-4), (128, 1e-4), (255, 1e-4)):
+    for h in (3, 127, 128, 255):
         O, LSE = oracle_mod.Oracle(case.segs, q[:, h:h + 1].cpu().contiguous(), k[:, h:h + 1].cpu().contiguous(),
                                    v[:, h:h + 1].cpu().contiguous(), None, case.scale).forward()
-        assert rel_err(o[:, h:h + 1], O) <= TOL_O and float(np.abs(lse[h:h + 1].double().cpu().numpy() - LSE).max()) <= tol
+        assert rel_err(o[:, h:h + 1], O) <= TOL_O and float(np.abs(lse[h:h + 1].double().cpu().numpy() - LSE).max()) <= 1e-4
 
 
 @pytest.mark.parametrize("name,segs,Hq,Hkv", [

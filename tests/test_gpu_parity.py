@@ -105,22 +105,26 @@ def _forward_only(oracle_mod, case, q, k, v):
 
 
 def test_forward_second_pass_forced(oracle_mod):
-    """The head_dim-128 forward keeps one reference maximum per row and hands rows whose scores outgrow it to a
-    second, rescaling pass.  With the growth limit set below any score every item takes the second pass."""
+    """The head_dim-128 forward keeps one reference maximum per row, of its first stage, and takes a block with a row whose scores outgrow it
+    a second time, with every row's maximum over all keys.  With the growth limit set below any score every block is taken twice: other
+    references, so other float32 roundings of LSE than with the default limit, and both as close to the oracle."""
     case = synth.ChunkCase("redo_forced", synth.hybrid_chunk(200, 500, [130, 70]), 400, 900, 8, 2, 128, 31)
     q, k, v, _ = make_inputs(case)
+    once = run_gpu(case, q, k, v, backward=False)
     ca.chunk_attn_test_set_fwd_rescale_limit(-1e30)
     try:
         eo, el = _forward_only(oracle_mod, case, q, k, v)
+        twice = run_gpu(case, q, k, v, backward=False)
     finally:
         ca.chunk_attn_test_set_fwd_rescale_limit(60.0)
-    print("forced second pass", eo, el, flush=True)
-    assert eo <= TOL_O and el <= 2e-2
+    print("blocks taken twice", eo, el, flush=True)
+    assert eo <= TOL_O and el <= 1e-4
+    assert not torch.equal(once[0], twice[0]) and not torch.equal(once[1], twice[1])  # (they were)
 
 
 def test_forward_scores_outgrow_first_tile(oracle_mod):
     """Scores that grow by hundreds of nats along the keys: the first tile's maximum is useless as a reference
-    for the later ones (exp2 would overflow), so the second pass must take over, on its own."""
+    for the later ones (exp2 would overflow), so blocks must be taken again, on their own."""
     n, Hq, Hkv, d = 700, 8, 2, 128
     case = synth.ChunkCase("growing_scores", [synth.Seg(0, n, 0, n)], n, n, Hq, Hkv, d, 32)
     q, k, v, _ = make_inputs(case)
@@ -129,4 +133,4 @@ def test_forward_scores_outgrow_first_tile(oracle_mod):
     k = (k.float() * 0.05 + ramp).to(torch.bfloat16)                        # up to ~136 nats at the last key
     eo, el = _forward_only(oracle_mod, case, q, k, v)
     print("growing scores", eo, el, flush=True)
-    assert eo <= TOL_O and el <= 5e-2
+    assert eo <= TOL_O and el <= 1.1e-3  # (136 nats as float32 sums of 128 products, each off by 2^-24 of the sum at most)

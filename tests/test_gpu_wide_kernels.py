@@ -30,11 +30,15 @@ def _case(segs, hq, hk):
 def test_tile_edges(oracle_mod, hq, hk, q_len, ctx, limit):
     case = _case([(0, q_len, 2, q_len + ctx), (q_len, 40, q_len + ctx + 2, 40)], hq, hk)
     q, k, v, _ = make_inputs(case)
+    once = run_gpu(case, q, k, v, backward=False)
     ca.chunk_attn_test_set_fwd_rescale_limit(limit)  # (a very low one: every block is taken twice)
     try:
         _check(oracle_mod, case, q, k, v)
+        got = run_gpu(case, q, k, v, backward=False)
     finally:
         ca.chunk_attn_test_set_fwd_rescale_limit(60.0)
+    if q_len + ctx > 2 * 64:  # (rows whose maximum lies past the two stages of the first reference)
+        assert torch.equal(once[0], got[0]) == (limit == 60.0)
 
 
 def test_late_growth_and_more_blocks_than_workgroups(oracle_mod):

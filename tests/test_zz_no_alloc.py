@@ -39,12 +39,12 @@ def test_static_forward_matches_the_workspace_forward_twice(d):
     big = synth.ChunkCase("hybrid_big", synth.hybrid_chunk(700, 1500, [300, 129, 64, 1, 257]), 1451, 2951, 8, 2, d, 71)
     small = synth.ChunkCase("packed_small", synth.packed_chunk([130, 33]), 163, 163, 8, 2, d, 72)
     _both(ca, lib, big)
-    _both(ca, lib, small)   # fewer items, tiles and flags than the call before: nothing stale may be picked up
+    _both(ca, lib, small)   # fewer items and pieces than the call before: nothing stale may be picked up
     _both(ca, lib, big)
 
 
 def test_static_forward_second_pass():
-    """Rows sent to the head_dim 128 forward's second pass read the transposed V images from the static array."""
+    """Blocks that the head_dim 128 forward takes twice, with the static array as with a workspace."""
     import paper_2509_21275_amd as ca
     lib = ctypes.CDLL(ca.LIB_PATH)
     lib.chunk_attn_fwd_static.restype = ctypes.c_int
@@ -67,7 +67,7 @@ def test_static_forward_refuses_what_does_not_fit():
     desc = ca.make_desc(case.segs, 4, 2, 64, 260, 260, case.scale)
     o = torch.empty_like(q); lse = torch.empty((4, 260), dtype=torch.float32, device="cuda")
     assert lib.chunk_attn_fwd_static(ctypes.byref(desc), P(q), P(k), P(v), P(o), P(lse), None) == ca.TOO_LARGE
-    # a transposed copy of V beyond 16 MiB: 40000 keys x 2 heads x 128 x 2 bytes = 20 MB
+    # room as for a transposed copy of V, beyond 16 MiB: 40000 keys x 2 heads x 128 x 2 bytes = 20 MB
     n = 40000
     desc = ca.make_desc([(0, 64, 0, n)], 8, 2, 128, 64, n, 0.1)
     f, _ = ca.chunk_attn_workspace_bytes(desc)
