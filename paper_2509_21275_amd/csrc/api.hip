@@ -352,7 +352,7 @@ __global__ __launch_bounds__(256) void plan_fwd_static_kernel(StaticSegs segs, i
       items[item + k] = p;
     }
     if (x < n_wholes) {
-      it.whole = n;
+      it.pieces = n;
       it.part = n > 1 ? part : -1;
       wholes[x] = it;
     }

@@ -84,13 +84,13 @@ __global__ __launch_bounds__(256) void fwd_merge_kernel(FwdMergeArgs) {
   const float* const ml = part0 + kPartRowFloats + (unit * 32 + l32) * 2;
   float m = ml[0], l = 0.f;
 #pragma unroll 4
-  for (int s = 1; s < it.whole; ++s) m = fmaxf(m, ml[s * step]);
+  for (int s = 1; s < it.pieces; ++s) m = fmaxf(m, ml[s * step]);
   f32x4 o[NQ];
 #pragma unroll
   for (int i = 0; i < NQ; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
   const float* const src = part0 + unit * 4096 + wave * (NQ * 256) + lane * 4;
 #pragma unroll 4
-  for (int s = 0; s < it.whole; ++s) {
+  for (int s = 0; s < it.pieces; ++s) {
     const f32x2 v2 = *reinterpret_cast<const f32x2*>(ml + s * step);
     const float f = __builtin_amdgcn_exp2f(v2[0] - m);
     l += v2[1] * f;

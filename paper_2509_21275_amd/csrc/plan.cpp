@@ -93,7 +93,7 @@ std::vector<FwdItem> plan_fwd(const chunk_attn_desc* d, int tile_rows) {
     }
   }
   by_sequence_then_walk(d, items);
-  for (FwdItem& it : items) it.whole = 1;
+  for (FwdItem& it : items) it.pieces = 1;
   return items;
 }
 
@@ -437,10 +437,9 @@ std::vector<DkvItem> cut_items(const std::vector<DkvItem>& wholes, int target, s
 std::vector<FwdItem> cut_items(std::vector<FwdItem>& wholes, int target) {
   std::vector<FwdItem> items;
   int32_t part = 0;
-  for (size_t w = 0; w < wholes.size(); ++w) {
-    FwdItem& whole = wholes[w];
+  for (FwdItem& whole : wholes) {
     const int stages = walk_stages(whole.n0, whole.q_rows), n = piece_count(stages, whole.n0, target);
-    whole.whole = n;
+    whole.pieces = n;
     whole.part = n > 1 ? part : -1;
     for (int k = 0; k < n; ++k) {
       const int b = piece_begin(stages, n, k) * kStageKeys;
@@ -448,7 +447,6 @@ std::vector<FwdItem> cut_items(std::vector<FwdItem>& wholes, int target) {
       it.kv_row0 += b;
       it.n0 -= b;
       it.keys = (k + 1 < n ? piece_begin(stages, n, k + 1) * kStageKeys : whole.keys) - b;
-      it.whole = (int32_t)w;
       it.part = n > 1 ? part++ : -1;
       items.push_back(it);
     }

@@ -35,7 +35,7 @@ struct FwdItem {
   int32_t pad;
   // head_dim 96 and 128, whose walks over the keys may be cut into pieces (choose_key_split; 64 and 256: one piece each):
   int32_t keys;      // keys of the item's own range: it sees min(n0 + r, keys) of them
-  int32_t whole;     // a piece: index of the whole item (as the host lists them).  A whole item: number of its pieces (1: not cut)
+  int32_t pieces;    // a whole item: the number of its pieces (1: not cut)
   int32_t part;      // a piece: its slot among the partial results, -1 if it is the whole item.  A whole item: its first slot
 };
 

@@ -61,8 +61,8 @@ static int one(const std::vector<chunk_attn_seg>& segs, int heads, int kv_heads,
     if (check(w, items, target, &parts)) return 1;
     size_t x = 0;
     for (size_t i = 0; i < w.size(); ++i) {
-      REQUIRE(w[i].whole >= 1 && (w[i].part >= 0) == (w[i].whole > 1) && (w[i].part < 0 || w[i].part == items[x].part));
-      for (int k = 0; k < w[i].whole; ++k, ++x) REQUIRE(items[x].whole == (int)i);
+      REQUIRE(w[i].pieces >= 1 && (w[i].part >= 0) == (w[i].pieces > 1) && (w[i].part < 0 || w[i].part == items[x].part));
+      for (int k = 0; k < w[i].pieces; ++k, ++x) REQUIRE(items[x].q_row0 == w[i].q_row0);
     }
     const auto q = plan_dq(&d, rows);
     std::vector<DqItem> cut;
