@@ -377,6 +377,8 @@ struct DkvParams {
   int32_t accumulate;
   int32_t out_f32;      // dk / dv point to fp32 arrays of the same shape
   int32_t* taken;       // 8 block-queue counters of the pipelined kernel (zero before the launch)
+  int32_t* ended;       // per queue, the blocks that have ended (zero before the launch)
+  int32_t side_by_side; // blocks of a queue that run at the same time, of which long equal walks start together (dkv_pipe_blocks); 0: none do
   float* parts;         // partial results of pieces (dkv_pipe_blocks), kPartRowFloats per (slot, key/value head)
   unsigned long long* clock_log;  // null, or where the pipelined kernel's workgroups log their clocks
   int32_t num_blocks;
@@ -792,6 +794,7 @@ __device__ __forceinline__ T load_uniform(const T* list, int x) {
 template <class P>
 using ArgsPtr = const __attribute__((address_space(4))) P*;
 
+constexpr int kStepsInStep = 2048;  // steps of dK/dV walks that start together
 template <int D, bool CUT>
 __device__ __forceinline__ void dkv_pipe_blocks(const ArgsPtr<DkvParams> args, const int mine) {
   constexpr int NW = 4;        // waves
@@ -838,17 +841,26 @@ __device__ __forceinline__ void dkv_pipe_blocks(const ArgsPtr<DkvParams> args, c
   // The workgroup is persistent: it claims one block (128 keys of one key/value head) after the other
   // (device_common.hpp) until none is left.  The next block is claimed before the current one's last few steps: early
   // enough for the answer to arrive by the time it is needed, and not earlier (that would fix the order of the blocks
-  // before it is known which workgroup is free first).  Blocks that walk the same rows do not wait for each other: that gained the L2
-  // something while every workgroup ran blocks of this kind; with those of dQ between them it saves no traffic (16384 queries on 131072 keys, 64/8
-  // heads, 39 - 48 GB with it, 37 - 49 without) and workgroups stand idle (873 queries on 5197 keys, 32/8, whole walks, backward 323 / 238 us).
+  // before it is known which workgroup is free first).
+  // Long equal walks (key blocks that every query sees) wait for the groups of `side_by_side` blocks before theirs, so that a group starts together and
+  // shares its rows in the L2: last of eight slices of 16384 queries, 64/8 heads, 84 - 126 -> 53 - 80 GB, the eight and a packed chunk together 50 -> 45 GB
+  // per launch; that slice, forward and backward, 232.3 -> 231.5 ms.  With shorter walks workgroups only stand idle: 873 queries on 5197 keys, 32/8, whole
+  // walks, backward 323 us with the waits, 238 without; 405 on 17711, 64/8, 829 / 740; walks of 1024 steps +- 0.1 %.  And where dQ blocks
+  // come first workgroups reach these one by one.
   int* const next_block = (int*)((__bf16*)smem + LDS_ELEMS);
   const int xcd = xcd_of_this_wave();
   clock_log_stamp(fresh(args).clock_log, 0);
   int blk = mine;
+  auto start_in_step = [&](const DkvParams& p, int b) __attribute__((always_inline)) {
+    if (CUT || p.side_by_side == 0 || b < 0) return;
+    const DkvItem it = load_uniform(p.items, b / p.num_kv_heads);
+    if (it.j0 + it.kv_rows <= it.ctx && (int64_t)it.n_qt * p.group >= kStepsInStep) wait_for_earlier_groups(p.ended, b, p.side_by_side);
+  };
   if (mine == kClaimBlocks) {
     if (wave == 0) {
       const DkvParams p = fresh(args);
       blk = block_claim_finish(p.taken, p.num_blocks, xcd, block_claim_issue(p.taken, xcd));
+      start_in_step(p, blk);
     }
     blk = broadcast_from_wave0(next_block, blk);
   }
@@ -1279,7 +1291,9 @@ __device__ __forceinline__ void dkv_pipe_blocks(const ArgsPtr<DkvParams> args, c
   int nb = 0;
   if (wave == 0) {
     const DkvParams p = fresh(args);
+    if (!CUT && p.side_by_side != 0 && lane == 0) __hip_atomic_fetch_add(p.ended + (blk & 7), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     nb = block_claim_finish(p.taken, p.num_blocks, xcd, pending_claim);
+    start_in_step(p, nb);
   }
   blk = broadcast_from_wave0(next_block, nb);
   }
@@ -2916,8 +2930,9 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_wide_kernel(DqParams) {
 // small chunks run both kinds side by side on compute units that one kind alone would leave idle, and no chunk ends twice.  The kind
 // with the longer walks goes first (`dq_phase`: the phase of dQ), so that long blocks do not start last.  Both kinds fill
 // the LDS and a wave's registers, whatever the order.  Forward and backward, two launches -> one: 557 causal tokens, 32/8 heads,
-// 123 -> 96 us; two slices of 3193 and 4999 queries (backwards only) 1886 -> 1801; long chunks are as fast either way (packed
-// 64K chunk, 8192 queries on 32768 keys: within 0.3 %).
+// 123 -> 96 us; two slices of 3193 and 4999 queries (backwards only) 1886 -> 1801; packed 64K chunk, 8192 queries on 32768 keys within 0.3 %;
+// 16384 queries on 131072 keys, 64/8, 230.8 -> 232.5 ms at most (four comparisons, 0.1 - 0.7 %): dQ blocks start as dK/dV blocks end, no longer together,
+// and fetch K and V more often.
 // ------------------------------------------------------------------------------------------------
 struct BwdPipeParams {
   DqParams dq;
@@ -3151,6 +3166,8 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
   pk.accumulate = a.accumulate ? 1 : 0;
   pk.out_f32 = a.dkv_f32 ? 1 : 0;
   pk.taken = reinterpret_cast<int32_t*>(ws + P.queues_off) + kBlockQueues;
+  pk.ended = pk.taken + kBlockQueues;
+  pk.side_by_side = P.dkv_in_step ? persistent_grid(0x7fffffff) / kBlockQueues : 0;
   pk.parts = reinterpret_cast<float*>(ws + P.fdq_off);
   pk.clock_log = clock_log(2);
   static_assert(DKV_KEYS == 128, "the head_dim 64 and 128 kernels cover 128 keys per workgroup");
@@ -3339,6 +3356,7 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, Cut cut) {
     for (const DqItem& it : P.dq_items) dq_longest = std::max(dq_longest, (std::min(it.n0 + it.q_rows - 1, it.keys) + kStageKeys - 1) / kStageKeys);
     for (const DkvItem& it : P.dkv_items) dkv_longest = std::max(dkv_longest, (it.n_qt - it.qt_first) * group);
     P.dq_first = dq_longest > dkv_longest || (d->head_dim == 64 && dq_longest == dkv_longest);  // (64: short_joins)
+    P.dkv_in_step = !P.dq_first && dkv_longest >= kStepsInStep;
   }
   // the layout does not depend on which backward runs: item and piece counts follow from the segment table
   for (int t = 0; t < d->num_segments; ++t) {
@@ -3354,9 +3372,9 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, Cut cut) {
   P.dkv_items_off = P.dq_cut_off + up16(P.n_dq_cut * sizeof(DqItem));
   P.dkv_cut_off = P.dkv_items_off + up16((P.dkv_split.target > 0 ? (size_t)P.dkv_split.pieces : n_dkv) * sizeof(DkvItem));
   P.qjobs_off = P.dkv_cut_off + up16(P.n_dkv_cut * sizeof(DkvItem));
-  // block-queue counters of the dQ and of the dK/dV kernel (zero in the blob)
+  // block-queue counters of the dQ and of the dK/dV kernel (zero in the blob): dQ queues, dK/dV queues, dK/dV blocks ended
   P.queues_off = P.qjobs_off + up16((size_t)P.q_tiles * sizeof(TileJob));
-  P.fitems_off = P.queues_off + up16(2 * kBlockQueues * sizeof(int32_t));
+  P.fitems_off = P.queues_off + up16(3 * kBlockQueues * sizeof(int32_t));
   // the workspace is sized for either backward (the mode may change between the size query and the call): the one-pass
   // backward has one item per (key block, key/value head) and at most 8 x that many workgroup slots
   const size_t n_fused = d->head_dim == 128 ? n_dkv_blocks(d) * (size_t)d->num_kv_heads : 0;

@@ -123,6 +123,19 @@ __device__ __forceinline__ int block_claim_finish(int32_t* taken, int total, int
   }
   return -1;
 }
+// Blocks that read the same rows side by side (one queue = one key/value head's blocks, `width` of them at a time): block `blk` (>= 0) starts
+// only when `ended[queue]`, the number of the queue's blocks that have ended, has reached the first index of its group of `width`.  Called by
+// one wave; the wait is bounded (the blocks waited for were claimed earlier and are running, so it ends by itself; the
+// bound only keeps a surprise from turning into a hang) and nothing but timing depends on it.
+__device__ __forceinline__ void wait_for_earlier_groups(const int32_t* ended, int blk, int width) {
+  const int need = (blk / 8) / width * width;
+  if (need == 0) return;
+  for (int spins = 0; spins < 256; ++spins) {
+    const int seen = __hip_atomic_load(ended + (blk & 7), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (__builtin_amdgcn_readfirstlane(seen) >= need) break;
+    __builtin_amdgcn_s_sleep(32);
+  }
+}
 // Hands a wave-uniform value of wave 0 to the whole workgroup through `slot` (LDS).  Contains a workgroup barrier
 // without a memory fence: outstanding global stores are not waited for.
 __device__ __forceinline__ int broadcast_from_wave0(int* slot, int value) {

@@ -135,6 +135,7 @@ struct BwdPlan {
   bool dq_wide = false;                    // head_dim 256: bwd_dq_wide_kernel runs
   int dq_waves = 0;                        // 32-row units of a dQ workgroup
   bool dq_first = false;                   // both kinds in one launch: the dQ blocks start before the dK/dV blocks
+  bool dkv_in_step = false;                // head_dim 96 and 128: long dK/dV walks start in groups (dkv_pipe_blocks)
   bool in_turn = false;                    // head_dim 96 and 128: a launch per kind, whose partial results take the same place
   // one-pass backward (head_dim 128): its items and workgroup order travel at the end of the blob; then the per-wave
   // progress counters and the status word (cleared by a kernel on every call) and the float32 dQ tiles

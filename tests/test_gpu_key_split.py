@@ -203,3 +203,22 @@ def test_cut_key_blocks_accumulate(oracle_mod, f32kv, d):
     _, dK, dV = orc.backward()
     for g, w in ((got[3], dK), (got[4], dV)):
         assert torch.all(g.cpu()[~cov] == 3.0) and rel_err(g.cpu()[cov], w[cov.numpy()] + 3.0) <= TOL_GRAD
+
+
+@pytest.mark.parametrize("d", [128, 96])
+def test_dkv_walks_that_start_in_groups(d):
+    """dK/dV walks of 2048 steps, four groups of 32 blocks for every key/value head, whose later groups wait for the earlier ones.  The waits change
+    no sum: the same bits twice, and those of one head group by itself, whose walks are cut and wait for none, up to the order of float32
+    sums, so one bf16 rounding (2^-8 of a value either way)."""
+    case = _case("in_step", [(0, 8192, 0, 16384)], 64, 8, d)
+    q, k, v, do = make_inputs(case)
+    first, again = run_gpu(case, q, k, v, do), run_gpu(case, q, k, v, do)
+    assert all(torch.equal(x, y) for x, y in zip(first, again))
+    o, lse, dq, dk, dv = first
+    for g in (0, 7):
+        one = dataclasses.replace(case, num_q_heads=8, num_kv_heads=1)
+        qh, kh = slice(8 * g, 8 * g + 8), slice(g, g + 1)
+        part = [x.contiguous() for x in (q[:, qh], k[:, kh], v[:, kh], do[:, qh])]
+        _, _, dq1, dk1, dv1 = run_gpu(one, *part)
+        for x, y in ((dq[:, qh], dq1), (dk[:, kh], dk1), (dv[:, kh], dv1)):
+            assert rel_err(x, y.double().cpu().numpy()) <= 2.0 ** -7
