@@ -843,8 +843,8 @@ __device__ __forceinline__ void dkv_pipe_blocks(const ArgsPtr<DkvParams> args, c
   // enough for the answer to arrive by the time it is needed, and not earlier (that would fix the order of the blocks
   // before it is known which workgroup is free first).
   // Long equal walks (key blocks that every query sees) wait for the groups of `side_by_side` blocks before theirs, so that a group starts together and
-  // shares its rows in the L2: last of eight slices of 16384 queries, 64/8 heads, 84 - 126 -> 53 - 80 GB, the eight and a packed chunk together 50 -> 45 GB
-  // per launch; that slice, forward and backward, 232.3 -> 231.5 ms.  With shorter walks workgroups only stand idle: 873 queries on 5197 keys, 32/8, whole
+  // shares its rows in the L2: last of eight slices of 16384 queries, 64/8 heads, 84 - 126 -> 53 - 97 GB (two runs each), the eight and a packed chunk together
+  // 50 - 55 -> 45 - 48 per launch; that slice, forward and backward, 232.3 -> 231.5 ms.  With shorter walks workgroups only stand idle: 873 queries on 5197 keys, 32/8, whole
   // walks, backward 323 us with the waits, 238 without; 405 on 17711, 64/8, 829 / 740; walks of 1024 steps +- 0.1 %.  And where dQ blocks
   // come first workgroups reach these one by one.
   int* const next_block = (int*)((__bf16*)smem + LDS_ELEMS);
