@@ -252,6 +252,9 @@ int chunk_attn_test_bwd_status_offset(const chunk_attn_desc* desc, size_t* offse
 #define CHUNK_ATTN_ROUTE_DKV_CUT 32      /* some of its walks over the query tiles are cut */
 #define CHUNK_ATTN_ROUTE_ONE_PASS 64     /* one-pass backward instead of the dQ and dK/dV kernels */
 int chunk_attn_test_routes(const chunk_attn_desc* desc, int32_t* routes);
+/* Test hook (host only): query heads per workgroup where the forward of a small chunk divides the keys of 32 rows among the waves of a
+ * workgroup (1, 2 or 4; the routes above are then those of a workspace too small for the reported size), else 0. */
+int chunk_attn_test_shared_heads(const chunk_attn_desc* desc, int32_t* heads);
 
 /* Static description of an error code; for CHUNK_ATTN_HIP_ERROR includes the last HIP error text. */
 const char* chunk_attn_strerror(int code);

@@ -181,7 +181,8 @@ inline size_t padded_bytes(int64_t rows, int heads, size_t elem) { return align_
 // the kernel arguments carry the items) then, for 96 and 128, the partial results of items whose walks are cut.
 struct FwdLayout {
   int tile_rows;
-  bool pipe;       // the pipelined kernel runs (head_dim 96 and 128, and 64 from a number of blocks on)
+  bool pipe;       // the pipelined kernel runs (head_dim 96 and 128, and 64 from a number of blocks on), unless
+  int share;       // > 0: fwd_share_kernel runs, its workgroups taking so many heads each
   KeySplit split;  // pipelined kernel: how the walks are cut
   size_t n_items, n_wholes, wholes_off, queues_off, blob_bytes, parts_off, total;
   int64_t blocks;
@@ -193,6 +194,10 @@ constexpr size_t kStaticScratchBytes = (size_t)16 << 20;
 
 // The lists of a layout whose sizes are known.
 void fill_fwd_lists(const chunk_attn_desc* d, FwdLayout& L) {
+  if (L.share > 0) {
+    L.items = plan_fwd(d, 32);
+    return;
+  }
   std::vector<FwdItem> wholes = plan_fwd(d, L.tile_rows);
   L.items = cut_items(wholes, L.split.target);
   for (const FwdItem& w : wholes)
@@ -245,6 +250,12 @@ void layout_fwd(const chunk_attn_desc* desc, FwdLayout& L, bool with_plan, bool 
   L.total = std::max(uncut_total, L.parts_off + align_up((size_t)L.split.parts * part_bytes));
   if (is_narrow(desc))  // (as much as with padded copies of Q, K, V and O)
     L.total = std::max(L.total, uncut_total + 2 * padded_bytes(d->total_q, d->num_q_heads, 2) + 2 * padded_bytes(d->total_kv, d->num_kv_heads, 2));
+  // (the layout of the workspace stays the other kernel's, so that its size does)
+  L.share = may_cut ? choose_shared_heads(desc, walks, inner, pipe, L.split.target > 0) : 0;
+  if (L.share > 0) {
+    L.n_items = (size_t)count_walks(d, 32).items;
+    L.blocks = (int64_t)L.n_items * (d->num_q_heads / L.share);
+  }
   if (with_plan) fill_fwd_lists(desc, L);
 }
 
@@ -425,6 +436,7 @@ NarrowBwdLayout narrow_bwd_layout(const chunk_attn_desc* d, size_t inner_bytes) 
 // runtime, with workgroups that find their block without a counter, and without the forward's second launch: 92 -> 73 us; 439
 // tokens, 8/2 heads, 87 -> 68; the static forward of 1501 + 203 keys next to 611 short rows 41 -> 30 us.
 bool fwd_inline(const FwdLayout& L, int head_dim) {
+  if (L.share > 0) return true;
   const bool claims = L.pipe || head_dim == 256;
   return L.n_items <= (size_t)kInlineItems && (!claims || L.blocks <= persistent_grid(L.blocks, fwd_per_cu(head_dim)));
 }
@@ -444,7 +456,7 @@ FwdParams fwd_params(const chunk_attn_desc* desc, const FwdLayout& L, char* ws, 
   p.num_q_heads = desc->num_q_heads;
   p.num_kv_heads = desc->num_kv_heads;
   p.group = desc->num_q_heads / desc->num_kv_heads;
-  p.heads_per_wg = heads_per_wg(p.group, fwd_waves(desc->head_dim));
+  p.heads_per_wg = L.share > 0 ? L.share : heads_per_wg(p.group, fwd_waves(desc->head_dim));
   p.head_splits = p.group / p.heads_per_wg;
   p.total_q = desc->total_q;
   p.scale_log2 = desc->softmax_scale * 1.4426950408889634f;
@@ -453,6 +465,7 @@ FwdParams fwd_params(const chunk_attn_desc* desc, const FwdLayout& L, char* ws, 
   p.ref_limit = g_fwd_rescale_limit.load();
   return p;
 }
+FwdKind fwd_kind(const FwdLayout& L) { return L.share > 0 ? kFwdShare : L.pipe ? kFwdPipe : kFwdPlain; }
 FwdLists fwd_lists(const FwdLayout& L) {
   FwdLists l;
   l.num_blocks = (int)L.blocks;
@@ -539,6 +552,16 @@ int chunk_attn_test_routes(const chunk_attn_desc* desc, int32_t* routes) {
   return CHUNK_ATTN_OK;
 }
 
+int chunk_attn_test_shared_heads(const chunk_attn_desc* desc, int32_t* heads) {
+  const int rc = validate(desc);
+  if (rc != CHUNK_ATTN_OK) return rc;
+  if (!heads) return CHUNK_ATTN_INVALID_ARG;
+  FwdLayout L;
+  layout_fwd(desc, L, false);
+  *heads = L.share;
+  return CHUNK_ATTN_OK;
+}
+
 int chunk_attn_test_set_fwd_rescale_limit(float log2_growth) {
   g_fwd_rescale_limit.store(log2_growth);
   return CHUNK_ATTN_OK;
@@ -616,7 +639,7 @@ int chunk_attn_fwd(const chunk_attn_desc* desc, const void* q, const void* k, co
   ProfileEvents pe = profile_events();
   profile_events() = ProfileEvents{};
   if (pe.start && (e = hipEventRecord(pe.start, stream)) != hipSuccess) return hip_fail(e, "event record");
-  e = launch_fwd(p, desc->head_dim, L.pipe, fwd_lists(L), stream);
+  e = launch_fwd(p, desc->head_dim, fwd_kind(L), fwd_lists(L), stream);
   if (e != hipSuccess) return hip_fail(e, "forward launch");
   if (pe.stop && (e = hipEventRecord(pe.stop, stream)) != hipSuccess) return hip_fail(e, "event record");
   return CHUNK_ATTN_OK;
@@ -650,7 +673,7 @@ int chunk_attn_fwd_static(const chunk_attn_desc* desc, const void* q, const void
                        L.split.target, reinterpret_cast<int32_t*>(ws + L.queues_off));
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "schedule kernel launch");
   }
-  e = launch_fwd(p, desc->head_dim, L.pipe, lists, stream);
+  e = launch_fwd(p, desc->head_dim, fwd_kind(L), lists, stream);
   if (e != hipSuccess) return hip_fail(e, "forward launch");
   return CHUNK_ATTN_OK;
 }

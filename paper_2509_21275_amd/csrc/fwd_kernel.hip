@@ -9,7 +9,7 @@
 // registers plus one exchange with the lane 32 away, and the bf16 probabilities are already laid out as the
 // B operand of O^T += V^T P^T (device_common.hpp, "C-order").
 //
-// Three kernels:
+// Four kernels:
 //   fwd_kernel       online softmax with a lazily moved reference maximum, one 32-row query block per wave,
 //                    tiles of 64 keys (rows, those of V read transposed, double-buffered).  Used for head_dim 64 unless its walks
 //                    are long (pipe_pays).
@@ -27,6 +27,7 @@
 //                    128 has too few items for the chip their walks are cut into pieces (plan.hpp); the pieces leave
 //                    float32 partial results, which fwd_merge_kernel puts together.
 //   fwd_wide_kernel  head_dim 256: the same with 32 query rows per wave.
+//   fwd_share_kernel head_dim 64 and 128, small chunks (choose_shared_heads): the waves of a workgroup divide the keys of 32 rows.
 #include <cstring>
 #include <type_traits>
 
@@ -1274,6 +1275,303 @@ __global__ __launch_bounds__(256, 1) void fwd_wide_kernel(FwdArgs) {
   }
 }
 
+// ------------------------------------------------------------------------------------------------
+// Forward of small chunks: a workgroup takes 32 query rows of HG heads of one group, and KS waves per head divide the keys: those of split x
+// take stages x, x + KS, ... of 32 keys.  The HG waves of a split share its stages (one barrier per step; a single head's waves wait for
+// nothing but their own copies), and the splits' sums meet in LDS at the end, where they are put together as fwd_merge_kernel does it.
+// What a small chunk waits for is one wave's chain of stages (a copy, reads, products, exponentials, products: 0.9 - 1.4 us a stage), so the
+// chain is cut eight ways where there is one head to a workgroup, and two waves per SIMD overlap.  More heads per workgroup read
+// a stage fewer times from the L2 and cut the chain less; choose_shared_heads weighs it.  Kernel before -> now, us: 1024 tokens, 8/8
+// heads, head_dim 64, 16.9 -> 7.9, 100 queries on 10100 keys, 32/8, 124 -> 40; head_dim 128, 500 tokens, 32/8, 21.5 -> 10.7, 8/8, 22.2 -> 8.0; 203
+// queries on 1704 keys with 611 packed tokens, 32/8, 30.1 -> 21.6.  One head with four waves and two slots each instead of eight with
+// one: 1000 tokens, 8/8, 15.1 instead of 11.2; there K of the next stage is copied once K has been read, V once V has been (both after V: 11.2 -> 11.0,
+// 3000 tokens, 8/8, 44.6 -> 42.1).  Two heads in one wave with four waves: 203 + 611 queries as above 29.0.
+//
+// Tiles are rows (a copy instruction fetches whole rows; chunk-major tiles touch up to eight times the cache lines): chunk c of row r sits at
+// c ^ share_swz(r), which serves 16-byte reads of 16 consecutive rows and transposed reads of four rows by four chunks without conflicts.
+// ------------------------------------------------------------------------------------------------
+template <int D>
+__host__ __device__ constexpr int share_swz(int r) {
+  return D == 64 ? ((r >> 3) & 1) | ((r >> 1) & 2) | ((r & 2) << 1) : ((r & 3) << 2) | ((r >> 2) & 3);
+}
+constexpr float kNoMax = -3.4028234e38f;  // reference maximum of a row that has seen no key yet
+template <int D, int HG, int KS, int NS>
+constexpr size_t share_smem() {  // the splits' slots of a K and a V tile and the heads' Q tiles, or each wave's O; a maximum and a sum per wave and row
+  const size_t tiles = (size_t)(KS * NS * 2 + HG) * 32 * D * 2, sums = (size_t)HG * KS * 32 * D * 4;
+  return (tiles > sums ? tiles : sums) + (size_t)HG * KS * 32 * 2 * sizeof(float);
+}
+
+template <int D, int HG, int KS, int NS>
+__global__ __launch_bounds__(HG * KS * 64, D == 64 ? 4 : HG * KS / 4) void fwd_share_kernel(FwdArgs) {
+  constexpr int W = HG * KS;
+  constexpr int C = D / 8, DK = D / 16, DB = D / 32;
+  constexpr int TILE = 32 * D * 2;    // bytes of a tile
+  constexpr int PT = C / 2;           // copies of 64 chunks per tile
+  constexpr int RPC = 64 / C;         // rows per copy
+  constexpr int PPW = 2 * PT / HG;    // copies of a stage per wave
+  constexpr int NQ = DB * 4;          // accumulator quarters of a head
+  constexpr int NQW = NQ / KS;        // of which a wave puts together
+  static_assert(NQ % KS == 0 && PPW % (D == 64 ? 2 : 4) == 0 && (HG == 1 || PT % PPW == 0));
+  static_assert(HG == 1 ? NS <= 2 : NS == 2 || NS == 3);
+  const FwdArgsPtr args = fwd_args();
+  const FwdParams p = load_params(&args->p);
+
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), unit = wave % HG, split = wave / HG;
+  const int l32 = lane & 31, hh = lane >> 5;
+  lds_bf16* const region = (lds_bf16*)(smem + split * (NS * 2 * TILE));
+  lds_bf16* const q_tiles = (lds_bf16*)(smem + KS * NS * 2 * TILE);  // [HG][32][D]
+  lds_f32* const ml = (lds_f32*)(smem + share_smem<D, HG, KS, NS>() - W * 32 * 2 * sizeof(float));
+  if constexpr (W > 4) stagger_wave_priority();
+
+  const int inner_n = p.num_kv_heads * p.head_splits, inner = blockIdx.x % inner_n;
+  const FwdItem it = load_item(p.items, args->items, blockIdx.x / inner_n);
+  const int kvh = inner % p.num_kv_heads, hs = inner / p.num_kv_heads;
+  const int head = kvh * p.group + hs * HG + unit;
+  const int n_keys = it.n0 + it.q_rows - 1;  // keys visible to the last row
+  const int nt = (n_keys + 31) / 32;
+  const int n_mine = nt > split ? (nt - split + KS - 1) / KS : 0;
+
+  const int64_t q_stride = (int64_t)p.num_q_heads * D;
+  const int kv_stride = p.num_kv_heads * D;
+
+  // copy i of a tile fills rows RPC i .. RPC (i + 1) - 1; a row's index splits into the lane's part and the copy's
+  const int c_row = lane / C, c_chunk = (lane % C) ^ share_swz<D>(c_row);
+  // ---- Q: the waves of a head copy every KS-th piece of its tile ----
+#pragma unroll
+  for (int x = 0; x < PT; x += KS) {
+    const int i = x + split;
+    if (PT % KS != 0 && i >= PT) break;
+    const int row = min(RPC * i + c_row, it.q_rows - 1);  // rows past the tile repeat the last one (never stored)
+    dma16(p.q + (int64_t)(it.q_row0 + row) * q_stride + (int64_t)head * D + (c_chunk ^ share_swz<D>(RPC * i)) * 8,
+          q_tiles + (unit * PT + i) * 512);
+  }
+  // ---- K and V: wave `unit` of a split copies pieces PPW unit .. + PPW - 1 of the 2 PT pieces of a stage (K, then V) ----
+  const int piece0 = unit * PPW;
+  const __bf16* const Kg = p.k + (int64_t)it.kv_row0 * kv_stride + (int64_t)kvh * D;
+  const __bf16* const Vg = p.v + (int64_t)it.kv_row0 * kv_stride + (int64_t)kvh * D;
+  const int row0 = HG == 1 ? 0 : RPC * (piece0 % PT);  // first row the wave copies
+  const __bf16* const Xg = HG == 1 || piece0 < PT ? Kg : Vg;
+  const int c_off = c_row * kv_stride;
+  auto copy_pieces = [&](int i, int slot, auto first_c, auto end_c) __attribute__((always_inline)) {
+    const int t = split + KS * i;
+    const int64_t toff = (int64_t)(32 * t + row0) * kv_stride;  // wave-uniform
+    lds_bf16* const dst = region + slot * TILE + piece0 * 512;
+    const int last_row = n_keys - 1 - 32 * t - row0;
+    static_for<decltype(first_c)::value, decltype(end_c)::value>([&](auto x_c) __attribute__((always_inline)) {
+      constexpr int x = decltype(x_c)::value, j = x % PT;
+      const __bf16* const src = (HG > 1 || x < PT ? Xg : Vg) + toff;
+      const int chunk = (c_chunk ^ share_swz<D>(RPC * j)) * 8;
+      if (last_row >= 31) dma16(src + (int64_t)(RPC * j) * kv_stride + (unsigned)(c_off + chunk), dst + x * 512);
+      else dma16(src + (int64_t)min(RPC * j + c_row, last_row) * kv_stride + chunk, dst + x * 512);  // (rows past the last one repeat it)
+    });
+  };
+  const std::integral_constant<int, 0> first;
+  const std::integral_constant<int, PT> half;
+  const std::integral_constant<int, PPW> all;
+  auto copy_stage = [&](int i, int slot) __attribute__((always_inline)) { copy_pieces(i, slot, first, all); };
+  constexpr int AHEAD = HG == 1 ? NS : NS - 1;  // stages copied before the first step
+  constexpr bool HALVES = HG == 1 && NS == 1;   // one slot: K of the next stage is copied once K has been read, V once V has been
+#pragma unroll
+  for (int s = 0; s < AHEAD; ++s)
+    if (s < n_mine) copy_stage(s, s);
+
+  const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  f32x16 oacc[DB];
+#pragma unroll
+  for (int db = 0; db < DB; ++db) oacc[db] = zero16;
+  float m_run = kNoMax, l_run = 0.f;
+  const float c = p.scale_log2, limit = fminf(8.0f, p.ref_limit);
+
+  // the Q copies have landed when at most those of the stages are outstanding
+  if (AHEAD > 1 && n_mine > 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(AHEAD * PPW) : "memory");
+  else if (n_mine > 0) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PPW) : "memory");
+  else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  wg_barrier();
+
+  // addresses inside a tile (bytes): rows (l32, chunk 2 ks + hh), k-steps an XOR apart; transposed: four rows by four chunks, blocks of
+  // 32 columns an XOR apart, rows r + 8 another one
+  const unsigned row_at = (unsigned)(l32 * (D * 2) + ((hh ^ share_swz<D>(l32)) * 16));
+  unsigned tr_at;
+  {
+    const int j = lane & 15, cl = 2 * ((lane >> 4) & 1) + ((j & 3) >> 1), r0 = 4 * hh + (j >> 2);
+    tr_at = (unsigned)(r0 * (D * 2) + ((cl ^ share_swz<D>(r0)) * 16) + 8 * (j & 1));
+  }
+  bf16x8 qf[DK];
+  {
+    const unsigned base = lds_addr(q_tiles) + unit * TILE + row_at;
+    static_for<0, DK>([&](auto ks_c) __attribute__((always_inline)) {
+      constexpr int ks = decltype(ks_c)::value;
+      qf[ks] = lds_asm_read16<0>(base ^ (ks * 32));
+    });
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int ks = 0; ks < DK; ++ks) asm volatile("" : "+v"(qf[ks]));
+  }
+
+  const unsigned k_base = lds_addr(region) + row_at, v_base = lds_addr(region) + TILE + tr_at;
+  int slot = 0;
+  const int n_steps = HG == 1 ? n_mine : (nt + KS - 1) / KS;
+  for (int i = 0; i < n_steps; ++i) {
+    const int t = split + KS * i;
+    constexpr int LATER = HG == 1 ? NS - 1 : NS - 2;  // stages after this one that may be outstanding
+    if constexpr (HALVES) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PT) : "memory");  // (V may be outstanding)
+    else if (LATER > 0 && i + 1 < n_mine) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LATER * PPW) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if constexpr (HG > 1) {
+      wg_barrier();  // every wave's share of the stage has landed, and every wave is done with the stage before it
+      if (i + NS - 1 < n_mine) copy_stage(i + NS - 1, slot == 0 ? NS - 1 : slot - 1);
+      if (i >= n_mine) continue;
+    }
+    const unsigned ka = k_base + slot * (2 * TILE), va = v_base + slot * (2 * TILE);
+    // ---- S^T = K Q^T: [32 keys] x [32 queries] ----
+    bf16x8 kf[DK];
+    static_for<0, DK>([&](auto ks_c) __attribute__((always_inline)) {
+      constexpr int ks = decltype(ks_c)::value;
+      kf[ks] = lds_asm_read16<0>(ka ^ (ks * 32));
+    });
+    f32x16 s;
+    asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(DK / 2) : "memory");
+#pragma unroll
+    for (int ks = 0; ks < DK / 2; ++ks) asm volatile("" : "+v"(kf[ks]));
+#pragma unroll
+    for (int ks = 0; ks < DK / 2; ++ks) s = mfma32(kf[ks], qf[ks], ks == 0 ? zero16 : s);
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int ks = DK / 2; ks < DK; ++ks) asm volatile("" : "+v"(kf[ks]));
+    // the operands of O^T += V^T P^T arrive while the second half of the scores and the probabilities are computed
+    s16x4 v_lo[2][DB], v_hi[2][DB];
+    auto read_v = [&]() __attribute__((always_inline)) {
+      static_for<0, 2 * DB>([&](auto x_c) __attribute__((always_inline)) {
+        constexpr int ks = decltype(x_c)::value / DB, db = decltype(x_c)::value % DB;
+        v_lo[ks][db] = lds_asm_read_tr<ks * 16 * D * 2>(va ^ (db * 64));
+        v_hi[ks][db] = lds_asm_read_tr<(ks * 16 + 8) * D * 2>(va ^ (db * 64 + share_swz<D>(8) * 16));
+      });
+    };
+    if constexpr (HALVES) {
+      if (i + 1 < n_mine) copy_pieces(i + 1, 0, first, half);
+    } else {
+      read_v();
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = DK / 2; ks < DK; ++ks) s = mfma32(kf[ks], qf[ks], s);
+    if constexpr (HALVES) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (i + 1 < n_mine) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PT) : "memory");
+      else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      read_v();
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // ---- mask: key j of the stage is visible to row r iff 32 t + j < n0 + r ----
+    if (32 * t + 32 > it.n0) {
+      const int lim = it.n0 + l32 - 32 * t;
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        if (8 * (e >> 2) + 4 * hh + (e & 3) >= lim) s[e] = -INFINITY;
+    }
+    float mx = fmaxf(fmaxf(s[0], s[1]), s[2]);
+#pragma unroll
+    for (int e = 3; e < 15; e += 2) mx = fmaxf(fmaxf(mx, s[e]), s[e + 1]);
+    mx = max_halves(fmaxf(mx, s[15]));
+    // (the reference only has to keep exp2 in range, so it follows the maximum when that is 2^8 past it, as in fwd_kernel)
+    if (__builtin_expect(__any((mx - m_run) * c > limit), 0)) {
+      const float m_new = fmaxf(m_run, mx);
+      const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c);
+      l_run *= alpha;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) oacc[db][e] *= alpha;
+      m_run = m_new;
+    }
+    const float mc = m_run == kNoMax ? 0.f : m_run * c;  // (no key of the row seen yet: every score is -inf)
+    float w[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) w[e] = __builtin_amdgcn_exp2f(s[e] * c - mc);
+    bf16x8 pf[2];
+    pf[0] = pack8(w[0], w[1], w[2], w[3], w[4], w[5], w[6], w[7]);
+    pf[1] = pack8(w[8], w[9], w[10], w[11], w[12], w[13], w[14], w[15]);
+    float ps0 = 0.f, ps1 = 0.f;
+    if constexpr (D == 64) {  // (the sums are those of fwd_kernel at 64, of the pipelined kernel at 128)
+      bf16x2 ones;
+      ones[0] = (__bf16)1.0f; ones[1] = (__bf16)1.0f;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        ps0 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pf[j], pf[j], 0, 1), ones, ps0, false);
+        ps1 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pf[j], pf[j], 2, 3), ones, ps1, false);
+        ps0 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pf[j], pf[j], 4, 5), ones, ps0, false);
+        ps1 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pf[j], pf[j], 6, 7), ones, ps1, false);
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 16; e += 2) {
+        ps0 += w[e];
+        ps1 += w[e + 1];
+      }
+    }
+    l_run += ps0 + ps1;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int x = 0; x < 2 * DB; ++x) asm volatile("" : "+v"(v_lo[x / DB][x % DB]), "+v"(v_hi[x / DB][x % DB]));
+    if constexpr (HG == 1) {
+      if (i + NS < n_mine) {  // (every read of the slot has returned)
+        if constexpr (HALVES) copy_pieces(i + 1, 0, half, all);
+        else copy_stage(i + NS, slot);
+      }
+    }
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int db = 0; db < DB; ++db) {
+        const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(v_lo[ks][db], v_hi[ks][db], 0, 1, 2, 3, 4, 5, 6, 7));
+        oacc[db] = mfma32(a, pf[ks], oacc[db]);
+      }
+    if constexpr (NS > 1) slot = slot + 1 == NS ? 0 : slot + 1;
+  }
+
+  // ---- the splits' results in LDS, then put together: the waves of a head take a share of its columns each ----
+  wg_barrier();  // every wave has read its last stage (and its last copies have landed)
+  if (n_mine > 0) {
+    lds_f32* const out = (lds_f32*)smem + wave * (NQ * 256) + lane * 4;
+#pragma unroll
+    for (int x = 0; x < NQ; ++x)
+      *(__attribute__((address_space(3))) f32x4*)(out + x * 256) =
+          f32x4{oacc[x / 4][4 * (x % 4)], oacc[x / 4][4 * (x % 4) + 1], oacc[x / 4][4 * (x % 4) + 2], oacc[x / 4][4 * (x % 4) + 3]};
+    const float l = sum_halves(l_run);
+    if (hh == 0) *(__attribute__((address_space(3))) f32x2*)(ml + (wave * 32 + l32) * 2) = f32x2{m_run, l};
+  }
+  __syncthreads();
+  const int quarter0 = split * NQW, parts = min(nt, KS);
+  float m = kNoMax, l = 0.f;
+  for (int w = 0; w < parts; ++w) m = fmaxf(m, ml[((w * HG + unit) * 32 + l32) * 2]);
+  f32x4 o[NQW];
+#pragma unroll
+  for (int x = 0; x < NQW; ++x) o[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const lds_f32* const src = (const lds_f32*)smem + (unit * NQ + quarter0) * 256 + lane * 4;
+  for (int w = 0; w < parts; ++w) {
+    const lds_f32* const e = ml + ((w * HG + unit) * 32 + l32) * 2;
+    const float f = __builtin_amdgcn_exp2f((e[0] - m) * c);
+    l += e[1] * f;
+#pragma unroll
+    for (int x = 0; x < NQW; ++x) {
+      const f32x4 v = lds_load4f(src + w * (HG * NQ * 256) + x * 256);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) o[x][r] += v[r] * f;
+    }
+  }
+  if (l32 < it.q_rows) {
+    const float inv = 1.0f / l;
+    __bf16* const op = p.o + (int64_t)(it.q_row0 + l32) * q_stride + (int64_t)head * D + 4 * hh;
+#pragma unroll
+    for (int x = 0; x < NQW; ++x)
+      *reinterpret_cast<bf16x4*>(op + (quarter0 + x) * 8) = pack4(o[x][0] * inv, o[x][1] * inv, o[x][2] * inv, o[x][3] * inv);
+    if (split == 0 && hh == 0) p.lse[(int64_t)head * p.total_q + it.q_row0 + l32] = (m * c + log2f(l)) * 0.6931471805599453f;
+  }
+}
+
 // The dynamic-LDS limit of a kernel is raised once per process (thread-safe: a function-local static).
 template <class K>
 static hipError_t raise_smem_limit(K kernel, size_t smem) {
@@ -1316,8 +1614,24 @@ static hipError_t launch_fwd_pipe(const FwdArgs& a, const FwdLists& lists, hipSt
   return launch_fwd_items<D, false>(a, smem, stream);
 }
 
-hipError_t launch_fwd(const FwdParams& p, int head_dim, bool pipe, const FwdLists& lists, hipStream_t stream) {
+template <int D, int HG, int KS, int NS>
+static hipError_t launch_fwd_share(const FwdArgs& a, hipStream_t stream) {
+  constexpr size_t smem = share_smem<D, HG, KS, NS>();
+  static_assert(smem <= 160 * 1024);
+  static const hipError_t attr = raise_smem_limit(&fwd_share_kernel<D, HG, KS, NS>, smem);
+  if (attr != hipSuccess) return attr;
+  hipLaunchKernelGGL((fwd_share_kernel<D, HG, KS, NS>), dim3(a.num_blocks), dim3(HG * KS * 64), smem, stream, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_fwd(const FwdParams& p, int head_dim, FwdKind kind, const FwdLists& lists, hipStream_t stream) {
   const FwdArgs a = fwd_launch_args(p, lists);
+  if (kind == kFwdShare) {
+    const int heads = p.heads_per_wg;
+    if (head_dim == 64)
+      return heads == 4 ? launch_fwd_share<64, 4, 2, 3>(a, stream) : heads == 2 ? launch_fwd_share<64, 2, 4, 2>(a, stream) : launch_fwd_share<64, 1, 8, 2>(a, stream);
+    return heads == 4 ? launch_fwd_share<128, 4, 2, 3>(a, stream) : heads == 2 ? launch_fwd_share<128, 2, 4, 2>(a, stream) : launch_fwd_share<128, 1, 8, 1>(a, stream);
+  }
   if (head_dim == 256) {
     const size_t smem = (size_t)10 * 32 * 256 * 2;  // four slots of K, five of V, and one tile more for the staging
     static const hipError_t attr = raise_smem_limit(&fwd_wide_kernel, smem);
@@ -1325,7 +1639,7 @@ hipError_t launch_fwd(const FwdParams& p, int head_dim, bool pipe, const FwdList
     hipLaunchKernelGGL(fwd_wide_kernel, dim3(persistent_grid(a.num_blocks)), dim3(256), smem, stream, a);
     return hipGetLastError();
   }
-  if (!pipe) {
+  if (kind != kFwdPipe) {
     const size_t smem = (size_t)4 * 64 * 64 * 2;  // two K tiles, two V tiles
     static const hipError_t attr = raise_smem_limit(&fwd_kernel, smem);
     if (attr != hipSuccess) return attr;

@@ -36,6 +36,7 @@ struct FwdParams {
 // Kernel arguments with room for a short list of items behind the parameters: a small chunk's schedule then needs no place in device
 // memory and no launch or copy to get there.  (3.6 KB in all; 4 KB are documented for a launch.)
 constexpr int kInlineItems = 104;
+static_assert(kInlineItems >= kMaxSharedItems);
 constexpr size_t kInlineBlob = 3584;  // bytes of a schedule that travels as a kernel argument on its way to device memory
 struct FwdArgs {
   FwdParams p;
@@ -173,7 +174,9 @@ struct FwdLists {
 };
 // workgroups of the pipelined forward on a CU
 constexpr int fwd_per_cu(int head_dim) { return head_dim == 64 ? 2 : 1; }
-// head_dim 96 and 128, and 64 if `pipe`: the pipelined kernel (and the launch that puts cut walks together); 256: fwd_wide_kernel; else fwd_kernel.
-hipError_t launch_fwd(const FwdParams& p, int head_dim, bool pipe, const FwdLists& lists, hipStream_t stream);
+// kFwdPipe: the pipelined kernel (and the launch that puts cut walks together); kFwdShare: fwd_share_kernel (head_dim 64 and 128); kFwdPlain: fwd_kernel
+// at head_dim 64, fwd_wide_kernel at 256.
+enum FwdKind { kFwdPlain, kFwdPipe, kFwdShare };
+hipError_t launch_fwd(const FwdParams& p, int head_dim, FwdKind kind, const FwdLists& lists, hipStream_t stream);
 
 }  // namespace chunk_attn

@@ -379,6 +379,62 @@ void choose_cut(const CutKind (&kinds)[N], int cus, const int64_t (&max_parts)[N
 }
 }  // namespace
 
+// Times (us) of the two kinds of forward, least squares in the logarithm over 260 drawn chunks of up to 104 tiles of 32 rows (1 - 3000 queries, contexts
+// of up to 20000 keys, 4 - 64 heads), each measured with every choice: first + the larger of what the longest walk takes and what all workgroups
+// take together on the chip's slots.  Off by 5 - 13 % (root mean square); the choice they make was never slower than the
+// other kernel there, 1.65 (head_dim 64) and 1.68 (128) times as fast on average where the best choice of all would be 1.66 and 1.70.
+// Examples, other kernel -> one, two, four heads: head_dim 64, 1024 tokens, 8/8 heads, 16.9 -> 7.9; four sequences of 512, 256, 128 and 128,
+// 8/8, 10.6 -> 6.0, 32/8, 11.1 -> 15.8, 9.3, 10.5; 100 queries on 10100 keys, 32/8, 124 -> 40, 62, 110; head_dim 128, 203 queries on 1704 keys with
+// 611 packed tokens, 32/8, 30.1 -> 26.1, 21.6, 31.7; eight sequences of 128, 32/8, 14.4 -> 18.1, 12.8, 9.7; 200 queries on 20200 keys, 32/8,
+// 90 -> 123, 192, 293 (walks cut over the whole chip).
+constexpr int kLongSharedWalk = 40;
+struct SharedCost {
+  double first, step, all_steps, workgroup, longest;  // first + max(step longest, all_steps steps + workgroup count + longest longest)
+  int slots;                                          // workgroups on the chip at a time
+};
+constexpr SharedCost kShared64[3] = {{3.2, 0.94, 1.17, 1.55, 0.13, 256}, {3.7, 0.74, 1.04, 2.58, 0.41, 512}, {4.1, 0.67, 0.70, 3.23, 0.45, 512}};
+constexpr SharedCost kShared128[3] = {{4.0, 1.45, 1.94, 1.89, 0.0, 256}, {4.6, 1.17, 1.45, 2.47, 0.09, 256}, {5.9, 0.91, 1.12, 3.69, 0.06, 256}};
+
+int choose_shared_heads(const chunk_attn_desc* d, const Walks& other, int inner, bool pipelined, bool cut) {
+  if (!(d->head_dim == 128 && pipelined) && !(d->head_dim == 64 && !pipelined)) return 0;
+  // (long walks that are not cut: enough blocks for the chip, and the pipelined kernel's steps are cheaper.  Walks of 40 - 73 stages gained 0 - 21 %
+  // in the chunks drawn, shorter ones 17 - 170 %)
+  if (d->head_dim == 128 && !cut && other.longest > kLongSharedWalk) return 0;
+  int64_t items = 0;
+  for (int t = 0; t < d->num_segments; ++t) {
+    items += (d->segments[t].q_len + 31) / 32;
+    if (items > kMaxSharedItems) return 0;
+  }
+  const double longest = (double)other.longest, all = (double)other.stages * inner / 256, blocks = (double)other.items * inner / 256;
+  // head_dim 64: the unpipelined kernel.  128: the pipelined one, whose walks are cut into pieces that even out
+  const double other_us = d->head_dim == 64 ? 3.85 + std::max(0.37 * longest, 0.12 * all + 1.36 * blocks + 0.36 * longest)
+                                            : 7.5 + std::max(all, std::min(longest, 8.0)) + 7.4 * blocks + 0.19 * std::min(longest, 103.0);
+  const int group = d->num_q_heads / d->num_kv_heads;
+  int best = 0;
+  double best_us = 0.95 * other_us;
+  for (int x = 0; x < 3; ++x) {
+    const int heads = 1 << x, splits = kSharedWaves / heads;
+    if (group % heads != 0) break;
+    int64_t steps = 0, most = 0;
+    for (int t = 0; t < d->num_segments; ++t) {
+      const chunk_attn_seg& s = d->segments[t];
+      for (int i0 = 0; i0 < s.q_len; i0 += 32) {
+        const int64_t n = (walk_stages(s.kv_len - s.q_len + i0 + 1, std::min(32, s.q_len - i0)) + splits - 1) / splits;
+        steps += n;
+        most = std::max(most, n);
+      }
+    }
+    const SharedCost& c = d->head_dim == 64 ? kShared64[x] : kShared128[x];
+    const double per_slot = (double)(d->num_q_heads / heads) / c.slots;
+    const double us = c.first + std::max(c.step * most, c.all_steps * steps * per_slot + c.workgroup * items * per_slot + c.longest * most);
+    if (us < best_us) {
+      best_us = us;
+      best = heads;
+    }
+  }
+  return best;
+}
+
 KeySplit choose_key_split(const chunk_attn_desc* d, int tile_rows, int inner, int cus, int64_t max_parts) {
   if (many_blocks(d, false, tile_rows, inner)) return KeySplit{};
   const CutKind kinds[1] = {key_walks(d, tile_rows, inner)};

@@ -138,6 +138,11 @@ struct Walks {
   int64_t largest = 0;  // items of the sequence that has most
 };
 Walks count_walks(const chunk_attn_desc* d, int tile_rows);
+// Query heads that a workgroup of the forward takes whose waves divide the keys of 32 rows (8 waves: 1, 2 or 4 heads, and as many of them per
+// head as are left), where that ends sooner by the estimate of plan.cpp than the head dimension's other kernel, whose walks are `other`, each
+// run for `inner` (key/value head, head split) pairs, on the software-pipelined kernel or not, cut into pieces or not; 0 where it does not.
+constexpr int kSharedWaves = 8, kMaxSharedItems = 104;  // (as many items as kernel arguments have room for)
+int choose_shared_heads(const chunk_attn_desc* d, const Walks& other, int inner, bool pipelined, bool cut);
 // The same for the key-stationary items (`keys` keys each) of one key/value head; a stage is a 32-row query tile of one head.
 Walks count_dkv_walks(const chunk_attn_desc* d, int keys);
 struct KeySplit {

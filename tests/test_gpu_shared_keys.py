@@ -1,0 +1,75 @@
+"""Small chunks whose forward divides the keys of 32 query rows among the waves of a workgroup (head dimensions 64 and 128), at the edges of tiles,
+stages and shares: against the fp64 oracle (2e-2 for O as everywhere; LSE: 1.1e-4 at 128, a float32 sum of unrounded probabilities, and
+2^-9 + 1e-4 at 64, where they are summed as rounded to bf16), the static forward bit for bit, and the same bits on a second run.  Every
+case asserts how many heads share a workgroup."""
+import pytest
+import torch
+
+import paper_2509_21275_amd as ca
+import synth
+from gpu_util import TOL_O, make_inputs, rel_err, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+CASES = [  # head dimension, segments, query heads, key/value heads, heads per workgroup
+    (64, [(0, 1, 0, 65)], 1, 1, 1),
+    (64, [(0, 33, 0, 33)], 8, 8, 1),                                          # a second tile of one row, two stages for eight waves
+    (64, [(0, 256, 3, 256), (256, 257, 260, 257), (513, 31, 520, 288)], 8, 8, 1),
+    (64, [(0, 100, 0, 3000)], 32, 8, 1),
+    (64, [(0, 65, 0, 513), (65, 64, 513, 576), (129, 1, 1089, 545)], 32, 8, 1),
+    (64, [(0, 700, 2, 700), (700, 33, 705, 400)], 32, 8, 2),
+    (64, [(0, 673, 0, 748), (673, 34, 748, 34), (707, 112, 782, 112)], 64, 8, 4),
+    (128, [(0, 1, 0, 1)], 1, 1, 1),
+    (128, [(0, 1, 0, 1100)], 8, 2, 1),
+    (128, [(0, 257, 0, 2000)], 3, 3, 1),
+    (128, [(0, 64, 0, 1024), (64, 65, 1024, 1089)], 16, 2, 1),
+    (128, [(0, 203, 0, 1704), (203, 211, 1704, 211), (414, 120, 1915, 120)], 32, 8, 2),
+    (128, [(0, 500, 3, 500)], 32, 8, 2),
+    (128, [(65 * i, 65, 65 * i, 65) for i in range(12)], 32, 8, 4),
+    (128, [(0, 1175, 0, 1175)], 32, 8, 4),
+]
+
+
+def _case(d, segs, hq, hk):
+    tq, tkv = max(s[0] + s[1] for s in segs), max(s[2] + s[3] for s in segs) + 3
+    return synth.ChunkCase("shared", [synth.Seg(*s) for s in segs], tq, tkv, hq, hk, d, 300 + len(segs) + hq)
+
+
+def _check(oracle_mod, case, q, k, v, o, lse):
+    O, LSE = oracle_mod.Oracle(case.segs, q.cpu(), k.cpu(), v.cpu(), None, case.scale).forward()
+    assert rel_err(o, O) <= TOL_O
+    assert float(abs(lse.double().cpu().numpy() - LSE).max()) <= (2.0 ** -9 + 1e-4 if case.head_dim == 64 else 1.1e-4)
+
+
+def _desc(case):
+    return ca.make_desc(case.segs, case.num_q_heads, case.num_kv_heads, case.head_dim, case.total_q, case.total_kv, case.scale)
+
+
+@pytest.mark.parametrize("d,segs,hq,hk,heads", CASES)
+def test_shared_keys(oracle_mod, d, segs, hq, hk, heads):
+    case = _case(d, segs, hq, hk)
+    assert ca.chunk_attn_test_shared_heads(_desc(case)) == heads
+    q, k, v, _ = make_inputs(case)
+    o, lse = run_gpu(case, q, k, v, backward=False)
+    again = run_gpu(case, q, k, v, backward=False)
+    assert torch.equal(o, again[0]) and torch.equal(lse, again[1])
+    _check(oracle_mod, case, q, k, v, o, lse)
+    o2, lse2 = torch.full_like(o, float("nan")), torch.full_like(lse, float("nan"))
+    ca.chunk_attn_fwd_static(_desc(case), q, k, v, o2, lse2)
+    torch.cuda.synchronize()
+    assert torch.equal(o, o2) and torch.equal(lse, lse2)
+
+
+@pytest.mark.parametrize("d,hq,hk", [(64, 8, 8), (64, 32, 8), (128, 8, 8), (128, 32, 8)])
+def test_shares_of_very_different_scores(oracle_mod, d, hq, hk):
+    """Scores grow by some hundred nats along the keys, so the references of the shares lie far apart and move many times."""
+    n = 450
+    case = _case(d, [(0, n, 0, n)], hq, hk)
+    assert ca.chunk_attn_test_shared_heads(_desc(case)) > 0
+    q, k, v, _ = make_inputs(case)
+    ramp = torch.zeros(k.shape[0], device=q.device)
+    ramp[:n] = torch.linspace(-2.0, 2.0, n, device=q.device)
+    q = torch.full_like(q, 4.0)
+    k = (k.float() * 0.05 + ramp.view(-1, 1, 1)).to(torch.bfloat16)
+    o, lse = run_gpu(case, q, k, v, backward=False)
+    _check(oracle_mod, case, q, k, v, o, lse)
