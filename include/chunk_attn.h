@@ -255,6 +255,9 @@ int chunk_attn_test_routes(const chunk_attn_desc* desc, int32_t* routes);
 /* Test hook (host only): query heads per workgroup where the forward of a small chunk divides the keys of 32 rows among the waves of a
  * workgroup (1, 2 or 4; the routes above are then those of a workspace too small for the reported size), else 0. */
 int chunk_attn_test_shared_heads(const chunk_attn_desc* desc, int32_t* heads);
+/* Test hook (host only): waves per workgroup where the backward of a small chunk divides its walks among the waves of a workgroup, in one
+ * launch (4 or 8), else 0. */
+int chunk_attn_test_shared_waves(const chunk_attn_desc* desc, int32_t* waves);
 
 /* Static description of an error code; for CHUNK_ATTN_HIP_ERROR includes the last HIP error text. */
 const char* chunk_attn_strerror(int code);

@@ -286,6 +286,15 @@ def chunk_attn_test_shared_heads(desc) -> int:
     return out.value
 
 
+def chunk_attn_test_shared_waves(desc) -> int:
+    """Test hook: waves per workgroup of the small chunks' backward, 0 where the other kernels run (host only)."""
+    out = ctypes.c_int32(0)
+    rc = _lib.chunk_attn_test_shared_waves(ctypes.byref(desc), ctypes.byref(out))
+    if rc != 0:
+        raise ChunkAttnError(rc)
+    return out.value
+
+
 def chunk_attn_test_bwd_status(desc, workspace) -> int:
     """Test hook: the status word the one-pass backward left in `workspace` (synchronises the device)."""
     import torch

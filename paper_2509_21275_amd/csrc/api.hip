@@ -465,6 +465,9 @@ FwdParams fwd_params(const chunk_attn_desc* desc, const FwdLayout& L, char* ws, 
   p.ref_limit = g_fwd_rescale_limit.load();
   return p;
 }
+// (the kernels of the small chunks' backward have no instantiation for head_dim 96; the test hook's other modes ask for particular kernels)
+bool may_share(const chunk_attn_desc* desc) { return !is_narrow(desc) && bwd_mode() == 0; }
+
 FwdKind fwd_kind(const FwdLayout& L) { return L.share > 0 ? kFwdShare : L.pipe ? kFwdPipe : kFwdPlain; }
 FwdLists fwd_lists(const FwdLayout& L) {
   FwdLists l;
@@ -559,6 +562,17 @@ int chunk_attn_test_shared_heads(const chunk_attn_desc* desc, int32_t* heads) {
   FwdLayout L;
   layout_fwd(desc, L, false);
   *heads = L.share;
+  return CHUNK_ATTN_OK;
+}
+
+int chunk_attn_test_shared_waves(const chunk_attn_desc* desc, int32_t* waves) {
+  const int rc = validate(desc);
+  if (rc != CHUNK_ATTN_OK) return rc;
+  if (!waves) return CHUNK_ATTN_INVALID_ARG;
+  const chunk_attn_desc w = widened(desc);
+  BwdPlan P;
+  bwd_layout(&w, P, false, kCutFine, may_share(desc));
+  *waves = P.share_waves;
   return CHUNK_ATTN_OK;
 }
 
@@ -692,7 +706,7 @@ int bwd_any(const chunk_attn_desc* desc, const void* q, const void* k, const voi
   const chunk_attn_desc w = widened(desc);
   BwdPlan P;
   auto needed = [&]() { return is_narrow(desc) ? narrow_bwd_layout(desc, P.total).total : P.total; };
-  bwd_layout(&w, P, true);
+  bwd_layout(&w, P, true, kCutFine, may_share(desc));
   if (workspace_bytes < needed()) bwd_layout(&w, P, true, kCutInPlace);  // too small for all partial results: fewer pieces, or
   if (workspace_bytes < needed()) bwd_layout(&w, P, true, kCutNone);     // none
   if (workspace_bytes < needed()) return CHUNK_ATTN_WORKSPACE_TOO_SMALL;
@@ -734,8 +748,9 @@ int bwd_any(const chunk_attn_desc* desc, const void* q, const void* k, const voi
   a.accumulate = accumulate_dkv != 0;
   a.dkv_f32 = dkv_f32;
   a.workspace = static_cast<char*>(workspace);
-  const std::vector<char> blob = bwd_blob(P);
   hipError_t e = hipSuccess;
+  if (P.share_waves > 0) return (e = launch_bwd_share(desc, a, P.share_waves, stream)) == hipSuccess ? CHUNK_ATTN_OK : hip_fail(e, "backward launch");
+  const std::vector<char> blob = bwd_blob(P);
   if (blob.size() > kInlineBlob && (e = g_ring.upload(a.workspace, blob.data(), blob.size(), stream)) != hipSuccess)
     return hip_fail(e, "schedule upload");
   e = launch_bwd(desc, a, P, blob, stream);  // (its pre-pass brings a smaller one along)

@@ -3129,17 +3129,7 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
     hipLaunchKernelGGL((bwd_pre_kernel<D>), dim3((unsigned)blocks), dim3(256), 0, stream, p);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  if (!a.accumulate) {  // rows no segment covers receive no gradient
-    for (const auto& gap : uncovered_kv_ranges(d)) {
-      const int esz = a.dkv_f32 ? 4 : 2;  // bytes per element of dK / dV
-      const int64_t n16 = (int64_t)(gap.second - gap.first) * d->num_kv_heads * D * esz / 16;
-      for (__bf16* base : {a.dk, a.dv}) {
-        u32x4* ptr = reinterpret_cast<u32x4*>(reinterpret_cast<char*>(base) + (int64_t)gap.first * d->num_kv_heads * D * esz);
-        hipLaunchKernelGGL(zero_fill_kernel, dim3((unsigned)((n16 + 255) / 256)), dim3(256), 0, stream, ptr, n16);
-      }
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-  }
+  if ((e = zero_uncovered(d, a, stream)) != hipSuccess) return e;
 
   const int group = d->num_q_heads / d->num_kv_heads;
   if constexpr (D == 128) {
@@ -3307,7 +3297,21 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
 
 }  // namespace
 
-void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, Cut cut) {
+hipError_t zero_uncovered(const chunk_attn_desc* d, const BwdArgs& a, hipStream_t stream) {
+  if (a.accumulate) return hipSuccess;
+  for (const auto& gap : uncovered_kv_ranges(d)) {
+    const int64_t row = (int64_t)d->num_kv_heads * d->head_dim * (a.dkv_f32 ? 4 : 2);  // bytes
+    const int64_t n16 = (gap.second - gap.first) * row / 16;
+    for (__bf16* base : {a.dk, a.dv})
+      hipLaunchKernelGGL(zero_fill_kernel, dim3((unsigned)((n16 + 255) / 256)), dim3(256), 0, stream,
+                         reinterpret_cast<u32x4*>(reinterpret_cast<char*>(base) + gap.first * row), n16);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, Cut cut, bool may_share) {
   P = BwdPlan{};
   const int group = d->num_q_heads / d->num_kv_heads;
   const bool pipe = d->head_dim == 128;
@@ -3339,7 +3343,10 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, Cut cut) {
   }
   if (!pipe && !P.dkv_pipe && cut == kCutFine)
     P.dkv_split = choose_tile_split(d, dkv_keys(d->head_dim), kCus, kMaxShortParts / d->num_kv_heads);
-  if (with_plan) {
+  if (may_share && (pipe || (d->head_dim == 64 && !P.dq_pipe)))
+    P.share_waves = choose_shared_waves(d, count_walks(d, dq_rows), d->num_kv_heads * (group / heads_per_wg(group, P.dq_waves)),
+                                        count_dkv_walks(d, dkv_keys(d->head_dim)), P.split.target > 0 || P.dkv_split.target > 0);
+  if (with_plan && P.share_waves == 0) {
     if (P.fused) {
       P.fplan = plan_fused(d, dkv_keys(d->head_dim), kNumXcd, fused_num_bufs(d, dkv_keys(d->head_dim)));
     } else {

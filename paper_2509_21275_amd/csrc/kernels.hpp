@@ -137,6 +137,7 @@ struct BwdPlan {
   int dq_waves = 0;                        // 32-row units of a dQ workgroup
   bool dq_first = false;                   // both kinds in one launch: the dQ blocks start before the dK/dV blocks
   bool dkv_in_step = false;                // head_dim 96 and 128: long dK/dV walks start in groups (dkv_pipe_blocks)
+  int share_waves = 0;                     // > 0: launch_bwd_share runs instead, with so many waves per workgroup
   bool in_turn = false;                    // head_dim 96 and 128: a launch per kind, whose partial results take the same place
   // one-pass backward (head_dim 128): its items and workgroup order travel at the end of the blob; then the per-wave
   // progress counters and the status word (cleared by a kernel on every call) and the float32 dQ tiles
@@ -159,9 +160,14 @@ hipError_t launch_bwd_fused(const chunk_attn_desc* d, const BwdArgs& a, const Bw
 // Fills the offsets (and, if with_plan, the schedules) for a validated descriptor.  kCutInPlace: only where the partial results of each kind fit
 // the room that head_dim 96 and 128 keep for dQ tiles anyway (workspaces of that size may be known to callers); kCutNone: no walk is cut.
 enum Cut { kCutNone, kCutInPlace, kCutFine };
-void bwd_layout(const chunk_attn_desc* d, BwdPlan& plan, bool with_plan, Cut cut = kCutFine);
+// may_share: the kernel of the small chunks may run (share_waves > 0), which needs no schedule; the sizes are the other kernels' either way.
+void bwd_layout(const chunk_attn_desc* d, BwdPlan& plan, bool with_plan, Cut cut = kCutFine, bool may_share = false);
 // The host image of the blob at the start of the workspace.
 std::vector<char> bwd_blob(const BwdPlan& plan);
+// Zeroes the rows of dK and dV that no segment covers, unless the call accumulates.
+hipError_t zero_uncovered(const chunk_attn_desc* d, const BwdArgs& a, hipStream_t stream);
+// The backward of a small chunk in one launch that needs no workspace, `waves` waves per workgroup (choose_shared_waves).
+hipError_t launch_bwd_share(const chunk_attn_desc* d, const BwdArgs& a, int waves, hipStream_t stream);
 // Enqueues the backward kernels.  A blob of more than kInlineBlob bytes must already be on its way to the workspace on `stream`.
 hipError_t launch_bwd(const chunk_attn_desc* d, const BwdArgs& a, const BwdPlan& plan, const std::vector<char>& blob, hipStream_t stream);
 

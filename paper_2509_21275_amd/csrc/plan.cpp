@@ -135,6 +135,19 @@ Walks count_walks(const chunk_attn_desc* d, int tile_rows) {
   return w;
 }
 
+std::vector<ShareBlock> share_blocks(const chunk_attn_desc* d, bool keys) {
+  std::vector<ShareBlock> out;
+  const int group = d->num_q_heads / d->num_kv_heads;
+  for (int t = 0; t < d->num_segments; ++t) {
+    const chunk_attn_seg& s = d->segments[t];
+    const int32_t C = s.kv_len - s.q_len, n_qt = (s.q_len + 31) / 32;
+    for (int32_t x = 0; 32 * x < (keys ? s.kv_len : s.q_len); ++x)
+      out.push_back({t, x, keys ? (int64_t)(n_qt - std::max(0, 32 * x - C) / 32) * group : walk_stages(C + 32 * x + 1, std::min(32, s.q_len - 32 * x))});
+  }
+  std::stable_sort(out.begin(), out.end(), [](const ShareBlock& a, const ShareBlock& b) { return a.steps > b.steps; });
+  return out;
+}
+
 Walks count_dkv_walks(const chunk_attn_desc* d, int keys) {
   Walks w;
   const int group = d->num_q_heads / d->num_kv_heads;
@@ -430,6 +443,71 @@ int choose_shared_heads(const chunk_attn_desc* d, const Walks& other, int inner,
     if (us < best_us) {
       best_us = us;
       best = heads;
+    }
+  }
+  return best;
+}
+
+// The same for the backward (us; 950 drawn chunks, the bounds of this function aside): first + the larger of what the longest dQ walk, the longest
+// dK/dV walk and all workgroups together take.  Off by 5 - 9 % (root mean square); chosen where it is 14 % ahead by the estimate: slower in 2 of
+// 720 chunks, by 6 % at most, and 1.96 (head_dim 64) and 1.40 (128) times as fast on average over all, where the best choice would be 1.98 and 1.40.
+// Examples, other kernels -> four, eight waves: head_dim 64, 596 tokens, 8/8 heads, 21.0 -> 11.9, 11.1; 117 queries, 4/1, on up to 5600 keys,
+// 92 -> 28, 23; 2205 tokens in 32 sequences, 32/8, 38 -> 37, 57; 2537 tokens, 64/8, 156 -> 203, 221; head_dim 128, 150 tokens, 32/8, 36.9 -> 19.1;
+// 764 tokens, 8/8, 50 -> 34; 1454 tokens, 32/8, 83 -> 112.
+struct SharedBwdCost {
+  double first, dq_step, dkv_step, all_dq, all_dkv, workgroup, longest;
+  int waves, slots;
+  double us(double dq_most, double dkv_most, double dq_all, double dkv_all, double blocks) const {
+    return first + std::max({dq_step * dq_most, dkv_step * dkv_most,
+                             (all_dq * dq_all + all_dkv * dkv_all + workgroup * blocks) / slots + longest * std::max(dq_most, dkv_most)});
+  }
+};
+constexpr SharedBwdCost kSharedBwd64[2] = {{4.4, 0.58, 1.42, 2.15, 0.61, 2.5, 0.17, 4, 512}, {4.0, 0.84, 2.14, 1.88, 1.22, 2.1, 0.25, 8, 256}};
+constexpr SharedBwdCost kSharedBwd128 = {6.0, 1.0, 2.5, 2.2, 1.5, 3.9, 0.1, 4, 256};
+
+int choose_shared_waves(const chunk_attn_desc* d, const Walks& dq, int inner, const Walks& dkv, bool cut) {
+  if (d->num_segments > kMaxShareSegs) return 0;
+  int64_t items = 0;
+  for (int t = 0; t < d->num_segments; ++t) {
+    items += (d->segments[t].q_len + 31) / 32 + ((int64_t)d->segments[t].kv_len + 31) / 32;
+    if (items > kMaxShareItems) return 0;
+  }
+  const double DL = (double)dq.longest, KL = (double)dkv.longest, DT = (double)dq.stages * inner / 256, KT = (double)dkv.stages * d->num_kv_heads / 256;
+  const double blocks = (double)(dq.items * inner + dkv.items * d->num_kv_heads) / 256;
+  double other;
+  if (d->head_dim == 64) {
+    // (long dK/dV walks are cut evenly already; dQ walks are not)
+    if (cut && dq.longest <= dkv.longest && dkv.longest > 32) return 0;
+    other = cut ? 16.6 + 1.08 * std::min(KL, 16.4) + 0.31 * KT + 0.46 * DL
+                : 7.1 + std::max({0.49 * DL, 0.73 * KL, 0.73 * KT + 2.4 * blocks + 0.41 * std::max(DL, KL)});
+  } else {
+    if (!cut && dq.longest > kLongSharedWalk) return 0;  // (as in the forward)
+    other = cut ? 18.6 + 0.22 * std::min(DL, 56.0) + 0.39 * std::min(KL, 36.0) + DT + 0.94 * KT + 10.8 * blocks + 0.016 * DL
+                : 17.0 + std::max({0.71 * DL, 0.95 * KL, 2.68 * DT + 1.06 * KT + 11.4 * blocks + 0.03 * std::max(DL, KL)});
+  }
+  const int group = d->num_q_heads / d->num_kv_heads;
+  int best = 0;
+  double best_us = 0.86 * other;
+  for (int x = 0; x < (d->head_dim == 64 ? 2 : 1); ++x) {
+    const SharedBwdCost& c = d->head_dim == 64 ? kSharedBwd64[x] : kSharedBwd128;
+    int64_t dq_most = 0, dkv_most = 0, dq_all = 0, dkv_all = 0, dq_items = 0, dkv_items = 0;
+    auto add = [&](int64_t steps, int64_t& items_of_kind, int64_t& most, int64_t& all) {
+      ++items_of_kind;
+      steps = (steps + c.waves - 1) / c.waves;
+      most = std::max(most, steps);
+      all += steps;
+    };
+    for (int t = 0; t < d->num_segments; ++t) {
+      const chunk_attn_seg& s = d->segments[t];
+      const int32_t C = s.kv_len - s.q_len, n_qt = (s.q_len + 31) / 32;
+      for (int32_t i0 = 0; i0 < s.q_len; i0 += 32) add(walk_stages(C + i0 + 1, std::min(32, s.q_len - i0)), dq_items, dq_most, dq_all);
+      for (int32_t j0 = 0; j0 < s.kv_len; j0 += 32) add((int64_t)(n_qt - std::max(0, j0 - C) / 32) * group, dkv_items, dkv_most, dkv_all);
+    }
+    const double us = c.us((double)dq_most, (double)dkv_most, (double)dq_all * d->num_q_heads, (double)dkv_all * d->num_kv_heads,
+                           (double)(dq_items * d->num_q_heads + dkv_items * d->num_kv_heads));
+    if (us < best_us) {
+      best_us = us;
+      best = c.waves;
     }
   }
   return best;

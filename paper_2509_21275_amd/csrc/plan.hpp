@@ -143,6 +143,17 @@ Walks count_walks(const chunk_attn_desc* d, int tile_rows);
 // run for `inner` (key/value head, head split) pairs, on the software-pipelined kernel or not, cut into pieces or not; 0 where it does not.
 constexpr int kSharedWaves = 8, kMaxSharedItems = 104;  // (as many items as kernel arguments have room for)
 int choose_shared_heads(const chunk_attn_desc* d, const Walks& other, int inner, bool pipelined, bool cut);
+// Blocks of the small chunks' backward: tiles of 32 rows of a segment's queries, or of its keys, and the steps of their walks, longest first.
+struct ShareBlock {
+  int32_t seg, tile;
+  int64_t steps;  // 32-key stages, or (32-query tile, head) pairs
+};
+constexpr int kMaxShareSegs = 64, kMaxShareItems = 640;
+std::vector<ShareBlock> share_blocks(const chunk_attn_desc* d, bool keys);
+// Waves per workgroup (4, or 8 at head_dim 64) of the backward whose waves divide the walks of 32-row blocks, where it ends sooner by the
+// estimate of plan.cpp than the head dimension's other kernels, whose walks are `dq` (each run for `inner` pairs) and `dkv` (for each
+// key/value head), some of them cut or none; 0 where it does not.
+int choose_shared_waves(const chunk_attn_desc* d, const Walks& dq, int inner, const Walks& dkv, bool cut);
 // The same for the key-stationary items (`keys` keys each) of one key/value head; a stage is a 32-row query tile of one head.
 Walks count_dkv_walks(const chunk_attn_desc* d, int keys);
 struct KeySplit {

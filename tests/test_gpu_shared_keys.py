@@ -1,4 +1,4 @@
-"""Small chunks whose forward divides the keys of 32 query rows among the waves of a workgroup (head dimensions 64 and 128), at the edges of tiles,
+"""Small chunks whose forward and backward divide the walks of 32 rows among the waves of a workgroup (head dimensions 64 and 128), at the edges of tiles,
 stages and shares: against the fp64 oracle (2e-2 for O as everywhere; LSE: 1.1e-4 at 128, a float32 sum of unrounded probabilities, and
 2^-9 + 1e-4 at 64, where they are summed as rounded to bf16), the static forward bit for bit, and the same bits on a second run.  Every
 case asserts how many heads share a workgroup."""
@@ -7,7 +7,7 @@ import torch
 
 import paper_2509_21275_amd as ca
 import synth
-from gpu_util import TOL_O, make_inputs, rel_err, run_gpu
+from gpu_util import TOL_GRAD, TOL_O, make_inputs, rel_err, run_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -73,3 +73,53 @@ def test_shares_of_very_different_scores(oracle_mod, d, hq, hk):
     k = (k.float() * 0.05 + ramp.view(-1, 1, 1)).to(torch.bfloat16)
     o, lse = run_gpu(case, q, k, v, backward=False)
     _check(oracle_mod, case, q, k, v, o, lse)
+
+
+BWD_CASES = [  # head dimension, segments, query heads, key/value heads, waves per workgroup
+    (64, [(0, 1, 0, 40)], 1, 1, 4),
+    (64, [(0, 33, 0, 33)], 8, 8, 4),
+    (64, [(0, 256, 3, 256), (256, 257, 260, 257), (513, 31, 520, 288)], 8, 8, 4),
+    (64, [(0, 596, 0, 596)], 8, 8, 8),
+    (64, [(0, 117, 0, 5600)], 4, 1, 8),
+    (64, [(0, 365, 2, 513), (365, 64, 515, 576), (429, 1, 1091, 545)], 16, 8, 4),
+    (64, [(97 * i, 97, 97 * i, 97) for i in range(10)], 8, 2, 4),
+    (64, [(0, 31, 0, 1000), (31, 95, 1003, 127)], 6, 2, 8),
+    (128, [(0, 1, 0, 40)], 1, 1, 4),
+    (128, [(0, 33, 0, 65)], 3, 3, 4),
+    (128, [(0, 257, 3, 257), (257, 31, 260, 288)], 8, 8, 4),
+    (128, [(0, 65, 0, 513), (65, 64, 515, 576)], 8, 2, 4),
+    (128, [(0, 150, 2, 150)], 32, 8, 4),
+    (128, [(0, 764, 0, 764)], 8, 8, 4),
+]
+
+
+@pytest.mark.parametrize("f32kv,accumulate", [(False, False), (False, True), (True, False), (True, True)])
+@pytest.mark.parametrize("d,segs,hq,hk,waves", BWD_CASES)
+def test_shared_walks_of_the_backward(oracle_mod, d, segs, hq, hk, waves, f32kv, accumulate):
+    """5e-2 of the oracle as everywhere, the same bits on a second run, rows outside every key range as they were or zero, and the other kernels'
+    results up to one bf16 rounding either way (2^-7).  (One query of many keys: with one or two, dS is a small difference of rounded values.)"""
+    case = _case(d, segs, hq, hk)
+    assert ca.chunk_attn_test_shared_waves(_desc(case)) == waves
+    q, k, v, do = make_inputs(case)
+    init = torch.full(k.shape, 3.0, device=q.device, dtype=torch.float32 if f32kv else torch.bfloat16)
+    run = lambda: run_gpu(case, q, k, v, do, accumulate=accumulate, dk_init=init, dv_init=init, f32kv=f32kv)
+    got, again = run(), run()
+    assert all(torch.equal(a, b) for a, b in zip(got, again))
+    cov = torch.zeros(case.total_kv, dtype=torch.bool)
+    for s in segs:
+        cov[s[2]:s[2] + s[3]] = True
+    old = 3.0 if accumulate else 0.0
+    orc = oracle_mod.Oracle(case.segs, q.cpu(), k.cpu(), v.cpu(), do.cpu(), case.scale)
+    orc.forward()
+    dQ, dK, dV = orc.backward()
+    assert rel_err(got[2], dQ) <= TOL_GRAD
+    for g, w in ((got[3], dK), (got[4], dV)):
+        assert torch.all(g.cpu()[~cov] == old) and rel_err(g.cpu()[cov], w[cov.numpy()] + old) <= TOL_GRAD
+    ca.chunk_attn_test_set_bwd_mode(1)
+    try:
+        assert ca.chunk_attn_test_shared_waves(_desc(case)) == 0
+        other = run()
+    finally:
+        ca.chunk_attn_test_set_bwd_mode(0)
+    for a, b in zip(got[2:], other[2:]):
+        assert rel_err(a, b.double().cpu().numpy()) <= 2.0 ** -7
