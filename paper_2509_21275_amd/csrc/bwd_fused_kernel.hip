@@ -169,7 +169,6 @@ __global__ __launch_bounds__(256, 1) void bwd_fused_pipe_kernel(FusedParams p) {
   constexpr int R_OFF = S_OFF + 2 * DS;    // [NS][RV] floats LSE rows, then [NS][RV] floats D rows
   lds_f32* const lse_s = (lds_f32*)(L + R_OFF);
   lds_f32* const dsum_s = lse_s + NS * RV;
-  constexpr int LDS_ELEMS = R_OFF + 2 * NS * RV * 2;  // in bf16 units
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -209,7 +208,11 @@ __global__ __launch_bounds__(256, 1) void bwd_fused_pipe_kernel(FusedParams p) {
       lds_store8(L + Q_OFF + DIST * QT + x * 8, z);
       lds_store8(L + G_OFF + DIST * QT + x * 8, z);
     }
-    for (int x = tid; x < (LDS_ELEMS - P_OFF) / 8; x += NW * 64) lds_store8(L + P_OFF + x * 8, z);
+    for (int x = tid; x < (R_OFF - P_OFF) / 8; x += NW * 64) lds_store8(L + P_OFF + x * 8, z);
+    // (row values of stages DIST .. NS - 1 only: a store to the first ones' by a wave that comes late would undo another wave's copy)
+    constexpr int ROWS = (NS - DIST) * RV * 2, ALL = NS * RV * 2;  // bf16 units of one set of row values
+    static_assert(2 * ROWS / 8 <= NW * 64);
+    if (tid < 2 * ROWS / 8) lds_store8(L + R_OFF + DIST * RV * 2 + (tid < ROWS / 8 ? tid * 8 : ALL - ROWS + tid * 8), z);
   }
 
   const int nqt = it.n_qt - it.qt_first;
