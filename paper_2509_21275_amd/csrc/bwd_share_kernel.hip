@@ -12,10 +12,12 @@
 // Tiles are rows, chunk c of row r at c ^ tile_swz(r) (as in fwd_share_kernel).
 //
 // Why: such a chunk's backward was three or four launches one after the other (pre-pass 4 us, dQ and dK/dV blocks, merge of cut walks 5 us), each
-// a serial chain of stages on few compute units.  Backward before -> now, us: head_dim 64, 596 tokens, 8/8 heads, 21.0 -> 11.1; 117 queries, 4/1,
-// on up to 5600 keys, 92 -> 23; head_dim 128, 150 tokens, 32/8, 36.9 -> 19.1; 764 tokens, 8/8, 50 -> 34; one query, 8/8, on 760 keys, 33 -> 13.
-// What is left is the start (arguments, first copies: 4 - 5 us), the chain of a wave (0.6 us a dQ stage, 1.4 a dK/dV stage at 64 with four waves, 1.0
-// and 2.5 at 128, one wave per SIMD) and the sums.  Four waves (64: two workgroups per compute unit) or eight: choose_shared_waves.
+// a serial chain of stages on few compute units.  Backward before -> now, us: head_dim 64, 8/8 heads, sequences of 256, 512, 128 and 128, 19.5 ->
+// 10.4; 100 queries on 10100 keys, 32/8, 175 -> 72; head_dim 128, 8/8, 500 tokens, 33.4 -> 14.7.
+// What is left is the start (arguments, first copies: 4 - 6 us), the chain of a wave (0.6 us a dQ stage and 1.1 a dK/dV stage at 64 with four waves, 1.0
+// and 1.8 at 128, one wave per SIMD) and the sums.  A dK/dV stage at 128 took 2.5 us with the rows of every copy clamped (a multiplication each), 2.2
+// without, 2.05 once O's loads were waited for ahead of the copies (rows_loaded), 1.84 with D by v_dot2 and copies from a scalar base.
+// Four waves (64: two workgroups per compute unit) or eight: choose_shared_waves.
 #include <cstring>
 #include <type_traits>
 
@@ -71,10 +73,10 @@ __device__ __forceinline__ float sum_row(float x) {
   return x;
 }
 __device__ __forceinline__ float dot8(bf16x8 a, bf16x8 b) {
-  float s = 0.f;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) s += (float)a[i] * (float)b[i];
-  return s;
+  float s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(a, a, 0, 1), __builtin_shufflevector(b, b, 0, 1), 0.f, false);
+  s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(a, a, 2, 3), __builtin_shufflevector(b, b, 2, 3), s, false);
+  s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(a, a, 4, 5), __builtin_shufflevector(b, b, 4, 5), s, false);
+  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(a, a, 6, 7), __builtin_shufflevector(b, b, 6, 7), s, false);
 }
 __device__ __forceinline__ bf16x8 join(s16x4 lo, s16x4 hi) {
   return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
@@ -96,16 +98,26 @@ struct ShareLane {
     const int j = lane & 15, cl = 2 * ((lane >> 4) & 1) + ((j & 3) >> 1), r0 = 4 * hh + (j >> 2);
     tr_at = (unsigned)(r0 * (D * 2) + ((cl ^ tile_swz<D>(r0)) * 16) + 8 * (j & 1));
   }
-  // element offset, in rows of `stride` elements, of the chunk that copy i of a tile puts at this lane's place; rows past `last` repeat it
+  // The chunk, of rows of `stride` elements, that copy i of a tile puts at this lane's place; rows past `last` (< 31) repeat it, which costs a
+  // multiplication for every copy: whole tiles find their chunks a scalar row and a constant XOR away from `c_off` = c_row * stride.
   template <int I>
-  __device__ __forceinline__ int64_t chunk_at(int64_t stride, int last) const {
-    return (int64_t)min(RPC * I + c_row, last) * stride + (c_chunk ^ tile_swz<D>(RPC * I)) * 8;
+  __device__ __forceinline__ const __bf16* chunk(const __bf16* src, int stride, int c_off, int last) const {
+    const int col = (c_chunk ^ tile_swz<D>(RPC * I)) * 8;
+    if (last >= 31)  // (bytes, so that the address is a scalar base and a 32-bit offset)
+      return reinterpret_cast<const __bf16*>(reinterpret_cast<const char*>(src + (int64_t)(RPC * I) * stride) + (unsigned)(2 * c_off + 2 * col));
+    return src + (int64_t)min(RPC * I + c_row, last) * stride + col;
   }
-  __device__ __forceinline__ void copy_tile(const __bf16* src, int64_t stride, int last, lds_bf16* dst) const {
-    static_for<0, PT>([&](auto i_c) __attribute__((always_inline)) {
-      constexpr int i = decltype(i_c)::value;
-      dma16(src + chunk_at<i>(stride, last), dst + i * 512);
-    });
+  __device__ __forceinline__ void copy_tile(const __bf16* src, int stride, int c_off, int last, lds_bf16* dst) const {
+    if (last >= 31)
+      static_for<0, PT>([&](auto i_c) __attribute__((always_inline)) {
+        constexpr int i = decltype(i_c)::value;
+        dma16(chunk<i>(src, stride, c_off, 31), dst + i * 512);
+      });
+    else
+      static_for<0, PT>([&](auto i_c) __attribute__((always_inline)) {
+        constexpr int i = decltype(i_c)::value;
+        dma16(src + (int64_t)min(RPC * i + c_row, last) * stride + (c_chunk ^ tile_swz<D>(RPC * i)) * 8, dst + i * 512);
+      });
   }
 };
 
@@ -144,8 +156,8 @@ __device__ __forceinline__ void share_dq_block(const ShareParams& p, const chunk
   const int kvh = inner % p.num_kv_heads, head = kvh * p.group + inner / p.num_kv_heads;
   const int q_rows = min(32, seg.q_len - 32 * tile), n0 = seg.kv_len - seg.q_len + 32 * tile + 1;
   const int n_keys = n0 + q_rows - 1, nt = (n_keys + 31) / 32, n_mine = nt > wave ? (nt - wave + W - 1) / W : 0;
-  const int64_t q_stride = (int64_t)p.num_q_heads * D, kv_stride = (int64_t)p.num_kv_heads * D;
-  const int64_t q_off = (int64_t)(seg.q_start + 32 * tile) * q_stride + (int64_t)head * D;
+  const int q_stride = p.num_q_heads * D, kv_stride = p.num_kv_heads * D, kv_c = L.c_row * kv_stride, q_c = L.c_row * q_stride;
+  const int64_t q_off = (int64_t)(seg.q_start + 32 * tile) * q_stride + head * D;
   const __bf16* const Kg = p.k + (int64_t)seg.kv_start * kv_stride + (int64_t)kvh * D;
   const __bf16* const Vg = p.v + (int64_t)seg.kv_start * kv_stride + (int64_t)kvh * D;
   lds_bf16* const region = (lds_bf16*)(smem + wave * 4 * TILE);
@@ -157,8 +169,8 @@ __device__ __forceinline__ void share_dq_block(const ShareParams& p, const chunk
   static_for<0, PT>([&](auto i_c) __attribute__((always_inline)) {
     constexpr int i = decltype(i_c)::value;
     if (i % W == wave) {
-      const int64_t at = q_off + L.template chunk_at<i>(q_stride, q_rows - 1);
-      nd[i] = dot8(*reinterpret_cast<const bf16x8*>(p.o + at), *reinterpret_cast<const bf16x8*>(p.d_o + at));
+      nd[i] = dot8(*reinterpret_cast<const bf16x8*>(L.template chunk<i>(p.o + q_off, q_stride, q_c, q_rows - 1)),
+                   *reinterpret_cast<const bf16x8*>(L.template chunk<i>(p.d_o + q_off, q_stride, q_c, q_rows - 1)));
     }
   });
   float lse2 = 0.f;
@@ -166,9 +178,8 @@ __device__ __forceinline__ void share_dq_block(const ShareParams& p, const chunk
   static_for<0, PT>([&](auto i_c) __attribute__((always_inline)) {
     constexpr int i = decltype(i_c)::value;
     if (i % W == wave) {
-      const int64_t at = q_off + L.template chunk_at<i>(q_stride, q_rows - 1);
-      dma16(p.q + at, own + i * 512);
-      dma16(p.d_o + at, own + TILE / 2 + i * 512);
+      dma16(L.template chunk<i>(p.q + q_off, q_stride, q_c, q_rows - 1), own + i * 512);
+      dma16(L.template chunk<i>(p.d_o + q_off, q_stride, q_c, q_rows - 1), own + TILE / 2 + i * 512);
     }
   });
   static_for<0, PT>([&](auto i_c) __attribute__((always_inline)) {
@@ -182,8 +193,8 @@ __device__ __forceinline__ void share_dq_block(const ShareParams& p, const chunk
   auto copy_stage = [&](int i, int slot) __attribute__((always_inline)) {
     const int t = wave + W * min(i, n_mine - 1);
     const int64_t off = (int64_t)(32 * t) * kv_stride;
-    L.copy_tile(Kg + off, kv_stride, n_keys - 1 - 32 * t, region + slot * TILE);
-    L.copy_tile(Vg + off, kv_stride, n_keys - 1 - 32 * t, region + slot * TILE + TILE / 2);
+    L.copy_tile(Kg + off, kv_stride, kv_c, n_keys - 1 - 32 * t, region + slot * TILE);
+    L.copy_tile(Vg + off, kv_stride, kv_c, n_keys - 1 - 32 * t, region + slot * TILE + TILE / 2);
   };
   if (n_mine > 0) {
     copy_stage(0, 0);
@@ -230,15 +241,9 @@ __device__ __forceinline__ void share_dq_block(const ShareParams& p, const chunk
       vf[ks] = lds_asm_read16<TILE>(ka ^ (ks * 32));
     });
     f32x16 s, dp;
-    asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(DK) : "memory");
-#pragma unroll
-    for (int ks = 0; ks < DK; ++ks) asm volatile("" : "+v"(kf[ks]));
-#pragma unroll
-    for (int ks = 0; ks < DK; ++ks) s = mfma32(kf[ks], qf[ks], ks == 0 ? zero16 : s);
-    __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-    for (int ks = 0; ks < DK; ++ks) asm volatile("" : "+v"(vf[ks]));
+    for (int ks = 0; ks < DK; ++ks) asm volatile("" : "+v"(kf[ks]), "+v"(vf[ks]));
     s16x4 lo[2][DB], hi[2][DB];  // operands of dQ^T += K^T dS^T
     static_for<0, 2 * DB>([&](auto x_c) __attribute__((always_inline)) {
       constexpr int ks = decltype(x_c)::value / DB, db = decltype(x_c)::value % DB;
@@ -247,7 +252,10 @@ __device__ __forceinline__ void share_dq_block(const ShareParams& p, const chunk
     });
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int ks = 0; ks < DK; ++ks) dp = mfma32(vf[ks], gf[ks], ks == 0 ? zero16 : dp);
+    for (int ks = 0; ks < DK; ++ks) {  // (two chains of products, one between the other's)
+      s = mfma32(kf[ks], qf[ks], ks == 0 ? zero16 : s);
+      dp = mfma32(vf[ks], gf[ks], ks == 0 ? zero16 : dp);
+    }
     float pe[16];
 #pragma unroll
     for (int e = 0; e < 16; ++e) pe[e] = __builtin_amdgcn_exp2f(s[e] * c - row_lse);
@@ -294,51 +302,69 @@ __device__ __forceinline__ void share_dkv_block(const ShareParams& p, const chun
   const int j0 = 32 * tile, kv_rows = min(32, seg.kv_len - j0), ctx = seg.kv_len - seg.q_len;
   const int qt_first = max(0, j0 - ctx) / 32, n_qt = (seg.q_len + 31) / 32, G = p.group;
   const int n_all = (n_qt - qt_first) * G, n_mine = n_all > wave ? (n_all - wave + W - 1) / W : 0;
-  const int64_t q_stride = (int64_t)p.num_q_heads * D, kv_stride = (int64_t)p.num_kv_heads * D;
-  const int64_t kv_off = (int64_t)(seg.kv_start + j0) * kv_stride + (int64_t)kvh * D;
+  const int q_stride = p.num_q_heads * D, kv_stride = p.num_kv_heads * D, kv_c = L.c_row * kv_stride, q_c = L.c_row * q_stride;
+  const int64_t kv_off = (int64_t)(seg.kv_start + j0) * kv_stride + kvh * D;
   lds_bf16* const region = (lds_bf16*)(smem + wave * 4 * TILE);
   lds_bf16* const own = (lds_bf16*)(smem + W * 4 * TILE);                       // K, V
   lds_f32* const rows = (lds_f32*)(smem + (W * 4 + 2) * TILE) + wave * 64;      // of the wave's stage: LSE log2(e) [32], -D [32]
 
-  // stage i of the wave: query tile and head (heads of a tile one after the other)
-  auto stage = [&](int i, int& i0, int& head) __attribute__((always_inline)) {
-    const unsigned n = (unsigned)(wave + W * i), t = n / (unsigned)G;
-    i0 = 32 * (qt_first + (int)t);
-    head = kvh * G + (int)(n - t * (unsigned)G);
+  // a stage of the wave: query tile and head of the group (heads of a tile one after the other); `next` finds the wave's next one
+  struct Stage {
+    int qt, h;
+  };
+  const int per_qt = W / G, per_h = W % G;
+  auto next = [&](Stage x) __attribute__((always_inline)) {
+    x.h += per_h;
+    x.qt += per_qt;
+    if (x.h >= G) {
+      x.h -= G;
+      ++x.qt;
+    }
+    return x;
   };
   bf16x8 of[PT];   // O of the next stage, as the copies lay out dO
   float lse = 0.f; // and its LSE, rows 0 .. 31 in the first 32 lanes
-  auto load_rows = [&](int i) __attribute__((always_inline)) {
-    int i0, head;
-    stage(min(i, n_mine - 1), i0, head);
-    const __bf16* const src = p.o + (int64_t)(seg.q_start + i0) * q_stride + (int64_t)head * D;
-    const int last = min(31, seg.q_len - 1 - i0);
+  auto load_rows = [&](Stage x) __attribute__((always_inline)) {
+    const int i0 = 32 * x.qt, head = kvh * G + x.h, last = seg.q_len - 1 - i0;
+    const __bf16* const src = p.o + (int64_t)(seg.q_start + i0) * q_stride + head * D;
     lse = p.lse[(int64_t)head * p.total_q + seg.q_start + i0 + min(L.l32, last)];
-    static_for<0, PT>([&](auto x_c) __attribute__((always_inline)) {
-      constexpr int x = decltype(x_c)::value;
-      of[x] = *reinterpret_cast<const bf16x8*>(src + L.template chunk_at<x>(q_stride, last));
-    });
+    if (last >= 31)
+      static_for<0, PT>([&](auto x_c) __attribute__((always_inline)) {
+        constexpr int n = decltype(x_c)::value;
+        of[n] = *reinterpret_cast<const bf16x8*>(L.template chunk<n>(src, q_stride, q_c, 31));
+      });
+    else
+      static_for<0, PT>([&](auto x_c) __attribute__((always_inline)) {
+        constexpr int n = decltype(x_c)::value;
+        of[n] = *reinterpret_cast<const bf16x8*>(L.template chunk<n>(src, q_stride, q_c, min(last, 30)));
+      });
   };
-  auto copy_stage = [&](int i, int slot) __attribute__((always_inline)) {
-    int i0, head;
-    stage(min(i, n_mine - 1), i0, head);
-    const int64_t off = (int64_t)(seg.q_start + i0) * q_stride + (int64_t)head * D;
-    const int last = min(31, seg.q_len - 1 - i0);
-    L.copy_tile(p.q + off, q_stride, last, region + slot * TILE);
-    L.copy_tile(p.d_o + off, q_stride, last, region + slot * TILE + TILE / 2);
+  // Stands where the loads of load_rows have long ended and no copy has been issued since the last one that must have landed: the compiler waits for
+  // a load by counting what was issued after it, and takes copies in branches for none, so that at its use it would wait for the next stage's copies.
+  auto rows_loaded = [&]() __attribute__((always_inline)) {
+    asm volatile("" : "+v"(lse));
+#pragma unroll
+    for (int x = 0; x < PT; ++x) asm volatile("" : "+v"(of[x]));
   };
+  auto copy_stage = [&](Stage x, int slot) __attribute__((always_inline)) {
+    const int i0 = 32 * x.qt, head = kvh * G + x.h, last = seg.q_len - 1 - i0;
+    const int64_t off = (int64_t)(seg.q_start + i0) * q_stride + head * D;
+    L.copy_tile(p.q + off, q_stride, q_c, last, region + slot * TILE);
+    L.copy_tile(p.d_o + off, q_stride, q_c, last, region + slot * TILE + TILE / 2);
+  };
+  Stage cur{qt_first + wave / G, wave % G}, ahead = n_mine > 1 ? next(cur) : cur;  // of the step, and the one after it
   static_for<0, PT>([&](auto i_c) __attribute__((always_inline)) {
     constexpr int i = decltype(i_c)::value;
     if (i % W == wave) {
-      const int64_t at = kv_off + L.template chunk_at<i>(kv_stride, kv_rows - 1);
-      dma16(p.k + at, own + i * 512);
-      dma16(p.v + at, own + TILE / 2 + i * 512);
+      dma16(L.template chunk<i>(p.k + kv_off, kv_stride, kv_c, kv_rows - 1), own + i * 512);
+      dma16(L.template chunk<i>(p.v + kv_off, kv_stride, kv_c, kv_rows - 1), own + TILE / 2 + i * 512);
     }
   });
   if (n_mine > 0) {
-    load_rows(0);
-    copy_stage(0, 0);
-    copy_stage(1, 1);
+    load_rows(cur);
+    copy_stage(cur, 0);
+    rows_loaded();
+    copy_stage(ahead, 1);
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * PT) : "memory");  // (all but the stages' copies)
   } else {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -368,44 +394,42 @@ __device__ __forceinline__ void share_dkv_block(const ShareParams& p, const chun
   const unsigned rv = lds_addr(rows) + 16 * L.hh;
   for (int i = 0; i < n_mine; ++i) {
     const int slot = i & 1;
-    int i0, head;
-    stage(i, i0, head);
+    const int i0 = 32 * cur.qt;
     const int valid = seg.q_len - i0;  // rows of the tile (32 or more: all)
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * PT) : "memory");  // the copies of the stage after this one may be outstanding
-    // ---- -D and LSE of the stage's rows, through LDS into the rows of the accumulators ----
-    {
-      bf16x8 g[PT];
-      static_for<0, PT>([&](auto x_c) __attribute__((always_inline)) {
-        constexpr int x = decltype(x_c)::value;
-        g[x] = lds_asm_read16<x * 1024>(d_base + slot * (2 * TILE));
-      });
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      static_for<0, PT>([&](auto x_c) __attribute__((always_inline)) {
-        constexpr int x = decltype(x_c)::value;
-        asm volatile("" : "+v"(g[x]));
-        const float s = sum_row<D / 8>(dot8(of[x], g[x]));
-        if (L.lane % (D / 8) == 0) lds_asm_write4(lds_addr(rows + 32 + RPC * x + L.c_row), (int)__float_as_uint(RPC * x + L.c_row < valid ? -s : 0.f));
-      });
-      if (L.lane < 32) lds_asm_write4(lds_addr(rows + L.lane), (int)__float_as_uint(L.lane < valid ? lse * kLog2e : INFINITY));
-      load_rows(i + 1);
-    }
     const unsigned ra = r_base + slot * (2 * TILE), ta = t_base + slot * (2 * TILE);
-    bf16x8 qf[DK], gf[DK];
+    bf16x8 qf[DK], gf[DK], g[PT];
     f32x4 r_lse[4], r_nd[4];
+    f32x16 s, dp;
     static_for<0, DK>([&](auto ks_c) __attribute__((always_inline)) {
       constexpr int ks = decltype(ks_c)::value;
       qf[ks] = lds_asm_read16<0>(ra ^ (ks * 32));
     });
-    static_for<0, 4>([&](auto g_c) __attribute__((always_inline)) {
-      constexpr int g = decltype(g_c)::value;
-      r_lse[g] = lds_asm_read16f<g * 32>(rv);
+    static_for<0, PT>([&](auto x_c) __attribute__((always_inline)) {
+      constexpr int x = decltype(x_c)::value;
+      g[x] = lds_asm_read16<x * 1024>(d_base + slot * (2 * TILE));
     });
-    f32x16 s, dp;
-    asm volatile("s_waitcnt lgkmcnt(4)" ::: "memory");
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
     for (int ks = 0; ks < DK; ++ks) asm volatile("" : "+v"(qf[ks]));
 #pragma unroll
+    for (int x = 0; x < PT; ++x) asm volatile("" : "+v"(g[x]));
+#pragma unroll
     for (int ks = 0; ks < DK; ++ks) s = mfma32(qf[ks], kf[ks], ks == 0 ? zero16 : s);
+    // ---- -D and LSE of the stage's rows, through LDS into the rows of the accumulators ----
+    float nd[PT];
+#pragma unroll
+    for (int x = 0; x < PT; ++x) nd[x] = sum_row<D / 8>(dot8(of[x], g[x]));
+    static_for<0, PT>([&](auto x_c) __attribute__((always_inline)) {
+      constexpr int x = decltype(x_c)::value;
+      if (L.lane % (D / 8) == 0) lds_asm_write4(lds_addr(rows + 32 + RPC * x + L.c_row), (int)__float_as_uint(RPC * x + L.c_row < valid ? -nd[x] : 0.f));
+    });
+    if (L.lane < 32) lds_asm_write4(lds_addr(rows + L.lane), (int)__float_as_uint(L.lane < valid ? lse * kLog2e : INFINITY));
+    load_rows(ahead);
+    static_for<0, 4>([&](auto g_c) __attribute__((always_inline)) {
+      constexpr int x = decltype(g_c)::value;
+      r_lse[x] = lds_asm_read16f<x * 32>(rv);
+    });
     __builtin_amdgcn_sched_barrier(0);
     static_for<0, DK>([&](auto ks_c) __attribute__((always_inline)) {
       constexpr int ks = decltype(ks_c)::value;
@@ -461,7 +485,10 @@ __device__ __forceinline__ void share_dkv_block(const ShareParams& p, const chun
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
     for (int x = 0; x < 2 * DB; ++x) asm volatile("" : "+v"(qlo[x / DB][x % DB]), "+v"(qhi[x / DB][x % DB]));
-    copy_stage(i + 2, slot);  // (every read of the slot has returned; past the end the last stage again, for nobody)
+    rows_loaded();
+    cur = ahead;
+    if (i + 2 < n_mine) ahead = next(ahead);
+    copy_stage(ahead, slot);  // (every read of the slot has returned; past the end the last stage again, for nobody)
 #pragma unroll
     for (int db = 0; db < DB; ++db) acc[DB + db] = mfma32(join(qlo[0][db], qhi[0][db]), f0, acc[DB + db]);
 #pragma unroll

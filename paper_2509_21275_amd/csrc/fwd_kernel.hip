@@ -1359,13 +1359,19 @@ __global__ __launch_bounds__(HG * KS * 64, D == 64 ? 4 : HG * KS / 4) void fwd_s
     const int64_t toff = (int64_t)(32 * t + row0) * kv_stride;  // wave-uniform
     lds_bf16* const dst = region + slot * TILE + piece0 * 512;
     const int last_row = n_keys - 1 - 32 * t - row0;
-    static_for<decltype(first_c)::value, decltype(end_c)::value>([&](auto x_c) __attribute__((always_inline)) {
-      constexpr int x = decltype(x_c)::value, j = x % PT;
-      const __bf16* const src = (HG > 1 || x < PT ? Xg : Vg) + toff;
-      const int chunk = (c_chunk ^ share_swz<D>(RPC * j)) * 8;
-      if (last_row >= 31) dma16(src + (int64_t)(RPC * j) * kv_stride + (unsigned)(c_off + chunk), dst + x * 512);
-      else dma16(src + (int64_t)min(RPC * j + c_row, last_row) * kv_stride + chunk, dst + x * 512);  // (rows past the last one repeat it)
-    });
+    auto src = [&](int x) __attribute__((always_inline)) { return (HG > 1 || x < PT ? Xg : Vg) + toff; };
+    if (last_row >= 31) {  // (a scalar base and a 32-bit offset in bytes)
+      static_for<decltype(first_c)::value, decltype(end_c)::value>([&](auto x_c) __attribute__((always_inline)) {
+        constexpr int x = decltype(x_c)::value, j = x % PT;
+        const char* const row = reinterpret_cast<const char*>(src(x) + (int64_t)(RPC * j) * kv_stride);
+        dma16(row + (unsigned)(2 * c_off + 16 * (c_chunk ^ share_swz<D>(RPC * j))), dst + x * 512);
+      });
+    } else {  // (rows past the last one repeat it)
+      static_for<decltype(first_c)::value, decltype(end_c)::value>([&](auto x_c) __attribute__((always_inline)) {
+        constexpr int x = decltype(x_c)::value, j = x % PT;
+        dma16(src(x) + (int64_t)min(RPC * j + c_row, last_row) * kv_stride + (c_chunk ^ share_swz<D>(RPC * j)) * 8, dst + x * 512);
+      });
+    }
   };
   const std::integral_constant<int, 0> first;
   const std::integral_constant<int, PT> half;

@@ -448,12 +448,12 @@ int choose_shared_heads(const chunk_attn_desc* d, const Walks& other, int inner,
   return best;
 }
 
-// The same for the backward (us; 950 drawn chunks, the bounds of this function aside): first + the larger of what the longest dQ walk, the longest
-// dK/dV walk and all workgroups together take.  Off by 5 - 9 % (root mean square); chosen where it is 14 % ahead by the estimate: slower in 2 of
-// 720 chunks, by 6 % at most, and 1.96 (head_dim 64) and 1.40 (128) times as fast on average over all, where the best choice would be 1.98 and 1.40.
-// Examples, other kernels -> four, eight waves: head_dim 64, 596 tokens, 8/8 heads, 21.0 -> 11.9, 11.1; 117 queries, 4/1, on up to 5600 keys,
-// 92 -> 28, 23; 2205 tokens in 32 sequences, 32/8, 38 -> 37, 57; 2537 tokens, 64/8, 156 -> 203, 221; head_dim 128, 150 tokens, 32/8, 36.9 -> 19.1;
-// 764 tokens, 8/8, 50 -> 34; 1454 tokens, 32/8, 83 -> 112.
+// The same for the backward (us; 1290 drawn chunks, the bounds of this function aside): first + the larger of what the longest dQ walk, the longest
+// dK/dV walk and all workgroups together take.  Off by 5 - 10 % (root mean square), so it is chosen where it is 14 % ahead by the estimate: in 780
+// of those chunks, none of them slower (at 10 % ahead 3, at 6 % 9), and 2.0 (head_dim 64) and 1.5 (128) times as fast on average over the chunks within
+// the bounds, where the best choice would be as much within 1 %.
+// Examples, other kernels -> this one: head_dim 64, 8/8 heads, 64 tokens, 8.7 -> 5.3, sequences of 256, 512, 128 and 128, 19.5 -> 10.4, 1024 tokens, 29.4 ->
+// 15.7; 100 queries on 10100 keys, 32/8, 175 -> 72; head_dim 128, 8/8, 500 tokens, 33.4 -> 14.7, 1000, 46.7 -> 27.8, 100 queries on 1100 keys, 45 -> 17.
 struct SharedBwdCost {
   double first, dq_step, dkv_step, all_dq, all_dkv, workgroup, longest;
   int waves, slots;
@@ -462,8 +462,8 @@ struct SharedBwdCost {
                              (all_dq * dq_all + all_dkv * dkv_all + workgroup * blocks) / slots + longest * std::max(dq_most, dkv_most)});
   }
 };
-constexpr SharedBwdCost kSharedBwd64[2] = {{4.4, 0.58, 1.42, 2.15, 0.61, 2.5, 0.17, 4, 512}, {4.0, 0.84, 2.14, 1.88, 1.22, 2.1, 0.25, 8, 256}};
-constexpr SharedBwdCost kSharedBwd128 = {6.0, 1.0, 2.5, 2.2, 1.5, 3.9, 0.1, 4, 256};
+constexpr SharedBwdCost kSharedBwd64[2] = {{4.5, 0.585, 1.11, 1.9, 0.69, 2.4, 0.18, 4, 512}, {4.1, 0.82, 1.82, 1.65, 1.31, 2.0, 0.2, 8, 256}};
+constexpr SharedBwdCost kSharedBwd128 = {6.3, 1.03, 1.84, 1.46, 1.74, 3.86, 0.08, 4, 256};
 
 int choose_shared_waves(const chunk_attn_desc* d, const Walks& dq, int inner, const Walks& dkv, bool cut) {
   if (d->num_segments > kMaxShareSegs) return 0;
@@ -478,12 +478,12 @@ int choose_shared_waves(const chunk_attn_desc* d, const Walks& dq, int inner, co
   if (d->head_dim == 64) {
     // (long dK/dV walks are cut evenly already; dQ walks are not)
     if (cut && dq.longest <= dkv.longest && dkv.longest > 32) return 0;
-    other = cut ? 16.6 + 1.08 * std::min(KL, 16.4) + 0.31 * KT + 0.46 * DL
-                : 7.1 + std::max({0.49 * DL, 0.73 * KL, 0.73 * KT + 2.4 * blocks + 0.41 * std::max(DL, KL)});
+    other = cut ? 13.7 + 0.53 * std::min(KL, 8.7) + 0.35 * KT + 0.45 * DL
+                : 7.1 + std::max({0.49 * DL, 0.73 * KL, 0.81 * KT + 2.1 * blocks + 0.4 * std::max(DL, KL)});
   } else {
     if (!cut && dq.longest > kLongSharedWalk) return 0;  // (as in the forward)
-    other = cut ? 18.6 + 0.22 * std::min(DL, 56.0) + 0.39 * std::min(KL, 36.0) + DT + 0.94 * KT + 10.8 * blocks + 0.016 * DL
-                : 17.0 + std::max({0.71 * DL, 0.95 * KL, 2.68 * DT + 1.06 * KT + 11.4 * blocks + 0.03 * std::max(DL, KL)});
+    other = cut ? 23.1 + 0.75 * std::min(DL, 9.0) + 0.19 * std::min(KL, 36.0) + 1.58 * DT + 0.98 * KT + 8.2 * blocks + 0.028 * DL
+                : 17.0 + std::max({0.72 * DL, 0.95 * KL, 2.53 * DT + 0.58 * KT + 14.8 * blocks});
   }
   const int group = d->num_q_heads / d->num_kv_heads;
   int best = 0;

@@ -79,7 +79,7 @@ BWD_CASES = [  # head dimension, segments, query heads, key/value heads, waves p
     (64, [(0, 1, 0, 40)], 1, 1, 4),
     (64, [(0, 33, 0, 33)], 8, 8, 4),
     (64, [(0, 256, 3, 256), (256, 257, 260, 257), (513, 31, 520, 288)], 8, 8, 4),
-    (64, [(0, 596, 0, 596)], 8, 8, 8),
+    (64, [(0, 596, 0, 596)], 4, 4, 8),
     (64, [(0, 117, 0, 5600)], 4, 1, 8),
     (64, [(0, 365, 2, 513), (365, 64, 515, 576), (429, 1, 1091, 545)], 16, 8, 4),
     (64, [(97 * i, 97, 97 * i, 97) for i in range(10)], 8, 2, 4),
