@@ -227,7 +227,8 @@ int chunk_attn_measure_set_clock_log(void* device_buffer, size_t bytes);
  * 0: the library's choice; 1: two kernels (dQ query-stationary, dK/dV key-stationary, P recomputed in both);
  * 2: one pass (the key-stationary kernel also forms dQ and adds it into float32 tiles in the workspace in a fixed
  * order).  Same results up to the order of float32 additions in dQ; both are bit-reproducible.  Process-wide; the
- * workspace size does not depend on it.  Returns CHUNK_ATTN_INVALID_ARG for any other value.
+ * workspace size does not depend on it.  In modes 1 and 2 the kernels of small chunks (chunk_attn_test_shared_heads, _waves) stay out of the way,
+ * in the forward as well and for every head_dim.  Returns CHUNK_ATTN_INVALID_ARG for any other value.
  */
 int chunk_attn_test_set_bwd_mode(int mode);
 

@@ -251,7 +251,7 @@ void layout_fwd(const chunk_attn_desc* desc, FwdLayout& L, bool with_plan, bool 
   if (is_narrow(desc))  // (as much as with padded copies of Q, K, V and O)
     L.total = std::max(L.total, uncut_total + 2 * padded_bytes(d->total_q, d->num_q_heads, 2) + 2 * padded_bytes(d->total_kv, d->num_kv_heads, 2));
   // (the layout of the workspace stays the other kernel's, so that its size does)
-  L.share = may_cut ? choose_shared_heads(desc, walks, inner, pipe, L.split.target > 0) : 0;
+  L.share = may_cut && bwd_mode() == 0 ? choose_shared_heads(desc, walks, inner, pipe, L.split.target > 0) : 0;
   if (L.share > 0) {
     L.n_items = (size_t)count_walks(d, 32).items;
     L.blocks = (int64_t)L.n_items * (d->num_q_heads / L.share);
@@ -465,9 +465,6 @@ FwdParams fwd_params(const chunk_attn_desc* desc, const FwdLayout& L, char* ws, 
   p.ref_limit = g_fwd_rescale_limit.load();
   return p;
 }
-// (the kernels of the small chunks' backward have no instantiation for head_dim 96; the test hook's other modes ask for particular kernels)
-bool may_share(const chunk_attn_desc* desc) { return !is_narrow(desc) && bwd_mode() == 0; }
-
 FwdKind fwd_kind(const FwdLayout& L) { return L.share > 0 ? kFwdShare : L.pipe ? kFwdPipe : kFwdPlain; }
 FwdLists fwd_lists(const FwdLayout& L) {
   FwdLists l;
@@ -571,7 +568,7 @@ int chunk_attn_test_shared_waves(const chunk_attn_desc* desc, int32_t* waves) {
   if (!waves) return CHUNK_ATTN_INVALID_ARG;
   const chunk_attn_desc w = widened(desc);
   BwdPlan P;
-  bwd_layout(&w, P, false, kCutFine, may_share(desc));
+  bwd_layout(&w, P, false, kCutFine, bwd_mode() == 0 ? desc->head_dim : 0);
   *waves = P.share_waves;
   return CHUNK_ATTN_OK;
 }
@@ -706,7 +703,7 @@ int bwd_any(const chunk_attn_desc* desc, const void* q, const void* k, const voi
   const chunk_attn_desc w = widened(desc);
   BwdPlan P;
   auto needed = [&]() { return is_narrow(desc) ? narrow_bwd_layout(desc, P.total).total : P.total; };
-  bwd_layout(&w, P, true, kCutFine, may_share(desc));
+  bwd_layout(&w, P, true, kCutFine, bwd_mode() == 0 ? desc->head_dim : 0);
   if (workspace_bytes < needed()) bwd_layout(&w, P, true, kCutInPlace);  // too small for all partial results: fewer pieces, or
   if (workspace_bytes < needed()) bwd_layout(&w, P, true, kCutNone);     // none
   if (workspace_bytes < needed()) return CHUNK_ATTN_WORKSPACE_TOO_SMALL;

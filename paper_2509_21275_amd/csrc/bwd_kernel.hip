@@ -3315,7 +3315,7 @@ hipError_t zero_uncovered(const chunk_attn_desc* d, const BwdArgs& a, hipStream_
   return hipSuccess;
 }
 
-void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, Cut cut, bool may_share) {
+void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, Cut cut, int share_dim) {
   P = BwdPlan{};
   const int group = d->num_q_heads / d->num_kv_heads;
   const bool pipe = d->head_dim == 128;
@@ -3347,8 +3347,8 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, Cut cut, b
   }
   if (!pipe && !P.dkv_pipe && cut == kCutFine)
     P.dkv_split = choose_tile_split(d, dkv_keys(d->head_dim), kCus, kMaxShortParts / d->num_kv_heads);
-  if (may_share && (pipe || (d->head_dim == 64 && !P.dq_pipe)))
-    P.share_waves = choose_shared_waves(d, count_walks(d, dq_rows), d->num_kv_heads * (group / heads_per_wg(group, P.dq_waves)),
+  if (share_dim > 0 && (pipe || (d->head_dim == 64 && !P.dq_pipe)))
+    P.share_waves = choose_shared_waves(d, share_dim, count_walks(d, dq_rows), d->num_kv_heads * (group / heads_per_wg(group, P.dq_waves)),
                                         count_dkv_walks(d, dkv_keys(d->head_dim)), P.split.target > 0 || P.dkv_split.target > 0);
   if (with_plan && P.share_waves == 0) {
     if (P.fused) {

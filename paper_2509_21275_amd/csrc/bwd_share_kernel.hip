@@ -1,4 +1,4 @@
-// Chunk attention backward of small chunks in one launch (head_dim 64 and 128): no pre-pass, no list in device memory, no merge.
+// Chunk attention backward of small chunks in one launch (head_dim 64, 96 and 128): no pre-pass, no list in device memory, no merge.
 //
 // The W waves of a workgroup share one small output tile and divide the walk that makes it:
 //   dQ      32 query rows of one head; wave w takes key stages w, w + W, ... of 32 keys:
@@ -30,6 +30,8 @@ namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
 
+// (head_dim 96: rows of 128 columns in LDS, whose last four chunks copy the last but them and are never read)
+constexpr int tile_cols(int d) { return d == 96 ? 128 : d; }
 template <int D>
 __host__ __device__ constexpr int tile_swz(int r) {
   return D == 64 ? ((r >> 3) & 1) | ((r >> 1) & 2) | ((r & 2) << 1) : ((r & 3) << 2) | ((r >> 2) & 3);
@@ -57,7 +59,7 @@ static_assert(sizeof(ShareArgs) <= 3840);
 
 // LDS: W waves' slots (two stages of two tiles each; at the end the wave's sums), the two stationary tiles, 32 values of LSE and of -D per wave
 template <int D, int W>
-constexpr size_t share_bwd_smem() { return (size_t)(W * 4 + 2) * 32 * D * 2 + (size_t)W * 64 * sizeof(float); }
+constexpr size_t share_bwd_smem() { return (size_t)(W * 4 + 2) * 32 * tile_cols(D) * 2 + (size_t)W * 64 * sizeof(float); }
 
 template <int CTRL>
 __device__ __forceinline__ float dpp_add(float x) {
@@ -85,7 +87,7 @@ __device__ __forceinline__ bf16x8 join(s16x4 lo, s16x4 hi) {
 // What both kinds of block use: the lane's place in copies and operand reads.
 template <int D>
 struct ShareLane {
-  static constexpr int C = D / 8, PT = C / 2, RPC = 64 / C, TILE = 32 * D * 2;
+  static constexpr int ROW = tile_cols(D) * 2, C = ROW / 16, PT = C / 2, RPC = 64 / C, TILE = 32 * ROW;  // ROW: bytes of a row in LDS
   int lane, l32, hh, c_row, c_chunk;
   unsigned row_at, tr_at;  // byte offsets in a tile of the row reads and of the transposed reads
   __device__ __forceinline__ ShareLane() {
@@ -94,15 +96,22 @@ struct ShareLane {
     hh = lane >> 5;
     c_row = lane / C;
     c_chunk = (lane % C) ^ tile_swz<D>(c_row);
-    row_at = (unsigned)(l32 * (D * 2) + ((hh ^ tile_swz<D>(l32)) * 16));
+    row_at = (unsigned)(l32 * ROW + ((hh ^ tile_swz<D>(l32)) * 16));
     const int j = lane & 15, cl = 2 * ((lane >> 4) & 1) + ((j & 3) >> 1), r0 = 4 * hh + (j >> 2);
-    tr_at = (unsigned)(r0 * (D * 2) + ((cl ^ tile_swz<D>(r0)) * 16) + 8 * (j & 1));
+    tr_at = (unsigned)(r0 * ROW + ((cl ^ tile_swz<D>(r0)) * 16) + 8 * (j & 1));
   }
+  template <int I>
+  __device__ __forceinline__ int column() const {  // of the lane's chunk in copy I of a tile
+    const int chunk = c_chunk ^ tile_swz<D>(RPC * I);
+    return (D == 96 ? min(chunk, D / 8 - 1) : chunk) * 8;
+  }
+  template <int I>
+  __device__ __forceinline__ bool in_row() const { return D != 96 || (c_chunk ^ tile_swz<D>(RPC * I)) < D / 8; }  // it is one of the row's
   // The chunk, of rows of `stride` elements, that copy i of a tile puts at this lane's place; rows past `last` (< 31) repeat it, which costs a
   // multiplication for every copy: whole tiles find their chunks a scalar row and a constant XOR away from `c_off` = c_row * stride.
   template <int I>
   __device__ __forceinline__ const __bf16* chunk(const __bf16* src, int stride, int c_off, int last) const {
-    const int col = (c_chunk ^ tile_swz<D>(RPC * I)) * 8;
+    const int col = column<I>();
     if (last >= 31)  // (bytes, so that the address is a scalar base and a 32-bit offset)
       return reinterpret_cast<const __bf16*>(reinterpret_cast<const char*>(src + (int64_t)(RPC * I) * stride) + (unsigned)(2 * c_off + 2 * col));
     return src + (int64_t)min(RPC * I + c_row, last) * stride + col;
@@ -116,7 +125,7 @@ struct ShareLane {
     else
       static_for<0, PT>([&](auto i_c) __attribute__((always_inline)) {
         constexpr int i = decltype(i_c)::value;
-        dma16(src + (int64_t)min(RPC * i + c_row, last) * stride + (c_chunk ^ tile_swz<D>(RPC * i)) * 8, dst + i * 512);
+        dma16(src + (int64_t)min(RPC * i + c_row, last) * stride + column<i>(), dst + i * 512);
       });
   }
 };
@@ -125,7 +134,7 @@ struct ShareLane {
 // columns.  `use(quarter, sum)` is called for each of the wave's own.
 template <int D, int W, int N, class F>
 __device__ __forceinline__ void add_shares(char* smem, int wave, int lane, int parts, const f32x16 (&acc)[N], F&& use) {
-  constexpr int NQ = N * 4, NQW = NQ / W, REGION = 4 * 32 * D * 2;
+  constexpr int NQ = N * 4, NQW = NQ / W, REGION = 4 * 32 * tile_cols(D) * 2;
   static_assert(NQ % W == 0 && NQ * 1024 <= REGION);
   if (wave < parts) {
     lds_f32* const out = (lds_f32*)(smem + wave * REGION) + lane * 4;
@@ -169,8 +178,9 @@ __device__ __forceinline__ void share_dq_block(const ShareParams& p, const chunk
   static_for<0, PT>([&](auto i_c) __attribute__((always_inline)) {
     constexpr int i = decltype(i_c)::value;
     if (i % W == wave) {
-      nd[i] = dot8(*reinterpret_cast<const bf16x8*>(L.template chunk<i>(p.o + q_off, q_stride, q_c, q_rows - 1)),
-                   *reinterpret_cast<const bf16x8*>(L.template chunk<i>(p.d_o + q_off, q_stride, q_c, q_rows - 1)));
+      const float x = dot8(*reinterpret_cast<const bf16x8*>(L.template chunk<i>(p.o + q_off, q_stride, q_c, q_rows - 1)),
+                           *reinterpret_cast<const bf16x8*>(L.template chunk<i>(p.d_o + q_off, q_stride, q_c, q_rows - 1)));
+      nd[i] = L.template in_row<i>() ? x : 0.f;
     }
   });
   float lse2 = 0.f;
@@ -185,8 +195,8 @@ __device__ __forceinline__ void share_dq_block(const ShareParams& p, const chunk
   static_for<0, PT>([&](auto i_c) __attribute__((always_inline)) {
     constexpr int i = decltype(i_c)::value;
     if (i % W == wave) {
-      const float s = sum_row<D / 8>(nd[i]);
-      if (L.lane % (D / 8) == 0) lds_asm_write4(lds_addr(rows + 32 + RPC * i + L.c_row), (int)__float_as_uint(-s));
+      const float s = sum_row<Lane::C>(nd[i]);
+      if (L.lane % Lane::C == 0) lds_asm_write4(lds_addr(rows + 32 + RPC * i + L.c_row), (int)__float_as_uint(-s));
     }
   });
   if (wave == W - 1 && L.lane < 32) lds_asm_write4(lds_addr(rows + L.lane), (int)__float_as_uint(lse2));
@@ -247,8 +257,8 @@ __device__ __forceinline__ void share_dq_block(const ShareParams& p, const chunk
     s16x4 lo[2][DB], hi[2][DB];  // operands of dQ^T += K^T dS^T
     static_for<0, 2 * DB>([&](auto x_c) __attribute__((always_inline)) {
       constexpr int ks = decltype(x_c)::value / DB, db = decltype(x_c)::value % DB;
-      lo[ks][db] = lds_asm_read_tr<ks * 16 * D * 2>(ta ^ (db * 64));
-      hi[ks][db] = lds_asm_read_tr<(ks * 16 + 8) * D * 2>(ta ^ (db * 64 + tile_swz<D>(8) * 16));
+      lo[ks][db] = lds_asm_read_tr<ks * 16 * Lane::ROW>(ta ^ (db * 64));
+      hi[ks][db] = lds_asm_read_tr<(ks * 16 + 8) * Lane::ROW>(ta ^ (db * 64 + tile_swz<D>(8) * 16));
     });
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -418,11 +428,14 @@ __device__ __forceinline__ void share_dkv_block(const ShareParams& p, const chun
     for (int ks = 0; ks < DK; ++ks) s = mfma32(qf[ks], kf[ks], ks == 0 ? zero16 : s);
     // ---- -D and LSE of the stage's rows, through LDS into the rows of the accumulators ----
     float nd[PT];
-#pragma unroll
-    for (int x = 0; x < PT; ++x) nd[x] = sum_row<D / 8>(dot8(of[x], g[x]));
     static_for<0, PT>([&](auto x_c) __attribute__((always_inline)) {
       constexpr int x = decltype(x_c)::value;
-      if (L.lane % (D / 8) == 0) lds_asm_write4(lds_addr(rows + 32 + RPC * x + L.c_row), (int)__float_as_uint(RPC * x + L.c_row < valid ? -nd[x] : 0.f));
+      const float part = dot8(of[x], g[x]);
+      nd[x] = sum_row<Lane::C>(L.template in_row<x>() ? part : 0.f);
+    });
+    static_for<0, PT>([&](auto x_c) __attribute__((always_inline)) {
+      constexpr int x = decltype(x_c)::value;
+      if (L.lane % Lane::C == 0) lds_asm_write4(lds_addr(rows + 32 + RPC * x + L.c_row), (int)__float_as_uint(RPC * x + L.c_row < valid ? -nd[x] : 0.f));
     });
     if (L.lane < 32) lds_asm_write4(lds_addr(rows + L.lane), (int)__float_as_uint(L.lane < valid ? lse * kLog2e : INFINITY));
     load_rows(ahead);
@@ -447,8 +460,8 @@ __device__ __forceinline__ void share_dkv_block(const ShareParams& p, const chun
     s16x4 glo[2][DB], ghi[2][DB];  // operands of dV^T += dO^T P
     static_for<0, 2 * DB>([&](auto x_c) __attribute__((always_inline)) {
       constexpr int ks = decltype(x_c)::value / DB, db = decltype(x_c)::value % DB;
-      glo[ks][db] = lds_asm_read_tr<TILE + ks * 16 * D * 2>(ta ^ (db * 64));
-      ghi[ks][db] = lds_asm_read_tr<TILE + (ks * 16 + 8) * D * 2>(ta ^ (db * 64 + tile_swz<D>(8) * 16));
+      glo[ks][db] = lds_asm_read_tr<TILE + ks * 16 * Lane::ROW>(ta ^ (db * 64));
+      ghi[ks][db] = lds_asm_read_tr<TILE + (ks * 16 + 8) * Lane::ROW>(ta ^ (db * 64 + tile_swz<D>(8) * 16));
     });
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -469,8 +482,8 @@ __device__ __forceinline__ void share_dkv_block(const ShareParams& p, const chun
     s16x4 qlo[2][DB], qhi[2][DB];  // operands of dK^T += Q^T dS
     static_for<0, 2 * DB>([&](auto x_c) __attribute__((always_inline)) {
       constexpr int ks = decltype(x_c)::value / DB, db = decltype(x_c)::value % DB;
-      qlo[ks][db] = lds_asm_read_tr<ks * 16 * D * 2>(ta ^ (db * 64));
-      qhi[ks][db] = lds_asm_read_tr<(ks * 16 + 8) * D * 2>(ta ^ (db * 64 + tile_swz<D>(8) * 16));
+      qlo[ks][db] = lds_asm_read_tr<ks * 16 * Lane::ROW>(ta ^ (db * 64));
+      qhi[ks][db] = lds_asm_read_tr<(ks * 16 + 8) * Lane::ROW>(ta ^ (db * 64 + tile_swz<D>(8) * 16));
     });
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -576,7 +589,7 @@ hipError_t launch_bwd_share(const chunk_attn_desc* d, const BwdArgs& a, int wave
   ProfileEvents pe = profile_events();
   profile_events() = ProfileEvents{};
   if (pe.start && (e = hipEventRecord(pe.start, stream)) != hipSuccess) return e;
-  e = d->head_dim == 128 ? launch<128, 4>(s, stream) : waves == 8 ? launch<64, 8>(s, stream) : launch<64, 4>(s, stream);
+  e = d->head_dim == 128 ? launch<128, 4>(s, stream) : d->head_dim == 96 ? launch<96, 4>(s, stream) : waves == 8 ? launch<64, 8>(s, stream) : launch<64, 4>(s, stream);
   if (e == hipSuccess && pe.stop) e = hipEventRecord(pe.stop, stream);
   return e;
 }

@@ -27,7 +27,7 @@
 //                    128 has too few items for the chip their walks are cut into pieces (plan.hpp); the pieces leave
 //                    float32 partial results, which fwd_merge_kernel puts together.
 //   fwd_wide_kernel  head_dim 256: the same with 32 query rows per wave.
-//   fwd_share_kernel head_dim 64 and 128, small chunks (choose_shared_heads): the waves of a workgroup divide the keys of 32 rows.
+//   fwd_share_kernel head_dim 64, 96 and 128, small chunks (choose_shared_heads): the waves of a workgroup divide the keys of 32 rows.
 #include <cstring>
 #include <type_traits>
 
@@ -1290,6 +1290,8 @@ __global__ __launch_bounds__(256, 1) void fwd_wide_kernel(FwdArgs) {
 // Tiles are rows (a copy instruction fetches whole rows; chunk-major tiles touch up to eight times the cache lines): chunk c of row r sits at
 // c ^ share_swz(r), which serves 16-byte reads of 16 consecutive rows and transposed reads of four rows by four chunks without conflicts.
 // ------------------------------------------------------------------------------------------------
+// (head_dim 96: rows of 128 columns in LDS, whose last four chunks copy the last but them and are never read)
+constexpr int share_cols(int d) { return d == 96 ? 128 : d; }
 template <int D>
 __host__ __device__ constexpr int share_swz(int r) {
   return D == 64 ? ((r >> 3) & 1) | ((r >> 1) & 2) | ((r & 2) << 1) : ((r & 3) << 2) | ((r >> 2) & 3);
@@ -1297,21 +1299,22 @@ __host__ __device__ constexpr int share_swz(int r) {
 constexpr float kNoMax = -3.4028234e38f;  // reference maximum of a row that has seen no key yet
 template <int D, int HG, int KS, int NS>
 constexpr size_t share_smem() {  // the splits' slots of a K and a V tile and the heads' Q tiles, or each wave's O; a maximum and a sum per wave and row
-  const size_t tiles = (size_t)(KS * NS * 2 + HG) * 32 * D * 2, sums = (size_t)HG * KS * 32 * D * 4;
+  const size_t tiles = (size_t)(KS * NS * 2 + HG) * 32 * share_cols(D) * 2, sums = (size_t)HG * KS * 32 * D * 4;
   return (tiles > sums ? tiles : sums) + (size_t)HG * KS * 32 * 2 * sizeof(float);
 }
 
 template <int D, int HG, int KS, int NS>
 __global__ __launch_bounds__(HG * KS * 64, D == 64 ? 4 : HG * KS / 4) void fwd_share_kernel(FwdArgs) {
   constexpr int W = HG * KS;
-  constexpr int C = D / 8, DK = D / 16, DB = D / 32;
-  constexpr int TILE = 32 * D * 2;    // bytes of a tile
+  constexpr int ROW = share_cols(D) * 2;  // bytes of a row in LDS
+  constexpr int C = ROW / 16, DK = D / 16, DB = D / 32;
+  constexpr int TILE = 32 * ROW;      // bytes of a tile
   constexpr int PT = C / 2;           // copies of 64 chunks per tile
   constexpr int RPC = 64 / C;         // rows per copy
   constexpr int PPW = 2 * PT / HG;    // copies of a stage per wave
   constexpr int NQ = DB * 4;          // accumulator quarters of a head
-  constexpr int NQW = NQ / KS;        // of which a wave puts together
-  static_assert(NQ % KS == 0 && PPW % (D == 64 ? 2 : 4) == 0 && (HG == 1 || PT % PPW == 0));
+  constexpr int NQW = (NQ + KS - 1) / KS;  // of which a wave puts together: consecutive ones, or every KS-th where they do not divide evenly
+  static_assert(PPW % (D == 64 ? 2 : 4) == 0 && (HG == 1 || PT % PPW == 0));
   static_assert(HG == 1 ? NS <= 2 : NS == 2 || NS == 3);
   const FwdArgsPtr args = fwd_args();
   const FwdParams p = load_params(&args->p);
@@ -1338,13 +1341,17 @@ __global__ __launch_bounds__(HG * KS * 64, D == 64 ? 4 : HG * KS / 4) void fwd_s
 
   // copy i of a tile fills rows RPC i .. RPC (i + 1) - 1; a row's index splits into the lane's part and the copy's
   const int c_row = lane / C, c_chunk = (lane % C) ^ share_swz<D>(c_row);
+  auto column = [&](int row_of_copy) __attribute__((always_inline)) {  // of the lane's chunk
+    const int chunk = c_chunk ^ share_swz<D>(row_of_copy);
+    return (D == 96 ? min(chunk, D / 8 - 1) : chunk) * 8;
+  };
   // ---- Q: the waves of a head copy every KS-th piece of its tile ----
 #pragma unroll
   for (int x = 0; x < PT; x += KS) {
     const int i = x + split;
     if (PT % KS != 0 && i >= PT) break;
     const int row = min(RPC * i + c_row, it.q_rows - 1);  // rows past the tile repeat the last one (never stored)
-    dma16(p.q + (int64_t)(it.q_row0 + row) * q_stride + (int64_t)head * D + (c_chunk ^ share_swz<D>(RPC * i)) * 8,
+    dma16(p.q + (int64_t)(it.q_row0 + row) * q_stride + (int64_t)head * D + column(RPC * i),
           q_tiles + (unit * PT + i) * 512);
   }
   // ---- K and V: wave `unit` of a split copies pieces PPW unit .. + PPW - 1 of the 2 PT pieces of a stage (K, then V) ----
@@ -1364,12 +1371,12 @@ __global__ __launch_bounds__(HG * KS * 64, D == 64 ? 4 : HG * KS / 4) void fwd_s
       static_for<decltype(first_c)::value, decltype(end_c)::value>([&](auto x_c) __attribute__((always_inline)) {
         constexpr int x = decltype(x_c)::value, j = x % PT;
         const char* const row = reinterpret_cast<const char*>(src(x) + (int64_t)(RPC * j) * kv_stride);
-        dma16(row + (unsigned)(2 * c_off + 16 * (c_chunk ^ share_swz<D>(RPC * j))), dst + x * 512);
+        dma16(row + (unsigned)(2 * (c_off + column(RPC * j))), dst + x * 512);
       });
     } else {  // (rows past the last one repeat it)
       static_for<decltype(first_c)::value, decltype(end_c)::value>([&](auto x_c) __attribute__((always_inline)) {
         constexpr int x = decltype(x_c)::value, j = x % PT;
-        dma16(src(x) + (int64_t)min(RPC * j + c_row, last_row) * kv_stride + (c_chunk ^ share_swz<D>(RPC * j)) * 8, dst + x * 512);
+        dma16(src(x) + (int64_t)min(RPC * j + c_row, last_row) * kv_stride + column(RPC * j), dst + x * 512);
       });
     }
   };
@@ -1398,11 +1405,11 @@ __global__ __launch_bounds__(HG * KS * 64, D == 64 ? 4 : HG * KS / 4) void fwd_s
 
   // addresses inside a tile (bytes): rows (l32, chunk 2 ks + hh), k-steps an XOR apart; transposed: four rows by four chunks, blocks of
   // 32 columns an XOR apart, rows r + 8 another one
-  const unsigned row_at = (unsigned)(l32 * (D * 2) + ((hh ^ share_swz<D>(l32)) * 16));
+  const unsigned row_at = (unsigned)(l32 * ROW + ((hh ^ share_swz<D>(l32)) * 16));
   unsigned tr_at;
   {
     const int j = lane & 15, cl = 2 * ((lane >> 4) & 1) + ((j & 3) >> 1), r0 = 4 * hh + (j >> 2);
-    tr_at = (unsigned)(r0 * (D * 2) + ((cl ^ share_swz<D>(r0)) * 16) + 8 * (j & 1));
+    tr_at = (unsigned)(r0 * ROW + ((cl ^ share_swz<D>(r0)) * 16) + 8 * (j & 1));
   }
   bf16x8 qf[DK];
   {
@@ -1452,8 +1459,8 @@ __global__ __launch_bounds__(HG * KS * 64, D == 64 ? 4 : HG * KS / 4) void fwd_s
     auto read_v = [&]() __attribute__((always_inline)) {
       static_for<0, 2 * DB>([&](auto x_c) __attribute__((always_inline)) {
         constexpr int ks = decltype(x_c)::value / DB, db = decltype(x_c)::value % DB;
-        v_lo[ks][db] = lds_asm_read_tr<ks * 16 * D * 2>(va ^ (db * 64));
-        v_hi[ks][db] = lds_asm_read_tr<(ks * 16 + 8) * D * 2>(va ^ (db * 64 + share_swz<D>(8) * 16));
+        v_lo[ks][db] = lds_asm_read_tr<ks * 16 * ROW>(va ^ (db * 64));
+        v_hi[ks][db] = lds_asm_read_tr<(ks * 16 + 8) * ROW>(va ^ (db * 64 + share_swz<D>(8) * 16));
       });
     };
     if constexpr (HALVES) {
@@ -1501,7 +1508,7 @@ __global__ __launch_bounds__(HG * KS * 64, D == 64 ? 4 : HG * KS / 4) void fwd_s
     pf[0] = pack8(w[0], w[1], w[2], w[3], w[4], w[5], w[6], w[7]);
     pf[1] = pack8(w[8], w[9], w[10], w[11], w[12], w[13], w[14], w[15]);
     float ps0 = 0.f, ps1 = 0.f;
-    if constexpr (D == 64) {  // (the sums are those of fwd_kernel at 64, of the pipelined kernel at 128)
+    if constexpr (D == 64) {  // (the sums are those of fwd_kernel at 64, of the pipelined kernel at 96 and 128)
       bf16x2 ones;
       ones[0] = (__bf16)1.0f; ones[1] = (__bf16)1.0f;
 #pragma unroll
@@ -1550,7 +1557,8 @@ __global__ __launch_bounds__(HG * KS * 64, D == 64 ? 4 : HG * KS / 4) void fwd_s
     if (hh == 0) *(__attribute__((address_space(3))) f32x2*)(ml + (wave * 32 + l32) * 2) = f32x2{m_run, l};
   }
   __syncthreads();
-  const int quarter0 = split * NQW, parts = min(nt, KS);
+  constexpr int QS = NQ % KS == 0 ? 1 : KS;
+  const int quarter0 = NQ % KS == 0 ? split * NQW : split, parts = min(nt, KS);
   float m = kNoMax, l = 0.f;
   for (int w = 0; w < parts; ++w) m = fmaxf(m, ml[((w * HG + unit) * 32 + l32) * 2]);
   f32x4 o[NQW];
@@ -1563,7 +1571,8 @@ __global__ __launch_bounds__(HG * KS * 64, D == 64 ? 4 : HG * KS / 4) void fwd_s
     l += e[1] * f;
 #pragma unroll
     for (int x = 0; x < NQW; ++x) {
-      const f32x4 v = lds_load4f(src + w * (HG * NQ * 256) + x * 256);
+      if (QS > 1 && quarter0 + QS * x >= NQ) break;
+      const f32x4 v = lds_load4f(src + w * (HG * NQ * 256) + x * (QS * 256));
 #pragma unroll
       for (int r = 0; r < 4; ++r) o[x][r] += v[r] * f;
     }
@@ -1573,7 +1582,8 @@ __global__ __launch_bounds__(HG * KS * 64, D == 64 ? 4 : HG * KS / 4) void fwd_s
     __bf16* const op = p.o + (int64_t)(it.q_row0 + l32) * q_stride + (int64_t)head * D + 4 * hh;
 #pragma unroll
     for (int x = 0; x < NQW; ++x)
-      *reinterpret_cast<bf16x4*>(op + (quarter0 + x) * 8) = pack4(o[x][0] * inv, o[x][1] * inv, o[x][2] * inv, o[x][3] * inv);
+      if (QS == 1 || quarter0 + QS * x < NQ)
+        *reinterpret_cast<bf16x4*>(op + (quarter0 + QS * x) * 8) = pack4(o[x][0] * inv, o[x][1] * inv, o[x][2] * inv, o[x][3] * inv);
     if (split == 0 && hh == 0) p.lse[(int64_t)head * p.total_q + it.q_row0 + l32] = (m * c + log2f(l)) * 0.6931471805599453f;
   }
 }
@@ -1636,6 +1646,8 @@ hipError_t launch_fwd(const FwdParams& p, int head_dim, FwdKind kind, const FwdL
     const int heads = p.heads_per_wg;
     if (head_dim == 64)
       return heads == 4 ? launch_fwd_share<64, 4, 2, 3>(a, stream) : heads == 2 ? launch_fwd_share<64, 2, 4, 2>(a, stream) : launch_fwd_share<64, 1, 8, 2>(a, stream);
+    if (head_dim == 96)
+      return heads == 4 ? launch_fwd_share<96, 4, 2, 3>(a, stream) : heads == 2 ? launch_fwd_share<96, 2, 4, 2>(a, stream) : launch_fwd_share<96, 1, 8, 1>(a, stream);
     return heads == 4 ? launch_fwd_share<128, 4, 2, 3>(a, stream) : heads == 2 ? launch_fwd_share<128, 2, 4, 2>(a, stream) : launch_fwd_share<128, 1, 8, 1>(a, stream);
   }
   if (head_dim == 256) {

@@ -160,8 +160,8 @@ hipError_t launch_bwd_fused(const chunk_attn_desc* d, const BwdArgs& a, const Bw
 // Fills the offsets (and, if with_plan, the schedules) for a validated descriptor.  kCutInPlace: only where the partial results of each kind fit
 // the room that head_dim 96 and 128 keep for dQ tiles anyway (workspaces of that size may be known to callers); kCutNone: no walk is cut.
 enum Cut { kCutNone, kCutInPlace, kCutFine };
-// may_share: the kernel of the small chunks may run (share_waves > 0), which needs no schedule; the sizes are the other kernels' either way.
-void bwd_layout(const chunk_attn_desc* d, BwdPlan& plan, bool with_plan, Cut cut = kCutFine, bool may_share = false);
+// share_dim: not 0: the kernel of the small chunks may run (share_waves > 0), at this head_dim (d's is 128 for 96); it needs no schedule; the sizes are the other kernels' either way.
+void bwd_layout(const chunk_attn_desc* d, BwdPlan& plan, bool with_plan, Cut cut = kCutFine, int share_dim = 0);
 // The host image of the blob at the start of the workspace.
 std::vector<char> bwd_blob(const BwdPlan& plan);
 // Zeroes the rows of dK and dV that no segment covers, unless the call accumulates.

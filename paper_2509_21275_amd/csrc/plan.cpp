@@ -400,6 +400,8 @@ void choose_cut(const CutKind (&kinds)[N], int cus, const int64_t (&max_parts)[N
 // 8/8, 10.6 -> 6.0, 32/8, 11.1 -> 15.8, 9.3, 10.5; 100 queries on 10100 keys, 32/8, 124 -> 40, 62, 110; head_dim 128, 203 queries on 1704 keys with
 // 611 packed tokens, 32/8, 30.1 -> 26.1, 21.6, 31.7; eight sequences of 128, 32/8, 14.4 -> 18.1, 12.8, 9.7; 200 queries on 20200 keys, 32/8,
 // 90 -> 123, 192, 293 (walks cut over the whole chip).
+// the other kernels at head_dim 96 against those at 128, which the estimates are for (of 820 drawn chunks one then got slower, by 9 %; with 1 seven did, by up to 26 %)
+constexpr double kOther96Fwd = 0.85, kOther96Bwd = 0.86;
 constexpr int kLongSharedWalk = 40;
 struct SharedCost {
   double first, step, all_steps, workgroup, longest;  // first + max(step longest, all_steps steps + workgroup count + longest longest)
@@ -409,10 +411,10 @@ constexpr SharedCost kShared64[3] = {{3.2, 0.94, 1.17, 1.55, 0.13, 256}, {3.7, 0
 constexpr SharedCost kShared128[3] = {{4.0, 1.45, 1.94, 1.89, 0.0, 256}, {4.6, 1.17, 1.45, 2.47, 0.09, 256}, {5.9, 0.91, 1.12, 3.69, 0.06, 256}};
 
 int choose_shared_heads(const chunk_attn_desc* d, const Walks& other, int inner, bool pipelined, bool cut) {
-  if (!(d->head_dim == 128 && pipelined) && !(d->head_dim == 64 && !pipelined)) return 0;
+  if (d->head_dim > 128 || (d->head_dim == 64 && pipelined)) return 0;
   // (long walks that are not cut: enough blocks for the chip, and the pipelined kernel's steps are cheaper.  Walks of 40 - 73 stages gained 0 - 21 %
   // in the chunks drawn, shorter ones 17 - 170 %)
-  if (d->head_dim == 128 && !cut && other.longest > kLongSharedWalk) return 0;
+  if (d->head_dim != 64 && !cut && other.longest > kLongSharedWalk) return 0;
   int64_t items = 0;
   for (int t = 0; t < d->num_segments; ++t) {
     items += (d->segments[t].q_len + 31) / 32;
@@ -424,7 +426,7 @@ int choose_shared_heads(const chunk_attn_desc* d, const Walks& other, int inner,
                                             : 7.5 + std::max(all, std::min(longest, 8.0)) + 7.4 * blocks + 0.19 * std::min(longest, 103.0);
   const int group = d->num_q_heads / d->num_kv_heads;
   int best = 0;
-  double best_us = 0.95 * other_us;
+  double best_us = (d->head_dim == 96 ? kOther96Fwd : 1.0) * 0.95 * other_us;
   for (int x = 0; x < 3; ++x) {
     const int heads = 1 << x, splits = kSharedWaves / heads;
     if (group % heads != 0) break;
@@ -465,7 +467,7 @@ struct SharedBwdCost {
 constexpr SharedBwdCost kSharedBwd64[2] = {{4.5, 0.585, 1.11, 1.9, 0.69, 2.4, 0.18, 4, 512}, {4.1, 0.82, 1.82, 1.65, 1.31, 2.0, 0.2, 8, 256}};
 constexpr SharedBwdCost kSharedBwd128 = {6.3, 1.03, 1.84, 1.46, 1.74, 3.86, 0.08, 4, 256};
 
-int choose_shared_waves(const chunk_attn_desc* d, const Walks& dq, int inner, const Walks& dkv, bool cut) {
+int choose_shared_waves(const chunk_attn_desc* d, int head_dim, const Walks& dq, int inner, const Walks& dkv, bool cut) {
   if (d->num_segments > kMaxShareSegs) return 0;
   int64_t items = 0;
   for (int t = 0; t < d->num_segments; ++t) {
@@ -475,7 +477,7 @@ int choose_shared_waves(const chunk_attn_desc* d, const Walks& dq, int inner, co
   const double DL = (double)dq.longest, KL = (double)dkv.longest, DT = (double)dq.stages * inner / 256, KT = (double)dkv.stages * d->num_kv_heads / 256;
   const double blocks = (double)(dq.items * inner + dkv.items * d->num_kv_heads) / 256;
   double other;
-  if (d->head_dim == 64) {
+  if (head_dim == 64) {
     // (long dK/dV walks are cut evenly already; dQ walks are not)
     if (cut && dq.longest <= dkv.longest && dkv.longest > 32) return 0;
     other = cut ? 13.7 + 0.53 * std::min(KL, 8.7) + 0.35 * KT + 0.45 * DL
@@ -487,9 +489,9 @@ int choose_shared_waves(const chunk_attn_desc* d, const Walks& dq, int inner, co
   }
   const int group = d->num_q_heads / d->num_kv_heads;
   int best = 0;
-  double best_us = 0.86 * other;
-  for (int x = 0; x < (d->head_dim == 64 ? 2 : 1); ++x) {
-    const SharedBwdCost& c = d->head_dim == 64 ? kSharedBwd64[x] : kSharedBwd128;
+  double best_us = (head_dim == 96 ? kOther96Bwd : 1.0) * 0.86 * other;
+  for (int x = 0; x < (head_dim == 64 ? 2 : 1); ++x) {
+    const SharedBwdCost& c = head_dim == 64 ? kSharedBwd64[x] : kSharedBwd128;
     int64_t dq_most = 0, dkv_most = 0, dq_all = 0, dkv_all = 0, dq_items = 0, dkv_items = 0;
     auto add = [&](int64_t steps, int64_t& items_of_kind, int64_t& most, int64_t& all) {
       ++items_of_kind;

@@ -1,5 +1,5 @@
-"""Small chunks whose forward and backward divide the walks of 32 rows among the waves of a workgroup (head dimensions 64 and 128), at the edges of tiles,
-stages and shares: against the fp64 oracle (2e-2 for O as everywhere; LSE: 1.1e-4 at 128, a float32 sum of unrounded probabilities, and
+"""Small chunks whose forward and backward divide the walks of 32 rows among the waves of a workgroup (head dimensions 64, 96 and 128), at the edges of tiles,
+stages and shares: against the fp64 oracle (2e-2 for O as everywhere; LSE: 1.1e-4 at 96 and 128, a float32 sum of unrounded probabilities, and
 2^-9 + 1e-4 at 64, where they are summed as rounded to bf16), the static forward bit for bit, and the same bits on a second run.  Every
 case asserts how many heads share a workgroup."""
 import pytest
@@ -27,6 +27,11 @@ CASES = [  # head dimension, segments, query heads, key/value heads, heads per w
     (128, [(0, 500, 3, 500)], 32, 8, 2),
     (128, [(65 * i, 65, 65 * i, 65) for i in range(12)], 32, 8, 4),
     (128, [(0, 1175, 0, 1175)], 32, 8, 4),
+    (96, [(0, 1, 0, 1100)], 8, 2, 1),
+    (96, [(0, 64, 0, 1024), (64, 65, 1024, 1089)], 16, 2, 1),
+    (96, [(0, 257, 3, 257), (257, 31, 260, 288)], 8, 8, 1),
+    (96, [(0, 500, 3, 500)], 32, 8, 2),
+    (96, [(65 * i, 65, 65 * i, 65) for i in range(12)], 32, 8, 4),
 ]
 
 
@@ -54,6 +59,8 @@ def test_shared_keys(oracle_mod, d, segs, hq, hk, heads):
     again = run_gpu(case, q, k, v, backward=False)
     assert torch.equal(o, again[0]) and torch.equal(lse, again[1])
     _check(oracle_mod, case, q, k, v, o, lse)
+    if ca.chunk_attn_workspace_bytes(_desc(case))[0] > 16 << 20:
+        return  # too large for the static forward, whatever kernel runs
     o2, lse2 = torch.full_like(o, float("nan")), torch.full_like(lse, float("nan"))
     ca.chunk_attn_fwd_static(_desc(case), q, k, v, o2, lse2)
     torch.cuda.synchronize()
@@ -90,6 +97,9 @@ BWD_CASES = [  # head dimension, segments, query heads, key/value heads, waves p
     (128, [(0, 65, 0, 513), (65, 64, 515, 576)], 8, 2, 4),
     (128, [(0, 150, 2, 150)], 32, 8, 4),
     (128, [(0, 764, 0, 764)], 8, 8, 4),
+    (96, [(0, 1, 0, 40)], 1, 1, 4),
+    (96, [(0, 257, 3, 257), (257, 31, 260, 288)], 8, 8, 4),
+    (96, [(0, 65, 0, 513), (65, 64, 515, 576)], 8, 2, 4),
 ]
 
 
@@ -123,3 +133,30 @@ def test_shared_walks_of_the_backward(oracle_mod, d, segs, hq, hk, waves, f32kv,
         ca.chunk_attn_test_set_bwd_mode(0)
     for a, b in zip(got[2:], other[2:]):
         assert rel_err(a, b.double().cpu().numpy()) <= 2.0 ** -7
+
+
+@pytest.mark.parametrize("d", [64, 96, 128])
+@pytest.mark.parametrize("segs,hq,hk", [
+    ([(0, 32, 0, 32), (32, 33, 32, 33), (65, 64, 65, 64), (129, 1, 129, 129), (130, 95, 258, 95)], 2, 2),
+    ([(0, 40, 0, 127), (40, 40, 127, 128), (80, 40, 255, 129), (120, 200, 384, 513)], 8, 2),
+    ([(0, 65, 0, 193)], 6, 2),
+    ([(0, 96, 0, 640), (96, 160, 640, 160)], 16, 2),
+])
+def test_small_chunks_through_the_other_kernels(oracle_mod, d, segs, hq, hk):
+    """The kernels of larger chunks at the edges of their tiles and walks, which only small chunks have."""
+    case = _case(d, segs, hq, hk)
+    q, k, v, do = make_inputs(case)
+    ca.chunk_attn_test_set_bwd_mode(1)
+    try:
+        assert ca.chunk_attn_test_shared_heads(_desc(case)) == 0 and ca.chunk_attn_test_shared_waves(_desc(case)) == 0
+        o, lse, dq, dk, dv = run_gpu(case, q, k, v, do)
+    finally:
+        ca.chunk_attn_test_set_bwd_mode(0)
+    _check(oracle_mod, case, q, k, v, o, lse)
+    orc = oracle_mod.Oracle(case.segs, q.cpu(), k.cpu(), v.cpu(), do.cpu(), case.scale)
+    orc.forward()
+    dQ, dK, dV = orc.backward()
+    cov = torch.zeros(case.total_kv, dtype=torch.bool)
+    for s in segs:
+        cov[s[2]:s[2] + s[3]] = True
+    assert max(rel_err(dq, dQ), rel_err(dk.cpu()[cov], dK[cov.numpy()]), rel_err(dv.cpu()[cov], dV[cov.numpy()])) <= TOL_GRAD
