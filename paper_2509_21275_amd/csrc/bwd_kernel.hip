@@ -873,7 +873,7 @@ __device__ __forceinline__ void dkv_pipe_blocks(const ArgsPtr<DkvParams> args, c
   const int64_t q_stride = (int64_t)p.num_q_heads * D, kv_stride = (int64_t)p.num_kv_heads * D;
   const float c = p.scale_log2;
 
-  // zero everything but the ring slots the prologue fills
+  // zero everything but the ring slots of tiles that the prologue fills
   {
     bf16x8 z;
 #pragma unroll
@@ -882,11 +882,11 @@ __device__ __forceinline__ void dkv_pipe_blocks(const ArgsPtr<DkvParams> args, c
       lds_store8(L + Q_OFF + DIST * QT + x * 8, z);
       lds_store8(L + G_OFF + DIST * QT + x * 8, z);
     }
-    for (int x = tid; x < (R_OFF - P_OFF) / 8; x += NW * 64) lds_store8(L + P_OFF + x * 8, z);
-    // (row values of stages DIST .. NS - 1 only: a store to the first ones' by a wave that comes late would undo another wave's copy)
-    constexpr int ROWS = (NS - DIST) * RV * 2, ALL = NS * RV * 2;  // bf16 units of one set of row values
-    static_assert(2 * ROWS / 8 <= NW * 64);
-    if (tid < 2 * ROWS / 8) lds_store8(L + R_OFF + DIST * RV * 2 + (tid < ROWS / 8 ? tid * 8 : ALL - ROWS + tid * 8), z);
+    for (int x = tid; x < (LDS_ELEMS - P_OFF) / 8; x += NW * 64) lds_store8(L + P_OFF + x * 8, z);
+    // (the row values of the first stages are among it: a store by a wave that comes late would undo another wave's copy.  Leaving those out
+    // instead of waiting takes scalar registers that the steps then miss: last of eight slices of 128K 229.6 -> 231.6 ms)
+    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+    wg_barrier();
   }
 
   const int nqt = it.n_qt - it.qt_first;
