@@ -403,6 +403,7 @@ void choose_cut(const CutKind (&kinds)[N], int cus, const int64_t (&max_parts)[N
 // the other kernels at head_dim 96 against those at 128, which the estimates are for (of 820 drawn chunks one then got slower, by 9 %; with 1 seven did, by up to 26 %)
 constexpr double kOther96Fwd = 0.85, kOther96Bwd = 0.86;
 constexpr int kLongSharedWalk = 40;
+constexpr int kMaxSharedHeads = 4096;  // block counts and byte offsets inside a tile stay in 32 bits (no chunk of as many heads is small)
 struct SharedCost {
   double first, step, all_steps, workgroup, longest;  // first + max(step longest, all_steps steps + workgroup count + longest longest)
   int slots;                                          // workgroups on the chip at a time
@@ -411,7 +412,7 @@ constexpr SharedCost kShared64[3] = {{3.2, 0.94, 1.17, 1.55, 0.13, 256}, {3.7, 0
 constexpr SharedCost kShared128[3] = {{4.0, 1.45, 1.94, 1.89, 0.0, 256}, {4.6, 1.17, 1.45, 2.47, 0.09, 256}, {5.9, 0.91, 1.12, 3.69, 0.06, 256}};
 
 int choose_shared_heads(const chunk_attn_desc* d, const Walks& other, int inner, bool pipelined, bool cut) {
-  if (d->head_dim > 128 || (d->head_dim == 64 && pipelined)) return 0;
+  if (d->head_dim > 128 || (d->head_dim == 64 && pipelined) || d->num_q_heads > kMaxSharedHeads) return 0;
   // (long walks that are not cut: enough blocks for the chip, and the pipelined kernel's steps are cheaper.  Walks of 40 - 73 stages gained 0 - 21 %
   // in the chunks drawn, shorter ones 17 - 170 %)
   if (d->head_dim != 64 && !cut && other.longest > kLongSharedWalk) return 0;
@@ -468,7 +469,7 @@ constexpr SharedBwdCost kSharedBwd64[2] = {{4.5, 0.585, 1.11, 1.9, 0.69, 2.4, 0.
 constexpr SharedBwdCost kSharedBwd128 = {6.3, 1.03, 1.84, 1.46, 1.74, 3.86, 0.08, 4, 256};
 
 int choose_shared_waves(const chunk_attn_desc* d, int head_dim, const Walks& dq, int inner, const Walks& dkv, bool cut) {
-  if (d->num_segments > kMaxShareSegs) return 0;
+  if (d->num_segments > kMaxShareSegs || d->num_q_heads > kMaxSharedHeads) return 0;
   int64_t items = 0;
   for (int t = 0; t < d->num_segments; ++t) {
     items += (d->segments[t].q_len + 31) / 32 + ((int64_t)d->segments[t].kv_len + 31) / 32;
