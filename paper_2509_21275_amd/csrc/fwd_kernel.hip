@@ -1396,6 +1396,7 @@ __global__ __launch_bounds__(HG * KS * 64, D == 64 ? 4 : HG * KS / 4) void fwd_s
   for (int db = 0; db < DB; ++db) oacc[db] = zero16;
   float m_run = kNoMax, l_run = 0.f;
   const float c = p.scale_log2, limit = fminf(8.0f, p.ref_limit);
+  const float c_move = fmaxf(c, 1e-30f);  // moves the reference off kNoMax for every score, however small the scale is
 
   // the Q copies have landed when at most those of the stages are outstanding
   if (AHEAD > 1 && n_mine > 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(AHEAD * PPW) : "memory");
@@ -1490,7 +1491,7 @@ __global__ __launch_bounds__(HG * KS * 64, D == 64 ? 4 : HG * KS / 4) void fwd_s
     for (int e = 3; e < 15; e += 2) mx = fmaxf(fmaxf(mx, s[e]), s[e + 1]);
     mx = max_halves(fmaxf(mx, s[15]));
     // (the reference only has to keep exp2 in range, so it follows the maximum when that is 2^8 past it, as in fwd_kernel)
-    if (__builtin_expect(__any((mx - m_run) * c > limit), 0)) {
+    if (__builtin_expect(__any((mx - m_run) * c_move > limit), 0)) {
       const float m_new = fmaxf(m_run, mx);
       const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c);
       l_run *= alpha;

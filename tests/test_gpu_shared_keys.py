@@ -82,6 +82,22 @@ def test_shares_of_very_different_scores(oracle_mod, d, hq, hk):
     _check(oracle_mod, case, q, k, v, o, lse)
 
 
+@pytest.mark.parametrize("scale", [3e-38, 1e-38, 1e-44])
+@pytest.mark.parametrize("d,hq,hk", [(64, 8, 8), (64, 32, 8), (96, 8, 2), (128, 8, 8), (128, 32, 8)])
+def test_smallest_scales(d, hq, hk, scale):
+    """Any scale above zero is a valid one.  With these every score is zero in float32 (below 1e-34), so LSE is ln of the number of visible keys, and O
+    their mean; a share's reference has to be its maximum all the same, and not the value that stands for "no key yet"."""
+    n, ctx = 70, 300
+    case = _case(d, [(0, n, 0, ctx + n)], hq, hk)
+    assert ca.chunk_attn_test_shared_heads(_desc(case)) > 0
+    q, k, v, _ = make_inputs(case)
+    o, lse = run_gpu(case, q, k, v, scale=scale, backward=False)
+    visible = torch.arange(ctx + 1, ctx + n + 1, dtype=torch.float64)
+    assert float((lse.double().cpu() - visible.log()).abs().max()) <= 2.0 ** -19  # (log2 of an exact sum of ones below 2^9: an ulp of 2^-20, times ln 2)
+    mean = v[:ctx + n].double().cpu().cumsum(0)[ctx:] / visible.view(-1, 1, 1)
+    assert rel_err(o, mean.repeat_interleave(hq // hk, 1).numpy()) <= TOL_O
+
+
 BWD_CASES = [  # head dimension, segments, query heads, key/value heads, waves per workgroup
     (64, [(0, 1, 0, 40)], 1, 1, 4),
     (64, [(0, 33, 0, 33)], 8, 8, 4),
