@@ -129,7 +129,7 @@ int chunk_attn_fwd_static(const chunk_attn_desc* desc, const void* q, const void
  * Backward for the loss L = sum(o .* d_o): dq for every query row; dk, dv for every
  * key/value row including context rows (section 2.1: gradients of a token's key and value
  * come from the tokens after it).  o and lse must be the outputs of chunk_attn_fwd on the
- * same inputs.
+ * same inputs; dq, dk and dv may overlap them, but no other input.
  *
  * accumulate_dkv == 0: dk/dv rows inside some segment's key range are overwritten, all
  *   other rows are set to zero.

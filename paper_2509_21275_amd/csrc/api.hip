@@ -159,6 +159,10 @@ std::atomic<float> g_fwd_rescale_limit{60.0f};
 std::atomic<int> g_bwd_mode{0};
 std::atomic<unsigned long long*> g_clock_log{nullptr};
 
+inline bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x < y + b_bytes && y < x + a_bytes;
+}
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 // ---- head_dim 96 ----
@@ -703,7 +707,14 @@ int bwd_any(const chunk_attn_desc* desc, const void* q, const void* k, const voi
   const chunk_attn_desc w = widened(desc);
   BwdPlan P;
   auto needed = [&]() { return is_narrow(desc) ? narrow_bwd_layout(desc, P.total).total : P.total; };
-  bwd_layout(&w, P, true, kCutFine, bwd_mode() == 0 ? desc->head_dim : 0);
+  // Gradients may take the place of O and LSE, which the other kernels read before they write any; the small chunks' kernel reads both all along.
+  const size_t q_bytes = (size_t)desc->total_q * desc->num_q_heads * desc->head_dim * 2, lse_bytes = (size_t)desc->total_q * desc->num_q_heads * 4;
+  const size_t kv_bytes = (size_t)desc->total_kv * desc->num_kv_heads * desc->head_dim * (dkv_f32 ? 4 : 2);
+  auto in_place_of = [&](const void* x, size_t bytes) {
+    return overlap(x, bytes, dq, q_bytes) || overlap(x, bytes, dk, kv_bytes) || overlap(x, bytes, dv, kv_bytes);
+  };
+  const bool in_place = in_place_of(o, q_bytes) || in_place_of(lse, lse_bytes);
+  bwd_layout(&w, P, true, kCutFine, bwd_mode() == 0 && !in_place ? desc->head_dim : 0);
   if (workspace_bytes < needed()) bwd_layout(&w, P, true, kCutInPlace);  // too small for all partial results: fewer pieces, or
   if (workspace_bytes < needed()) bwd_layout(&w, P, true, kCutNone);     // none
   if (workspace_bytes < needed()) return CHUNK_ATTN_WORKSPACE_TOO_SMALL;

@@ -151,6 +151,34 @@ def test_shared_walks_of_the_backward(oracle_mod, d, segs, hq, hk, waves, f32kv,
         assert rel_err(a, b.double().cpu().numpy()) <= 2.0 ** -7
 
 
+@pytest.mark.parametrize("place", ["dq over o", "dk over o", "dv over o", "dq over lse"])
+@pytest.mark.parametrize("d", [64, 96, 128])
+def test_gradients_in_the_place_of_what_they_come_from(d, place):
+    """A caller may write a gradient over O or LSE.  The kernels that read both before they write any then run: the bits of buffers apart."""
+    n, heads = 257, 8
+    case = synth.ChunkCase("in_place", [synth.Seg(0, n, 0, n)], n, n, heads, heads, d, 318)
+    desc = _desc(case)
+    assert ca.chunk_attn_test_shared_waves(desc) > 0
+    q, k, v, do = make_inputs(case)
+    ca.chunk_attn_test_set_bwd_mode(1)
+    try:
+        o, lse, *want = run_gpu(case, q, k, v, do)
+    finally:
+        ca.chunk_attn_test_set_bwd_mode(0)
+    got = {"dq": torch.empty_like(q), "dk": torch.empty_like(k), "dv": torch.empty_like(v)}
+    grad, source = place.split(" over ")
+    if source == "o":
+        got[grad].copy_(o)
+        o = got[grad]
+    else:
+        inside = got[grad].view(-1)[:2 * lse.numel()].view(torch.float32).view(lse.shape)
+        inside.copy_(lse)
+        lse = inside
+    ca.chunk_attn_bwd(desc, q, k, v, o, do, lse, got["dq"], got["dk"], got["dv"], 0, ca.alloc_workspace(desc))
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(got.values(), want))
+
+
 @pytest.mark.parametrize("d", [64, 96, 128])
 @pytest.mark.parametrize("segs,hq,hk", [
     ([(0, 32, 0, 32), (32, 33, 32, 33), (65, 64, 65, 64), (129, 1, 129, 129), (130, 95, 258, 95)], 2, 2),
