@@ -392,42 +392,84 @@ void choose_cut(const CutKind (&kinds)[N], int cus, const int64_t (&max_parts)[N
 }
 }  // namespace
 
-// Times (us) of the two kinds of forward, least squares in the logarithm over 260 drawn chunks of up to 104 tiles of 32 rows (1 - 3000 queries, contexts
-// of up to 20000 keys, 4 - 64 heads), each measured with every choice: first + the larger of what the longest walk takes and what all workgroups
-// take together on the chip's slots.  Off by 5 - 13 % (root mean square); the choice they make was never slower than the
-// other kernel there, 1.65 (head_dim 64) and 1.68 (128) times as fast on average where the best choice of all would be 1.66 and 1.70.
+constexpr int kLongSharedWalk = 40;
+constexpr int kMaxSharedHeads = 4096;  // block counts and byte offsets inside a tile stay in 32 bits (no chunk of as many heads is small)
+
+// Times (us) of the two kinds of forward: first + the larger of what the longest walk takes and what all workgroups take together on the chip's slots.
+// Least squares in the logarithm over 8500 drawn chunks of up to 104 tiles of 32 rows (1 - 3300 queries, up to 6 contexts of up to 20000 keys, 1 - 128
+// query and 1 - 64 key/value heads), each measured with every choice, 5000 of them on tensors of the call before (in the caches where they fit) and
+// 3500 on tensors that come from memory.  Off by 5 - 13 % (root mean square).  At 96 and 128 a stage from memory costs this kernel more than the
+// other one (one head to a workgroup has room for a single slot per wave: its copies' latency shows), so there are two sets, and the choice has to be ahead by
+// both.  One set for tensors in the caches, at 5 % ahead, was up to 1.7 times slower than the other kernel where few queries meet thousands of
+// keys of many key/value heads (13 queries on 14478 keys, 64/64, head_dim 96: 104 -> 172; 4 on 7246, 128/16, 128: 49 -> 80).
+// With the shares of the other kernel's time that are asked for now, 15 of 11500 chosen chunks of other draws (in the caches and from memory) were
+// slower by more than 2 %, the worst by 17 % (71 query heads on one key/value head, 19 us instead of 16); all drawn chunks together 1.62 (head_dim 64),
+// 1.46 (96) and 1.51 (128) times as fast as without it (from memory 1.35, 1.34 and 1.36), where the best choice would be 1.66, 1.59 and 1.66 (1.37,
+// 1.40 and 1.42).
 // Examples, other kernel -> one, two, four heads: head_dim 64, 1024 tokens, 8/8 heads, 16.9 -> 7.9; four sequences of 512, 256, 128 and 128,
 // 8/8, 10.6 -> 6.0, 32/8, 11.1 -> 15.8, 9.3, 10.5; 100 queries on 10100 keys, 32/8, 124 -> 40, 62, 110; head_dim 128, 203 queries on 1704 keys with
 // 611 packed tokens, 32/8, 30.1 -> 26.1, 21.6, 31.7; eight sequences of 128, 32/8, 14.4 -> 18.1, 12.8, 9.7; 200 queries on 20200 keys, 32/8,
 // 90 -> 123, 192, 293 (walks cut over the whole chip).
-// the other kernels at head_dim 96 against those at 128, which the estimates are for (of 820 drawn chunks one then got slower, by 9 %; with 1 seven did, by up to 26 %)
-constexpr double kOther96Fwd = 0.85, kOther96Bwd = 0.86;
-constexpr int kLongSharedWalk = 40;
-constexpr int kMaxSharedHeads = 4096;  // block counts and byte offsets inside a tile stay in 32 bits (no chunk of as many heads is small)
 struct SharedCost {
-  double first, step, all_steps, workgroup, longest;  // first + max(step longest, all_steps steps + workgroup count + longest longest)
-  int slots;                                          // workgroups on the chip at a time
+  double first, step, all_steps, workgroup, longest, mb;  // first + max(step longest, all_steps steps + workgroup count + longest longest) + mb MB of K and V
+  int slots;                                              // workgroups on the chip at a time
+  double us(double most, double steps, double workgroups, double kv_mb) const {
+    return first + std::max(step * most, (all_steps * steps + workgroup * workgroups) / slots + longest * most) + mb * kv_mb;
+  }
 };
-constexpr SharedCost kShared64[3] = {{3.2, 0.94, 1.17, 1.55, 0.13, 256}, {3.7, 0.74, 1.04, 2.58, 0.41, 512}, {4.1, 0.67, 0.70, 3.23, 0.45, 512}};
-constexpr SharedCost kShared128[3] = {{4.0, 1.45, 1.94, 1.89, 0.0, 256}, {4.6, 1.17, 1.45, 2.47, 0.09, 256}, {5.9, 0.91, 1.12, 3.69, 0.06, 256}};
+// [tensors in the caches, from memory][one, two, four heads].  (At 96 and 128 the step of one head from memory is a line that few chunks lie above, 2.5 and
+// 2.8; the mean is 1.9 and 2.1.)
+constexpr SharedCost kShared64[2][3] = {
+    {{3.2, 0.80, 1.05, 1.64, 0.0, 0.08, 256}, {3.5, 0.74, 1.29, 2.38, 0.27, 0.021, 512}, {4.2, 0.64, 1.03, 3.22, 0.34, 0.054, 512}},
+    {{6.3, 1.14, 1.10, 2.06, 0.0, 0.441, 256}, {6.5, 1.0, 1.26, 3.16, 0.24, 0.621, 512}, {7.6, 0.64, 0.95, 4.59, 0.41, 0.05, 512}}};
+constexpr SharedCost kShared96[2][3] = {
+    {{3.7, 1.18, 1.63, 1.97, 0.0, 0.119, 256}, {3.9, 1.05, 1.22, 2.40, 0.126, 0.02, 256}, {4.9, 0.81, 0.94, 3.64, 0.09, 0.022, 256}},
+    {{6.4, 2.50, 1.65, 2.31, 0.33, 0.299, 256}, {6.7, 1.39, 1.25, 2.89, 0.21, 0.436, 256}, {8.5, 0.81, 0.90, 4.68, 0.20, 0.061, 256}}};
+constexpr SharedCost kShared128[2][3] = {
+    {{3.8, 1.23, 1.61, 2.17, 0.0, 0.088, 256}, {4.3, 1.17, 1.39, 2.67, 0.14, 0.03, 256}, {5.4, 0.96, 1.14, 4.13, 0.12, 0.009, 256}},
+    {{6.3, 2.80, 1.67, 2.49, 0.41, 0.234, 256}, {7.1, 1.51, 1.38, 3.20, 0.30, 0.324, 256}, {9.1, 0.95, 0.98, 5.34, 0.39, 0.033, 256}}};
+// The other kernels: that of 64, a workgroup per block, and the pipelined one of 96 and 128, whose walks are cut into pieces that even out.
+struct PlainFwdCost {
+  double first, walk, all, block, longest, mb;
+  double us(const Walks& w, double inner, double kv_mb) const {
+    const double per_cu = inner / 256;
+    return first + std::max(walk * w.longest, (all * w.stages + block * w.items) * per_cu + longest * w.longest) + mb * kv_mb;
+  }
+};
+struct PipeFwdCost {
+  double first, short_walk, block, longest, all, mb;
+  double us(const Walks& w, double inner, double kv_mb) const {
+    const double stages = (double)w.longest, per_cu = inner / 256;
+    return first + std::max(all * w.stages * per_cu, std::min(stages, short_walk)) + block * w.items * per_cu + longest * std::min(stages, 103.0) + mb * kv_mb;
+  }
+};
+constexpr PlainFwdCost kOther64[2] = {{4.0, 0.37, 0.186, 1.10, 0.32, 0.0}, {7.4, 0.38, 0.184, 1.74, 0.30, 0.196}};
+constexpr PipeFwdCost kOther96[2] = {{6.6, 8.3, 7.1, 0.137, 0.88, 0.0}, {11.0, 8.4, 8.8, 0.141, 0.91, 0.011}};
+constexpr PipeFwdCost kOther128[2] = {{7.5, 9.2, 7.6, 0.168, 1.0, 0.0}, {12.0, 9.2, 9.5, 0.157, 1.0, 0.047}};
+constexpr double kAheadFwd64[2] = {0.92, 0.92}, kAheadFwd[2] = {0.77, 0.96};  // shares of the other kernel's time
 
 int choose_shared_heads(const chunk_attn_desc* d, const Walks& other, int inner, bool pipelined, bool cut) {
   if (d->head_dim > 128 || (d->head_dim == 64 && pipelined) || d->num_q_heads > kMaxSharedHeads) return 0;
-  // (long walks that are not cut: enough blocks for the chip, and the pipelined kernel's steps are cheaper.  Walks of 40 - 73 stages gained 0 - 21 %
-  // in the chunks drawn, shorter ones 17 - 170 %)
+  // (long walks that are not cut: mostly enough blocks for the chip, and the pipelined kernel's steps are cheaper.  Of 247 drawn chunks 121 were slower
+  // with this kernel by more than 2 %, up to 2.8 times; 100 would gain more than 15 %, which the line gives away: few blocks that no cut takes)
   if (d->head_dim != 64 && !cut && other.longest > kLongSharedWalk) return 0;
   int64_t items = 0;
   for (int t = 0; t < d->num_segments; ++t) {
     items += (d->segments[t].q_len + 31) / 32;
     if (items > kMaxSharedItems) return 0;
   }
-  const double longest = (double)other.longest, all = (double)other.stages * inner / 256, blocks = (double)other.items * inner / 256;
-  // head_dim 64: the unpipelined kernel.  128: the pipelined one, whose walks are cut into pieces that even out
-  const double other_us = d->head_dim == 64 ? 3.85 + std::max(0.37 * longest, 0.12 * all + 1.36 * blocks + 0.36 * longest)
-                                            : 7.5 + std::max(all, std::min(longest, 8.0)) + 7.4 * blocks + 0.19 * std::min(longest, 103.0);
+  int64_t keys = 0;
+  for (int t = 0; t < d->num_segments; ++t) keys += d->segments[t].kv_len;
+  const double kv_mb = (double)keys * d->num_kv_heads * d->head_dim * 4e-6;
+  double limit[2];  // what the shared kernel may take
+  for (int m = 0; m < 2; ++m)
+    limit[m] = d->head_dim == 64   ? kAheadFwd64[m] * kOther64[m].us(other, inner, kv_mb)
+               : d->head_dim == 96 ? kAheadFwd[m] * kOther96[m].us(other, inner, kv_mb)
+                                   : kAheadFwd[m] * kOther128[m].us(other, inner, kv_mb);
+  const SharedCost(&costs)[2][3] = d->head_dim == 64 ? kShared64 : d->head_dim == 96 ? kShared96 : kShared128;
   const int group = d->num_q_heads / d->num_kv_heads;
   int best = 0;
-  double best_us = (d->head_dim == 96 ? kOther96Fwd : 1.0) * 0.95 * other_us;
+  double best_share = 1.0;
   for (int x = 0; x < 3; ++x) {
     const int heads = 1 << x, splits = kSharedWaves / heads;
     if (group % heads != 0) break;
@@ -440,17 +482,18 @@ int choose_shared_heads(const chunk_attn_desc* d, const Walks& other, int inner,
         most = std::max(most, n);
       }
     }
-    const SharedCost& c = d->head_dim == 64 ? kShared64[x] : kShared128[x];
-    const double per_slot = (double)(d->num_q_heads / heads) / c.slots;
-    const double us = c.first + std::max(c.step * most, c.all_steps * steps * per_slot + c.workgroup * items * per_slot + c.longest * most);
-    if (us < best_us) {
-      best_us = us;
+    const double wgs = (double)(d->num_q_heads / heads);
+    double now = 0.0;
+    for (int m = 0; m < 2; ++m) now = std::max(now, costs[m][x].us((double)most, steps * wgs, items * wgs, kv_mb) / limit[m]);
+    if (now < best_share) {
+      best_share = now;
       best = heads;
     }
   }
   return best;
 }
 
+constexpr double kOther96Bwd = 0.86;  // the other kernels at head_dim 96 against those at 128, which the estimate is for
 // The same for the backward (us; 1290 drawn chunks, the bounds of this function aside): first + the larger of what the longest dQ walk, the longest
 // dK/dV walk and all workgroups together take.  Off by 5 - 10 % (root mean square), so it is chosen where it is 14 % ahead by the estimate: in 780
 // of those chunks, none of them slower (at 10 % ahead 3, at 6 % 9), and 2.0 (head_dim 64) and 1.5 (128) times as fast on average over the chunks within

@@ -136,6 +136,22 @@ def test_routes(ca, segs, Hq, Hkv, dim, fwd, dq, dkv):
     assert (ca.ROUTE_FWD_CUT, ca.ROUTE_DQ_PIPELINED, ca.ROUTE_DKV_PIPELINED, ca.ROUTE_ONE_PASS) == (2, 4, 16, 64)
 
 
+@pytest.mark.parametrize("dim,Hq,Hkv,segs,heads,waves", [
+    # few queries on thousands of keys: the other kernels cut these walks over the whole chip, and were up to 1.7 times as fast
+    (96, 64, 64, [(0, 13, 0, 14478)], 0, 0), (128, 32, 32, [(0, 33, 0, 7207), (33, 13, 7207, 17827)], 0, 0), (128, 128, 16, [(0, 4, 0, 7246)], 0, 0),
+    (128, 1, 1, [(0, 4, 0, 3733)], 0, 0),
+    # and what they are for
+    (64, 8, 8, packed(256, 512, 128, 128), 1, 4), (64, 32, 8, [(0, 100, 0, 10100)], 1, 4), (96, 8, 8, packed(500), 1, 4), (128, 8, 8, packed(500), 1, 4),
+    (128, 32, 8, [(0, 203, 0, 1704), (203, 246, 1704, 246), (449, 145, 1950, 145), (594, 220, 2095, 220)], 2, 0), (128, 32, 8, packed(*[128] * 8), 4, None),
+])
+def test_small_chunks_run_the_shared_kernels_where_those_are_faster(ca, dim, Hq, Hkv, segs, heads, waves):
+    d = desc(ca, segs, Hq=Hq, Hkv=Hkv, d=dim)
+    if heads is not None:
+        assert ca.chunk_attn_test_shared_heads(d) == heads
+    if waves is not None:
+        assert ca.chunk_attn_test_shared_waves(d) == waves
+
+
 @pytest.mark.parametrize("segs,kw,code", [
     ([(0, 0, 0, 4)], {"tq": 4}, "BAD_SEGMENT"),                        # empty query range
     ([(0, 8, 0, 4)], {}, "BAD_SEGMENT"),                          # fewer keys than queries
