@@ -493,11 +493,14 @@ int choose_shared_heads(const chunk_attn_desc* d, const Walks& other, int inner,
   return best;
 }
 
-constexpr double kOther96Bwd = 0.86;  // the other kernels at head_dim 96 against those at 128, which the estimate is for
-// The same for the backward (us; 1290 drawn chunks, the bounds of this function aside): first + the larger of what the longest dQ walk, the longest
-// dK/dV walk and all workgroups together take.  Off by 5 - 10 % (root mean square), so it is chosen where it is 14 % ahead by the estimate: in 780
-// of those chunks, none of them slower (at 10 % ahead 3, at 6 % 9), and 2.0 (head_dim 64) and 1.5 (128) times as fast on average over the chunks within
-// the bounds, where the best choice would be as much within 1 %.
+// The same for the backward: first + the larger of what the longest dQ walk, the longest dK/dV walk and all workgroups together take, least
+// squares over 1290 drawn chunks, off by 5 - 10 % (root mean square).  The other kernels' estimates of 96 and 128 are off by 8 - 19 %, most where few
+// queries meet a few thousand keys and both kinds of walk are cut (they take 33 us there where 48 are estimated), so what is asked for is well ahead; 96 is
+// estimated as 128.  At 14 % ahead (26 % at 96) 113 of 8500 chosen chunks of other draws were slower by more than 2 %, by up to 38 % (17 queries on 1551 keys in two
+// sequences, 128/16 heads, head_dim 128: 35.5 -> 48.9; 7 on 2747, 64/8: 33 -> 40; 38 on 2460, 32/8, 96: 31.1 -> 34.0); with the shares asked for now 2 of 9800, by 6 %.
+// All drawn chunks together, 5000 on the tensors of the call before, are 1.66 (head_dim 64), 1.31 (96) and 1.36 (128) times as fast as without it, where the best
+// choice would be 1.76, 1.51 and 1.56 (2500 on tensors from memory, none slower: 1.58, 1.32 and 1.33 of 1.67, 1.49 and 1.51).
+constexpr double kAheadBwd64 = 0.80, kAheadBwd96 = 0.62, kAheadBwd128 = 0.68;  // shares of the other kernels' time
 // Examples, other kernels -> this one: head_dim 64, 8/8 heads, 64 tokens, 8.7 -> 5.3, sequences of 256, 512, 128 and 128, 19.5 -> 10.4, 1024 tokens, 29.4 ->
 // 15.7; 100 queries on 10100 keys, 32/8, 175 -> 72; head_dim 128, 8/8, 500 tokens, 33.4 -> 14.7, 1000, 46.7 -> 27.8, 100 queries on 1100 keys, 45 -> 17.
 struct SharedBwdCost {
@@ -522,18 +525,22 @@ int choose_shared_waves(const chunk_attn_desc* d, int head_dim, const Walks& dq,
   const double blocks = (double)(dq.items * inner + dkv.items * d->num_kv_heads) / 256;
   double other;
   if (head_dim == 64) {
-    // (long dK/dV walks are cut evenly already; dQ walks are not)
+    // (long dK/dV walks are cut evenly already; dQ walks are not.  Of 393 drawn chunks 120 were slower with this kernel by more than 2 %, up to 3.1
+    // times, and 190 would gain more than 15 %, up to 2.6 times, which the line gives away)
     if (cut && dq.longest <= dkv.longest && dkv.longest > 32) return 0;
     other = cut ? 13.7 + 0.53 * std::min(KL, 8.7) + 0.35 * KT + 0.45 * DL
                 : 7.1 + std::max({0.49 * DL, 0.73 * KL, 0.81 * KT + 2.1 * blocks + 0.4 * std::max(DL, KL)});
   } else {
-    if (!cut && dq.longest > kLongSharedWalk) return 0;  // (as in the forward)
+    // (as in the forward.  Of 647 drawn chunks 183 were slower by more than 2 %, up to 2.2 times; 439 would gain more than 15 %, up to 3.2 times, which the
+    // line gives away: few queries on a long context, whose dQ walks find no room for partial results, 10 on 14018 keys, 8/8 heads, head_dim 128,
+    // 377 us where this kernel takes 118)
+    if (!cut && dq.longest > kLongSharedWalk) return 0;
     other = cut ? 23.1 + 0.75 * std::min(DL, 9.0) + 0.19 * std::min(KL, 36.0) + 1.58 * DT + 0.98 * KT + 8.2 * blocks + 0.028 * DL
                 : 17.0 + std::max({0.72 * DL, 0.95 * KL, 2.53 * DT + 0.58 * KT + 14.8 * blocks});
   }
   const int group = d->num_q_heads / d->num_kv_heads;
   int best = 0;
-  double best_us = (head_dim == 96 ? kOther96Bwd : 1.0) * 0.86 * other;
+  double best_us = (head_dim == 64 ? kAheadBwd64 : head_dim == 96 ? kAheadBwd96 : kAheadBwd128) * other;
   for (int x = 0; x < (head_dim == 64 ? 2 : 1); ++x) {
     const SharedBwdCost& c = head_dim == 64 ? kSharedBwd64[x] : kSharedBwd128;
     int64_t dq_most = 0, dkv_most = 0, dq_all = 0, dkv_all = 0, dq_items = 0, dkv_items = 0;

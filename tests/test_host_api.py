@@ -139,7 +139,10 @@ def test_routes(ca, segs, Hq, Hkv, dim, fwd, dq, dkv):
 @pytest.mark.parametrize("dim,Hq,Hkv,segs,heads,waves", [
     # few queries on thousands of keys: the other kernels cut these walks over the whole chip, and were up to 1.7 times as fast
     (96, 64, 64, [(0, 13, 0, 14478)], 0, 0), (128, 32, 32, [(0, 33, 0, 7207), (33, 13, 7207, 17827)], 0, 0), (128, 128, 16, [(0, 4, 0, 7246)], 0, 0),
-    (128, 1, 1, [(0, 4, 0, 3733)], 0, 0),
+    (128, 1, 1, [(0, 4, 0, 3733)], 0, 0), (128, 64, 8, [(0, 7, 0, 2747)], None, 0), (96, 64, 8, [(0, 15, 0, 2381)], None, 0),
+    (96, 32, 8, [(0, 38, 0, 2460)], None, 0), (128, 128, 16, [(0, 2, 0, 1125), (2, 15, 1125, 426)], None, 0), (128, 8, 8, [(0, 499, 0, 2440)], None, 0),
+    # many short walks of many key/value heads
+    (128, 64, 64, packed(51, 26, *[89] * 25), None, 0), (128, 64, 64, [(0, 189, 0, 264)], None, 0),
     # and what they are for
     (64, 8, 8, packed(256, 512, 128, 128), 1, 4), (64, 32, 8, [(0, 100, 0, 10100)], 1, 4), (96, 8, 8, packed(500), 1, 4), (128, 8, 8, packed(500), 1, 4),
     (128, 32, 8, [(0, 203, 0, 1704), (203, 246, 1704, 246), (449, 145, 1950, 145), (594, 220, 2095, 220)], 2, 0), (128, 32, 8, packed(*[128] * 8), 4, None),
