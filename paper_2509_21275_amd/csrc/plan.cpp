@@ -514,13 +514,14 @@ struct SharedBwdCost {
 constexpr SharedBwdCost kSharedBwd64[2] = {{4.5, 0.585, 1.11, 1.9, 0.69, 2.4, 0.18, 4, 512}, {4.1, 0.82, 1.82, 1.65, 1.31, 2.0, 0.2, 8, 256}};
 constexpr SharedBwdCost kSharedBwd128 = {6.3, 1.03, 1.84, 1.46, 1.74, 3.86, 0.08, 4, 256};
 
-int choose_shared_waves(const chunk_attn_desc* d, int head_dim, const Walks& dq, int inner, const Walks& dkv, bool cut) {
-  if (d->num_segments > kMaxShareSegs || d->num_q_heads > kMaxSharedHeads) return 0;
+bool shared_backward_fits(const chunk_attn_desc* d) {
+  if (d->num_segments > kMaxShareSegs || d->num_q_heads > kMaxSharedHeads) return false;
   int64_t items = 0;
-  for (int t = 0; t < d->num_segments; ++t) {
-    items += (d->segments[t].q_len + 31) / 32 + ((int64_t)d->segments[t].kv_len + 31) / 32;
-    if (items > kMaxShareItems) return 0;
-  }
+  for (int t = 0; t < d->num_segments; ++t) items += (d->segments[t].q_len + 31) / 32 + ((int64_t)d->segments[t].kv_len + 31) / 32;
+  return items <= kMaxShareItems;
+}
+
+int choose_shared_waves(const chunk_attn_desc* d, int head_dim, const Walks& dq, int inner, const Walks& dkv, bool cut) {
   const double DL = (double)dq.longest, KL = (double)dkv.longest, DT = (double)dq.stages * inner / 256, KT = (double)dkv.stages * d->num_kv_heads / 256;
   const double blocks = (double)(dq.items * inner + dkv.items * d->num_kv_heads) / 256;
   double other;

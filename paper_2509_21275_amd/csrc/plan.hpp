@@ -150,9 +150,11 @@ struct ShareBlock {
 };
 constexpr int kMaxShareSegs = 64, kMaxShareItems = 640;
 std::vector<ShareBlock> share_blocks(const chunk_attn_desc* d, bool keys);
+// Whether the kernel arguments have room for a chunk's blocks and its block counts stay in 32 bits.
+bool shared_backward_fits(const chunk_attn_desc* d);
 // Waves per workgroup (4, or 8 at head_dim 64) of the backward whose waves divide the walks of 32-row blocks, where it ends sooner by the
 // estimate of plan.cpp than the head dimension's other kernels, whose walks are `dq` (each run for `inner` pairs) and `dkv` (for each
-// key/value head), some of them cut or none; 0 where it does not.  (`head_dim`: that of the tensors; d's is 128 for 96.)
+// key/value head), some of them cut or none; 0 where it does not.  For chunks that fit.  (`head_dim`: that of the tensors; d's is 128 for 96.)
 int choose_shared_waves(const chunk_attn_desc* d, int head_dim, const Walks& dq, int inner, const Walks& dkv, bool cut);
 // The same for the key-stationary items (`keys` keys each) of one key/value head; a stage is a 32-row query tile of one head.
 Walks count_dkv_walks(const chunk_attn_desc* d, int keys);

@@ -88,6 +88,35 @@ static int check_plan_cover(unsigned seed) {
     }
     REQUIRE(got == want);
   }
+  // the small chunks' backward: every 32-row tile of queries and of keys once, longest walk first, with the steps that its kernel counts: stages of
+  // 32 keys up to the last visible one; (query tile, head of the group) pairs that see a key of the tile
+  if (chunk_attn::shared_backward_fits(&d)) {
+    REQUIRE(n_seg <= chunk_attn::kMaxShareSegs);
+    size_t n_blocks = 0;
+    for (const bool keys : {false, true}) {
+      const auto blocks = chunk_attn::share_blocks(&d, keys);
+      n_blocks += blocks.size();
+      std::vector<std::vector<int>> seen(n_seg);
+      for (int t = 0; t < n_seg; ++t) seen[t].assign(((keys ? segs[t].kv_len : segs[t].q_len) + 31) / 32, 0);
+      for (size_t b = 0; b < blocks.size(); ++b) {
+        REQUIRE(b == 0 || blocks[b - 1].steps >= blocks[b].steps);
+        REQUIRE(blocks[b].seg >= 0 && blocks[b].seg < n_seg);
+        REQUIRE(blocks[b].tile >= 0 && blocks[b].tile < (int)seen[blocks[b].seg].size());
+        ++seen[blocks[b].seg][blocks[b].tile];
+        const auto& s = segs[blocks[b].seg];
+        const int C = s.kv_len - s.q_len, r0 = 32 * blocks[b].tile;
+        int steps = 0;
+        if (keys)
+          for (int qt = 0; 32 * qt < s.q_len; ++qt) steps += C + std::min(32 * qt + 32, s.q_len) - 1 >= r0 ? d.num_q_heads / d.num_kv_heads : 0;
+        else
+          steps = (C + std::min(r0 + 32, s.q_len) + 31) / 32;
+        REQUIRE(blocks[b].steps == steps && steps > 0);
+      }
+      for (const auto& tiles : seen)
+        for (int x : tiles) REQUIRE(x == 1);
+    }
+    REQUIRE(n_blocks <= (size_t)chunk_attn::kMaxShareItems);
+  }
   // the one-pass backward's plan: the same cover, and chains in which every block follows a block that sees at least
   // the query tiles it sees, pinned to one XCD and handed out after its predecessor
   for (int bufs : {1, 2, 4}) {

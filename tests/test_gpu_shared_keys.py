@@ -20,6 +20,7 @@ CASES = [  # head dimension, segments, query heads, key/value heads, heads per w
     (64, [(0, 700, 2, 700), (700, 33, 705, 400)], 32, 8, 2),
     (64, [(0, 181, 0, 187), (181, 23, 187, 579), (204, 3, 766, 4), (207, 6, 770, 606), (213, 102, 1376, 581)], 48, 12, 4),
     (128, [(0, 1, 0, 1)], 1, 1, 1),
+    (128, [(0, 32, 0, 32)], 4096, 8, 4),
     (128, [(0, 1, 0, 1100)], 8, 2, 1),
     (128, [(0, 257, 0, 2000)], 3, 3, 1),
     (128, [(0, 64, 0, 1024), (64, 65, 1024, 1089)], 16, 2, 1),
@@ -107,6 +108,9 @@ BWD_CASES = [  # head dimension, segments, query heads, key/value heads, waves p
     (64, [(0, 365, 2, 513), (365, 64, 515, 576), (429, 1, 1091, 545)], 16, 8, 4),
     (64, [(97 * i, 97, 97 * i, 97) for i in range(10)], 8, 2, 4),
     (64, [(0, 31, 0, 1000), (31, 95, 1003, 127)], 6, 2, 8),
+    (64, [(32 * i, 32, 288 * i, 288) for i in range(64)], 1, 1, 4),            # as many segments and tiles as the arguments have room for
+    (128, [(32 * i, 32, 288 * i, 288) for i in range(64)], 1, 1, 4),
+    (128, [(0, 32, 0, 32)], 4096, 8, 4),                                      # as many heads
     (128, [(0, 1, 0, 40)], 1, 1, 4),
     (128, [(0, 33, 0, 65)], 3, 3, 4),
     (128, [(0, 257, 3, 257), (257, 31, 260, 288)], 8, 8, 4),

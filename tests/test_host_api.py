@@ -155,6 +155,26 @@ def test_small_chunks_run_the_shared_kernels_where_those_are_faster(ca, dim, Hq,
         assert ca.chunk_attn_test_shared_waves(d) == waves
 
 
+def contexts(n, last=288):
+    """n segments of 32 queries on 288 keys (10 tiles of 32 rows each), the last one on `last` keys."""
+    return [(32 * i, 32, 288 * i, last if i == n - 1 else 288) for i in range(n)]
+
+
+@pytest.mark.parametrize("dim", [64, 96, 128])
+def test_bounds_of_the_small_chunks_kernels(ca, dim):
+    """What their kernel arguments have room for (104 tiles of 32 query rows in the forward; 64 segments, 640 tiles of queries and keys in the
+    backward), and the number of heads up to which their offsets stay in 32 bits: taken at the bound, left to the other kernels one past it."""
+    heads = lambda segs, Hq=1, Hkv=1: ca.chunk_attn_test_shared_heads(desc(ca, segs, Hq, Hkv, dim))
+    waves = lambda segs, Hq=1, Hkv=1: ca.chunk_attn_test_shared_waves(desc(ca, segs, Hq, Hkv, dim))
+    assert heads(packed(*[20] * 104)) == 1 and heads(packed(*[20] * 105)) == 0
+    assert heads(packed(*[20] * 103, 33)) == 0
+    assert waves(packed(*[20] * 64)) == 4 and waves(packed(*[20] * 65)) == 0
+    assert waves(contexts(64)) == 4 and waves(contexts(64, last=289)) == 0
+    one = [(0, 1, 0, 1)]
+    assert waves(one, 4096, 8) > 0 and waves(one, 8192, 8) == 0
+    assert heads(one, 8192, 8) == 0 and (dim == 64 or heads(one, 4096, 8) == 4)
+
+
 @pytest.mark.parametrize("segs,kw,code", [
     ([(0, 0, 0, 4)], {"tq": 4}, "BAD_SEGMENT"),                        # empty query range
     ([(0, 8, 0, 4)], {}, "BAD_SEGMENT"),                          # fewer keys than queries
