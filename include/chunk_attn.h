@@ -223,12 +223,11 @@ int chunk_attn_measure_mfma_rate_on(int milliseconds, int workgroups, void* scra
 int chunk_attn_measure_set_clock_log(void* device_buffer, size_t bytes);
 
 /*
- * Test and measurement hook: which backward chunk_attn_bwd / chunk_attn_bwd_f32kv run for head_dim 128.
- * 0: the library's choice; 1: two kernels (dQ query-stationary, dK/dV key-stationary, P recomputed in both);
- * 2: one pass (the key-stationary kernel also forms dQ and adds it into float32 tiles in the workspace in a fixed
- * order).  Same results up to the order of float32 additions in dQ; both are bit-reproducible.  Process-wide; the
- * workspace size does not depend on it.  In modes 1 and 2 the kernels of small chunks (chunk_attn_test_shared_heads, _waves) stay out of the way,
- * in the forward as well and for every head_dim.  Returns CHUNK_ATTN_INVALID_ARG for any other value.
+ * Test and measurement hook: which kernels the library may run.  0: its choice.  1: not the small chunks' kernels (CHUNK_ATTN_ROUTE_FWD_SHARED and
+ * _BWD_SHARED), neither forward nor backward, whatever the head_dim: what larger chunks run, the backward as two kernels (dQ query-stationary, dK/dV
+ * key-stationary, P recomputed in both).  2: as 1, and for head_dim 96 and 128 the backward in one pass (the key-stationary kernel also forms dQ and
+ * adds it into float32 tiles in the workspace in a fixed order).  Same results up to the order of float32 additions and the rounding of P and dS;
+ * all are bit-reproducible.  Process-wide; the workspace size does not depend on it.  Returns CHUNK_ATTN_INVALID_ARG for any other value.
  */
 int chunk_attn_test_set_bwd_mode(int mode);
 
@@ -242,8 +241,8 @@ int chunk_attn_test_set_bwd_mode(int mode);
 int chunk_attn_test_bwd_status_offset(const chunk_attn_desc* desc, size_t* offset);
 
 /*
- * Test hook: which kernels chunk_attn_fwd and chunk_attn_bwd choose for `desc` (given workspaces of the reported sizes), as
- * a sum of the bits below.  Decided on the host from the descriptor alone (and, for the last bit, the backward mode).
+ * Test hook: which kernels chunk_attn_fwd and chunk_attn_bwd run for `desc` (given workspaces of the reported sizes, and gradients that overlap neither
+ * o nor lse), as a sum of the bits below.  Decided on the host from the descriptor and the backward mode alone.
  */
 #define CHUNK_ATTN_ROUTE_FWD_PIPELINED 1 /* software-pipelined forward of head_dim 64, 96 and 128 (256 has one kernel only) */
 #define CHUNK_ATTN_ROUTE_FWD_CUT 2       /* some of its walks over the keys are cut into pieces */
@@ -252,12 +251,12 @@ int chunk_attn_test_bwd_status_offset(const chunk_attn_desc* desc, size_t* offse
 #define CHUNK_ATTN_ROUTE_DKV_PIPELINED 16
 #define CHUNK_ATTN_ROUTE_DKV_CUT 32      /* some of its walks over the query tiles are cut */
 #define CHUNK_ATTN_ROUTE_ONE_PASS 64     /* one-pass backward instead of the dQ and dK/dV kernels */
+#define CHUNK_ATTN_ROUTE_FWD_SHARED 128  /* small chunk: the waves of a workgroup divide the keys of 32 rows (and neither bit of the forward above) */
+#define CHUNK_ATTN_ROUTE_BWD_SHARED 256  /* small chunk: they divide the walks of the backward, one launch (and none of its bits above) */
 int chunk_attn_test_routes(const chunk_attn_desc* desc, int32_t* routes);
-/* Test hook (host only): query heads per workgroup where the forward of a small chunk divides the keys of 32 rows among the waves of a
- * workgroup (1, 2 or 4; the routes above are then those of a workspace too small for the reported size), else 0. */
+/* Test hook (host only): query heads per workgroup of the small chunks' forward (1, 2 or 4), 0 where another kernel runs. */
 int chunk_attn_test_shared_heads(const chunk_attn_desc* desc, int32_t* heads);
-/* Test hook (host only): waves per workgroup where the backward of a small chunk divides its walks among the waves of a workgroup, in one
- * launch (4 or 8), else 0. */
+/* Test hook (host only): waves per workgroup of the small chunks' backward (4 or 8), 0 where the other kernels run. */
 int chunk_attn_test_shared_waves(const chunk_attn_desc* desc, int32_t* waves);
 
 /* Static description of an error code; for CHUNK_ATTN_HIP_ERROR includes the last HIP error text. */

@@ -253,18 +253,18 @@ def clock_log_sums(buffer) -> dict:
 
 
 def chunk_attn_test_set_bwd_mode(mode: int) -> None:
-    """Test hook: 0 = library's choice, 1 = two-kernel backward, 2 = one-pass backward (head_dim 128)."""
+    """Test hook: 0 = library's choice, 1 = the kernels of larger chunks whatever the size, 2 = as 1, with the one-pass backward (head_dim 96, 128)."""
     rc = _lib.chunk_attn_test_set_bwd_mode(ctypes.c_int(mode))
     if rc != 0:
         raise ChunkAttnError(rc)
 
 
-ROUTE_FWD_PIPELINED, ROUTE_FWD_CUT, ROUTE_DQ_PIPELINED, ROUTE_DQ_CUT, ROUTE_DKV_PIPELINED, ROUTE_DKV_CUT, ROUTE_ONE_PASS = \
-    (1 << i for i in range(7))
+(ROUTE_FWD_PIPELINED, ROUTE_FWD_CUT, ROUTE_DQ_PIPELINED, ROUTE_DQ_CUT, ROUTE_DKV_PIPELINED, ROUTE_DKV_CUT, ROUTE_ONE_PASS, ROUTE_FWD_SHARED,
+ ROUTE_BWD_SHARED) = (1 << i for i in range(9))
 
 
 def chunk_attn_test_routes(desc) -> int:
-    """Test hook: the kernels the library chooses for a chunk, as a sum of ROUTE_* bits (host only)."""
+    """Test hook: the kernels the library runs for a chunk, as a sum of ROUTE_* bits (host only)."""
     out = ctypes.c_int32(0)
     rc = _lib.chunk_attn_test_routes(ctypes.byref(desc), ctypes.byref(out))
     if rc != 0:

@@ -545,10 +545,10 @@ int chunk_attn_test_routes(const chunk_attn_desc* desc, int32_t* routes) {
   layout_fwd(desc, L, false);
   const chunk_attn_desc w = widened(desc);
   BwdPlan P;
-  bwd_layout(&w, P, false);
-  *routes = (L.pipe ? CHUNK_ATTN_ROUTE_FWD_PIPELINED : 0) | (L.split.target > 0 ? CHUNK_ATTN_ROUTE_FWD_CUT : 0);
-  if (P.fused) {
-    *routes |= CHUNK_ATTN_ROUTE_ONE_PASS;
+  bwd_layout(&w, P, false, kCutFine, bwd_mode() == 0 ? desc->head_dim : 0);
+  *routes = L.share > 0 ? CHUNK_ATTN_ROUTE_FWD_SHARED : (L.pipe ? CHUNK_ATTN_ROUTE_FWD_PIPELINED : 0) | (L.split.target > 0 ? CHUNK_ATTN_ROUTE_FWD_CUT : 0);
+  if (P.fused || P.share_waves > 0) {
+    *routes |= P.fused ? CHUNK_ATTN_ROUTE_ONE_PASS : CHUNK_ATTN_ROUTE_BWD_SHARED;
     return CHUNK_ATTN_OK;
   }
   *routes |= (P.dq_pipe ? CHUNK_ATTN_ROUTE_DQ_PIPELINED : 0) | (P.split.target > 0 ? CHUNK_ATTN_ROUTE_DQ_CUT : 0) |

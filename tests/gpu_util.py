@@ -1,4 +1,6 @@
 """Helpers for the GPU parity tests: run the library through its C ABI and compare with the oracle."""
+import contextlib
+
 import numpy as np
 import torch
 
@@ -40,8 +42,19 @@ def run_gpu(case, q, k, v, do=None, accumulate=False, dk_init=None, dv_init=None
     return o, lse, dq, dk, dv
 
 
+@contextlib.contextmanager
+def kernels(mode):
+    """Mode 1: a small chunk runs the kernels of larger ones, and not those made for small chunks (mode 0: the library's choice)."""
+    import paper_2509_21275_amd as ca
+    ca.chunk_attn_test_set_bwd_mode(mode)
+    try:
+        yield
+    finally:
+        ca.chunk_attn_test_set_bwd_mode(0)
+
+
 def routes(case):
-    """Which kernels the library chooses for a case (ROUTE_* bits)."""
+    """Which kernels the library runs for a case (ROUTE_* bits)."""
     import paper_2509_21275_amd as ca
     return ca.chunk_attn_test_routes(ca.make_desc(case.segs, case.num_q_heads, case.num_kv_heads, case.head_dim, case.total_q,
                                                   case.total_kv, case.scale))

@@ -9,7 +9,7 @@ import torch
 
 import synth
 import paper_2509_21275_amd as ca
-from gpu_util import TOL_GRAD, TOL_O, make_inputs, rel_err, routes, run_gpu
+from gpu_util import TOL_GRAD, TOL_O, kernels, make_inputs, rel_err, routes, run_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -113,14 +113,17 @@ def test_pipelined_kernels_of_head_dim_96(oracle_mod, name, segs, Hq, Hkv):
     tq, tkv = max(s[0] + s[1] for s in segs), max(s[2] + s[3] for s in segs)
     case = synth.ChunkCase(f"{name}_d96", [synth.Seg(*s) for s in segs], tq, tkv, Hq, Hkv, 96, 500 + len(name))
     q, k, v, do = make_inputs(case)
-    got = run_gpu(case, q, k, v, do)
+    with kernels(1):
+        assert routes(case) & ALL_PIPELINED == ALL_PIPELINED
+        got = run_gpu(case, q, k, v, do)
     orc = oracle_mod.Oracle(case.segs, q.cpu(), k.cpu(), v.cpu(), do.cpu(), case.scale)
     O, LSE = orc.forward(); dQ, dK, dV = orc.backward()
     errs = [rel_err(a, b) for a, b in zip(got, (O, LSE, dQ, dK, dV))]
     print(case.name, errs, flush=True)
     assert errs[0] <= TOL_O and errs[1] <= 1e-4 and max(errs[2:]) <= TOL_GRAD
     wide = dataclasses.replace(case, head_dim=128)
-    ref = run_gpu(wide, *(torch.nn.functional.pad(x, (0, 32)) for x in (q, k, v, do)), scale=case.scale)
+    with kernels(1):
+        ref = run_gpu(wide, *(torch.nn.functional.pad(x, (0, 32)) for x in (q, k, v, do)), scale=case.scale)
     for a, b in zip(got, ref):
         b = b if b.dim() == 2 else b[..., :96]
         assert rel_err(a, b.double().cpu().numpy()) <= 2.0 ** -7
@@ -168,11 +171,11 @@ def test_pipelined_kernels_of_head_dim_64(oracle_mod, name, segs, Hq, Hkv, want)
         assert rel_err(acc[3][:, h:h + 1].cpu()[cov], dK[cov] + 3.0) <= TOL_GRAD and rel_err(acc[4][:, h:h + 1].cpu()[cov], dV[cov] + 3.0) <= TOL_GRAD
 
 
-@pytest.mark.parametrize("d", [64, 256])
+@pytest.mark.parametrize("d,mode,want", [(64, 1, 0), (256, 1, 0), (64, 0, ca.ROUTE_FWD_SHARED | ca.ROUTE_BWD_SHARED)])
 @pytest.mark.parametrize("Hq,Hkv", [(2, 2), (4, 1), (6, 2)])
-def test_tile_edges_of_the_kernels_for_short_walks(oracle_mod, d, Hq, Hkv):
-    """Head dimensions 64 and 256 below the pipelined kernels' sizes (asserted): key counts on both sides of the 32- and 64-row tiles the
-    forward and dQ kernels read rows and transposed operands from, contexts that are and are not whole tiles, single rows.
+def test_tile_edges_of_the_kernels_for_short_walks(oracle_mod, d, mode, want, Hq, Hkv):
+    """Head dimensions 64 and 256 below the pipelined kernels' sizes, and the small chunks' kernels of 64 (asserted): key counts on both sides of the
+    32- and 64-row tiles the forward and dQ kernels read rows and transposed operands from, contexts that are and are not whole tiles, single rows.
     (LSE: that of 64 sums the probabilities as rounded to bf16, 2^-9 of the sum at most.)"""
     lens = [(1, 1), (31, 31), (32, 32), (33, 33), (63, 64), (64, 65), (65, 65), (1, 96), (2, 128), (40, 129), (95, 191), (129, 193)]
     segs, tq, tkv = [], 0, 0
@@ -180,9 +183,10 @@ def test_tile_edges_of_the_kernels_for_short_walks(oracle_mod, d, Hq, Hkv):
         segs.append((tq, n, tkv, keys))
         tq, tkv = tq + n, tkv + keys
     case = synth.ChunkCase(f"tile_edges_d{d}", [synth.Seg(*s) for s in segs], tq, tkv, Hq, Hkv, d, 610 + Hq)
-    assert routes(case) == 0
     q, k, v, do = make_inputs(case)
-    o, lse, dq, dk, dv = run_gpu(case, q, k, v, do)
+    with kernels(mode):
+        assert routes(case) == want
+        o, lse, dq, dk, dv = run_gpu(case, q, k, v, do)
     orc = oracle_mod.Oracle(case.segs, q.cpu(), k.cpu(), v.cpu(), do.cpu(), case.scale)
     O, LSE = orc.forward(); dQ, dK, dV = orc.backward()
     assert float(np.abs(lse.double().cpu().numpy() - LSE).max()) <= (2.0 ** -9 + 1e-4 if d == 64 else 1e-4)

@@ -2,7 +2,8 @@
 against the fp64 oracle (2e-2 for O, 5e-2 for the gradients, as everywhere), against the uncut run (the same heads among so
 many copies of them that nothing is cut; both are bf16 roundings of float32 sums in different orders, so they differ by about one
 rounding: 2^-7 of the largest value), and bit for bit between the workspace and the static forward and, where the workspace
-has no room for pieces, with the uncut run.  Every case asserts which walks the library cuts."""
+has no room for pieces, with the uncut run.  Every case asserts which walks the library cuts.  (Small chunks have kernels of their own, which cut
+nothing: everything here runs those of larger ones, where the small workspaces are tested also by default.)"""
 import dataclasses
 
 import pytest
@@ -10,9 +11,16 @@ import torch
 
 import synth
 import paper_2509_21275_amd as ca
-from gpu_util import TOL_GRAD, TOL_O, make_inputs, rel_err, routes, run_gpu
+from gpu_util import TOL_GRAD, TOL_O, kernels, make_inputs, rel_err, routes, run_gpu
 
 pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _kernels_of_larger_chunks():
+    with kernels(1):
+        yield
+
 
 FWD, DQ, DKV = ca.ROUTE_FWD_CUT, ca.ROUTE_DQ_CUT, ca.ROUTE_DKV_CUT
 CUT = FWD | DQ | DKV
@@ -89,14 +97,16 @@ def test_cut_walks(oracle_mod, name, segs, hq, hk, cut, d):
         assert rel_err(got, want.double().cpu().numpy()) <= tol
 
 
+@pytest.mark.parametrize("mode", [1, 0])
 @pytest.mark.parametrize("name,segs,hq,hk,cut", [c for c in CASES if c[0] in ("ragged_slice", "dq_walks", "key_blocks", "causal_from_the_start")],
                          ids=["ragged_slice", "causal_from_the_start", "dq_walks", "key_blocks"])
-def test_workspace_without_room_for_pieces(name, segs, hq, hk, cut):
+def test_workspace_without_room_for_pieces(name, segs, hq, hk, cut, mode):
     """Forward and backward accept a workspace of the uncut layout's size and then run uncut: the uncut run's bits.  (At
-    head_dim 96 the reported sizes have room for pieces anyway.)"""
+    head_dim 96 the reported sizes have room for pieces anyway.  By default (mode 0) a small chunk does so too.)"""
     case = _case(name, segs, hq, hk)
     q, k, v, do = make_inputs(case)
     o, lse, dq, dk, dv = _uncut(case, q, k, v, do)
+    ca.chunk_attn_test_set_bwd_mode(mode)
     desc = ca.make_desc(case.segs, hq, hk, 128, case.total_q, case.total_kv, case.scale)
     fwd, bwd = ca.chunk_attn_workspace_bytes(desc)
     o2, lse2, dq2, dk2, dv2 = (torch.full_like(x, float("nan")) for x in (o, lse, dq, dk, dv))

@@ -8,7 +8,7 @@ import torch
 
 import synth
 import paper_2509_21275_amd as ca
-from gpu_util import TOL_GRAD, TOL_O, make_inputs, rel_err, run_gpu
+from gpu_util import TOL_GRAD, TOL_O, kernels, make_inputs, rel_err, routes, run_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -73,13 +73,16 @@ EDGE = [
 ]
 
 
+@pytest.mark.parametrize("mode", [0, 1])
 @pytest.mark.parametrize("name,segs,Hq,Hkv,d", EDGE, ids=[e[0] for e in EDGE])
-def test_edge_cases(oracle_mod, name, segs, Hq, Hkv, d):
+def test_edge_cases(oracle_mod, name, segs, Hq, Hkv, d, mode):
+    """By default most of these chunks run the small chunks' kernels, in mode 1 the ones that the comments above are about."""
     tq = max(s[0] + s[1] for s in segs)
     tkv = max(s[2] + s[3] for s in segs) + 3          # trailing key rows that no segment covers
     case = synth.ChunkCase(name, [synth.Seg(*s) for s in segs], tq, tkv, Hq, Hkv, d, 4242 + len(name))
     q, k, v, do = make_inputs(case)
-    o, lse, dq, dk, dv = run_gpu(case, q, k, v, do)
+    with kernels(mode):
+        o, lse, dq, dk, dv = run_gpu(case, q, k, v, do)
     orc = oracle_mod.Oracle(case.segs, q.cpu(), k.cpu(), v.cpu(), do.cpu(), case.scale)
     O, LSE = orc.forward(); dQ, dK, dV = orc.backward()
     errs = (rel_err(o, O), rel_err(dq, dQ), rel_err(dk, dK), rel_err(dv, dV))
@@ -104,33 +107,40 @@ def _forward_only(oracle_mod, case, q, k, v):
     return rel_err(o, O), float(np.abs(lse.double().cpu().numpy() - LSE).max())
 
 
-def test_forward_second_pass_forced(oracle_mod):
-    """The head_dim-128 forward keeps one reference maximum per row, of its first stage, and takes a block with a row whose scores outgrow it
+@pytest.mark.parametrize("d", [128, 96])
+def test_forward_second_pass_forced(oracle_mod, d):
+    """The pipelined forward of head_dim 128 and 96 keeps one reference maximum per row, of its first stage, and takes a block with a row whose scores outgrow it
     a second time, with every row's maximum over all keys.  With the growth limit set below any score every block is taken twice: other
     references, so other float32 roundings of LSE than with the default limit, and both as close to the oracle."""
-    case = synth.ChunkCase("redo_forced", synth.hybrid_chunk(200, 500, [130, 70]), 400, 900, 8, 2, 128, 31)
+    case = synth.ChunkCase("redo_forced", synth.hybrid_chunk(200, 500, [130, 70]), 400, 900, 8, 2, d, 31)
     q, k, v, _ = make_inputs(case)
-    once = run_gpu(case, q, k, v, backward=False)
-    ca.chunk_attn_test_set_fwd_rescale_limit(-1e30)
-    try:
-        eo, el = _forward_only(oracle_mod, case, q, k, v)
-        twice = run_gpu(case, q, k, v, backward=False)
-    finally:
-        ca.chunk_attn_test_set_fwd_rescale_limit(60.0)
+    with kernels(1):
+        assert routes(case) & ca.ROUTE_FWD_PIPELINED
+        once = run_gpu(case, q, k, v, backward=False)
+        ca.chunk_attn_test_set_fwd_rescale_limit(-1e30)
+        try:
+            eo, el = _forward_only(oracle_mod, case, q, k, v)
+            twice = run_gpu(case, q, k, v, backward=False)
+        finally:
+            ca.chunk_attn_test_set_fwd_rescale_limit(60.0)
     print("blocks taken twice", eo, el, flush=True)
     assert eo <= TOL_O and el <= 1e-4
     assert not torch.equal(once[0], twice[0]) and not torch.equal(once[1], twice[1])  # (they were)
 
 
-def test_forward_scores_outgrow_first_tile(oracle_mod):
+@pytest.mark.parametrize("mode,want", [(1, ca.ROUTE_FWD_PIPELINED), (0, ca.ROUTE_FWD_SHARED)])
+@pytest.mark.parametrize("d", [128, 96])
+def test_forward_scores_outgrow_first_tile(oracle_mod, d, mode, want):
     """Scores that grow by hundreds of nats along the keys: the first tile's maximum is useless as a reference
     for the later ones (exp2 would overflow), so blocks must be taken again, on their own."""
-    n, Hq, Hkv, d = 700, 8, 2, 128
+    n, Hq, Hkv = 700, 8, 2
     case = synth.ChunkCase("growing_scores", [synth.Seg(0, n, 0, n)], n, n, Hq, Hkv, d, 32)
     q, k, v, _ = make_inputs(case)
     ramp = torch.linspace(0.0, 3.0, n, device=q.device).view(n, 1, 1)
     q = (torch.ones_like(q) * 4.0).to(torch.bfloat16)                       # q . k_j = 4 * 128 * ramp_j * scale
     k = (k.float() * 0.05 + ramp).to(torch.bfloat16)                        # up to ~136 nats at the last key
-    eo, el = _forward_only(oracle_mod, case, q, k, v)
+    with kernels(mode):
+        assert routes(case) & (ca.ROUTE_FWD_PIPELINED | ca.ROUTE_FWD_SHARED) == want
+        eo, el = _forward_only(oracle_mod, case, q, k, v)
     print("growing scores", eo, el, flush=True)
     assert eo <= TOL_O and el <= 1.1e-3  # (136 nats as float32 sums of 128 products, each off by 2^-24 of the sum at most)

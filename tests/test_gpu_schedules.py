@@ -1,27 +1,34 @@
 """How a chunk's schedule reaches the device follows from its size: as kernel arguments (up to 104 forward items, up to 3584
 bytes of backward lists) or through device memory, with a workgroup per block (up to 256 blocks, dQ and dK/dV together in the
 backward) or with blocks claimed through counters.  Chunks on both sides of every line against the fp64 oracle (2e-2 for O, 5e-2 for the
-gradients, as everywhere), twice for the same bits, and the static forward bit for bit."""
+gradients, as everywhere), twice for the same bits, and the static forward bit for bit.  These are lines of the larger chunks' kernels; the small
+chunks', of 104 forward items as well, run where the library chooses them."""
 import pytest
 import torch
 
 import paper_2509_21275_amd as ca
 import synth
-from gpu_util import TOL_GRAD, TOL_O, make_inputs, rel_err, run_gpu
+from gpu_util import TOL_GRAD, TOL_O, kernels, make_inputs, rel_err, routes, run_gpu
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("d", [128, 96, 64, 256])
+@pytest.mark.parametrize("d,mode", [(128, 1), (96, 1), (64, 1), (256, 1), (128, 0), (96, 0), (64, 0)])
 @pytest.mark.parametrize("n,hq,hk", [
     (16, 8, 8), (17, 8, 8),     # 256 and 272 dQ and dK/dV blocks
     (32, 8, 8), (33, 8, 8),     # 256 and 264 forward blocks
     (36, 4, 4), (37, 4, 4),     # 3552 and 3648 bytes of backward lists
     (104, 2, 1), (105, 2, 1),   # forward items
 ])
-def test_schedules_on_both_sides_of_each_line(oracle_mod, n, hq, hk, d):
+def test_schedules_on_both_sides_of_each_line(oracle_mod, n, hq, hk, d, mode):
+    with kernels(mode):
+        _schedules_on_both_sides_of_each_line(oracle_mod, n, hq, hk, d, mode)
+
+
+def _schedules_on_both_sides_of_each_line(oracle_mod, n, hq, hk, d, mode):
     case = synth.ChunkCase(f"schedule{n}", synth.packed_chunk([33 if i % 2 else 40 for i in range(n)]), sum(33 if i % 2 else 40 for i in range(n)),
                            sum(33 if i % 2 else 40 for i in range(n)), hq, hk, d, 70 + n)
+    assert mode == 0 or not routes(case) & (ca.ROUTE_FWD_SHARED | ca.ROUTE_BWD_SHARED)
     q, k, v, do = make_inputs(case)
     got = run_gpu(case, q, k, v, do)
     again = run_gpu(case, q, k, v, do)
@@ -51,16 +58,24 @@ def test_dq_and_dkv_blocks_in_one_launch(oracle_mod, d, n, rows, ctx, hq, hk):
     """The unpipelined dK/dV kernels of head dimensions 64 and 256 share their launch with dQ; the same bits on a second run."""
     segs = [synth.Seg(rows * i, rows, (rows + ctx) * i, rows + ctx) for i in range(n)]
     case = synth.ChunkCase("joint", segs, n * rows, n * (rows + ctx), hq, hk, d, 90 + n)
-    assert not ca.chunk_attn_test_routes(ca.make_desc(segs, hq, hk, d, case.total_q, case.total_kv, case.scale)) & (ca.ROUTE_DQ_PIPELINED | ca.ROUTE_DKV_PIPELINED)
     q, k, v, do = make_inputs(case)
-    got = run_gpu(case, q, k, v, do)
-    assert all(torch.equal(a, b) for a, b in zip(got, run_gpu(case, q, k, v, do)))
+    with kernels(1):
+        assert not routes(case) & (ca.ROUTE_DQ_PIPELINED | ca.ROUTE_DKV_PIPELINED | ca.ROUTE_BWD_SHARED)
+        got = run_gpu(case, q, k, v, do)
+        assert all(torch.equal(a, b) for a, b in zip(got, run_gpu(case, q, k, v, do)))
     orc = oracle_mod.Oracle(case.segs, q.cpu(), k.cpu(), v.cpu(), do.cpu(), case.scale)
     orc.forward()
     dQ, dK, dV = orc.backward()
     assert max(rel_err(got[2], dQ), rel_err(got[3], dK), rel_err(got[4], dV)) <= TOL_GRAD
 
 
+@pytest.fixture
+def kernels_of_larger_chunks():
+    with kernels(1):
+        yield
+
+
+@pytest.mark.usefixtures("kernels_of_larger_chunks")
 @pytest.mark.parametrize("f32kv", [False, True])
 @pytest.mark.parametrize("d,segs,hq,hk", [
     (64, [(0, 1100, 5, 1400), (1100, 77, 1410, 77)], 6, 2),      # pieces of three query heads per tile, a ragged last block

@@ -8,7 +8,7 @@ import torch
 
 import paper_2509_21275_amd as ca
 import synth
-from gpu_util import TOL_GRAD, TOL_O, make_inputs, rel_err, run_gpu
+from gpu_util import TOL_GRAD, TOL_O, kernels, make_inputs, rel_err, run_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -51,8 +51,8 @@ def test_late_growth_and_more_blocks_than_workgroups(oracle_mod):
 
 
 @pytest.mark.parametrize("limit", [60.0, -1e30])
-@pytest.mark.parametrize("d", [256, 64])
-def test_rounding_of_the_probabilities_cancels_in_the_quotient(d, limit):
+@pytest.mark.parametrize("d,mode", [(256, 1), (64, 1), (64, 0)])
+def test_rounding_of_the_probabilities_cancels_in_the_quotient(d, mode, limit):
     """V is one everywhere, so that every row of O is one.  All keys but the first have the same probability relative to it, 0.5018, which bf16
     rounds to 0.5: divided by a sum of unrounded probabilities, O would be 0.9964 for many keys, 0.9961 in bf16.  Divided by the sum of what
     is multiplied with V it is one up to float32 sums of a few hundred terms, which is one in bf16.  LSE takes the unrounded sum at 256,
@@ -65,7 +65,8 @@ def test_rounding_of_the_probabilities_cancels_in_the_quotient(d, limit):
     case = synth.ChunkCase("ones", [synth.Seg(0, n, 0, n + ctx)], n, n + ctx, hq, hk, d, 0)
     ca.chunk_attn_test_set_fwd_rescale_limit(limit)
     try:
-        o, lse = run_gpu(case, q, k, v, scale=0.68955, backward=False)
+        with kernels(mode):
+            o, lse = run_gpu(case, q, k, v, scale=0.68955, backward=False)
     finally:
         ca.chunk_attn_test_set_fwd_rescale_limit(60.0)
     assert torch.all(o == 1.0)

@@ -129,11 +129,24 @@ def packed(*lens):
     (packed(*[200] * 32), 32, 8, 256, "", "", "p"),
 ])
 def test_routes(ca, segs, Hq, Hkv, dim, fwd, dq, dkv):
-    """Which kernels a chunk runs; the tests on the GPU assert with the same hook that they reach the path they are named for."""
+    """Which kernels a chunk runs; the tests on the GPU assert with the same hook that they reach the path they are named for.  The table is that of mode 1:
+    by default some of the small chunks run the kernels made for them, and the hook then says so and nothing of the kernels that do not run."""
     bits = {"": 0, "p": 1, "pc": 3}
     d = desc(ca, segs, Hq=Hq, Hkv=Hkv, d=dim)
-    assert ca.chunk_attn_test_routes(d) == bits[fwd] | bits[dq] << 2 | bits[dkv] << 4
+    forward, backward = bits[fwd], bits[dq] << 2 | bits[dkv] << 4
+    ca.chunk_attn_test_set_bwd_mode(1)
+    try:
+        assert ca.chunk_attn_test_routes(d) == forward | backward
+        assert ca.chunk_attn_test_shared_heads(d) == ca.chunk_attn_test_shared_waves(d) == 0
+    finally:
+        ca.chunk_attn_test_set_bwd_mode(0)
+    if ca.chunk_attn_test_shared_heads(d):
+        forward = ca.ROUTE_FWD_SHARED
+    if ca.chunk_attn_test_shared_waves(d):
+        backward = ca.ROUTE_BWD_SHARED
+    assert ca.chunk_attn_test_routes(d) == forward | backward
     assert (ca.ROUTE_FWD_CUT, ca.ROUTE_DQ_PIPELINED, ca.ROUTE_DKV_PIPELINED, ca.ROUTE_ONE_PASS) == (2, 4, 16, 64)
+    assert (ca.ROUTE_FWD_SHARED, ca.ROUTE_BWD_SHARED) == (128, 256)
 
 
 @pytest.mark.parametrize("dim,Hq,Hkv,segs,heads,waves", [
@@ -153,6 +166,8 @@ def test_small_chunks_run_the_shared_kernels_where_those_are_faster(ca, dim, Hq,
         assert ca.chunk_attn_test_shared_heads(d) == heads
     if waves is not None:
         assert ca.chunk_attn_test_shared_waves(d) == waves
+    assert bool(ca.chunk_attn_test_routes(d) & ca.ROUTE_FWD_SHARED) == bool(ca.chunk_attn_test_shared_heads(d))
+    assert bool(ca.chunk_attn_test_routes(d) & ca.ROUTE_BWD_SHARED) == bool(ca.chunk_attn_test_shared_waves(d))
 
 
 def contexts(n, last=288):

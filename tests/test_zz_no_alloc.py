@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import synth
-from gpu_util import make_inputs
+from gpu_util import kernels, make_inputs, routes
 
 pytestmark = pytest.mark.gpu
 
@@ -31,29 +31,35 @@ def _both(ca, lib, case):
     assert torch.equal(o, o_ref) and torch.equal(lse, lse_ref)
 
 
-@pytest.mark.parametrize("d", [128, 64, 96, 256])
-def test_static_forward_matches_the_workspace_forward_twice(d):
+@pytest.mark.parametrize("d,mode", [(128, 1), (64, 1), (96, 1), (256, 0), (128, 0), (64, 0), (96, 0)])
+def test_static_forward_matches_the_workspace_forward_twice(d, mode):
+    """With the kernels of larger chunks (mode 1; at 128 and 96 the big chunk's walks are cut, with the pieces in the array), and the small chunks' own."""
     import paper_2509_21275_amd as ca
     lib = ctypes.CDLL(ca.LIB_PATH)
     lib.chunk_attn_fwd_static.restype = ctypes.c_int
     big = synth.ChunkCase("hybrid_big", synth.hybrid_chunk(700, 1500, [300, 129, 64, 1, 257]), 1451, 2951, 8, 2, d, 71)
     small = synth.ChunkCase("packed_small", synth.packed_chunk([130, 33]), 163, 163, 8, 2, d, 72)
-    _both(ca, lib, big)
-    _both(ca, lib, small)   # fewer items and pieces than the call before: nothing stale may be picked up
-    _both(ca, lib, big)
+    with kernels(mode):
+        assert bool(routes(big) & ca.ROUTE_FWD_CUT) == (d in (96, 128) and mode == 1)
+        _both(ca, lib, big)
+        _both(ca, lib, small)   # fewer items and pieces than the call before: nothing stale may be picked up
+        _both(ca, lib, big)
 
 
-def test_static_forward_second_pass():
-    """Blocks that the head_dim 128 forward takes twice, with the static array as with a workspace."""
+@pytest.mark.parametrize("d", [128, 96])
+def test_static_forward_second_pass(d):
+    """Blocks that the pipelined forward takes twice, with the static array as with a workspace."""
     import paper_2509_21275_amd as ca
     lib = ctypes.CDLL(ca.LIB_PATH)
     lib.chunk_attn_fwd_static.restype = ctypes.c_int
-    case = synth.ChunkCase("redo_forced", synth.hybrid_chunk(200, 500, [130, 70]), 400, 900, 8, 2, 128, 31)
-    ca.chunk_attn_test_set_fwd_rescale_limit(-1e30)
-    try:
-        _both(ca, lib, case)
-    finally:
-        ca.chunk_attn_test_set_fwd_rescale_limit(60.0)
+    case = synth.ChunkCase("redo_forced", synth.hybrid_chunk(200, 500, [130, 70]), 400, 900, 8, 2, d, 31)
+    with kernels(1):
+        assert routes(case) & ca.ROUTE_FWD_PIPELINED
+        ca.chunk_attn_test_set_fwd_rescale_limit(-1e30)
+        try:
+            _both(ca, lib, case)
+        finally:
+            ca.chunk_attn_test_set_fwd_rescale_limit(60.0)
 
 
 def test_static_forward_refuses_what_does_not_fit():
@@ -79,11 +85,19 @@ def test_static_forward_refuses_what_does_not_fit():
     torch.cuda.synchronize()
 
 
-def test_static_forward_under_graph_capture():
+@pytest.fixture(params=[1, 0], ids=["larger_chunks_kernels", "default"])
+def mode(request):
+    with kernels(request.param):
+        yield request.param
+
+
+def test_static_forward_under_graph_capture(mode):
     """The callers the entry point is for: captured into a HIP graph (after one eager call, which takes the scratch
-    array's address) and replayed several times with eager work in between, every replay gives the eager bits."""
+    array's address) and replayed several times with eager work in between, every replay gives the eager bits.  Captured are the cut forward, its
+    pieces in the array, and the launch that puts them together; by default the small chunks' forward."""
     import paper_2509_21275_amd as ca
     case = synth.ChunkCase("hybrid_big", synth.hybrid_chunk(700, 1500, [300, 129, 64, 1, 257]), 1451, 2951, 8, 2, 128, 71)
+    assert routes(case) & (ca.ROUTE_FWD_CUT | ca.ROUTE_FWD_SHARED) == (ca.ROUTE_FWD_CUT if mode == 1 else ca.ROUTE_FWD_SHARED)
     q, k, v, _ = make_inputs(case)
     desc = ca.make_desc(case.segs, 8, 2, 128, case.total_q, case.total_kv, case.scale)
     o_ref = torch.empty_like(q); lse_ref = torch.empty((8, case.total_q), dtype=torch.float32, device="cuda")
