@@ -1,7 +1,7 @@
 """LDS reads written as instructions (lds_asm_read*) are invisible to the compiler: a register they fill may be used only after
 an s_waitcnt that covers the read, and only naming the register in that statement (or in an empty one behind it) keeps the
-compiler from moving the use in front of it.  This looks at the source of every pipelined step: each array that a
-read fills is an operand of a wait in the same step."""
+compiler from moving the use in front of it.  This looks at the source of every pipelined step, and of the small chunks' kernels: each
+array that a read fills is an operand of a wait in the same step or kernel."""
 import os
 import re
 import shutil
@@ -14,9 +14,9 @@ from paper_2509_21275_amd.build import FLAGS
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2509_21275_amd", "csrc")
 
 
-def lambda_bodies(text, name):
-    """Bodies of the lambdas `auto name = [&](...) ... { ... };`"""
-    for m in re.finditer(r"auto %s = \[&\]" % name, text):
+def bodies(text, head):
+    """Bodies of the lambdas or functions that start with `head` (a pattern up to the parameters)."""
+    for m in re.finditer(head, text):
         at = text.index("{", m.end())
         depth, i = 0, at
         while True:
@@ -43,7 +43,7 @@ def statements(body):
 @pytest.mark.parametrize("source", ["fwd_kernel.hip", "bwd_kernel.hip", "bwd_fused_kernel.hip"])
 def test_every_array_read_in_a_step_is_tied_to_a_wait(source):
     text = open(os.path.join(CSRC, source)).read()
-    steps = list(lambda_bodies(text, "step"))
+    steps = list(bodies(text, r"auto step = \[&\]"))
     found = 0
     for body, line in steps:
         filled = set(re.findall(r"\b(\w+)(?:\[[^=;]*\])? = (?:lds_asm_read\w*|load_\w+)\b", body))
@@ -51,6 +51,17 @@ def test_every_array_read_in_a_step_is_tied_to_a_wait(source):
         tied = set(re.findall(r'"\+v"\((\w+)', " ".join(statements(body))))
         assert filled <= tied, f"{source}:{line}: {sorted(filled - tied)} read from LDS, but no wait names them"
     assert found >= 1
+
+
+@pytest.mark.parametrize("source,kernel,arrays", [("fwd_kernel.hip", "fwd_share_kernel", 4), ("bwd_share_kernel.hip", "share_dq_block", 8),
+                                                 ("bwd_share_kernel.hip", "share_dkv_block", 11)])
+def test_every_array_read_in_a_small_chunks_kernel_is_tied_to_a_wait(source, kernel, arrays):
+    text = open(os.path.join(CSRC, source)).read()
+    (body, line), = bodies(text, r"void %s\(" % kernel)
+    filled = set(re.findall(r"\b(\w+)(?:\[[^=;]*\])? = lds_asm_read\w*\b", body)) | set(re.findall(r'asm volatile\("ds_read[^"]*" : "=v"\((\w+)', body))
+    tied = set(re.findall(r'"\+v"\((\w+)', " ".join(statements(body))))
+    assert len(filled) == arrays, sorted(filled)
+    assert filled <= tied, f"{source}:{line}: {sorted(filled - tied)} read from LDS, but no wait names them"
 
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
