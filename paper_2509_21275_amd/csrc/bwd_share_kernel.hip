@@ -9,7 +9,7 @@
 // its own LDS slots, so that it waits for nothing but its copies, and the waves' sums meet in LDS at the end, added in wave order.
 // D_i = <dO_i, O_i> is made where it is used: by a dQ workgroup for its 32 rows, by a dK/dV wave for every stage (O comes in registers
 // a stage ahead, in the order in which the copies lay out dO).
-// Tiles are rows, chunk c of row r at c ^ tile_swz(r) (as in fwd_share_kernel).
+// Tiles are rows swizzled by share_swz, as in fwd_share_kernel.
 //
 // Why: such a chunk's backward was three or four launches one after the other (pre-pass 4 us, dQ and dK/dV blocks, merge of cut walks 5 us), each
 // a serial chain of stages on few compute units.  Backward before -> now, us: head_dim 64, 8/8 heads, sequences of 256, 512, 128 and 128, 19.5 ->
@@ -18,7 +18,6 @@
 // and 1.8 at 128, one wave per SIMD) and the sums.  A dK/dV stage at 128 took 2.5 us with the rows of every copy clamped (a multiplication each), 2.2
 // without, 2.05 once O's loads were waited for ahead of the copies (rows_loaded), 1.84 with D by v_dot2 and copies from a scalar base.
 // Four waves (64: two workgroups per compute unit) or eight: choose_shared_waves.
-#include <cstring>
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -29,13 +28,6 @@ namespace chunk_attn {
 namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
-
-// (head_dim 96: rows of 128 columns in LDS, whose last four chunks copy the last but them and are never read)
-constexpr int tile_cols(int d) { return d == 96 ? 128 : d; }
-template <int D>
-__host__ __device__ constexpr int tile_swz(int r) {
-  return D == 64 ? ((r >> 3) & 1) | ((r >> 1) & 2) | ((r & 2) << 1) : ((r & 3) << 2) | ((r >> 2) & 3);
-}
 
 struct ShareParams {
   const __bf16 *q, *k, *v, *o, *d_o;
@@ -59,7 +51,7 @@ static_assert(sizeof(ShareArgs) <= 3840);
 
 // LDS: W waves' slots (two stages of two tiles each; at the end the wave's sums), the two stationary tiles, 32 values of LSE and of -D per wave
 template <int D, int W>
-constexpr size_t share_bwd_smem() { return (size_t)(W * 4 + 2) * 32 * tile_cols(D) * 2 + (size_t)W * 64 * sizeof(float); }
+constexpr size_t share_bwd_smem() { return (size_t)(W * 4 + 2) * 32 * share_cols(D) * 2 + (size_t)W * 64 * sizeof(float); }
 
 template <int CTRL>
 __device__ __forceinline__ float dpp_add(float x) {
@@ -87,7 +79,7 @@ __device__ __forceinline__ bf16x8 join(s16x4 lo, s16x4 hi) {
 // What both kinds of block use: the lane's place in copies and operand reads.
 template <int D>
 struct ShareLane {
-  static constexpr int ROW = tile_cols(D) * 2, C = ROW / 16, PT = C / 2, RPC = 64 / C, TILE = 32 * ROW;  // ROW: bytes of a row in LDS
+  static constexpr int ROW = share_cols(D) * 2, C = ROW / 16, PT = C / 2, RPC = 64 / C, TILE = 32 * ROW;  // ROW: bytes of a row in LDS
   int lane, l32, hh, c_row, c_chunk;
   unsigned row_at, tr_at;  // byte offsets in a tile of the row reads and of the transposed reads
   __device__ __forceinline__ ShareLane() {
@@ -95,18 +87,18 @@ struct ShareLane {
     l32 = lane & 31;
     hh = lane >> 5;
     c_row = lane / C;
-    c_chunk = (lane % C) ^ tile_swz<D>(c_row);
-    row_at = (unsigned)(l32 * ROW + ((hh ^ tile_swz<D>(l32)) * 16));
+    c_chunk = (lane % C) ^ share_swz<D>(c_row);
+    row_at = (unsigned)(l32 * ROW + ((hh ^ share_swz<D>(l32)) * 16));
     const int j = lane & 15, cl = 2 * ((lane >> 4) & 1) + ((j & 3) >> 1), r0 = 4 * hh + (j >> 2);
-    tr_at = (unsigned)(r0 * ROW + ((cl ^ tile_swz<D>(r0)) * 16) + 8 * (j & 1));
+    tr_at = (unsigned)(r0 * ROW + ((cl ^ share_swz<D>(r0)) * 16) + 8 * (j & 1));
   }
   template <int I>
   __device__ __forceinline__ int column() const {  // of the lane's chunk in copy I of a tile
-    const int chunk = c_chunk ^ tile_swz<D>(RPC * I);
+    const int chunk = c_chunk ^ share_swz<D>(RPC * I);
     return (D == 96 ? min(chunk, D / 8 - 1) : chunk) * 8;
   }
   template <int I>
-  __device__ __forceinline__ bool in_row() const { return D != 96 || (c_chunk ^ tile_swz<D>(RPC * I)) < D / 8; }  // it is one of the row's
+  __device__ __forceinline__ bool in_row() const { return D != 96 || (c_chunk ^ share_swz<D>(RPC * I)) < D / 8; }  // it is one of the row's
   // The chunk, of rows of `stride` elements, that copy i of a tile puts at this lane's place; rows past `last` (< 31) repeat it, which costs a
   // multiplication for every copy: whole tiles find their chunks a scalar row and a constant XOR away from `c_off` = c_row * stride.
   template <int I>
@@ -134,7 +126,7 @@ struct ShareLane {
 // columns.  `use(quarter, sum)` is called for each of the wave's own.
 template <int D, int W, int N, class F>
 __device__ __forceinline__ void add_shares(char* smem, int wave, int lane, int parts, const f32x16 (&acc)[N], F&& use) {
-  constexpr int NQ = N * 4, NQW = NQ / W, REGION = 4 * 32 * tile_cols(D) * 2;
+  constexpr int NQ = N * 4, NQW = NQ / W, REGION = 4 * 32 * share_cols(D) * 2;
   static_assert(NQ % W == 0 && NQ * 1024 <= REGION);
   if (wave < parts) {
     lds_f32* const out = (lds_f32*)(smem + wave * REGION) + lane * 4;
@@ -258,7 +250,7 @@ __device__ __forceinline__ void share_dq_block(const ShareParams& p, const chunk
     static_for<0, 2 * DB>([&](auto x_c) __attribute__((always_inline)) {
       constexpr int ks = decltype(x_c)::value / DB, db = decltype(x_c)::value % DB;
       lo[ks][db] = lds_asm_read_tr<ks * 16 * Lane::ROW>(ta ^ (db * 64));
-      hi[ks][db] = lds_asm_read_tr<(ks * 16 + 8) * Lane::ROW>(ta ^ (db * 64 + tile_swz<D>(8) * 16));
+      hi[ks][db] = lds_asm_read_tr<(ks * 16 + 8) * Lane::ROW>(ta ^ (db * 64 + share_swz<D>(8) * 16));
     });
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -461,7 +453,7 @@ __device__ __forceinline__ void share_dkv_block(const ShareParams& p, const chun
     static_for<0, 2 * DB>([&](auto x_c) __attribute__((always_inline)) {
       constexpr int ks = decltype(x_c)::value / DB, db = decltype(x_c)::value % DB;
       glo[ks][db] = lds_asm_read_tr<TILE + ks * 16 * Lane::ROW>(ta ^ (db * 64));
-      ghi[ks][db] = lds_asm_read_tr<TILE + (ks * 16 + 8) * Lane::ROW>(ta ^ (db * 64 + tile_swz<D>(8) * 16));
+      ghi[ks][db] = lds_asm_read_tr<TILE + (ks * 16 + 8) * Lane::ROW>(ta ^ (db * 64 + share_swz<D>(8) * 16));
     });
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -483,7 +475,7 @@ __device__ __forceinline__ void share_dkv_block(const ShareParams& p, const chun
     static_for<0, 2 * DB>([&](auto x_c) __attribute__((always_inline)) {
       constexpr int ks = decltype(x_c)::value / DB, db = decltype(x_c)::value % DB;
       qlo[ks][db] = lds_asm_read_tr<ks * 16 * Lane::ROW>(ta ^ (db * 64));
-      qhi[ks][db] = lds_asm_read_tr<(ks * 16 + 8) * Lane::ROW>(ta ^ (db * 64 + tile_swz<D>(8) * 16));
+      qhi[ks][db] = lds_asm_read_tr<(ks * 16 + 8) * Lane::ROW>(ta ^ (db * 64 + share_swz<D>(8) * 16));
     });
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll

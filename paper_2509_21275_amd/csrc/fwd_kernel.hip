@@ -1287,15 +1287,8 @@ __global__ __launch_bounds__(256, 1) void fwd_wide_kernel(FwdArgs) {
 // one: 1000 tokens, 8/8, 15.1 instead of 11.2; there K of the next stage is copied once K has been read, V once V has been (both after V: 11.2 -> 11.0,
 // 3000 tokens, 8/8, 44.6 -> 42.1).  Two heads in one wave with four waves: 203 + 611 queries as above 29.0.
 //
-// Tiles are rows (a copy instruction fetches whole rows; chunk-major tiles touch up to eight times the cache lines): chunk c of row r sits at
-// c ^ share_swz(r), which serves 16-byte reads of 16 consecutive rows and transposed reads of four rows by four chunks without conflicts.
+// Tiles are rows (a copy instruction fetches whole rows; chunk-major tiles touch up to eight times the cache lines), swizzled by share_swz.
 // ------------------------------------------------------------------------------------------------
-// (head_dim 96: rows of 128 columns in LDS, whose last four chunks copy the last but them and are never read)
-constexpr int share_cols(int d) { return d == 96 ? 128 : d; }
-template <int D>
-__host__ __device__ constexpr int share_swz(int r) {
-  return D == 64 ? ((r >> 3) & 1) | ((r >> 1) & 2) | ((r & 2) << 1) : ((r & 3) << 2) | ((r >> 2) & 3);
-}
 constexpr float kNoMax = -3.4028234e38f;  // reference maximum of a row that has seen no key yet
 template <int D, int HG, int KS, int NS>
 constexpr size_t share_smem() {  // the splits' slots of a K and a V tile and the heads' Q tiles, or each wave's O; a maximum and a sum per wave and row

@@ -130,6 +130,15 @@ __device__ __forceinline__ int cm_elem(int r, int c) { return (c * 32 + (r ^ ((c
 __device__ __forceinline__ int row_swz(int r) { return ((r >> 3) & 1) | ((r >> 1) & 2) | ((r & 2) << 1); }
 __device__ __forceinline__ int row_elem(int r, int c) { return (r * 8 + (c ^ row_swz(r))) * 8; }
 
+// Tiles of 32 rows of the small chunks' kernels: chunk c of row r sits at c ^ share_swz(r), which serves 16-byte reads of 16 consecutive rows and
+// transposed reads of four rows by four chunks without conflicts (64: row_swz).  head_dim 96: rows of 128 columns in LDS, whose last four chunks
+// copy the last but them and are never read.
+constexpr int share_cols(int d) { return d == 96 ? 128 : d; }
+template <int D>
+__host__ __device__ constexpr int share_swz(int r) {
+  return D == 64 ? ((r >> 3) & 1) | ((r >> 1) & 2) | ((r & 2) << 1) : ((r & 3) << 2) | ((r >> 2) & 3);
+}
+
 // LDS accesses as opaque instructions, for the software-pipelined kernels.  The compiler makes a wave wait for ALL of its
 // outstanding global->LDS copies before an LDS read it cannot tell apart from their destinations (the
 // transpose read in particular), which would serialise the copies of later stages with the reads of the
