@@ -255,7 +255,7 @@ void layout_fwd(const chunk_attn_desc* desc, FwdLayout& L, bool with_plan, bool 
   if (is_narrow(desc))  // (as much as with padded copies of Q, K, V and O)
     L.total = std::max(L.total, uncut_total + 2 * padded_bytes(d->total_q, d->num_q_heads, 2) + 2 * padded_bytes(d->total_kv, d->num_kv_heads, 2));
   // (the layout of the workspace stays the other kernel's, so that its size does)
-  L.share = may_cut && bwd_mode() == 0 ? choose_shared_heads(desc, walks, inner, pipe, L.split.target > 0) : 0;
+  L.share = may_cut && bwd_mode() == 0 ? choose_shared_heads(desc, walks, inner, pipe, L.split) : 0;
   if (L.share > 0) {
     L.n_items = (size_t)count_walks(d, 32).items;
     L.blocks = (int64_t)L.n_items * (d->num_q_heads / L.share);

@@ -395,40 +395,38 @@ void choose_cut(const CutKind (&kinds)[N], int cus, const int64_t (&max_parts)[N
 constexpr int kLongSharedWalk = 40;
 constexpr int kMaxSharedHeads = 4096;  // block counts and byte offsets inside a tile stay in 32 bits (no chunk of as many heads is small)
 
-// Times (us) of the two kinds of forward: first + the larger of what the longest walk takes and what all workgroups take together on the chip's slots.
-// Least squares in the logarithm over 8500 drawn chunks of up to 104 tiles of 32 rows (1 - 3300 queries, up to 6 contexts of up to 20000 keys, 1 - 128
-// query and 1 - 64 key/value heads), each measured with every choice, 5000 of them on tensors of the call before (in the caches where they fit) and
-// 3500 on tensors that come from memory.  Off by 5 - 13 % (root mean square).  At 96 and 128 a stage from memory costs this kernel more than the
-// other one (one head to a workgroup has room for a single slot per wave: its copies' latency shows), so there are two sets, and the choice has to be ahead by
-// both.  One set for tensors in the caches, at 5 % ahead, was up to 1.7 times slower than the other kernel where few queries meet thousands of
-// keys of many key/value heads (13 queries on 14478 keys, 64/64, head_dim 96: 104 -> 172; 4 on 7246, 128/16, 128: 49 -> 80).
-// With the shares of the other kernel's time that are asked for now, 15 of 11500 chosen chunks of other draws (in the caches and from memory) were
-// slower by more than 2 %, the worst by 17 % (71 query heads on one key/value head, 19 us instead of 16); all drawn chunks together 1.62 (head_dim 64),
-// 1.46 (96) and 1.51 (128) times as fast as without it (from memory 1.35, 1.34 and 1.36), where the best choice would be 1.66, 1.59 and 1.66 (1.37,
-// 1.40 and 1.42).
+// Times (us) of the two kinds of forward.  Least squares in the logarithm over 8500 drawn chunks of up to 104 tiles of 32 rows (1 - 3300 queries, up to
+// 6 contexts of up to 20000 keys, 1 - 128 query and 1 - 64 key/value heads), each measured with every choice, 5000 of them on the tensors of the call
+// before (in the caches where they fit) and 3500 on tensors that come from memory.  Off by 5 - 10 % (root mean square; the other kernels by 7).  A
+// stage from memory costs this kernel more than the other ones (at 96 and 128 one head to a workgroup has room for a single slot per wave: its
+// copies' latency shows), so there are two sets, and the choice has to be ahead by both.  A single set for tensors in the caches, without the
+// rounds of workgroups and the pieces of cut walks, was up to 1.7 times slower than the other kernel where few queries meet thousands of keys of many
+// key/value heads (13 queries on 14478 keys, 64/64, head_dim 96: 104 -> 172; 4 on 7246, 128/16, 128, from memory: 49 -> 80).  Of 10000 chosen
+// chunks of other draws 17 are slower by more than 2 %, by 16 % at most (71 heads on one key/value head), of 8500 from memory 41, by 21 % at most (258
+// queries on 4180 keys, 32/8, 128).  All chunks together, by head_dim 64, 96 and 128, 1.64, 1.51 and 1.56 times as fast as without the kernel (from
+// memory 1.36, 1.36 and 1.38), where the best choice would be 1.66, 1.59 and 1.66 (1.37, 1.40 and 1.42).
 // Examples, other kernel -> one, two, four heads: head_dim 64, 1024 tokens, 8/8 heads, 16.9 -> 7.9; four sequences of 512, 256, 128 and 128,
 // 8/8, 10.6 -> 6.0, 32/8, 11.1 -> 15.8, 9.3, 10.5; 100 queries on 10100 keys, 32/8, 124 -> 40, 62, 110; head_dim 128, 203 queries on 1704 keys with
 // 611 packed tokens, 32/8, 30.1 -> 26.1, 21.6, 31.7; eight sequences of 128, 32/8, 14.4 -> 18.1, 12.8, 9.7; 200 queries on 20200 keys, 32/8,
 // 90 -> 123, 192, 293 (walks cut over the whole chip).
-struct SharedCost {
-  double first, step, all_steps, workgroup, longest, mb;  // first + max(step longest, all_steps steps + workgroup count + longest longest) + mb MB of K and V
-  int slots;                                              // workgroups on the chip at a time
+struct SharedCost {  // the larger of what the longest walk and what all workgroups take; rounds: workgroups over those on the chip at a time, rounded up
+  double first, step, all_steps, workgroup, longest, mb, round;
+  int slots;  // workgroups on the chip at a time
   double us(double most, double steps, double workgroups, double kv_mb) const {
-    return first + std::max(step * most, (all_steps * steps + workgroup * workgroups) / slots + longest * most) + mb * kv_mb;
+    return first + std::max(step * most, (all_steps * steps + workgroup * workgroups) / slots + longest * most) + mb * kv_mb + round * std::ceil(workgroups / slots);
   }
 };
-// [tensors in the caches, from memory][one, two, four heads].  (At 96 and 128 the step of one head from memory is a line that few chunks lie above, 2.5 and
-// 2.8; the mean is 1.9 and 2.1.)
+// [tensors in the caches, from memory][one, two, four heads].  (At 96 and 128 the step of one head from memory is 1.1 times the mean one.)
 constexpr SharedCost kShared64[2][3] = {
-    {{3.2, 0.80, 1.05, 1.64, 0.0, 0.08, 256}, {3.5, 0.74, 1.29, 2.38, 0.27, 0.021, 512}, {4.2, 0.64, 1.03, 3.22, 0.34, 0.054, 512}},
-    {{6.3, 1.14, 1.10, 2.06, 0.0, 0.441, 256}, {6.5, 1.0, 1.26, 3.16, 0.24, 0.621, 512}, {7.6, 0.64, 0.95, 4.59, 0.41, 0.05, 512}}};
+    {{1.72, 0.771, 1.01, 0.23, 0.033, 0.083, 1.75, 256}, {2.83, 0.739, 1.24, 1.89, 0.315, 0.017, 0.75, 512}, {3.14, 0.642, 0.953, 2.59, 0.394, 0.047, 1.09, 512}},
+    {{4.79, 1.12, 1.01, 0.59, 0.18, 0.44, 1.72, 256}, {5.62, 0.993, 1.20, 2.50, 0.29, 0.62, 0.90, 512}, {6.86, 0.638, 0.92, 4.15, 0.43, 0.046, 0.76, 512}}};
 constexpr SharedCost kShared96[2][3] = {
-    {{3.7, 1.18, 1.63, 1.97, 0.0, 0.119, 256}, {3.9, 1.05, 1.22, 2.40, 0.126, 0.02, 256}, {4.9, 0.81, 0.94, 3.64, 0.09, 0.022, 256}},
-    {{6.4, 2.50, 1.65, 2.31, 0.33, 0.299, 256}, {6.7, 1.39, 1.25, 2.89, 0.21, 0.436, 256}, {8.5, 0.81, 0.90, 4.68, 0.20, 0.061, 256}}};
+    {{2.23, 1.14, 1.57, 0.60, 0.035, 0.126, 1.70, 256}, {2.80, 1.04, 1.17, 1.46, 0.20, 0.025, 1.18, 256}, {3.95, 0.81, 0.914, 2.90, 0.12, 0.023, 1.0, 256}},
+    {{4.88, 2.06, 1.54, 0.95, 0.515, 0.30, 1.66, 256}, {5.77, 1.38, 1.21, 2.07, 0.29, 0.43, 1.01, 256}, {7.41, 0.807, 0.87, 3.78, 0.24, 0.061, 1.14, 256}}};
 constexpr SharedCost kShared128[2][3] = {
-    {{3.8, 1.23, 1.61, 2.17, 0.0, 0.088, 256}, {4.3, 1.17, 1.39, 2.67, 0.14, 0.03, 256}, {5.4, 0.96, 1.14, 4.13, 0.12, 0.009, 256}},
-    {{6.3, 2.80, 1.67, 2.49, 0.41, 0.234, 256}, {7.1, 1.51, 1.38, 3.20, 0.30, 0.324, 256}, {9.1, 0.95, 0.98, 5.34, 0.39, 0.033, 256}}};
-// The other kernels: that of 64, a workgroup per block, and the pipelined one of 96 and 128, whose walks are cut into pieces that even out.
+    {{1.94, 1.19, 1.53, 0.51, 0.07, 0.093, 2.08, 256}, {2.74, 1.15, 1.28, 1.43, 0.28, 0.029, 1.63, 256}, {4.32, 0.954, 1.105, 3.21, 0.16, 0.011, 1.19, 256}},
+    {{4.65, 2.30, 1.53, 1.05, 0.68, 0.23, 1.75, 256}, {5.78, 1.50, 1.31, 2.03, 0.40, 0.33, 1.48, 256}, {7.94, 0.948, 0.935, 4.43, 0.45, 0.024, 1.18, 256}}};
+// The other kernels: that of 64, a workgroup per block, and the pipelined one of 96 and 128, whose walks may be cut into pieces.
 struct PlainFwdCost {
   double first, walk, all, block, longest, mb;
   double us(const Walks& w, double inner, double kv_mb) const {
@@ -437,22 +435,24 @@ struct PlainFwdCost {
   }
 };
 struct PipeFwdCost {
-  double first, short_walk, block, longest, all, mb;
-  double us(const Walks& w, double inner, double kv_mb) const {
-    const double stages = (double)w.longest, per_cu = inner / 256;
-    return first + std::max(all * w.stages * per_cu, std::min(stages, short_walk)) + block * w.items * per_cu + longest * std::min(stages, 103.0) + mb * kv_mb;
+  double first, piece, all, round, block, cut, part, mb;
+  double us(const Walks& w, const KeySplit& split, double inner, double kv_mb) const {
+    const double per_cu = inner / 256, blocks = (split.target > 0 ? split.pieces : w.items) * per_cu;
+    const double longest = (double)(split.target > 0 ? std::min<int64_t>(split.target, w.longest) : w.longest);
+    return first + std::max(piece * longest, all * w.stages * per_cu) + round * std::ceil(blocks) + block * blocks +
+           (split.target > 0 ? cut + part * split.parts * per_cu : 0.0) + mb * kv_mb;
   }
 };
-constexpr PlainFwdCost kOther64[2] = {{4.0, 0.37, 0.186, 1.10, 0.32, 0.0}, {7.4, 0.38, 0.184, 1.74, 0.30, 0.196}};
-constexpr PipeFwdCost kOther96[2] = {{6.6, 8.3, 7.1, 0.137, 0.88, 0.0}, {11.0, 8.4, 8.8, 0.141, 0.91, 0.011}};
-constexpr PipeFwdCost kOther128[2] = {{7.5, 9.2, 7.6, 0.168, 1.0, 0.0}, {12.0, 9.2, 9.5, 0.157, 1.0, 0.047}};
-constexpr double kAheadFwd64[2] = {0.92, 0.92}, kAheadFwd[2] = {0.77, 0.96};  // shares of the other kernel's time
+constexpr PlainFwdCost kOther64[2] = {{3.98, 0.368, 0.186, 1.10, 0.319, 0.0}, {7.44, 0.382, 0.182, 1.74, 0.305, 0.195}};
+constexpr PipeFwdCost kOther96[2] = {{0.66, 0.618, 0.709, 7.84, 2.80, 6.09, 2.35, 0.021}, {5.71, 0.606, 0.708, 7.39, 4.23, 5.97, 0.0, 0.092}};
+constexpr PipeFwdCost kOther128[2] = {{1.52, 0.687, 0.796, 7.87, 3.55, 7.56, 1.62, 0.037}, {6.04, 0.673, 0.788, 8.05, 4.90, 7.15, 0.0, 0.108}};
+constexpr double kAheadFwd = 0.97;  // share of the other kernel's time that is asked for
 
-int choose_shared_heads(const chunk_attn_desc* d, const Walks& other, int inner, bool pipelined, bool cut) {
+int choose_shared_heads(const chunk_attn_desc* d, const Walks& other, int inner, bool pipelined, const KeySplit& split) {
   if (d->head_dim > 128 || (d->head_dim == 64 && pipelined) || d->num_q_heads > kMaxSharedHeads) return 0;
   // (long walks that are not cut: mostly enough blocks for the chip, and the pipelined kernel's steps are cheaper.  Of 247 drawn chunks 121 were slower
   // with this kernel by more than 2 %, up to 2.8 times; 100 would gain more than 15 %, which the line gives away: few blocks that no cut takes)
-  if (d->head_dim != 64 && !cut && other.longest > kLongSharedWalk) return 0;
+  if (d->head_dim != 64 && split.target == 0 && other.longest > kLongSharedWalk) return 0;
   int64_t items = 0;
   for (int t = 0; t < d->num_segments; ++t) {
     items += (d->segments[t].q_len + 31) / 32;
@@ -463,9 +463,7 @@ int choose_shared_heads(const chunk_attn_desc* d, const Walks& other, int inner,
   const double kv_mb = (double)keys * d->num_kv_heads * d->head_dim * 4e-6;
   double limit[2];  // what the shared kernel may take
   for (int m = 0; m < 2; ++m)
-    limit[m] = d->head_dim == 64   ? kAheadFwd64[m] * kOther64[m].us(other, inner, kv_mb)
-               : d->head_dim == 96 ? kAheadFwd[m] * kOther96[m].us(other, inner, kv_mb)
-                                   : kAheadFwd[m] * kOther128[m].us(other, inner, kv_mb);
+    limit[m] = kAheadFwd * (d->head_dim == 64 ? kOther64[m].us(other, inner, kv_mb) : (d->head_dim == 96 ? kOther96 : kOther128)[m].us(other, split, inner, kv_mb));
   const SharedCost(&costs)[2][3] = d->head_dim == 64 ? kShared64 : d->head_dim == 96 ? kShared96 : kShared128;
   const int group = d->num_q_heads / d->num_kv_heads;
   int best = 0;
@@ -483,10 +481,10 @@ int choose_shared_heads(const chunk_attn_desc* d, const Walks& other, int inner,
       }
     }
     const double wgs = (double)(d->num_q_heads / heads);
-    double now = 0.0;
-    for (int m = 0; m < 2; ++m) now = std::max(now, costs[m][x].us((double)most, steps * wgs, items * wgs, kv_mb) / limit[m]);
-    if (now < best_share) {
-      best_share = now;
+    auto share = [&](int m) { return costs[m][x].us((double)most, steps * wgs, items * wgs, kv_mb) / limit[m]; };
+    const double cached = share(0), memory = share(1);
+    if (cached < 1.0 && memory < 1.0 && cached * memory < best_share) {
+      best_share = cached * memory;
       best = heads;
     }
   }

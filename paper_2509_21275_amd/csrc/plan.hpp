@@ -138,11 +138,16 @@ struct Walks {
   int64_t largest = 0;  // items of the sequence that has most
 };
 Walks count_walks(const chunk_attn_desc* d, int tile_rows);
+struct KeySplit {
+  int target = 0;      // argument of piece_count; 0: nothing is cut
+  int64_t pieces = 0;  // items to run (pieces and whole items)
+  int64_t parts = 0;   // pieces among them that write a partial result
+};
 // Query heads that a workgroup of the forward takes whose waves divide the keys of 32 rows (8 waves: 1, 2 or 4 heads, and as many of them per
 // head as are left), where that ends sooner by the estimate of plan.cpp than the head dimension's other kernel, whose walks are `other`, each
-// run for `inner` (key/value head, head split) pairs, on the software-pipelined kernel or not, cut into pieces or not; 0 where it does not.
+// run for `inner` (key/value head, head split) pairs, on the software-pipelined kernel or not, cut as `split` says; 0 where it does not.
 constexpr int kSharedWaves = 8, kMaxSharedItems = 104;  // (as many items as kernel arguments have room for)
-int choose_shared_heads(const chunk_attn_desc* d, const Walks& other, int inner, bool pipelined, bool cut);
+int choose_shared_heads(const chunk_attn_desc* d, const Walks& other, int inner, bool pipelined, const KeySplit& split);
 // Blocks of the small chunks' backward: tiles of 32 rows of a segment's queries, or of its keys, and the steps of their walks, longest first.
 struct ShareBlock {
   int32_t seg, tile;
@@ -158,11 +163,6 @@ bool shared_backward_fits(const chunk_attn_desc* d);
 int choose_shared_waves(const chunk_attn_desc* d, int head_dim, const Walks& dq, int inner, const Walks& dkv, bool cut);
 // The same for the key-stationary items (`keys` keys each) of one key/value head; a stage is a 32-row query tile of one head.
 Walks count_dkv_walks(const chunk_attn_desc* d, int keys);
-struct KeySplit {
-  int target = 0;      // argument of piece_count; 0: nothing is cut
-  int64_t pieces = 0;  // items to run (pieces and whole items)
-  int64_t parts = 0;   // pieces among them that write a partial result
-};
 // The cut that ends first by the estimate of plan.cpp, given that each item is run for `inner` (key/value head, head
 // split) pairs on `cus` compute units; at most `max_parts` partial results.
 KeySplit choose_key_split(const chunk_attn_desc* d, int tile_rows, int inner, int cus, int64_t max_parts);

@@ -18,13 +18,14 @@ CASES = [  # head dimension, segments, query heads, key/value heads, heads per w
     (64, [(0, 100, 0, 3000)], 32, 8, 1),
     (64, [(0, 65, 0, 513), (65, 64, 513, 576), (129, 1, 1089, 545)], 32, 8, 1),
     (64, [(0, 700, 2, 700), (700, 33, 705, 400)], 32, 8, 2),
-    (64, [(0, 181, 0, 187), (181, 23, 187, 579), (204, 3, 766, 4), (207, 6, 770, 606), (213, 102, 1376, 581)], 48, 12, 4),
+    (64, [(0, 165, 0, 166), (165, 11, 166, 11), (176, 33, 177, 34), (209, 2, 211, 462)], 128, 16, 4),
     (128, [(0, 1, 0, 1)], 1, 1, 1),
     (128, [(0, 32, 0, 32)], 4096, 8, 4),
     (128, [(0, 1, 0, 1100)], 8, 2, 1),
     (128, [(0, 257, 0, 2000)], 3, 3, 1),
     (128, [(0, 64, 0, 1024), (64, 65, 1024, 1089)], 16, 2, 1),
-    (128, [(0, 203, 0, 1704), (203, 211, 1704, 211), (414, 120, 1915, 120)], 32, 8, 2),
+    (128, [(0, 203, 0, 1704), (203, 211, 1704, 211), (414, 120, 1915, 120)], 32, 8, 1),
+    (128, [(0, 203, 0, 1704), (203, 246, 1704, 246), (449, 145, 1950, 145), (594, 220, 2095, 220)], 32, 8, 2),
     (128, [(0, 500, 3, 500)], 32, 8, 2),
     (128, [(65 * i, 65, 65 * i, 65) for i in range(12)], 32, 8, 4),
     (128, [(0, 600, 0, 600)], 64, 8, 4),
