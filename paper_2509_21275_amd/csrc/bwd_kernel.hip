@@ -3349,7 +3349,7 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, Cut cut, i
     P.dkv_split = choose_tile_split(d, dkv_keys(d->head_dim), kCus, kMaxShortParts / d->num_kv_heads);
   if (share_dim > 0 && (pipe || (d->head_dim == 64 && !P.dq_pipe)) && shared_backward_fits(d))  // (before walks are counted)
     P.share_waves = choose_shared_waves(d, share_dim, count_walks(d, dq_rows), d->num_kv_heads * (group / heads_per_wg(group, P.dq_waves)),
-                                        count_dkv_walks(d, dkv_keys(d->head_dim)), P.split.target > 0 || P.dkv_split.target > 0);
+                                        count_dkv_walks(d, dkv_keys(d->head_dim)), P.split, P.dkv_split);
   if (with_plan && P.share_waves == 0) {
     if (P.fused) {
       P.fplan = plan_fused(d, dkv_keys(d->head_dim), kNumXcd, fused_num_bufs(d, dkv_keys(d->head_dim)));

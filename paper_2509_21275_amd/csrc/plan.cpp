@@ -491,26 +491,34 @@ int choose_shared_heads(const chunk_attn_desc* d, const Walks& other, int inner,
   return best;
 }
 
-// The same for the backward: first + the larger of what the longest dQ walk, the longest dK/dV walk and all workgroups together take, least
-// squares over 1290 drawn chunks, off by 5 - 10 % (root mean square).  The other kernels' estimates of 96 and 128 are off by 8 - 19 %, most where few
-// queries meet a few thousand keys and both kinds of walk are cut (they take 33 us there where 48 are estimated), so what is asked for is well ahead; 96 is
-// estimated as 128.  At 14 % ahead (26 % at 96) 113 of 8500 chosen chunks of other draws were slower by more than 2 %, by up to 38 % (17 queries on 1551 keys in two
-// sequences, 128/16 heads, head_dim 128: 35.5 -> 48.9; 7 on 2747, 64/8: 33 -> 40; 38 on 2460, 32/8, 96: 31.1 -> 34.0); with the shares asked for now 2 of 9800, by 6 %.
-// All drawn chunks together, 5000 on the tensors of the call before, are 1.66 (head_dim 64), 1.31 (96) and 1.36 (128) times as fast as without it, where the best
-// choice would be 1.76, 1.51 and 1.56 (2500 on tensors from memory, none slower: 1.58, 1.32 and 1.33 of 1.67, 1.49 and 1.51).
-constexpr double kAheadBwd64 = 0.80, kAheadBwd96 = 0.62, kAheadBwd128 = 0.68;  // shares of the other kernels' time
+// The same for the backward, least squares over 5000 drawn chunks on the tensors of the call before.  Off by 5 - 8 % (root mean square), the other
+// kernels by 7 - 9.  (From memory this kernel gains on the other ones, so one set is enough.)  An estimate from 1290 chunks that knew neither rounds nor
+// the pieces of cut walks, off by 8 - 19 % for the other kernels, was slower by more than 2 % in 122 of 13000 chosen chunks of other draws, by up to 38 % (17
+// queries on 1551 keys in two sequences, 128/16 heads, head_dim 128: 35.5 -> 48.9; 7 on 2747, 64/8: 33 -> 40; 38 on 2460, 32/8, 96: 31.1 -> 34.0).  With
+// this one and the shares asked for, 9 of 11000 chosen chunks of other draws are, by 14 % at most, 2 of 5700 from memory, by 3 %.  All chunks together,
+// by head_dim 64, 96 and 128, 1.65, 1.34 and 1.38 times as fast as without the kernel (from memory 1.58, 1.35 and 1.35), where the best choice would be
+// 1.76, 1.51 and 1.56 (1.67, 1.49 and 1.51): most of the difference is in the chunks that choose_shared_waves refuses outright.
 // Examples, other kernels -> this one: head_dim 64, 8/8 heads, 64 tokens, 8.7 -> 5.3, sequences of 256, 512, 128 and 128, 19.5 -> 10.4, 1024 tokens, 29.4 ->
 // 15.7; 100 queries on 10100 keys, 32/8, 175 -> 72; head_dim 128, 8/8, 500 tokens, 33.4 -> 14.7, 1000, 46.7 -> 27.8, 100 queries on 1100 keys, 45 -> 17.
 struct SharedBwdCost {
-  double first, dq_step, dkv_step, all_dq, all_dkv, workgroup, longest;
+  double first, dq_step, dkv_step, all_dq, all_dkv, workgroup, longest, round, mb;
   int waves, slots;
-  double us(double dq_most, double dkv_most, double dq_all, double dkv_all, double blocks) const {
+  double us(double dq_most, double dkv_most, double dq_all, double dkv_all, double blocks, double kv_mb) const {
     return first + std::max({dq_step * dq_most, dkv_step * dkv_most,
-                             (all_dq * dq_all + all_dkv * dkv_all + workgroup * blocks) / slots + longest * std::max(dq_most, dkv_most)});
+                             (all_dq * dq_all + all_dkv * dkv_all + workgroup * blocks) / slots + longest * std::max(dq_most, dkv_most)}) +
+           round * std::ceil(blocks / slots) + mb * kv_mb;
   }
 };
-constexpr SharedBwdCost kSharedBwd64[2] = {{4.5, 0.585, 1.11, 1.9, 0.69, 2.4, 0.18, 4, 512}, {4.1, 0.82, 1.82, 1.65, 1.31, 2.0, 0.2, 8, 256}};
-constexpr SharedBwdCost kSharedBwd128 = {6.3, 1.03, 1.84, 1.46, 1.74, 3.86, 0.08, 4, 256};
+constexpr SharedBwdCost kSharedBwd64[2] = {{4.13, 0.565, 1.068, 1.94, 0.592, 2.08, 0.087, 0.443, 0.168, 4, 512}, {4.07, 0.641, 1.488, 2.51, 0.277, 1.03, 0.152, 0.402, 0.818, 8, 256}};
+constexpr SharedBwdCost kSharedBwd96 = {5.06, 0.881, 1.664, 1.433, 1.469, 2.65, 0.137, 0.955, 0.067, 4, 256};
+constexpr SharedBwdCost kSharedBwd128 = {5.53, 0.969, 1.762, 1.754, 1.415, 2.87, 0.13, 0.922, 0.093, 4, 256};
+struct OtherBwdCost {
+  double first, dq_piece, dkv_piece, all_dq, all_dkv, block, round, cut, part, mb;
+};
+constexpr OtherBwdCost kOtherBwd64 = {5.99, 0.487, 0.728, 0.32, 0.877, 1.80, 0.878, 2.24, 15.3, 0.156};
+constexpr OtherBwdCost kOtherBwd96 = {8.69, 0.634, 0.835, 0.493, 0.982, 6.37, 6.23, 4.35, 17.4, 0.223};
+constexpr OtherBwdCost kOtherBwd128 = {9.44, 0.723, 0.94, 0.841, 1.04, 6.37, 7.24, 5.33, 15.6, 0.213};
+constexpr double kAheadBwd64 = 0.90, kAheadBwd96 = 0.82, kAheadBwd128 = 0.85;  // shares of the other kernels' time that are asked for
 
 bool shared_backward_fits(const chunk_attn_desc* d) {
   if (d->num_segments > kMaxShareSegs || d->num_q_heads > kMaxSharedHeads) return false;
@@ -519,29 +527,32 @@ bool shared_backward_fits(const chunk_attn_desc* d) {
   return items <= kMaxShareItems;
 }
 
-int choose_shared_waves(const chunk_attn_desc* d, int head_dim, const Walks& dq, int inner, const Walks& dkv, bool cut) {
-  const double DL = (double)dq.longest, KL = (double)dkv.longest, DT = (double)dq.stages * inner / 256, KT = (double)dkv.stages * d->num_kv_heads / 256;
-  const double blocks = (double)(dq.items * inner + dkv.items * d->num_kv_heads) / 256;
-  double other;
-  if (head_dim == 64) {
-    // (long dK/dV walks are cut evenly already; dQ walks are not.  Of 393 drawn chunks 120 were slower with this kernel by more than 2 %, up to 3.1
-    // times, and 190 would gain more than 15 %, up to 2.6 times, which the line gives away)
-    if (cut && dq.longest <= dkv.longest && dkv.longest > 32) return 0;
-    other = cut ? 13.7 + 0.53 * std::min(KL, 8.7) + 0.35 * KT + 0.45 * DL
-                : 7.1 + std::max({0.49 * DL, 0.73 * KL, 0.81 * KT + 2.1 * blocks + 0.4 * std::max(DL, KL)});
-  } else {
-    // (as in the forward.  Of 647 drawn chunks 183 were slower by more than 2 %, up to 2.2 times; 439 would gain more than 15 %, up to 3.2 times, which the
-    // line gives away: few queries on a long context, whose dQ walks find no room for partial results, 10 on 14018 keys, 8/8 heads, head_dim 128,
-    // 377 us where this kernel takes 118)
-    if (!cut && dq.longest > kLongSharedWalk) return 0;
-    other = cut ? 23.1 + 0.75 * std::min(DL, 9.0) + 0.19 * std::min(KL, 36.0) + 1.58 * DT + 0.98 * KT + 8.2 * blocks + 0.028 * DL
-                : 17.0 + std::max({0.72 * DL, 0.95 * KL, 2.53 * DT + 0.58 * KT + 14.8 * blocks});
-  }
+int choose_shared_waves(const chunk_attn_desc* d, int head_dim, const Walks& dq, int inner, const Walks& dkv, const KeySplit& dq_split, const KeySplit& dkv_split) {
+  const bool dq_cut = dq_split.target > 0, dkv_cut = dkv_split.target > 0, cut = dq_cut || dkv_cut;
+  // (long dK/dV walks are cut evenly already; dQ walks are not.  Of 393 drawn chunks 120 were slower with this kernel by more than 2 %, up to 3.1
+  // times, and 190 would gain more than 15 %, up to 2.6 times, which the line gives away)
+  if (head_dim == 64 && cut && dq.longest <= dkv.longest && dkv.longest > 32) return 0;
+  // (as in the forward.  Of 647 drawn chunks 183 were slower by more than 2 %, up to 2.2 times; 439 would gain more than 15 %, up to 3.2 times, which the
+  // line gives away: few queries on a long context, whose dQ walks find no room for partial results, 10 on 14018 keys, 8/8 heads, head_dim 128,
+  // 377 us where this kernel takes 118)
+  if (head_dim != 64 && !cut && dq.longest > kLongSharedWalk) return 0;
   const int group = d->num_q_heads / d->num_kv_heads;
+  int64_t keys = 0;
+  for (int t = 0; t < d->num_segments; ++t) keys += d->segments[t].kv_len;
+  const double kv_mb = (double)keys * d->num_kv_heads * head_dim * 4e-6;
+  const OtherBwdCost& o = head_dim == 64 ? kOtherBwd64 : head_dim == 96 ? kOtherBwd96 : kOtherBwd128;
+  const double dq_piece = (double)(dq_cut ? std::min<int64_t>(dq_split.target, dq.longest) : dq.longest);
+  const double dkv_piece = (double)(dkv_cut ? std::min<int64_t>((int64_t)dkv_split.target * group, dkv.longest) : dkv.longest);
+  const double blocks = (double)((dq_cut ? dq_split.pieces : dq.items) * inner + (dkv_cut ? dkv_split.pieces : dkv.items) * d->num_kv_heads) / 256;
+  const double parts = (double)((dq_cut ? dq_split.parts : 0) * inner + (dkv_cut ? dkv_split.parts : 0) * d->num_kv_heads) / 256;
+  const double other = o.first +
+                       std::max({o.dq_piece * dq_piece, o.dkv_piece * dkv_piece,
+                                 (o.all_dq * dq.stages * inner + o.all_dkv * dkv.stages * d->num_kv_heads) / 256 + o.block * blocks}) +
+                       o.round * std::ceil(blocks) + (cut ? o.cut : 0.0) + o.part * parts + o.mb * kv_mb;
   int best = 0;
   double best_us = (head_dim == 64 ? kAheadBwd64 : head_dim == 96 ? kAheadBwd96 : kAheadBwd128) * other;
   for (int x = 0; x < (head_dim == 64 ? 2 : 1); ++x) {
-    const SharedBwdCost& c = head_dim == 64 ? kSharedBwd64[x] : kSharedBwd128;
+    const SharedBwdCost& c = head_dim == 64 ? kSharedBwd64[x] : head_dim == 96 ? kSharedBwd96 : kSharedBwd128;
     int64_t dq_most = 0, dkv_most = 0, dq_all = 0, dkv_all = 0, dq_items = 0, dkv_items = 0;
     auto add = [&](int64_t steps, int64_t& items_of_kind, int64_t& most, int64_t& all) {
       ++items_of_kind;
@@ -556,7 +567,7 @@ int choose_shared_waves(const chunk_attn_desc* d, int head_dim, const Walks& dq,
       for (int32_t j0 = 0; j0 < s.kv_len; j0 += 32) add((int64_t)(n_qt - std::max(0, j0 - C) / 32) * group, dkv_items, dkv_most, dkv_all);
     }
     const double us = c.us((double)dq_most, (double)dkv_most, (double)dq_all * d->num_q_heads, (double)dkv_all * d->num_kv_heads,
-                           (double)(dq_items * d->num_q_heads + dkv_items * d->num_kv_heads));
+                           (double)(dq_items * d->num_q_heads + dkv_items * d->num_kv_heads), kv_mb);
     if (us < best_us) {
       best_us = us;
       best = c.waves;

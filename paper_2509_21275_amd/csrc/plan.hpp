@@ -159,8 +159,8 @@ std::vector<ShareBlock> share_blocks(const chunk_attn_desc* d, bool keys);
 bool shared_backward_fits(const chunk_attn_desc* d);
 // Waves per workgroup (4, or 8 at head_dim 64) of the backward whose waves divide the walks of 32-row blocks, where it ends sooner by the
 // estimate of plan.cpp than the head dimension's other kernels, whose walks are `dq` (each run for `inner` pairs) and `dkv` (for each
-// key/value head), some of them cut or none; 0 where it does not.  For chunks that fit.  (`head_dim`: that of the tensors; d's is 128 for 96.)
-int choose_shared_waves(const chunk_attn_desc* d, int head_dim, const Walks& dq, int inner, const Walks& dkv, bool cut);
+// key/value head), cut as the splits say; 0 where it does not.  For chunks that fit.  (`head_dim`: that of the tensors; d's is 128 for 96.)
+int choose_shared_waves(const chunk_attn_desc* d, int head_dim, const Walks& dq, int inner, const Walks& dkv, const KeySplit& dq_split, const KeySplit& dkv_split);
 // The same for the key-stationary items (`keys` keys each) of one key/value head; a stage is a 32-row query tile of one head.
 Walks count_dkv_walks(const chunk_attn_desc* d, int keys);
 // The cut that ends first by the estimate of plan.cpp, given that each item is run for `inner` (key/value head, head
