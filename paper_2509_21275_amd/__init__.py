@@ -272,6 +272,15 @@ def chunk_attn_test_routes(desc) -> int:
     return out.value
 
 
+def chunk_attn_test_dkv_keys(desc) -> int:
+    """Test hook: key rows per dK/dV block of the backward that the library runs for a chunk (host only)."""
+    out = ctypes.c_int32(0)
+    rc = _lib.chunk_attn_test_dkv_keys(ctypes.byref(desc), ctypes.byref(out))
+    if rc != 0:
+        raise ChunkAttnError(rc)
+    return out.value
+
+
 def chunk_attn_test_shared_heads(desc) -> int:
     """Test hook: query heads per workgroup of the forward whose waves divide the keys of 32 rows, 0 where another kernel runs (host only)."""
     out = ctypes.c_int32(0)

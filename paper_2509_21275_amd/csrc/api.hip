@@ -556,6 +556,17 @@ int chunk_attn_test_routes(const chunk_attn_desc* desc, int32_t* routes) {
   return CHUNK_ATTN_OK;
 }
 
+int chunk_attn_test_dkv_keys(const chunk_attn_desc* desc, int32_t* keys) {
+  const int rc = validate(desc);
+  if (rc != CHUNK_ATTN_OK) return rc;
+  if (!keys) return CHUNK_ATTN_INVALID_ARG;
+  const chunk_attn_desc w = widened(desc);
+  BwdPlan P;
+  bwd_layout(&w, P, false, kCutFine, bwd_mode() == 0 ? desc->head_dim : 0);
+  *keys = P.share_waves > 0 ? 32 : P.dkv_tall ? kTallKeys : dkv_keys(w.head_dim);
+  return CHUNK_ATTN_OK;
+}
+
 int chunk_attn_test_shared_heads(const chunk_attn_desc* desc, int32_t* heads) {
   const int rc = validate(desc);
   if (rc != CHUNK_ATTN_OK) return rc;

@@ -1305,6 +1305,452 @@ __device__ __forceinline__ void dkv_pipe_blocks(const ArgsPtr<DkvParams> args, c
 }
 
 // ------------------------------------------------------------------------------------------------
+// dkv_tall_blocks (head_dim 128 and 96): the dK/dV blocks of bwd_pipe_kernel where they end sooner than those of dkv_pipe_blocks (tall_pays)
+//
+// A workgroup covers 256 keys, each of its four waves all four contractions of 64 of them: no wave roles, no hand-over, half the barriers, and a stage that
+// has been copied to LDS serves twice the keys.  Stage n is the n-th (head, 32-row query tile) of the walk, as in dkv_pipe_blocks; step g is
+//     S(g) = Q K^T     dK^T += Q^T dS(g-1)     dP(g) = dO V^T - D     dV^T += dO^T P(g)             (matrix pipe, in this order)
+//     dS(g-1) = P(g-1) dP(g-1)  until dK^T needs it,  P(g) = exp2(S(g) c - LSE)  until dV^T needs it,  dS(g) from dP(g)'s end on   (vector)
+// as 4 D / 16 mini-steps of one LDS operand fragment and the two MFMAs it feeds (one per 32-key block), each MFMA with its even share of the vector
+// work behind it.  That order keeps one tile each of S, dP, P and dS alive, 80 registers at most: with K and V fragments (128 at head_dim 128) and the
+// accumulators (256, all the accumulation registers there are) a wave has no room for a second one.  -D is what the sum of dP starts from, and one copy
+// of a stage is issued every NF / PER mini-steps (behind each other they hold the wave up).  What few registers are left decides: two of them reloaded
+// from scratch in every step, each time with a wait for all copies in flight, made a step 2800 -> 3330 cycles (a test looks for that).
+// Bound by the power limit: 8192 queries on 32768 keys, 32/8 heads, the matrix pipes are busy 73 % of the cycles of these blocks, at 1.78 GHz, where
+// dkv_pipe_blocks' were busy 59 % at 1.95 GHz (head_dim 96: 63 % at 1.88, 50 % at 2.09); cycles per 64 MFMAs of a wave 3470 -> 2800, time of these blocks 6.38 -> 5.63
+// ms (96: 5.26 -> 4.66), of the backward 10.75 -> 10.18 (8.76 -> 8.40).  What a step could still save is little: twice the row fragments' reads cost 2.7
+// % of its time, 96 more vector instructions 6 %, twice the copies 2.2 %.
+// ------------------------------------------------------------------------------------------------
+// LDS instructions of one step in program order and the waits that follow from it: mini-step m issues the read of fragment m + AHEAD (two instructions
+// for a transposed one; past the end the next step's first), then extra(m) reads of row values after its first MFMA.  What extra(m) reads is there at
+// the wait of mini-step m + AHEAD + 1.
+template <int DK, int AHEAD>
+struct TallOrder {
+  static constexpr int NF = 4 * DK;
+  static constexpr int EXP0 = DK + 2, DS0 = 3 * DK + 2;  // mini-steps in which the vector work of P and of dS starts; each lasts 2 DK of them
+  static constexpr int cost(int k) { return (k % NF) / DK % 2 == 1 ? 2 : 1; }
+  static constexpr int exps(int m) { return spread(32, EXP0, EXP0 + 2 * DK, m); }  // scores done by the end of mini-step m
+  static constexpr int dss(int m) { return spread(32, DS0, DS0 + 2 * DK, m); }     // (m < 2 NF: the work goes on in the next step)
+  static constexpr int lse_use(int quad) {  // first mini-step that needs the LSE of rows 8 quad + 4 hh ..+3
+    int m = EXP0;
+    while (exps(m) <= 8 * quad) ++m;
+    return m;
+  }
+  static constexpr int lse_read(int quad) { return lse_use(quad) - AHEAD - 1; }
+  static constexpr int d_use() { return 2 * DK; }  // the -D tile: four reads, two in each of two mini-steps
+  static constexpr int extra(int m) {
+    int n = 0;
+    for (int q = 0; q < 4; ++q) n += lse_read(q) == m ? 1 : 0;
+    return n + (m == d_use() - AHEAD - 2 || m == d_use() - AHEAD - 1 ? 2 : 0);
+  }
+  static constexpr int wait(int m) {
+    int n = extra((m - AHEAD + NF) % NF);
+    for (int i = m - AHEAD + 1; i < m; ++i) n += cost((i + AHEAD + NF) % NF) + extra((i + NF) % NF);
+    return n;
+  }
+  // P and dS of the rows of a k-step are packed before the first product that reads them (pair 7 when element 16 has been done)
+  static_assert(exps(3 * DK - 1) >= 17 && exps(3 * DK + DK / 2 - 1) == 32 && dss(NF + DK - 1) >= 16 && dss(NF + DK + DK / 2 - 1) == 32, "the order of a step");
+};
+static_assert(TallOrder<8, 4>::lse_read(0) == 5 && TallOrder<8, 4>::lse_read(3) == 17 && TallOrder<8, 4>::exps(25) == 32 && TallOrder<8, 4>::dss(41) == 32 &&
+              TallOrder<8, 4>::wait(0) == 3 && TallOrder<8, 4>::wait(5) == 4 && TallOrder<8, 4>::wait(14) == 9, "worked out by hand");
+
+template <int D>
+__device__ __forceinline__ void dkv_tall_blocks(const ArgsPtr<DkvParams> args, const int mine) {
+  constexpr int NW = 4;        // waves
+  constexpr int BM = 32;       // query rows per stage
+  constexpr int KC = D / 8;    // 16-byte chunks per operand row
+  constexpr int DK = D / 16;   // k-steps over the head dimension
+  constexpr int DB = D / 32;   // 32-row blocks of dK^T / dV^T
+  constexpr int QT = BM * D;   // elements per operand tile
+  constexpr int DIST = 6;      // stages copied ahead
+  constexpr int NS = DIST + 2; // ring slots: stages g - 1 and g in use, g + 1 .. g + DIST on their way
+  constexpr int NF = 4 * DK;   // fragments (mini-steps) per step: Q rows, Q^T, dO rows, dO^T
+  constexpr int AHEAD = D == 128 ? 4 : 5, RING = 8;   // fragments in flight, names of the fragment ring
+  constexpr int NP = BM * KC / 64;     // 64-slot pieces per tile
+  constexpr int PER = 2 * NP / NW;     // pieces per wave and stage
+  constexpr int RV = 64;               // floats per slot of the LSE / D rows (32 used; a whole wave copies them)
+  constexpr int BOOK = NF - 2;
+  using Order = TallOrder<DK, AHEAD>;
+  constexpr int COPY_EVERY = NF / PER;  // mini-steps from one copy of a stage to the next
+  static_assert(NF % RING == 0 && 2 * DB == DK && NP % 2 == 0 && NF % PER == 0 && NF - 3 <= BOOK, "the schedule of a step");
+
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  lds_bf16* const L = (lds_bf16*)smem;
+  constexpr int R_OFF = NS * 2 * QT;       // slot n % NS holds stage n: [QT] Q rows, then [QT] dO rows (chunk-major); behind the ring
+  lds_f32* const lse_s = (lds_f32*)(L + R_OFF);   // [NS][RV] LSE rows, then [NS][RV] D rows
+  lds_f32* const dsum_s = lse_s + NS * RV;
+  int* const next_block = (int*)((__bf16*)smem + R_OFF + 2 * NS * RV * 2);
+
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // (the lane is counted anew where it is needed: held in registers, it and what follows from it would take those of the steps)
+  auto lane_id = []() __attribute__((always_inline)) {
+    int l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(l));
+    return l;
+  };
+
+  // Persistent, and long equal walks start in groups, as in dkv_pipe_blocks.
+  const int xcd = xcd_of_this_wave();
+  clock_log_stamp(fresh(args).clock_log, 0);
+  int blk = mine;
+  auto start_in_step = [&](const DkvParams& p, int b) __attribute__((always_inline)) {
+    if (p.side_by_side == 0 || b < 0) return;
+    const DkvItem it = load_uniform(p.items, b / p.num_kv_heads);
+    if (it.j0 + it.kv_rows <= it.ctx && (int64_t)it.n_qt * p.group >= kStepsInStep) wait_for_earlier_groups(p.ended, b, p.side_by_side);
+  };
+  if (mine == kClaimBlocks) {
+    if (wave == 0) {
+      const DkvParams p = fresh(args);
+      blk = block_claim_finish(p.taken, p.num_blocks, xcd, block_claim_issue(p.taken, xcd));
+      start_in_step(p, blk);
+    }
+    blk = broadcast_from_wave0(next_block, blk);
+  }
+  while (blk >= 0) {
+  int pending_claim = 0;
+  const DkvParams p = fresh(args);
+  const int kvh = blk % p.num_kv_heads;
+  const DkvItem it = load_uniform(p.items, blk / p.num_kv_heads);
+  const int G = p.group;
+  const int64_t q_stride = (int64_t)p.num_q_heads * D, kv_stride = (int64_t)p.num_kv_heads * D;
+  const float c = p.scale_log2;
+
+  // the Q tile of the slot before the first one, which step 0 reads as stage -1's (dS(-1) = 0)
+  {
+    bf16x8 z;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) z[i] = (__bf16)0.0f;
+    for (int x = wave * 64 + lane_id(); x < QT / 8; x += NW * 64) lds_store8(L + (NS - 1) * 2 * QT + x * 8, z);
+  }
+
+  const int nqt = it.n_qt - it.qt_first;
+  const int n_iter = nqt * G;
+
+  // ---- staging (see dkv_pipe_blocks): copy i of a wave is piece i * 4 + wave of the stage's 2 NP, those of Q first; waves 0 and 1 also copy the
+  // stage's LSE and D rows.  Rows past the segment's last query repeat it (their P is 0) ----
+  // (piece p is chunks 2 p and 2 p + 1 of the rows; p is odd for all copies of a wave or for none, so that they share their rows' order)
+  unsigned v_off;  // byte offset of the lane's chunk of piece 0 or 1 from the tile's first row, but for the piece's own 32 bytes
+  const int last_row = it.q_len - 1 - (it.n_qt - 1) * BM;
+  auto set_offsets = [&](int max_row) __attribute__((always_inline)) {
+    const int lane = lane_id(), hh = lane >> 5, row = (lane & 31) ^ ((2 * (wave & 1) + hh) << 2);
+    v_off = (unsigned)(min(row, max_row) * (int)q_stride + 8 * hh) * 2u;
+  };
+  const bool down = it.reverse != 0;
+  const int qt_start = down ? it.n_qt - 1 : it.qt_first;
+  const int64_t roff0 = (int64_t)(it.q_row_seg + qt_start * BM) * q_stride + (int64_t)(kvh * G) * D;
+  const int64_t rv_first = ((int64_t)(kvh * G) * p.total_q_tiles + it.q_tile0) * 64 + qt_start * BM;
+  const char* d_q = reinterpret_cast<const char*>(p.q + roff0);
+  const char* d_g = reinterpret_cast<const char*>(p.d_o + roff0);
+  const char* d_r = reinterpret_cast<const char*>((wave & 1 ? p.dsp : p.lse2p) + rv_first);
+  const int64_t head_bytes = (int64_t)D * 2;
+  const int64_t head_rows_bytes = p.total_q_tiles * 64 * 4;
+  const int64_t tile_bytes = (down ? -1 : 1) * (int64_t)BM * q_stride * 2 - (G - 1) * head_bytes;
+  const int64_t tile_rows_bytes = (down ? -1 : 1) * (int64_t)BM * 4 - (G - 1) * head_rows_bytes;
+  int d_heads = G, d_tiles = nqt;
+  const int d_ragged = down ? nqt : 1;  // d_tiles while the segment's last query tile is the one to copy
+  unsigned d_slot = 0;
+  lds_f32* const rows_dst = wave & 1 ? dsum_s : lse_s;
+  set_offsets(d_tiles == d_ragged ? last_row : BM - 1);
+  auto dma_rows = [&]() __attribute__((always_inline)) {
+    if (wave < 2) dma4(d_r + (unsigned)lane_id() * 4u, rows_dst + d_slot * RV);
+  };
+  auto dma_piece = [&](int i) __attribute__((always_inline)) {
+    const int piece = i * NW + wave;
+    const bool of_q = NP % NW == 0 ? i < NP / NW : piece < NP;
+    asm volatile("" : "+v"(v_off));  // (widened here, not in registers held for it)
+    dma16((of_q ? d_q + piece * 32 : d_g + (piece - NP) * 32) + v_off, L + d_slot * (2 * QT) + piece * 512);
+  };
+  auto dma_advance = [&]() __attribute__((always_inline)) {
+    if (d_heads > 1) {
+      --d_heads;
+      d_q += head_bytes; d_g += head_bytes; d_r += head_rows_bytes;
+    } else {  // on to the next query tile; after the last stage, stay on it
+      const bool more = d_tiles > 1;
+      d_tiles -= more ? 1 : 0;
+      d_heads = more ? G : 1;
+      const int64_t tb = more ? tile_bytes : 0, tr = more ? tile_rows_bytes : 0;
+      d_q += tb; d_g += tb; d_r += tr;
+      if (__builtin_expect(more && (d_tiles == d_ragged || d_tiles + 1 == d_ragged), 0)) set_offsets(d_tiles == d_ragged ? last_row : BM - 1);
+    }
+    d_slot = d_slot == NS - 1 ? 0u : d_slot + 1;
+  };
+
+  // byte addresses of this lane's operand reads in the Q tile of slot 0; the dO tile is a constant further
+  // (odd k-steps: chunk 2 + hh instead of hh is 1024 bytes further with bit 3 of the row turned over; rows r0 + 8: the same bit)
+  constexpr unsigned ROW8 = 8 * 16;
+  unsigned ev0, lo0, lse0;
+  {
+    const int lane = lane_id(), l32 = lane & 31, hh = lane >> 5;
+    const int j = lane & 15, cl = 2 * ((lane >> 4) & 1) + ((j & 3) >> 1), r0 = 4 * hh + (j >> 2);
+    ev0 = lds_addr(L + cm_elem(l32, hh));
+    lo0 = lds_addr(L + cm_elem(r0, cl) + 4 * (j & 1));
+    lse0 = lds_addr(lse_s + 4 * hh);
+  }
+  constexpr unsigned SLOT = 2 * QT * 2;           // bytes per ring slot
+  constexpr int DO_TILE = QT * 2;                 // bytes from the Q tile to the dO tile
+  constexpr int D_ROWS = NS * RV * 4;             // bytes from the LSE rows to the D rows
+  auto load_rows = [&](unsigned ev_addr, unsigned od_addr, auto ks_c, auto tile_c) __attribute__((always_inline)) {
+    constexpr int ks = decltype(ks_c)::value;
+    constexpr int off = (ks >> 1) * (4 * 32 * 8) * 2 + (ks & 1) * 1024 + decltype(tile_c)::value;
+    return lds_asm_read16<off>((ks & 1) ? od_addr : ev_addr);
+  };
+  auto load_t = [&](unsigned lo_addr, unsigned hi_addr, auto m_c, auto tile_c) __attribute__((always_inline)) {
+    constexpr int m = decltype(m_c)::value;  // ks2 * DB + db
+    constexpr int off = ((m / DB) * (16 * 8) + (m % DB) * (4 * 32 * 8)) * 2 + decltype(tile_c)::value;
+    const s16x4 lo = lds_asm_read_tr<off>(lo_addr);
+    const s16x4 hi = lds_asm_read_tr<off>(hi_addr);
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
+  constexpr std::integral_constant<int, 0> in_q{};
+  constexpr std::integral_constant<int, DO_TILE> in_do{};
+
+  // K and V fragments (B operands): lane holds X[key = 64 wave + 32 kb + l32][16 ks + 8 hh ..+7]
+  bf16x8 kf[2][DK], vf[2][DK];
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb) {
+    const int lane = lane_id();
+    const int64_t grow = it.kv_row0 + min(64 * wave + 32 * kb + (lane & 31), it.kv_rows - 1);
+    const int64_t off = grow * kv_stride + (int64_t)kvh * D + 8 * (lane >> 5);
+#pragma unroll
+    for (int ks = 0; ks < DK; ++ks) {
+      kf[kb][ks] = *reinterpret_cast<const bf16x8*>(p.k + off + 16 * ks);
+      vf[kb][ks] = *reinterpret_cast<const bf16x8*>(p.v + off + 16 * ks);
+    }
+  }
+  // prologue: the copies of stages 0 .. DIST - 1
+#pragma unroll
+  for (int s = 0; s < DIST; ++s) {
+    dma_rows();
+#pragma unroll
+    for (int i = 0; i < PER; ++i) dma_piece(i);
+    dma_advance();
+  }
+  // stages 0 and 1 have landed (a wait the compiler can see, for the fragments).  (Waves 0 and 1 have a copy more per stage and wait for up to
+  // DIST - 2 copies more than they need; so do the waits at the end of a step.)
+  wait_all_but<(DIST - 2) * PER>();
+  wg_barrier();
+
+  const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  f32x16 dk[2][DB], dv[2][DB];  // dK^T, dV^T: [D] x [32 keys of block kb]
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+    for (int db = 0; db < DB; ++db) dk[kb][db] = dv[kb][db] = zero16;
+  f32x16 s[2], dp[2];           // S and dP - D: [key block]
+  u32x4 pw[2][2], sw[2][2];     // P and dS as B operands: [key block][k-step], pairs of bf16
+  dp[0] = dp[1] = zero16;
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) pw[kb][ks] = sw[kb][ks] = u32x4{0, 0, 0, 0};
+  bf16x8 fr[RING];
+  static_for<0, AHEAD>([&](auto k_c) __attribute__((always_inline)) { fr[decltype(k_c)::value] = load_rows(ev0, ev0 ^ ROW8, k_c, in_q); });
+
+  // key index of this lane's column of block 0 relative to the context: query i of the segment sees the column of block kb
+  // iff i >= jrel + l32 + 32 kb
+  const int jrel = it.j0 + 64 * wave - it.ctx;          // (lane 0)
+  const int jrel_hi = it.j0 + 64 * wave + 63 - it.ctx;  // of the wave's last key
+  int s_cur = 0;        // slot of stage g
+  int s_qt = qt_start;  // query tile of stage g
+  int s_heads = G;      // heads of that tile still to come, counting stage g's
+
+  auto step = [&](int g) __attribute__((always_inline)) {
+    const int s_nxt = s_cur == NS - 1 ? 0 : s_cur + 1, s_prv = s_cur == 0 ? NS - 1 : s_cur - 1;
+    const unsigned c_ev = ev0 + s_cur * SLOT, c_od = c_ev ^ ROW8, n_ev = ev0 + s_nxt * SLOT, n_od = n_ev ^ ROW8;
+    const unsigned c_lo = lo0 + s_cur * SLOT, c_hi = c_lo ^ ROW8, p_lo = lo0 + s_prv * SLOT, p_hi = p_lo ^ ROW8;
+    const unsigned r_cur = lse0 + s_cur * (RV * 4);
+    f32x4 rl[4];          // LSE of rows 8 g4 + 4 hh + 0..3
+    f32x4 rd[4];          // -D of the same rows
+    f32x16 rd16;
+    float e_hold;         // the first exponential (or dS) of a pair, until the second one is there
+    // Element x of the vector work: rows in the order in which the products need them, 4 g4 + (x % 4) of block (x / 4) % 2, g4 = x / 8.
+    auto exp_one = [&](auto x_c) __attribute__((always_inline)) {
+      constexpr int x = decltype(x_c)::value, g4 = x / 8, kb = x / 4 % 2, i = 4 * g4 + x % 4;
+      float e = __builtin_amdgcn_exp2f(s[kb][i] * c - rl[g4][i & 3]);
+      asm volatile("" : "+v"(e));
+      s[kb][i] = e;
+    };
+    auto pack_p = [&](auto y_c) __attribute__((always_inline)) {  // pair y: elements 2 y and 2 y + 1
+      constexpr int y = decltype(y_c)::value, kb = y / 2 % 2, w = 2 * (y / 4) + y % 2;
+      bf16x2 v;
+      v[0] = (__bf16)s[kb][2 * w]; v[1] = (__bf16)s[kb][2 * w + 1];
+      unsigned u = __builtin_bit_cast(unsigned, v);
+      asm volatile("" : "+v"(u));
+      pw[kb][w / 4][w % 4] = u;
+    };
+    auto ds_one = [&](auto x_c) __attribute__((always_inline)) {
+      constexpr int x = decltype(x_c)::value, kb = x / 4 % 2, i = 4 * (x / 8) + x % 4, w = i / 2;
+      const unsigned pu = pw[kb][w / 4][w % 4];
+      const float pf = __uint_as_float(i % 2 == 0 ? pu << 16 : pu & 0xffff0000u);
+      float e = pf * dp[kb][i];
+      if constexpr (i % 2 == 0) {
+        asm volatile("" : "+v"(e));
+        e_hold = e;
+      } else {
+        bf16x2 v;
+        v[0] = (__bf16)e_hold; v[1] = (__bf16)e;
+        unsigned u = __builtin_bit_cast(unsigned, v);
+        asm volatile("" : "+v"(u));
+        sw[kb][w / 4][w % 4] = u;
+      }
+    };
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<0, NF>([&](auto m_c) __attribute__((always_inline)) {
+      constexpr int m = decltype(m_c)::value;
+      constexpr int lgkm = Order::wait(m);
+      static_assert(lgkm >= 0 && lgkm <= 15, "lgkmcnt is a 4-bit counter");
+      asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(fr[m % RING]) : "n"(lgkm));
+      if constexpr (m == Order::lse_use(0)) asm volatile("" : "+v"(rl[0]));  // (the row values that this wait covers)
+      if constexpr (m == Order::lse_use(1)) asm volatile("" : "+v"(rl[1]));
+      if constexpr (m == Order::lse_use(2)) asm volatile("" : "+v"(rl[2]));
+      if constexpr (m == Order::lse_use(3)) asm volatile("" : "+v"(rl[3]));
+      if constexpr (m == Order::d_use()) {
+        asm volatile("" : "+v"(rd[0]), "+v"(rd[1]), "+v"(rd[2]), "+v"(rd[3]));
+#pragma unroll
+        for (int i = 0; i < 16; ++i) rd16[i] = rd[i >> 2][i & 3];
+      }
+      if constexpr (m == Order::EXP0) {  // scores that a query does not see, and whole stages past the end of the walk
+        const bool valid = g < n_iter;
+        if (__builtin_expect(!valid || s_qt * BM < jrel_hi, 0)) {
+          const int lane = lane_id();
+          const int lim0 = valid ? jrel - s_qt * BM + (lane & 31) - 4 * (lane >> 5) : 0x40000000, lim1 = lim0 + 32;
+          const float none = -INFINITY;
+          asm volatile("s_nop 15\n\ts_nop 7" : "+v"(s[0]), "+v"(s[1]));  // S(g) has been written
+          // (a compare and a select at a time: 32 masks at once take scalar registers that the steps then miss)
+#pragma unroll
+          for (int kb = 0; kb < 2; ++kb)
+            static_for<0, 16>([&](auto i_c) __attribute__((always_inline)) {
+              constexpr int i = decltype(i_c)::value;
+              float x = s[kb][i];
+              const int lim = kb ? lim1 : lim0;
+              asm volatile("v_cmp_lt_i32 vcc, %1, %2\n\ts_nop 1\n\tv_cndmask_b32 %0, %0, %3, vcc" : "+v"(x) : "n"(8 * (i >> 2) + (i & 3)), "v"(lim), "v"(none) : "vcc");
+              s[kb][i] = x;
+            });
+        }
+      }
+      {  // read the fragment of mini-step m + AHEAD (past the end: the next step's Q rows)
+        constexpr int mm = m + AHEAD;
+        if constexpr (mm < DK) fr[mm % RING] = load_rows(c_ev, c_od, std::integral_constant<int, mm>{}, in_q);
+        else if constexpr (mm < 2 * DK) fr[mm % RING] = load_t(p_lo, p_hi, std::integral_constant<int, mm - DK>{}, in_q);
+        else if constexpr (mm < 3 * DK) fr[mm % RING] = load_rows(c_ev, c_od, std::integral_constant<int, mm - 2 * DK>{}, in_do);
+        else if constexpr (mm < NF) fr[mm % RING] = load_t(c_lo, c_hi, std::integral_constant<int, mm - 3 * DK>{}, in_do);
+        else fr[mm % RING] = load_rows(n_ev, n_od, std::integral_constant<int, mm - NF>{}, in_q);
+      }
+      const bf16x8 fa = fr[m % RING];
+      auto mma = [&](auto kb_c) __attribute__((always_inline)) {
+        constexpr int kb = decltype(kb_c)::value;
+        const bf16x8& a_ = fa;  // (named references: variables used only inside an asm statement are not captured)
+        if constexpr (m < DK) {
+          f32x16& d_ = s[kb];
+          const bf16x8& b_ = kf[kb][m];
+          if (m == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d_) : "v"(a_), "v"(b_));
+          else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d_) : "v"(a_), "v"(b_));
+        } else if constexpr (m < 2 * DK) {
+          constexpr int ks = (m - DK) / DB, db = (m - DK) % DB;
+          dk[kb][db] = mfma32(fa, __builtin_bit_cast(bf16x8, sw[kb][ks]), dk[kb][db]);
+        } else if constexpr (m < 3 * DK) {
+          constexpr int ks = m - 2 * DK;
+          f32x16& d_ = dp[kb];
+          const bf16x8& b_ = vf[kb][ks];
+          const f32x16& c_ = rd16;
+          if (ks == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" : "=&v"(d_) : "v"(a_), "v"(b_), "v"(c_));
+          else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d_) : "v"(a_), "v"(b_));
+        } else {
+          constexpr int ks = (m - 3 * DK) / DB, db = (m - 3 * DK) % DB;
+          dv[kb][db] = mfma32(fa, __builtin_bit_cast(bf16x8, pw[kb][ks]), dv[kb][db]);
+        }
+      };
+      // exponentials, then pairs packed one element late (an exponential cannot be used by the next instruction)
+      constexpr int e0 = Order::exps(m - 1), e1 = Order::exps(m), em = e0 + (e1 - e0 + 1) / 2;
+      constexpr int n0 = Order::dss(m - 1), n1 = Order::dss(m), nm = n0 + (n1 - n0 + 1) / 2;
+      constexpr int l0 = Order::dss(m + NF - 1), l1 = Order::dss(m + NF), lm = l0 + (l1 - l0 + 1) / 2;  // of the stage before
+      mma(std::integral_constant<int, 0>{});
+      if constexpr (m >= Order::EXP0) {
+        static_for<e0, em>(exp_one);
+        static_for<(e0 > 0 ? (e0 - 1) / 2 : 0), (em > 0 ? (em - 1) / 2 : 0)>(pack_p);
+        if constexpr (m >= Order::DS0) static_for<n0, nm>(ds_one);
+      } else {
+        static_for<l0, lm>(ds_one);
+      }
+      static_for<0, 4>([&](auto q_c) __attribute__((always_inline)) {
+        constexpr int q = decltype(q_c)::value;
+        if constexpr (m == Order::lse_read(q)) rl[q] = lds_asm_read16f<32 * q>(r_cur);
+        if constexpr (m == Order::d_use() - AHEAD - 2 + q / 2) rd[q] = lds_asm_read16f<D_ROWS + 32 * q>(r_cur);
+      });
+      __builtin_amdgcn_sched_barrier(0);
+      mma(std::integral_constant<int, 1>{});
+      if constexpr (m >= Order::EXP0) {
+        static_for<em, e1>(exp_one);
+        static_for<(em > 0 ? (em - 1) / 2 : 0), (e1 == 32 && e0 < 32 ? 16 : e1 > 0 ? (e1 - 1) / 2 : 0)>(pack_p);
+        if constexpr (m >= Order::DS0) static_for<nm, n1>(ds_one);
+      } else {
+        static_for<lm, l1>(ds_one);
+      }
+      if constexpr (m == Order::d_use() + 1) asm volatile("" ::"v"(rd16));  // (its registers stay: the first MFMAs of dP read them late)
+      if constexpr (m == 1) dma_rows();
+      if constexpr (m % COPY_EVERY == COPY_EVERY - 3) dma_piece(m / COPY_EVERY);
+      if constexpr (m == BOOK) {  // bookkeeping for the next step (this step's copies have been issued)
+        dma_advance();
+        s_cur = s_nxt;
+        if (--s_heads == 0) {
+          s_heads = G;
+          s_qt += down ? -1 : 1;
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    // stage g + 2 must have landed; the copies of the DIST - 2 stages after it may still be in flight
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((DIST - 2) * PER) : "memory");
+    wg_barrier();
+  };
+  // the last product is dK^T of stage n - 1 in step n
+  const int claim_at = max(0, n_iter - 2);  // the step before which wave 0 claims the next block
+  for (int g = 0; g <= n_iter; ++g) {
+    if (g == claim_at && wave == 0 && mine == kClaimBlocks) pending_claim = block_claim_issue(fresh(args).taken, xcd);
+    step(g);
+  }
+  // the last step's reads ahead are nobody's operands; their registers stay taken until they have arrived
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(fr[i]));
+  // every copy of this wave has landed: once all waves have met at the barrier that hands out the next block, the ring may be filled again
+  __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
+
+  {
+    const DkvParams p = fresh(args);
+    const int64_t kv_stride = (int64_t)p.num_kv_heads * D;
+    const int lane = lane_id(), l32 = lane & 31, hh = lane >> 5;
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+      const int kr = 64 * wave + 32 * kb + l32;
+      if (kr < it.kv_rows) {
+        const int64_t off = ((int64_t)it.kv_row0 + kr) * kv_stride + (int64_t)kvh * D;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            const int64_t e = off + 32 * db + 8 * g + 4 * hh;
+            dkv_store4(p, p.dv, e, dv[kb][db][4 * g], dv[kb][db][4 * g + 1], dv[kb][db][4 * g + 2], dv[kb][db][4 * g + 3]);
+            dkv_store4(p, p.dk, e, dk[kb][db][4 * g] * p.scale, dk[kb][db][4 * g + 1] * p.scale, dk[kb][db][4 * g + 2] * p.scale,
+                       dk[kb][db][4 * g + 3] * p.scale);
+          }
+      }
+    }
+  }
+  if (mine != kClaimBlocks) break;
+  // on to the next block; the stores of the epilogue are not waited for here
+  int nb = 0;
+  if (wave == 0) {
+    const DkvParams p = fresh(args);
+    if (p.side_by_side != 0 && lane_id() == 0) __hip_atomic_fetch_add(p.ended + (blk & 7), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    nb = block_claim_finish(p.taken, p.num_blocks, xcd, pending_claim);
+    start_in_step(p, nb);
+  }
+  blk = broadcast_from_wave0(next_block, nb);
+  }
+  clock_log_stamp(fresh(args).clock_log, 1);
+}
+
+// ------------------------------------------------------------------------------------------------
 // bwd_dkv_narrow_pipe (head_dim 64)
 //
 // With half the head dimension a wave has the registers for all four contractions of its 64 keys (K and V fragments, dK^T and
@@ -2943,7 +3389,7 @@ struct BwdPipeParams {
   DkvParams dkv;
   int32_t dq_phase;
 };
-template <int D, bool CUT>
+template <int D, bool CUT, bool TALL>
 __global__ __launch_bounds__(256, 1) void bwd_pipe_kernel(BwdPipeParams) {
   typedef const __attribute__((address_space(4))) BwdPipeParams* args_ptr;
   for (int phase = 0; phase < 2; ++phase) {
@@ -2958,6 +3404,7 @@ __global__ __launch_bounds__(256, 1) void bwd_pipe_kernel(BwdPipeParams) {
       mine = phase == 0 ? ((int)blockIdx.x < first ? (int)blockIdx.x : -1) : (int)blockIdx.x - first;
     }
     if (is_dq) dq_pipe_blocks<D, CUT>(&args->dq, mine);
+    else if constexpr (TALL) dkv_tall_blocks<D>(&args->dkv, mine);
     else dkv_pipe_blocks<D, CUT>(&args->dkv, mine);
     if (mine >= 0) break;
   }
@@ -3098,6 +3545,9 @@ bool dq_wide_pays(const Walks& w) { return 2 * w.stages >= 11 * w.items; }
 // tokens, 64/8, 394 / 366; 300 queries on 3000 keys, 32/8, 231 / 162; 128 sequences of 128, 32/8, 733 / 700; 40 of 150, 8/8, 122 / 109 (dQ first 113).
 bool short_joins(const BwdPlan& P, int64_t blocks, int threads) { return !P.dq_pipe && !P.dkv_pipe && blocks * threads < (int64_t)1 << 32; }
 
+// keys per dK/dV block of what runs
+int dkv_block_keys(const BwdPlan& P, int head_dim) { return P.dkv_tall ? kTallKeys : dkv_keys(head_dim); }
+
 // workgroups of the pipelined dK/dV kernels on a CU
 constexpr int dkv_per_cu(int head_dim) { return head_dim == 64 ? 2 : 1; }
 
@@ -3190,15 +3640,21 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
       if (!dkv) p.dkv.num_blocks = 0;
       const size_t n_dq_cut = dq ? P.n_dq_cut : 0, n_dkv_cut = dkv ? P.n_dkv_cut : 0;
       const dim3 grid((unsigned)persistent_grid((int64_t)p.dq.num_blocks + p.dkv.num_blocks));
-      if (n_dq_cut == 0 && n_dkv_cut == 0) {
-        static const hipError_t attr = raise_smem_limit(&bwd_pipe_kernel<D, false>, smem);
+      if (P.dkv_tall) {
+        static const hipError_t attr = raise_smem_limit(&bwd_pipe_kernel<D, false, true>, smem);
         if (attr != hipSuccess) return attr;
-        hipLaunchKernelGGL((bwd_pipe_kernel<D, false>), grid, dim3(256), smem, stream, p);
+        hipLaunchKernelGGL((bwd_pipe_kernel<D, false, true>), grid, dim3(256), smem, stream, p);
         return hipGetLastError();
       }
-      static const hipError_t attr = raise_smem_limit(&bwd_pipe_kernel<D, true>, smem);
+      if (n_dq_cut == 0 && n_dkv_cut == 0) {
+        static const hipError_t attr = raise_smem_limit(&bwd_pipe_kernel<D, false, false>, smem);
+        if (attr != hipSuccess) return attr;
+        hipLaunchKernelGGL((bwd_pipe_kernel<D, false, false>), grid, dim3(256), smem, stream, p);
+        return hipGetLastError();
+      }
+      static const hipError_t attr = raise_smem_limit(&bwd_pipe_kernel<D, true, false>, smem);
       if (attr != hipSuccess) return attr;
-      hipLaunchKernelGGL((bwd_pipe_kernel<D, true>), grid, dim3(256), smem, stream, p);
+      hipLaunchKernelGGL((bwd_pipe_kernel<D, true, false>), grid, dim3(256), smem, stream, p);
       const hipError_t err = hipGetLastError();
       if (err != hipSuccess) return err;
       const int64_t dq_units = 8 * (int64_t)n_dq_cut * d->num_kv_heads * pq.head_splits, dkv_units = 8 * (int64_t)n_dkv_cut * d->num_kv_heads;
@@ -3350,6 +3806,9 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, Cut cut, i
   if (share_dim > 0 && (pipe || (d->head_dim == 64 && !P.dq_pipe)) && shared_backward_fits(d))  // (before walks are counted)
     P.share_waves = choose_shared_waves(d, share_dim, count_walks(d, dq_rows), d->num_kv_heads * (group / heads_per_wg(group, P.dq_waves)),
                                         count_dkv_walks(d, dkv_keys(d->head_dim)), P.split, P.dkv_split);
+  // (kCutFine: what runs where a workspace is too small for a chunk's cut keeps to the blocks of the cut run, whose sums it repeats but for their order)
+  if (pipe && cut == kCutFine && !P.fused && P.share_waves == 0 && P.split.target == 0 && P.dkv_split.target == 0)
+    P.dkv_tall = tall_pays(d, dq_rows, d->num_kv_heads * (group / heads_per_wg(group, P.dq_waves)), dkv_keys(d->head_dim), kCus);
   if (with_plan && P.share_waves == 0) {
     if (P.fused) {
       P.fplan = plan_fused(d, dkv_keys(d->head_dim), kNumXcd, fused_num_bufs(d, dkv_keys(d->head_dim)));
@@ -3359,7 +3818,7 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, Cut cut, i
       // the pipelined kernels walk either way; the key blocks of one key/value head that run at the same time are the
       // workgroups of the launch over the number of key/value heads
       const int side_by_side = P.dkv_pipe ? std::max(1, persistent_grid(0x7fffffff, dkv_per_cu(d->head_dim)) / d->num_kv_heads) : 0;
-      P.dkv_items = plan_dkv(d, dkv_keys(d->head_dim), P.dkv_split.target > 0 ? 0 : side_by_side);
+      P.dkv_items = plan_dkv(d, dkv_block_keys(P, d->head_dim), P.dkv_split.target > 0 ? 0 : side_by_side);
       if (P.dkv_split.target > 0) P.dkv_items = cut_items(P.dkv_items, P.dkv_split.target, &P.dkv_cut);
     }
     P.qjobs = query_tile_jobs(d, 64);

@@ -2,6 +2,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <numeric>
 
 namespace chunk_attn {
 
@@ -226,6 +227,26 @@ CutKind key_walks(const chunk_attn_desc* d, int tile_rows, int inner) {
   return k;
 }
 
+// Ends of the last of `cost` (blocks in the order in which they start), dealt to `workers` as they become free; `free_at` is a heap, earliest first.
+int64_t deal(const std::vector<int64_t>& cost, int workers, std::vector<int64_t>& free_at) {
+  free_at.assign(workers, 0);
+  int64_t last = 0;
+  for (int64_t c : cost) {
+    const int64_t end = free_at[0] + c;
+    last = std::max(last, end);
+    int at = 0;  // the earliest one takes the block and sinks to its place
+    for (int child; (child = 2 * at + 1) < workers; at = child) {
+      if (child + 1 < workers && free_at[child + 1] < free_at[child]) ++child;
+      if (free_at[child] >= end) break;
+      free_at[at] = free_at[child];
+    }
+    free_at[at] = end;
+  }
+  return last;
+}
+// Blocks of queue 0 among the `inner` ones that start at block b: those divisible by 8.
+int64_t in_queue(int64_t b, int inner) { return (b + inner + 7) / 8 - (b + 7) / 8; }
+
 CutKind tile_walks(const chunk_attn_desc* d, int keys) {
   CutKind k;
   k.inner = d->num_kv_heads;
@@ -246,13 +267,10 @@ void choose_cut(const CutKind (&kinds)[N], int cus, const int64_t (&max_parts)[N
   constexpr int kStart = 12 * kUnit, kPart = 6 * kUnit, kMerge = 6 * kUnit;
   constexpr int64_t kPartsPerStep = 32;  // partial results (128 KB per block) read per step
   const int workers = std::max(1, cus / 8);
-  std::vector<int> cost;
-  std::vector<int64_t> free_at;
+  std::vector<int64_t> cost, free_at;
   int64_t total = 0;    // work of queue 0 ...
   int largest = 0;      // ... and its longest block
   bool many = false;
-  // blocks of queue 0 among the `inner` ones that start at block b: those divisible by 8
-  auto in_queue = [](int64_t b, int inner) { return (b + inner + 7) / 8 - (b + 7) / 8; };
   auto count_pieces = [&](KeySplit (&k)[N]) {
     for (int i = 0; i < N; ++i) {
       k[i].pieces = k[i].parts = 0;
@@ -308,22 +326,9 @@ void choose_cut(const CutKind (&kinds)[N], int cus, const int64_t (&max_parts)[N
         for (int x = 0; x < n; ++x, block += kind.inner)
           cost.insert(cost.end(), in_queue(block, kind.inner), kind.steps(w, n, x) * kind.cost + kStart + (n > 1 ? kPart : 0));
       }
-      std::sort(cost.begin() + first, cost.end(), [](int a, int b) { return a > b; });
+      std::sort(cost.begin() + first, cost.end(), [](int64_t a, int64_t b) { return a > b; });
     }
-    free_at.assign(workers, 0);  // a heap, earliest first
-    int64_t last = 0;
-    for (int c : cost) {
-      const int64_t end = free_at[0] + c;
-      last = std::max(last, end);
-      int at = 0;  // the earliest one takes the block and sinks to its place
-      for (int child; (child = 2 * at + 1) < workers; at = child) {
-        if (child + 1 < workers && free_at[child + 1] < free_at[child]) ++child;
-        if (free_at[child] >= end) break;
-        free_at[at] = free_at[child];
-      }
-      free_at[at] = end;
-    }
-    return last + merge_time(k);
+    return deal(cost, workers, free_at) + merge_time(k);
   };
   int longest = 0, shortest = 0x7fffffff;  // steps
   for (int i = 0; i < N; ++i) {
@@ -604,6 +609,42 @@ void refine_bwd_split(const chunk_attn_desc* d, int tile_rows, int inner, int ke
   choose_cut<2>(kinds, cus, {max_parts / inner, max_parts / d->num_kv_heads}, best, alone);
   *dq = best[0];
   *dkv = best[1];
+}
+
+// The estimate of refine_bwd_split for uncut walks, with the dK/dV blocks of either size: a step of 256 keys counts as 33/20 of one of 128 (1.61 by its cycles,
+// at a lower clock), its start as 16 steps instead of 12.  Of 388 drawn chunks of 60 us and more (backward, 128 and 96, up to 65536 keys) those that it picks take 3.9 %
+// less, all 388 together, where the best choice would save 4.1 %; two are slower by more than 2 % (3.8: 148 sequences of 129 tokens, 28/4 heads, 475 us).
+// 14147 queries on 14216 keys, 32/8 heads, 4718 -> 4283 us; 4977 on 38367, 64/8, 16275 -> 15116; 3193 on 8192, 32/8, 1116 -> 1044; what stays: 5251 causal tokens,
+// 32/8, 687 (blocks of 256 keys: 931), 4596, 40/8, 680 (982), 6403 on 10177, 28/4, 1884 (2032).
+// (More blocks than kManyBlocks even out by themselves; dealing them would take the host longer than it is worth, 0.1 us each.)
+bool tall_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int cus) {
+  constexpr size_t kManyBlocks = 1024;  // of a queue
+  constexpr int kStep = 20, kDqStage = 25, kTallStep = 33, kStart = 12 * kStep, kTallStart = 16 * kStep;
+  const int workers = std::max(1, cus / 8), group = d->num_q_heads / d->num_kv_heads;
+  // the blocks of queue 0, by kind, longest first
+  auto costs = [&](const CutKind& kind, int step, int start, std::vector<int64_t>& out) {
+    out.clear();
+    int64_t block = 0;
+    for (const auto& w : kind.walks) {
+      out.insert(out.end(), in_queue(block, kind.inner), (int64_t)w.len * kind.steps_per_unit() * step + start);
+      block += kind.inner;
+    }
+    std::sort(out.begin(), out.end(), [](int64_t a, int64_t b) { return a > b; });
+  };
+  std::vector<int64_t> dq, dkv, both, free_at;
+  const CutKind q = key_walks(d, tile_rows, inner);
+  costs(q, kDqStage, kStart, dq);
+  auto end = [&](int block_keys, int step, int start) {
+    const CutKind k = tile_walks(d, block_keys);
+    costs(k, step, start, dkv);
+    const bool dq_first = q.longest > (int64_t)k.longest * group;  // (bwd_layout)
+    both = dq_first ? dq : dkv;
+    const std::vector<int64_t>& second = dq_first ? dkv : dq;
+    if (both.size() + second.size() > kManyBlocks) return std::accumulate(dq.begin(), dq.end(), std::accumulate(dkv.begin(), dkv.end(), (int64_t)0)) / workers;
+    both.insert(both.end(), second.begin(), second.end());
+    return deal(both, workers, free_at);
+  };
+  return end(kTallKeys, kTallStep, kTallStart) < end(keys, kStep, kStart);
 }
 
 std::vector<DkvItem> cut_items(const std::vector<DkvItem>& wholes, int target, std::vector<DkvItem>* cut) {

@@ -174,6 +174,9 @@ KeySplit choose_tile_split(const chunk_attn_desc* d, int keys, int cus, int64_t 
 // themselves (`dq` and `dkv` as they come) anew, or none, with all blocks counted and room for `max_parts` partial results of blocks of either kind.
 // (Each kind by itself has room for fewer, and its pieces may crowd out the other kind's blocks.)
 void refine_bwd_split(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int cus, int64_t max_parts, KeySplit* dq, KeySplit* dkv);
+// Whether the dK/dV blocks of head_dim 96 and 128, none of them cut, end sooner as kTallKeys keys each (dkv_tall_blocks) than as `keys` each.
+constexpr int kTallKeys = 256;
+bool tall_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int cus);
 // The key-stationary items to run for such a cut, longest walk first, of equal ones those that walk the same tiles side by
 // side; `cut` receives the whole items that were cut.
 std::vector<DkvItem> cut_items(const std::vector<DkvItem>& wholes, int target, std::vector<DkvItem>* cut);

@@ -1,0 +1,49 @@
+"""Which chunks of head dimensions 96 and 128 run dK/dV blocks of 256 keys, and what their steps compile to."""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+import paper_2509_21275_amd as ca
+from paper_2509_21275_amd.build import FLAGS
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2509_21275_amd", "csrc")
+
+
+@pytest.mark.parametrize("segs,hq,hk,keys", [
+    ([(0, 8192, 0, 32768)], 32, 8, 256),                            # long walks, four blocks to a compute unit
+    ([(0, 1024, 0, 32768)], 32, 8, 256),
+    ([(0, 16384, 0, 16384)], 64, 8, 256),
+    ([(1000 * i, 1000, 1000 * i, 1000) for i in range(64)], 32, 8, 256),
+    ([(0, 3193, 0, 8192)], 32, 8, 256),
+    ([(0, 4999, 0, 4999)], 32, 8, 128),                              # 160 blocks of 256 keys, the longest twice the even share
+    ([(129 * i, 129, 129 * i, 129) for i in range(64)], 32, 8, 128),  # most of a second 128 keys would be empty
+    ([(0, 1024, 0, 1024)], 8, 8, 32),                                # a small chunk
+])
+@pytest.mark.parametrize("d", [96, 128])
+def test_blocks_that_end_sooner(d, segs, hq, hk, keys):
+    tq, tkv = sum(s[1] for s in segs), segs[-1][2] + segs[-1][3]
+    desc = ca.make_desc(segs, hq, hk, d, tq, tkv, d ** -0.5)
+    cut = ca.chunk_attn_test_routes(desc) & (ca.ROUTE_DQ_CUT | ca.ROUTE_DKV_CUT)
+    assert ca.chunk_attn_test_dkv_keys(desc) == keys and not (cut and keys == 256)
+
+
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+
+@pytest.mark.skipif(shutil.which(HIPCC) is None, reason="needs hipcc")
+def test_steps_of_full_registers_touch_no_scratch(tmp_path):
+    """The steps of kernels whose accumulators fill the accumulation registers spill nothing: a reload in a step waits for all copies in flight
+    (two of them made the dK/dV blocks of head dimension 128 a fifth slower)."""
+    out = str(tmp_path / "bwd.s")
+    r = subprocess.run([HIPCC, *FLAGS, "-x", "hip", "--cuda-device-only", "-S", os.path.join(CSRC, "bwd_kernel.hip"), "-o", out],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    text = open(out).read()
+    for name in ("bwd_pipe_kernelILi128ELb0ELb1", "bwd_pipe_kernelILi96ELb0ELb1"):
+        at = re.search(r"^\S*%s\S*:" % name, text, re.M).end()
+        blocks = re.split(r"^\.LBB\S+:", text[at:text.index(".Lfunc_end", at)], flags=re.M)
+        steps = [b for b in blocks if b.count("v_mfma") >= 4]
+        assert steps and not any("scratch_" in b for b in steps), name
