@@ -563,7 +563,7 @@ int chunk_attn_test_dkv_keys(const chunk_attn_desc* desc, int32_t* keys) {
   const chunk_attn_desc w = widened(desc);
   BwdPlan P;
   bwd_layout(&w, P, false, kCutFine, bwd_mode() == 0 ? desc->head_dim : 0);
-  *keys = P.share_waves > 0 ? 32 : P.dkv_tall ? kTallKeys : dkv_keys(w.head_dim);
+  *keys = P.share_waves > 0 ? 32 : dkv_block_keys(P, w.head_dim);
   return CHUNK_ATTN_OK;
 }
 

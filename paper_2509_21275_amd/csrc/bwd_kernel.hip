@@ -2158,424 +2158,379 @@ __global__ __launch_bounds__(128, 1) void bwd_dkv_narrow_pipe_kernel(DkvParams p
 }
 
 // ------------------------------------------------------------------------------------------------
-// bwd_dkv_wide_pipe (head_dim 256)
+// dkv_wide_blocks (head_dim 256): the dK/dV blocks of bwd_pipe_kernel
 //
-// One wave per SIMD, a workgroup of 4 waves covers 64 keys.  A dK^T or dV^T accumulator for 64 keys takes 256 registers, so the
-// waves have three roles: wave 0, 1 (score waves, 32 keys each, K and V fragments in accumulation registers) run in step g
-//     dP(g) = dO V^T     S(g+1) = Q K^T     P(g) = exp2(S(g) c - LSE),  dS(g) = P(g) (dP(g) - D)
-// and hand P(g) and dS(g) (bf16) over through LDS; wave 2 runs dV^T += dO^T P(g-1), wave 3 dK^T += Q^T dS(g-1), both for all
-// 64 keys.  Every wave has 32 MFMAs per step; a fragment of the gradient waves feeds two of them, one of the score waves one
-// (for both to feed two, S and dP would have to sit in different waves, and Q or dO wait two steps longer in an LDS that
-// has no room for it).  Stage n is the n-th (head, 32-row query tile) of the walk.  LDS is full: five stages of Q (g - 1 and
-// g + 1 in use in step g, g in between, g + 2 and g + 3 on their way) and four of dO (g - 1 and g in use, g + 1 and g + 2 on
-// their way), so that every copy has more than a step to land.  (With four of each, copies had to land within their step and
-// the waves waited for them more than half of the time.)  That leaves room for one P and one dS, so a step has a second
-// barrier in its middle, between the gradient waves' reads of the hand-over and the score waves' next stores; and the score
-// waves do not read ahead over the end of a step, but begin it with exponentials while their first fragments arrive.
-// Against bwd_dkv_kernel (the same split as for head_dim 64, 32 keys per wave, no pipelining): packed 64K chunk, 32/8 heads,
-// 23.8 -> 16.2 ms.
+// One wave per SIMD, no wave roles, as dkv_tall_blocks: a workgroup covers 128 keys, each of its four waves all four contractions of 32 of them, whose
+// accumulators fill the accumulation registers and whose K and V fragments take half of the others.  Stage n is the n-th (head, 32-row query tile) of
+// the walk; step g is
+//     S(g) = Q K^T     dP(g) = dO V^T - D     dV^T += dO^T P(g)     dK^T += Q^T dS(g)               (matrix pipe, in this order)
+//     P(g) = exp2(S(g) c - LSE)  until dV^T needs it,  dS(g) = P(g) dP(g)  until dK^T needs it        (vector)
+// as 64 mini-steps of one LDS operand fragment and the MFMA it feeds.  There is half the vector work per MFMA of head_dim 128, so that it fits under the
+// products of dP and dV, and nothing but fragments lives from one step to the next: a stage leaves LDS with its step, and four slots of Q and dO
+// are enough for copies to have a step to land.  P stays in float32 for dS.
+// A step is bound by its LDS reads (96, and 8 of row values, 16 cycles each to issue; the CU reads 256 KB of LDS per step): its 64 MFMAs take 2048 of 2680 cycles,
+// at 1.74 GHz (the power limit).  Against two score waves that handed P and dS to two gradient waves, for 64 keys, in a launch behind that of dQ: packed
+// 64K chunk, 32/8 heads, forward and backward, 35.3 -> 32.0 ms; backward of 7307 causal tokens 3.6 -> 2.5.
 // ------------------------------------------------------------------------------------------------
+// The schedule of a step, as TallOrder.
+template <int DK, int AHEAD>
+struct WideOrder {
+  static constexpr int NF = 4 * DK;
+  static constexpr int EXP0 = DK + 3, DS0 = 2 * DK + 3;
+  static constexpr int cost(int k) { return (k % NF) / DK >= 2 ? 2 : 1; }
+  static constexpr int exps(int m) { return spread(16, EXP0, 2 * DK + 5, m); }  // scores done by the end of mini-step m
+  static constexpr int dss(int m) { return spread(16, DS0, 3 * DK + 5, m); }
+  static constexpr int lse_use(int quad) {  // first mini-step that needs the LSE of rows 8 quad + 4 hh ..+3
+    int m = EXP0;
+    while (exps(m) <= 4 * quad) ++m;
+    return m;
+  }
+  static constexpr int lse_read(int quad) { return lse_use(quad) - AHEAD - 1; }
+  static constexpr int d_use() { return DK; }  // the -D tile
+  static constexpr int d_read(int quad) { return DK - AHEAD - 4 + quad; }
+  static constexpr int extra(int m) {
+    int n = 0;
+    for (int q = 0; q < 4; ++q) n += (lse_read(q) == m ? 1 : 0) + (d_read(q) == m ? 1 : 0);
+    return n;
+  }
+  static constexpr int wait(int m) {
+    int n = extra((m - AHEAD + NF) % NF);
+    for (int i = m - AHEAD + 1; i < m; ++i) n += cost((i + AHEAD + NF) % NF) + extra((i + NF) % NF);
+    return n;
+  }
+  static_assert(exps(2 * DK - 1) >= 9 && exps(2 * DK + DK / 2 - 1) == 16 && dss(3 * DK - 1) >= 8 && dss(3 * DK + DK / 2 - 1) == 16, "the order of a step");
+};
 template <int D>
-__global__ __launch_bounds__(256, 1) void bwd_dkv_wide_pipe_kernel(DkvParams p, int num_blocks) {
+__device__ __forceinline__ void dkv_wide_blocks(const ArgsPtr<DkvParams> args, const int mine) {
   constexpr int NW = 4;        // waves
   constexpr int BM = 32;       // query rows per stage
   constexpr int KC = D / 8;    // 16-byte chunks per operand row
   constexpr int DK = D / 16;   // k-steps over the head dimension
   constexpr int DB = D / 32;   // 32-row blocks of dK^T / dV^T
   constexpr int QT = BM * D;   // elements per operand tile
-  constexpr int NSQ = 5, NSG = 4;  // ring slots of Q and dO
+  constexpr int DIST = 3;      // stages copied ahead
+  constexpr int NS = DIST + 1; // ring slots: stage g in use, g + 1 .. g + DIST on their way
+  constexpr int NF = 4 * DK;   // fragments (mini-steps) per step: Q rows, dO rows, dO^T, Q^T
+  constexpr int AHEAD = 6, RING = 8;   // fragments in flight, names of the fragment ring
   constexpr int NP = BM * KC / 64;     // 64-slot pieces per tile
-  constexpr int AHEAD = 4, RING = 8;   // fragments in flight, registers of the fragment ring
-  constexpr int PS = 2 * 2 * 64 * 8;   // elements of P or dS of a stage: 2 key blocks x 2 k-steps x 64 lanes x 8
+  constexpr int PER = 2 * NP / NW;     // pieces per wave and stage
   constexpr int RV = 64;               // floats per slot of the LSE / D rows (32 used; a whole wave copies them)
-  constexpr int PER_A = 2, PER_W = NP - PER_A;  // pieces a score wave / a gradient wave copies per stage
-  static_assert(D == 256 && PER_A % 2 == 0 && PER_W <= 2 * DB, "the schedule of a step");
+  constexpr int BOOK = NF - 2;
+  using Order = WideOrder<DK, AHEAD>;
+  constexpr int COPY_EVERY = NF / PER;  // mini-steps from one copy of a stage to the next
+  static_assert(D == 256 && NF % RING == 0 && 2 * DB == DK && NF % PER == 0 && NF - 3 <= BOOK, "the schedule of a step");
 
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   lds_bf16* const L = (lds_bf16*)smem;
-  constexpr int Q_OFF = 0;                 // [NSQ][QT]  Q rows of stage n in slot n % NSQ (chunk-major)
-  constexpr int G_OFF = Q_OFF + NSQ * QT;  // [NSG][QT]  dO rows
-  constexpr int P_OFF = G_OFF + NSG * QT;  // [PS]       P hand-over
-  constexpr int S_OFF = P_OFF + PS;        // [PS]       dS hand-over
-  constexpr int R_OFF = S_OFF + PS;        // [NSQ][RV] floats LSE rows, then [NSG][RV] floats D rows
-  lds_f32* const lse_s = (lds_f32*)(L + R_OFF);
-  lds_f32* const dsum_s = lse_s + NSQ * RV;
+  constexpr int R_OFF = NS * 2 * QT;       // slot n % NS holds stage n: [QT] Q rows, then [QT] dO rows (chunk-major); behind the ring
+  lds_f32* const lse_s = (lds_f32*)(L + R_OFF);   // [NS][RV] LSE rows, then [NS][RV] D rows
+  lds_f32* const dsum_s = lse_s + NS * RV;
+  int* const next_block = (int*)((__bf16*)smem + R_OFF + 2 * NS * RV * 2);
 
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l32 = lane & 31, hh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // (the lane is counted anew where it is needed: held in registers, it and what follows from it would take those of the steps)
+  auto lane_id = []() __attribute__((always_inline)) {
+    int l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(l));
+    return l;
+  };
 
   // Persistent, as dkv_pipe_blocks.
-  __shared__ int next_block;
   const int xcd = xcd_of_this_wave();
-  int blk = 0;
-  if (wave == 0) blk = block_claim_finish(p.taken, num_blocks, xcd, block_claim_issue(p.taken, xcd));
-  blk = broadcast_from_wave0(&next_block, blk);
+  clock_log_stamp(fresh(args).clock_log, 0);
+  int blk = mine;
+  if (mine == kClaimBlocks) {
+    if (wave == 0) {
+      const DkvParams p = fresh(args);
+      blk = block_claim_finish(p.taken, p.num_blocks, xcd, block_claim_issue(p.taken, xcd));
+    }
+    blk = broadcast_from_wave0(next_block, blk);
+  }
   while (blk >= 0) {
   int pending_claim = 0;
+  const DkvParams p = fresh(args);
   const int kvh = blk % p.num_kv_heads;
-  const DkvItem it = p.items[blk / p.num_kv_heads];
+  const DkvItem it = load_uniform(p.items, blk / p.num_kv_heads);
   const int G = p.group;
   const int64_t q_stride = (int64_t)p.num_q_heads * D, kv_stride = (int64_t)p.num_kv_heads * D;
   const float c = p.scale_log2;
 
-  // what step 0 reads of stage -1: the rings' last slots and the hand-over
-  {
-    bf16x8 z;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) z[i] = (__bf16)0.0f;
-    for (int x = tid; x < QT / 8; x += NW * 64) {
-      lds_store8(L + Q_OFF + (NSQ - 1) * QT + x * 8, z);
-      lds_store8(L + G_OFF + (NSG - 1) * QT + x * 8, z);
-    }
-    for (int x = tid; x < 2 * PS / 8; x += NW * 64) lds_store8(L + P_OFF + x * 8, z);
-  }
+  const int nqt = it.n_qt - it.qt_first;
+  const int n_iter = nqt * G;
 
-  const int n_iter = (it.n_qt - it.qt_first) * G;  // stages
-
-  // ---- staging: waves 0 and 3 copy Q (wave 0 also the LSE rows), waves 1 and 2 dO (wave 1 also the D rows); the NP pieces of
-  // a tile (a piece is two chunk columns of 32 rows) are dealt unevenly, PER_A to the score wave.  Past the last stage the
-  // last one is copied again. ----
-  const bool score_wave = wave < 2;
-  const bool of_q = wave == 0 || wave == 3;
-  const int first_piece = score_wave ? 0 : PER_A;
-  unsigned v_full[2], v_last[2];  // byte offset of the lane's chunk of an even / odd piece, without the piece's columns
-  {
-    const int last_row = it.q_len - 1 - (it.n_qt - 1) * BM;
-#pragma unroll
-    for (int par = 0; par < 2; ++par) {
-      const int row = l32 ^ (((2 * par + hh) & 3) << 2);
-      v_full[par] = (unsigned)(row * (int)q_stride + hh * 8) * 2u;
-      v_last[par] = (unsigned)(min(row, last_row) * (int)q_stride + hh * 8) * 2u;
-    }
-  }
+  // ---- staging (see dkv_pipe_blocks): copy i of a wave is piece i * 4 + wave of the stage's 2 NP, those of Q first; waves 0 and 1 also copy the
+  // stage's LSE and D rows.  Rows past the segment's last query repeat it (their P is 0) ----
+  // (piece p is chunks 2 p and 2 p + 1 of the rows; p is odd for all copies of a wave or for none, so that they share their rows' order)
+  unsigned v_off;  // byte offset of the lane's chunk of piece 0 or 1 from the tile's first row, but for the piece's own 32 bytes
+  const int last_row = it.q_len - 1 - (it.n_qt - 1) * BM;
+  auto set_offsets = [&](int max_row) __attribute__((always_inline)) {
+    const int lane = lane_id(), hh = lane >> 5, row = (lane & 31) ^ ((2 * (wave & 1) + hh) << 2);
+    v_off = (unsigned)(min(row, max_row) * (int)q_stride + 8 * hh) * 2u;
+  };
   const bool down = it.reverse != 0;
   const int qt_start = down ? it.n_qt - 1 : it.qt_first;
+  const int64_t roff0 = (int64_t)(it.q_row_seg + qt_start * BM) * q_stride + (int64_t)(kvh * G) * D;
   const int64_t rv_first = ((int64_t)(kvh * G) * p.total_q_tiles + it.q_tile0) * 64 + qt_start * BM;
-  const char* d_x = reinterpret_cast<const char*>((of_q ? p.q : p.d_o) + (int64_t)(it.q_row_seg + qt_start * BM) * q_stride + (int64_t)(kvh * G) * D) +
-                    first_piece * 32;
-  const char* d_r = reinterpret_cast<const char*>((wave ? p.dsp : p.lse2p) + rv_first);
+  const char* d_q = reinterpret_cast<const char*>(p.q + roff0);
+  const char* d_g = reinterpret_cast<const char*>(p.d_o + roff0);
+  const char* d_r = reinterpret_cast<const char*>((wave & 1 ? p.dsp : p.lse2p) + rv_first);
   const int64_t head_bytes = (int64_t)D * 2;
   const int64_t head_rows_bytes = p.total_q_tiles * 64 * 4;
-  const int64_t tile_bytes = (down ? -1 : 1) * (int64_t)BM * q_stride * 2 - (G - 1) * head_bytes;  // from the last head to the first, next tile
+  const int64_t tile_bytes = (down ? -1 : 1) * (int64_t)BM * q_stride * 2 - (G - 1) * head_bytes;
   const int64_t tile_rows_bytes = (down ? -1 : 1) * (int64_t)BM * 4 - (G - 1) * head_rows_bytes;
-  int d_heads = G, d_tiles = it.n_qt - it.qt_first;
-  const int d_ragged = down ? d_tiles : 1;  // d_tiles while the segment's last query tile is the one to copy
-  lds_bf16* const ring = L + (of_q ? Q_OFF : G_OFF) + first_piece * 512;
-  const unsigned ring_end = (unsigned)(((of_q ? NSQ : NSG) - 1) * QT);
-  unsigned d_slot = 0;  // element offset of the slot inside the ring (slot index x QT)
-  const unsigned lane4 = (unsigned)lane * 4u;
-  lds_f32* const rows_dst = wave ? dsum_s : lse_s;
-  auto dma_rows = [&]() __attribute__((always_inline)) { dma4(d_r + lane4, rows_dst + d_slot / (QT / RV)); };
-  auto dma_piece = [&](int i) __attribute__((always_inline)) {  // (the first piece of every wave is even)
-    const unsigned voff = d_tiles == d_ragged ? v_last[i & 1] : v_full[i & 1];
-    dma16(d_x + i * 32 + voff, ring + i * 512 + d_slot);
+  int d_heads = G, d_tiles = nqt;
+  const int d_ragged = down ? nqt : 1;  // d_tiles while the segment's last query tile is the one to copy
+  unsigned d_slot = 0;
+  lds_f32* const rows_dst = wave & 1 ? dsum_s : lse_s;
+  set_offsets(d_tiles == d_ragged ? last_row : BM - 1);
+  auto dma_rows = [&]() __attribute__((always_inline)) {
+    if (wave < 2) dma4(d_r + (unsigned)lane_id() * 4u, rows_dst + d_slot * RV);
+  };
+  auto dma_piece = [&](int i) __attribute__((always_inline)) {
+    const int piece = i * NW + wave;
+    const bool of_q = NP % NW == 0 ? i < NP / NW : piece < NP;
+    asm volatile("" : "+v"(v_off));  // (widened here, not in registers held for it)
+    dma16((of_q ? d_q + piece * 32 : d_g + (piece - NP) * 32) + v_off, L + d_slot * (2 * QT) + piece * 512);
   };
   auto dma_advance = [&]() __attribute__((always_inline)) {
     if (d_heads > 1) {
       --d_heads;
-      d_x += head_bytes; d_r += head_rows_bytes;
+      d_q += head_bytes; d_g += head_bytes; d_r += head_rows_bytes;
     } else {  // on to the next query tile; after the last stage, stay on it
       const bool more = d_tiles > 1;
       d_tiles -= more ? 1 : 0;
       d_heads = more ? G : 1;
-      d_x += more ? tile_bytes : 0;
-      d_r += more ? tile_rows_bytes : 0;
+      const int64_t tb = more ? tile_bytes : 0, tr = more ? tile_rows_bytes : 0;
+      d_q += tb; d_g += tb; d_r += tr;
+      if (__builtin_expect(more && (d_tiles == d_ragged || d_tiles + 1 == d_ragged), 0)) set_offsets(d_tiles == d_ragged ? last_row : BM - 1);
     }
-    d_slot = d_slot == ring_end ? 0u : d_slot + (unsigned)QT;
+    d_slot = d_slot == NS - 1 ? 0u : d_slot + 1;
   };
-  const int ahead = of_q ? 3 : 2;  // stages copied before step 0
-  constexpr unsigned SLOT = QT * 2;  // bytes per ring slot
-  const int claim_at = max(0, n_iter - 3) & ~1;  // the step pair before which wave 0 claims the next block
 
-  if (score_wave) {
-    // ================= score waves: 32 keys, S, P, dP, dS =================
-    bf16x8 kf[DK], vf[DK];  // B operands: lane holds X[key = 32 wave + l32][16 ks + 8 hh ..+7]
-    {
-      const int64_t off = ((int64_t)it.kv_row0 + min(32 * wave + l32, it.kv_rows - 1)) * kv_stride + (int64_t)kvh * D + 8 * hh;
-#pragma unroll
-      for (int ks = 0; ks < DK; ++ks) {
-        kf[ks] = *reinterpret_cast<const bf16x8*>(p.k + off + 16 * ks);
-        vf[ks] = *reinterpret_cast<const bf16x8*>(p.v + off + 16 * ks);
-      }
-    }
-    for (int s = 0; s < ahead; ++s) {
-      dma_rows();
-#pragma unroll
-      for (int i = 0; i < PER_A; ++i) dma_piece(i);
-      dma_advance();
-    }
-    __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0), visible to the compiler
-    wg_barrier();
+  // byte addresses of this lane's operand reads in the Q tile of slot 0; the dO tile is a constant further
+  // (odd k-steps: chunk 2 + hh instead of hh is 1024 bytes further with bit 3 of the row turned over; rows r0 + 8: the same bit)
+  constexpr unsigned ROW8 = 8 * 16;
+  unsigned ev0, lo0, lse0;
+  {
+    const int lane = lane_id(), l32 = lane & 31, hh = lane >> 5;
+    const int j = lane & 15, cl = 2 * ((lane >> 4) & 1) + ((j & 3) >> 1), r0 = 4 * hh + (j >> 2);
+    ev0 = lds_addr(L + cm_elem(l32, hh));
+    lo0 = lds_addr(L + cm_elem(r0, cl) + 4 * (j & 1));
+    lse0 = lds_addr(lse_s + 4 * hh);
+  }
+  constexpr unsigned SLOT = 2 * QT * 2;           // bytes per ring slot
+  constexpr int DO_TILE = QT * 2;                 // bytes from the Q tile to the dO tile
+  constexpr int D_ROWS = NS * RV * 4;             // bytes from the LSE rows to the D rows
+  auto load_rows = [&](unsigned ev_addr, unsigned od_addr, auto ks_c, auto tile_c) __attribute__((always_inline)) {
+    constexpr int ks = decltype(ks_c)::value;
+    constexpr int off = (ks >> 1) * (4 * 32 * 8) * 2 + (ks & 1) * 1024 + decltype(tile_c)::value;
+    return lds_asm_read16<off>((ks & 1) ? od_addr : ev_addr);
+  };
+  auto load_t = [&](unsigned lo_addr, unsigned hi_addr, auto m_c, auto tile_c) __attribute__((always_inline)) {
+    constexpr int m = decltype(m_c)::value;  // ks2 * DB + db
+    constexpr int off = ((m / DB) * (16 * 8) + (m % DB) * (4 * 32 * 8)) * 2 + decltype(tile_c)::value;
+    const s16x4 lo = lds_asm_read_tr<off>(lo_addr);
+    const s16x4 hi = lds_asm_read_tr<off>(hi_addr);
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
+  constexpr std::integral_constant<int, 0> in_q{};
+  constexpr std::integral_constant<int, DO_TILE> in_do{};
 
-    constexpr int NF = 2 * DK;  // fragments (mini-steps of one MFMA): dO rows of stage g, Q rows of stage g + 1
-    // vector work: exponentials 0 .. EXP_PRE - 1 before the first mini-step, the others spread over mini-steps EXP0 .. EXP1 - 1,
-    // the pairs of dS over DS0 .. DS1 - 1; dP(g) is complete after mini-step DK - 1
-    constexpr int EXP_PRE = 6, EXP0 = 0, EXP1 = 14, DS0 = 19, DS1 = 28;
-    constexpr int P_WRITE = 16, S_WRITE0 = 24, S_WRITE1 = 28, D_READ = 4, LSE_READ = 20;
-    static_assert(spread(8, DS0, DS1, S_WRITE0 - 1) >= 4 && spread(8, DS0, DS1, S_WRITE1 - 1) == 8 && DS0 >= DK + 3, "dS before its stores");
-    // LDS instructions of mini-step k after its fragment read, and the wait for fragment m: the instructions issued between
-    // its read (four mini-steps before; those of 0 .. 3 at the start of the step) and mini-step m
-    auto extra = [](int k) constexpr {
-      return (k == P_WRITE || k == P_WRITE + 1 || k == S_WRITE0 || k == S_WRITE1 || (k >= D_READ && k < D_READ + 4) ||
-              (k >= LSE_READ && k < LSE_READ + 4)) ? 1 : 0;
-    };
-    auto lds_wait = [extra](int m) constexpr {
-      int n = NF - 1 - m < AHEAD - 1 ? NF - 1 - m : AHEAD - 1;
-      for (int i = m < AHEAD ? 0 : m - AHEAD; i < m; ++i) n += extra(i);
-      return n;
-    };
-
-    const unsigned ev0 = lds_addr(L + Q_OFF + cm_elem(l32, hh)), od0 = lds_addr(L + Q_OFF + cm_elem(l32, 2 + hh));
-    constexpr int DO_RING = (G_OFF - Q_OFF) * 2;  // bytes from the Q ring to the dO ring: added to the address
-    const unsigned lse0 = lds_addr(lse_s + 4 * hh);
-    constexpr int D_ROWS = NSQ * RV * 4;
-    const unsigned hand0 = lds_addr(L + P_OFF + wave * 1024 + lane * 8);
-    auto load_rows = [&](unsigned ev_addr, unsigned od_addr, auto ks_c) __attribute__((always_inline)) {
-      constexpr int ks = decltype(ks_c)::value;
-      return lds_asm_read16<(ks >> 1) * (4 * 32 * 8) * 2>((ks & 1) ? od_addr : ev_addr);
-    };
-    f32x16 x[2], dp;
-    f32x4 rl[4], rd[4];  // LSE and -D of rows 8 g4 + 4 hh + 0..3
-    bf16x8 fr[RING];
-    {  // S(0), the LSE rows of stage 0
-      static_for<0, 2>([&](auto half_c) __attribute__((always_inline)) {
-        constexpr int k0 = decltype(half_c)::value * (DK / 2);
-        bf16x8 a[DK / 2];
-        static_for<0, DK / 2>([&](auto k_c) __attribute__((always_inline)) {
-          a[decltype(k_c)::value] = load_rows(ev0, od0, std::integral_constant<int, k0 + decltype(k_c)::value>{});
-        });
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  // K and V fragments (B operands): lane holds X[key = 32 wave + l32][16 ks + 8 hh ..+7]
+  bf16x8 kf[DK], vf[DK];
+  {
+    const int lane = lane_id();
+    const int64_t grow = it.kv_row0 + min(32 * wave + (lane & 31), it.kv_rows - 1);
+    const int64_t off = grow * kv_stride + (int64_t)kvh * D + 8 * (lane >> 5);
 #pragma unroll
-        for (int k = 0; k < DK / 2; ++k) asm volatile("" : "+v"(a[k]));  // (after the wait, in this order)
-#pragma unroll
-        for (int k = 0; k < DK / 2; ++k) {
-          f32x16& d_ = x[0];
-          const bf16x8& b_ = kf[k0 + k];
-          if (k0 + k == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d_) : "v"(a[k]), "a"(b_));
-          else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d_) : "v"(a[k]), "a"(b_));
-        }
-      });
-      static_for<0, 4>([&](auto g_c) __attribute__((always_inline)) { rl[decltype(g_c)::value] = lds_asm_read16f<32 * decltype(g_c)::value>(lse0); });
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-      for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(rl[i]));
-      mfma_settle();
-    }
-    // key index of this lane's column relative to the context: query i of the segment sees it iff i >= jrel
-    const int jrel = it.j0 + 32 * wave + l32 - it.ctx, jrel_hi = it.j0 + 32 * wave + 31 - it.ctx;
-    int s_g = 0, s_q = 1;              // slots of dO of stage g and of Q of stage g + 1
-    int s_qt = qt_start, s_heads = G;  // query tile of stage g; heads of the tile still to come
-
-    auto step = [&](int g, f32x16& cur, f32x16& nxt) __attribute__((always_inline)) {
-      const unsigned g_ev = ev0 + DO_RING + s_g * SLOT, g_od = od0 + DO_RING + s_g * SLOT;
-      const unsigned q_ev = ev0 + s_q * SLOT, q_od = od0 + s_q * SLOT;
-      const unsigned r_cur = lse0 + s_g * (RV * 4), r_nxt = lse0 + s_q * (RV * 4);
-      // entry (query 8 (i / 4) + 4 hh + i % 4 of the tile, the lane's key) is visible iff 8 (i / 4) + i % 4 >= lim
-      const bool valid = g < n_iter;
-      if (__builtin_expect(!valid || s_qt * BM < jrel_hi, 0)) {
-        const int lim = valid ? jrel - s_qt * BM - 4 * hh : 0x40000000;
-        asm volatile("s_nop 15\n\ts_nop 7" : "+v"(cur));  // S(g) has been written
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-          if (8 * (i >> 2) + (i & 3) < lim) cur[i] = -INFINITY;
-      }
-      float pf[16];             // P(g)
-      unsigned pw[8], sw[8];    // P(g), dS(g), packed pairs
-      auto pack_p = [&](int j) __attribute__((always_inline)) {  // (one pair late, see bwd_dkv_narrow_pipe_kernel)
-        bf16x2 w;
-        w[0] = (__bf16)pf[2 * j]; w[1] = (__bf16)pf[2 * j + 1];
-        unsigned wu = __builtin_bit_cast(unsigned, w);
-        asm volatile("" : "+v"(wu));
-        pw[j] = wu;
-      };
-      auto exp_one = [&](auto i_c) __attribute__((always_inline)) {
-        constexpr int i = decltype(i_c)::value;
-        if constexpr (i > 0 && i % 2 == 0) pack_p(i / 2 - 1);
-        pf[i] = __builtin_amdgcn_exp2f(cur[i] * c - rl[i >> 2][i & 3]);
-        asm volatile("" : "+v"(pf[i]));
-      };
-      auto ds_pair = [&](auto j_c) __attribute__((always_inline)) {
-        constexpr int j = decltype(j_c)::value, i = 2 * j;
-        bf16x2 w;
-        w[0] = (__bf16)(pf[i] * (dp[i] + rd[i >> 2][i & 3]));
-        w[1] = (__bf16)(pf[i + 1] * (dp[i + 1] + rd[i >> 2][(i & 3) + 1]));
-        unsigned wu = __builtin_bit_cast(unsigned, w);
-        asm volatile("" : "+v"(wu));
-        sw[j] = wu;
-      };
-      auto frag_of = [](const unsigned* w) __attribute__((always_inline)) {
-        const u32x4 v = {w[0], w[1], w[2], w[3]};
-        return __builtin_bit_cast(bf16x8, v);
-      };
-      asm volatile("s_nop 15\n\ts_nop 7" ::: "memory");  // S(g) has been written
-      static_for<0, AHEAD>([&](auto k_c) __attribute__((always_inline)) { fr[decltype(k_c)::value] = load_rows(g_ev, g_od, k_c); });
-      __builtin_amdgcn_sched_barrier(0);
-      static_for<0, EXP_PRE>(exp_one);
-      __builtin_amdgcn_sched_barrier(0);
-      static_for<0, NF>([&](auto m_c) __attribute__((always_inline)) {
-        constexpr int m = decltype(m_c)::value;
-        if constexpr (m == DS0)
-          asm volatile("s_waitcnt lgkmcnt(%5)" : "+v"(fr[m % RING]), "+v"(rd[0]), "+v"(rd[1]), "+v"(rd[2]), "+v"(rd[3]) : "n"(lds_wait(m)));
-        else
-          asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(fr[m % RING]) : "n"(lds_wait(m)));
-        {  // read the fragment of mini-step m + AHEAD
-          constexpr int mm = m + AHEAD;
-          if constexpr (mm < DK) fr[mm % RING] = load_rows(g_ev, g_od, std::integral_constant<int, mm>{});
-          else if constexpr (mm < NF) fr[mm % RING] = load_rows(q_ev, q_od, std::integral_constant<int, mm - DK>{});
-        }
-        const bf16x8 fa = fr[m % RING];
-        {
-          const bf16x8& a_ = fa;  // (named references: variables used only inside an asm statement are not captured)
-          if constexpr (m < DK) {
-            const bf16x8& b_ = vf[m];
-            f32x16& d_ = dp;
-            if (m == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d_) : "v"(a_), "a"(b_));
-            else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d_) : "v"(a_), "a"(b_));
-          } else {
-            const bf16x8& b_ = kf[m - DK];
-            f32x16& d_ = nxt;
-            if (m == DK) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d_) : "v"(a_), "a"(b_));
-            else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d_) : "v"(a_), "a"(b_));
-          }
-        }
-        static_for<EXP_PRE + spread(16 - EXP_PRE, EXP0, EXP1, m - 1), EXP_PRE + spread(16 - EXP_PRE, EXP0, EXP1, m)>(exp_one);
-        static_for<spread(8, DS0, DS1, m - 1), spread(8, DS0, DS1, m)>(ds_pair);
-        if constexpr (m == EXP1) pack_p(7);
-        if constexpr (m == P_WRITE) {
-          wg_barrier();  // the gradient waves have read the hand-over of stage g - 1
-          lds_asm_write16<0>(hand0, frag_of(pw));
-        }
-        if constexpr (m == P_WRITE + 1) lds_asm_write16<1024>(hand0, frag_of(pw + 4));
-        if constexpr (m == S_WRITE0) lds_asm_write16<(S_OFF - P_OFF) * 2>(hand0, frag_of(sw));
-        if constexpr (m == S_WRITE1) lds_asm_write16<(S_OFF - P_OFF) * 2 + 1024>(hand0, frag_of(sw + 4));
-        if constexpr (m >= D_READ && m < D_READ + 4) rd[m - D_READ] = lds_asm_read16f<D_ROWS + 32 * (m - D_READ)>(r_cur);
-        if constexpr (m >= LSE_READ && m < LSE_READ + 4) rl[m - LSE_READ] = lds_asm_read16f<32 * (m - LSE_READ)>(r_nxt);
-        if constexpr (m < 2 * PER_A && m % 2 == 1) dma_piece(m / 2);
-        if constexpr (m == 2 * PER_A + 1) dma_rows();
-        if constexpr (m == 2 * PER_A + 4) {  // bookkeeping for the next step (this step's copies have been issued)
-          dma_advance();
-          s_g = (s_g + 1) & (NSG - 1);
-          s_q = s_q == NSQ - 1 ? 0 : s_q + 1;
-          if (--s_heads == 0) {
-            s_heads = G;
-            s_qt += down ? -1 : 1;
-          }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      });
-      // this wave's copies of the step before have landed (those of this step may still be in flight); its hand-over has
-      // been stored and the LSE rows of the next step have arrived
-      asm volatile("s_waitcnt vmcnt(%4) lgkmcnt(0)" : "+v"(rl[0]), "+v"(rl[1]), "+v"(rl[2]), "+v"(rl[3]) : "n"(PER_A + 1) : "memory");
-      wg_barrier();
-    };
-    for (int g = 0; g <= n_iter; g += 2) {
-      if (g == claim_at && wave == 0) pending_claim = block_claim_issue(p.taken, xcd);
-      step(g, x[0], x[1]);
-      step(g + 1, x[1], x[0]);
-    }
-    __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
-  } else {
-    // ================= gradient waves: dV^T += dO^T P (wave 2), dK^T += Q^T dS (wave 3), 64 keys =================
-    const bool of_k = wave == 3;
-    for (int s = 0; s < ahead; ++s) {
-#pragma unroll
-      for (int i = 0; i < PER_W; ++i) dma_piece(i);
-      dma_advance();
-    }
-    __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0), visible to the compiler
-    wg_barrier();
-
-    constexpr int NF = 2 * DB;  // fragments (mini-steps of two MFMAs): the transposed tile of stage g - 1
-    unsigned lo0, hi0;
-    {
-      const int j = lane & 15, cl = 2 * ((lane >> 4) & 1) + ((j & 3) >> 1), r0 = 4 * hh + (j >> 2);
-      lo0 = lds_addr(L + (of_k ? Q_OFF : G_OFF) + cm_elem(r0, cl) + 4 * (j & 1));
-      hi0 = lds_addr(L + (of_k ? Q_OFF : G_OFF) + cm_elem(r0 + 8, cl) + 4 * (j & 1));
-    }
-    const unsigned hand0 = lds_addr(L + (of_k ? S_OFF : P_OFF) + lane * 8);
-    auto load_t = [&](unsigned lo_addr, unsigned hi_addr, auto m_c) __attribute__((always_inline)) {
-      constexpr int m = decltype(m_c)::value;  // ks2 * DB + db
-      constexpr int off = ((m / DB) * (16 * 8) + (m % DB) * (4 * 32 * 8)) * 2;
-      const s16x4 lo = lds_asm_read_tr<off>(lo_addr);
-      const s16x4 hi = lds_asm_read_tr<off>(hi_addr);
-      return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-    };
-    const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    f32x16 acc[2][DB];  // [D] x [32 keys of block kb]
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int db = 0; db < DB; ++db) acc[kb][db] = zero16;
-    bf16x8 fr[RING], b[2][2];  // fragment ring; P or dS of stage g - 1: [key block][k-step]
-    const int last_slot = (of_k ? NSQ : NSG) - 1;
-    int s_prv = last_slot;     // slot of stage g - 1
-    static_for<0, AHEAD>([&](auto m_c) __attribute__((always_inline)) { fr[decltype(m_c)::value] = load_t(lo0 + last_slot * SLOT, hi0 + last_slot * SLOT, m_c); });
-
-    auto step = [&]() __attribute__((always_inline)) {
-      const int s_cur = s_prv == last_slot ? 0 : s_prv + 1;
-      const unsigned t_lo = lo0 + s_prv * SLOT, t_hi = hi0 + s_prv * SLOT, n_lo = lo0 + s_cur * SLOT, n_hi = hi0 + s_cur * SLOT;
-      b[0][0] = lds_asm_read16<0>(hand0);
-      b[0][1] = lds_asm_read16<1024>(hand0);
-      b[1][0] = lds_asm_read16<2048>(hand0);
-      b[1][1] = lds_asm_read16<3072>(hand0);
-      __builtin_amdgcn_sched_barrier(0);
-      static_for<0, NF>([&](auto m_c) __attribute__((always_inline)) {
-        constexpr int m = decltype(m_c)::value;
-        if constexpr (m == 0)
-          asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(fr[0]), "+v"(fr[1]), "+v"(fr[2]), "+v"(fr[3]), "+v"(b[0][0]), "+v"(b[0][1]), "+v"(b[1][0]), "+v"(b[1][1]));
-        else
-          asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(fr[m % RING]) : "n"(2 * (AHEAD - 1)));
-        {  // read the fragment of mini-step m + AHEAD (past the end: stage g's first)
-          constexpr int mm = m + AHEAD;
-          if constexpr (mm < NF) fr[mm % RING] = load_t(t_lo, t_hi, std::integral_constant<int, mm>{});
-          else fr[mm % RING] = load_t(n_lo, n_hi, std::integral_constant<int, mm - NF>{});
-        }
-        const bf16x8 fa = fr[m % RING];
-        constexpr int ks = m / DB, db = m % DB;
-        acc[0][db] = mfma32(fa, b[0][ks], acc[0][db]);
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (m < PER_W) dma_piece(m);
-        acc[1][db] = mfma32(fa, b[1][ks], acc[1][db]);
-        if constexpr (m == NF / 2 - 1) wg_barrier();  // the hand-over has been read: it may be overwritten
-        if constexpr (m == NF - 2) {
-          dma_advance();
-          s_prv = s_cur;
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      });
-      // this wave's copies of the step before have landed
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER_W) : "memory");
-      wg_barrier();
-    };
-    for (int g = 0; g <= n_iter; g += 2) {
-      step();
-      step();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(fr[i]));
-    __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
-    __bf16* const out = of_k ? p.dk : p.dv;
-    const float f = of_k ? p.scale : 1.0f;
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-      const int kr = 32 * kb + l32;
-      if (kr < it.kv_rows) {
-        const int64_t off = ((int64_t)it.kv_row0 + kr) * kv_stride + (int64_t)kvh * D;
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-          for (int g = 0; g < 4; ++g)
-            dkv_store4(p, out, off + 32 * db + 8 * g + 4 * hh, acc[kb][db][4 * g] * f, acc[kb][db][4 * g + 1] * f,
-                       acc[kb][db][4 * g + 2] * f, acc[kb][db][4 * g + 3] * f);
-      }
+    for (int ks = 0; ks < DK; ++ks) {
+      kf[ks] = *reinterpret_cast<const bf16x8*>(p.k + off + 16 * ks);
+      vf[ks] = *reinterpret_cast<const bf16x8*>(p.v + off + 16 * ks);
     }
   }
+  // prologue: the copies of stages 0 .. DIST - 1
+#pragma unroll
+  for (int s = 0; s < DIST; ++s) {
+    dma_rows();
+#pragma unroll
+    for (int i = 0; i < PER; ++i) dma_piece(i);
+    dma_advance();
+  }
+  // stages 0 and 1 have landed (a wait the compiler can see, for the fragments).  (Waves 0 and 1 have a copy more per stage and wait for up to
+  // DIST - 2 copies more than they need; so do the waits at the end of a step.)
+  wait_all_but<(DIST - 2) * PER>();
+  wg_barrier();
+
+  const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  f32x16 dk[DB], dv[DB];  // dK^T, dV^T: [D] x [32 keys]
+#pragma unroll
+  for (int db = 0; db < DB; ++db) dk[db] = dv[db] = zero16;
+  f32x16 s, dp;           // S, then P, and dP - D
+  u32x4 pw[2], sw[2];     // P and dS as B operands: [k-step], pairs of bf16
+  bf16x8 fr[RING];
+  static_for<0, AHEAD>([&](auto k_c) __attribute__((always_inline)) { fr[decltype(k_c)::value] = load_rows(ev0, ev0 ^ ROW8, k_c, in_q); });
+
+  // index of the wave's first key relative to the context: query i of the segment sees the column of this lane iff i >= jrel + l32
+  const int jrel = it.j0 + 32 * wave - it.ctx;
+  int s_cur = 0;        // slot of stage g
+  int s_qt = qt_start;  // query tile of stage g
+  int s_heads = G;      // heads of that tile still to come, counting stage g's
+
+  auto step = [&]() __attribute__((always_inline)) {
+    const int s_nxt = s_cur == NS - 1 ? 0 : s_cur + 1;
+    const unsigned c_ev = ev0 + s_cur * SLOT, c_od = c_ev ^ ROW8, n_ev = ev0 + s_nxt * SLOT, n_od = n_ev ^ ROW8;
+    const unsigned c_lo = lo0 + s_cur * SLOT, c_hi = c_lo ^ ROW8;
+    const unsigned r_cur = lse0 + s_cur * (RV * 4);
+    f32x4 rl[4];          // LSE of rows 8 g4 + 4 hh + 0..3
+    f32x4 rd[4];          // -D of the same rows
+    f32x16 rd16;
+    float e_hold;         // the first exponential (or dS) of a pair, until the second one is there
+    auto exp_one = [&](auto i_c) __attribute__((always_inline)) {
+      constexpr int i = decltype(i_c)::value;
+      float e = __builtin_amdgcn_exp2f(s[i] * c - rl[i / 4][i & 3]);
+      asm volatile("" : "+v"(e));
+      s[i] = e;
+    };
+    auto pack_p = [&](auto w_c) __attribute__((always_inline)) {  // pair w: scores 2 w and 2 w + 1
+      constexpr int w = decltype(w_c)::value;
+      bf16x2 v;
+      v[0] = (__bf16)s[2 * w]; v[1] = (__bf16)s[2 * w + 1];
+      unsigned u = __builtin_bit_cast(unsigned, v);
+      asm volatile("" : "+v"(u));
+      pw[w / 4][w % 4] = u;
+    };
+    auto ds_one = [&](auto i_c) __attribute__((always_inline)) {
+      constexpr int i = decltype(i_c)::value, w = i / 2;
+      float e = s[i] * dp[i];
+      if constexpr (i % 2 == 0) {
+        asm volatile("" : "+v"(e));
+        e_hold = e;
+      } else {
+        bf16x2 v;
+        v[0] = (__bf16)e_hold; v[1] = (__bf16)e;
+        unsigned u = __builtin_bit_cast(unsigned, v);
+        asm volatile("" : "+v"(u));
+        sw[w / 4][w % 4] = u;
+      }
+    };
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<0, NF>([&](auto m_c) __attribute__((always_inline)) {
+      constexpr int m = decltype(m_c)::value;
+      constexpr int lgkm = Order::wait(m);
+      static_assert(lgkm >= 0 && lgkm <= 15, "lgkmcnt is a 4-bit counter");
+      asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(fr[m % RING]) : "n"(lgkm));
+      if constexpr (m == Order::lse_use(0)) asm volatile("" : "+v"(rl[0]));  // (the row values that this wait covers)
+      if constexpr (m == Order::lse_use(1)) asm volatile("" : "+v"(rl[1]));
+      if constexpr (m == Order::lse_use(2)) asm volatile("" : "+v"(rl[2]));
+      if constexpr (m == Order::lse_use(3)) asm volatile("" : "+v"(rl[3]));
+      if constexpr (m == Order::d_use()) {
+        asm volatile("" : "+v"(rd[0]), "+v"(rd[1]), "+v"(rd[2]), "+v"(rd[3]));
+#pragma unroll
+        for (int i = 0; i < 16; ++i) rd16[i] = rd[i >> 2][i & 3];
+      }
+      if constexpr (m == Order::EXP0) {  // scores that a query does not see
+        if (__builtin_expect(s_qt * BM < jrel + 31, 0)) {
+          const int lane = lane_id();
+          const int lim = jrel - s_qt * BM + (lane & 31) - 4 * (lane >> 5);
+          const float none = -INFINITY;
+          asm volatile("s_nop 15\n\ts_nop 7" : "+v"(s));  // S(g) has been written
+          // (a compare and a select at a time: 16 masks at once take scalar registers that the steps then miss)
+          static_for<0, 16>([&](auto i_c) __attribute__((always_inline)) {
+            constexpr int i = decltype(i_c)::value;
+            float x = s[i];
+            asm volatile("v_cmp_lt_i32 vcc, %1, %2\n\ts_nop 1\n\tv_cndmask_b32 %0, %0, %3, vcc" : "+v"(x) : "n"(8 * (i >> 2) + (i & 3)), "v"(lim), "v"(none) : "vcc");
+            s[i] = x;
+          });
+        }
+      }
+      {  // read the fragment of mini-step m + AHEAD (past the end: the next step's Q rows)
+        constexpr int mm = m + AHEAD;
+        if constexpr (mm < DK) fr[mm % RING] = load_rows(c_ev, c_od, std::integral_constant<int, mm>{}, in_q);
+        else if constexpr (mm < 2 * DK) fr[mm % RING] = load_rows(c_ev, c_od, std::integral_constant<int, mm - DK>{}, in_do);
+        else if constexpr (mm < 3 * DK) fr[mm % RING] = load_t(c_lo, c_hi, std::integral_constant<int, mm - 2 * DK>{}, in_do);
+        else if constexpr (mm < NF) fr[mm % RING] = load_t(c_lo, c_hi, std::integral_constant<int, mm - 3 * DK>{}, in_q);
+        else fr[mm % RING] = load_rows(n_ev, n_od, std::integral_constant<int, mm - NF>{}, in_q);
+      }
+      const bf16x8 fa = fr[m % RING];
+      if constexpr (m < DK) {
+        if (m == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(s) : "v"(fa), "v"(kf[m]));
+        else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(s) : "v"(fa), "v"(kf[m]));
+      } else if constexpr (m < 2 * DK) {
+        constexpr int ks = m - DK;
+        if (ks == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" : "=&v"(dp) : "v"(fa), "v"(vf[ks]), "v"(rd16));
+        else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(dp) : "v"(fa), "v"(vf[ks]));
+      } else if constexpr (m < 3 * DK) {
+        constexpr int ks = (m - 2 * DK) / DB, db = (m - 2 * DK) % DB;
+        dv[db] = mfma32(fa, __builtin_bit_cast(bf16x8, pw[ks]), dv[db]);
+      } else {
+        constexpr int ks = (m - 3 * DK) / DB, db = (m - 3 * DK) % DB;
+        dk[db] = mfma32(fa, __builtin_bit_cast(bf16x8, sw[ks]), dk[db]);
+      }
+      // exponentials, pairs packed one element late (an exponential cannot be used by the next instruction), and dS
+      constexpr int e0 = Order::exps(m - 1), e1 = Order::exps(m), n0 = Order::dss(m - 1), n1 = Order::dss(m);
+      static_for<e0, e1>(exp_one);
+      static_for<(e0 == 16 ? 8 : e0 > 0 ? (e0 - 1) / 2 : 0), (e0 == 16 ? 8 : e1 == 16 ? 8 : e1 > 0 ? (e1 - 1) / 2 : 0)>(pack_p);
+      static_for<n0, n1>(ds_one);
+      static_for<0, 4>([&](auto q_c) __attribute__((always_inline)) {
+        constexpr int q = decltype(q_c)::value;
+        if constexpr (m == Order::lse_read(q)) rl[q] = lds_asm_read16f<32 * q>(r_cur);
+        if constexpr (m == Order::d_read(q)) rd[q] = lds_asm_read16f<D_ROWS + 32 * q>(r_cur);
+      });
+      if constexpr (m == Order::d_use() + 3) asm volatile("" ::"v"(rd16));  // (its registers stay: the first MFMA of dP reads them late)
+      if constexpr (m == 1) dma_rows();
+      if constexpr (m % COPY_EVERY == COPY_EVERY - 3) dma_piece(m / COPY_EVERY);
+      if constexpr (m == BOOK) {  // bookkeeping for the next step (this step's copies have been issued)
+        dma_advance();
+        s_cur = s_nxt;
+        if (--s_heads == 0) {
+          s_heads = G;
+          s_qt += down ? -1 : 1;
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    // stage g + 2 must have landed; the copies of the DIST - 2 stages after it may still be in flight
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((DIST - 2) * PER) : "memory");
+    wg_barrier();
+  };
+  const int claim_at = max(0, n_iter - 3);  // the step before which wave 0 claims the next block
+  for (int g = 0; g < n_iter; ++g) {
+    if (g == claim_at && wave == 0 && mine == kClaimBlocks) pending_claim = block_claim_issue(fresh(args).taken, xcd);
+    step();
+  }
+  // the last step's reads ahead are nobody's operands; their registers stay taken until they have arrived
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(fr[i]));
+  // every copy of this wave has landed: once all waves have met at the barrier that hands out the next block, the ring may be filled again
+  __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
+
+  {
+    const DkvParams p = fresh(args);
+    const int64_t kv_stride = (int64_t)p.num_kv_heads * D;
+    const int lane = lane_id(), hh = lane >> 5;
+    const int kr = 32 * wave + (lane & 31);
+    if (kr < it.kv_rows) {
+      const int64_t off = ((int64_t)it.kv_row0 + kr) * kv_stride + (int64_t)kvh * D;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int64_t e = off + 32 * db + 8 * g + 4 * hh;
+          dkv_store4(p, p.dv, e, dv[db][4 * g], dv[db][4 * g + 1], dv[db][4 * g + 2], dv[db][4 * g + 3]);
+          dkv_store4(p, p.dk, e, dk[db][4 * g] * p.scale, dk[db][4 * g + 1] * p.scale, dk[db][4 * g + 2] * p.scale, dk[db][4 * g + 3] * p.scale);
+        }
+    }
+  }
+  if (mine != kClaimBlocks) break;
   // on to the next block; the stores of the epilogue are not waited for here
   int nb = 0;
-  if (wave == 0) nb = block_claim_finish(p.taken, num_blocks, xcd, pending_claim);
-  blk = broadcast_from_wave0(&next_block, nb);
+  if (wave == 0) {
+    const DkvParams p = fresh(args);
+    nb = block_claim_finish(p.taken, p.num_blocks, xcd, pending_claim);
   }
+  blk = broadcast_from_wave0(next_block, nb);
+  }
+  clock_log_stamp(fresh(args).clock_log, 1);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -3374,7 +3329,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_wide_kernel(DqParams) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// bwd_pipe (head_dim 128 and 96): the dQ and the dK/dV blocks of a chunk in one launch
+// bwd_pipe (head_dim 128 and 96, and 256 where wide_pays): the dQ and the dK/dV blocks of a chunk in one launch
 //
 // The two kinds of block need nothing of each other, so a workgroup that finds no more blocks of one kind goes on to the other:
 // small chunks run both kinds side by side on compute units that one kind alone would leave idle, and no chunk ends twice.  The kind
@@ -3382,7 +3337,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_wide_kernel(DqParams) {
 // the LDS and a wave's registers, whatever the order.  Forward and backward, two launches -> one: 557 causal tokens, 32/8 heads,
 // 123 -> 96 us; two slices of 3193 and 4999 queries (backwards only) 1886 -> 1801; packed 64K chunk, 8192 queries on 32768 keys within 0.3 %;
 // 16384 queries on 131072 keys, 64/8, 230.8 -> 232.5 ms at most (four comparisons, 0.1 - 0.7 %): dQ blocks start as dK/dV blocks end, no longer together,
-// and fetch K and V more often.
+// and fetch K and V more often.  Head_dim 256, 250 queries on 4730 keys, 16/8 heads, backward, 236 -> 168 us; 512 on 8704, 8/8, 384 -> 281.
 // ------------------------------------------------------------------------------------------------
 struct BwdPipeParams {
   DqParams dq;
@@ -3391,6 +3346,7 @@ struct BwdPipeParams {
 };
 template <int D, bool CUT, bool TALL>
 __global__ __launch_bounds__(256, 1) void bwd_pipe_kernel(BwdPipeParams) {
+  static_assert(D != 256 || (!CUT && TALL), "head_dim 256: dq_wide_blocks and dkv_wide_blocks");
   typedef const __attribute__((address_space(4))) BwdPipeParams* args_ptr;
   for (int phase = 0; phase < 2; ++phase) {
     if (phase > 0) wg_barrier();  // every wave has read that no block of the other kind is left: the LDS may be written again
@@ -3403,7 +3359,10 @@ __global__ __launch_bounds__(256, 1) void bwd_pipe_kernel(BwdPipeParams) {
       const int first = args->dq_phase == 0 ? args->dq.num_blocks : args->dkv.num_blocks;
       mine = phase == 0 ? ((int)blockIdx.x < first ? (int)blockIdx.x : -1) : (int)blockIdx.x - first;
     }
-    if (is_dq) dq_pipe_blocks<D, CUT>(&args->dq, mine);
+    if constexpr (D == 256) {
+      if (is_dq) dq_wide_blocks(&args->dq, mine);
+      else dkv_wide_blocks<D>(&args->dkv, mine);
+    } else if (is_dq) dq_pipe_blocks<D, CUT>(&args->dq, mine);
     else if constexpr (TALL) dkv_tall_blocks<D>(&args->dkv, mine);
     else dkv_pipe_blocks<D, CUT>(&args->dkv, mine);
     if (mine >= 0) break;
@@ -3503,24 +3462,18 @@ size_t n_dkv_blocks(const chunk_attn_desc* d) {
   return n;
 }
 
-// Whether head_dim 64 and 256 run their pipelined dK/dV kernels, given the walks of one key/value head.  Those kernels' blocks
-// start and end more slowly than bwd_dkv_kernel's, which has several of them on a CU, so they need two blocks per CU and
-//   64:  24 stages for each of the 512 workgroups that run at a time, and below three blocks per CU walks that are nearly equal
-//        or belong to several sequences, none with more than a quarter of the blocks (one or two long causal sequences
-//        put long walks on the same CU, which then ends last),
-//   256: walks of 14 stages on average.
-// Measured backward, bwd_dkv_kernel / pipelined, head_dim 64 (stages per workgroup): 64 sequences of 64, 8/8 heads (2) 28 / 38
+// Whether head_dim 64 runs its pipelined dK/dV kernel, given the walks of one key/value head.  Its blocks start and end more slowly than
+// bwd_dkv_kernel's, which has several of them on a CU, so it needs two blocks per CU, 24 stages for each of the 512 workgroups that run at a time, and
+// below three blocks per CU walks that are nearly equal or belong to several sequences, none with more than a quarter of the blocks (one or two long causal
+// sequences put long walks on the same CU, which then ends last).
+// Measured backward, bwd_dkv_kernel / pipelined (stages per workgroup): 64 sequences of 64, 8/8 heads (2) 28 / 38
 // us; 64 of 128, 32/8 (16) 83 / 86; 64 of 256, 8/8 (12) 77 / 78; 32 of 256, 32/8 (24) 106 / 101; 128 of 128, 32/8 (32) 170 /
 // 175; 64 of 256 (48) 217 / 202; 16 of 1024 (144) 478 / 390; 128 queries on 16384 keys (32) 325 / 320, 512 (126) 450 / 407.
 // Causal sequences with 512 blocks, 32/8 heads: eight of 1024 265 / 215, four of 2048 438 / 365, two of 4096 604 / 647, one of
 // 8192 1099 / 1222; 8/2: four of 8192 1554 / 1233, two of 16384 2256 / 2414; with 768 blocks: three of 4096 1028 / 811.
-// Head_dim 256 (stages per block): 64 sequences of 64, 8/8 heads (2) 73 / 90; 64 of 256 (5) 334 / 346; 128 of 64, 32/8 (8)
-// 320 / 345; 64 of 128 (12) 381 / 389; 32 of 200 (16) 365 / 322; 64 of 256 (20) 915 / 794; 512 queries on 4096 keys, 8/8
-// (15) 257 / 258, on 8192 490 / 483.
 bool dkv_pipe_pays(const chunk_attn_desc* d, const Walks& w) {
   const int64_t blocks = w.items * d->num_kv_heads, stages = w.stages * d->num_kv_heads;
   if (blocks < 2 * kCus) return false;
-  if (d->head_dim != 64) return stages >= 14 * blocks;
   return stages >= 24 * 2 * kCus && (blocks >= 3 * kCus || 4 * w.largest <= w.items || 10 * stages >= 9 * 2 * kCus * w.longest);
 }
 
@@ -3530,12 +3483,6 @@ bool dkv_pipe_pays(const chunk_attn_desc* d, const Walks& w) {
 // 3000 805 / 754.  What the estimate leaves alone (6500 tokens at 64, 3500 at 256) runs as before.
 constexpr int64_t kMaxShortParts = 2 * kCus;  // partial results of such a chunk (64 MB at most)
 
-// Whether head_dim 256 runs bwd_dq_wide_kernel, whose blocks start and end more slowly than bwd_dq_kernel's: from walks of 5.5 stages on
-// average on.  Backward, bwd_dq_kernel / wide (heads, mean walk): 64 sequences of 70, 8/8 (3) 100 / 105 us; of 170 (5) 190 / 197; of 220 (5.5)
-// 283 / 277; four of 256, 8/8 (6) 50 / 49; 148 queries on 595 keys, 8/2 (17) 76 / 72; 32/8 heads: eight sequences of 220 (4) 107 / 111, 64 of 220 (4) 639 / 652,
-// 64 of 256 (4.5) 776 / 760; 1024 causal tokens (16.5) 144 / 135; 909 on 5603 keys (161) 638 / 598.
-bool dq_wide_pays(const Walks& w) { return 2 * w.stages >= 11 * w.items; }
-
 // Whether a chunk of head_dim 64 or 256 runs its dQ and dK/dV blocks in one launch (bwd_short_kernel): where neither kind is pipelined with
 // blocks of its own shape, as long as one grid holds both.  The kind with the longer walks goes first; at 64, dQ if they are equal.  (A dQ block
 // of 64 holds the place of eight waves in that launch, which the other kind going on under it outweighs.)
@@ -3544,9 +3491,6 @@ bool dq_wide_pays(const Walks& w) { return 2 * w.stages >= 11 * w.items; }
 // times 64 queries on 2000 keys 91 / 67 (dK/dV first 99); head_dim 256, 512 tokens, 8/8, 65 / 38; 148 queries on 595 keys, 8/2, 71 / 42; 1500
 // tokens, 64/8, 394 / 366; 300 queries on 3000 keys, 32/8, 231 / 162; 128 sequences of 128, 32/8, 733 / 700; 40 of 150, 8/8, 122 / 109 (dQ first 113).
 bool short_joins(const BwdPlan& P, int64_t blocks, int threads) { return !P.dq_pipe && !P.dkv_pipe && blocks * threads < (int64_t)1 << 32; }
-
-// keys per dK/dV block of what runs
-int dkv_block_keys(const BwdPlan& P, int head_dim) { return P.dkv_tall ? kTallKeys : dkv_keys(head_dim); }
 
 // workgroups of the pipelined dK/dV kernels on a CU
 constexpr int dkv_per_cu(int head_dim) { return head_dim == 64 ? 2 : 1; }
@@ -3694,6 +3638,25 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
       if (P.n_dkv_cut == 0) e = P.dq_wide ? run(std::false_type{}, wide) : run(std::false_type{}, std::false_type{});
       else e = P.dq_wide ? run(std::true_type{}, wide) : run(std::true_type{}, std::false_type{});
       if (e != hipSuccess) return e;
+    } else if (D == 256 && P.dkv_pipe) {
+      BwdPipeParams p;
+      p.dq = pq;
+      p.dkv = pk;
+      p.dq_phase = P.dq_first ? 0 : 1;
+      // dQ: six ring slots of K and four of V; dK/dV: four of two 32-row operand tiles and of their LSE and D rows, the word that announces the next block
+      const size_t dq_smem = (size_t)10 * 32 * D * 2, dkv_smem = (size_t)2 * 4 * 32 * D * 2 + 2 * 4 * 64 * sizeof(float) + 16;
+      const size_t smem = std::max(dq_smem, dkv_smem);
+      auto run = [&]() {
+        if constexpr (D == 256) {
+          static const hipError_t attr = raise_smem_limit(&bwd_pipe_kernel<D, false, true>, smem);
+          if (attr != hipSuccess) return attr;
+          hipError_t err;
+          if (pe.start && (err = hipEventRecord(pe.start, stream)) != hipSuccess) return err;
+          hipLaunchKernelGGL((bwd_pipe_kernel<D, false, true>), dim3((unsigned)persistent_grid(dq_blocks + dkv_blocks)), dim3(256), smem, stream, p);
+        }
+        return hipGetLastError();
+      };
+      if ((e = run()) != hipSuccess) return e;
     } else if (D == 256 && P.dq_wide) {
       const size_t smem = (size_t)10 * 32 * D * 2;  // six slots of K and four of V
       static const hipError_t attr = raise_smem_limit(&bwd_dq_wide_kernel, smem);
@@ -3721,16 +3684,6 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
         if (pe.start && (e = hipEventRecord(pe.start, stream)) != hipSuccess) return e;
         hipLaunchKernelGGL((bwd_dkv_narrow_pipe_kernel<D>), dim3((unsigned)persistent_grid(dkv_blocks, dkv_per_cu(D))), dim3(128), smem, stream, pk,
                            (int)dkv_blocks);
-      }
-    }
-    if constexpr (D == 256) {
-      if (P.dkv_pipe) {
-        // 5 + 4 ring slots of 32-row Q and dO tiles with their LSE and D rows, a P and a dS hand-over slot
-        const size_t smem = (size_t)9 * 32 * D * 2 + 2 * 2048 * 2 + 9 * 64 * sizeof(float);
-        static const hipError_t attr = raise_smem_limit(&bwd_dkv_wide_pipe_kernel<D>, smem);
-        if (attr != hipSuccess) return attr;
-        if (pe.start && (e = hipEventRecord(pe.start, stream)) != hipSuccess) return e;
-        hipLaunchKernelGGL((bwd_dkv_wide_pipe_kernel<D>), dim3((unsigned)persistent_grid(dkv_blocks)), dim3(256), smem, stream, pk, (int)dkv_blocks);
       }
     }
     if (!joint && !P.dkv_pipe) {
@@ -3771,6 +3724,8 @@ hipError_t zero_uncovered(const chunk_attn_desc* d, const BwdArgs& a, hipStream_
   return hipSuccess;
 }
 
+int dkv_block_keys(const BwdPlan& P, int head_dim) { return P.dkv_tall ? kTallKeys : head_dim == 256 && P.dkv_pipe ? kWideKeys : dkv_keys(head_dim); }
+
 void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, Cut cut, int share_dim) {
   P = BwdPlan{};
   const int group = d->num_q_heads / d->num_kv_heads;
@@ -3781,9 +3736,10 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, Cut cut, i
     P.dq_pipe = pipe_pays(count_walks(d, tile_rows(group, 8)), d->num_kv_heads * (group / heads_per_wg(group, 8)));
     if (P.dq_pipe) P.dq_waves = 8;
   }
-  if (!pipe) P.dkv_pipe = dkv_pipe_pays(d, count_dkv_walks(d, dkv_keys(d->head_dim)));
   const int dq_rows = tile_rows(group, P.dq_waves);
-  if (d->head_dim == 256) P.dq_wide = dq_wide_pays(count_walks(d, dq_rows));
+  if (d->head_dim == 64) P.dkv_pipe = dkv_pipe_pays(d, count_dkv_walks(d, dkv_keys(64)));
+  if (d->head_dim == 256) P.dkv_pipe = wide_pays(d, dq_rows, d->num_kv_heads * (group / heads_per_wg(group, P.dq_waves)), dkv_keys(256), kCus);
+  if (d->head_dim == 256) P.dq_wide = P.dkv_pipe || dq_wide_pays(count_walks(d, dq_rows));
   P.q_tiles = count_tiles(d, false, 64);
   P.qt32_tiles = count_tiles(d, false, 32);
   // head_dim 128: room for dQ tiles in float32, for the one-pass backward or for the partial results of cut dQ walks

@@ -131,7 +131,7 @@ struct BwdPlan {
   size_t n_dq_cut = 0, n_dkv_cut = 0;
   size_t dq_items_off = 0, dq_cut_off = 0, dkv_items_off = 0, dkv_cut_off = 0, qjobs_off = 0, queues_off = 0, upload_bytes = 0, blob_bytes = 0;
   size_t lse2p_off = 0, dsp_off = 0, dq_parts_off = 0, total = 0;
-  // (head_dim 96 and 128 always; dQ: 64 where pipe_pays; dK/dV: 64 and 256 where dkv_pipe_pays)
+  // (head_dim 96 and 128 always; dQ: 64 where pipe_pays; dK/dV: 64 where dkv_pipe_pays, 256 where wide_pays)
   bool dq_pipe = false, dkv_pipe = false;  // the pipelined kernels run
   bool dq_wide = false;                    // head_dim 256: bwd_dq_wide_kernel runs
   int dq_waves = 0;                        // 32-row units of a dQ workgroup
@@ -150,6 +150,8 @@ struct BwdPlan {
 constexpr size_t kFusedSinkBytes = 64 * 16384;  // scratch dQ tiles of the one-pass backward, behind its status word
 constexpr int kNumXcd = 8;  // XCDs of an MI355X: workgroup b runs on XCD b % 8
 
+// keys per dK/dV block of a plan that runs no kernel of the small chunks
+int dkv_block_keys(const BwdPlan& plan, int head_dim);
 // 0: the library's choice, 1: the two-kernel backward, 2: the one-pass backward (head_dim 128 only)
 int bwd_mode();
 // Device memory the caller has set aside for the clock logs of the three pipelined kernels (null: none), and the section

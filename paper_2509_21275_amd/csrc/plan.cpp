@@ -247,6 +247,18 @@ int64_t deal(const std::vector<int64_t>& cost, int workers, std::vector<int64_t>
 // Blocks of queue 0 among the `inner` ones that start at block b: those divisible by 8.
 int64_t in_queue(int64_t b, int inner) { return (b + inner + 7) / 8 - (b + 7) / 8; }
 
+// The costs of queue 0's blocks of a kind, none of them cut, largest first.
+void queue_costs(const CutKind& kind, int step, int start, std::vector<int64_t>& out) {
+  out.clear();
+  int64_t block = 0;
+  for (const auto& w : kind.walks) {
+    out.insert(out.end(), in_queue(block, kind.inner), (int64_t)w.len * kind.steps_per_unit() * step + start);
+    block += kind.inner;
+  }
+  std::sort(out.begin(), out.end(), [](int64_t a, int64_t b) { return a > b; });
+}
+constexpr size_t kManyBlocks = 1024;  // of a queue: they even out by themselves, and dealing them would take the host longer than it is worth, 0.1 us each
+
 CutKind tile_walks(const chunk_attn_desc* d, int keys) {
   CutKind k;
   k.inner = d->num_kv_heads;
@@ -616,27 +628,15 @@ void refine_bwd_split(const chunk_attn_desc* d, int tile_rows, int inner, int ke
 // less, all 388 together, where the best choice would save 4.1 %; two are slower by more than 2 % (3.8: 148 sequences of 129 tokens, 28/4 heads, 475 us).
 // 14147 queries on 14216 keys, 32/8 heads, 4718 -> 4283 us; 4977 on 38367, 64/8, 16275 -> 15116; 3193 on 8192, 32/8, 1116 -> 1044; what stays: 5251 causal tokens,
 // 32/8, 687 (blocks of 256 keys: 931), 4596, 40/8, 680 (982), 6403 on 10177, 28/4, 1884 (2032).
-// (More blocks than kManyBlocks even out by themselves; dealing them would take the host longer than it is worth, 0.1 us each.)
 bool tall_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int cus) {
-  constexpr size_t kManyBlocks = 1024;  // of a queue
   constexpr int kStep = 20, kDqStage = 25, kTallStep = 33, kStart = 12 * kStep, kTallStart = 16 * kStep;
   const int workers = std::max(1, cus / 8), group = d->num_q_heads / d->num_kv_heads;
-  // the blocks of queue 0, by kind, longest first
-  auto costs = [&](const CutKind& kind, int step, int start, std::vector<int64_t>& out) {
-    out.clear();
-    int64_t block = 0;
-    for (const auto& w : kind.walks) {
-      out.insert(out.end(), in_queue(block, kind.inner), (int64_t)w.len * kind.steps_per_unit() * step + start);
-      block += kind.inner;
-    }
-    std::sort(out.begin(), out.end(), [](int64_t a, int64_t b) { return a > b; });
-  };
   std::vector<int64_t> dq, dkv, both, free_at;
   const CutKind q = key_walks(d, tile_rows, inner);
-  costs(q, kDqStage, kStart, dq);
+  queue_costs(q, kDqStage, kStart, dq);
   auto end = [&](int block_keys, int step, int start) {
     const CutKind k = tile_walks(d, block_keys);
-    costs(k, step, start, dkv);
+    queue_costs(k, step, start, dkv);
     const bool dq_first = q.longest > (int64_t)k.longest * group;  // (bwd_layout)
     both = dq_first ? dq : dkv;
     const std::vector<int64_t>& second = dq_first ? dkv : dq;
@@ -645,6 +645,33 @@ bool tall_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int
     return deal(both, workers, free_at);
   };
   return end(kTallKeys, kTallStep, kTallStart) < end(keys, kStep, kStart);
+}
+
+// From two blocks of `keys` per CU and 14 steps each on average on, of 277 drawn chunks two are slower with the pipelined blocks, by 3 and 9 % (thousands of blocks of less
+// than 100 keys).  Below that chunks whose dQ walks are of 8 stages or more on average are decided by estimates in us: the pipelined blocks of both kinds dealt as in tall_pays; the unpipelined ones, whose walks may be cut
+// and so know no longest one, by their number and steps.  Least squares in the logarithm over 556 drawn chunks of 60 us and more (up to 65536 keys, 8 - 64
+// query heads), each run both ways; off by 11 and 8 % (root mean square).  All 556 together take 18.4 % less than with the unpipelined kernels, with the better
+// of the two for each 18.7; eight are slower by more than 2 %, by 11 % at most.  Unpipelined / pipelined: 2668 causal tokens, 8/8 heads, 184 / 148 us; 1428 queries on
+// 3445 keys, 32/8, 578 / 407; 10770 causal, 28/4, 7202 / 4677; 7307, 32/8, 3571 / 2456; what stays: 4335, 8/2, 386 / 655; 899, 64/8, 172 / 298.
+bool wide_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int cus) {
+  const Walks w = count_dkv_walks(d, keys);
+  if (w.items * d->num_kv_heads >= 2 * cus && w.stages >= 14 * w.items) return true;
+  const Walks wq = count_walks(d, tile_rows);
+  if (wq.stages < 8 * wq.items) return false;
+  constexpr int kUs = 20, kDqStage = 24, kDqStart = 16 * kUs, kStep = 29, kStart = 20 * kUs;
+  const int workers = std::max(1, cus / 8), group = d->num_q_heads / d->num_kv_heads;
+  const CutKind q = key_walks(d, tile_rows, inner), k = tile_walks(d, kWideKeys);
+  std::vector<int64_t> dq, dkv, free_at;
+  queue_costs(q, kDqStage, kDqStart, dq);
+  queue_costs(k, kStep, kStart, dkv);
+  const bool dq_first = q.longest > (int64_t)k.longest * group;  // (bwd_layout)
+  std::vector<int64_t>&both = dq_first ? dq : dkv, &second = dq_first ? dkv : dq;
+  both.insert(both.end(), second.begin(), second.end());
+  const int64_t end = both.size() > kManyBlocks ? std::accumulate(both.begin(), both.end(), (int64_t)0) / workers : deal(both, workers, free_at);
+  const double pipelined = 1.57 + 0.984 / kUs * end;
+  const double per_cu = 1.0 / cus, dq_all = std::max((double)wq.stages * inner * per_cu, (double)wq.longest);
+  const double other = 23.1 + 0.42 * dq_all + (21.6 * wq.items * inner + (1.911 * w.stages + 4.71 * w.items) * d->num_kv_heads) * per_cu;
+  return pipelined < 0.96 * other;
 }
 
 std::vector<DkvItem> cut_items(const std::vector<DkvItem>& wholes, int target, std::vector<DkvItem>* cut) {

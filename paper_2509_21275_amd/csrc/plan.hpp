@@ -177,6 +177,14 @@ void refine_bwd_split(const chunk_attn_desc* d, int tile_rows, int inner, int ke
 // Whether the dK/dV blocks of head_dim 96 and 128, none of them cut, end sooner as kTallKeys keys each (dkv_tall_blocks) than as `keys` each.
 constexpr int kTallKeys = 256;
 bool tall_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int cus);
+// Whether head_dim 256 runs the pipelined dQ blocks (dq_wide_blocks) by themselves, which start and end more slowly than bwd_dq_kernel's: from walks of 5.5 stages on
+// average on.  Backward, bwd_dq_kernel / wide (heads, mean walk): 64 sequences of 70, 8/8 (3) 100 / 105 us; of 170 (5) 190 / 197; of 220 (5.5)
+// 283 / 277; four of 256, 8/8 (6) 50 / 49; 148 queries on 595 keys, 8/2 (17) 76 / 72; 32/8 heads: eight sequences of 220 (4) 107 / 111, 64 of 220 (4) 639 / 652,
+// 64 of 256 (4.5) 776 / 760; 1024 causal tokens (16.5) 144 / 135; 909 on 5603 keys (161) 638 / 598.
+inline bool dq_wide_pays(const Walks& w) { return 2 * w.stages >= 11 * w.items; }
+// Whether head_dim 256 runs its pipelined dK/dV blocks, of kWideKeys keys, rather than those of bwd_dkv_kernel, of `keys` (by estimates of both).
+constexpr int kWideKeys = 128;
+bool wide_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int cus);
 // The key-stationary items to run for such a cut, longest walk first, of equal ones those that walk the same tiles side by
 // side; `cut` receives the whole items that were cut.
 std::vector<DkvItem> cut_items(const std::vector<DkvItem>& wholes, int target, std::vector<DkvItem>* cut);

@@ -1,4 +1,4 @@
-"""Which chunks of head dimensions 96 and 128 run dK/dV blocks of 256 keys, and what their steps compile to."""
+"""Which chunks of head dimensions 96 and 128 run dK/dV blocks of 256 keys, which of 256 the pipelined ones of 128 keys, and what their steps compile to."""
 import os
 import re
 import shutil
@@ -30,6 +30,22 @@ def test_blocks_that_end_sooner(d, segs, hq, hk, keys):
     assert ca.chunk_attn_test_dkv_keys(desc) == keys and not (cut and keys == 256)
 
 
+@pytest.mark.parametrize("segs,hq,hk,keys", [
+    ([(0, 16384, 0, 16384)], 32, 8, 128),
+    ([(1000 * i, 1000, 1000 * i, 1000) for i in range(64)], 32, 8, 128),   # two blocks of 64 keys per compute unit and 14 steps each
+    ([(0, 1428, 0, 3445)], 32, 8, 128),                                     # by the estimates
+    ([(0, 2668, 0, 2668)], 8, 8, 128),
+    ([(0, 4335, 0, 4335)], 8, 2, 64),                                       # few blocks with long walks, which the other kernels cut
+    ([(0, 899, 0, 899)], 64, 8, 64),
+    ([(64 * i, 64, 64 * i, 64) for i in range(64)], 8, 8, 64),              # half of every block of 128 keys would be empty
+])
+def test_blocks_of_head_dim_256(segs, hq, hk, keys):
+    tq, tkv = sum(s[1] for s in segs), segs[-1][2] + segs[-1][3]
+    desc = ca.make_desc(segs, hq, hk, 256, tq, tkv, 0.0625)
+    assert ca.chunk_attn_test_dkv_keys(desc) == keys
+    assert bool(ca.chunk_attn_test_routes(desc) & ca.ROUTE_DKV_PIPELINED) == (keys == 128)
+
+
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 
@@ -42,7 +58,7 @@ def test_steps_of_full_registers_touch_no_scratch(tmp_path):
                        capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
     text = open(out).read()
-    for name in ("bwd_pipe_kernelILi128ELb0ELb1", "bwd_pipe_kernelILi96ELb0ELb1"):
+    for name in ("bwd_pipe_kernelILi128ELb0ELb1", "bwd_pipe_kernelILi96ELb0ELb1", "bwd_pipe_kernelILi256ELb0ELb1"):
         at = re.search(r"^\S*%s\S*:" % name, text, re.M).end()
         blocks = re.split(r"^\.LBB\S+:", text[at:text.index(".Lfunc_end", at)], flags=re.M)
         steps = [b for b in blocks if b.count("v_mfma") >= 4]
