@@ -1330,7 +1330,8 @@ __device__ __forceinline__ void store_key_rows(lds_bf16* stage, const f32x16 (&x
 }
 
 // ------------------------------------------------------------------------------------------------
-// dkv_tall_blocks (head_dim 128 and 96): the dK/dV blocks of bwd_pipe_kernel where they end sooner than those of dkv_pipe_blocks (tall_pays)
+// dkv_tall_blocks (head_dim 128, 96 and 64): the dK/dV blocks of bwd_pipe_kernel where they end sooner than those of dkv_pipe_blocks (tall_pays) or, at 64, than
+// those of bwd_dkv_narrow_pipe_kernel in a launch behind that of dQ (narrow_tall_pays)
 //
 // A workgroup covers 256 keys, each of its four waves all four contractions of 64 of them: no wave roles, no hand-over, half the barriers, and a stage that
 // has been copied to LDS serves twice the keys.  Stage n is the n-th (head, 32-row query tile) of the walk, as in dkv_pipe_blocks; step g is
@@ -1343,8 +1344,8 @@ __device__ __forceinline__ void store_key_rows(lds_bf16* stage, const f32x16 (&x
 // from scratch in every step, each time with a wait for all copies in flight, made a step 2800 -> 3330 cycles (a test looks for that).
 // Bound by the power limit: 8192 queries on 32768 keys, 32/8 heads, the matrix pipes are busy 73 % of the cycles of these blocks, at 1.78 GHz, where
 // dkv_pipe_blocks' were busy 59 % at 1.95 GHz (head_dim 96: 63 % at 1.88, 50 % at 2.09); cycles per 64 MFMAs of a wave 3470 -> 2800, time of these blocks 6.38 -> 5.63
-// ms (96: 5.26 -> 4.66), of the backward 10.75 -> 10.18 (8.76 -> 8.40).  What a step could still save is little: twice the row fragments' reads cost 2.7
-// % of its time, 96 more vector instructions 6 %, twice the copies 2.2 %.
+// ms (96: 5.26 -> 4.66), of the backward 10.75 -> 10.18 (8.76 -> 8.40); at 64, 8192 queries on 16384 keys, 3.00 -> 2.72.  What a step could still save is little: twice the row fragments' reads cost 2.7
+// % of its time, 96 more vector instructions 6 %, twice the copies 2.2 %.  Head_dim 64 has registers for P in float32, which dS then takes (32 instructions less).
 // ------------------------------------------------------------------------------------------------
 // LDS instructions of one step in program order and the waits that follow from it: mini-step m issues the read of fragment m + AHEAD (two instructions
 // for a transposed one; past the end the next step's first), then extra(m) reads of row values after its first MFMA.  What extra(m) reads is there at
@@ -1390,14 +1391,15 @@ __device__ __forceinline__ void dkv_tall_blocks(const ArgsPtr<DkvParams> args, c
   constexpr int DIST = 6;      // stages copied ahead
   constexpr int NS = DIST + 2; // ring slots: stages g - 1 and g in use, g + 1 .. g + DIST on their way
   constexpr int NF = 4 * DK;   // fragments (mini-steps) per step: Q rows, Q^T, dO rows, dO^T
-  constexpr int AHEAD = D == 128 ? 4 : 5, RING = 8;   // fragments in flight, names of the fragment ring
+  constexpr int AHEAD = D == 96 ? 5 : 4, RING = 8;   // fragments in flight, names of the fragment ring
   constexpr int NP = BM * KC / 64;     // 64-slot pieces per tile
   constexpr int PER = 2 * NP / NW;     // pieces per wave and stage
   constexpr int RV = 64;               // floats per slot of the LSE / D rows (32 used; a whole wave copies them)
   constexpr int BOOK = NF - 2;
+  constexpr bool KEEP_P = D == 64;     // P stays in float32 for dS (32 registers more, 32 instructions of a step less)
   using Order = TallOrder<DK, AHEAD>;
   constexpr int COPY_EVERY = NF / PER;  // mini-steps from one copy of a stage to the next
-  static_assert(NF % RING == 0 && 2 * DB == DK && NP % 2 == 0 && NF % PER == 0 && NF - 3 <= BOOK, "the schedule of a step");
+  static_assert(NF % RING == 0 && AHEAD <= DK && 2 * DB == DK && NP % 2 == 0 && NF % PER == 0 && NF - 3 <= BOOK, "the schedule of a step");
 
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   lds_bf16* const L = (lds_bf16*)smem;
@@ -1561,7 +1563,9 @@ __device__ __forceinline__ void dkv_tall_blocks(const ArgsPtr<DkvParams> args, c
   for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
     for (int db = 0; db < DB; ++db) dk[kb][db] = dv[kb][db] = zero16;
-  f32x16 s[2], dp[2];           // S and dP - D: [key block]
+  f32x16 s[2], dp[2];           // S (then P, packed into pw) and dP - D: [key block]
+  f32x16 ps[2];                 // KEEP_P: P
+  if constexpr (KEEP_P) ps[0] = ps[1] = zero16;
   u32x4 pw[2][2], sw[2][2];     // P and dS as B operands: [key block][k-step], pairs of bf16
   dp[0] = dp[1] = zero16;
 #pragma unroll
@@ -1593,12 +1597,12 @@ __device__ __forceinline__ void dkv_tall_blocks(const ArgsPtr<DkvParams> args, c
       constexpr int x = decltype(x_c)::value, g4 = x / 8, kb = x / 4 % 2, i = 4 * g4 + x % 4;
       float e = __builtin_amdgcn_exp2f(s[kb][i] * c - rl[g4][i & 3]);
       asm volatile("" : "+v"(e));
-      s[kb][i] = e;
+      (KEEP_P ? ps : s)[kb][i] = e;
     };
     auto pack_p = [&](auto y_c) __attribute__((always_inline)) {  // pair y: elements 2 y and 2 y + 1
       constexpr int y = decltype(y_c)::value, kb = y / 2 % 2, w = 2 * (y / 4) + y % 2;
       bf16x2 v;
-      v[0] = (__bf16)s[kb][2 * w]; v[1] = (__bf16)s[kb][2 * w + 1];
+      v[0] = (__bf16)(KEEP_P ? ps : s)[kb][2 * w]; v[1] = (__bf16)(KEEP_P ? ps : s)[kb][2 * w + 1];
       unsigned u = __builtin_bit_cast(unsigned, v);
       asm volatile("" : "+v"(u));
       pw[kb][w / 4][w % 4] = u;
@@ -1606,8 +1610,7 @@ __device__ __forceinline__ void dkv_tall_blocks(const ArgsPtr<DkvParams> args, c
     auto ds_one = [&](auto x_c) __attribute__((always_inline)) {
       constexpr int x = decltype(x_c)::value, kb = x / 4 % 2, i = 4 * (x / 8) + x % 4, w = i / 2;
       const unsigned pu = pw[kb][w / 4][w % 4];
-      const float pf = __uint_as_float(i % 2 == 0 ? pu << 16 : pu & 0xffff0000u);
-      float e = pf * dp[kb][i];
+      float e = (KEEP_P ? ps[kb][i] : __uint_as_float(i % 2 == 0 ? pu << 16 : pu & 0xffff0000u)) * dp[kb][i];
       if constexpr (i % 2 == 0) {
         asm volatile("" : "+v"(e));
         e_hold = e;
@@ -3368,7 +3371,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_wide_kernel(DqParams) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// bwd_pipe (head_dim 128 and 96, and 256 where wide_pays): the dQ and the dK/dV blocks of a chunk in one launch
+// bwd_pipe (head_dim 128 and 96, 256 where wide_pays and 64 where narrow_tall_pays): the dQ and the dK/dV blocks of a chunk in one launch
 //
 // The two kinds of block need nothing of each other, so a workgroup that finds no more blocks of one kind goes on to the other:
 // small chunks run both kinds side by side on compute units that one kind alone would leave idle, and no chunk ends twice.  The kind
@@ -3677,25 +3680,19 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
       if (P.n_dkv_cut == 0) e = P.dq_wide ? run(std::false_type{}, wide) : run(std::false_type{}, std::false_type{});
       else e = P.dq_wide ? run(std::true_type{}, wide) : run(std::true_type{}, std::false_type{});
       if (e != hipSuccess) return e;
-    } else if (D == 256 && P.dkv_pipe) {
+    } else if ((D == 256 && P.dkv_pipe) || (D == 64 && P.dkv_tall)) {
       BwdPipeParams p;
       p.dq = pq;
       p.dkv = pk;
       p.dq_phase = P.dq_first ? 0 : 1;
-      // dQ: six ring slots of K and four of V; dK/dV: four of two 32-row operand tiles and of their LSE and D rows, the word that announces the next block
-      const size_t dq_smem = (size_t)10 * 32 * D * 2, dkv_smem = (size_t)2 * 4 * 32 * D * 2 + 2 * 4 * 64 * sizeof(float) + 16;
-      const size_t smem = std::max(dq_smem, dkv_smem);
-      auto run = [&]() {
-        if constexpr (D == 256) {
-          static const hipError_t attr = raise_smem_limit(&bwd_pipe_kernel<D, false, true>, smem);
-          if (attr != hipSuccess) return attr;
-          hipError_t err;
-          if (pe.start && (err = hipEventRecord(pe.start, stream)) != hipSuccess) return err;
-          hipLaunchKernelGGL((bwd_pipe_kernel<D, false, true>), dim3((unsigned)persistent_grid(dq_blocks + dkv_blocks)), dim3(256), smem, stream, p);
-        }
-        return hipGetLastError();
-      };
-      if ((e = run()) != hipSuccess) return e;
+      // 256: six ring slots of K and four of V, and as many of two 32-row operand tiles and of their LSE and D rows as dkv_wide_blocks has; 64: as at 96 and 128
+      constexpr int kSlots = D == 256 ? 4 : 8;
+      constexpr size_t dq_smem = D == 256 ? (size_t)10 * 32 * D * 2 : (size_t)2 * (DQ_PIPE_DIST + 3) * 32 * D * 2 + (size_t)4 * 64 * D * 2;
+      constexpr size_t dkv_smem = (size_t)2 * kSlots * 32 * D * 2 + 2 * kSlots * 64 * sizeof(float) + 16, smem = dq_smem > dkv_smem ? dq_smem : dkv_smem;
+      static const hipError_t attr = raise_smem_limit(&bwd_pipe_kernel<D, false, true>, smem);
+      if (attr != hipSuccess) return attr;
+      if (pe.start && (e = hipEventRecord(pe.start, stream)) != hipSuccess) return e;
+      hipLaunchKernelGGL((bwd_pipe_kernel<D, false, true>), dim3((unsigned)persistent_grid(dq_blocks + dkv_blocks)), dim3(256), smem, stream, p);
     } else if (D == 256 && P.dq_wide) {
       const size_t smem = (size_t)10 * 32 * D * 2;  // six slots of K and four of V
       static const hipError_t attr = raise_smem_limit(&bwd_dq_wide_kernel, smem);
@@ -3715,7 +3712,7 @@ hipError_t launch_bwd_t(const chunk_attn_desc* d, const BwdArgs& a, const BwdPla
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if constexpr (D == 64) {
-      if (P.dkv_pipe) {
+      if (P.dkv_pipe && !P.dkv_tall) {
         // 6 ring slots of two 32-row operand tiles and their LSE and D rows
         const size_t smem = (size_t)2 * 6 * 32 * D * 2 + 2 * 6 * 64 * sizeof(float);
         static const hipError_t attr = raise_smem_limit(&bwd_dkv_narrow_pipe_kernel<D>, smem);
@@ -3779,6 +3776,8 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, Cut cut, i
   if (d->head_dim == 64) P.dkv_pipe = dkv_pipe_pays(d, count_dkv_walks(d, dkv_keys(64)));
   if (d->head_dim == 256) P.dkv_pipe = wide_pays(d, dq_rows, d->num_kv_heads * (group / heads_per_wg(group, P.dq_waves)), dkv_keys(256), kCus);
   if (d->head_dim == 256) P.dq_wide = P.dkv_pipe || dq_wide_pays(count_walks(d, dq_rows));
+  if (d->head_dim == 64 && P.dq_pipe && P.dkv_pipe)
+    P.dkv_tall = narrow_tall_pays(d, dq_rows, d->num_kv_heads * (group / heads_per_wg(group, P.dq_waves)), dkv_keys(64), kCus);
   P.q_tiles = count_tiles(d, false, 64);
   P.qt32_tiles = count_tiles(d, false, 32);
   // head_dim 128: room for dQ tiles in float32, for the one-pass backward or for the partial results of cut dQ walks
@@ -3812,7 +3811,7 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, Cut cut, i
       if (P.split.target > 0) P.dq_items = cut_items(P.dq_items, P.split.target, &P.dq_cut);
       // the pipelined kernels walk either way; the key blocks of one key/value head that run at the same time are the
       // workgroups of the launch over the number of key/value heads
-      const int side_by_side = P.dkv_pipe ? std::max(1, persistent_grid(0x7fffffff, dkv_per_cu(d->head_dim)) / d->num_kv_heads) : 0;
+      const int side_by_side = P.dkv_pipe ? std::max(1, persistent_grid(0x7fffffff, P.dkv_tall ? 1 : dkv_per_cu(d->head_dim)) / d->num_kv_heads) : 0;
       P.dkv_items = plan_dkv(d, dkv_block_keys(P, d->head_dim), P.dkv_split.target > 0 ? 0 : side_by_side);
       if (P.dkv_split.target > 0) P.dkv_items = cut_items(P.dkv_items, P.dkv_split.target, &P.dkv_cut);
     }

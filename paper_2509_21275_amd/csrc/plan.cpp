@@ -271,6 +271,20 @@ CutKind tile_walks(const chunk_attn_desc* d, int keys) {
   return k;
 }
 
+// When the last of queue 0's blocks of both kinds ends, none of them cut, in the order in which one launch starts them: a dQ block costs `dq_stage` per stage and `dq_start`
+// more, a dK/dV block of `keys` keys `step` per step and `start` more.
+int64_t joint_end(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int dq_stage, int dq_start, int step, int start, int cus) {
+  const CutKind q = key_walks(d, tile_rows, inner), k = tile_walks(d, keys);
+  std::vector<int64_t> dq, dkv, free_at;
+  queue_costs(q, dq_stage, dq_start, dq);
+  queue_costs(k, step, start, dkv);
+  const bool dq_first = q.longest > (int64_t)k.longest * k.group;  // (bwd_layout)
+  std::vector<int64_t>&both = dq_first ? dq : dkv, &second = dq_first ? dkv : dq;
+  both.insert(both.end(), second.begin(), second.end());
+  const int workers = std::max(1, cus / 8);
+  return both.size() > kManyBlocks ? std::accumulate(both.begin(), both.end(), (int64_t)0) / workers : deal(both, workers, free_at);
+}
+
 // The cut of N kinds of block that share the compute units, one split each; at most max_parts[i] partial results of kind i.
 // `first` (or null): a cut to look at besides those into equal shares.
 template <int N>
@@ -630,21 +644,7 @@ void refine_bwd_split(const chunk_attn_desc* d, int tile_rows, int inner, int ke
 // 32/8, 687 (blocks of 256 keys: 931), 4596, 40/8, 680 (982), 6403 on 10177, 28/4, 1884 (2032).
 bool tall_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int cus) {
   constexpr int kStep = 20, kDqStage = 25, kTallStep = 33, kStart = 12 * kStep, kTallStart = 16 * kStep;
-  const int workers = std::max(1, cus / 8), group = d->num_q_heads / d->num_kv_heads;
-  std::vector<int64_t> dq, dkv, both, free_at;
-  const CutKind q = key_walks(d, tile_rows, inner);
-  queue_costs(q, kDqStage, kStart, dq);
-  auto end = [&](int block_keys, int step, int start) {
-    const CutKind k = tile_walks(d, block_keys);
-    queue_costs(k, step, start, dkv);
-    const bool dq_first = q.longest > (int64_t)k.longest * group;  // (bwd_layout)
-    both = dq_first ? dq : dkv;
-    const std::vector<int64_t>& second = dq_first ? dkv : dq;
-    if (both.size() + second.size() > kManyBlocks) return std::accumulate(dq.begin(), dq.end(), std::accumulate(dkv.begin(), dkv.end(), (int64_t)0)) / workers;
-    both.insert(both.end(), second.begin(), second.end());
-    return deal(both, workers, free_at);
-  };
-  return end(kTallKeys, kTallStep, kTallStart) < end(keys, kStep, kStart);
+  return joint_end(d, tile_rows, inner, kTallKeys, kDqStage, kStart, kTallStep, kTallStart, cus) < joint_end(d, tile_rows, inner, keys, kDqStage, kStart, kStep, kStart, cus);
 }
 
 // From two blocks of `keys` per CU and 14 steps each on average on, of 277 drawn chunks two are slower with the pipelined blocks, by 3 and 9 % (thousands of blocks of less
@@ -659,19 +659,21 @@ bool wide_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int
   const Walks wq = count_walks(d, tile_rows);
   if (wq.stages < 8 * wq.items) return false;
   constexpr int kUs = 20, kDqStage = 24, kDqStart = 16 * kUs, kStep = 29, kStart = 20 * kUs;
-  const int workers = std::max(1, cus / 8), group = d->num_q_heads / d->num_kv_heads;
-  const CutKind q = key_walks(d, tile_rows, inner), k = tile_walks(d, kWideKeys);
-  std::vector<int64_t> dq, dkv, free_at;
-  queue_costs(q, kDqStage, kDqStart, dq);
-  queue_costs(k, kStep, kStart, dkv);
-  const bool dq_first = q.longest > (int64_t)k.longest * group;  // (bwd_layout)
-  std::vector<int64_t>&both = dq_first ? dq : dkv, &second = dq_first ? dkv : dq;
-  both.insert(both.end(), second.begin(), second.end());
-  const int64_t end = both.size() > kManyBlocks ? std::accumulate(both.begin(), both.end(), (int64_t)0) / workers : deal(both, workers, free_at);
-  const double pipelined = 1.57 + 0.984 / kUs * end;
+  const double pipelined = 1.57 + 0.984 / kUs * joint_end(d, tile_rows, inner, kWideKeys, kDqStage, kDqStart, kStep, kStart, cus);
   const double per_cu = 1.0 / cus, dq_all = std::max((double)wq.stages * inner * per_cu, (double)wq.longest);
   const double other = 23.1 + 0.42 * dq_all + (21.6 * wq.items * inner + (1.911 * w.stages + 4.71 * w.items) * d->num_kv_heads) * per_cu;
   return pipelined < 0.96 * other;
+}
+
+// Times (us) as in wide_pays, of chunks of head_dim 64 whose dQ and dK/dV are pipelined as launches of their own, or in one with dK/dV blocks of kTallKeys keys.  Off by 8 %
+// (445 drawn chunks of 60 us and more) and 5 % (54 of these kinds).  Of the 54 it picks 50, of which none is slower; all 54 take 7.7 % less, with the better of the two for each
+// 7.8.  8192 queries on 16384 keys, 32/8 heads, backward, 2998 -> 2718 us; 8192 causal tokens 1129 -> 1005.
+bool narrow_tall_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int cus) {
+  const Walks w = count_dkv_walks(d, keys), wq = count_walks(d, tile_rows);
+  const double per_cu = 1.0 / cus;
+  const double two = 104.7 + (0.382 * wq.stages + 15.9 * wq.items) * inner * per_cu + 0.022 * wq.longest + (0.639 * w.stages + 4.31 * w.items) * d->num_kv_heads * per_cu + 0.16 * w.longest;
+  constexpr int kUs = 20, kDqStage = 16, kDqStart = 16 * kUs, kStep = 22, kStart = 18 * kUs;
+  return 0.839 / kUs * joint_end(d, tile_rows, inner, kTallKeys, kDqStage, kDqStart, kStep, kStart, cus) < two;
 }
 
 std::vector<DkvItem> cut_items(const std::vector<DkvItem>& wholes, int target, std::vector<DkvItem>* cut) {

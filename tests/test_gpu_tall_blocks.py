@@ -1,4 +1,4 @@
-"""dK/dV blocks of 256 keys (head dimensions 96 and 128): ragged last blocks and query tiles, waves whose keys no query or few queries see, groups of one to
+"""dK/dV blocks of 256 keys (head dimensions 64, 96 and 128): ragged last blocks and query tiles, waves whose keys no query or few queries see, groups of one to
 four heads, walks of one step and in both directions, rows outside key ranges, accumulation and float32 buffers, against the fp64 oracle."""
 import numpy as np
 import pytest
@@ -27,8 +27,13 @@ def _case(segs, hq, hk, d):
     return case
 
 
-@pytest.mark.parametrize("d", [128, 96])
-@pytest.mark.parametrize("segs,hq,hk", CASES)
+NARROW = [  # of head dimension 64: walks long enough for the pipelined kernels
+    ([(0, 640, 0, 4097)], 256, 64),                                              # one key in the last block
+    ([(0, 257, 0, 4001), (257, 255, 4010, 4351)], 256, 64),                       # one row in the last tile, keys no segment has, 255 keys in the last block
+]
+
+
+@pytest.mark.parametrize("segs,hq,hk,d", [(*c, d) for c in CASES for d in (128, 96)] + [(*c, 64) for c in NARROW])
 def test_edges_of_blocks_and_tiles(oracle_mod, segs, hq, hk, d):
     case = _case(segs, hq, hk, d)
     q, k, v, do = make_inputs(case)

@@ -1,4 +1,4 @@
-"""Which chunks of head dimensions 96 and 128 run dK/dV blocks of 256 keys, which of 256 the pipelined ones of 128 keys, and what their steps compile to."""
+"""Which chunks of head dimensions 64, 96 and 128 run dK/dV blocks of 256 keys, which of 256 the pipelined ones of 128 keys, and what their steps compile to."""
 import os
 import re
 import shutil
@@ -46,6 +46,17 @@ def test_blocks_of_head_dim_256(segs, hq, hk, keys):
     assert bool(ca.chunk_attn_test_routes(desc) & ca.ROUTE_DKV_PIPELINED) == (keys == 128)
 
 
+@pytest.mark.parametrize("segs,hq,hk,keys", [
+    ([(0, 8192, 0, 16384)], 32, 8, 256), ([(0, 2048, 0, 16384)], 64, 8, 256),
+    ([(0, 10790, 0, 10833)], 8, 2, 128),                                    # one of the kinds is not pipelined
+    ([(0, 129, 0, 4351), (129, 1, 4360, 3900)], 512, 256, 128),             # short dK/dV walks
+])
+def test_blocks_of_head_dim_64(segs, hq, hk, keys):
+    tq, tkv = sum(s[1] for s in segs), segs[-1][2] + segs[-1][3]
+    desc = ca.make_desc(segs, hq, hk, 64, tq, tkv, 0.125)
+    assert ca.chunk_attn_test_dkv_keys(desc) == keys
+
+
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 
@@ -58,7 +69,7 @@ def test_steps_of_full_registers_touch_no_scratch(tmp_path):
                        capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
     text = open(out).read()
-    for name in ("bwd_pipe_kernelILi128ELb0ELb1", "bwd_pipe_kernelILi96ELb0ELb1", "bwd_pipe_kernelILi256ELb0ELb1"):
+    for name in ("bwd_pipe_kernelILi64ELb0ELb1", "bwd_pipe_kernelILi128ELb0ELb1", "bwd_pipe_kernelILi96ELb0ELb1", "bwd_pipe_kernelILi256ELb0ELb1"):
         at = re.search(r"^\S*%s\S*:" % name, text, re.M).end()
         blocks = re.split(r"^\.LBB\S+:", text[at:text.index(".Lfunc_end", at)], flags=re.M)
         steps = [b for b in blocks if b.count("v_mfma") >= 4]
