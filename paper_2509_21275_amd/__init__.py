@@ -281,6 +281,15 @@ def chunk_attn_test_dkv_keys(desc) -> int:
     return out.value
 
 
+def chunk_attn_test_fwd_rows(desc) -> int:
+    """Test hook: query rows per wave of the forward that the library runs for a chunk (host only)."""
+    out = ctypes.c_int32(0)
+    rc = _lib.chunk_attn_test_fwd_rows(ctypes.byref(desc), ctypes.byref(out))
+    if rc != 0:
+        raise ChunkAttnError(rc)
+    return out.value
+
+
 def chunk_attn_test_shared_heads(desc) -> int:
     """Test hook: query heads per workgroup of the forward whose waves divide the keys of 32 rows, 0 where another kernel runs (host only)."""
     out = ctypes.c_int32(0)

@@ -187,6 +187,7 @@ struct FwdLayout {
   int tile_rows;
   bool pipe;       // the pipelined kernel runs (head_dim 96 and 128, and 64 from a number of blocks on), unless
   int share;       // > 0: fwd_share_kernel runs, its workgroups taking so many heads each
+  bool tall;       // head_dim 256: fwd_tall_kernel runs
   KeySplit split;  // pipelined kernel: how the walks are cut
   size_t n_items, n_wholes, wholes_off, queues_off, blob_bytes, parts_off, total;
   int64_t blocks;
@@ -254,6 +255,13 @@ void layout_fwd(const chunk_attn_desc* desc, FwdLayout& L, bool with_plan, bool 
   L.total = std::max(uncut_total, L.parts_off + align_up((size_t)L.split.parts * part_bytes));
   if (is_narrow(desc))  // (as much as with padded copies of Q, K, V and O)
     L.total = std::max(L.total, uncut_total + 2 * padded_bytes(d->total_q, d->num_q_heads, 2) + 2 * padded_bytes(d->total_kv, d->num_kv_heads, 2));
+  L.tall = d->head_dim == 256 && fwd_tall_pays(d, L.tile_rows, inner, kCus);
+  if (L.tall) {  // (the size stays that of the other kernel's items, of which there are more)
+    L.tile_rows *= 2;
+    L.n_wholes = (size_t)count_walks(d, L.tile_rows).items;
+    place(L.n_wholes);
+    L.blocks = (int64_t)L.n_items * inner;
+  }
   // (the layout of the workspace stays the other kernel's, so that its size does)
   L.share = may_cut && bwd_mode() == 0 ? choose_shared_heads(desc, walks, inner, pipe, L.split) : 0;
   if (L.share > 0) {
@@ -469,7 +477,7 @@ FwdParams fwd_params(const chunk_attn_desc* desc, const FwdLayout& L, char* ws, 
   p.ref_limit = g_fwd_rescale_limit.load();
   return p;
 }
-FwdKind fwd_kind(const FwdLayout& L) { return L.share > 0 ? kFwdShare : L.pipe ? kFwdPipe : kFwdPlain; }
+FwdKind fwd_kind(const FwdLayout& L) { return L.share > 0 ? kFwdShare : L.tall ? kFwdTall : L.pipe ? kFwdPipe : kFwdPlain; }
 FwdLists fwd_lists(const FwdLayout& L) {
   FwdLists l;
   l.num_blocks = (int)L.blocks;
@@ -564,6 +572,16 @@ int chunk_attn_test_dkv_keys(const chunk_attn_desc* desc, int32_t* keys) {
   BwdPlan P;
   bwd_layout(&w, P, false, kCutFine, bwd_mode() == 0 ? desc->head_dim : 0);
   *keys = P.share_waves > 0 ? 32 : dkv_block_keys(P, w.head_dim);
+  return CHUNK_ATTN_OK;
+}
+
+int chunk_attn_test_fwd_rows(const chunk_attn_desc* desc, int32_t* rows) {
+  const int rc = validate(desc);
+  if (rc != CHUNK_ATTN_OK) return rc;
+  if (!rows) return CHUNK_ATTN_INVALID_ARG;
+  FwdLayout L;
+  layout_fwd(desc, L, false);
+  *rows = L.share > 0 ? 32 : L.pipe || L.tall ? 64 : 32;
   return CHUNK_ATTN_OK;
 }
 

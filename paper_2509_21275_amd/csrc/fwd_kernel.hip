@@ -27,6 +27,7 @@
 //                    128 has too few items for the chip their walks are cut into pieces (plan.hpp); the pieces leave
 //                    float32 partial results, which fwd_merge_kernel puts together.
 //   fwd_wide_kernel  head_dim 256: the same with 32 query rows per wave.
+//   fwd_tall_kernel  head_dim 256, with 64 query rows per wave: chunks of more blocks than compute units, where it ends sooner (fwd_tall_pays).
 //   fwd_share_kernel head_dim 64, 96 and 128, small chunks (choose_shared_heads): the waves of a workgroup divide the keys of 32 rows.
 #include <cstring>
 #include <type_traits>
@@ -1276,6 +1277,402 @@ __global__ __launch_bounds__(256, 1) void fwd_wide_kernel(FwdArgs) {
 }
 
 // ------------------------------------------------------------------------------------------------
+// Forward of head_dim 256 with 64 query rows per wave, where that ends sooner than fwd_wide_kernel (fwd_tall_pays)
+//
+// As in the backward's dkv_tall_blocks the accumulators (O^T of 64 rows) fill the accumulation registers and Q takes half of the others, so that every
+// fragment feeds two MFMAs (one per 32-row unit): half the LDS reads and copies per MFMA.  Step t is
+//     S^T(t) = K(t) Q^T      O^T += V(t-1)^T P^T(t-1)                                  (matrix pipe, in this order)
+//     P^T(t) = exp2(S^T(t) c - m c)  from the end of S^T(t) until the next step's second half needs it       (vector)
+// as 32 mini-steps of one LDS fragment and the two MFMAs it feeds, each MFMA with its even share of the vector work behind it.  Four ring slots of K and of V:
+// K(t), V(t - 1) and what is read ahead in use, K(t + 3) and V(t + 2) on their way.  Reference maxima, both sums and blocks that are taken again
+// as in fwd_wide_kernel.
+// Bound by the rate at which MFMAs issue (their share of the cycles times the clock that the power limit leaves).  fwd_wide_kernel -> this, us, 32/8 heads:
+// packed 64K tokens 8254 -> 6471, 8192 queries on 32768 keys 7329 -> 5658, 4096 causal tokens 302 -> 242, 64 sequences of 256 253 -> 235.
+// ------------------------------------------------------------------------------------------------
+// The schedule of a step: mini-step m issues the read of fragment m + AHEAD (two instructions for those of V^T, the second half).
+template <int DK, int AHEAD>
+struct FwdTallOrder {
+  static constexpr int NF = 2 * DK, DB = DK / 2;
+  static constexpr int EXP0 = DK + 2;  // mini-step in which the vector work starts
+  static constexpr int cost(int k) { return (k % NF) >= DK ? 2 : 1; }
+  static constexpr int exps(int m) { return spread(32, EXP0, EXP0 + 2 * DK - 4, m); }  // scores done by the end of mini-step m (from NF on: of the next step)
+  static constexpr int wait(int m) {
+    int n = 0;
+    for (int i = m - AHEAD + 1; i < m; ++i) n += cost((i + AHEAD + NF) % NF);
+    return n;
+  }
+  // P of a k-step's keys is packed before the first product that reads it (pair 7 when score 16 has been done)
+  static_assert(exps(NF + DK - 1) >= 17 && exps(NF + DK + DB - 1) == 32 && exps(NF + DK - 2) == 32, "the order of a step");
+};
+
+__global__ __launch_bounds__(256, 1) void fwd_tall_kernel(FwdArgs) {
+  constexpr int D = 256;
+  const FwdArgsPtr args = fwd_args();
+  const FwdParams p = load_params(&args->p);
+  const int num_blocks = args->num_blocks;
+  constexpr int NW = 4;        // waves
+  constexpr int BN = 32;       // key rows per stage
+  constexpr int KC = D / 8;    // 16-byte chunks per K / V row
+  constexpr int DK = D / 16;   // k-steps of S^T = K Q^T
+  constexpr int DB = D / 32;   // 32-row blocks of O^T
+  constexpr int KT = BN * D;   // elements per tile
+  constexpr int NS = 4;        // ring slots of K and of V
+  constexpr int NF = 2 * DK;   // fragments (mini-steps) per step: K rows, V^T
+  constexpr int AHEAD = 4, RING = 8;      // fragments in flight, names of the fragment ring
+  constexpr int PER = BN * KC / 64 / NW;  // global->LDS copies per wave, tile and stage
+  constexpr int COPY_EVERY = NF / (2 * PER);
+  using Order = FwdTallOrder<DK, AHEAD>;
+  static_assert(2 * DB == DK && NF % RING == 0 && NF % (2 * PER) == 0 && COPY_EVERY > 1, "the schedule of a step");
+
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  lds_bf16* const L = (lds_bf16*)smem;
+  constexpr int V_OFF = NS * KT;         // [NS][KT] K rows of stage n in slot n % NS (chunk-major), then V likewise; at the end the waves' rows of O
+  int* const next_block = (int*)((__bf16*)smem + 2 * NS * KT);
+  volatile int* const outgrown = (volatile int*)(next_block + 1);  // some wave has seen a row outgrow its reference maximum
+
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // (the lane is counted anew where it is needed, as in dkv_tall_blocks)
+  auto lane_id = []() __attribute__((always_inline)) {
+    int l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(l));
+    return l;
+  };
+
+  const int xcd = xcd_of_this_wave();
+  const bool direct = num_blocks <= (int)gridDim.x;
+  int blk = blockIdx.x;
+  if (!direct) {
+    if (wave == 0) blk = block_claim_finish(p.taken, num_blocks, xcd, block_claim_issue(p.taken, xcd));
+    blk = broadcast_from_wave0(next_block, blk);
+  }
+  bool again = false;  // the block is taken a second time, with every row's true maximum
+  int pending_claim = 0;
+  while (blk >= 0) {
+  wg_barrier();  // every wave has read the announcement and `outgrown`
+  const int inner_n = p.num_kv_heads * p.head_splits;
+  const int inner = __builtin_amdgcn_readfirstlane(blk % inner_n);
+  const FwdItem it = load_item(p.items, args->items, __builtin_amdgcn_readfirstlane(blk / inner_n));
+  const int kvh = __builtin_amdgcn_readfirstlane(inner % p.num_kv_heads), hs = inner / p.num_kv_heads;
+  const int head = kvh * p.group + hs * p.heads_per_wg + wave % p.heads_per_wg;
+  const int wave_row0 = (wave / p.heads_per_wg) * 64;  // the wave's rows are wave_row0 .. + 63 of `head`
+  const int n_wg = it.n0 + it.q_rows - 1;              // keys the last valid row sees
+  const int nt = (n_wg + BN - 1) / BN;                 // stages
+  const int64_t q_stride = (int64_t)p.num_q_heads * D, kv_stride = (int64_t)p.num_kv_heads * D;
+  const __bf16* __restrict__ Kg = p.k + (int64_t)it.kv_row0 * kv_stride + (int64_t)kvh * D;
+  const __bf16* __restrict__ Vg = p.v + (int64_t)it.kv_row0 * kv_stride + (int64_t)kvh * D;
+
+  // ---- staging: copy i of a wave is piece 4 i + wave of a tile, 64 consecutive slots = two chunk columns of 32 rows, which have the same order of rows for all
+  // copies of a wave.  Past the last stage the last one is copied again, rows past the last key repeat it (masked). ----
+  unsigned v_full, v_last;  // byte offset of the lane's chunk from the tile's first row, but for the piece's own 32 bytes: full tile, last tile
+  {
+    const int lane = lane_id(), hh = lane >> 5, row = (lane & 31) ^ ((2 * (wave & 1) + hh) << 2);
+    v_full = (unsigned)(row * (int)kv_stride + 8 * hh) * 2u;
+    v_last = (unsigned)(min(row, n_wg - 1 - (nt - 1) * BN) * (int)kv_stride + 8 * hh) * 2u;
+  }
+  struct Stream {  // the next stage to copy, its first row, its slot
+    int t, slot;
+    const char* row;
+  };
+  Stream ks{0, 0, reinterpret_cast<const char*>(Kg)}, vs{0, 0, reinterpret_cast<const char*>(Vg)};
+  auto copy_piece = [&](const Stream& st, int ring, int i) __attribute__((always_inline)) {
+    const int piece = i * NW + wave;
+    unsigned off = st.t == nt - 1 ? v_last : v_full;
+    asm volatile("" : "+v"(off));
+    dma16(st.row + piece * 32 + off, L + ring + st.slot * KT + piece * 512);
+  };
+  auto advance = [&](Stream& st) __attribute__((always_inline)) {
+    if (st.t + 1 < nt) {
+      ++st.t;
+      st.row += BN * kv_stride * 2;
+    }
+    st.slot = st.slot == NS - 1 ? 0 : st.slot + 1;
+  };
+  auto copy_tile = [&](Stream& st, int ring) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) copy_piece(st, ring, i);
+    advance(st);
+  };
+
+  // byte addresses of this lane's operand reads in the tile of slot 0 (as in dkv_tall_blocks)
+  constexpr unsigned ROW8 = 8 * 16;
+  unsigned ev0, lo0;
+  {
+    const int lane = lane_id(), l32 = lane & 31, hh = lane >> 5;
+    const int j = lane & 15, cl = 2 * ((lane >> 4) & 1) + ((j & 3) >> 1), r0 = 4 * hh + (j >> 2);
+    ev0 = lds_addr(L + cm_elem(l32, hh));
+    lo0 = lds_addr(L + V_OFF + cm_elem(r0, cl) + 4 * (j & 1));
+  }
+  constexpr unsigned SLOT = KT * 2;  // bytes per ring slot
+  auto load_rows = [&](unsigned ev_addr, unsigned od_addr, auto ks_c) __attribute__((always_inline)) {
+    constexpr int k = decltype(ks_c)::value;
+    return lds_asm_read16<(k >> 1) * (4 * 32 * 8) * 2 + (k & 1) * 1024>((k & 1) ? od_addr : ev_addr);
+  };
+  auto load_t = [&](unsigned lo_addr, unsigned hi_addr, auto m_c) __attribute__((always_inline)) {
+    constexpr int m = decltype(m_c)::value;  // ks2 * DB + db
+    constexpr int off = ((m / DB) * (16 * 8) + (m % DB) * (4 * 32 * 8)) * 2;
+    const s16x4 lo = lds_asm_read_tr<off>(lo_addr);
+    const s16x4 hi = lds_asm_read_tr<off>(hi_addr);
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
+
+  // prologue: K of stages 0 .. 2, V of stages 0 and 1, the wave's rows of Q
+#pragma unroll
+  for (int n = 0; n < 3; ++n) copy_tile(ks, 0);
+#pragma unroll
+  for (int n = 0; n < 2; ++n) copy_tile(vs, V_OFF);
+  bf16x8 qf[2][DK];  // B operands of S^T = K Q^T: lane holds Q[row = 32 u + l32][16 ks + 8 hh ..+7]
+  {
+    const int lane = lane_id();
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int r = min(wave_row0 + 32 * u + (lane & 31), it.q_rows - 1);  // rows past the tile repeat the last one (never stored)
+      const __bf16* const src = p.q + (int64_t)(it.q_row0 + r) * q_stride + (int64_t)head * D + 8 * (lane >> 5);
+#pragma unroll
+      for (int k = 0; k < DK; ++k) qf[u][k] = *reinterpret_cast<const bf16x8*>(src + 16 * k);
+    }
+    bf16x8 z;  // V(-1), read in step 0 (P(-1) = 0)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) z[i] = (__bf16)0.0f;
+#pragma unroll
+    for (int i = 0; i < KT / (NW * 64 * 8); ++i) lds_store8(L + V_OFF + (NS - 1) * KT + (i * NW * 64 + wave * 64 + lane) * 8, z);
+    if (threadIdx.x == 0) *outgrown = 0;
+  }
+  wait_all_but<0>();  // (a wait the compiler can see, so that it puts none for these loads into the loop)
+  wg_barrier();
+
+  const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  const float c = p.scale_log2;
+  f32x16 x[2][2];    // S^T, then P^T: [buffer][unit]
+  u32x4 f[2][2][2];  // P^T as B operands: [buffer][unit][k-step], pairs of bf16
+  bf16x8 fr[RING];
+
+  // The reference maximum of each row, over stages 0 and 1 (fwd_wide_kernel)
+  float mc[2], l_run[2] = {0.f, 0.f}, l_rnd[2] = {0.f, 0.f}, ps[2] = {0.f, 0.f}, pr[2] = {0.f, 0.f};  // (ps, pr: a stage's own sums)
+  bf16x2 ones;
+  ones[0] = (__bf16)1.0f; ones[1] = (__bf16)1.0f;
+  {
+    const int lane = lane_id();
+    bf16x8 a[DK];
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      static_for<0, DK>([&](auto ks_c) __attribute__((always_inline)) { a[decltype(ks_c)::value] = load_rows(ev0 + n * SLOT, (ev0 + n * SLOT) ^ ROW8, ks_c); });
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+      for (int k = 0; k < DK; ++k) asm volatile("" : "+v"(a[k]));  // (after the wait, in this order)
+#pragma unroll
+      for (int k = 0; k < DK; ++k)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) x[n][u] = mfma32(a[k], qf[u][k], k == 0 ? zero16 : x[n][u]);
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int lim = it.n0 + wave_row0 + 32 * u + (lane & 31);  // visible iff key index < lim (>= 1)
+      float mx = -INFINITY;
+#pragma unroll
+      for (int n = 0; n < 2; ++n)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (BN * n + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3) < lim) mx = fmaxf(mx, x[n][u][i]);
+      mc[u] = max_halves(mx) * c;
+    }
+  }
+  if (__builtin_expect(again, 0)) {  // the maximum over all stages: K read from global memory
+    const int lane = lane_id();
+    float mx[2] = {-INFINITY, -INFINITY};
+    for (int n = 0; n < nt; ++n) {
+      const __bf16* kr = Kg + (int64_t)min(BN * n + (lane & 31), n_wg - 1) * kv_stride + 8 * (lane >> 5);
+      f32x16 d[2] = {zero16, zero16};
+#pragma unroll
+      for (int k = 0; k < DK; ++k) {
+        const bf16x8 a = *reinterpret_cast<const bf16x8*>(kr + 16 * k);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) d[u] = mfma32(a, qf[u][k], d[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int lim = it.n0 + wave_row0 + 32 * u + (lane & 31) - BN * n;
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (8 * (i >> 2) + 4 * (lane >> 5) + (i & 3) < lim) mx[u] = fmaxf(mx[u], d[u][i]);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) mc[u] = max_halves(mx[u]) * c;
+  }
+
+  f32x16 oacc[2][DB];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+#pragma unroll
+    for (int db = 0; db < DB; ++db) oacc[u][db] = zero16;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) x[1][u][i] = i < 8 ? 0.f : -INFINITY;  // P(-1) = 0, of which the second half is still S(-1)
+#pragma unroll
+    for (int k = 0; k < 2; ++k) f[0][u][k] = f[1][u][k] = u32x4{0, 0, 0, 0};
+  }
+  static_for<0, AHEAD>([&](auto k_c) __attribute__((always_inline)) { fr[decltype(k_c)::value] = load_rows(ev0, ev0 ^ ROW8, k_c); });
+
+  int slot = 0;  // of K(t) and V(t)
+  auto step = [&](int t, f32x16 (&so)[2], f32x16 (&sn)[2], u32x4 (&po)[2][2], u32x4 (&pn)[2][2]) __attribute__((always_inline)) {
+    const int prv = slot == 0 ? NS - 1 : slot - 1, nxt = slot == NS - 1 ? 0 : slot + 1;
+    const unsigned k_ev = ev0 + slot * SLOT, k_od = k_ev ^ ROW8, n_ev = ev0 + nxt * SLOT, n_od = n_ev ^ ROW8;
+    const unsigned t_lo = lo0 + prv * SLOT, t_hi = t_lo ^ ROW8;
+    // Element y of the vector work: 4 g4 + (y % 4) of unit (y / 4) % 2, g4 = y / 8; the rows of a k-step come first.  A pair is packed, and added to
+    // the sums, one element late (an exponential cannot be used by the next instruction).
+    auto exp_one = [&](f32x16 (&s)[2], auto y_c) __attribute__((always_inline)) {
+      constexpr int y = decltype(y_c)::value, u = y / 4 % 2, i = 4 * (y / 8) + y % 4;
+      float e = __builtin_amdgcn_exp2f(s[u][i] * c - mc[u]);
+      asm volatile("" : "+v"(e));
+      s[u][i] = e;
+    };
+    auto pack = [&](f32x16 (&s)[2], u32x4 (&pw)[2][2], auto j_c) __attribute__((always_inline)) {
+      constexpr int j = decltype(j_c)::value, u = j / 2 % 2, w = 2 * (j / 4) + j % 2;
+      bf16x2 v;
+      v[0] = (__bf16)s[u][2 * w]; v[1] = (__bf16)s[u][2 * w + 1];
+      ps[u] += s[u][2 * w] + s[u][2 * w + 1];
+      asm volatile("" : "+v"(ps[u]));
+      pr[u] = __builtin_amdgcn_fdot2_f32_bf16(v, ones, pr[u], false);
+      asm volatile("" : "+v"(pr[u]));
+      unsigned b = __builtin_bit_cast(unsigned, v);
+      asm volatile("" : "+v"(b));
+      pw[u][w / 4][w % 4] = b;
+    };
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<0, NF>([&](auto m_c) __attribute__((always_inline)) {
+      constexpr int m = decltype(m_c)::value;
+      asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(fr[m % RING]) : "n"(Order::wait(m)));
+      if constexpr (m == Order::EXP0) {  // keys that a row does not see, and whole stages past the end of the walk
+        if (__builtin_expect(BN * (t + 1) > it.n0 + wave_row0, 0)) {
+          const int lane = lane_id();
+          const int lim0 = t < nt ? it.n0 + wave_row0 + (lane & 31) - BN * t - 4 * (lane >> 5) : -0x40000000, lim1 = lim0 + 32;
+          const float none = -INFINITY;
+          asm volatile("s_nop 15\n\ts_nop 7" : "+v"(sn[0]), "+v"(sn[1]));  // S(t) has been written
+#pragma unroll
+          for (int u = 0; u < 2; ++u)
+            static_for<0, 16>([&](auto i_c) __attribute__((always_inline)) {
+              constexpr int i = decltype(i_c)::value;
+              float v = sn[u][i];
+              const int lim = u ? lim1 : lim0;
+              asm volatile("v_cmp_ge_i32 vcc, %1, %2\n\ts_nop 1\n\tv_cndmask_b32 %0, %0, %3, vcc" : "+v"(v) : "n"(8 * (i >> 2) + (i & 3)), "v"(lim), "v"(none) : "vcc");
+              sn[u][i] = v;
+            });
+        }
+      }
+      {  // read the fragment of mini-step m + AHEAD (past the end: the next step's K rows)
+        constexpr int mm = m + AHEAD;
+        if constexpr (mm < DK) fr[mm % RING] = load_rows(k_ev, k_od, std::integral_constant<int, mm>{});
+        else if constexpr (mm < NF) fr[mm % RING] = load_t(t_lo, t_hi, std::integral_constant<int, mm - DK>{});
+        else fr[mm % RING] = load_rows(n_ev, n_od, std::integral_constant<int, mm - NF>{});
+      }
+      const bf16x8 fa = fr[m % RING];
+      auto mma = [&](auto u_c) __attribute__((always_inline)) {
+        constexpr int u = decltype(u_c)::value;
+        if constexpr (m < DK) {
+          const bf16x8& a_ = fa;  // (named references: variables used only inside an asm statement are not captured)
+          f32x16& d_ = sn[u];
+          const bf16x8& b_ = qf[u][m];
+          if (m == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d_) : "v"(a_), "v"(b_));
+          else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d_) : "v"(a_), "v"(b_));
+        } else {
+          constexpr int k = (m - DK) / DB, db = (m - DK) % DB;
+          oacc[u][db] = mfma32(fa, __builtin_bit_cast(bf16x8, po[u][k]), oacc[u][db]);
+        }
+      };
+      constexpr int M = m >= Order::EXP0 ? m : m + NF;  // (from EXP0 on the work is this stage's, before it the last one's)
+      constexpr int e0 = Order::exps(M - 1), e1 = Order::exps(M), em = e0 + (e1 - e0 + 1) / 2;
+      auto work = [&](auto lo_c, auto hi_c, auto last_c) __attribute__((always_inline)) {
+        constexpr int lo = decltype(lo_c)::value, hi = decltype(hi_c)::value;
+        constexpr int j0 = lo == 32 ? 16 : lo > 0 ? (lo - 1) / 2 : 0, j1 = hi == 32 && decltype(last_c)::value ? 16 : hi > 0 ? (hi - 1) / 2 : 0;
+        f32x16(&s)[2] = m >= Order::EXP0 ? sn : so;
+        u32x4(&pw)[2][2] = m >= Order::EXP0 ? pn : po;
+        static_for<lo, hi>([&](auto y_c) __attribute__((always_inline)) { exp_one(s, y_c); });
+        if constexpr (j0 < j1) static_for<j0, j1>([&](auto j_c) __attribute__((always_inline)) { pack(s, pw, j_c); });
+      };
+      mma(std::integral_constant<int, 0>{});
+      if constexpr (e0 < em) work(std::integral_constant<int, e0>{}, std::integral_constant<int, em>{}, std::bool_constant<em == 32 && em == e1>{});
+      __builtin_amdgcn_sched_barrier(0);
+      mma(std::integral_constant<int, 1>{});
+      if constexpr (em < e1) work(std::integral_constant<int, em>{}, std::integral_constant<int, e1>{}, std::true_type{});
+      if constexpr (m == Order::EXP0 - 1) {  // (the stage before is complete)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          l_run[u] += ps[u];
+          l_rnd[u] += pr[u];
+          ps[u] = pr[u] = 0.f;
+        }
+      }
+      if constexpr (m % COPY_EVERY == 1) {  // K(t + 3) and V(t + 2), one copy every COPY_EVERY mini-steps
+        if constexpr (m / COPY_EVERY % 2 == 0) copy_piece(ks, 0, m / COPY_EVERY / 2);
+        else copy_piece(vs, V_OFF, m / COPY_EVERY / 2);
+      }
+      if constexpr (m == NF - 2) {  // bookkeeping for the next step (this step's copies have been issued)
+        advance(ks);
+        advance(vs);
+        slot = nxt;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    // the copies of the step before (K(t + 2), V(t + 1)) must have landed; this step's may still be in flight
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * PER) : "memory");
+    wg_barrier();
+  };
+  // the last product is O^T of stage nt - 1 in step nt; a pair of steps may run one past that, which contributes nothing
+  const int claim_at = max(0, nt - 3) & ~1;
+  for (int t = 0; t <= nt; t += 2) {
+    if (t == claim_at && wave == 0 && !again && !direct) pending_claim = block_claim_issue(p.taken, xcd);
+    step(t, x[1], x[0], f[1], f[0]);
+    step(t + 1, x[0], x[1], f[0], f[1]);
+  }
+  // the last step's reads ahead are nobody's operands; their registers stay taken until they have arrived
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(fr[i]));
+  const float big = __builtin_amdgcn_exp2f(p.ref_limit);
+  if (__builtin_expect(__any(!(l_run[0] < big) || !(l_run[1] < big)), 0)) *outgrown = 1;
+  // every copy of this wave has landed (the last ones rewrote slots nobody reads)
+  __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
+  wg_barrier();  // nobody reads the rings, and nobody copies into them, any more: O may be staged there
+  const bool retake = __builtin_amdgcn_readfirstlane(*outgrown) != 0 && !again;
+  if (__builtin_expect(retake, 0)) {  // (the same for all waves)
+    again = true;
+    continue;
+  }
+  again = false;
+
+  // ---- epilogue: O = O^T / l, LSE = ln(l) + m scale, through 64 rows of LDS of the wave's own ----
+  {
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));
+    const int l32 = lane & 31, hh = lane >> 5;
+    lds_bf16* const stage = L + wave * (64 * D);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const float l_tot = sum_halves(l_run[u]), inv = 1.0f / sum_halves(l_rnd[u]);
+      const int r = wave_row0 + 32 * u + l32;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          *(__attribute__((address_space(3))) bf16x4*)(stage + tile_elem<KC>(32 * u + l32, 4 * db + g) + 4 * hh) =
+              pack4(oacc[u][db][4 * g] * inv, oacc[u][db][4 * g + 1] * inv, oacc[u][db][4 * g + 2] * inv, oacc[u][db][4 * g + 3] * inv);
+      if (r < it.q_rows && hh == 0) p.lse[(int64_t)head * p.total_q + it.q_row0 + r] = (mc[u] + log2f(l_tot)) * 0.6931471805599453f;
+    }
+    __bf16* const obase = p.o + (int64_t)(it.q_row0 + wave_row0) * q_stride + (int64_t)head * D;
+#pragma unroll 4
+    for (int i = 0; i < 64 * KC / 64; ++i) {
+      const int y = i * 64 + lane, row = y / KC, ch = unswz<KC>(row, y % KC);
+      const bf16x8 v = lds_load8(stage + y * 8);
+      if (wave_row0 + row < it.q_rows) *reinterpret_cast<bf16x8*>(obase + (int64_t)row * q_stride + ch * 8) = v;
+    }
+  }
+  if (direct) break;
+  // on to the next block; the stores above are not waited for here
+  int nb = 0;
+  if (wave == 0) nb = block_claim_finish(p.taken, num_blocks, xcd, pending_claim);
+  blk = broadcast_from_wave0(next_block, nb);
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
 // Forward of small chunks: a workgroup takes 32 query rows of HG heads of one group, and KS waves per head divide the keys: those of split x
 // take stages x, x + KS, ... of 32 keys.  The HG waves of a split share its stages (one barrier per step; a single head's waves wait for
 // nothing but their own copies), and the splits' sums meet in LDS at the end, where they are put together as fwd_merge_kernel does it.
@@ -1643,6 +2040,13 @@ hipError_t launch_fwd(const FwdParams& p, int head_dim, FwdKind kind, const FwdL
     if (head_dim == 96)
       return heads == 4 ? launch_fwd_share<96, 4, 2, 3>(a, stream) : heads == 2 ? launch_fwd_share<96, 2, 4, 2>(a, stream) : launch_fwd_share<96, 1, 8, 1>(a, stream);
     return heads == 4 ? launch_fwd_share<128, 4, 2, 3>(a, stream) : heads == 2 ? launch_fwd_share<128, 2, 4, 2>(a, stream) : launch_fwd_share<128, 1, 8, 1>(a, stream);
+  }
+  if (kind == kFwdTall) {
+    const size_t smem = (size_t)8 * 32 * 256 * 2 + 16;  // four slots of K and of V, two words
+    static const hipError_t attr = raise_smem_limit(&fwd_tall_kernel, smem);
+    if (attr != hipSuccess) return attr;
+    hipLaunchKernelGGL(fwd_tall_kernel, dim3(persistent_grid(a.num_blocks)), dim3(256), smem, stream, a);
+    return hipGetLastError();
   }
   if (head_dim == 256) {
     const size_t smem = (size_t)10 * 32 * 256 * 2;  // four slots of K, five of V, and one tile more for the staging

@@ -184,8 +184,8 @@ struct FwdLists {
 // workgroups of the pipelined forward on a CU
 constexpr int fwd_per_cu(int head_dim) { return head_dim == 64 ? 2 : 1; }
 // kFwdPipe: the pipelined kernel (and the launch that puts cut walks together); kFwdShare: fwd_share_kernel (head_dim 64, 96 and 128); kFwdPlain: fwd_kernel
-// at head_dim 64, fwd_wide_kernel at 256.
-enum FwdKind { kFwdPlain, kFwdPipe, kFwdShare };
+// at head_dim 64, fwd_wide_kernel at 256; kFwdTall: fwd_tall_kernel (256).
+enum FwdKind { kFwdPlain, kFwdPipe, kFwdShare, kFwdTall };
 hipError_t launch_fwd(const FwdParams& p, int head_dim, FwdKind kind, const FwdLists& lists, hipStream_t stream);
 
 }  // namespace chunk_attn

@@ -271,6 +271,10 @@ CutKind tile_walks(const chunk_attn_desc* d, int keys) {
   return k;
 }
 
+int64_t last_end(const std::vector<int64_t>& cost, int workers, std::vector<int64_t>& free_at) {
+  return cost.size() > kManyBlocks ? std::accumulate(cost.begin(), cost.end(), (int64_t)0) / workers : deal(cost, workers, free_at);
+}
+
 // When the last of queue 0's blocks of both kinds ends, none of them cut, in the order in which one launch starts them: a dQ block costs `dq_stage` per stage and `dq_start`
 // more, a dK/dV block of `keys` keys `step` per step and `start` more.
 int64_t joint_end(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int dq_stage, int dq_start, int step, int start, int cus) {
@@ -281,8 +285,7 @@ int64_t joint_end(const chunk_attn_desc* d, int tile_rows, int inner, int keys, 
   const bool dq_first = q.longest > (int64_t)k.longest * k.group;  // (bwd_layout)
   std::vector<int64_t>&both = dq_first ? dq : dkv, &second = dq_first ? dkv : dq;
   both.insert(both.end(), second.begin(), second.end());
-  const int workers = std::max(1, cus / 8);
-  return both.size() > kManyBlocks ? std::accumulate(both.begin(), both.end(), (int64_t)0) / workers : deal(both, workers, free_at);
+  return last_end(both, std::max(1, cus / 8), free_at);
 }
 
 // The cut of N kinds of block that share the compute units, one split each; at most max_parts[i] partial results of kind i.
@@ -663,6 +666,20 @@ bool wide_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int
   const double per_cu = 1.0 / cus, dq_all = std::max((double)wq.stages * inner * per_cu, (double)wq.longest);
   const double other = 23.1 + 0.42 * dq_all + (21.6 * wq.items * inner + (1.911 * w.stages + 4.71 * w.items) * d->num_kv_heads) * per_cu;
   return pipelined < 0.96 * other;
+}
+
+// Blocks of the two kinds dealt as in tall_pays, in 1/20 us: 0.95 us per stage of 32 keys and 12 us more for 32 rows per wave, 1.3 and 22 for 64; off by 9 and 11 %
+// over those of 700 drawn chunks (up to 65536 keys, 8 - 64 query heads) that take 15 us or more.  Of the 700 it picks 205, of which three are slower by more than 2 %
+// (9 % at most: 209 sequences of 203 tokens, 8/2 heads, 183 us); all 700 take 4.6 % less (mean logarithm), with the better of the two for each 4.9.  32 / 64 rows per
+// wave: 8192 queries on 32768 keys, 32/8 heads, 7329 / 5658 us, 4096 causal tokens 302 / 242; what stays: 2668 causal tokens, 8/8, 85 / 115.
+bool fwd_tall_pays(const chunk_attn_desc* d, int tile_rows, int inner, int cus) {
+  if (count_walks(d, tile_rows).items * inner <= cus) return false;  // (all blocks run at once, and short ones end sooner)
+  auto end = [&](int rows, int stage, int start) {
+    std::vector<int64_t> cost, free_at;
+    queue_costs(key_walks(d, rows, inner), stage, start, cost);
+    return last_end(cost, std::max(1, cus / 8), free_at);
+  };
+  return 100 * end(2 * tile_rows, 26, 440) < 97 * end(tile_rows, 19, 240);
 }
 
 // Times (us) as in wide_pays, of chunks of head_dim 64 whose dQ and dK/dV are pipelined as launches of their own, or in one with dK/dV blocks of kTallKeys keys.  Off by 8 %

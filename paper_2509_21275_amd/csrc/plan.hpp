@@ -182,6 +182,8 @@ bool tall_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int
 // 283 / 277; four of 256, 8/8 (6) 50 / 49; 148 queries on 595 keys, 8/2 (17) 76 / 72; 32/8 heads: eight sequences of 220 (4) 107 / 111, 64 of 220 (4) 639 / 652,
 // 64 of 256 (4.5) 776 / 760; 1024 causal tokens (16.5) 144 / 135; 909 on 5603 keys (161) 638 / 598.
 inline bool dq_wide_pays(const Walks& w) { return 2 * w.stages >= 11 * w.items; }
+// Whether the forward of head_dim 256 ends sooner with blocks of twice `tile_rows` query rows, 64 per wave (fwd_tall_kernel), than of `tile_rows` (fwd_wide_kernel).
+bool fwd_tall_pays(const chunk_attn_desc* d, int tile_rows, int inner, int cus);
 // Whether a chunk of head_dim 64 whose dQ and dK/dV are both pipelined ends sooner in one launch, with dK/dV blocks of kTallKeys keys, than in two, of `keys`.
 bool narrow_tall_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int cus);
 // Whether head_dim 256 runs its pipelined dK/dV blocks, of kWideKeys keys, rather than those of bwd_dkv_kernel, of `keys` (by estimates of both).

@@ -1,4 +1,5 @@
-"""Which chunks of head dimensions 64, 96 and 128 run dK/dV blocks of 256 keys, which of 256 the pipelined ones of 128 keys, and what their steps compile to."""
+"""Which chunks of head dimensions 64, 96 and 128 run dK/dV blocks of 256 keys, which of 256 the pipelined ones of 128 keys and which the forward of 64 query
+rows per wave, and what their steps compile to."""
 import os
 import re
 import shutil
@@ -57,6 +58,19 @@ def test_blocks_of_head_dim_64(segs, hq, hk, keys):
     assert ca.chunk_attn_test_dkv_keys(desc) == keys
 
 
+@pytest.mark.parametrize("segs,hq,hk,rows", [
+    ([(0, 4096, 0, 4096)], 32, 8, 64), ([(0, 2048, 0, 32768)], 32, 8, 64), ([(300 * i, 300, 300 * i, 300) for i in range(64)], 32, 8, 64),
+    ([(0, 640, 0, 640)], 256, 64, 64),
+    ([(0, 1024, 0, 1024)], 32, 8, 32),                                      # no more blocks of 32 rows per wave than compute units
+    ([(0, 2668, 0, 2668)], 8, 8, 32),                                       # the first, long blocks of 64 rows end last
+    ([(128 * i, 128, 128 * i, 128) for i in range(64)], 16, 16, 32),        # half of every block of 256 rows would be empty
+])
+def test_forward_of_head_dim_256(segs, hq, hk, rows):
+    tq, tkv = sum(s[1] for s in segs), segs[-1][2] + segs[-1][3]
+    desc = ca.make_desc(segs, hq, hk, 256, tq, tkv, 0.0625)
+    assert ca.chunk_attn_test_fwd_rows(desc) == rows and not ca.chunk_attn_test_routes(desc) & ca.ROUTE_FWD_PIPELINED
+
+
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 
@@ -64,13 +78,13 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 def test_steps_of_full_registers_touch_no_scratch(tmp_path):
     """The steps of kernels whose accumulators fill the accumulation registers spill nothing: a reload in a step waits for all copies in flight
     (two of them made the dK/dV blocks of head dimension 128 a fifth slower)."""
-    out = str(tmp_path / "bwd.s")
-    r = subprocess.run([HIPCC, *FLAGS, "-x", "hip", "--cuda-device-only", "-S", os.path.join(CSRC, "bwd_kernel.hip"), "-o", out],
-                       capture_output=True, text=True)
-    assert r.returncode == 0, r.stderr[-2000:]
-    text = open(out).read()
-    for name in ("bwd_pipe_kernelILi64ELb0ELb1", "bwd_pipe_kernelILi128ELb0ELb1", "bwd_pipe_kernelILi96ELb0ELb1", "bwd_pipe_kernelILi256ELb0ELb1"):
-        at = re.search(r"^\S*%s\S*:" % name, text, re.M).end()
-        blocks = re.split(r"^\.LBB\S+:", text[at:text.index(".Lfunc_end", at)], flags=re.M)
-        steps = [b for b in blocks if b.count("v_mfma") >= 4]
-        assert steps and not any("scratch_" in b for b in steps), name
+    for src, names in (("bwd_kernel.hip", ["bwd_pipe_kernelILi%dELb0ELb1" % d for d in (64, 96, 128, 256)]), ("fwd_kernel.hip", ["fwd_tall_kernel"])):
+        out = str(tmp_path / "kernels.s")
+        r = subprocess.run([HIPCC, *FLAGS, "-x", "hip", "--cuda-device-only", "-S", os.path.join(CSRC, src), "-o", out], capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr[-2000:]
+        text = open(out).read()
+        for name in names:
+            at = re.search(r"^\S*%s\S*:" % name, text, re.M).end()
+            blocks = re.split(r"^\.LBB\S+:", text[at:text.index(".Lfunc_end", at)], flags=re.M)
+            steps = [b for b in blocks if b.count("v_mfma") >= 4]
+            assert steps and not any("scratch_" in b for b in steps), name
