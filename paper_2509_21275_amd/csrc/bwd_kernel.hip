@@ -5,15 +5,15 @@
 // only one of them in registers.  Float atomics for the other one are far too slow on this chip at the
 // rate an attention backward produces them, so each reduction gets blocks of its own kind and every output
 // element is written exactly once, or put together from the partial results of a walk that was cut, in a fixed order (the result is
-// also bit-reproducible).  Both kinds of block share a launch (bwd_pipe_kernel, bwd_short_kernel) except in long chunks of head_dim 64 and 256:
+// also bit-reproducible).  Both kinds of block share a launch (bwd_pipe_kernel, bwd_short_kernel) except where they do not end sooner so (head_dim 64 and 256, bwd_layout):
 //
 //   bwd_pre   D_i = <dO_i, O_i> and LSE_i log2(e) per (head, row), stored in arrays padded to 64-row
 //             tiles per segment (+inf / 0 in the padding, so padded rows yield P = 0);
 //   bwd_dq    query-stationary, like the forward: S^T = K Q^T and dP^T = V dO^T per 32-key tile,
 //             dS^T = P^T (dP^T - D), dQ^T += K^T dS^T with dS^T fed back from the accumulator registers;
-//   bwd_dkv   key-stationary: one workgroup per 128 keys of one key/value head, walking the query heads of
-//             the group and the 32-row query tiles that see those keys; two wave roles per key block,
-//             S = Q K^T, P, dV^T += dO^T P  and  dP = dO V^T, dS, dK^T += Q^T dS (see the kernel).
+//   bwd_dkv   key-stationary: one workgroup per 64 to 256 keys of one key/value head (dkv_block_keys), walking the query heads of
+//             the group and the 32-row query tiles that see those keys: S = Q K^T, P, dV^T += dO^T P  and  dP = dO V^T, dS,
+//             dK^T += Q^T dS, in two wave roles (dkv_pipe_blocks) or all in each wave (the others).
 // P is recomputed from the saved log-sum-exp in both.  All operands reach LDS by global->LDS copies.
 #include <cstring>
 #include <cstdlib>

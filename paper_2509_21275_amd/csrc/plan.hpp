@@ -52,7 +52,7 @@ struct DqItem {
                      // were cut: the first slot)
 };
 
-// Work item of the dK/dV kernel: up to 128 consecutive key rows of one segment and the 32-row query tiles
+// Work item of the dK/dV kernel: up to 256 consecutive key rows of one segment and the 32-row query tiles
 // (aligned to the segment's first query) that contain at least one query seeing them.
 struct DkvItem {
   int32_t kv_row0;    // first key row of the tile (global)
