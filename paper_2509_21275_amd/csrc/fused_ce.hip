@@ -6,23 +6,30 @@
 // The exponential of an element is evaluated twice (for the sum and for the gradient) rather than kept: the vector work of
 // a row is several times shorter than the time HBM needs to deliver it.  Workgroups walk the rows with a grid stride.
 //
-// Two kernels.  Rows of up to 131072 logits (fused_ce_kernel) stay in 128 registers per lane; maximum and sum are two passes
-// over them.  Longer rows (fused_ce_long_kernel) take more registers and LDS; with one workgroup per compute unit nothing
-// hides the vector work between the last load and the first store, so the sum is taken while the row arrives, against the
-// running maximum of the thread's own chunks (moved once per group of chunks), and the threads' (maximum, sum) pairs are
-// merged once per row.  Measured: 4096 rows of 151936 logits 538 us, 4.6 TB/s (a copy of the same bytes by the runtime: 5.5
-// TB/s; with three passes over memory, as such rows took before: 780 us), 2048 of 200064 539 -> 391 us.  On shorter rows the
-// one-pass sum is the slower one (16384 rows of 8000: 119 -> 148 us; 256 of 64000: 14.1 -> 15.0).
+// Two kernels.  fused_ce_kernel: rows of up to 65536 logits, and of up to 131072 where there are fewer than two per compute unit; they stay in at most 128
+// registers per lane, maximum and sum are two passes over them, and two or more workgroups on a compute unit (or the other compute units) hide each other's vector work.
+// fused_ce_long_kernel: longer rows take more registers, the longest LDS, too, so that one workgroup has the compute unit.  It takes the sum while the row
+// arrives, against the running maximum of the thread's own chunks (moved once per group of chunks), merges the threads' (maximum, sum) pairs once per row, and as it
+// stores a chunk's gradient it loads that chunk of its next row into the same registers: reads stay in flight through the vector work of the gradients, a third of
+// a row's time.  us, a row after the other -> so -> and past the caches (kStreamBytes): 4096 rows of 151936 logits 534 (4.7 TB/s) -> 516 -> 498 (5.0; a copy of
+// the same bytes by the runtime: 5.5), 1024 of 262144 276 -> 245 -> 221, 4096 of 128000 454 -> 431 -> 414 (before: fused_ce_kernel), 700 of 140000 86 -> 78.
+// Where the long kernel is the slower one: 16384 rows of 8000 119 -> 148; 64 of 128256 19.5 -> 21.4, 300 of 100000 37.7 -> 38.5 (512 of 70000 35.3 -> 31.4).
 #include <hip/hip_runtime.h>
 
 #include "../../include/fused_ce.h"
 #include "device_common.hpp"
+#include "kernels.hpp"
 #include "tiles.hpp"
 
 namespace chunk_attn {
 namespace {
 
 constexpr int kThreads = 512;
+// Logits of more bytes than the last-level cache (256 MiB) holds stream past the caches; what fits is kept for those who wrote it and who read it next.
+// fused_ce_long_kernel, us, kept / streamed: 512 rows of 262144 (268 MB) 104 / 113, 1024 of 131072 (268) 103 / 111, 900 of 151936 (273) 128 / 123, 4096 of 66000 (541) 241 /
+// 234.  fused_ce_kernel, which has more workgroups' rows in flight, a little later: 4400 of 32000 (282) 106.2 / 107.2, 6000 of 24000 (288) 107.3 / 103.7,
+// 16384 of 16000 (524) 200 / 182, 65536 of 4096 (537) 387 / 324 (loads kept and stores streamed: 386).
+constexpr int64_t kStreamBytes = (int64_t)256 << 20, kStreamBytesShort = (int64_t)272 << 20;
 constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
 
 __device__ __forceinline__ float wave_max(float x) {
@@ -36,8 +43,21 @@ __device__ __forceinline__ float wave_sum(float x) {
   return x;
 }
 
+// STREAM: what is loaded and stored is not kept in the caches (kStreamBytes).
+template <bool STREAM>
+__device__ __forceinline__ bf16x8 load_chunk_at(const void* from) {
+  const bf16x8* const p = reinterpret_cast<const bf16x8*>(from);
+  return STREAM ? __builtin_nontemporal_load(p) : *p;
+}
+template <bool STREAM>
+__device__ __forceinline__ void store_chunk_at(void* to, bf16x8 x) {
+  bf16x8* const p = reinterpret_cast<bf16x8*>(to);
+  if constexpr (STREAM) __builtin_nontemporal_store(x, p);
+  else *p = x;
+}
+
 // NCH: 16-byte chunks per thread (a row has at most 512 * 8 * NCH logits; 32 chunks = 128 registers is what fits)
-template <int NCH>
+template <int NCH, bool STREAM>
 __global__ __launch_bounds__(kThreads) void fused_ce_kernel(__bf16* __restrict__ logits, const int32_t* __restrict__ targets,
                                                             float* __restrict__ loss, int64_t rows, int vocab,
                                                             int64_t row_stride, float grad_scale) {
@@ -53,7 +73,7 @@ __global__ __launch_bounds__(kThreads) void fused_ce_kernel(__bf16* __restrict__
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
       const int ch = c * kThreads + tid;
-      if (ch < n_chunks) v[c] = *reinterpret_cast<const bf16x8*>(z + (int64_t)ch * 8);
+      if (ch < n_chunks) v[c] = load_chunk_at<STREAM>(z + (int64_t)ch * 8);
     }
     // Between the three passes the row is kept as it was loaded (packed bf16): the opaque statements stop the compiler
     // from keeping a widened fp32 copy of the whole row alive, which would not fit the register file.
@@ -103,18 +123,18 @@ __global__ __launch_bounds__(kThreads) void fused_ce_kernel(__bf16* __restrict__
           if (d == e) pe -= 1.0f;
           g[e] = (__bf16)(pe * scale);
         }
-        *reinterpret_cast<bf16x8*>(z + (int64_t)ch * 8) = g;
+        store_chunk_at<STREAM>(z + (int64_t)ch * 8, g);
       }
     }
     __syncthreads();  // red[] is reused by the next row
   }
 }
 
-// Longer rows, up to 262144 logits.  NCH: 16-byte chunks per thread kept in registers, NL: further ones kept in LDS (a row has at most
+// Longer rows, up to 262144 logits.  FULL: chunks that every lane has.  NCH: 16-byte chunks per thread kept in registers, NL: further ones kept in LDS (a row has at most
 // 512 * 8 * (NCH + NL) logits).  A compute unit has 512 KB of registers and 160 KB of LDS and a row of 262144 logits takes
 // 512 KB, so the longest rows need both: chunks past the NCH-th are copied global -> LDS (wave w's chunk c in 1 KB at
 // c * 8 + w; each lane reads back what its own wave copied, so no barrier is needed).
-template <int NCH, int NL>
+template <int NCH, int NL, int FULL, bool STREAM>
 __global__ __launch_bounds__(kThreads) void fused_ce_long_kernel(__bf16* __restrict__ logits, const int32_t* __restrict__ targets,
                                                             float* __restrict__ loss, int64_t rows, int vocab,
                                                             int64_t row_stride, float grad_scale) {
@@ -130,36 +150,45 @@ __global__ __launch_bounds__(kThreads) void fused_ce_long_kernel(__bf16* __restr
   bf16x8 ninf8;
 #pragma unroll
   for (int e = 0; e < 8; ++e) ninf8[e] = (__bf16)-INFINITY;
-  int set = 0;
-  for (int64_t row = blockIdx.x; row < rows; row += gridDim.x, set ^= 1) {
-    __bf16* const z = logits + row * row_stride;
-    const int y = targets[row];
+  // The first FULL chunks every lane has.  Of the others it may lack some: of a chunk that only some lanes have the others load the row's last 16 bytes, and what a lane
+  // lacks counts as -inf and is not stored.  Loads are only behind wave-uniform branches: behind one that masks lanes the compiler waits for all of them at once.
+  const unsigned lane_off = (unsigned)tid * 16u;
+  const int last = (n_chunks - 1) / kThreads;  // the chunk that some lanes may lack; all lanes lack the ones behind it
+  const unsigned last_off = (unsigned)min(tid, n_chunks - 1 - last * kThreads) * 16u;
+  auto load_chunk = [&](const char* zb, int c) __attribute__((always_inline)) {
+    unsigned off = lane_off, off_l = last_off;
+    asm volatile("" : "+v"(off), "+v"(off_l));  // (the choice is made here, not kept in a register for each chunk)
+    if (c >= FULL) off = c < last ? off : off_l;
+    return load_chunk_at<STREAM>(zb + c * kThreads * 16 + off);
+  };
+  auto has_chunk = [&](int c) __attribute__((always_inline)) {
+    int t = tid;
+    asm volatile("" : "+v"(t));
+    return c < FULL || t < n_chunks - c * kThreads;
+  };
+  auto copy_chunk = [&](const char* zb, int c) __attribute__((always_inline)) {  // (to LDS; lanes past the row copy its last chunk, ignored below)
+    if ((NCH + c) * kThreads + wave * 64 < n_chunks) {
+      const int ch = min((NCH + c) * kThreads + tid, n_chunks - 1);
+      dma16(zb + (int64_t)ch * 16, tail + (c * NW + wave) * 512);
+    }
+  };
+  int64_t row = blockIdx.x;
+  char* zb = reinterpret_cast<char*>(logits + row * row_stride);
+  int y = targets[row];
+  auto target_logit = [&](const char* from, int at) __attribute__((always_inline)) {  // (every thread: one cached load; not used where the row is ignored)
+    return reinterpret_cast<const unsigned short*>(from)[at < 0 || at >= vocab ? 0 : at];
+  };
+  unsigned zy = target_logit(zb, y);  // its bits
+  bf16x8 v[NCH];
+#pragma unroll 1
+  for (int c = 0; c < NL; ++c) copy_chunk(zb, c);
+#pragma unroll
+  for (int c = 0; c < NCH; ++c) {
+    if (c >= FULL) v[c] = ninf8;
+    if (c < FULL || c <= last) v[c] = load_chunk(zb, c);
+  }
+  for (int set = 0;; set ^= 1) {
     const bool ignored = y < 0 || y >= vocab;
-    const float zy = ignored ? 0.f : (float)z[y];  // read before the row is overwritten (every thread: one cached load)
-    if constexpr (NL > 0) {
-#pragma unroll
-      for (int c = 0; c < NL; ++c) {  // lanes past the row copy its last chunk (ignored below)
-        if ((NCH + c) * kThreads + wave * 64 < n_chunks) {
-          const int ch = min((NCH + c) * kThreads + tid, n_chunks - 1);
-          dma16(z + (int64_t)ch * 8, tail + (c * NW + wave) * 512);
-        }
-      }
-    }
-    // (the row's last chunks are the only ones some lanes lack: they read as -inf and are not stored; everything else
-    // branches on wave-uniform conditions, from a scalar base address and one 32-bit offset per lane)
-    char* const zb = reinterpret_cast<char*>(z);
-    const unsigned lane_off = (unsigned)tid * 16u;
-    bf16x8 v[NCH];
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      const char* base = zb + c * kThreads * 16;
-      if ((c + 1) * kThreads <= n_chunks) {
-        v[c] = *reinterpret_cast<const bf16x8*>(base + lane_off);
-      } else {
-        v[c] = ninf8;
-        if (c * kThreads + tid < n_chunks) v[c] = *reinterpret_cast<const bf16x8*>(base + lane_off);
-      }
-    }
     // Maximum (mx, in log2 units: the rounded product is what every exponent is taken against, so that it drops out of
     // the result) and sum of the thread's chunks, group by group.  A thread whose chunks so far are all -inf (or absent) keeps
     // the maximum at -inf and counts against 0 instead, where they contribute exp2(-inf) = 0.
@@ -181,10 +210,10 @@ __global__ __launch_bounds__(kThreads) void fused_ce_long_kernel(__bf16* __restr
     };
 #pragma unroll
     for (int c0 = 0; c0 < NCH; c0 += GRP) {
-      if (c0 * kThreads >= n_chunks) continue;
+      if (c0 >= FULL && c0 * kThreads >= n_chunks) continue;
       bf16x8 g[GRP];
 #pragma unroll
-      for (int c = 0; c < GRP; ++c) g[c] = v[c0 + c];
+      for (int c = 0; c < GRP; ++c) g[c] = has_chunk(c0 + c) ? v[c0 + c] : ninf8;
       count_group(g);
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -197,7 +226,7 @@ __global__ __launch_bounds__(kThreads) void fused_ce_long_kernel(__bf16* __restr
 #pragma unroll
         for (int c = 0; c < GRP; ++c) {
           g[c] = lds_load8(tail + ((c0 + c) * NW + wave) * 512 + lane * 8);
-          if ((NCH + c0 + c) * kThreads + tid >= n_chunks) g[c] = ninf8;
+          if (!has_chunk(NCH + c0 + c)) g[c] = ninf8;
         }
         count_group(g);
       }
@@ -211,6 +240,7 @@ __global__ __launch_bounds__(kThreads) void fused_ce_long_kernel(__bf16* __restr
       red_m[set][wave] = wm;
       red_s[set][wave] = sum;
     }
+    asm volatile("" : "+v"(zy));  // (it has arrived before any wave overwrites the row)
     __syncthreads();
     float bm = red_m[set][0];
 #pragma unroll
@@ -220,10 +250,11 @@ __global__ __launch_bounds__(kThreads) void fused_ce_long_kernel(__bf16* __restr
     for (int w = 0; w < NW; ++w)
       sum += red_m[set][w] == -INFINITY ? red_s[set][w] : red_s[set][w] * __builtin_amdgcn_exp2f(red_m[set][w] - bm);
     const float lse2 = bm + __builtin_amdgcn_logf(sum);  // log2 of the sum of exponentials
-    if (tid == 0) loss[row] = ignored ? 0.f : lse2 * kLn2 - zy;
+    if (tid == 0) loss[row] = ignored ? 0.f : lse2 * kLn2 - __builtin_bit_cast(float, zy << 16);
     const float scale = ignored ? 0.f : grad_scale;
+    const int y_lane = y - tid * 8;  // (of this row)
     auto store_chunk = [&](bf16x8 x, int c) __attribute__((always_inline)) {
-      const int d = y - (c * kThreads + tid) * 8;  // position of the target inside this chunk, if it is there
+      const int d = y_lane - c * (kThreads * 8);  // position of the target inside this chunk, if it is there
       bf16x8 g;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
@@ -231,43 +262,62 @@ __global__ __launch_bounds__(kThreads) void fused_ce_long_kernel(__bf16* __restr
         if (d == e) pe -= 1.0f;
         g[e] = (__bf16)(pe * scale);
       }
-      *reinterpret_cast<bf16x8*>(zb + c * kThreads * 16 + lane_off) = g;
+      store_chunk_at<STREAM>(zb + c * kThreads * 16 + lane_off, g);
     };
+    // As a chunk is stored its place takes that chunk of the workgroup's next row.
+    const int64_t next = row + gridDim.x;
+    const bool more = next < rows;
+    char* const zn = reinterpret_cast<char*>(logits + next * row_stride);
+    if (more) {
+      y = targets[next];
+      zy = target_logit(zn, y);
+    }
     // The row is kept as it was loaded (packed bf16): the opaque statements stop the compiler from keeping a widened
     // fp32 copy of the whole row alive, which would not fit the register file.
 #pragma unroll
     for (int c = 0; c < NCH; ++c) asm volatile("" : "+v"(v[c]));
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
-      if ((c + 1) * kThreads <= n_chunks) store_chunk(v[c], c);
-      else if (c * kThreads + tid < n_chunks) store_chunk(v[c], c);
+      if (has_chunk(c)) store_chunk(v[c], c);
+      if (more && (c < FULL || c <= last)) v[c] = load_chunk(zn, c);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    if constexpr (NL > 0) {
 #pragma unroll 2
-      for (int c = 0; c < NL; ++c) {
-        if ((NCH + c) * kThreads + tid < n_chunks) store_chunk(lds_load8(tail + (c * NW + wave) * 512 + lane * 8), NCH + c);
-      }
+    for (int c = 0; c < NL; ++c) {
+      if (has_chunk(NCH + c)) store_chunk(lds_load8(tail + (c * NW + wave) * 512 + lane * 8), NCH + c);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (the chunk has been read: a copy may take its place)
+      if (more) copy_chunk(zn, c);
     }
+    if (!more) break;
+    row = next;
+    zb = zn;
   }
 }
 
-template <int NCH, int NL = 0>
-hipError_t launch(void* logits, const int32_t* targets, float* loss, int64_t rows, int vocab, int64_t row_stride,
-                  float grad_scale, hipStream_t stream) {
-  // two workgroups per compute unit when the registers allow it, rows dealt round robin
-  const dim3 grid((unsigned)(rows < 512 ? rows : 512));
-  if constexpr (NCH <= 32) {
-    hipLaunchKernelGGL((fused_ce_kernel<NCH>), grid, dim3(kThreads), 0, stream, (__bf16*)logits, targets, loss, rows, vocab,
+template <int NCH, int NL, int FULL, bool STREAM>
+hipError_t launch_as(void* logits, const int32_t* targets, float* loss, int64_t rows, int vocab, int64_t row_stride,
+                     float grad_scale, hipStream_t stream) {
+  if constexpr (FULL == 0) {
+    // two workgroups per compute unit when the registers allow it, rows dealt round robin
+    const dim3 grid((unsigned)(rows < 512 ? rows : 512));
+    hipLaunchKernelGGL((fused_ce_kernel<NCH, STREAM>), grid, dim3(kThreads), 0, stream, (__bf16*)logits, targets, loss, rows, vocab,
                        row_stride, grad_scale);
   } else {
     constexpr size_t smem = (size_t)NL * kThreads * 16;
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&fused_ce_long_kernel<NCH, NL>),
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&fused_ce_long_kernel<NCH, NL, FULL, STREAM>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL((fused_ce_long_kernel<NCH, NL>), grid, dim3(kThreads), smem, stream, (__bf16*)logits, targets, loss, rows,
+    const dim3 grid((unsigned)persistent_grid(rows));  // one per compute unit is what the registers allow: each goes through its share of the rows
+    hipLaunchKernelGGL((fused_ce_long_kernel<NCH, NL, FULL, STREAM>), grid, dim3(kThreads), smem, stream, (__bf16*)logits, targets, loss, rows,
                        vocab, row_stride, grad_scale);
   }
   return hipGetLastError();
+}
+template <int NCH, int NL = 0, int FULL = 0>
+hipError_t launch(void* logits, const int32_t* targets, float* loss, int64_t rows, int vocab, int64_t row_stride,
+                  float grad_scale, hipStream_t stream) {
+  return rows * (int64_t)vocab * 2 > (FULL == 0 ? kStreamBytesShort : kStreamBytes) ? launch_as<NCH, NL, FULL, true>(logits, targets, loss, rows, vocab, row_stride, grad_scale, stream)
+                                                  : launch_as<NCH, NL, FULL, false>(logits, targets, loss, rows, vocab, row_stride, grad_scale, stream);
 }
 
 }  // namespace
@@ -285,9 +335,10 @@ extern "C" int fused_ce_inplace(void* logits, const int32_t* targets, float* los
   hipError_t e;
   if (per_thread <= 8) e = launch<8>(logits, targets, loss, rows, vocab, row_stride, grad_scale, s);
   else if (per_thread <= 16) e = launch<16>(logits, targets, loss, rows, vocab, row_stride, grad_scale, s);
-  else if (per_thread <= 32) e = launch<32>(logits, targets, loss, rows, vocab, row_stride, grad_scale, s);
-  else if (per_thread <= 40) e = launch<40>(logits, targets, loss, rows, vocab, row_stride, grad_scale, s);
-  else e = launch<46, 18>(logits, targets, loss, rows, vocab, row_stride, grad_scale, s);
+  else if (per_thread <= 32 && rows < 2 * kCus) e = launch<32>(logits, targets, loss, rows, vocab, row_stride, grad_scale, s);
+  else if (per_thread <= 32) e = launch<32, 0, 16>(logits, targets, loss, rows, vocab, row_stride, grad_scale, s);
+  else if (per_thread <= 40) e = launch<40, 0, 32>(logits, targets, loss, rows, vocab, row_stride, grad_scale, s);
+  else e = launch<46, 18, 40>(logits, targets, loss, rows, vocab, row_stride, grad_scale, s);
   static_assert(FUSED_CE_MAX_VOCAB <= kThreads * 8 * (46 + 18), "the longest row fits registers and LDS");
   return e == hipSuccess ? CHUNK_ATTN_OK : CHUNK_ATTN_HIP_ERROR;
 }

@@ -132,3 +132,30 @@ def test_workgroups_that_run_several_rows(rows, vocab):
     got = buf[check].cpu().double().numpy()
     assert np.abs(loss[check].cpu().double().numpy() - want_loss).max() <= 2e-4 * max(1.0, np.abs(want_loss).max())
     assert np.all(np.abs(got - want_grad) <= 2.0 ** -8 * np.abs(want_grad) + 2.0 ** -8 * 0.5 * 1e-3)
+
+
+@pytest.mark.parametrize("rows,vocab", [
+    (511, 65544), (512, 65544), (700, 131064), (520, 131072),            # up to 131072 logits: which kernel depends on the number of rows
+    (520, 131080), (515, 163840), (515, 163848), (510, 188424),          # logits that the last-level cache holds ...
+    (1030, 131072), (900, 151936), (720, 188432), (35000, 4096)])        # ... and some more than it does
+def test_a_row_and_the_next_one_of_its_workgroup(rows, vocab):
+    """A workgroup loads its next row as it stores the one before: rows of a stride that is no multiple of a cache line, some masked (-inf) up to their last
+    chunks, around the multiples of 256 and 512 and at the end against the oracle, with the tolerances above; what lies between the rows stays as it was."""
+    from paper_2509_21275_amd.fused_ce import fused_ce_inplace
+    g = torch.Generator(device="cuda").manual_seed(rows + vocab)
+    buf = torch.randn((rows, vocab + 8), generator=g, device="cuda", dtype=torch.bfloat16)
+    buf += torch.linspace(-30.0, 30.0, rows, device="cuda").to(torch.bfloat16)[torch.randperm(rows, generator=g, device="cuda")].view(-1, 1)
+    buf[1::5, vocab - vocab // 3:vocab] = float("-inf")
+    buf[2::5, 8:vocab // 2] = float("-inf")
+    targets = torch.randint(0, 8, (rows,), generator=g, device="cuda", dtype=torch.int32)
+    targets[3::5] = vocab - 1
+    targets[torch.arange(7, rows, 97, device="cuda")] = -1
+    check = [r for r in (0, 1, 2, 3, 7, 254, 255, 256, 257, 258, 511, 512, 513, 767, 768, 1024, rows - 2, rows - 1) if r < rows]
+    want_loss, want_grad = orc.cross_entropy(buf[check, :vocab].cpu().double().numpy(), targets[check].cpu().numpy(), 0.5)
+    between, loss = buf[:, vocab:].clone(), torch.full((rows,), float("nan"), device="cuda")
+    fused_ce_inplace(buf[:, :vocab], targets, loss, 0.5)
+    torch.cuda.synchronize()
+    got = buf[check, :vocab].cpu().double().numpy()
+    assert bool(torch.isfinite(loss).all()) and torch.equal(buf[:, vocab:], between)
+    assert np.abs(loss[check].cpu().double().numpy() - want_loss).max() <= 2e-4 * max(1.0, np.abs(want_loss).max())
+    assert np.all(np.abs(got - want_grad) <= 2.0 ** -8 * np.abs(want_grad) + 2.0 ** -8 * 0.5 * 1e-3)
