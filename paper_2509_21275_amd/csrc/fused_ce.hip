@@ -11,7 +11,7 @@
 // fused_ce_long_kernel: longer rows take more registers, the longest LDS, too, so that one workgroup has the compute unit.  It takes the sum while the row
 // arrives, against the running maximum of the thread's own chunks (moved once per group of chunks), merges the threads' (maximum, sum) pairs once per row, and as it
 // stores a chunk's gradient it loads that chunk of its next row into the same registers: reads stay in flight through the vector work of the gradients, a third of
-// a row's time.  us, a row after the other -> so -> and past the caches (kStreamBytes): 4096 rows of 151936 logits 534 (4.7 TB/s) -> 516 -> 498 (5.0; a copy of
+// a row's time.  us, a row after the other -> so -> and past the caches: 4096 rows of 151936 logits 534 (4.7 TB/s) -> 516 -> 498 (5.0; a copy of
 // the same bytes by the runtime: 5.5), 1024 of 262144 276 -> 245 -> 221, 4096 of 128000 454 -> 431 -> 414 (before: fused_ce_kernel), 700 of 140000 86 -> 78.
 // Where the long kernel is the slower one: 16384 rows of 8000 119 -> 148; 64 of 128256 19.5 -> 21.4, 300 of 100000 37.7 -> 38.5 (512 of 70000 35.3 -> 31.4).
 #include <hip/hip_runtime.h>
@@ -26,10 +26,15 @@ namespace {
 
 constexpr int kThreads = 512;
 // Logits of more bytes than the last-level cache (256 MiB) holds stream past the caches; what fits is kept for those who wrote it and who read it next.
-// fused_ce_long_kernel, us, kept / streamed: 512 rows of 262144 (268 MB) 104 / 113, 1024 of 131072 (268) 103 / 111, 900 of 151936 (273) 128 / 123, 4096 of 66000 (541) 241 /
-// 234.  fused_ce_kernel, which has more workgroups' rows in flight, a little later: 4400 of 32000 (282) 106.2 / 107.2, 6000 of 24000 (288) 107.3 / 103.7,
-// 16384 of 16000 (524) 200 / 182, 65536 of 4096 (537) 387 / 324 (loads kept and stores streamed: 386).
-constexpr int64_t kStreamBytes = (int64_t)256 << 20, kStreamBytesShort = (int64_t)272 << 20;
+// Rows of whole cache lines (kStreamAll), us, kept / streamed: fused_ce_long_kernel, 512 rows of 262144 (268 MB) 104 / 113, 1024 of 131072 (268) 103 / 111, 900 of
+// 151936 (273) 128 / 123, 4096 of 151936 (1245) 516 / 498; fused_ce_kernel, which has more rows in flight, a little later: 4400 of 32000 (282) 106.2 / 107.2, 6000 of
+// 24000 (288) 107.3 / 103.7, 16384 of 16000 (524) 200 / 182, 65536 of 4096 (537) 387 / 324 (stores only: 386).
+// Where rows begin inside a line, so does every wave's share of a chunk, and the two waves that share a line may each fetch it from memory.  With rows of up to 16384
+// logits that costs less than streaming gains (kept / all: 32768 of 8008 252 / 225, 16384 of 16008 200 / 189); with up to 32768 all is slower and stores only are, too
+// (kept / stores / all: 16384 of 32760 422 / 439 / 444, 8192 of 32008 210 / 214 / 210); longer ones stream their stores, from a larger size on: 1100 of 131064 (288)
+// 131 / 135 / -, 1024 of 151944 (311) 134 / 138 / -, 1100 of 151944 (334) 163 / 160 / -, 1024 of 262136 (537) 261 / 241 / 245, 4096 of 65528 (537) 225 / 207 / 217.
+constexpr int64_t kStreamBytes = (int64_t)256 << 20, kStreamBytesShort = (int64_t)272 << 20, kStreamStoresBytes = (int64_t)320 << 20;
+constexpr int kShortRow = 16384;
 constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
 
 __device__ __forceinline__ float wave_max(float x) {
@@ -43,21 +48,22 @@ __device__ __forceinline__ float wave_sum(float x) {
   return x;
 }
 
-// STREAM: what is loaded and stored is not kept in the caches (kStreamBytes).
-template <bool STREAM>
+// What passes the caches by.
+enum Stream { kKeep, kStreamStores, kStreamAll };
+template <Stream STREAM>
 __device__ __forceinline__ bf16x8 load_chunk_at(const void* from) {
   const bf16x8* const p = reinterpret_cast<const bf16x8*>(from);
-  return STREAM ? __builtin_nontemporal_load(p) : *p;
+  return STREAM == kStreamAll ? __builtin_nontemporal_load(p) : *p;
 }
-template <bool STREAM>
+template <Stream STREAM>
 __device__ __forceinline__ void store_chunk_at(void* to, bf16x8 x) {
   bf16x8* const p = reinterpret_cast<bf16x8*>(to);
-  if constexpr (STREAM) __builtin_nontemporal_store(x, p);
+  if constexpr (STREAM != kKeep) __builtin_nontemporal_store(x, p);
   else *p = x;
 }
 
 // NCH: 16-byte chunks per thread (a row has at most 512 * 8 * NCH logits; 32 chunks = 128 registers is what fits)
-template <int NCH, bool STREAM>
+template <int NCH, Stream STREAM>
 __global__ __launch_bounds__(kThreads) void fused_ce_kernel(__bf16* __restrict__ logits, const int32_t* __restrict__ targets,
                                                             float* __restrict__ loss, int64_t rows, int vocab,
                                                             int64_t row_stride, float grad_scale) {
@@ -134,7 +140,7 @@ __global__ __launch_bounds__(kThreads) void fused_ce_kernel(__bf16* __restrict__
 // 512 * 8 * (NCH + NL) logits).  A compute unit has 512 KB of registers and 160 KB of LDS and a row of 262144 logits takes
 // 512 KB, so the longest rows need both: chunks past the NCH-th are copied global -> LDS (wave w's chunk c in 1 KB at
 // c * 8 + w; each lane reads back what its own wave copied, so no barrier is needed).
-template <int NCH, int NL, int FULL, bool STREAM>
+template <int NCH, int NL, int FULL, Stream STREAM>
 __global__ __launch_bounds__(kThreads) void fused_ce_long_kernel(__bf16* __restrict__ logits, const int32_t* __restrict__ targets,
                                                             float* __restrict__ loss, int64_t rows, int vocab,
                                                             int64_t row_stride, float grad_scale) {
@@ -294,7 +300,7 @@ __global__ __launch_bounds__(kThreads) void fused_ce_long_kernel(__bf16* __restr
   }
 }
 
-template <int NCH, int NL, int FULL, bool STREAM>
+template <int NCH, int NL, int FULL, Stream STREAM>
 hipError_t launch_as(void* logits, const int32_t* targets, float* loss, int64_t rows, int vocab, int64_t row_stride,
                      float grad_scale, hipStream_t stream) {
   if constexpr (FULL == 0) {
@@ -316,8 +322,19 @@ hipError_t launch_as(void* logits, const int32_t* targets, float* loss, int64_t 
 template <int NCH, int NL = 0, int FULL = 0>
 hipError_t launch(void* logits, const int32_t* targets, float* loss, int64_t rows, int vocab, int64_t row_stride,
                   float grad_scale, hipStream_t stream) {
-  return rows * (int64_t)vocab * 2 > (FULL == 0 ? kStreamBytesShort : kStreamBytes) ? launch_as<NCH, NL, FULL, true>(logits, targets, loss, rows, vocab, row_stride, grad_scale, stream)
-                                                  : launch_as<NCH, NL, FULL, false>(logits, targets, loss, rows, vocab, row_stride, grad_scale, stream);
+  auto as = [&](auto stream_c) {
+    return launch_as<NCH, NL, FULL, decltype(stream_c)::value>(logits, targets, loss, rows, vocab, row_stride, grad_scale, stream);
+  };
+  const std::integral_constant<Stream, kKeep> keep;
+  if constexpr (FULL == 0 && NCH == 32) return as(keep);  // (fewer than 512 rows)
+  else {
+    const int64_t bytes = rows * (int64_t)vocab * 2;
+    const bool whole_lines = ((uintptr_t)logits & 127) == 0 && row_stride % 64 == 0;
+    if (whole_lines || (FULL == 0 && vocab <= kShortRow))
+      return bytes > (FULL == 0 ? kStreamBytesShort : kStreamBytes) ? as(std::integral_constant<Stream, kStreamAll>{}) : as(keep);
+    if (NCH <= 8 || bytes <= kStreamStoresBytes) return as(keep);
+    return as(std::integral_constant<Stream, kStreamStores>{});
+  }
 }
 
 }  // namespace

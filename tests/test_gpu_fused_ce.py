@@ -137,13 +137,15 @@ def test_workgroups_that_run_several_rows(rows, vocab):
 @pytest.mark.parametrize("rows,vocab", [
     (511, 65544), (512, 65544), (700, 131064), (520, 131072),            # up to 131072 logits: which kernel depends on the number of rows
     (520, 131080), (515, 163840), (515, 163848), (510, 188424),          # logits that the last-level cache holds ...
-    (1030, 131072), (900, 151936), (720, 188432), (35000, 4096)])        # ... and some more than it does
-def test_a_row_and_the_next_one_of_its_workgroup(rows, vocab):
-    """A workgroup loads its next row as it stores the one before: rows of a stride that is no multiple of a cache line, some masked (-inf) up to their last
+    (1300, 131072), (1110, 151936), (900, 188432), (35800, 4096), (2600, 65528)])  # ... and some more than it does
+@pytest.mark.parametrize("whole_lines", [False, True])
+def test_a_row_and_the_next_one_of_its_workgroup(rows, vocab, whole_lines):
+    """A workgroup loads its next row as it stores the one before: rows of a stride that is a multiple of a cache line, or not, some masked (-inf) up to their last
     chunks, around the multiples of 256 and 512 and at the end against the oracle, with the tolerances above; what lies between the rows stays as it was."""
     from paper_2509_21275_amd.fused_ce import fused_ce_inplace
     g = torch.Generator(device="cuda").manual_seed(rows + vocab)
-    buf = torch.randn((rows, vocab + 8), generator=g, device="cuda", dtype=torch.bfloat16)
+    stride = vocab + 8 if (vocab + 8) % 64 != 0 else vocab + 16
+    buf = torch.randn((rows, (vocab + 64) // 64 * 64 if whole_lines else stride), generator=g, device="cuda", dtype=torch.bfloat16)
     buf += torch.linspace(-30.0, 30.0, rows, device="cuda").to(torch.bfloat16)[torch.randperm(rows, generator=g, device="cuda")].view(-1, 1)
     buf[1::5, vocab - vocab // 3:vocab] = float("-inf")
     buf[2::5, 8:vocab // 2] = float("-inf")
