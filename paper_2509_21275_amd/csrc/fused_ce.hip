@@ -35,6 +35,11 @@ constexpr int kThreads = 512;
 // 131 / 135 / -, 1024 of 151944 (311) 134 / 138 / -, 1100 of 151944 (334) 163 / 160 / -, 1024 of 262136 (537) 261 / 241 / 245, 4096 of 65528 (537) 225 / 207 / 217.
 constexpr int64_t kStreamBytes = (int64_t)256 << 20, kStreamBytesShort = (int64_t)272 << 20, kStreamStoresBytes = (int64_t)320 << 20;
 constexpr int kShortRow = 16384;
+// Above 2 GiB rows of 65544 to 131072 logits lose what they gain below, by measurement (why was not found).  Whole lines, fused_ce_kernel / long kernel kept / streamed: 16384
+// rows of 131072 (4.3 GB) 1686 / 1657 / 1740, 12000 1249 / 1217 / 1268, 8192 (2 GiB) 868 / 837 / 849; others, fused_ce_kernel / long kernel, stores streamed:
+// 16384 of 131064 1717 / 1772, 16384 of 100000 1337 / 1338.  Longer rows and shorter ones gain there, too: 14000 of 151936 1727 -> 1660, 32768 of 65536 1653 -> 1602.
+constexpr int64_t kManyBytes = (int64_t)2 << 30;
+bool whole_lines(const void* logits, int64_t row_stride) { return ((uintptr_t)logits & 127) == 0 && row_stride % 64 == 0; }
 constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
 
 __device__ __forceinline__ float wave_max(float x) {
@@ -326,11 +331,11 @@ hipError_t launch(void* logits, const int32_t* targets, float* loss, int64_t row
     return launch_as<NCH, NL, FULL, decltype(stream_c)::value>(logits, targets, loss, rows, vocab, row_stride, grad_scale, stream);
   };
   const std::integral_constant<Stream, kKeep> keep;
-  if constexpr (FULL == 0 && NCH == 32) return as(keep);  // (fewer than 512 rows)
+  if constexpr (FULL == 0 && NCH == 32) return as(keep);  // (fewer than 512 rows, or more than kManyBytes)
   else {
     const int64_t bytes = rows * (int64_t)vocab * 2;
-    const bool whole_lines = ((uintptr_t)logits & 127) == 0 && row_stride % 64 == 0;
-    if (whole_lines || (FULL == 0 && vocab <= kShortRow))
+    if (NCH == 32 && bytes > kManyBytes) return as(keep);
+    if (whole_lines(logits, row_stride) || (FULL == 0 && vocab <= kShortRow))
       return bytes > (FULL == 0 ? kStreamBytesShort : kStreamBytes) ? as(std::integral_constant<Stream, kStreamAll>{}) : as(keep);
     if (NCH <= 8 || bytes <= kStreamStoresBytes) return as(keep);
     return as(std::integral_constant<Stream, kStreamStores>{});
@@ -352,7 +357,7 @@ extern "C" int fused_ce_inplace(void* logits, const int32_t* targets, float* los
   hipError_t e;
   if (per_thread <= 8) e = launch<8>(logits, targets, loss, rows, vocab, row_stride, grad_scale, s);
   else if (per_thread <= 16) e = launch<16>(logits, targets, loss, rows, vocab, row_stride, grad_scale, s);
-  else if (per_thread <= 32 && rows < 2 * kCus) e = launch<32>(logits, targets, loss, rows, vocab, row_stride, grad_scale, s);
+  else if (per_thread <= 32 && (rows < 2 * kCus || (rows * (int64_t)vocab * 2 > kManyBytes && !whole_lines(logits, row_stride)))) e = launch<32>(logits, targets, loss, rows, vocab, row_stride, grad_scale, s);
   else if (per_thread <= 32) e = launch<32, 0, 16>(logits, targets, loss, rows, vocab, row_stride, grad_scale, s);
   else if (per_thread <= 40) e = launch<40, 0, 32>(logits, targets, loss, rows, vocab, row_stride, grad_scale, s);
   else e = launch<46, 18, 40>(logits, targets, loss, rows, vocab, row_stride, grad_scale, s);
