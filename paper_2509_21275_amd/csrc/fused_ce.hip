@@ -6,7 +6,7 @@
 // The exponential of an element is evaluated twice (for the sum and for the gradient) rather than kept: the vector work of
 // a row is several times shorter than the time HBM needs to deliver it.  Workgroups walk the rows with a grid stride.
 //
-// Two kernels.  fused_ce_kernel: rows of up to 65536 logits, and of up to 131072 where there are fewer than two per compute unit; they stay in at most 128
+// Two kernels.  fused_ce_kernel: rows of up to 65536 logits, and of up to 131072 where there are fewer than two per compute unit (or very many, kManyBytes); they stay in at most 128
 // registers per lane, maximum and sum are two passes over them, and two or more workgroups on a compute unit (or the other compute units) hide each other's vector work.
 // fused_ce_long_kernel: longer rows take more registers, the longest LDS, too, so that one workgroup has the compute unit.  It takes the sum while the row
 // arrives, against the running maximum of the thread's own chunks (moved once per group of chunks), merges the threads' (maximum, sum) pairs once per row, and as it
