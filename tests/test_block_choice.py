@@ -1,0 +1,18 @@
+"""Which blocks the estimates choose for chunks whose other blocks were measured to be faster, and what the choice costs the host."""
+import pytest
+
+import paper_2509_21275_amd as ca
+
+
+def _desc(segs, hq, hk, d):
+    return ca.make_desc(segs, hq, hk, d, sum(s[1] for s in segs), segs[-1][2] + segs[-1][3], d ** -0.5)
+
+
+def _packed(count, length):
+    return [(length * i, length, length * i, length) for i in range(count)]
+
+
+@pytest.mark.parametrize("count,length,hq,hk", [(350, 146, 28, 4), (145, 150, 28, 4), (348, 148, 8, 2)])
+def test_blocks_are_numbered_as_they_start(count, length, hq, hk):
+    """Two key blocks to a sequence, a long one and a short one, two or four key/value heads: every eighth block of a launch is as often one as the other."""
+    assert ca.chunk_attn_test_dkv_keys(_desc(_packed(count, length), hq, hk, 128)) == 128
