@@ -247,18 +247,37 @@ int64_t deal(const std::vector<int64_t>& cost, int workers, std::vector<int64_t>
 // Blocks of queue 0 among the `inner` ones that start at block b: those divisible by 8.
 int64_t in_queue(int64_t b, int inner) { return (b + inner + 7) / 8 - (b + 7) / 8; }
 
-// The costs of queue 0's blocks of a kind, none of them cut, largest first, which is the order in which blocks are numbered, too.  (Numbered by the segment table, of 350 sequences
-// of 146 tokens with four key/value heads only the first and longer key block of each would be in queue 0.)
-void queue_costs(const CutKind& kind, int step, int start, std::vector<int64_t>& out) {
+// Steps of the walks of one head, none of them cut, in the order in which a launch starts and numbers their blocks: of query-stationary ones sequence by sequence
+// (by_sequence_then_walk), of key-stationary ones the longest first.  (Numbered by the segment table, of 350 sequences of 146 tokens with four key/value heads only the
+// first and longer key block of each would be in queue 0.)
+std::vector<int> key_walks_as_started(const chunk_attn_desc* d, int tile_rows) {
+  std::vector<int> order(d->num_segments), lens;
+  std::iota(order.begin(), order.end(), 0);
+  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return d->segments[a].kv_len > d->segments[b].kv_len; });
+  for (int t : order) {
+    const chunk_attn_seg& s = d->segments[t];
+    for (int32_t i0 = (s.q_len - 1) / tile_rows * tile_rows; i0 >= 0; i0 -= tile_rows)
+      lens.push_back((int)walk_stages(s.kv_len - s.q_len + i0 + 1, std::min<int32_t>(tile_rows, s.q_len - i0)));
+  }
+  return lens;
+}
+std::vector<int> tile_walks_as_started(const chunk_attn_desc* d, int keys) {
+  const int group = d->num_q_heads / d->num_kv_heads;
   std::vector<int> lens;
-  lens.reserve(kind.walks.size());
-  for (const auto& w : kind.walks) lens.push_back(w.len);
+  for (int t = 0; t < d->num_segments; ++t) {
+    const chunk_attn_seg& s = d->segments[t];
+    const int32_t C = s.kv_len - s.q_len, n_qt = (s.q_len + 31) / 32;
+    for (int32_t j0 = 0; j0 < s.kv_len; j0 += keys) lens.push_back((n_qt - std::max<int32_t>(0, j0 - C) / 32) * group);
+  }
   std::sort(lens.begin(), lens.end(), [](int a, int b) { return a > b; });
-  out.clear();
+  return lens;
+}
+// The costs of queue 0's blocks of walks of `lens` steps, `inner` blocks each, behind those that `out` holds.
+void queue_costs(const std::vector<int>& lens, int inner, int step, int start, std::vector<int64_t>& out) {
   int64_t block = 0;
   for (int len : lens) {
-    out.insert(out.end(), in_queue(block, kind.inner), (int64_t)len * kind.steps_per_unit() * step + start);
-    block += kind.inner;
+    out.insert(out.end(), in_queue(block, inner), (int64_t)len * step + start);
+    block += inner;
   }
 }
 constexpr size_t kManyBlocks = 1024;  // of a queue: they even out by themselves, and dealing them would take the host longer than it is worth, 0.1 us each
@@ -282,13 +301,12 @@ int64_t last_end(const std::vector<int64_t>& cost, int workers, std::vector<int6
 // When the last of queue 0's blocks of both kinds ends, none of them cut, in the order in which one launch starts them: a dQ block costs `dq_stage` per stage and `dq_start`
 // more, a dK/dV block of `keys` keys `step` per step and `start` more.
 int64_t joint_end(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int dq_stage, int dq_start, int step, int start, int cus) {
-  const CutKind q = key_walks(d, tile_rows, inner), k = tile_walks(d, keys);
-  std::vector<int64_t> dq, dkv, free_at;
-  queue_costs(q, dq_stage, dq_start, dq);
-  queue_costs(k, step, start, dkv);
-  const bool dq_first = q.longest > (int64_t)k.longest * k.group;  // (bwd_layout)
-  std::vector<int64_t>&both = dq_first ? dq : dkv, &second = dq_first ? dkv : dq;
-  both.insert(both.end(), second.begin(), second.end());
+  const std::vector<int> q = key_walks_as_started(d, tile_rows), k = tile_walks_as_started(d, keys);
+  std::vector<int64_t> both, free_at;
+  const bool dq_first = *std::max_element(q.begin(), q.end()) > k[0];  // (bwd_layout)
+  if (dq_first) queue_costs(q, inner, dq_stage, dq_start, both);
+  queue_costs(k, d->num_kv_heads, step, start, both);
+  if (!dq_first) queue_costs(q, inner, dq_stage, dq_start, both);
   return last_end(both, std::max(1, cus / 8), free_at);
 }
 
@@ -645,13 +663,15 @@ void refine_bwd_split(const chunk_attn_desc* d, int tile_rows, int inner, int ke
 }
 
 // The estimate of refine_bwd_split for uncut walks, with the dK/dV blocks of either size: a step of 256 keys counts as 33/20 of one of 128 (1.61 by its cycles,
-// at a lower clock), its start as 16 steps instead of 12.  Of 388 drawn chunks of 60 us and more (backward, 128 and 96, up to 65536 keys) those that it picks take 3.9 %
-// less, all 388 together, where the best choice would save 4.1 %; two are slower by more than 2 % (3.8: 148 sequences of 129 tokens, 28/4 heads, 475 us).
+// at a lower clock), its start as 16 steps instead of 12, and 256 keys have to be ahead by a fortieth: what the estimate cannot tell apart keeps the blocks of 128.
+// Of 534 drawn chunks of 60 us and more (backward, 128 and 96, up to 65536 keys, half of them of many short sequences) it picks 252, of which one is slower by more than 1.5 % (1.7: 39
+// sequences of 248 tokens, 40/8 heads, 291 us); all 534 take 3.3 % less in the mean, with the better of the two for each 3.6.  (Without the margin, 13 are slower, by 34 % at most.)
 // 14147 queries on 14216 keys, 32/8 heads, 4718 -> 4283 us; 4977 on 38367, 64/8, 16275 -> 15116; 3193 on 8192, 32/8, 1116 -> 1044; what stays: 5251 causal tokens,
-// 32/8, 687 (blocks of 256 keys: 931), 4596, 40/8, 680 (982), 6403 on 10177, 28/4, 1884 (2032).
+// 32/8, 687 (blocks of 256 keys: 931), 4596, 40/8, 680 (982), 6403 on 10177, 28/4, 1884 (2032), 129 sequences of 222 tokens, 40/8, 834 (868).
 bool tall_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int cus) {
   constexpr int kStep = 20, kDqStage = 25, kTallStep = 33, kStart = 12 * kStep, kTallStart = 16 * kStep;
-  return joint_end(d, tile_rows, inner, kTallKeys, kDqStage, kStart, kTallStep, kTallStart, cus) < joint_end(d, tile_rows, inner, keys, kDqStage, kStart, kStep, kStart, cus);
+  const int64_t tall = joint_end(d, tile_rows, inner, kTallKeys, kDqStage, kStart, kTallStep, kTallStart, cus);
+  return 40 * tall < 39 * joint_end(d, tile_rows, inner, keys, kDqStage, kStart, kStep, kStart, cus);
 }
 
 // From two blocks of `keys` per CU and 14 steps each on average on, of 277 drawn chunks two are slower with the pipelined blocks, by 3 and 9 % (thousands of blocks of less
@@ -680,7 +700,7 @@ bool fwd_tall_pays(const chunk_attn_desc* d, int tile_rows, int inner, int cus) 
   if (count_walks(d, tile_rows).items * inner <= cus) return false;  // (all blocks run at once, and short ones end sooner)
   auto end = [&](int rows, int stage, int start) {
     std::vector<int64_t> cost, free_at;
-    queue_costs(key_walks(d, rows, inner), stage, start, cost);
+    queue_costs(key_walks_as_started(d, rows), inner, stage, start, cost);
     return last_end(cost, std::max(1, cus / 8), free_at);
   };
   return 100 * end(2 * tile_rows, 26, 440) < 97 * end(tile_rows, 19, 240);

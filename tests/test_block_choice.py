@@ -16,3 +16,10 @@ def _packed(count, length):
 def test_blocks_are_numbered_as_they_start(count, length, hq, hk):
     """Two key blocks to a sequence, a long one and a short one, two or four key/value heads: every eighth block of a launch is as often one as the other."""
     assert ca.chunk_attn_test_dkv_keys(_desc(_packed(count, length), hq, hk, 128)) == 128
+
+
+@pytest.mark.parametrize("count,length,hq,hk,d", [
+    (94, 178, 32, 8, 128), (129, 222, 40, 8, 128), (126, 213, 32, 8, 128),    # 256 keys end as late as 128 by the estimate
+    (10, 560, 32, 8, 128), (125, 255, 40, 8, 96)])
+def test_equal_estimates_keep_the_smaller_blocks(count, length, hq, hk, d):
+    assert ca.chunk_attn_test_dkv_keys(_desc(_packed(count, length), hq, hk, d)) == 128
