@@ -692,18 +692,22 @@ bool wide_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int
   return pipelined < 0.96 * other;
 }
 
-// Blocks of the two kinds dealt as in tall_pays, in 1/20 us: 0.95 us per stage of 32 keys and 12 us more for 32 rows per wave, 1.3 and 22 for 64; off by 9 and 11 %
-// over those of 700 drawn chunks (up to 65536 keys, 8 - 64 query heads) that take 15 us or more.  Of the 700 it picks 205, of which three are slower by more than 2 %
-// (9 % at most: 209 sequences of 203 tokens, 8/2 heads, 183 us); all 700 take 4.6 % less (mean logarithm), with the better of the two for each 4.9.  32 / 64 rows per
-// wave: 8192 queries on 32768 keys, 32/8 heads, 7329 / 5658 us, 4096 causal tokens 302 / 242; what stays: 2668 causal tokens, 8/8, 85 / 115.
+// Blocks of the two kinds dealt as in tall_pays, in 1/20 us: 0.95 us per stage of 32 keys and 12 us more for 32 rows per wave, 1.3 and 22 for 64; off by 5 and 9 %
+// over 600 drawn chunks (up to 65536 keys, 8 - 64 query heads, half of them of many short sequences).  64 rows have to be ahead by a tenth in the work of all blocks, which is
+// what short walks are misjudged by, and by a twentieth in the end of the last one.  Of the 600 it picks 260, none slower by more than 1.5 %; all 600 take 5.8 % less in
+// the mean, with the better of the two for each 6.2.  (By the end alone and 3 %: 18 are slower, by 9 % at most.)  32 / 64 rows per wave: 8192 queries on 32768 keys, 32/8 heads,
+// 7329 / 5658 us, 4096 causal tokens 302 / 242; what stays: 2668 causal tokens, 8/8, 85 / 115, 62 sequences of 241 tokens, 28/4, 235 / 250, eight of 1520, 8/8, 126 / 134.
 bool fwd_tall_pays(const chunk_attn_desc* d, int tile_rows, int inner, int cus) {
-  if (count_walks(d, tile_rows).items * inner <= cus) return false;  // (all blocks run at once, and short ones end sooner)
+  constexpr int kStage = 19, kStart = 240, kTallStage = 26, kTallStart = 440;
+  const Walks w = count_walks(d, tile_rows), tall = count_walks(d, 2 * tile_rows);
+  if (w.items * inner <= cus) return false;  // (all blocks run at once, and short ones end sooner)
+  if (10 * (tall.stages * kTallStage + tall.items * kTallStart) >= 9 * (w.stages * kStage + w.items * kStart)) return false;
   auto end = [&](int rows, int stage, int start) {
     std::vector<int64_t> cost, free_at;
     queue_costs(key_walks_as_started(d, rows), inner, stage, start, cost);
     return last_end(cost, std::max(1, cus / 8), free_at);
   };
-  return 100 * end(2 * tile_rows, 26, 440) < 97 * end(tile_rows, 19, 240);
+  return 20 * end(2 * tile_rows, kTallStage, kTallStart) < 19 * end(tile_rows, kStage, kStart);
 }
 
 // Times (us) as in wide_pays, of chunks of head_dim 64 whose dQ and dK/dV are pipelined as launches of their own, or in one with dK/dV blocks of kTallKeys keys.  Off by 8 %

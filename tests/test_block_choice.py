@@ -23,3 +23,10 @@ def test_blocks_are_numbered_as_they_start(count, length, hq, hk):
     (10, 560, 32, 8, 128), (125, 255, 40, 8, 96)])
 def test_equal_estimates_keep_the_smaller_blocks(count, length, hq, hk, d):
     assert ca.chunk_attn_test_dkv_keys(_desc(_packed(count, length), hq, hk, d)) == 128
+
+
+@pytest.mark.parametrize("count,length,hq,hk", [
+    (62, 241, 28, 4), (228, 256, 28, 4), (250, 235, 8, 8), (161, 101, 32, 8), (75, 124, 64, 8),  # short walks
+    (8, 1520, 8, 8), (9, 1428, 8, 2)])                                                            # the last sequences' long blocks start late
+def test_forward_of_256_keeps_32_rows(count, length, hq, hk):
+    assert ca.chunk_attn_test_fwd_rows(_desc(_packed(count, length), hq, hk, 256)) == 32
