@@ -674,22 +674,24 @@ bool tall_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int
   return 40 * tall < 39 * joint_end(d, tile_rows, inner, keys, kDqStage, kStart, kStep, kStart, cus);
 }
 
-// From two blocks of `keys` per CU and 14 steps each on average on, of 277 drawn chunks two are slower with the pipelined blocks, by 3 and 9 % (thousands of blocks of less
-// than 100 keys).  Below that chunks whose dQ walks are of 8 stages or more on average are decided by estimates in us: the pipelined blocks of both kinds dealt as in tall_pays; the unpipelined ones, whose walks may be cut
+// Pipelined from two blocks of `keys` per CU and 14 steps each on average on, unless most of the larger blocks' second halves are empty (sequences of up to 64 keys: 331 of
+// 51 tokens, 28/4 heads, unpipelined / pipelined 649 / 801 us; 278 of 70 934 / 784).  Below that chunks whose dQ walks are of 8 stages or more on average are decided by
+// estimates in us: the pipelined blocks of both kinds dealt as in tall_pays; the unpipelined ones, whose walks may be cut
 // and so know no longest one, by their number and steps.  Least squares in the logarithm over 556 drawn chunks of 60 us and more (up to 65536 keys, 8 - 64
-// query heads), each run both ways; off by 11 and 8 % (root mean square).  All 556 together take 18.4 % less than with the unpipelined kernels, with the better
-// of the two for each 18.7; eight are slower by more than 2 %, by 11 % at most.  Unpipelined / pipelined: 2668 causal tokens, 8/8 heads, 184 / 148 us; 1428 queries on
+// query heads), each run both ways; off by 11 and 8 % (root mean square), so that the pipelined ones have to be ahead by 9.  Of 900 drawn chunks, half of them of many short
+// sequences, it picks 603, of which two are slower by more than 1.5 % than what ran without these blocks (3.0 at most: 2112 causal tokens, 8/8, 106 us); all 900 take 10.8 % less in the mean, with
+// the better of the two for each 13.0.  Unpipelined / pipelined: 2668 causal tokens, 8/8 heads, 184 / 148 us; 1428 queries on
 // 3445 keys, 32/8, 578 / 407; 10770 causal, 28/4, 7202 / 4677; 7307, 32/8, 3571 / 2456; what stays: 4335, 8/2, 386 / 655; 899, 64/8, 172 / 298.
 bool wide_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int cus) {
   const Walks w = count_dkv_walks(d, keys);
-  if (w.items * d->num_kv_heads >= 2 * cus && w.stages >= 14 * w.items) return true;
+  if (w.items * d->num_kv_heads >= 2 * cus && w.stages >= 14 * w.items && 10 * count_tiles(d, true, kWideKeys) <= 7 * w.items) return true;
   const Walks wq = count_walks(d, tile_rows);
   if (wq.stages < 8 * wq.items) return false;
   constexpr int kUs = 20, kDqStage = 24, kDqStart = 16 * kUs, kStep = 29, kStart = 20 * kUs;
   const double pipelined = 1.57 + 0.984 / kUs * joint_end(d, tile_rows, inner, kWideKeys, kDqStage, kDqStart, kStep, kStart, cus);
   const double per_cu = 1.0 / cus, dq_all = std::max((double)wq.stages * inner * per_cu, (double)wq.longest);
   const double other = 23.1 + 0.42 * dq_all + (21.6 * wq.items * inner + (1.911 * w.stages + 4.71 * w.items) * d->num_kv_heads) * per_cu;
-  return pipelined < 0.96 * other;
+  return pipelined < 0.91 * other;
 }
 
 // Blocks of the two kinds dealt as in tall_pays, in 1/20 us: 0.95 us per stage of 32 keys and 12 us more for 32 rows per wave, 1.3 and 22 for 64; off by 5 and 9 %

@@ -30,3 +30,10 @@ def test_equal_estimates_keep_the_smaller_blocks(count, length, hq, hk, d):
     (8, 1520, 8, 8), (9, 1428, 8, 2)])                                                            # the last sequences' long blocks start late
 def test_forward_of_256_keeps_32_rows(count, length, hq, hk):
     assert ca.chunk_attn_test_fwd_rows(_desc(_packed(count, length), hq, hk, 256)) == 32
+
+
+@pytest.mark.parametrize("segs,hq,hk,keys", [
+    (_packed(166, 57), 28, 4, 64), (_packed(331, 51), 28, 4, 64), (_packed(278, 70), 28, 4, 128),   # a block of 128 keys would be half empty, or not
+    ([(0, 371, 0, 2337)] + [(371 + 172 * i, 172, 2337 + 172 * i, 172) for i in range(19)], 8, 2, 64)])  # ahead by less than the estimates are off by
+def test_blocks_of_256_that_stay(segs, hq, hk, keys):
+    assert ca.chunk_attn_test_dkv_keys(_desc(segs, hq, hk, 256)) == keys
