@@ -662,54 +662,66 @@ void refine_bwd_split(const chunk_attn_desc* d, int tile_rows, int inner, int ke
   *dkv = best[1];
 }
 
-// The estimate of refine_bwd_split for uncut walks, with the dK/dV blocks of either size: a step of 256 keys counts as 33/20 of one of 128 (1.61 by its cycles,
-// at a lower clock), its start as 16 steps instead of 12, and 256 keys have to be ahead by a fortieth: what the estimate cannot tell apart keeps the blocks of 128.
-// Of 534 drawn chunks of 60 us and more (backward, 128 and 96, up to 65536 keys, half of them of many short sequences) it picks 252, of which one is slower by more than 1.5 % (1.7: 39
-// sequences of 248 tokens, 40/8 heads, 291 us); all 534 take 3.3 % less in the mean, with the better of the two for each 3.6.  (Without the margin, 13 are slower, by 34 % at most.)
-// 14147 queries on 14216 keys, 32/8 heads, 4718 -> 4283 us; 4977 on 38367, 64/8, 16275 -> 15116; 3193 on 8192, 32/8, 1116 -> 1044; what stays: 5251 causal tokens,
-// 32/8, 687 (blocks of 256 keys: 931), 4596, 40/8, 680 (982), 6403 on 10177, 28/4, 1884 (2032), 129 sequences of 222 tokens, 40/8, 834 (868).
+// The estimate of refine_bwd_split for uncut walks, with the dK/dV blocks of either size: a step of 256 keys counts as 8/5 of one of 128 (1.61 by its cycles), the start and end of
+// either as ten steps of 128 and of a dQ block as twelve, and 256 keys have to be ahead by a twentieth: what the estimate cannot tell apart keeps the blocks of 128.
+// Of 924 drawn chunks of 60 us and more (backward, 128 and 96, up to 65536 keys, 1 - 8 query heads to a key/value head, two thirds of them of many short sequences) it picks 564, of
+// which five are slower by more than 1.5 % (2.7 at most: 18 sequences of 202 tokens, 32/8 heads, 104 us); all 924 take 4.4 % less in the mean, with the better of the two for each
+// 4.6.  (Without the margin, and 16 steps for the start of 256 keys, 18 are slower, by 34 % at most.)
+// 14147 queries on 14216 keys, 32/8 heads, 4718 -> 4283 us; 4977 on 38367, 64/8, 16275 -> 15116; 3193 on 8192, 32/8, 1116 -> 1044; eight sequences of 300 tokens, 64/64, 216 -> 204;
+// what stays: 5251 causal tokens, 32/8, 687 (blocks of 256 keys: 931), 4596, 40/8, 680 (982), 6403 on 10177, 28/4, 1884 (2032), 129 sequences of 222 tokens, 40/8, 834 (868).
 bool tall_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int cus) {
-  constexpr int kStep = 20, kDqStage = 25, kTallStep = 33, kStart = 12 * kStep, kTallStart = 16 * kStep;
-  const int64_t tall = joint_end(d, tile_rows, inner, kTallKeys, kDqStage, kStart, kTallStep, kTallStart, cus);
-  return 40 * tall < 39 * joint_end(d, tile_rows, inner, keys, kDqStage, kStart, kStep, kStart, cus);
+  constexpr int kStep = 20, kDqStage = 25, kTallStep = 32, kDqStart = 12 * kStep, kStart = 10 * kStep;
+  const int64_t tall = joint_end(d, tile_rows, inner, kTallKeys, kDqStage, kDqStart, kTallStep, kStart, cus);
+  return 20 * tall < 19 * joint_end(d, tile_rows, inner, keys, kDqStage, kDqStart, kStep, kStart, cus);
 }
 
 // Pipelined from two blocks of `keys` per CU and 14 steps each on average on, unless most of the larger blocks' second halves are empty (sequences of up to 64 keys: 331 of
-// 51 tokens, 28/4 heads, unpipelined / pipelined 649 / 801 us; 278 of 70 934 / 784).  Below that chunks whose dQ walks are of 8 stages or more on average are decided by
+// 51 tokens, 28/4 heads, unpipelined / pipelined 649 / 801 us; 278 of 70 934 / 784).  Below that chunks whose dQ walks are of 5 stages or more on average are decided by
 // estimates in us: the pipelined blocks of both kinds dealt as in tall_pays; the unpipelined ones, whose walks may be cut
-// and so know no longest one, by their number and steps.  Least squares in the logarithm over 556 drawn chunks of 60 us and more (up to 65536 keys, 8 - 64
-// query heads), each run both ways; off by 11 and 8 % (root mean square), so that the pipelined ones have to be ahead by 9.  Of 900 drawn chunks, half of them of many short
-// sequences, it picks 603, of which two are slower by more than 1.5 % than what ran without these blocks (3.0 at most: 2112 causal tokens, 8/8, 106 us); all 900 take 10.8 % less in the mean, with
-// the better of the two for each 13.0.  Unpipelined / pipelined: 2668 causal tokens, 8/8 heads, 184 / 148 us; 1428 queries on
+// and so know no longest one, by their number and steps.  Least squares in the relative error over 1140 drawn chunks of 60 us and more (up to 65536 keys, 1 - 8 query heads to a
+// key/value head, two thirds of them of many short sequences), each run both ways; off by 7 and 10 % (root mean square), so that the pipelined ones have to be ahead by 5.  Of the 1140 it
+// picks 830, of which two are slower by more than 1.5 % than without these blocks (3.0 at most: 2112 causal tokens, 8/8, 106 us); all take 12.1 % less in the mean, with
+// the better of the two for each 13.3.  Unpipelined / pipelined: 2668 causal tokens, 8/8 heads, 184 / 148 us; 1428 queries on
 // 3445 keys, 32/8, 578 / 407; 10770 causal, 28/4, 7202 / 4677; 7307, 32/8, 3571 / 2456; what stays: 4335, 8/2, 386 / 655; 899, 64/8, 172 / 298.
 bool wide_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int cus) {
   const Walks w = count_dkv_walks(d, keys);
   if (w.items * d->num_kv_heads >= 2 * cus && w.stages >= 14 * w.items && 10 * count_tiles(d, true, kWideKeys) <= 7 * w.items) return true;
   const Walks wq = count_walks(d, tile_rows);
-  if (wq.stages < 8 * wq.items) return false;
-  constexpr int kUs = 20, kDqStage = 24, kDqStart = 16 * kUs, kStep = 29, kStart = 20 * kUs;
-  const double pipelined = 1.57 + 0.984 / kUs * joint_end(d, tile_rows, inner, kWideKeys, kDqStage, kDqStart, kStep, kStart, cus);
+  if (wq.stages < 5 * wq.items) return false;
+  constexpr int kUs = 20, kDqStage = 24, kDqStart = 18 * kUs, kStep = 26, kStart = 15 * kUs;
+  const double pipelined = 4.7 + 1.035 / kUs * joint_end(d, tile_rows, inner, kWideKeys, kDqStage, kDqStart, kStep, kStart, cus);
   const double per_cu = 1.0 / cus, dq_all = std::max((double)wq.stages * inner * per_cu, (double)wq.longest);
-  const double other = 23.1 + 0.42 * dq_all + (21.6 * wq.items * inner + (1.911 * w.stages + 4.71 * w.items) * d->num_kv_heads) * per_cu;
-  return pipelined < 0.91 * other;
+  const double other = 20.7 + 0.138 * dq_all + (16.5 * wq.items * inner + (2.09 * w.stages + 10.0 * w.items) * d->num_kv_heads) * per_cu;
+  return pipelined < 0.95 * other;
 }
 
-// Blocks of the two kinds dealt as in tall_pays, in 1/20 us: 0.95 us per stage of 32 keys and 12 us more for 32 rows per wave, 1.3 and 22 for 64; off by 5 and 9 %
-// over 600 drawn chunks (up to 65536 keys, 8 - 64 query heads, half of them of many short sequences).  64 rows have to be ahead by a tenth in the work of all blocks, which is
-// what short walks are misjudged by, and by a twentieth in the end of the last one.  Of the 600 it picks 260, none slower by more than 1.5 %; all 600 take 5.8 % less in
-// the mean, with the better of the two for each 6.2.  (By the end alone and 3 %: 18 are slower, by 9 % at most.)  32 / 64 rows per wave: 8192 queries on 32768 keys, 32/8 heads,
-// 7329 / 5658 us, 4096 causal tokens 302 / 242; what stays: 2668 causal tokens, 8/8, 85 / 115, 62 sequences of 241 tokens, 28/4, 235 / 250, eight of 1520, 8/8, 126 / 134.
+// Blocks dealt as in tall_pays, in a fifth of a stage of 32 rows per wave, whose start and end take as long as seven of them; a stage of 64 rows counts as 7/5, its start and end as
+// 15 stages.  Either kernel runs its stages in pairs, with one more for the last product.  Where a workgroup takes one head (an odd number of heads to a key/value head: 256 rows to a block of 64 per
+// wave), some wave masks keys in most stages of a short walk, and 64 rows have to take a twenty-fifth less work and end sooner; elsewhere no more work, and a twenty-fifth
+// later by the estimate is soon enough from two blocks of 64 rows per compute unit on.  With a few more blocks than compute units the end hangs on their order: ahead by a twentieth.  Of 840 drawn chunks (up to 65536 keys, 1 - 8 query
+// heads to a key/value head, two thirds of them of many short sequences) it picks 392, of which one is slower by more than 1.5 % (1.9: eleven sequences
+// of 333 tokens, 32/16 heads, 80 us); all 840 take 5.3 % less in the mean, with the better of the two for each 5.5.  (Without the pairs, and by the end alone: 31 are slower, by 9 % at most.)  32 / 64 rows
+// per wave: 8192 queries on 32768 keys, 32/8 heads, 7329 / 5658 us, 4096 causal tokens 302 / 242; what stays: 2668 causal tokens, 8/8, 85 / 115, 62 sequences of 241 tokens, 28/4, 235 /
+// 250, eight of 1520, 8/8, 126 / 134, eleven of 701, 8/8, 64 / 71.
 bool fwd_tall_pays(const chunk_attn_desc* d, int tile_rows, int inner, int cus) {
-  constexpr int kStage = 19, kStart = 240, kTallStage = 26, kTallStart = 440;
-  const Walks w = count_walks(d, tile_rows), tall = count_walks(d, 2 * tile_rows);
-  if (w.items * inner <= cus) return false;  // (all blocks run at once, and short ones end sooner)
-  if (10 * (tall.stages * kTallStage + tall.items * kTallStart) >= 9 * (w.stages * kStage + w.items * kStart)) return false;
-  auto end = [&](int rows, int stage, int start) {
+  if (count_walks(d, tile_rows).items * inner <= cus) return false;  // (all blocks run at once, and short ones end sooner)
+  struct Times { int64_t work = 0, end = 0; };
+  auto times = [&](int rows, int stage, int start) {
+    std::vector<int> lens = key_walks_as_started(d, rows);
+    Times t;
+    for (int& len : lens) {
+      len = (len & ~1) + 2;
+      t.work += (int64_t)len * stage + start;
+    }
     std::vector<int64_t> cost, free_at;
-    queue_costs(key_walks_as_started(d, rows), inner, stage, start, cost);
-    return last_end(cost, std::max(1, cus / 8), free_at);
+    queue_costs(lens, inner, stage, start, cost);
+    t.end = last_end(cost, std::max(1, cus / 8), free_at);
+    return t;
   };
-  return 20 * end(2 * tile_rows, kTallStage, kTallStart) < 19 * end(tile_rows, kStage, kStart);
+  const Times rows32 = times(tile_rows, 5, 35), rows64 = times(2 * tile_rows, 7, 75);
+  const int64_t blocks = count_tiles(d, false, 2 * tile_rows) * inner;
+  const bool one_head = tile_rows >= 128, few = blocks > cus && 4 * blocks <= 5 * cus;
+  return 100 * rows64.work < (one_head ? 96 : 100) * rows32.work && 100 * rows64.end < (few ? 95 : one_head || blocks <= 2 * cus ? 100 : 104) * rows32.end;
 }
 
 // Times (us) as in wide_pays, of chunks of head_dim 64 whose dQ and dK/dV are pipelined as launches of their own, or in one with dK/dV blocks of kTallKeys keys.  Off by 8 %

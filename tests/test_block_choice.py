@@ -25,9 +25,15 @@ def test_equal_estimates_keep_the_smaller_blocks(count, length, hq, hk, d):
     assert ca.chunk_attn_test_dkv_keys(_desc(_packed(count, length), hq, hk, d)) == 128
 
 
+@pytest.mark.parametrize("count,length,heads,d", [(8, 300, 64, 128), (8, 300, 64, 96), (32, 300, 16, 128), (8, 360, 64, 128), (40, 300, 64, 128)])
+def test_a_query_head_to_a_key_value_head(count, length, heads, d):
+    """Chunks that blocks of 256 keys make faster by 4 to 8 %."""
+    assert ca.chunk_attn_test_dkv_keys(_desc(_packed(count, length), heads, heads, d)) == 256
+
+
 @pytest.mark.parametrize("count,length,hq,hk", [
     (62, 241, 28, 4), (228, 256, 28, 4), (250, 235, 8, 8), (161, 101, 32, 8), (75, 124, 64, 8),  # short walks
-    (8, 1520, 8, 8), (9, 1428, 8, 2)])                                                            # the last sequences' long blocks start late
+    (8, 1520, 8, 8), (9, 1428, 8, 2), (11, 701, 8, 8)])                                                            # the last sequences' long blocks start late
 def test_forward_of_256_keeps_32_rows(count, length, hq, hk):
     assert ca.chunk_attn_test_fwd_rows(_desc(_packed(count, length), hq, hk, 256)) == 32
 
