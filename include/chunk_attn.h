@@ -256,6 +256,8 @@ int chunk_attn_test_bwd_status_offset(const chunk_attn_desc* desc, size_t* offse
 int chunk_attn_test_routes(const chunk_attn_desc* desc, int32_t* routes);
 /** Test hook: key rows per dK/dV block of the backward that chunk_attn_test_routes describes (32, 64, 128 or 256). */
 int chunk_attn_test_dkv_keys(const chunk_attn_desc* desc, int32_t* keys);
+/** Test hook (host only): 1 where long dK/dV walks of that backward start in groups, else 0. */
+int chunk_attn_test_dkv_in_step(const chunk_attn_desc* desc, int32_t* in_step);
 /** Test hook (host only): query rows per wave of the forward (32 or 64). */
 int chunk_attn_test_fwd_rows(const chunk_attn_desc* desc, int32_t* rows);
 /* Test hook (host only): query heads per workgroup of the small chunks' forward (1, 2 or 4), 0 where another kernel runs. */

@@ -281,6 +281,15 @@ def chunk_attn_test_dkv_keys(desc) -> int:
     return out.value
 
 
+def chunk_attn_test_dkv_in_step(desc) -> bool:
+    """Test hook: whether long dK/dV walks of the backward start in groups (host only)."""
+    out = ctypes.c_int32(0)
+    rc = _lib.chunk_attn_test_dkv_in_step(ctypes.byref(desc), ctypes.byref(out))
+    if rc != 0:
+        raise ChunkAttnError(rc)
+    return bool(out.value)
+
+
 def chunk_attn_test_fwd_rows(desc) -> int:
     """Test hook: query rows per wave of the forward that the library runs for a chunk (host only)."""
     out = ctypes.c_int32(0)

@@ -575,6 +575,17 @@ int chunk_attn_test_dkv_keys(const chunk_attn_desc* desc, int32_t* keys) {
   return CHUNK_ATTN_OK;
 }
 
+int chunk_attn_test_dkv_in_step(const chunk_attn_desc* desc, int32_t* in_step) {
+  const int rc = validate(desc);
+  if (rc != CHUNK_ATTN_OK) return rc;
+  if (!in_step) return CHUNK_ATTN_INVALID_ARG;
+  const chunk_attn_desc w = widened(desc);
+  BwdPlan P;
+  bwd_layout(&w, P, true, kCutFine, bwd_mode() == 0 ? desc->head_dim : 0);
+  *in_step = P.dkv_in_step ? 1 : 0;
+  return CHUNK_ATTN_OK;
+}
+
 int chunk_attn_test_fwd_rows(const chunk_attn_desc* desc, int32_t* rows) {
   const int rc = validate(desc);
   if (rc != CHUNK_ATTN_OK) return rc;

@@ -846,7 +846,8 @@ __device__ __forceinline__ void dkv_pipe_blocks(const ArgsPtr<DkvParams> args, c
   // shares its rows in the L2: last of eight slices of 16384 queries, 64/8 heads, 84 - 126 -> 53 - 97 GB (two runs each), the eight and a packed chunk together
   // 50 - 55 -> 45 - 48 per launch; that slice, forward and backward, 232.3 -> 231.5 ms.  With shorter walks workgroups only stand idle: 873 queries on 5197 keys, 32/8, whole
   // walks, backward 323 us with the waits, 238 without; 405 on 17711, 64/8, 829 / 740; walks of 1024 steps +- 0.1 %.  And where dQ blocks
-  // come first workgroups reach these one by one.
+  // come first workgroups reach these one by one.  (Head_dim 64, whose steps are half as long, does not wait: of six
+  // chunks with such walks none was faster with the waits: 12719 queries on 13105 keys, 64/8 heads, 4441 with, 4341 without, 21790 on 65580, 32/8, 29391 / 29148, 19169 on 19834, 64/8, 9798 / 9797.)
   int* const next_block = (int*)((__bf16*)smem + LDS_ELEMS);
   const int xcd = xcd_of_this_wave();
   clock_log_stamp(fresh(args).clock_log, 0);
@@ -1421,7 +1422,7 @@ __device__ __forceinline__ void dkv_tall_blocks(const ArgsPtr<DkvParams> args, c
   clock_log_stamp(fresh(args).clock_log, 0);
   int blk = mine;
   auto start_in_step = [&](const DkvParams& p, int b) __attribute__((always_inline)) {
-    if (p.side_by_side == 0 || b < 0) return;
+    if (D == 64 || p.side_by_side == 0 || b < 0) return;
     const DkvItem it = load_uniform(p.items, b / p.num_kv_heads);
     if (it.j0 + it.kv_rows <= it.ctx && (int64_t)it.n_qt * p.group >= kStepsInStep) wait_for_earlier_groups(p.ended, b, p.side_by_side);
   };
@@ -1777,7 +1778,7 @@ __device__ __forceinline__ void dkv_tall_blocks(const ArgsPtr<DkvParams> args, c
   int nb = 0;
   if (wave == 0) {
     const DkvParams p = fresh(args);
-    if (p.side_by_side != 0 && lane_id() == 0) __hip_atomic_fetch_add(p.ended + (blk & 7), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (D != 64 && p.side_by_side != 0 && lane_id() == 0) __hip_atomic_fetch_add(p.ended + (blk & 7), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     nb = block_claim_finish(p.taken, p.num_blocks, xcd, pending_claim);
     start_in_step(p, nb);
   }
@@ -3820,7 +3821,7 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, Cut cut, i
     for (const DqItem& it : P.dq_items) dq_longest = std::max(dq_longest, (std::min(it.n0 + it.q_rows - 1, it.keys) + kStageKeys - 1) / kStageKeys);
     for (const DkvItem& it : P.dkv_items) dkv_longest = std::max(dkv_longest, (it.n_qt - it.qt_first) * group);
     P.dq_first = dq_longest > dkv_longest || (d->head_dim == 64 && dq_longest == dkv_longest);  // (64: short_joins)
-    P.dkv_in_step = !P.dq_first && dkv_longest >= kStepsInStep;
+    P.dkv_in_step = pipe && !P.dq_first && dkv_longest >= kStepsInStep;
   }
   // the layout does not depend on which backward runs: item and piece counts follow from the segment table
   for (int t = 0; t < d->num_segments; ++t) {

@@ -137,7 +137,7 @@ struct BwdPlan {
   int dq_waves = 0;                        // 32-row units of a dQ workgroup
   bool dq_first = false;                   // both kinds in one launch: the dQ blocks start before the dK/dV blocks
   bool dkv_tall = false;                   // head_dim 64, 96 and 128: the dK/dV blocks are those of dkv_tall_blocks
-  bool dkv_in_step = false;                // head_dim 96 and 128: long dK/dV walks start in groups (dkv_pipe_blocks)
+  bool dkv_in_step = false;                // head_dim 96 and 128: long dK/dV walks start in groups (dkv_pipe_blocks, dkv_tall_blocks)
   int share_waves = 0;                     // > 0: launch_bwd_share runs instead, with so many waves per workgroup
   bool in_turn = false;                    // head_dim 96 and 128: a launch per kind, whose partial results take the same place
   // one-pass backward (head_dim 128): its items and workgroup order travel at the end of the blob; then the per-wave

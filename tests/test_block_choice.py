@@ -43,3 +43,9 @@ def test_forward_of_256_keeps_32_rows(count, length, hq, hk):
     ([(0, 371, 0, 2337)] + [(371 + 172 * i, 172, 2337 + 172 * i, 172) for i in range(19)], 8, 2, 64)])  # ahead by less than the estimates are off by
 def test_blocks_of_256_that_stay(segs, hq, hk, keys):
     assert ca.chunk_attn_test_dkv_keys(_desc(segs, hq, hk, 256)) == keys
+
+
+@pytest.mark.parametrize("d,keys,in_step", [(128, 256, True), (96, 256, True), (64, 256, False)])
+def test_long_walks_that_start_in_groups(d, keys, in_step):
+    desc = _desc([(0, 8192, 0, 16384)], 64, 8, d)
+    assert ca.chunk_attn_test_dkv_keys(desc) == keys and ca.chunk_attn_test_dkv_in_step(desc) == in_step
