@@ -3777,8 +3777,7 @@ void bwd_layout(const chunk_attn_desc* d, BwdPlan& P, bool with_plan, Cut cut, i
   if (d->head_dim == 64) P.dkv_pipe = dkv_pipe_pays(d, count_dkv_walks(d, dkv_keys(64)));
   if (d->head_dim == 256) P.dkv_pipe = wide_pays(d, dq_rows, d->num_kv_heads * (group / heads_per_wg(group, P.dq_waves)), dkv_keys(256), kCus);
   if (d->head_dim == 256) P.dq_wide = P.dkv_pipe || dq_wide_pays(count_walks(d, dq_rows));
-  if (d->head_dim == 64 && P.dq_pipe && P.dkv_pipe)
-    P.dkv_tall = narrow_tall_pays(d, dq_rows, d->num_kv_heads * (group / heads_per_wg(group, P.dq_waves)), dkv_keys(64), kCus);
+  if (d->head_dim == 64 && P.dq_pipe && P.dkv_pipe) P.dkv_tall = narrow_tall_pays(group, count_dkv_walks(d, dkv_keys(64)));
   P.q_tiles = count_tiles(d, false, 64);
   P.qt32_tiles = count_tiles(d, false, 32);
   // head_dim 128: room for dQ tiles in float32, for the one-pass backward or for the partial results of cut dQ walks

@@ -724,17 +724,6 @@ bool fwd_tall_pays(const chunk_attn_desc* d, int tile_rows, int inner, int cus) 
   return 100 * rows64.work < (one_head ? 96 : 100) * rows32.work && 100 * rows64.end < (few ? 95 : one_head || blocks <= 2 * cus ? 100 : 104) * rows32.end;
 }
 
-// Times (us) as in wide_pays, of chunks of head_dim 64 whose dQ and dK/dV are pipelined as launches of their own, or in one with dK/dV blocks of kTallKeys keys.  Off by 8 %
-// (445 drawn chunks of 60 us and more) and 5 % (54 of these kinds).  Of the 54 it picks 50, of which none is slower; all 54 take 7.7 % less, with the better of the two for each
-// 7.8.  8192 queries on 16384 keys, 32/8 heads, backward, 2998 -> 2718 us; 8192 causal tokens 1129 -> 1005.
-bool narrow_tall_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int cus) {
-  const Walks w = count_dkv_walks(d, keys), wq = count_walks(d, tile_rows);
-  const double per_cu = 1.0 / cus;
-  const double two = 104.7 + (0.382 * wq.stages + 15.9 * wq.items) * inner * per_cu + 0.022 * wq.longest + (0.639 * w.stages + 4.31 * w.items) * d->num_kv_heads * per_cu + 0.16 * w.longest;
-  constexpr int kUs = 20, kDqStage = 16, kDqStart = 16 * kUs, kStep = 22, kStart = 18 * kUs;
-  return 0.839 / kUs * joint_end(d, tile_rows, inner, kTallKeys, kDqStage, kDqStart, kStep, kStart, cus) < two;
-}
-
 std::vector<DkvItem> cut_items(const std::vector<DkvItem>& wholes, int target, std::vector<DkvItem>* cut) {
   std::vector<DkvItem> items;
   int32_t part = 0;

@@ -184,8 +184,11 @@ bool tall_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int
 inline bool dq_wide_pays(const Walks& w) { return 2 * w.stages >= 11 * w.items; }
 // Whether the forward of head_dim 256 ends sooner with blocks of twice `tile_rows` query rows, 64 per wave (fwd_tall_kernel), than of `tile_rows` (fwd_wide_kernel).
 bool fwd_tall_pays(const chunk_attn_desc* d, int tile_rows, int inner, int cus);
-// Whether a chunk of head_dim 64 whose dQ and dK/dV are both pipelined ends sooner in one launch, with dK/dV blocks of kTallKeys keys, than in two, of `keys`.
-bool narrow_tall_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int cus);
+// Whether a chunk of head_dim 64 whose dQ and dK/dV are both pipelined runs them in one launch, with dK/dV blocks of kTallKeys keys, rather than in two: where several query heads
+// share a key/value head, from 8 steps per walk (`w`, of blocks of 128 keys) on.  One launch to two, geometric mean (chunks): one query head 1.01 (43; 0.94 - 1.05), two 0.97 (260; 1.02 at most),
+// three 0.95 (50), four and more 0.93 (141; 1.01 at most); walks of 9 to 30 steps 0.92 - 0.99 (26).  Two launches -> one: 8192 queries on 16384 keys, 32/8 heads, backward, 2998 -> 2718
+// us, 8192 causal tokens 1129 -> 1005; what stays: 16317 queries on 16594 keys, 16/16, 1749 (one launch: 1822).
+inline bool narrow_tall_pays(int group, const Walks& w) { return group > 1 && w.stages >= 8 * w.items; }
 // Whether head_dim 256 runs its pipelined dK/dV blocks, of kWideKeys keys, rather than those of bwd_dkv_kernel, of `keys` (by estimates of both).
 constexpr int kWideKeys = 128;
 bool wide_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int cus);

@@ -49,3 +49,10 @@ def test_blocks_of_256_that_stay(segs, hq, hk, keys):
 def test_long_walks_that_start_in_groups(d, keys, in_step):
     desc = _desc([(0, 8192, 0, 16384)], 64, 8, d)
     assert ca.chunk_attn_test_dkv_keys(desc) == keys and ca.chunk_attn_test_dkv_in_step(desc) == in_step
+
+
+@pytest.mark.parametrize("segs,hq,hk,keys", [
+    ([(0, 16317, 0, 16594)], 16, 16, 128), ([(0, 12000, 0, 12000)], 32, 32, 128),                       # a query head to a key/value head: two launches
+    ([(0, 12000, 0, 12000)], 32, 16, 256), ([(0, 223, 0, 5186)], 512, 256, 256), ([(0, 451, 0, 9405)], 512, 128, 256)])  # several: one, walks of few steps, too
+def test_one_launch_of_64(segs, hq, hk, keys):
+    assert ca.chunk_attn_test_dkv_keys(_desc(segs, hq, hk, 64)) == keys
