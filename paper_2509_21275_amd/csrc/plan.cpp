@@ -121,17 +121,17 @@ std::vector<DqItem> plan_dq(const chunk_attn_desc* d, int tile_rows) {
   return items;
 }
 
+// (Part of every call, so by segment: the tiles of a segment walk ceil(C / 32) + r, + 2 r ... stages, r 32-row units to a tile, and the last one all of its keys.)
 Walks count_walks(const chunk_attn_desc* d, int tile_rows) {
   Walks w;
+  const int64_t r = tile_rows / 32;
   for (int t = 0; t < d->num_segments; ++t) {
     const chunk_attn_seg& s = d->segments[t];
-    w.largest = std::max<int64_t>(w.largest, (s.q_len + tile_rows - 1) / tile_rows);
-    for (int32_t i0 = 0; i0 < s.q_len; i0 += tile_rows) {
-      const int64_t stages = walk_stages(s.kv_len - s.q_len + i0 + 1, std::min<int32_t>(tile_rows, s.q_len - i0));
-      ++w.items;
-      w.stages += stages;
-      w.longest = std::max(w.longest, stages);
-    }
+    const int64_t n = ((int64_t)s.q_len + tile_rows - 1) / tile_rows, before = ((int64_t)s.kv_len - s.q_len + 31) / 32, last = ((int64_t)s.kv_len + 31) / 32;
+    w.largest = std::max(w.largest, n);
+    w.items += n;
+    w.stages += (n - 1) * before + r * (n * (n - 1) / 2) + last;
+    w.longest = std::max(w.longest, last);
   }
   return w;
 }
@@ -149,18 +149,19 @@ std::vector<ShareBlock> share_blocks(const chunk_attn_desc* d, bool keys) {
   return out;
 }
 
+// (By segment, too: blocks that begin inside the context, or where it ends, walk all query tiles, the others keys / 32 fewer from one to the next.)
 Walks count_dkv_walks(const chunk_attn_desc* d, int keys) {
   Walks w;
-  const int group = d->num_q_heads / d->num_kv_heads;
+  const int64_t group = d->num_q_heads / d->num_kv_heads, r = keys / 32;
   for (int t = 0; t < d->num_segments; ++t) {
     const chunk_attn_seg& s = d->segments[t];
-    const int32_t C = s.kv_len - s.q_len, n_qt = (s.q_len + 31) / 32;
-    w.longest = std::max<int64_t>(w.longest, (int64_t)n_qt * group);
-    w.largest = std::max<int64_t>(w.largest, (s.kv_len + keys - 1) / keys);
-    for (int32_t j0 = 0; j0 < s.kv_len; j0 += keys) {
-      ++w.items;
-      w.stages += (int64_t)(n_qt - std::max<int32_t>(0, j0 - C) / 32) * group;
-    }
+    const int64_t C = (int64_t)s.kv_len - s.q_len, n_qt = ((int64_t)s.q_len + 31) / 32, n = ((int64_t)s.kv_len + keys - 1) / keys;
+    const int64_t whole = C / keys + 1, part = n - whole;  // (n >= whole: the last block begins behind C / keys blocks)
+    w.longest = std::max(w.longest, n_qt * group);
+    w.largest = std::max(w.largest, n);
+    w.items += n;
+    // block j begins at key keys j, behind ceil(C / 32) query tiles' worth of context: it lacks r j - ceil(C / 32) of the query tiles
+    w.stages += (n * n_qt - (r * ((whole + n - 1) * part / 2) - part * ((C + 31) / 32))) * group;
   }
   return w;
 }
@@ -227,60 +228,124 @@ CutKind key_walks(const chunk_attn_desc* d, int tile_rows, int inner) {
   return k;
 }
 
-// Ends of the last of `cost` (blocks in the order in which they start), dealt to `workers` as they become free; `free_at` is a heap, earliest first.
-int64_t deal(const std::vector<int64_t>& cost, int workers, std::vector<int64_t>& free_at) {
-  free_at.assign(workers, 0);
+// Blocks of queue 0 among the `inner` ones that start at block b: those divisible by 8.
+int64_t in_queue(int64_t b, int64_t inner) { return (b + inner + 7) / 8 - (b + 7) / 8; }
+
+// The blocks of queue 0 in the order in which they start.
+struct Starts {
+  struct Run { int64_t cost, blocks; };  // one after the other, of equal cost
+  std::vector<Run> runs;
+  int64_t work = 0, longest = 0;
+  void add(int64_t cost, int64_t blocks) {
+    if (blocks == 0) return;
+    work += cost * blocks;
+    longest = std::max(longest, cost);
+    if (!runs.empty() && runs.back().cost == cost) runs.back().blocks += blocks;
+    else runs.push_back(Run{cost, blocks});
+  }
+};
+
+// When the last block ends if they are dealt to `workers` as they become free.
+int64_t deal(const Starts& starts, int workers) {
+  std::vector<int64_t> heap(workers, 0);  // when they become free, the earliest first
+  int64_t* const free_at = heap.data();
   int64_t last = 0;
-  for (int64_t c : cost) {
-    const int64_t end = free_at[0] + c;
-    last = std::max(last, end);
-    int at = 0;  // the earliest one takes the block and sinks to its place
-    for (int child; (child = 2 * at + 1) < workers; at = child) {
-      if (child + 1 < workers && free_at[child + 1] < free_at[child]) ++child;
-      if (free_at[child] >= end) break;
-      free_at[at] = free_at[child];
+  for (const Starts::Run& run : starts.runs) {
+    int64_t n = run.blocks;
+    if (n >= workers && last - free_at[0] <= run.cost) {  // none becomes free a second time before all have: each takes one block of a round
+      const int64_t rounds = n / workers;
+      for (int w = 0; w < workers; ++w) free_at[w] += rounds * run.cost;
+      last = *std::max_element(free_at, free_at + workers);
+      n -= rounds * workers;
     }
-    free_at[at] = end;
+    for (; n > 0; --n) {
+      const int64_t end = free_at[0] + run.cost;
+      last = std::max(last, end);
+      int at = 0;  // the earliest one takes the block and sinks to its place
+      for (int child; (child = 2 * at + 1) < workers; at = child) {
+        if (child + 1 < workers && free_at[child + 1] < free_at[child]) ++child;
+        if (free_at[child] >= end) break;
+        free_at[at] = free_at[child];
+      }
+      free_at[at] = end;
+    }
   }
   return last;
 }
-// Blocks of queue 0 among the `inner` ones that start at block b: those divisible by 8.
-int64_t in_queue(int64_t b, int inner) { return (b + inner + 7) / 8 - (b + 7) / 8; }
 
-// Steps of the walks of one head, none of them cut, in the order in which a launch starts and numbers their blocks: of query-stationary ones sequence by sequence
-// (by_sequence_then_walk), of key-stationary ones the longest first.  (Numbered by the segment table, of 350 sequences of 146 tokens with four key/value heads only the
-// first and longer key block of each would be in queue 0.)
-std::vector<int> key_walks_as_started(const chunk_attn_desc* d, int tile_rows) {
-  std::vector<int> order(d->num_segments), lens;
+// From so many blocks of a queue on they even out by themselves: neither listed (a list costs the host 10 ns a block) nor dealt (20), but summed.
+constexpr int64_t kManyBlocks = 1024;
+// (No runs: the sum is what there is to know.)
+int64_t last_end(const Starts& s, int workers) { return s.runs.empty() ? s.work / workers : deal(s, workers); }
+// Whether x times the end of `a` is before y times that of `b`.  (A last block starts when the others' work has been shared out at the latest, so most pairs need no dealing.)
+bool ends_before(const Starts& a, int64_t x, const Starts& b, int64_t y, int workers) {
+  const bool few = !a.runs.empty() && !b.runs.empty();
+  if (few && x * (a.work / workers + 1 + a.longest) < y * std::max(b.work / workers, b.longest)) return true;
+  if (few && x * std::max(a.work / workers, a.longest) >= y * (b.work / workers + 1 + b.longest)) return false;
+  return x * last_end(a, workers) < y * last_end(b, workers);
+}
+
+// Stages of the walks of one head, none of them cut, in the order in which a launch starts and numbers their blocks: sequence by sequence (by_sequence_then_walk).
+// (Numbered by the segment table, of 350 sequences of 146 tokens with four key/value heads only the first and longer key block of each would be in queue 0.)
+template <class F>
+void key_walks_of(const chunk_attn_seg& s, int tile_rows, F&& walk) {
+  for (int32_t i0 = (s.q_len - 1) / tile_rows * tile_rows; i0 >= 0; i0 -= tile_rows)
+    walk(walk_stages(s.kv_len - s.q_len + i0 + 1, std::min<int32_t>(tile_rows, s.q_len - i0)));
+}
+template <class F>
+void key_walks_as_started(const chunk_attn_desc* d, int tile_rows, F&& walk) {
+  std::vector<int> order(d->num_segments);
   std::iota(order.begin(), order.end(), 0);
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return d->segments[a].kv_len > d->segments[b].kv_len; });
-  for (int t : order) {
-    const chunk_attn_seg& s = d->segments[t];
-    for (int32_t i0 = (s.q_len - 1) / tile_rows * tile_rows; i0 >= 0; i0 -= tile_rows)
-      lens.push_back((int)walk_stages(s.kv_len - s.q_len + i0 + 1, std::min<int32_t>(tile_rows, s.q_len - i0)));
-  }
-  return lens;
+  for (int t : order) key_walks_of(d->segments[t], tile_rows, walk);
 }
-std::vector<int> tile_walks_as_started(const chunk_attn_desc* d, int keys) {
+// Steps of those of key blocks, which start longest first: behind each other where whole blocks of context walk all query tiles, else counted by length.
+template <class F>
+void tile_walks_as_started(const chunk_attn_desc* d, int keys, F&& walks) {
   const int group = d->num_q_heads / d->num_kv_heads;
-  std::vector<int> lens;
+  int most = 0;
+  for (int t = 0; t < d->num_segments; ++t) most = std::max(most, (d->segments[t].q_len + 31) / 32);
+  std::vector<int32_t> blocks(most + 1, 0);  // by query tiles
   for (int t = 0; t < d->num_segments; ++t) {
     const chunk_attn_seg& s = d->segments[t];
-    const int32_t C = s.kv_len - s.q_len, n_qt = (s.q_len + 31) / 32;
-    for (int32_t j0 = 0; j0 < s.kv_len; j0 += keys) lens.push_back((n_qt - std::max<int32_t>(0, j0 - C) / 32) * group);
+    const int32_t C = s.kv_len - s.q_len, n_qt = (s.q_len + 31) / 32, whole = C / keys + 1;
+    blocks[n_qt] += whole;
+    for (int64_t j0 = (int64_t)whole * keys; j0 < s.kv_len; j0 += keys) ++blocks[n_qt - (j0 - C) / 32];
   }
-  std::sort(lens.begin(), lens.end(), [](int a, int b) { return a > b; });
-  return lens;
+  for (int tiles = most; tiles >= 0; --tiles)
+    if (blocks[tiles] > 0) walks((int64_t)tiles * group, blocks[tiles]);
 }
-// The costs of queue 0's blocks of walks of `lens` steps, `inner` blocks each, behind those that `out` holds.
-void queue_costs(const std::vector<int>& lens, int inner, int step, int start, std::vector<int64_t>& out) {
-  int64_t block = 0;
-  for (int len : lens) {
-    out.insert(out.end(), in_queue(block, inner), (int64_t)len * step + start);
-    block += inner;
+
+// The blocks of both kinds, none of them cut, as one launch starts them: a dQ block costs `dq_stage` per stage and `dq_start`
+// more, a dK/dV block of `keys` keys `step` per step and `start` more.
+Starts joint_starts(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int dq_stage, int dq_start, int step, int start) {
+  const Walks q = count_walks(d, tile_rows), k = count_dkv_walks(d, keys);
+  const int64_t q_blocks = q.items * inner, k_blocks = k.items * d->num_kv_heads;
+  Starts s;
+  if (q_blocks + k_blocks > 8 * kManyBlocks) {
+    s.work = ((q.stages * dq_stage + q.items * dq_start) * inner + (k.stages * step + k.items * start) * d->num_kv_heads) / 8;
+    return s;
   }
+  auto add_keys = [&]() {
+    int64_t block = 0;
+    key_walks_as_started(d, tile_rows, [&](int64_t stages) {
+      s.add(stages * dq_stage + dq_start, in_queue(block, inner));
+      block += inner;
+    });
+  };
+  auto add_tiles = [&]() {
+    int64_t block = 0;
+    tile_walks_as_started(d, keys, [&](int64_t steps, int64_t n) {
+      s.add(steps * step + start, in_queue(block, n * d->num_kv_heads));
+      block += n * d->num_kv_heads;
+    });
+  };
+  const bool dq_first = q.longest > k.longest;  // (bwd_layout)
+  if (dq_first) add_keys();
+  add_tiles();
+  if (!dq_first) add_keys();
+  return s;
 }
-constexpr size_t kManyBlocks = 1024;  // of a queue: they even out by themselves, and dealing them would take the host longer than it is worth, 0.1 us each
 
 CutKind tile_walks(const chunk_attn_desc* d, int keys) {
   CutKind k;
@@ -294,22 +359,6 @@ CutKind tile_walks(const chunk_attn_desc* d, int keys) {
   return k;
 }
 
-int64_t last_end(const std::vector<int64_t>& cost, int workers, std::vector<int64_t>& free_at) {
-  return cost.size() > kManyBlocks ? std::accumulate(cost.begin(), cost.end(), (int64_t)0) / workers : deal(cost, workers, free_at);
-}
-
-// When the last of queue 0's blocks of both kinds ends, none of them cut, in the order in which one launch starts them: a dQ block costs `dq_stage` per stage and `dq_start`
-// more, a dK/dV block of `keys` keys `step` per step and `start` more.
-int64_t joint_end(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int dq_stage, int dq_start, int step, int start, int cus) {
-  const std::vector<int> q = key_walks_as_started(d, tile_rows), k = tile_walks_as_started(d, keys);
-  std::vector<int64_t> both, free_at;
-  const bool dq_first = *std::max_element(q.begin(), q.end()) > k[0];  // (bwd_layout)
-  if (dq_first) queue_costs(q, inner, dq_stage, dq_start, both);
-  queue_costs(k, d->num_kv_heads, step, start, both);
-  if (!dq_first) queue_costs(q, inner, dq_stage, dq_start, both);
-  return last_end(both, std::max(1, cus / 8), free_at);
-}
-
 // The cut of N kinds of block that share the compute units, one split each; at most max_parts[i] partial results of kind i.
 // `first` (or null): a cut to look at besides those into equal shares.
 template <int N>
@@ -318,7 +367,7 @@ void choose_cut(const CutKind (&kinds)[N], int cus, const int64_t (&max_parts)[N
   constexpr int kStart = 12 * kUnit, kPart = 6 * kUnit, kMerge = 6 * kUnit;
   constexpr int64_t kPartsPerStep = 32;  // partial results (128 KB per block) read per step
   const int workers = std::max(1, cus / 8);
-  std::vector<int64_t> cost, free_at;
+  std::vector<int64_t> cost;
   int64_t total = 0;    // work of queue 0 ...
   int largest = 0;      // ... and its longest block
   bool many = false;
@@ -365,21 +414,22 @@ void choose_cut(const CutKind (&kinds)[N], int cus, const int64_t (&max_parts)[N
   // (needs count_work of the same splits)
   auto estimate = [&](const KeySplit (&k)[N]) -> int64_t {
     if (many) return std::max<int64_t>(total / workers, largest) + merge_time(k);  // many small blocks fill every gap
-    cost.clear();
+    Starts starts;
     const bool swap = N > 1 && longest_steps(0, k) <= longest_steps(N - 1, k);  // the kind with the longer walks starts first (bwd_layout)
     for (int j = 0; j < N; ++j) {
       const int i = swap ? N - 1 - j : j;
       const CutKind& kind = kinds[i];
-      const size_t first = cost.size();
       int64_t block = 0;
+      cost.clear();
       for (const auto& w : kind.walks) {
         const int n = kind.pieces(w, k[i].target);
         for (int x = 0; x < n; ++x, block += kind.inner)
           cost.insert(cost.end(), in_queue(block, kind.inner), kind.steps(w, n, x) * kind.cost + kStart + (n > 1 ? kPart : 0));
       }
-      std::sort(cost.begin() + first, cost.end(), [](int64_t a, int64_t b) { return a > b; });
+      std::sort(cost.begin(), cost.end(), [](int64_t a, int64_t b) { return a > b; });
+      for (int64_t c : cost) starts.add(c, 1);
     }
-    return deal(cost, workers, free_at) + merge_time(k);
+    return deal(starts, workers) + merge_time(k);
   };
   int longest = 0, shortest = 0x7fffffff;  // steps
   for (int i = 0; i < N; ++i) {
@@ -671,8 +721,8 @@ void refine_bwd_split(const chunk_attn_desc* d, int tile_rows, int inner, int ke
 // what stays: 5251 causal tokens, 32/8, 687 (blocks of 256 keys: 931), 4596, 40/8, 680 (982), 6403 on 10177, 28/4, 1884 (2032), 129 sequences of 222 tokens, 40/8, 834 (868).
 bool tall_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int cus) {
   constexpr int kStep = 20, kDqStage = 25, kTallStep = 32, kDqStart = 12 * kStep, kStart = 10 * kStep;
-  const int64_t tall = joint_end(d, tile_rows, inner, kTallKeys, kDqStage, kDqStart, kTallStep, kStart, cus);
-  return 20 * tall < 19 * joint_end(d, tile_rows, inner, keys, kDqStage, kDqStart, kStep, kStart, cus);
+  return ends_before(joint_starts(d, tile_rows, inner, kTallKeys, kDqStage, kDqStart, kTallStep, kStart), 20,
+                     joint_starts(d, tile_rows, inner, keys, kDqStage, kDqStart, kStep, kStart), 19, std::max(1, cus / 8));
 }
 
 // Pipelined from two blocks of `keys` per CU and 14 steps each on average on, unless most of the larger blocks' second halves are empty (sequences of up to 64 keys: 331 of
@@ -689,7 +739,7 @@ bool wide_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int
   const Walks wq = count_walks(d, tile_rows);
   if (wq.stages < 5 * wq.items) return false;
   constexpr int kUs = 20, kDqStage = 24, kDqStart = 18 * kUs, kStep = 26, kStart = 15 * kUs;
-  const double pipelined = 4.7 + 1.035 / kUs * joint_end(d, tile_rows, inner, kWideKeys, kDqStage, kDqStart, kStep, kStart, cus);
+  const double pipelined = 4.7 + 1.035 / kUs * last_end(joint_starts(d, tile_rows, inner, kWideKeys, kDqStage, kDqStart, kStep, kStart), std::max(1, cus / 8));
   const double per_cu = 1.0 / cus, dq_all = std::max((double)wq.stages * inner * per_cu, (double)wq.longest);
   const double other = 20.7 + 0.138 * dq_all + (16.5 * wq.items * inner + (2.09 * w.stages + 10.0 * w.items) * d->num_kv_heads) * per_cu;
   return pipelined < 0.95 * other;
@@ -704,24 +754,29 @@ bool wide_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int
 // per wave: 8192 queries on 32768 keys, 32/8 heads, 7329 / 5658 us, 4096 causal tokens 302 / 242; what stays: 2668 causal tokens, 8/8, 85 / 115, 62 sequences of 241 tokens, 28/4, 235 /
 // 250, eight of 1520, 8/8, 126 / 134, eleven of 701, 8/8, 64 / 71.
 bool fwd_tall_pays(const chunk_attn_desc* d, int tile_rows, int inner, int cus) {
-  if (count_walks(d, tile_rows).items * inner <= cus) return false;  // (all blocks run at once, and short ones end sooner)
-  struct Times { int64_t work = 0, end = 0; };
-  auto times = [&](int rows, int stage, int start) {
-    std::vector<int> lens = key_walks_as_started(d, rows);
-    Times t;
-    for (int& len : lens) {
-      len = (len & ~1) + 2;
-      t.work += (int64_t)len * stage + start;
-    }
-    std::vector<int64_t> cost, free_at;
-    queue_costs(lens, inner, stage, start, cost);
-    t.end = last_end(cost, std::max(1, cus / 8), free_at);
-    return t;
+  const Walks w32 = count_walks(d, tile_rows), w64 = count_walks(d, 2 * tile_rows);
+  if (w32.items * inner <= cus) return false;  // (all blocks run at once, and short ones end sooner)
+  auto starts = [&](int rows, int64_t items, int stage, int start, int64_t* work) {
+    Starts s;
+    *work = 0;
+    auto cost = [&](int stages) { return (int64_t)((stages & ~1) + 2) * stage + start; };
+    for (int t = 0; t < d->num_segments; ++t) key_walks_of(d->segments[t], rows, [&](int stages) { *work += cost(stages); });
+    s.work = *work * inner / 8;
+    if (items * inner > 8 * kManyBlocks) return s;
+    s.work = 0;
+    int64_t block = 0;
+    key_walks_as_started(d, rows, [&](int stages) {
+      s.add(cost(stages), in_queue(block, inner));
+      block += inner;
+    });
+    return s;
   };
-  const Times rows32 = times(tile_rows, 5, 35), rows64 = times(2 * tile_rows, 7, 75);
-  const int64_t blocks = count_tiles(d, false, 2 * tile_rows) * inner;
+  int64_t work32, work64;
+  const Starts rows32 = starts(tile_rows, w32.items, 5, 35, &work32), rows64 = starts(2 * tile_rows, w64.items, 7, 75, &work64);
+  const int64_t blocks = w64.items * inner;
   const bool one_head = tile_rows >= 128, few = blocks > cus && 4 * blocks <= 5 * cus;
-  return 100 * rows64.work < (one_head ? 96 : 100) * rows32.work && 100 * rows64.end < (few ? 95 : one_head || blocks <= 2 * cus ? 100 : 104) * rows32.end;
+  return 100 * work64 < (one_head ? 96 : 100) * work32 &&
+         ends_before(rows64, 100, rows32, few ? 95 : one_head || blocks <= 2 * cus ? 100 : 104, std::max(1, cus / 8));
 }
 
 std::vector<DkvItem> cut_items(const std::vector<DkvItem>& wholes, int target, std::vector<DkvItem>* cut) {

@@ -1,4 +1,9 @@
 """Which blocks the estimates choose for chunks whose other blocks were measured to be faster, and what the choice costs the host."""
+import os
+import shutil
+import subprocess
+import time
+
 import pytest
 
 import paper_2509_21275_amd as ca
@@ -56,3 +61,26 @@ def test_long_walks_that_start_in_groups(d, keys, in_step):
     ([(0, 12000, 0, 12000)], 32, 16, 256), ([(0, 223, 0, 5186)], 512, 256, 256), ([(0, 451, 0, 9405)], 512, 128, 256)])  # several: one, walks of few steps, too
 def test_one_launch_of_64(segs, hq, hk, keys):
     assert ca.chunk_attn_test_dkv_keys(_desc(segs, hq, hk, 64)) == keys
+
+
+def test_walks_are_counted_by_segment(tmp_path):
+    if shutil.which("g++") is None:
+        pytest.skip("needs g++")
+    root, exe = os.path.dirname(os.path.dirname(os.path.abspath(__file__))), str(tmp_path / "walk_counts")
+    r = subprocess.run(["g++", "-std=c++17", "-O1", "-I", os.path.join(root, "include"), os.path.join(root, "tests", "native", "walk_counts.cpp"),
+                        os.path.join(root, "paper_2509_21275_amd", "csrc", "plan.cpp"), "-o", exe], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout[-2000:]
+
+
+@pytest.mark.parametrize("d", [96, 128, 256])
+def test_large_chunks_cost_the_choice_no_list(d):
+    """2^27 query rows (a list of their blocks took seconds and gigabytes) in less than 20 ms, most of it the tiles' parities at 256."""
+    desc = _desc([(0, 1 << 27, 0, 1 << 27)], 64, 64, d)
+    best = 1.0
+    for _ in range(5):
+        begin = time.perf_counter()
+        ca.chunk_attn_workspace_bytes(desc)
+        best = min(best, time.perf_counter() - begin)
+    assert best < 0.02
