@@ -713,16 +713,17 @@ void refine_bwd_split(const chunk_attn_desc* d, int tile_rows, int inner, int ke
 }
 
 // The estimate of refine_bwd_split for uncut walks, with the dK/dV blocks of either size: a step of 256 keys counts as 8/5 of one of 128 (1.61 by its cycles), the start and end of
-// either as ten steps of 128 and of a dQ block as twelve, and 256 keys have to be ahead by a twentieth: what the estimate cannot tell apart keeps the blocks of 128.
-// Of 924 drawn chunks of 60 us and more (backward, 128 and 96, up to 65536 keys, 1 - 8 query heads to a key/value head, two thirds of them of many short sequences) it picks 564, of
-// which five are slower by more than 1.5 % (2.7 at most: 18 sequences of 202 tokens, 32/8 heads, 104 us); all 924 take 4.4 % less in the mean, with the better of the two for each
-// 4.6.  (Without the margin, and 16 steps for the start of 256 keys, 18 are slower, by 34 % at most.)
+// either as ten steps of 128 and of a dQ block as twelve, and 256 keys have to be ahead by a twentieth, for what the estimate cannot tell apart keeps the blocks of 128 (where dQ blocks start first, just
+// ahead: the ends of few dK/dV blocks behind them come out too late).  Of 999 drawn chunks of 60 us and more (backward, 128 and 96, up to 65536 keys, 1 - 8 query heads to a key/value head, two
+// thirds of them of many short sequences) it picks 634, of which seven are slower by more than 1.5 % (2.9 at most: 277 sequences, 63653 tokens, 64/8 heads, 2902 us); all 999 take 4.6 % less in the
+// mean.  (Without the margin, and 16 steps for the start of 256 keys, 18 of 924 are slower, by 34 % at most.)
 // 14147 queries on 14216 keys, 32/8 heads, 4718 -> 4283 us; 4977 on 38367, 64/8, 16275 -> 15116; 3193 on 8192, 32/8, 1116 -> 1044; eight sequences of 300 tokens, 64/64, 216 -> 204;
 // what stays: 5251 causal tokens, 32/8, 687 (blocks of 256 keys: 931), 4596, 40/8, 680 (982), 6403 on 10177, 28/4, 1884 (2032), 129 sequences of 222 tokens, 40/8, 834 (868).
 bool tall_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int cus) {
   constexpr int kStep = 20, kDqStage = 25, kTallStep = 32, kDqStart = 12 * kStep, kStart = 10 * kStep;
+  const bool dq_first = count_walks(d, tile_rows).longest > count_dkv_walks(d, keys).longest;  // (bwd_layout)
   return ends_before(joint_starts(d, tile_rows, inner, kTallKeys, kDqStage, kDqStart, kTallStep, kStart), 20,
-                     joint_starts(d, tile_rows, inner, keys, kDqStage, kDqStart, kStep, kStart), 19, std::max(1, cus / 8));
+                     joint_starts(d, tile_rows, inner, keys, kDqStage, kDqStart, kStep, kStart), dq_first ? 20 : 19, std::max(1, cus / 8));
 }
 
 // Pipelined from two blocks of `keys` per CU and 14 steps each on average on, unless most of the larger blocks' second halves are empty (sequences of up to 64 keys: 331 of
@@ -730,12 +731,12 @@ bool tall_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int
 // estimates in us: the pipelined blocks of both kinds dealt as in tall_pays; the unpipelined ones, whose walks may be cut
 // and so know no longest one, by their number and steps.  Least squares in the relative error over 1140 drawn chunks of 60 us and more (up to 65536 keys, 1 - 8 query heads to a
 // key/value head, two thirds of them of many short sequences), each run both ways; off by 7 and 10 % (root mean square), so that the pipelined ones have to be ahead by 5.  Of the 1140 it
-// picks 830, of which two are slower by more than 1.5 % than without these blocks (3.0 at most: 2112 causal tokens, 8/8, 106 us); all take 12.1 % less in the mean, with
+// picks 829, of which three are slower by more than 1.5 % than without these blocks (3.0 at most: 2112 causal tokens, 8/8, 106 us); all take 12.1 % less in the mean, with
 // the better of the two for each 13.3.  Unpipelined / pipelined: 2668 causal tokens, 8/8 heads, 184 / 148 us; 1428 queries on
 // 3445 keys, 32/8, 578 / 407; 10770 causal, 28/4, 7202 / 4677; 7307, 32/8, 3571 / 2456; what stays: 4335, 8/2, 386 / 655; 899, 64/8, 172 / 298.
 bool wide_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int cus) {
   const Walks w = count_dkv_walks(d, keys);
-  if (w.items * d->num_kv_heads >= 2 * cus && w.stages >= 14 * w.items && 10 * count_tiles(d, true, kWideKeys) <= 7 * w.items) return true;
+  if (w.items * d->num_kv_heads >= 2 * cus && w.stages >= 14 * w.items && 4 * count_tiles(d, true, kWideKeys) <= 3 * w.items) return true;
   const Walks wq = count_walks(d, tile_rows);
   if (wq.stages < 5 * wq.items) return false;
   constexpr int kUs = 20, kDqStage = 24, kDqStart = 18 * kUs, kStep = 26, kStart = 15 * kUs;
@@ -748,8 +749,9 @@ bool wide_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int
 // Blocks dealt as in tall_pays, in a fifth of a stage of 32 rows per wave, whose start and end take as long as seven of them; a stage of 64 rows counts as 7/5, its start and end as
 // 15 stages.  Either kernel runs its stages in pairs, with one more for the last product.  Where a workgroup takes one head (an odd number of heads to a key/value head: 256 rows to a block of 64 per
 // wave), some wave masks keys in most stages of a short walk, and 64 rows have to take a twenty-fifth less work and end sooner; elsewhere no more work, and a twenty-fifth
-// later by the estimate is soon enough from two blocks of 64 rows per compute unit on.  With a few more blocks than compute units the end hangs on their order: ahead by a twentieth.  Of 840 drawn chunks (up to 65536 keys, 1 - 8 query
-// heads to a key/value head, two thirds of them of many short sequences) it picks 392, of which one is slower by more than 1.5 % (1.9: eleven sequences
+// later by the estimate is soon enough from two blocks of 64 rows per compute unit on.  With a few more blocks than compute units the end hangs on their order: ahead by a twentieth;
+// with no more, they all start at once, and the end alone decides (up to 1.06 of the other's: of 42 such chunks those below are faster by 2 - 30 %, those above slower but for one).  Of 840 drawn chunks (up to 65536 keys, 1 - 8 query
+// heads to a key/value head, two thirds of them of many short sequences) it picks 394, of which one is slower by more than 1.5 % (1.9: eleven sequences
 // of 333 tokens, 32/16 heads, 80 us); all 840 take 5.3 % less in the mean, with the better of the two for each 5.5.  (Without the pairs, and by the end alone: 31 are slower, by 9 % at most.)  32 / 64 rows
 // per wave: 8192 queries on 32768 keys, 32/8 heads, 7329 / 5658 us, 4096 causal tokens 302 / 242; what stays: 2668 causal tokens, 8/8, 85 / 115, 62 sequences of 241 tokens, 28/4, 235 /
 // 250, eight of 1520, 8/8, 126 / 134, eleven of 701, 8/8, 64 / 71.
@@ -774,9 +776,11 @@ bool fwd_tall_pays(const chunk_attn_desc* d, int tile_rows, int inner, int cus) 
   int64_t work32, work64;
   const Starts rows32 = starts(tile_rows, w32.items, 5, 35, &work32), rows64 = starts(2 * tile_rows, w64.items, 7, 75, &work64);
   const int64_t blocks = w64.items * inner;
-  const bool one_head = tile_rows >= 128, few = blocks > cus && 4 * blocks <= 5 * cus;
+  const int workers = std::max(1, cus / 8);
+  if (blocks <= cus) return ends_before(rows64, 100, rows32, 106, workers);
+  const bool one_head = tile_rows >= 128;
   return 100 * work64 < (one_head ? 96 : 100) * work32 &&
-         ends_before(rows64, 100, rows32, few ? 95 : one_head || blocks <= 2 * cus ? 100 : 104, std::max(1, cus / 8));
+         ends_before(rows64, 100, rows32, 4 * blocks <= 5 * cus ? 95 : one_head || blocks <= 2 * cus ? 100 : 104, workers);
 }
 
 std::vector<DkvItem> cut_items(const std::vector<DkvItem>& wholes, int target, std::vector<DkvItem>* cut) {

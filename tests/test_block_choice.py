@@ -43,6 +43,12 @@ def test_forward_of_256_keeps_32_rows(count, length, hq, hk):
     assert ca.chunk_attn_test_fwd_rows(_desc(_packed(count, length), hq, hk, 256)) == 32
 
 
+@pytest.mark.parametrize("segs,hq,hk", [(_packed(8, 255), 28, 4), (_packed(9, 369), 16, 8), ([(0, 2214, 0, 7168)], 16, 16)])
+def test_forward_of_256_whose_blocks_all_start_at_once(segs, hq, hk):
+    """No more blocks of 64 rows per wave than compute units: faster by 14 to 17 %."""
+    assert ca.chunk_attn_test_fwd_rows(_desc(segs, hq, hk, 256)) == 64
+
+
 @pytest.mark.parametrize("segs,hq,hk,keys", [
     (_packed(166, 57), 28, 4, 64), (_packed(331, 51), 28, 4, 64), (_packed(278, 70), 28, 4, 128),   # a block of 128 keys would be half empty, or not
     ([(0, 371, 0, 2337)] + [(371 + 172 * i, 172, 2337 + 172 * i, 172) for i in range(19)], 8, 2, 64)])  # ahead by less than the estimates are off by
@@ -84,3 +90,10 @@ def test_large_chunks_cost_the_choice_no_list(d):
         ca.chunk_attn_workspace_bytes(desc)
         best = min(best, time.perf_counter() - begin)
     assert best < 0.02
+
+
+@pytest.mark.parametrize("segs,heads", [
+    ([(0, 11481, 0, 11581)] + [(11481 + 292 * i, 292, 11581 + 292 * i, 292) for i in range(22)], 8),   # faster by 8 %
+    ([(0, 5863, 0, 10447)] + [(5863 + 190 * i, 190, 10447 + 190 * i, 190) for i in range(3)], 8)])
+def test_dq_blocks_that_start_first(segs, heads):
+    assert ca.chunk_attn_test_dkv_keys(_desc(segs, heads, heads, 128)) == 256
