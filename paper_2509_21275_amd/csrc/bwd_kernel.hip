@@ -847,7 +847,7 @@ __device__ __forceinline__ void dkv_pipe_blocks(const ArgsPtr<DkvParams> args, c
   // 50 - 55 -> 45 - 48 per launch; that slice, forward and backward, 232.3 -> 231.5 ms.  With shorter walks workgroups only stand idle: 873 queries on 5197 keys, 32/8, whole
   // walks, backward 323 us with the waits, 238 without; 405 on 17711, 64/8, 829 / 740; walks of 1024 steps +- 0.1 %.  And where dQ blocks
   // come first workgroups reach these one by one.  (Head_dim 64, whose steps are half as long, does not wait: of six
-  // chunks with such walks none was faster with the waits: 12719 queries on 13105 keys, 64/8 heads, 4441 with, 4341 without, 21790 on 65580, 32/8, 29391 / 29148, 19169 on 19834, 64/8, 9798 / 9797.)
+  // chunks with such walks none was faster with the waits: 12719 queries on 13105 keys, 64/8 heads, 4441 with, 4341 without, on another box 4442 / 4441, 21790 on 65580, 32/8, 29391 / 29148.)
   int* const next_block = (int*)((__bf16*)smem + LDS_ELEMS);
   const int xcd = xcd_of_this_wave();
   clock_log_stamp(fresh(args).clock_log, 0);
@@ -1417,12 +1417,12 @@ __device__ __forceinline__ void dkv_tall_blocks(const ArgsPtr<DkvParams> args, c
     return l;
   };
 
-  // Persistent, and long equal walks start in groups, as in dkv_pipe_blocks.
+  // Persistent, and long equal walks start in groups, as in dkv_pipe_blocks.  (At 64 none do, by side_by_side: compiled without them, these blocks were 0.3 - 0.8 % slower.)
   const int xcd = xcd_of_this_wave();
   clock_log_stamp(fresh(args).clock_log, 0);
   int blk = mine;
   auto start_in_step = [&](const DkvParams& p, int b) __attribute__((always_inline)) {
-    if (D == 64 || p.side_by_side == 0 || b < 0) return;
+    if (p.side_by_side == 0 || b < 0) return;
     const DkvItem it = load_uniform(p.items, b / p.num_kv_heads);
     if (it.j0 + it.kv_rows <= it.ctx && (int64_t)it.n_qt * p.group >= kStepsInStep) wait_for_earlier_groups(p.ended, b, p.side_by_side);
   };
@@ -1778,7 +1778,7 @@ __device__ __forceinline__ void dkv_tall_blocks(const ArgsPtr<DkvParams> args, c
   int nb = 0;
   if (wave == 0) {
     const DkvParams p = fresh(args);
-    if (D != 64 && p.side_by_side != 0 && lane_id() == 0) __hip_atomic_fetch_add(p.ended + (blk & 7), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (p.side_by_side != 0 && lane_id() == 0) __hip_atomic_fetch_add(p.ended + (blk & 7), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     nb = block_claim_finish(p.taken, p.num_blocks, xcd, pending_claim);
     start_in_step(p, nb);
   }

@@ -343,7 +343,9 @@ hipError_t launch(void* logits, const int32_t* targets, float* loss, int64_t row
   if constexpr (FULL == 0 && NCH == 32) return as(keep);  // (fewer than two rows per compute unit)
   else if constexpr (FULL == 0) {
     if (whole || vocab <= kShortRow) return bytes > kStreamBytesShort ? as(all) : as(keep);
-    return NCH <= 8 || bytes <= kStreamBytes ? as(keep) : as(stores);
+    if constexpr (NCH > 8)
+      if (bytes > kStreamBytes) return as(stores);
+    return as(keep);
   } else {
     if (row_each || bytes <= kStreamBytes) return as(keep);
     return whole ? as(all) : as(stores);
