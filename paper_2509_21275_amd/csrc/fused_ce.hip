@@ -6,9 +6,8 @@
 // The exponential of an element is evaluated twice (for the sum and for the gradient) rather than kept: the vector work of
 // a row is several times shorter than the time HBM needs to deliver it.  Workgroups walk the rows with a grid stride.
 //
-// Two kernels.  fused_ce_kernel: rows of up to 65536 logits, and of up to 131072 where there are fewer than two per compute unit; they stay in at most 128
-// registers per lane, maximum and sum are two passes over them.  With 8, 16 and 32 chunks to a lane it takes 70, 118 and 215 registers: several workgroups on a compute unit hide each
-// other's vector work, but for rows of more than 65536 logits, whose workgroups have the compute unit to themselves.
+// Two kernels.  fused_ce_kernel: rows of up to 65536 logits, and of up to 131072 where there are fewer than two per compute unit (or very many, kManyBytes); they stay in at most 128
+// registers per lane, maximum and sum are two passes over them, and two or more workgroups on a compute unit (or the other compute units) hide each other's vector work.
 // fused_ce_long_kernel: longer rows take more registers, the longest LDS, too, so that one workgroup has the compute unit.  It takes the sum while the row
 // arrives, against the running maximum of the thread's own chunks (moved once per group of chunks), merges the threads' (maximum, sum) pairs once per row, and as it
 // stores a chunk's gradient it loads that chunk of its next row into the same registers: reads stay in flight through the vector work of the gradients, a third of
@@ -26,23 +25,20 @@ namespace chunk_attn {
 namespace {
 
 constexpr int kThreads = 512;
-// Logits of many more bytes than the last-level cache (256 MiB) holds stream past the caches; what fits, or nearly so, is kept for those who wrote it and who read it next.
-// Rows of whole cache lines (kStreamAll), us, kept / streamed: fused_ce_long_kernel, 512 rows of 262144 (256 MiB) 104 / 113, 966 of 151936 (280) 121 / 126, 1128 of 128256 (276)
-// 126 / 132, 1348 (330) 158 / 160, 1138 of 151936 (330) 157 / 155, 904 of 200064 (345) 177 / 170, 4096 of 151936 (1187) 516 / 498; fused_ce_kernel, which has more rows in flight, from
-// a little more than the cache on: 4400 of 32000 (269) 106.2 / 107.2, 6000 of 24000 (275) 107.3 / 103.7, 16384 of 16000 (500) 200 / 182, 65536 of 4096 (512) 387 / 324 (stores only: 386).
+// Logits of more bytes than the last-level cache (256 MiB) holds stream past the caches; what fits is kept for those who wrote it and who read it next.
+// Rows of whole cache lines (kStreamAll), us, kept / streamed: fused_ce_long_kernel, 512 rows of 262144 (268 MB) 104 / 113, 1024 of 131072 (268) 103 / 111, 900 of
+// 151936 (273) 128 / 123, 4096 of 151936 (1245) 516 / 498; fused_ce_kernel, which has more rows in flight, a little later: 4400 of 32000 (282) 106.2 / 107.2, 6000 of
+// 24000 (288) 107.3 / 103.7, 16384 of 16000 (524) 200 / 182, 65536 of 4096 (537) 387 / 324 (stores only: 386).
 // Where rows begin inside a line, so does every wave's share of a chunk, and the two waves that share a line may each fetch it from memory.  With rows of up to 16384
 // logits that costs less than streaming gains (kept / all: 32768 of 8008 252 / 225, 16384 of 16008 200 / 189); with up to 32768 all is slower and stores only are, too
-// (kept / stores / all: 16384 of 32760 422 / 439 / 444, 8192 of 32008 210 / 214 / 210); longer ones stream their stores: 1100 of 131064 (275)
-// 131 / 135 / -, 1024 of 151944 (297) 134 / 138 / -, 1100 of 151944 (319) 163 / 160 / -, 1024 of 262136 (512) 261 / 241 / 245, 4096 of 65528 (512) 225 / 207 / 217.
-constexpr int64_t kStreamBytesShort = (int64_t)272 << 20, kStreamBytes = (int64_t)320 << 20;
+// (kept / stores / all: 16384 of 32760 422 / 439 / 444, 8192 of 32008 210 / 214 / 210); longer ones stream their stores, from a larger size on: 1100 of 131064 (288)
+// 131 / 135 / -, 1024 of 151944 (311) 134 / 138 / -, 1100 of 151944 (334) 163 / 160 / -, 1024 of 262136 (537) 261 / 241 / 245, 4096 of 65528 (537) 225 / 207 / 217.
+constexpr int64_t kStreamBytes = (int64_t)256 << 20, kStreamBytesShort = (int64_t)272 << 20, kStreamStoresBytes = (int64_t)320 << 20;
 constexpr int kShortRow = 16384;
-// A workgroup of the long kernel goes through several rows, whose loads then run under the stores before them, or takes one, and the hardware hands the rows out in order.  The second is the faster
-// one (a) for long rows that are a little more than the last-level cache holds, which the loads ahead drive out of it too soon, and (b) above 2 GiB for rows of up to 131072 logits (the
-// rows in flight stay side by side; what of memory that suits was not found).  Several rows / one, us, each kept: (a) 691 rows of 200064 (264 MiB) 132 / 119, 910 of 151944 (264) 132 / 119, 532 of
-// 262136 (266) 164 / 146, 1079 of 128256 133 / 124; less: 512 of 262136 (256) 104.7 / 104.6, 1024 of 131072 (256) 103 / 114, more: 1128 of 128256 (276) 126 / 131, 952 of 151936 (276) 122 / 122; shorter rows:
-// 2007 of 70016 (268) 120 / 128, 1373 of 100032 (262) 127 / 125, 1415 (270) 126 / 129.  (b) 16384 of 131072 1663 / 1640, of 131064 1816 / 1670, of 100000 1395 / 1315, of 70016 913 / 912, of 70000 973 / 918.
-constexpr int64_t kCacheBytes = (int64_t)256 << 20, kNearCacheBytes = (int64_t)272 << 20, kManyBytes = (int64_t)2 << 30;
-constexpr int kNearCacheRow = 114688;
+// Above 2 GiB rows of 65544 to 131072 logits lose what they gain below, by measurement (why was not found).  Whole lines, fused_ce_kernel / long kernel kept / streamed: 16384
+// rows of 131072 (4.3 GB) 1686 / 1657 / 1740, 12000 1249 / 1217 / 1268, 8192 (2 GiB) 868 / 837 / 849; others, fused_ce_kernel / long kernel, stores streamed:
+// 16384 of 131064 1717 / 1772, 16384 of 100000 1337 / 1338.  Longer rows and shorter ones gain there, too: 14000 of 151936 1727 -> 1660, 32768 of 65536 1653 -> 1602.
+constexpr int64_t kManyBytes = (int64_t)2 << 30;
 bool whole_lines(const void* logits, int64_t row_stride) { return ((uintptr_t)logits & 127) == 0 && row_stride % 64 == 0; }
 constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
 
@@ -311,9 +307,9 @@ __global__ __launch_bounds__(kThreads) void fused_ce_long_kernel(__bf16* __restr
 
 template <int NCH, int NL, int FULL, Stream STREAM>
 hipError_t launch_as(void* logits, const int32_t* targets, float* loss, int64_t rows, int vocab, int64_t row_stride,
-                     float grad_scale, hipStream_t stream, bool row_each) {
+                     float grad_scale, hipStream_t stream) {
   if constexpr (FULL == 0) {
-    // two workgroups per compute unit where the registers allow it, rows dealt round robin
+    // two workgroups per compute unit when the registers allow it, rows dealt round robin
     const dim3 grid((unsigned)(rows < 512 ? rows : 512));
     hipLaunchKernelGGL((fused_ce_kernel<NCH, STREAM>), grid, dim3(kThreads), 0, stream, (__bf16*)logits, targets, loss, rows, vocab,
                        row_stride, grad_scale);
@@ -322,7 +318,7 @@ hipError_t launch_as(void* logits, const int32_t* targets, float* loss, int64_t 
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&fused_ce_long_kernel<NCH, NL, FULL, STREAM>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (attr != hipSuccess) return attr;
-    const dim3 grid((unsigned)(row_each ? rows : persistent_grid(rows)));  // (one per compute unit is what the registers allow)
+    const dim3 grid((unsigned)persistent_grid(rows));  // one per compute unit is what the registers allow: each goes through its share of the rows
     hipLaunchKernelGGL((fused_ce_long_kernel<NCH, NL, FULL, STREAM>), grid, dim3(kThreads), smem, stream, (__bf16*)logits, targets, loss, rows,
                        vocab, row_stride, grad_scale);
   }
@@ -331,24 +327,18 @@ hipError_t launch_as(void* logits, const int32_t* targets, float* loss, int64_t 
 template <int NCH, int NL = 0, int FULL = 0>
 hipError_t launch(void* logits, const int32_t* targets, float* loss, int64_t rows, int vocab, int64_t row_stride,
                   float grad_scale, hipStream_t stream) {
-  const int64_t bytes = rows * (int64_t)vocab * 2;
-  const bool whole = whole_lines(logits, row_stride);
-  const bool row_each = FULL > 0 && ((bytes > kCacheBytes && bytes <= kNearCacheBytes && vocab > kNearCacheRow) || (NCH == 32 && bytes > kManyBytes));
   auto as = [&](auto stream_c) {
-    return launch_as<NCH, NL, FULL, decltype(stream_c)::value>(logits, targets, loss, rows, vocab, row_stride, grad_scale, stream, row_each);
+    return launch_as<NCH, NL, FULL, decltype(stream_c)::value>(logits, targets, loss, rows, vocab, row_stride, grad_scale, stream);
   };
   const std::integral_constant<Stream, kKeep> keep;
-  const std::integral_constant<Stream, kStreamStores> stores;
-  const std::integral_constant<Stream, kStreamAll> all;
-  if constexpr (FULL == 0 && NCH == 32) return as(keep);  // (fewer than two rows per compute unit)
-  else if constexpr (FULL == 0) {
-    if (whole || vocab <= kShortRow) return bytes > kStreamBytesShort ? as(all) : as(keep);
-    if constexpr (NCH > 8)
-      if (bytes > kStreamBytes) return as(stores);
-    return as(keep);
-  } else {
-    if (row_each || bytes <= kStreamBytes) return as(keep);
-    return whole ? as(all) : as(stores);
+  if constexpr (FULL == 0 && NCH == 32) return as(keep);  // (fewer than 512 rows, or more than kManyBytes)
+  else {
+    const int64_t bytes = rows * (int64_t)vocab * 2;
+    if (NCH == 32 && bytes > kManyBytes) return as(keep);
+    if (whole_lines(logits, row_stride) || (FULL == 0 && vocab <= kShortRow))
+      return bytes > (FULL == 0 ? kStreamBytesShort : kStreamBytes) ? as(std::integral_constant<Stream, kStreamAll>{}) : as(keep);
+    if (NCH <= 8 || bytes <= kStreamStoresBytes) return as(keep);
+    return as(std::integral_constant<Stream, kStreamStores>{});
   }
 }
 
@@ -367,7 +357,7 @@ extern "C" int fused_ce_inplace(void* logits, const int32_t* targets, float* los
   hipError_t e;
   if (per_thread <= 8) e = launch<8>(logits, targets, loss, rows, vocab, row_stride, grad_scale, s);
   else if (per_thread <= 16) e = launch<16>(logits, targets, loss, rows, vocab, row_stride, grad_scale, s);
-  else if (per_thread <= 32 && rows < 2 * kCus) e = launch<32>(logits, targets, loss, rows, vocab, row_stride, grad_scale, s);
+  else if (per_thread <= 32 && (rows < 2 * kCus || (rows * (int64_t)vocab * 2 > kManyBytes && !whole_lines(logits, row_stride)))) e = launch<32>(logits, targets, loss, rows, vocab, row_stride, grad_scale, s);
   else if (per_thread <= 32) e = launch<32, 0, 16>(logits, targets, loss, rows, vocab, row_stride, grad_scale, s);
   else if (per_thread <= 40) e = launch<40, 0, 32>(logits, targets, loss, rows, vocab, row_stride, grad_scale, s);
   else e = launch<46, 18, 40>(logits, targets, loss, rows, vocab, row_stride, grad_scale, s);
