@@ -7,7 +7,8 @@
 // a row is several times shorter than the time HBM needs to deliver it.  Workgroups walk the rows with a grid stride.
 //
 // Two kernels.  fused_ce_kernel: rows of up to 65536 logits, and of up to 131072 where there are fewer than two per compute unit (or very many, kManyBytes); they stay in at most 128
-// registers per lane, maximum and sum are two passes over them, and two or more workgroups on a compute unit (or the other compute units) hide each other's vector work.
+// registers per lane, maximum and sum are two passes over them.  With 8, 16 and 32 chunks to a lane it takes 70, 118 and 215 registers: two or more workgroups on a compute unit hide each
+// other's vector work, but for rows of more than 65536 logits, whose workgroups have the compute unit to themselves.
 // fused_ce_long_kernel: longer rows take more registers, the longest LDS, too, so that one workgroup has the compute unit.  It takes the sum while the row
 // arrives, against the running maximum of the thread's own chunks (moved once per group of chunks), merges the threads' (maximum, sum) pairs once per row, and as it
 // stores a chunk's gradient it loads that chunk of its next row into the same registers: reads stay in flight through the vector work of the gradients, a third of
@@ -35,7 +36,12 @@ constexpr int kThreads = 512;
 // 131 / 135 / -, 1024 of 151944 (311) 134 / 138 / -, 1100 of 151944 (334) 163 / 160 / -, 1024 of 262136 (537) 261 / 241 / 245, 4096 of 65528 (537) 225 / 207 / 217.
 constexpr int64_t kStreamBytes = (int64_t)256 << 20, kStreamBytesShort = (int64_t)272 << 20, kStreamStoresBytes = (int64_t)320 << 20;
 constexpr int kShortRow = 16384;
-// Above 2 GiB rows of 65544 to 131072 logits lose what they gain below, by measurement (why was not found).  Whole lines, fused_ce_kernel / long kernel kept / streamed: 16384
+// (Figures of the operator repeated on its own output.  Where the logits are written first, kept rows leave the cache full of gradients, which costs the next writer, too: refill and operator, kept /
+// streamed, 1128 rows of 128256 (289) 247 / 230, 952 of 151936 (289) 243 / 220, and 900 rows or so of 151936 that are not whole lines, 126 us before the next row's loads and 131 with
+// them when repeated, take 242 and 239.)
+// Above 2 GiB rows of 65544 to 131072 logits lose what they gain below, by measurement: with a compute unit to itself a workgroup of either kernel has nobody to hide its vector work, and why the long
+// kernel's loads ahead help less there was not found (a row to each workgroup, handed out in order: 16384 of 131064 1816 -> 1670, of 131072 1663 -> 1640, but with the logits written first only
+// 3501 -> 3463 and 3647 -> 3657 of refill and operator).  Whole lines, fused_ce_kernel / long kernel kept / streamed: 16384
 // rows of 131072 (4.3 GB) 1686 / 1657 / 1740, 12000 1249 / 1217 / 1268, 8192 (2 GiB) 868 / 837 / 849; others, fused_ce_kernel / long kernel, stores streamed:
 // 16384 of 131064 1717 / 1772, 16384 of 100000 1337 / 1338.  Longer rows and shorter ones gain there, too: 14000 of 151936 1727 -> 1660, 32768 of 65536 1653 -> 1602.
 constexpr int64_t kManyBytes = (int64_t)2 << 30;
@@ -309,7 +315,7 @@ template <int NCH, int NL, int FULL, Stream STREAM>
 hipError_t launch_as(void* logits, const int32_t* targets, float* loss, int64_t rows, int vocab, int64_t row_stride,
                      float grad_scale, hipStream_t stream) {
   if constexpr (FULL == 0) {
-    // two workgroups per compute unit when the registers allow it, rows dealt round robin
+    // two workgroups per compute unit where the registers allow it, rows dealt round robin (at 32 chunks, one to a compute unit, 256 and 512 workgroups take the same time)
     const dim3 grid((unsigned)(rows < 512 ? rows : 512));
     hipLaunchKernelGGL((fused_ce_kernel<NCH, STREAM>), grid, dim3(kThreads), 0, stream, (__bf16*)logits, targets, loss, rows, vocab,
                        row_stride, grad_scale);
@@ -337,8 +343,9 @@ hipError_t launch(void* logits, const int32_t* targets, float* loss, int64_t row
     if (NCH == 32 && bytes > kManyBytes) return as(keep);
     if (whole_lines(logits, row_stride) || (FULL == 0 && vocab <= kShortRow))
       return bytes > (FULL == 0 ? kStreamBytesShort : kStreamBytes) ? as(std::integral_constant<Stream, kStreamAll>{}) : as(keep);
-    if (NCH <= 8 || bytes <= kStreamStoresBytes) return as(keep);
-    return as(std::integral_constant<Stream, kStreamStores>{});
+    if constexpr (NCH > 8)
+      if (bytes > kStreamStoresBytes) return as(std::integral_constant<Stream, kStreamStores>{});
+    return as(keep);
   }
 }
 

@@ -161,3 +161,31 @@ def test_a_row_and_the_next_one_of_its_workgroup(rows, vocab, whole_lines):
     assert bool(torch.isfinite(loss).all()) and torch.equal(buf[:, vocab:], between)
     assert np.abs(loss[check].cpu().double().numpy() - want_loss).max() <= 2e-4 * max(1.0, np.abs(want_loss).max())
     assert np.all(np.abs(got - want_grad) <= 2.0 ** -8 * np.abs(want_grad) + 2.0 ** -8 * 0.5 * 1e-3)
+
+
+@pytest.mark.parametrize("rows,vocab", [
+    (1380, 100000), (1060, 131072), (1100, 128256), (900, 151936), (530, 262136),   # a little more than the last-level cache holds
+    (16400, 65544), (8200, 131072), (8250, 131064)])                                # more than 2 GiB: several rows to a workgroup of either kernel
+@pytest.mark.parametrize("whole_lines", [False, True])
+def test_more_than_the_cache_and_more_than_2_gib(rows, vocab, whole_lines):
+    """Logits of sizes at which the choice of kernel and of streaming changes, as above: some rows, the last among them, against the oracle; what lies between
+    the rows stays as it was."""
+    from paper_2509_21275_amd.fused_ce import fused_ce_inplace
+    g = torch.Generator(device="cuda").manual_seed(rows + vocab)
+    stride = vocab + 8 if (vocab + 8) % 64 != 0 else vocab + 16
+    buf = torch.empty((rows, (vocab + 64) // 64 * 64 if whole_lines else stride), device="cuda", dtype=torch.bfloat16)
+    for r in range(0, rows, 1024):
+        buf[r:r + 1024].normal_(generator=g)
+    buf[1::5, vocab - vocab // 3:vocab] = float("-inf")
+    targets = torch.randint(0, 8, (rows,), generator=g, device="cuda", dtype=torch.int32)
+    targets[3::5] = vocab - 1
+    targets[torch.arange(7, rows, 97, device="cuda")] = -1
+    check = [r for r in (0, 1, 3, 7, 255, 256, 511, 512, rows // 2, rows - 2, rows - 1)]
+    want_loss, want_grad = orc.cross_entropy(buf[check, :vocab].cpu().double().numpy(), targets[check].cpu().numpy(), 0.5)
+    between, loss = buf[:, vocab:].clone(), torch.full((rows,), float("nan"), device="cuda")
+    fused_ce_inplace(buf[:, :vocab], targets, loss, 0.5)
+    torch.cuda.synchronize()
+    got = buf[check, :vocab].cpu().double().numpy()
+    assert bool(torch.isfinite(loss).all()) and torch.equal(buf[:, vocab:], between)
+    assert np.abs(loss[check].cpu().double().numpy() - want_loss).max() <= 2e-4 * max(1.0, np.abs(want_loss).max())
+    assert np.all(np.abs(got - want_grad) <= 2.0 ** -8 * np.abs(want_grad) + 2.0 ** -8 * 0.5 * 1e-3)
