@@ -727,18 +727,19 @@ bool tall_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int
 }
 
 // Pipelined from two blocks of `keys` per CU and 14 steps each on average on, unless most of the larger blocks' second halves are empty (sequences of up to 64 keys: 331 of
-// 51 tokens, 28/4 heads, unpipelined / pipelined 649 / 801 us; 278 of 70 934 / 784).  Below that chunks whose dQ walks are of 5 stages or more on average are decided by
+// 51 tokens, 28/4 heads, unpipelined / pipelined 649 / 801 us; 278 of 70 934 / 784).  Below that chunks whose dQ walks are of 8 stages or more on average are decided by
 // estimates in us: the pipelined blocks of both kinds dealt as in tall_pays; the unpipelined ones, whose walks may be cut
 // and so know no longest one, by their number and steps.  Least squares in the relative error over 1140 drawn chunks of 60 us and more (up to 65536 keys, 1 - 8 query heads to a
 // key/value head, two thirds of them of many short sequences), each run both ways; off by 7 and 10 % (root mean square), so that the pipelined ones have to be ahead by 5.  Of the 1140 it
-// picks 829, of which three are slower by more than 1.5 % than without these blocks (3.0 at most: 2112 causal tokens, 8/8, 106 us); all take 12.1 % less in the mean, with
-// the better of the two for each 13.3.  Unpipelined / pipelined: 2668 causal tokens, 8/8 heads, 184 / 148 us; 1428 queries on
+// picks 755, of which three are slower by more than 1.5 % than without these blocks (3.0 at most: 2112 causal tokens, 8/8, 106 us); all take 11.0 % less in the mean, with
+// the better of the two for each 13.1.  Of the walks of 5 to 8 stages it would pick 74, 3 to 18 % faster; those that take less than 60 us (ten sequences of 200 tokens, 4/4 heads), which were not
+// measured, look the same to it, and all of them keep the unpipelined blocks.  Unpipelined / pipelined: 2668 causal tokens, 8/8 heads, 184 / 148 us; 1428 queries on
 // 3445 keys, 32/8, 578 / 407; 10770 causal, 28/4, 7202 / 4677; 7307, 32/8, 3571 / 2456; what stays: 4335, 8/2, 386 / 655; 899, 64/8, 172 / 298.
 bool wide_pays(const chunk_attn_desc* d, int tile_rows, int inner, int keys, int cus) {
   const Walks w = count_dkv_walks(d, keys);
   if (w.items * d->num_kv_heads >= 2 * cus && w.stages >= 14 * w.items && 4 * count_tiles(d, true, kWideKeys) <= 3 * w.items) return true;
   const Walks wq = count_walks(d, tile_rows);
-  if (wq.stages < 5 * wq.items) return false;
+  if (wq.stages < 8 * wq.items) return false;
   constexpr int kUs = 20, kDqStage = 24, kDqStart = 18 * kUs, kStep = 26, kStart = 15 * kUs;
   const double pipelined = 4.7 + 1.035 / kUs * last_end(joint_starts(d, tile_rows, inner, kWideKeys, kDqStage, kDqStart, kStep, kStart), std::max(1, cus / 8));
   const double per_cu = 1.0 / cus, dq_all = std::max((double)wq.stages * inner * per_cu, (double)wq.longest);

@@ -51,6 +51,7 @@ def test_forward_of_256_whose_blocks_all_start_at_once(segs, hq, hk):
 
 @pytest.mark.parametrize("segs,hq,hk,keys", [
     (_packed(166, 57), 28, 4, 64), (_packed(331, 51), 28, 4, 64), (_packed(278, 70), 28, 4, 128),   # a block of 128 keys would be half empty, or not
+    (_packed(10, 200), 4, 4, 64), (_packed(11, 200), 4, 4, 64), (_packed(15, 352), 8, 8, 64), (_packed(15, 370), 8, 8, 128),   # dQ walks of 5.5, of 7.7 and of 8 stages
     ([(0, 371, 0, 2337)] + [(371 + 172 * i, 172, 2337 + 172 * i, 172) for i in range(19)], 8, 2, 64)])  # ahead by less than the estimates are off by
 def test_blocks_of_256_that_stay(segs, hq, hk, keys):
     assert ca.chunk_attn_test_dkv_keys(_desc(segs, hq, hk, 256)) == keys

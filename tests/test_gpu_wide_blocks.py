@@ -34,7 +34,7 @@ def _blocks(segs, hq, hk):
     ([(0, 223, 0, 223), (223, 414, 226, 414), (637, 123, 643, 925)], 16, 16, True, True),
     ([(0, 277, 0, 4165), (277, 23, 4165, 3768), (300, 243, 7933, 243)], 12, 4, True, True),
     ([(0, 34, 0, 1622), (34, 174, 1625, 1580)], 32, 8, True, True),
-    ([(0, 174, 0, 174), (174, 261, 177, 261)], 16, 16, False, False),
+    ([(0, 500, 0, 500), (500, 461, 503, 461)], 16, 16, False, False),
     ([(0, 279, 0, 890), (279, 258, 893, 258)], 32, 8, False, False),
     ([(0, 408, 0, 408), (408, 141, 411, 141), (549, 306, 552, 920)], 16, 8, False, True),
     ([(0, 175, 3, 175), (175, 218, 181, 1002)], 32, 8, False, True),
