@@ -210,7 +210,7 @@ int chunk_attn_measure_mfma_rate_on(int milliseconds, int workgroups, void* scra
 
 /*
  * Measurement hook (not part of the method): the clock the pipelined kernels (forward, and the dQ and dK/dV blocks of the backward, of head_dim 96
- * and 128; forward and dQ of 64 where they run pipelined) actually run at.  `device_buffer`: DEVICE memory, 8-byte aligned, at least CHUNK_ATTN_CLOCK_LOG_BYTES
+ * and 128; of 64 forward and dQ where they run pipelined, and dK/dV where it runs in one launch with dQ; of 256 dK/dV where it does) actually run at.  `device_buffer`: DEVICE memory, 8-byte aligned, at least CHUNK_ATTN_CLOCK_LOG_BYTES
  * (else CHUNK_ATTN_WORKSPACE_TOO_SMALL; CHUNK_ATTN_INVALID_ARG if misaligned), owned by the caller and kept alive until
  * the hook is switched off with a null pointer.  While it is set, every workgroup of those kernels writes four 64-bit
  * values when it starts and when it has run out of work: section k of the buffer (k = 0 forward, 1 dQ, 2 dK/dV; 4096
@@ -244,7 +244,7 @@ int chunk_attn_test_bwd_status_offset(const chunk_attn_desc* desc, size_t* offse
  * Test hook: which kernels chunk_attn_fwd and chunk_attn_bwd run for `desc` (given workspaces of the reported sizes, and gradients that overlap neither
  * o nor lse), as a sum of the bits below.  Decided on the host from the descriptor and the backward mode alone.
  */
-#define CHUNK_ATTN_ROUTE_FWD_PIPELINED 1 /* software-pipelined forward of head_dim 64, 96 and 128 (256 has one kernel only) */
+#define CHUNK_ATTN_ROUTE_FWD_PIPELINED 1 /* software-pipelined forward of head_dim 64, 96 and 128 (256 is pipelined, too, and has no bit: chunk_attn_test_fwd_rows) */
 #define CHUNK_ATTN_ROUTE_FWD_CUT 2       /* some of its walks over the keys are cut into pieces */
 #define CHUNK_ATTN_ROUTE_DQ_PIPELINED 4
 #define CHUNK_ATTN_ROUTE_DQ_CUT 8

@@ -1343,7 +1343,7 @@ __device__ __forceinline__ void store_key_rows(lds_bf16* stage, const f32x16 (&x
 // accumulators (256, all the accumulation registers there are) a wave has no room for a second one.  -D is what the sum of dP starts from, and one copy
 // of a stage is issued every NF / PER mini-steps (behind each other they hold the wave up).  What few registers are left decides: two of them reloaded
 // from scratch in every step, each time with a wait for all copies in flight, made a step 2800 -> 3330 cycles (a test looks for that).
-// Bound by the power limit: 8192 queries on 32768 keys, 32/8 heads, the matrix pipes are busy 73 % of the cycles of these blocks, at 1.78 GHz, where
+// Bound by the issue of MFMAs at the clock that the chip's power leaves: 8192 queries on 32768 keys, 32/8 heads, the matrix pipes are busy 73 % of the cycles of these blocks, at 1.78 GHz (MFMAs alone: 96 % at 1.79), where
 // dkv_pipe_blocks' were busy 59 % at 1.95 GHz (head_dim 96: 63 % at 1.88, 50 % at 2.09); cycles per 64 MFMAs of a wave 3470 -> 2800, time of these blocks 6.38 -> 5.63
 // ms (96: 5.26 -> 4.66), of the backward 10.75 -> 10.18 (8.76 -> 8.40); at 64, 8192 queries on 16384 keys, 3.00 -> 2.72.  What a step could still save is little: twice the row fragments' reads cost 2.7
 // % of its time, 96 more vector instructions 6 %, twice the copies 2.2 %.  Head_dim 64 has registers for P in float32, which dS then takes (32 instructions less).
@@ -2206,7 +2206,7 @@ __global__ __launch_bounds__(128, 1) void bwd_dkv_narrow_pipe_kernel(DkvParams p
 // products of dP and dV, and nothing but fragments lives from one step to the next: a stage leaves LDS with its step, and four slots of Q and dO
 // are enough for copies to have a step to land.  P stays in float32 for dS.
 // A step is bound by its LDS reads (96, and 8 of row values, 16 cycles each to issue; the CU reads 256 KB of LDS per step): its 64 MFMAs take 2048 of 2680 cycles,
-// at 1.74 GHz (the power limit).  Against two score waves that handed P and dS to two gradient waves, for 64 keys, in a launch behind that of dQ: packed
+// at 1.74 GHz.  Against two score waves that handed P and dS to two gradient waves, for 64 keys, in a launch behind that of dQ: packed
 // 64K chunk, 32/8 heads, forward and backward, 35.3 -> 32.0 ms; backward of 7307 causal tokens 3.6 -> 2.5.
 // ------------------------------------------------------------------------------------------------
 // The schedule of a step, as TallOrder.

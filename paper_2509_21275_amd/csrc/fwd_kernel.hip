@@ -1286,7 +1286,7 @@ __global__ __launch_bounds__(256, 1) void fwd_wide_kernel(FwdArgs) {
 // as 32 mini-steps of one LDS fragment and the two MFMAs it feeds, each MFMA with its even share of the vector work behind it.  Four ring slots of K and of V:
 // K(t), V(t - 1) and what is read ahead in use, K(t + 3) and V(t + 2) on their way.  Reference maxima, both sums and blocks that are taken again
 // as in fwd_wide_kernel.
-// Bound by the rate at which MFMAs issue (their share of the cycles times the clock that the power limit leaves).  fwd_wide_kernel -> this, us, 32/8 heads:
+// Bound by the rate at which MFMAs issue (their share of the cycles times the clock that the chip's power leaves).  fwd_wide_kernel -> this, us, 32/8 heads:
 // packed 64K tokens 8254 -> 6471, 8192 queries on 32768 keys 7329 -> 5658, 4096 causal tokens 302 -> 242, 64 sequences of 256 253 -> 235.
 // ------------------------------------------------------------------------------------------------
 // The schedule of a step: mini-step m issues the read of fragment m + AHEAD (two instructions for those of V^T, the second half).

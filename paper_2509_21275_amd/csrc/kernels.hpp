@@ -154,7 +154,7 @@ constexpr int kNumXcd = 8;  // XCDs of an MI355X: workgroup b runs on XCD b % 8
 int dkv_block_keys(const BwdPlan& plan, int head_dim);
 // 0: the library's choice, 1: the two-kernel backward, 2: the one-pass backward (head_dim 128 only)
 int bwd_mode();
-// Device memory the caller has set aside for the clock logs of the three pipelined kernels (null: none), and the section
+// Device memory the caller has set aside for the clock logs of the pipelined kernels (null: none), and the section
 // of kernel `which` in it (0 forward, 1 dQ, 2 dK/dV), kClockLogEntries values of 8 bytes each.
 constexpr size_t kClockLogEntries = 4 * 1024;
 unsigned long long* clock_log(int which);
